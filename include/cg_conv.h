@@ -49,7 +49,10 @@ enum { CG_EPI_RELU = 1u, CG_EPI_AFFINE = 2u, CG_EPI_RESIDUAL = 4u };
  * channel groups are whole 32-byte runs) when the shape allows, else the large-tile matrix-core
  * kernel (3x3 and 1x1 layers, fully connected layers as 1x1 layers on a 1x1 image, channel groups of
  * whole 16-byte runs), else the plain one-thread-per-activation kernel.  All of them compute the
- * same layer. */
+ * same layer.  A handle made with AUTO runs a batch of few output pixels, and every layer outside the two
+ * tiled families whose pixels are whole 16-byte runs of channels, on a small-tile matrix-core kernel (any
+ * float or int8 type); cg_conv_info still names the family that covers the shape.  A family asked for by
+ * name is what runs. */
 enum {
   CG_VARIANT_AUTO = 0,
   CG_VARIANT_NAIVE = 1,
@@ -140,7 +143,8 @@ size_t cg_conv_packed_bytes(const cg_conv_desc* desc);
  * must be ordered after that stream's work.  On failure *out is NULL. */
 int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream);
 
-/* Device scratch a forward call of batch n needs (may be 0). */
+/* Device scratch a forward call of batch n needs (may be 0; not monotonic in n: a small batch may share its
+ * tiles' sums through it). */
 size_t cg_conv_workspace_bytes(const cg_conv* h, int32_t n);
 
 /*

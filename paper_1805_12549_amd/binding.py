@@ -43,6 +43,9 @@ if len(_hip_runtimes_mapped()) > 1:
     raise ImportError("two HIP runtimes are mapped into this process (%s); import torch before anything "
                       "that loads libamdhip64" % ", ".join(_hip_runtimes_mapped()))
 
+# the current stream's address without building a Stream object per call
+_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+
 CG_OK, CG_EINVAL, CG_EUNSUPPORTED, CG_ENOMEM, CG_EHIP = 0, 1, 2, 3, 4
 CG_F32, CG_BF16, CG_I8, CG_I32 = 0, 1, 2, 3
 CG_EPI_RELU, CG_EPI_AFFINE, CG_EPI_RESIDUAL = 1, 2, 4
@@ -137,9 +140,7 @@ def cg_conv_workspace_bytes(handle: int, n: int) -> int:
 def cg_conv_forward(handle: int, n: int, x: int, residual: int, y: int, bitmap: int, counts: int,
                     workspace: int, workspace_bytes: int, hip_stream: int = 0) -> None:
     """All tensor arguments are raw device addresses (0 = NULL)."""
-    rc = _lib.cg_conv_forward(C.c_void_p(handle), n, C.c_void_p(x), C.c_void_p(residual), C.c_void_p(y),
-                              C.c_void_p(bitmap), C.c_void_p(counts), C.c_void_p(workspace), workspace_bytes,
-                              C.c_void_p(hip_stream))
+    rc = _lib.cg_conv_forward(handle, n, x, residual, y, bitmap, counts, workspace, workspace_bytes, hip_stream)
     if rc != CG_OK:
         raise CGError(rc, cg_last_error())
 
@@ -283,37 +284,42 @@ class GatedConv:
         self.variant, self.ho, self.wo = cg_conv_info(self.handle)
         self.n_max, self.c_out, self.out_dtype = n_max, c_out, out_dtype
         self.words = (c_out + 31) // 32
+        self._y_dtype = getattr(torch, _TORCH_OUT[out_dtype])
         self._ws = None
+        self._ws_need = {}      # workspace bytes per batch size
 
     def _stream_ptr(self):
-        s = self.stream if self.stream is not None else self._torch.cuda.current_stream()
-        return s.cuda_stream
+        if self.stream is not None:
+            return self.stream.cuda_stream
+        return _raw_stream(_current_device())
 
     def forward(self, x, residual=None, y=None, bitmap=True, counts=True):
         """x: torch device tensor [n,H,W,C_in] (contiguous NHWC).  Returns (y, bitmap, counts)."""
-        torch = self._torch
+        empty = self._torch.empty
         n = x.shape[0]
-        dev = x.device
         if y is None:
-            y = torch.empty((n, self.ho, self.wo, self.c_out), dtype=getattr(torch, _TORCH_OUT[self.out_dtype]),
-                            device=dev)
+            y = empty((n, self.ho, self.wo, self.c_out), dtype=self._y_dtype, device=x.device)
         if bitmap is True:
-            bitmap = torch.empty((n * self.ho * self.wo, self.words), dtype=torch.int32, device=dev)
+            bitmap = empty((n * self.ho * self.wo, self.words), dtype=self._torch.int32, device=x.device)
         elif bitmap is False:
             bitmap = None
         if counts is True:
-            counts = torch.empty(2 + n * self.c_out, dtype=torch.int32, device=dev)
+            counts = empty(2 + n * self.c_out, dtype=self._torch.int32, device=x.device)
         elif counts is False:
             counts = None
-        need = cg_conv_workspace_bytes(self.handle, n)
+        need = self._ws_need.get(n)
+        if need is None:
+            need = self._ws_need[n] = cg_conv_workspace_bytes(self.handle, n)
         ws_ptr = 0
         if need:
             if self._ws is None or self._ws.numel() < need + 256:
-                self._ws = torch.empty(need + 256, dtype=torch.uint8, device=dev)
+                self._ws = empty(need + 256, dtype=self._torch.uint8, device=x.device)
             ws_ptr = (self._ws.data_ptr() + 255) & ~255
-        cg_conv_forward(self.handle, n, x.data_ptr(), residual.data_ptr() if residual is not None else 0,
-                        y.data_ptr(), bitmap.data_ptr() if bitmap is not None else 0,
-                        counts.data_ptr() if counts is not None else 0, ws_ptr, need, self._stream_ptr())
+        rc = _lib.cg_conv_forward(self.handle, n, x.data_ptr(), 0 if residual is None else residual.data_ptr(), y.data_ptr(),
+                                  0 if bitmap is None else bitmap.data_ptr(), 0 if counts is None else counts.data_ptr(),
+                                  ws_ptr, need, self._stream_ptr())
+        if rc != CG_OK:
+            raise CGError(rc, cg_last_error())
         return y, bitmap, counts
 
     def close(self):

@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <limits>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -61,8 +62,24 @@ struct Layout {
   size_t table_stride;   // bytes per table
   size_t w_base_off, w_base_bytes;
   size_t w_cond_off, w_cond_bytes;
-  size_t wpk_base_off, wpk_cond_off;
+  size_t wpk_base_off, wpk_cond_off;       // prepacked weights of the tiled kernel, if one covers the layer
+  size_t wpd_base_off, wpd_cond_off;       // prepacked weights of the small-tile kernel, if it may be picked
   size_t total;
+};
+
+}  // namespace
+
+namespace {
+
+enum Kernel { kNaive, kRows, kTile, kDirect };
+
+// What one batch size runs on.
+struct CallPlan {
+  int n;
+  Kernel kernel;
+  cg::Mfma3Plan rows;
+  cg::TilePlan tile;
+  cg::DirectPlan direct;
 };
 
 }  // namespace
@@ -70,11 +87,16 @@ struct Layout {
 struct cg_conv {
   cg_conv_desc d;           // copy of the descriptor (host pointers are dead after create)
   int ho, wo, c_cond;
-  int variant;              // resolved CG_VARIANT_*
-  cg::Mfma3Plan plan3;
-  cg::TilePlan plan4;
+  int variant;              // resolved CG_VARIANT_*: the kernel family that covers the shape
+  bool direct_ok;           // the small-tile kernel's weights are packed too
+  CallPlan first;           // plan for n_max
   Layout lay;
+  cg::Params base;          // what is the same in every call
   std::vector<uint32_t> staging;  // host image of the tables; kept alive for the async copy
+  // plans of other batch sizes, made on first use and kept (at most kKept of them)
+  static constexpr size_t kKept = 8;
+  mutable std::mutex lock;
+  mutable std::vector<CallPlan> kept;
 };
 
 namespace {
@@ -149,7 +171,8 @@ int validate(const cg_conv_desc* d, int* ho, int* wo) {
   return CG_OK;
 }
 
-Layout make_layout(const cg_conv_desc& d, size_t wpk_base_bytes, size_t wpk_cond_bytes) {
+Layout make_layout(const cg_conv_desc& d, size_t wpk_base_bytes, size_t wpk_cond_bytes, size_t wpd_base_bytes,
+                   size_t wpd_cond_bytes) {
   Layout l{};
   const size_t eb = (size_t)elem_bytes(d.in_dtype);
   const size_t taps = (size_t)d.kh * d.kw;
@@ -165,6 +188,10 @@ Layout make_layout(const cg_conv_desc& d, size_t wpk_base_bytes, size_t wpk_cond
   off += align256(wpk_base_bytes);
   l.wpk_cond_off = off;
   off += align256(wpk_cond_bytes);
+  l.wpd_base_off = off;
+  off += align256(wpd_base_bytes);
+  l.wpd_cond_off = off;
+  off += align256(wpd_cond_bytes);
   l.total = off;
   return l;
 }
@@ -172,8 +199,10 @@ Layout make_layout(const cg_conv_desc& d, size_t wpk_base_bytes, size_t wpk_cond
 struct Plans {
   cg::Mfma3Plan v3;
   cg::TilePlan v4;
+  cg::DirectPlan vd;
   int variant;
-  size_t wpk_base_bytes, wpk_cond_bytes;
+  bool direct_ok;
+  size_t wpk_base_bytes, wpk_cond_bytes, wpd_base_bytes, wpd_cond_bytes;
 };
 
 // compute units of the current device (256 where no device answers: the plan is then the MI355X one)
@@ -200,9 +229,104 @@ int resolve_variant(const cg_conv_desc& d, Plans* pl) {
   int v = d.variant;
   if (v == CG_VARIANT_AUTO) v = pl->v3.ok ? CG_VARIANT_MFMA_ROWS : pl->v4.ok ? CG_VARIANT_TILE : CG_VARIANT_NAIVE;
   pl->variant = v;
+  pl->vd = cg::direct_plan(d, d.n_max, cu_count());
+  pl->direct_ok = d.variant == CG_VARIANT_AUTO && pl->vd.ok;      // (a family that was asked for by name is what runs)
+  pl->wpd_base_bytes = pl->direct_ok ? pl->vd.wpk_bytes[0] : 0;
+  pl->wpd_cond_bytes = pl->direct_ok ? pl->vd.wpk_bytes[1] : 0;
   pl->wpk_base_bytes = v == CG_VARIANT_TILE ? pl->v4.wpk_base_bytes : v == CG_VARIANT_MFMA_ROWS ? pl->v3.wpk_base_bytes : 0;
   pl->wpk_cond_bytes = v == CG_VARIANT_TILE ? pl->v4.wpk_cond_bytes : v == CG_VARIANT_MFMA_ROWS ? pl->v3.wpk_cond_bytes : 0;
   return CG_OK;
+}
+
+// The kernel a batch runs on.  (Layers that neither tiled family covers: the small-tile kernel.)
+void pick_kernel(const cg_conv* h, CallPlan* c) {
+  c->kernel = h->variant == CG_VARIANT_MFMA_ROWS ? kRows : h->variant == CG_VARIANT_TILE ? kTile : kNaive;
+  if (!h->direct_ok || !c->direct.ok) return;
+  // One round of tiles over the compute units (two where the tiled kernels start late: int8, 1x1) is where
+  // the small-tile kernel's time starts to grow; measured over one to 64 images of the ResNet-18 layers,
+  // e.g. 512 channels at 7x7 bf16: 10 against 22 us at one image, 17.5 / 24 at 16, 32 / 25 at 32.
+  const int rounds = h->d.in_dtype == CG_BF16 && h->d.kh == 3 ? 1 : 2;
+  if (c->kernel == kNaive || c->direct.tiles <= rounds * cu_count()) c->kernel = kDirect;
+}
+
+// The launch shape follows the batch of the call: a smaller batch than n_max is planned afresh and the
+// new plan is used if it reads the prepacked weights the same way.
+CallPlan plan_call(const cg_conv* h, int n) {
+  CallPlan c = h->first;
+  c.n = n;
+  cg_conv_desc dn = h->d;
+  dn.n_max = n;
+  if (h->variant == CG_VARIANT_MFMA_ROWS) {
+    const cg::Mfma3Plan q = cg::mfma3_plan(dn, cu_count());
+    if (q.ok && q.cps == c.rows.cps && q.grp_mode == c.rows.grp_mode && q.gsp == c.rows.gsp &&
+        q.stages[0] == c.rows.stages[0] && q.stages[1] == c.rows.stages[1])
+      c.rows = q;
+  } else if (h->variant == CG_VARIANT_TILE) {
+    const cg::TilePlan q = cg::tile_plan(dn, cu_count());
+    if (q.ok && q.taps == c.tile.taps && q.cps == c.tile.cps && q.wn == c.tile.wn && q.grp_mode == c.tile.grp_mode &&
+        q.gsp == c.tile.gsp && q.stages[0] == c.tile.stages[0] && q.stages[1] == c.tile.stages[1])
+      c.tile = q;
+  }
+  if (h->direct_ok) c.direct = cg::direct_plan(dn, n, cu_count());
+  pick_kernel(h, &c);
+  return c;
+}
+
+CallPlan call_plan(const cg_conv* h, int n) {
+  if (n == h->first.n) return h->first;
+  std::lock_guard<std::mutex> g(h->lock);
+  for (const CallPlan& c : h->kept)
+    if (c.n == n) return c;
+  const CallPlan c = plan_call(h, n);
+  if (h->kept.size() >= cg_conv::kKept) h->kept.erase(h->kept.begin());
+  h->kept.push_back(c);
+  return c;
+}
+
+cg::Params base_params(const cg_conv* h) {
+  const cg_conv_desc& d = h->d;
+  const char* pk = (const char*)d.packed;
+  const Layout& l = h->lay;
+  cg::Params p{};
+  p.h = d.h;
+  p.w = d.w;
+  p.c_in = d.c_in;
+  p.c_out = d.c_out;
+  p.c_base = d.c_base;
+  p.c_cond = h->c_cond;
+  p.kh = d.kh;
+  p.kw = d.kw;
+  p.stride = d.stride;
+  p.pad = d.pad;
+  p.ho = h->ho;
+  p.wo = h->wo;
+  p.x_pixel_stride = d.x_pixel_stride;
+  p.epilogue = d.epilogue;
+  p.in_dtype = d.in_dtype;
+  p.out_dtype = d.out_dtype;
+  p.gated = h->c_cond > 0;
+  p.rq_shift = d.rq_shift;
+  p.rq_res_mult = d.rq_res_mult;
+  p.words = (d.c_out + 31) / 32;
+  p.groups = d.groups > 1 ? d.groups : 1;
+  p.cpg = d.c_out / p.groups;
+  p.shuffle = d.shuffle;
+  const size_t ts = l.table_stride;
+  p.thr_f = (const float*)(pk + 0 * ts);
+  p.thr_hi_f = (const float*)(pk + 1 * ts);
+  p.thr_i = (const int32_t*)(pk + 0 * ts);
+  p.sc0 = (const float*)(pk + 2 * ts);
+  p.sh0 = (const float*)(pk + 3 * ts);
+  p.sc1 = (const float*)(pk + 4 * ts);
+  p.sh1 = (const float*)(pk + 5 * ts);
+  p.mult0 = (const int32_t*)(pk + 2 * ts);
+  p.mult1 = (const int32_t*)(pk + 3 * ts);
+  p.bias = (const int32_t*)(pk + 4 * ts);
+  p.w_base = pk + l.w_base_off;
+  p.w_cond = pk + l.w_cond_off;
+  p.table_stride = ts;
+  p.zeros = pk + 7 * ts;       // the last table is never written: zeros
+  return p;
 }
 
 inline uint32_t f2u(float f) {
@@ -255,7 +379,7 @@ size_t cg_conv_packed_bytes(const cg_conv_desc* desc) {
   if (validate(desc, &ho, &wo) != CG_OK) return 0;
   Plans pl;
   if (resolve_variant(*desc, &pl) != CG_OK) return 0;
-  return make_layout(*desc, pl.wpk_base_bytes, pl.wpk_cond_bytes).total;
+  return make_layout(*desc, pl.wpk_base_bytes, pl.wpk_cond_bytes, pl.wpd_base_bytes, pl.wpd_cond_bytes).total;
 }
 
 int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
@@ -269,8 +393,7 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   rc = resolve_variant(d, &pl);
   if (rc != CG_OK) return rc;
   const int variant = pl.variant;
-  const cg::Mfma3Plan& plan3 = pl.v3;
-  const Layout lay = make_layout(d, pl.wpk_base_bytes, pl.wpk_cond_bytes);
+  const Layout lay = make_layout(d, pl.wpk_base_bytes, pl.wpk_cond_bytes, pl.wpd_base_bytes, pl.wpd_cond_bytes);
   if (!d.packed) return fail(CG_EINVAL, "packed is NULL");
   if (((uintptr_t)d.packed & 255) != 0) return fail(CG_EINVAL, "packed must be 256-byte aligned");
   if (d.packed_bytes < lay.total)
@@ -284,9 +407,14 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   h->wo = wo;
   h->c_cond = d.c_in - d.c_base;
   h->variant = variant;
-  h->plan3 = plan3;
-  h->plan4 = pl.v4;
+  h->direct_ok = pl.direct_ok;
   h->lay = lay;
+  h->first.n = d.n_max;
+  h->first.rows = pl.v3;
+  h->first.tile = pl.v4;
+  h->first.direct = pl.vd;
+  pick_kernel(h, &h->first);
+  h->base = base_params(h);
 
   // Host image of the per-channel tables.
   //   float path: 0 thr, 1 thr_hi, 2 sc0, 3 sh0, 4 sc1, 5 sh1
@@ -340,24 +468,12 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
     e = hipMemcpyAsync(pk + lay.w_base_off, d.w_base, lay.w_base_bytes, hipMemcpyDeviceToDevice, s);
   if (e == hipSuccess && lay.w_cond_bytes)
     e = hipMemcpyAsync(pk + lay.w_cond_off, d.w_cond, lay.w_cond_bytes, hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess && variant != CG_VARIANT_NAIVE) {
-    cg::Params p{};
-    p.c_in = d.c_in;
-    p.c_out = d.c_out;
-    p.c_base = d.c_base;
-    p.c_cond = h->c_cond;
-    p.kh = d.kh;
-    p.kw = d.kw;
-    p.in_dtype = d.in_dtype;
-    p.groups = d.groups > 1 ? d.groups : 1;
-    p.cpg = d.c_out / p.groups;
-    p.w_base = pk + lay.w_base_off;
-    p.w_cond = pk + lay.w_cond_off;
-    if (variant == CG_VARIANT_TILE)
-      e = cg::launch_tile_pack(pl.v4, p, pk + lay.wpk_base_off, pk + lay.wpk_cond_off, s);
-    else
-      e = cg::launch_mfma3_pack(plan3, p, pk + lay.wpk_base_off, pk + lay.wpk_cond_off, s);
-  }
+  if (e == hipSuccess && variant == CG_VARIANT_TILE)
+    e = cg::launch_tile_pack(pl.v4, h->base, pk + lay.wpk_base_off, pk + lay.wpk_cond_off, s);
+  if (e == hipSuccess && variant == CG_VARIANT_MFMA_ROWS)
+    e = cg::launch_mfma3_pack(pl.v3, h->base, pk + lay.wpk_base_off, pk + lay.wpk_cond_off, s);
+  if (e == hipSuccess && pl.direct_ok)
+    e = cg::launch_direct_pack(pl.vd, h->base, pk + lay.wpd_base_off, pk + lay.wpd_cond_off, s);
   if (e != hipSuccess) {
     const int code = fail(CG_EHIP, "cg_conv_create: %s", hipGetErrorString(e));
     delete h;
@@ -377,34 +493,30 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
 }
 
 namespace {
-// Workspace layout: [decision bitmap of the batch][per-(image, channel) counts of the first pass]
-// [channel mask].  The row-tiled kernel counts fired gates from a decision bitmap; it goes to the
-// workspace when the caller asks for counts without a bitmap, and so does the first pass of the
-// channel-wise gate.  The other two areas exist only with the channel-wise gate.
+// Workspace layout: [decision bitmap of the batch][channel mask][partial sums].  Fired gates are counted from a
+// decision bitmap; it goes to the workspace when the caller asks for counts without a bitmap, and so
+// does the first pass of the channel-wise gate.  The mask exists only with the channel-wise gate, the
+// partial sums only where several workgroups share a tile's K.
 struct WsLayout {
-  size_t bitmap_off, bitmap_bytes, counts_off, counts_bytes, mask_off, mask_bytes, total;
+  size_t bitmap_off, bitmap_bytes, mask_off, mask_bytes, partial_off, total;
 };
-WsLayout ws_layout(const cg_conv* h, int32_t n) {
+WsLayout ws_layout(const cg_conv* h, int32_t n, const CallPlan& c) {
   WsLayout w{};
   const size_t words = (size_t)(h->d.c_out + 31) / 32;
   const bool chan_gate = h->c_cond > 0 && h->d.tau_c > 0.0f;
-  if ((h->variant == CG_VARIANT_MFMA_ROWS || h->variant == CG_VARIANT_TILE) && h->c_cond > 0)
-    w.bitmap_bytes = align256((size_t)n * h->ho * h->wo * words * 4);
-  if (chan_gate) {
-    w.counts_bytes = align256((2 + (size_t)n * h->d.c_out) * 4);
-    w.mask_bytes = align256((size_t)n * words * 4);
-  }
+  if (h->c_cond > 0) w.bitmap_bytes = align256((size_t)n * h->ho * h->wo * words * 4);
+  if (chan_gate) w.mask_bytes = align256((size_t)n * words * 4);
   w.bitmap_off = 0;
-  w.counts_off = w.bitmap_bytes;
-  w.mask_off = w.counts_off + w.counts_bytes;
-  w.total = w.mask_off + w.mask_bytes;
+  w.mask_off = w.bitmap_bytes;
+  w.partial_off = w.mask_off + w.mask_bytes;
+  w.total = w.partial_off + (c.kernel == kDirect ? align256(c.direct.partial_bytes) : 0);
   return w;
 }
 }  // namespace
 
 size_t cg_conv_workspace_bytes(const cg_conv* h, int32_t n) {
   if (!h || n <= 0) return 0;
-  return ws_layout(h, n).total;
+  return ws_layout(h, n, call_plan(h, n)).total;
 }
 
 int cg_conv_info(const cg_conv* h, int32_t* ho, int32_t* wo) {
@@ -418,8 +530,10 @@ int cg_conv_info(const cg_conv* h, int32_t* ho, int32_t* wo) {
 
 namespace {
 
+// counts: [n][c_out] fired counts; total: their sum, cleared first if clear_total (both NULL or neither)
 int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap,
-                 uint32_t* counts, void* workspace, size_t workspace_bytes, void* hip_stream);
+                 uint32_t* counts, uint32_t* total, bool clear_total, void* workspace, size_t workspace_bytes,
+                 void* hip_stream);
 
 }  // namespace
 
@@ -427,7 +541,8 @@ extern "C" {
 
 int cg_conv_forward(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap,
                     uint32_t* counts, void* workspace, size_t workspace_bytes, void* hip_stream) {
-  return forward_impl(h, n, x, residual, y, bitmap, counts, workspace, workspace_bytes, hip_stream);
+  return forward_impl(h, n, x, residual, y, bitmap, counts ? counts + 2 : nullptr, counts, true, workspace, workspace_bytes,
+                      hip_stream);
 }
 
 int cg_conv_forward_noalloc(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap,
@@ -435,6 +550,25 @@ int cg_conv_forward_noalloc(cg_conv* h, int32_t n, const void* x, const void* re
   if (!h) return fail(CG_EINVAL, "handle is NULL");
   if (n < 0 || n > h->d.n_max) return fail(CG_EINVAL, "n = %d is outside [0, n_max = %d]", n, h->d.n_max);
   const size_t need = n > 0 ? cg_conv_workspace_bytes(h, n) : 0;
+  if (need > kScratchBytes && h->variant == CG_VARIANT_NAIVE && cg_conv_workspace_bytes(h, 1) <= kScratchBytes && x && y) {
+    // layers of this family take any batch: as many images at a time as the scratch array serves
+    const cg_conv_desc& d = h->d;
+    const int step = (int)(kScratchBytes / cg_conv_workspace_bytes(h, 1));
+    void* ws = scratch_of_current_device();
+    if (!ws) return CG_EHIP;
+    const size_t xi = (size_t)d.h * d.w * d.x_pixel_stride * elem_bytes(d.in_dtype), px = (size_t)h->ho * h->wo;
+    const size_t yi = px * d.c_out * elem_bytes(d.out_dtype);
+    const size_t ri = px * d.c_out * elem_bytes(d.in_dtype == CG_I8 ? CG_I8 : d.out_dtype);
+    for (int i = 0; i < n; i += step) {
+      const int m = n - i < step ? n - i : step;
+      const int rc = forward_impl(h, m, (const char*)x + i * xi, residual ? (const char*)residual + i * ri : nullptr,
+                                  (char*)y + i * yi, bitmap ? bitmap + i * px * ((d.c_out + 31) / 32) : nullptr,
+                                  counts ? counts + 2 + (size_t)i * d.c_out : nullptr, counts, i == 0, ws, kScratchBytes,
+                                  hip_stream);
+      if (rc != CG_OK) return rc;
+    }
+    return CG_OK;
+  }
   if (need > kScratchBytes)
     return fail(CG_EUNSUPPORTED, "this call needs %zu bytes of scratch; the library's fixed scratch array holds %zu",
                 need, kScratchBytes);
@@ -443,7 +577,7 @@ int cg_conv_forward_noalloc(cg_conv* h, int32_t n, const void* x, const void* re
     ws = scratch_of_current_device();
     if (!ws) return CG_EHIP;
   }
-  return forward_impl(h, n, x, residual, y, bitmap, counts, ws, need, hip_stream);
+  return forward_impl(h, n, x, residual, y, bitmap, counts ? counts + 2 : nullptr, counts, true, ws, need, hip_stream);
 }
 
 void cg_conv_destroy(cg_conv* h) { delete h; }
@@ -453,18 +587,21 @@ void cg_conv_destroy(cg_conv* h) { delete h; }
 namespace {
 
 int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap,
-                 uint32_t* counts, void* workspace, size_t workspace_bytes, void* hip_stream) {
+                 uint32_t* counts, uint32_t* total, bool clear_total, void* workspace, size_t workspace_bytes,
+                 void* hip_stream) {
   if (!h) return fail(CG_EINVAL, "handle is NULL");
   if (n < 0 || n > h->d.n_max) return fail(CG_EINVAL, "n = %d is outside [0, n_max = %d]", n, h->d.n_max);
   if (n == 0) return CG_OK;
   if (!x || !y) return fail(CG_EINVAL, "x and y must not be NULL");
   if ((h->d.epilogue & CG_EPI_RESIDUAL) && !residual)
     return fail(CG_EINVAL, "residual is NULL but the layer was created with CG_EPI_RESIDUAL");
-  if (counts && ((uintptr_t)counts & 7)) return fail(CG_EINVAL, "counts must be 8-byte aligned");
-  if (h->variant != CG_VARIANT_NAIVE &&
-      ((((uintptr_t)x) | ((uintptr_t)y) | ((uintptr_t)residual) | ((uintptr_t)bitmap)) & 15))
+  if (total && ((uintptr_t)total & 7)) return fail(CG_EINVAL, "counts must be 8-byte aligned");
+  const bool aligned = ((((uintptr_t)x) | ((uintptr_t)y) | ((uintptr_t)residual) | ((uintptr_t)bitmap)) & 15) == 0;
+  if (h->variant != CG_VARIANT_NAIVE && !aligned)
     return fail(CG_EINVAL, "x, y, residual and bitmap must be 16-byte aligned");
-  const size_t need = cg_conv_workspace_bytes(h, n);
+  CallPlan cp = call_plan(h, n);
+  const WsLayout wl = ws_layout(h, n, cp);
+  const size_t need = wl.total;
   if (need > 0 && (!workspace || workspace_bytes < need))
     return fail(CG_EINVAL, "workspace of %zu bytes is smaller than the %zu required", workspace_bytes, need);
   if (need > 0 && ((uintptr_t)workspace & 255)) return fail(CG_EINVAL, "workspace must be 256-byte aligned");
@@ -472,118 +609,59 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
   const cg_conv_desc& d = h->d;
   const char* pk = (const char*)d.packed;
   const Layout& l = h->lay;
-  cg::Params p{};
+  cg::Params p = h->base;
   p.n = n;
-  p.h = d.h;
-  p.w = d.w;
-  p.c_in = d.c_in;
-  p.c_out = d.c_out;
-  p.c_base = d.c_base;
-  p.c_cond = h->c_cond;
-  p.kh = d.kh;
-  p.kw = d.kw;
-  p.stride = d.stride;
-  p.pad = d.pad;
-  p.ho = h->ho;
-  p.wo = h->wo;
-  p.x_pixel_stride = d.x_pixel_stride;
   p.m_total = (long long)n * h->ho * h->wo;
-  p.epilogue = d.epilogue;
-  p.in_dtype = d.in_dtype;
-  p.out_dtype = d.out_dtype;
-  p.gated = h->c_cond > 0;
-  p.rq_shift = d.rq_shift;
-  p.rq_res_mult = d.rq_res_mult;
-  p.words = (d.c_out + 31) / 32;
-  p.groups = d.groups > 1 ? d.groups : 1;
-  p.cpg = d.c_out / p.groups;
-  p.shuffle = d.shuffle;
-  const size_t ts = l.table_stride;
-  p.thr_f = (const float*)(pk + 0 * ts);
-  p.thr_hi_f = (const float*)(pk + 1 * ts);
-  p.thr_i = (const int32_t*)(pk + 0 * ts);
-  p.sc0 = (const float*)(pk + 2 * ts);
-  p.sh0 = (const float*)(pk + 3 * ts);
-  p.sc1 = (const float*)(pk + 4 * ts);
-  p.sh1 = (const float*)(pk + 5 * ts);
-  p.mult0 = (const int32_t*)(pk + 2 * ts);
-  p.mult1 = (const int32_t*)(pk + 3 * ts);
-  p.bias = (const int32_t*)(pk + 4 * ts);
-  p.w_base = pk + l.w_base_off;
-  p.w_cond = pk + l.w_cond_off;
-  p.table_stride = ts;
-  p.zeros = pk + 7 * ts;       // the last table is never written: zeros
   p.x = x;
   p.residual = residual;
   p.y = y;
   p.bitmap = bitmap;
   p.counts = counts;
+  p.total = total;
+  p.clear_total = counts && clear_total;
 
-  // The launch shape follows the batch of this call: a smaller batch than n_max is planned afresh
-  // and the new plan is used if it reads the prepacked weights the same way.
-  cg::Mfma3Plan plan3 = h->plan3;
-  cg::TilePlan plan4 = h->plan4;
-  if (n != d.n_max && h->variant != CG_VARIANT_NAIVE) {
-    cg_conv_desc dn = d;
-    dn.n_max = n;
-    if (h->variant == CG_VARIANT_MFMA_ROWS) {
-      const cg::Mfma3Plan q = cg::mfma3_plan(dn, cu_count());
-      if (q.ok && q.cps == plan3.cps && q.grp_mode == plan3.grp_mode && q.gsp == plan3.gsp &&
-          q.stages[0] == plan3.stages[0] && q.stages[1] == plan3.stages[1])
-        plan3 = q;
-    } else {
-      const cg::TilePlan q = cg::tile_plan(dn, cu_count());
-      if (q.ok && q.taps == plan4.taps && q.cps == plan4.cps && q.wn == plan4.wn && q.grp_mode == plan4.grp_mode &&
-          q.gsp == plan4.gsp && q.stages[0] == plan4.stages[0] && q.stages[1] == plan4.stages[1])
-        plan4 = q;
-    }
-  }
-
+  if (cp.kernel == kDirect && !aligned) cp.kernel = kNaive;      // (only where the plain kernel is the layer's family)
   hipStream_t s = (hipStream_t)hip_stream;
-  hipError_t e = hipSuccess;
-  const WsLayout wl = ws_layout(h, n);
   char* ws = (char*)workspace;
+  auto launch = [&](const cg::Params& q) -> hipError_t {
+    switch (cp.kernel) {
+      case kRows: return cg::launch_mfma3(cp.rows, q, pk + l.wpk_base_off, pk + l.wpk_cond_off, s);
+      case kTile: return cg::launch_tile(cp.tile, q, pk + l.wpk_base_off, pk + l.wpk_cond_off, s);
+      case kDirect: return cg::launch_direct(cp.direct, q, pk + l.wpd_base_off, pk + l.wpd_cond_off, ws + wl.partial_off, s);
+      default: return cg::launch_naive(q, s);
+    }
+  };
+  hipError_t e = hipSuccess;
   if (p.gated && d.tau_c > 0.0f) {
-    // Channel-wise gate (Sec. 3.2): a first pass over the base path and the gate gives the fired
-    // count of every (image, channel); the channels at or above tau_c * Ho * Wo form the mask that
-    // the full pass ANDs into its decisions.
+    // Channel-wise gate (Sec. 3.2): a first pass over the base path and the gate gives the decisions,
+    // counted per (image, channel); the channels at or above tau_c * Ho * Wo form the mask that the
+    // full pass ANDs into its decisions.
     const double need_d = std::ceil((double)d.tau_c * (double)((long long)h->ho * h->wo));
     const uint32_t need_u = need_d >= 4294967295.0 ? 0xffffffffu : (uint32_t)need_d;
-    uint32_t* pre_counts = (uint32_t*)(ws + wl.counts_off);
     uint32_t* mask = (uint32_t*)(ws + wl.mask_off);
     cg::Params q = p;
     q.gate_only = 1;
     q.y = nullptr;
-    q.counts = nullptr;
-    q.bitmap = nullptr;
-    if (h->variant == CG_VARIANT_MFMA_ROWS || h->variant == CG_VARIANT_TILE) {
-      q.bitmap = (uint32_t*)(ws + wl.bitmap_off);
-      e = h->variant == CG_VARIANT_TILE ? cg::launch_tile(plan4, q, pk + l.wpk_base_off, pk + l.wpk_cond_off, s)
-                                        : cg::launch_mfma3(plan3, q, pk + l.wpk_base_off, pk + l.wpk_cond_off, s);
-      if (e == hipSuccess) e = cg::launch_bitmap_chan_mask(q, q.bitmap, need_u, mask, s);
-    } else {
-      e = cg::launch_zero_u32(pre_counts, 2 + (size_t)n * d.c_out, s);
-      q.counts = pre_counts;
-      if (e == hipSuccess) e = cg::launch_naive(q, s);
-      if (e == hipSuccess) e = cg::launch_chan_mask(pre_counts, n, d.c_out, p.words, need_u, mask, s);
-    }
+    q.counts = q.total = nullptr;
+    q.clear_total = 0;
+    q.bitmap = (uint32_t*)(ws + wl.bitmap_off);
+    e = launch(q);
+    if (e == hipSuccess) e = cg::launch_bitmap_chan_mask(q, q.bitmap, need_u, mask, s);
     p.chan_mask = mask;
   }
-  if (e == hipSuccess && counts) e = cg::launch_zero_u32(counts, 2 + (size_t)n * d.c_out, s);
-  if (e == hipSuccess && (h->variant == CG_VARIANT_MFMA_ROWS || h->variant == CG_VARIANT_TILE)) {
-    const size_t bm_words = (size_t)p.m_total * p.words;
-    if (!p.gated) {
-      if (bitmap) e = cg::launch_zero_u32(bitmap, bm_words, s);   // a dense layer has no decisions
-    } else if (counts && !bitmap) {
-      p.bitmap = (uint32_t*)(ws + wl.bitmap_off);   // free again once the mask exists
-    }
-    if (e == hipSuccess)
-      e = h->variant == CG_VARIANT_TILE ? cg::launch_tile(plan4, p, pk + l.wpk_base_off, pk + l.wpk_cond_off, s)
-                                        : cg::launch_mfma3(plan3, p, pk + l.wpk_base_off, pk + l.wpk_cond_off, s);
-    if (e == hipSuccess && counts && p.gated) e = cg::launch_bitmap_counts(p, p.bitmap, s);
-  } else if (e == hipSuccess) {
-    e = cg::launch_naive(p, s);
+  if (!p.gated) {
+    // a dense layer has no decisions
+    if (e == hipSuccess && counts)       // (the first call's counts follow the total)
+      e = clear_total ? cg::launch_zero_u32(total, 2 + (size_t)n * d.c_out, s) : cg::launch_zero_u32(counts, (size_t)n * d.c_out, s);
+    if (e == hipSuccess && bitmap) e = cg::launch_zero_u32(bitmap, (size_t)p.m_total * p.words, s);
+    p.counts = p.total = nullptr;
+    p.clear_total = 0;
+    p.bitmap = nullptr;
+  } else if (counts && !bitmap) {
+    p.bitmap = (uint32_t*)(ws + wl.bitmap_off);   // free again once the mask exists
   }
+  if (e == hipSuccess) e = launch(p);
+  if (e == hipSuccess && counts && p.gated) e = cg::launch_bitmap_counts(p, p.bitmap, s);
   if (e != hipSuccess) return fail(CG_EHIP, "cg_conv_forward: %s", hipGetErrorString(e));
   return CG_OK;
 }

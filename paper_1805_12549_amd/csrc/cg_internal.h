@@ -24,8 +24,8 @@ struct Params {
   int groups;              // >= 1; > 1: channel grouping (Sec. 3.3), output group i has input group i as base
   int cpg;                 // output channels per group = c_out / groups
   int shuffle;             // y (and the residual) in shuffled channel order: channel j of group i at j*groups + i
-  int gate_only;           // first pass of the channel-wise gate: base path and gate only; writes the bitmap
-                           // (row-tiled kernel) or the per-(image, channel) counts (plain kernel), nothing else
+  int gate_only;           // first pass of the channel-wise gate: base path and gate only; writes the bitmap,
+                           // nothing else
   const uint32_t* chan_mask;  // second pass: [n][words] bits of the channels that keep their conditional
                               // path (Sec. 3.2 channel-wise gate), ANDed into the decisions; or NULL
 
@@ -47,7 +47,9 @@ struct Params {
   const void* residual;
   void* y;
   uint32_t* bitmap;
-  uint32_t* counts;
+  uint32_t* counts;        // [n][c_out] fired counts, or NULL; counted from the bitmap after the layer kernel
+  uint32_t* total;         // their 64-bit sum (two words), or NULL; counting adds to it
+  int clear_total;         // the layer kernel zeroes the total
 };
 
 // Geometry of the large-tile matrix-core kernel (kernels_tile.hip): four wavefronts per workgroup,
@@ -136,19 +138,44 @@ struct Mfma3Plan {
   size_t wpk_base_bytes, wpk_cond_bytes;
 };
 
+// Geometry of the small-tile matrix-core kernel (kernels_direct.hip): 16*pf output pixels x 32*cg
+// channels per tile, operands straight from global memory.
+struct DirectPlan {
+  int ok;
+  int elem_bytes, ch;      // bytes per element; channels per 16-byte chunk
+  int taps;                // 9 or 1
+  int pf, cg;              // 16-pixel fragments and 32-channel groups per tile
+  int split;               // wavefronts of a workgroup that share a tile's K; 1: a wavefront walks all of it
+  int nwb;                 // of which walk the base path
+  int slices;              // workgroups that share a tile's K (their sums meet in the workspace)
+  int n_cblk;              // tiles across the channels
+  int tiles;               // tiles in all
+  int px_wgs;              // workgroups across the pixels
+  unsigned x_bytes;        // size of x
+  // Channel chunks per tap and phase.  The base phase starts at the first chunk of the 64-channel block's
+  // first group and walks chunks[0] of them; the conditional phase walks all chunks but the gap_len ones
+  // from there on.  strad: bytes of the base group in its last, partly used chunk (ungrouped layers).
+  int chunks[2], total_chunks, gap_len, strad;
+  int ksteps[2];           // K steps (four chunks) per phase
+  int n_grp;               // 32-channel groups of the packed weights
+  size_t wpk_bytes[2];
+  size_t partial_bytes;    // workspace for the slices' sums
+};
+
+DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu);
+hipError_t launch_direct_pack(const DirectPlan& plan, const Params& p, void* wpk_base, void* wpk_cond, hipStream_t s);
+hipError_t launch_direct(const DirectPlan& plan, const Params& p, const void* wpk_base, const void* wpk_cond, void* partial,
+                         hipStream_t s);
+
 Mfma3Plan mfma3_plan(const cg_conv_desc& d, int n_cu);
 hipError_t launch_mfma3_pack(const Mfma3Plan& plan, const Params& p, void* wpk_base, void* wpk_cond, hipStream_t s);
 hipError_t launch_mfma3(const Mfma3Plan& plan, const Params& p, const void* wpk_base, const void* wpk_cond,
                         hipStream_t s);
-// per-(image, channel) fired counts and their total (into p.counts, total pre-zeroed) from a decision bitmap
+// per-(image, channel) fired counts and their total (into p.counts / p.total) from a decision bitmap
 hipError_t launch_bitmap_counts(const Params& p, const uint32_t* bitmap, hipStream_t s);
 // channel-wise gate: mask[img][w] bit b = (fired count of channel 32*w + b in image img, from the bitmap) >= need
 hipError_t launch_bitmap_chan_mask(const Params& p, const uint32_t* bitmap, uint32_t need, uint32_t* mask,
                                    hipStream_t s);
-
-// channel-wise gate: mask[img][w] bit b = counts[2 + img*c_out + 32*w + b] >= need
-hipError_t launch_chan_mask(const uint32_t* counts, int n, int c_out, int words, uint32_t need, uint32_t* mask,
-                            hipStream_t s);
 
 // launchers (return hipError_t from the last launch)
 hipError_t launch_naive(const Params& p, hipStream_t s);

@@ -281,6 +281,7 @@ __global__ __launch_bounds__(NWV * 64, 2) void gated_conv_rows_kernel(
   const int total_rows = p.n * p.ho;
   const int R0 = tile * g.tr;
   if (R0 >= total_rows) return;
+  if (p.clear_total && blockIdx.x == 0 && tid < 2) p.total[tid] = 0u;
 
   const int S0 = g.stages[0];                       // super-stages of the base phase
   const int S = S0 + ((p.gated && !p.gate_only) ? g.stages[1] : 0);   // a gate-only pass stops after the base phase
@@ -891,7 +892,8 @@ __global__ void pack_rows_kernel(const char* __restrict__ w, char* __restrict__ 
 // the block instead writes the word of the channels whose count reaches `need` (the channel-wise
 // gate of Sec. 3.2) and leaves `counts` alone.
 __global__ void bitmap_counts_kernel(const uint32_t* __restrict__ bitmap, int words, int hw, int c_out,
-                                     uint32_t* __restrict__ counts, uint32_t* __restrict__ mask, uint32_t need) {
+                                     uint32_t* __restrict__ counts, unsigned long long* __restrict__ total,
+                                     uint32_t* __restrict__ mask, uint32_t need) {
   __shared__ uint32_t cnt[32];
   const int w = blockIdx.x % words, img = blockIdx.x / words;
   const int lane = threadIdx.x & 63;
@@ -917,10 +919,10 @@ __global__ void bitmap_counts_kernel(const uint32_t* __restrict__ bitmap, int wo
       if (lane == 0) mask[(long long)img * words + w] = (uint32_t)keep;
       return;
     }
-    if (lane < 32 && co < c_out) counts[2 + (long long)img * c_out + co] = v;
+    if (lane < 32 && co < c_out) counts[(long long)img * c_out + co] = v;
 #pragma unroll
     for (int sft = 16; sft >= 1; sft >>= 1) v += (uint32_t)__shfl_xor((int)v, sft, 64);
-    if (lane == 0 && v) atomicAdd((unsigned long long*)counts, (unsigned long long)v);
+    if (lane == 0 && v) atomicAdd(total, (unsigned long long)v);
   }
 }
 
@@ -929,7 +931,8 @@ __global__ void bitmap_counts_kernel(const uint32_t* __restrict__ bitmap, int wo
 // blocks and one atomic per block instead of one block and one atomic per word.
 __global__ void bitmap_counts_small_kernel(const uint32_t* __restrict__ bitmap, int words, int hw, int c_out,
                                            long long items, uint32_t* __restrict__ counts,
-                                           uint32_t* __restrict__ mask, uint32_t need) {
+                                           unsigned long long* __restrict__ total_out, uint32_t* __restrict__ mask,
+                                           uint32_t need) {
   __shared__ uint32_t part[4];
   const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   uint32_t total = 0u;
@@ -945,7 +948,7 @@ __global__ void bitmap_counts_small_kernel(const uint32_t* __restrict__ bitmap, 
       if (mask) {
         keep |= (c >= need ? 1u : 0u) << b;
       } else {
-        counts[2 + img * c_out + co] = c;
+        counts[img * c_out + co] = c;
         total += c;
       }
     }
@@ -958,7 +961,7 @@ __global__ void bitmap_counts_small_kernel(const uint32_t* __restrict__ bitmap, 
   __syncthreads();
   if (threadIdx.x == 0) {
     const unsigned long long v = (unsigned long long)part[0] + part[1] + part[2] + part[3];
-    if (v) atomicAdd((unsigned long long*)counts, v);
+    if (v) atomicAdd(total_out, v);
   }
 }
 
@@ -1235,11 +1238,11 @@ hipError_t launch_bitmap_counts(const Params& p, const uint32_t* bitmap, hipStre
   if (blocks <= 0) return hipSuccess;
   if (p.ho * p.wo <= kSmallMap) {
     hipLaunchKernelGGL(bitmap_counts_small_kernel, dim3((unsigned)((blocks + 255) / 256)), dim3(256), 0, s, bitmap,
-                       p.words, p.ho * p.wo, p.c_out, blocks, p.counts, (uint32_t*)nullptr, 0u);
+                       p.words, p.ho * p.wo, p.c_out, blocks, p.counts, (unsigned long long*)p.total, (uint32_t*)nullptr, 0u);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(bitmap_counts_kernel, dim3((unsigned)blocks), dim3(256), 0, s, bitmap, p.words, p.ho * p.wo,
-                     p.c_out, p.counts, (uint32_t*)nullptr, 0u);
+                     p.c_out, p.counts, (unsigned long long*)p.total, (uint32_t*)nullptr, 0u);
   return hipGetLastError();
 }
 
@@ -1249,11 +1252,11 @@ hipError_t launch_bitmap_chan_mask(const Params& p, const uint32_t* bitmap, uint
   if (blocks <= 0) return hipSuccess;
   if (p.ho * p.wo <= kSmallMap) {
     hipLaunchKernelGGL(bitmap_counts_small_kernel, dim3((unsigned)((blocks + 255) / 256)), dim3(256), 0, s, bitmap,
-                       p.words, p.ho * p.wo, p.c_out, blocks, (uint32_t*)nullptr, mask, need);
+                       p.words, p.ho * p.wo, p.c_out, blocks, (uint32_t*)nullptr, (unsigned long long*)nullptr, mask, need);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(bitmap_counts_kernel, dim3((unsigned)blocks), dim3(256), 0, s, bitmap, p.words, p.ho * p.wo,
-                     p.c_out, (uint32_t*)nullptr, mask, need);
+                     p.c_out, (uint32_t*)nullptr, (unsigned long long*)nullptr, mask, need);
   return hipGetLastError();
 }
 

@@ -102,43 +102,18 @@ __global__ __launch_bounds__(256) void naive_kernel(Params p) {
         store_int(p, o, finish_int(p, acc, branch1, co, o));
       }
     }
-    if (fired && p.counts) atomicAdd(&p.counts[2 + (long long)img * p.c_out + co], 1u);
   }
 
   const unsigned long long mask = __ballot(fired);
   const int lane = threadIdx.x & 63;
   if (p.bitmap && (lane & 31) == 0 && m < p.m_total)
     p.bitmap[t >> 5] = (uint32_t)(lane ? (mask >> 32) : mask);
-  if (p.counts && lane == 0 && mask) {
-    atomicAdd((unsigned long long*)p.counts, (unsigned long long)__popcll(mask));
-  }
+  if (p.clear_total && t < 2) p.total[t] = 0u;
 }
 
 __global__ void zero_u32_kernel(uint32_t* ptr, size_t words) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < words) ptr[i] = 0u;
-}
-
-__global__ void chan_mask_kernel(const uint32_t* __restrict__ counts, int n, int c_out, int words, uint32_t need,
-                                 uint32_t* __restrict__ mask) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n * words) return;
-  const int img = i / words, w = i - img * words;
-  uint32_t bits = 0u;
-  for (int b = 0; b < 32; ++b) {
-    const int co = 32 * w + b;
-    if (co < c_out && counts[2 + (long long)img * c_out + co] >= need) bits |= 1u << b;
-  }
-  mask[i] = bits;
-}
-
-hipError_t launch_chan_mask(const uint32_t* counts, int n, int c_out, int words, uint32_t need, uint32_t* mask,
-                            hipStream_t s) {
-  const int total = n * words;
-  if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(chan_mask_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, counts, n, c_out,
-                     words, need, mask);
-  return hipGetLastError();
 }
 
 hipError_t launch_zero_u32(uint32_t* ptr, size_t words, hipStream_t s) {

@@ -622,6 +622,7 @@ __global__ __launch_bounds__(kNT) void gated_conv_tile_kernel(Params p, TilePlan
   asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
   __builtin_amdgcn_s_waitcnt(CG_TILE_VMCNT(0));
   __syncthreads();
+  if (p.clear_total && blockIdx.x == 0 && tid < 2) p.total[tid] = 0u;
   if (p.gated && p.bitmap) {
     for (int i = tid; i < bmv * WPP; i += kNT) {
       const int px = i / WPP, w = i % WPP;

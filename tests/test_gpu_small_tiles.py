@@ -1,0 +1,87 @@
+"""GPU parity of the small-tile matrix-core kernel (operands straight from global memory) against the CPU
+oracle, through the C ABI: channel counts that are multiples of nothing large, base groups that end
+inside a 16-byte chunk, single images, fp32, both forms (K split over wavefronts / one wavefront per tile)."""
+import numpy as np
+import pytest
+
+from paper_1805_12549_amd import binding as B
+from paper_1805_12549_amd import workloads as W
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+def _say(rep):
+    print("\n  " + str(rep), flush=True)
+    return rep
+
+
+def S(n, h, w, ci, co, **kw):
+    return W.LayerShape("%dx%dx%d_%d>%d" % (n, h, w, ci, co) + "".join("_%s%d" % i for i in sorted(kw.items())), n, h, w, ci, co, **kw)
+
+
+SHAPES = [
+    S(1, 32, 32, 16, 16),                     # the smallest configuration
+    S(5, 45, 33, 96, 80),                     # c_out ends inside a fragment
+    S(1, 3, 3, 16, 8, pad=0),                 # one output pixel, eight channels
+    S(2, 9, 11, 48, 33),                      # c_out odd: element stores
+    S(3, 7, 7, 16, 48, groups=8),             # base groups of two channels: inside a chunk
+    S(2, 13, 9, 80, 96, groups=5, stride=2),  # three fragments across the channels
+    S(1, 14, 14, 256, 256),                   # one image, deep
+    S(1, 7, 7, 512, 512),
+    S(40, 33, 31, 16, 64),                    # enough tiles for one wavefront each
+    S(9, 5, 6, 96, 112, k=1, pad=0),
+    S(70, 1, 1, 160, 48, k=1, pad=0),
+    S(2, 14, 14, 64, 128, k=1, pad=0, stride=2, groups=8),
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=[s.name for s in SHAPES])
+def test_small_tiles(shape):
+    rng = np.random.default_rng(shape.n * 7 + shape.c_out)
+    c = shape.c_out
+    aff = dict(scale0=rng.uniform(0.5, 1.5, c), shift0=rng.normal(0, 0.1, c),
+               scale1=rng.uniform(0.5, 1.5, c), shift1=rng.normal(0, 0.1, c))
+    res = rng.standard_normal((shape.n, shape.ho, shape.wo, c)).astype(np.float32)
+    full = B.CG_EPI_RELU | B.CG_EPI_AFFINE | B.CG_EPI_RESIDUAL
+    kind = "coherent" if min(shape.h, shape.w) >= 8 else "iid"
+    inp = W.make_inputs(shape, 7000 + c + shape.h, kind=kind, rho=0.3, round_bf16=True)
+    gate = W.calibrate_gate(inp, 0.3, sample_images=None)
+    _say(P.run_float(inp, gate, in_dtype=B.CG_F32, out_dtype=B.CG_F32, affine=aff, residual=res, epilogue=full, name=shape.name + " fp32"))
+    _say(P.run_float(inp, gate, in_dtype=B.CG_F32, out_dtype=B.CG_BF16, n_run=1, tau_c=0.3, name=shape.name + " fp32 channel-wise gate"))
+    if shape.c_in % 8 == 0:
+        _say(P.run_float(inp, gate, out_dtype=B.CG_BF16, affine=aff, residual=res, epilogue=full, name=shape.name + " bf16"))
+        _say(P.run_float(inp, gate, out_dtype=B.CG_F32, delta_hi=gate.delta + 0.8, n_run=(shape.n + 1) // 2, name=shape.name + " bf16 two-sided"))
+        _say(P.run_float(inp, None, out_dtype=B.CG_F32, name=shape.name + " bf16 dense")) if shape.groups == 1 else None
+    if shape.c_in % 16 == 0:
+        q = W.quantize_int8(W.make_inputs(shape, 7100 + c + shape.h, kind=kind, rho=0.35))
+        thr = W.calibrate_gate_int8(q, 0.35, sample_images=None)
+        res8 = rng.integers(-128, 128, (shape.n, shape.ho, shape.wo, c)).astype(np.int8)
+        _say(P.run_int8(q, thr, name=shape.name + " int8"))
+        _say(P.run_int8(q, thr, out_i8=True, rq=W.requant_params(q, rng), residual=res8, rq_res_mult=1 << 14,
+                        epilogue=B.CG_EPI_RESIDUAL | B.CG_EPI_RELU, n_run=1, name=shape.name + " int8 requantised"))
+
+
+@pytest.mark.parametrize("shape", [S(3, 9, 9, 64, 64, groups=4), S(2, 8, 10, 96, 48, groups=4), S(1, 10, 10, 48, 144, groups=3)],
+                         ids=lambda s: s.name)
+def test_small_tiles_grouped(shape):
+    inp = W.make_inputs(shape, 7300 + shape.c_out, kind="coherent", rho=0.3, round_bf16=True, grouped=True)
+    gate = W.calibrate_gate(inp, 0.3, sample_images=None)
+    for dt in (B.CG_F32, B.CG_BF16):
+        _say(P.run_float(inp, gate, in_dtype=dt, shuffle=True, name=shape.name + " grouped shuffled"))
+        _say(P.run_float(inp, gate, in_dtype=dt, n_run=1, out_dtype=B.CG_BF16, name=shape.name + " grouped n=1"))
+
+
+def test_base_group_inside_a_chunk_keeps_the_paths_apart():
+    """A value that is not finite in a conditional channel of the base group's last chunk reaches no base sum."""
+    import torch
+    w_b, w_c = torch.ones((32, 3, 3, 4), dtype=torch.bfloat16, device="cuda"), torch.ones((32, 3, 3, 12), dtype=torch.bfloat16, device="cuda")
+    x = torch.ones((1, 8, 8, 16), dtype=torch.bfloat16, device="cuda")
+    x[..., 4:] = float("inf")
+    layer = B.GatedConv(n_max=1, h=8, w=8, c_in=16, c_out=32, c_base=4, w_base=w_b, w_cond=w_c, in_dtype=B.CG_BF16,
+                        out_dtype=B.CG_F32, gate_mean=np.zeros(32), gate_var=np.ones(32), delta=np.full(32, 1e6))
+    y, bitmap, counts = layer.forward(x)
+    torch.cuda.synchronize()
+    assert int(bitmap.abs().sum()) == 0 and int(counts[0]) == 0
+    assert float(y.max()) == 36.0 and float(y.min()) == 16.0
+    layer.close()
