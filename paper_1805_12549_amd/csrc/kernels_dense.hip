@@ -20,7 +20,6 @@ using cg::float_to_bf16;
 
 constexpr int kTile = 8;      // output pixels per block edge
 constexpr int kCb = 64;       // output channels per block
-constexpr int kMaxTaps = 7 * 7 * 4;
 
 // Direct convolution for c_in <= 4.  Block = 8x8 output pixels x 64 output channels, 256 threads:
 // thread (px, g) accumulates channels [16g, 16g+16) of pixel px.  A wavefront holds one g and 64
@@ -114,198 +113,384 @@ __global__ __launch_bounds__(256) void small_cin_conv_kernel(const uint16_t* __r
   }
 }
 
-// The ImageNet input layer's shape (7x7, stride 2, three input channels) on the matrix cores.
-// Block = 16x16 output pixels x 64 channels, four wavefronts, each 64 pixels x 64 channels as 2x2
-// 32x32 MFMA blocks.  K is ordered kernel row by kernel row; within a row the 21 values (column,
-// channel) of a pixel are 21 contiguous bf16 of the input patch, padded to 24 = three 8-element
-// chunks (the three extra elements meet zero weights), so the pixel operand of a chunk is 16
-// contiguous bytes of the LDS patch, read as four words (the start is only 4-byte aligned).
-// 7 rows x 3 chunks = 21 chunks, padded to 22 = 11 K steps of 16.  The product is taken with the
-// weights as the row operand and their rows permuted (row rho holds channel
-// 16*((rho/4)%2) + 4*(rho/8) + rho%4), which leaves every lane with 16 consecutive channels of
-// one pixel per accumulator.
 typedef __attribute__((ext_vector_type(8))) __bf16 stem_bf16x8;
 typedef __attribute__((ext_vector_type(16))) float stem_f32x16;
 typedef __attribute__((ext_vector_type(4))) int stem_i32x4;
 
-//
-// POOL: the 3x3 stride-2 max pooling (padding 1) that follows the layer in a ResNet is applied in
-// the block: the 16x16 tile then starts one row and column before an even position and yields the
-// 7x7 pooled pixels whose windows it holds (neighbouring tiles overlap by two rows / columns); the
-// converted outputs meet in an LDS tile, positions outside the layer's output count as -inf, and
-// only the pooled tensor is written.
-template <bool POOL>
-__global__ __launch_bounds__(256) void conv7x7s2c3_mfma_kernel(const uint16_t* __restrict__ x,
-                                                               const uint16_t* __restrict__ w,
-                                                               const float* __restrict__ scale,
-                                                               const float* __restrict__ shift, uint16_t* __restrict__ y,
-                                                               int n, int h, int wd, int c_out, int pad, int ho, int wo,
-                                                               int relu, int tpb) {
-  constexpr int K = 7, CI = 3, ST = 2, TILE = 16, TAPS = K * K * CI;
-  constexpr int PE = (TILE - 1) * ST + K;          // 37 patch rows / columns in use
-  constexpr int PR = 120;                          // bf16 per patch row (111 in use, the rest zero)
-  constexpr int PROWS = PE + 1;                    // one more zero row for the padding chunk
-  constexpr int NQ = 22;                           // 8-element K chunks
-  __shared__ __align__(16) uint16_t wl[NQ * kCb * 8];    // [chunk][row][8]
-  __shared__ __align__(16) uint16_t xl[PROWS * PR];
-  __shared__ __align__(16) uint16_t ol[POOL ? TILE * TILE * kCb : 8];   // [tile pixel][64 channels] (POOL)
-  constexpr int PT = 7;                            // pooled rows / columns per tile (POOL)
-  const int pho = (ho - 1) / 2 + 1, pwo = (wo - 1) / 2 + 1;   // pooled output size (POOL)
-  const int tid = threadIdx.x;
-  // one block walks tpb tiles of a row: the weights are laid out once per block
-  const int tiles_w = POOL ? (pwo + PT - 1) / PT : (wo + TILE - 1) / TILE;
-  const int tiles_h = POOL ? (pho + PT - 1) / PT : (ho + TILE - 1) / TILE;
-  const int strips = (tiles_w + tpb - 1) / tpb;
-  int b = blockIdx.x;
-  const int tw0 = (b % strips) * tpb;
-  b /= strips;
-  const int th = b % tiles_h;
-  const int img = b / tiles_h;
-  const int cb = blockIdx.y;
-  const int tw1 = tw0 + tpb < tiles_w ? tw0 + tpb : tiles_w;
+// two floats as bf16 (round to nearest even), a in the low half
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
 
-  // weights: chunk q = (kernel row q/3, elements 8*(q%3) .. +8 of its 24), row = permuted channel.
-  // A thread lays out one (channel, kernel row): 21 contiguous weights become three chunks, the
-  // last three elements zero; the 22nd chunk of every row is zero.
-  if (tid < kCb) *(uint4*)(wl + (((NQ - 1) * kCb + tid) << 3)) = uint4{0u, 0u, 0u, 0u};
-  {
-    const uint16_t* wsrc = w + (long long)cb * kCb * TAPS;
-    for (int pr = tid; pr < kCb * K; pr += 256) {
-      const int col = pr / K, r = pr - col * K;
-      const uint16_t* src = wsrc + col * TAPS + r * (K * CI);
-      uint16_t v[24];
-#pragma unroll
-      for (int e = 0; e < K * CI; ++e) v[e] = src[e];
-      v[21] = v[22] = v[23] = 0;
-      const int ch = col & 31;
-      const int row = (col & 32) + 8 * ((ch & 15) >> 2) + 4 * (ch >> 4) + (ch & 3);   // inverse of the row permutation
-      uint16_t* dst = wl + (((3 * r) * kCb + row) << 3);
-      *(uint4*)(dst) = *(const uint4*)(v);
-      *(uint4*)(dst + kCb * 8) = *(const uint4*)(v + 8);
-      *(uint4*)(dst + 2 * kCb * 8) = *(const uint4*)(v + 16);
-    }
-  }
-  const int lane = tid & 63, wave = tid >> 6;
+// The ImageNet input layer's shape (7x7, stride 2, three input channels) on the matrix cores, with (POOL) the 3x3
+// stride-2 max pooling (padding 1) that follows it in a ResNet.
+//
+// A workgroup of two wavefronts walks down a band of output rows.  A wavefront holds the weights of 64 channels in
+// registers (K = 7 kernel rows x 24 elements, 88 registers) and multiplies, per row of the layer's output, two
+// fragments of 32 columns: the even columns 2*pc and the odd ones 2*pc + 1 of the pooled columns pc = first - 1 + lane.
+// A pooled value is then the maximum of a lane's even column, its odd column and its left neighbour's odd column
+// (lane 0 is there for that only), over three rows of which the last is kept for the next pooled row: the layer is
+// computed once, but for one row per band and two columns per fragment.  The product is taken with the weights as the
+// row operand and their rows permuted (row rho holds channel 16*((rho/4)%2) + 4*(rho/8) + rho%4), which leaves every
+// lane with 16 consecutive channels of one pixel per accumulator.
+//
+// Rows of the input lie in a ring of LDS rows; the next step's four are loaded while this step's are multiplied.  Within a
+// kernel row a pixel's 21 values (column, channel) are contiguous; with an odd padding one element before them is
+// taken as well (zero weight), so that every read starts on a word; 24 elements = three 16-byte chunks, 22 chunks
+// (the last one zero) = 11 K steps of 16.
+//
+// Maxima of sums instead of outputs: the output function is monotone in the sum, rising where the scale is not negative;
+// channels with a negative scale take negated weights and the scale's magnitude (both exact).
+//
+// What bounds it: the matrix cores (44 instructions of 32 clocks per output row and 28 pooled columns; half of the time with
+// two wavefronts to a SIMD) and as often the LDS reads of the pixel operands.  Images of 224x224 with pooling: 256 in
+// 98 us, 64 in 36, 16 in 18; 240, 66 and 22 in the form before (16x16 tiles gathered as single elements, 1.31 times
+// the products, outputs exchanged through LDS for the pooling).
+constexpr int kStemPitch = 1664;                 // bytes of a ring row: 63 pooled columns' input and the window's rest
+constexpr int kStemRing = 16;
+constexpr int kStemPieces = kStemPitch / 16 - 1; // 16-byte pieces of a row
+constexpr int kStemCols = 31;                    // pooled columns of a fragment, at most
+
+struct StemArgs {
+  const uint16_t* x;
+  const uint16_t* w;
+  const float* scale;
+  const float* shift;
+  uint16_t* y;
+  int h, wd, c_out, pad, ho, wo, relu;
+  int oh, ow;                                    // output of the kernel: pooled, or column pairs and row pairs of the layer's
+  int cpf, col_wgs;                              // pooled columns per wavefront; workgroups across the columns
+  int band, bands;                               // pooled rows per workgroup; workgroups across the rows
+};
+
+struct __attribute__((packed, aligned(2))) StemPiece {
+  stem_i32x4 v;
+};
+
+template <bool POOL>
+__global__ __launch_bounds__(128, 2) void conv7x7s2c3_kernel(StemArgs a) {
+  constexpr int K = 7, CI = 3, TAPS = K * K * CI, ST = 11;
+  __shared__ __align__(16) char ring[kStemRing * kStemPitch];   // first the weights, then input rows
+  __shared__ __align__(16) float tab[2 * kCb];                  // |scale|, shift
+  __shared__ __align__(16) int fillers[2][4];                   // the 22nd chunk of a pixel: zeros; -inf, zeros
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lj = lane & 31, lh = lane >> 5;
-  // this lane's pixels: fragment 2*wave + fp covers tile rows 2*(2*wave+fp) and the next
-  int pbase[2];
+  const int cb = blockIdx.y;
+  int b = blockIdx.x;
+  const int cw = b % a.col_wgs;
+  b /= a.col_wgs;
+  const int p0 = (b % a.bands) * a.band, img = b / a.bands;
+  const int p1 = p0 + a.band < a.oh ? p0 + a.band : a.oh;
+
+  // ---- rows of the input: 16-byte piece t of row `hi` by thread t.  A ring row starts (16 bytes in) with element el0 of
+  // the image's row; pieces start at multiples of eight elements, so that no piece straddles the image's left edge.
+  const int lead = a.pad & 1;                    // elements before the window
+  const int first = cw * 2 * a.cpf;              // first pooled column of the workgroup
+  const int el0 = (4 * (first - 1) - a.pad) * CI - lead, row_els = a.wd * CI;
+  const int piece0 = (el0 & ~7) + tid * 8;       // first element of this thread's piece
+  const uint16_t* const ximg = a.x + (long long)img * a.h * row_els;
+  const bool in_row = tid < kStemPieces && piece0 >= 0 && piece0 + 8 <= row_els;
+  const bool cut = tid < kStemPieces && piece0 < row_els && piece0 + 8 > row_els;    // (rows of whole pieces have none)
+  auto load_piece = [&](int hi) __attribute__((always_inline)) {
+    stem_i32x4 v = {0, 0, 0, 0};
+    if ((unsigned)hi < (unsigned)a.h) {
+      const uint16_t* src = ximg + (long long)hi * row_els + piece0;
+      if (in_row) v = ((const StemPiece*)src)->v;
+      if ((row_els & 7) && cut) {
+#pragma nounroll
+        for (int e = 0; e < (row_els & 7); ++e) {
+          const int bits = (int)((uint32_t)src[e] << (16 * (e & 1)));
 #pragma unroll
-  for (int fp = 0; fp < 2; ++fp) {
-    const int oh = 2 * (2 * wave + fp) + (lj >> 4), ow = lj & 15;
-    pbase[fp] = (oh * ST) * PR + ow * ST * CI;     // element offset of the pixel's window, kernel row 0
-  }
-  for (int tw = tw0; tw < tw1; ++tw) {
-  if (tw > tw0) __syncthreads();                   // the previous tile's patch has been read
-  // input patch as bf16, zero outside the image and in the padding
-  const int oy0 = POOL ? 2 * PT * th - 1 : th * TILE, ox0 = POOL ? 2 * PT * tw - 1 : tw * TILE;   // the tile's first output pixel
-  const int h0 = oy0 * ST - pad, w0 = ox0 * ST - pad;
-  // a thread fills one patch pixel (three channels) at a time; 40 pixel positions per row, the ones
-  // past the patch edge or outside the image are zero
-  constexpr int PPR = PR / CI;
+          for (int d = 0; d < 4; ++d) v[d] |= e >> 1 == d ? bits : 0;
+        }
+      }
+    }
+    return v;
+  };
+  auto keep_piece = [&](int hi, stem_i32x4 v) __attribute__((always_inline)) {
+    if (tid < kStemPieces) {                     // (el0 is even)
+      int* dst = (int*)(ring + ((hi + 64) & (kStemRing - 1)) * kStemPitch + 16 + (piece0 - el0) * 2);
 #pragma unroll
-  for (int u = 0; u < (PROWS * PPR + 255) / 256; ++u) {
-    const int pp = tid + 256 * u;
-    const int ph = pp / PPR, pw = pp - ph * PPR;
-    const int hi = h0 + ph, wi = w0 + pw;
-    uint16_t v0 = 0, v1 = 0, v2 = 0;
-    if (pp < PROWS * PPR && ph < PE && pw < PE && hi >= 0 && hi < h && wi >= 0 && wi < wd) {
-      const uint16_t* src = x + (((long long)img * h + hi) * wd + wi) * CI;
-      v0 = src[0];
-      v1 = src[1];
-      v2 = src[2];
+      for (int e = 0; e < 4; ++e) dst[e] = v[e];
     }
-    if (pp < PROWS * PPR) {
-      uint16_t* dst = xl + ph * PR + pw * CI;
-      dst[0] = v0;
-      dst[1] = v1;
-      dst[2] = v2;
+  };
+  // output row r of the layer reads input rows 2r - pad .. + 6; the first step's rows start at r = 2*p0 - 1
+  const int hi0 = (POOL ? 4 * p0 - 2 : 4 * p0) - a.pad;
+  constexpr int NFIRST = POOL ? 11 : 9;
+  stem_i32x4 fill[NFIRST];
+#pragma unroll
+  for (int k = 0; k < NFIRST; ++k) fill[k] = load_piece(hi0 + k);
+
+  // ---- weights through LDS: [chunk][row][8 elements]; a thread lays out a kernel row of a channel at a time (three
+  // chunks from 24 elements of which the first and last ones may be its neighbours': those become zero)
+  {
+    constexpr int ROWS = kCb * K, PER = (ROWS + 127) / 128;
+    const uint16_t* wsrc = a.w + (long long)cb * kCb * TAPS - lead;
+    stem_i32x4 v[PER][3];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int pr = tid + 128 * u;              // = channel * 7 + kernel row
+#pragma unroll
+      for (int part = 0; part < 3; ++part) v[u][part] = stem_i32x4{0, 0, 0, 0};
+      if (pr > 0 && pr < ROWS - 1) {
+#pragma unroll
+        for (int part = 0; part < 3; ++part) v[u][part] = ((const StemPiece*)(wsrc + pr * (K * CI) + part * 8))->v;
+      } else if (pr < ROWS) {                    // the ends of the array
+#pragma unroll
+        for (int e = 0; e < K * CI; ++e) {
+          const uint32_t el = (uint32_t)wsrc[pr * (K * CI) + e + lead];
+          const uint32_t even = el << (16 * (e & 1)), odd = el << (16 * ((e + 1) & 1));   // without and with the lead
+          v[u][e / 8][e % 8 / 2] |= lead ? 0 : (int)even;
+          v[u][(e + 1) / 8][(e + 1) % 8 / 2] |= lead ? (int)odd : 0;
+        }
+      }
     }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int pr = tid + 128 * u;
+      if (pr >= ROWS) break;
+      const int co = pr / K, kr = pr - co * K, ch = co & 31;
+      const int row = (co & 32) + 8 * ((ch & 15) >> 2) + 4 * (ch >> 4) + (ch & 3);   // inverse of the row permutation
+      const int flip = a.scale && a.scale[cb * kCb + co] < 0.0f ? (int)0x80008000u : 0;
+      v[u][0][0] &= lead ? (int)0xffff0000u : -1;
+      v[u][2][2] &= lead ? -1 : 0xffff;          // elements 21 + lead and on
+      v[u][2][3] = 0;
+#pragma unroll
+      for (int part = 0; part < 3; ++part) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[u][part][e] ^= flip;
+        *(stem_i32x4*)(ring + ((3 * kr + part) * kCb + row) * 16) = v[u][part];
+      }
+    }
+    if (tid < kCb) {
+      tab[tid] = a.scale ? fabsf(a.scale[cb * kCb + tid]) : 1.0f;
+      tab[kCb + tid] = a.shift ? a.shift[cb * kCb + tid] : 0.0f;
+    }
+    if (tid < 8) fillers[tid >> 2][tid & 3] = tid == 4 ? 0xff80 : 0;
   }
   __syncthreads();
-
-  stem_f32x16 acc[2][2];
+  stem_i32x4 wf[ST][2];
 #pragma unroll
-  for (int fp = 0; fp < 2; ++fp)
-#pragma unroll
-    for (int fc = 0; fc < 2; ++fc)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[fp][fc][i] = 0.0f;
-#pragma unroll
-  for (int st = 0; st < NQ / 2; ++st) {
-    const int q = 2 * st + lh;                     // this lane half's chunk of the K step
-    const int r = q / 3, j0 = (q % 3) * 8;
-    stem_i32x4 a[2], bq[2];
-#pragma unroll
-    for (int fc = 0; fc < 2; ++fc) a[fc] = *(const stem_i32x4*)(wl + ((q * kCb + 32 * fc + lj) << 3));
-#pragma unroll
-    for (int fp = 0; fp < 2; ++fp) {
-      const uint32_t* src = (const uint32_t*)(xl + pbase[fp] + r * PR + j0);
-      bq[fp] = stem_i32x4{(int)src[0], (int)src[1], (int)src[2], (int)src[3]};
-    }
-#pragma unroll
-    for (int fp = 0; fp < 2; ++fp)
-#pragma unroll
-      for (int fc = 0; fc < 2; ++fc)
-        acc[fp][fc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(stem_bf16x8, a[fc]),
-                                                              __builtin_bit_cast(stem_bf16x8, bq[fp]), acc[fp][fc], 0, 0, 0);
-  }
-#pragma unroll
-  for (int fp = 0; fp < 2; ++fp) {
-    const int oy = oy0 + 2 * (2 * wave + fp) + (lj >> 4), ox = ox0 + (lj & 15);
-    const bool inside = oy >= 0 && oy < ho && ox >= 0 && ox < wo;
-    if (!POOL && !inside) continue;
+  for (int st = 0; st < ST; ++st)
 #pragma unroll
     for (int fc = 0; fc < 2; ++fc) {
-      const int co0 = cb * kCb + 32 * fc + 16 * lh;
-      float sc[16], sh[16];
+      // this lane half's chunk: kernel rows 0..2 and 3..5 side by side, then row 6; the 22nd chunk is 1, 0, 0, ...
+      const int q = st < 9 ? st + 9 * lh : st == 9 ? 18 + 2 * lh : 19;
+      wf[st][fc] = *(const stem_i32x4*)(ring + (q * kCb + 32 * fc + lj) * 16);
+      if (st == ST - 1 && lh) wf[st][fc] = stem_i32x4{0x3f80, 0, 0, 0};
+    }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < NFIRST; ++k) keep_piece(hi0 + k, fill[k]);
+  __syncthreads();
+
+  const int pc = first + wave * a.cpf - 1 + lj;  // this lane's pooled column
+  const int pcc = pc < a.ow ? pc : a.ow - 1;     // (lanes past the last one read its input)
+  const int col = 16 + (pcc - first + 1) * (4 * CI * 2);        // bytes from the ring row's start to the even column's window
+  const bool odd_in = 2 * pc + 1 >= 0 && 2 * pc + 1 < a.wo;     // the odd column lies inside the layer's output
+  const bool mine = lj >= 1 && lj <= a.cpf && pc < a.ow;        // this lane writes
+
+  // sums of row r: even and odd columns
+  auto row_sums = [&](int r, stem_f32x16 (&acc)[2][2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+      for (int fc = 0; fc < 2; ++fc)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[o][fc][i] = 0.0f;
+    const int top = 2 * r - a.pad + 64;
+    auto row_at = [&](int kr) __attribute__((always_inline)) { return ((top + kr) & (kStemRing - 1)) * kStemPitch; };
+    // (the odd columns' addresses are hidden from the compiler: it would read what the two have in common once and copy
+    // it into place, which needs the value at once)
+    unsigned at[4], at1[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      at[k] = (unsigned)(col + (k == 3 ? row_at(6) : lh ? row_at(k + 3) : row_at(k)));
+      at1[k] = at[k] + 2 * CI * 2;
+      asm("" : "+v"(at1[k]));
+    }
+    // operands of two K steps ahead are on their way while a step is multiplied
+    stem_i32x4 even[3], odd[3];
+    auto read_step = [&](int st) __attribute__((always_inline)) {
+      const int k = st / 3 < 3 ? st / 3 : 3, ofs = st < 9 ? st % 3 * 16 : st == 9 ? 32 * lh : 16;
+      const char *src = ring + at[k] + ofs, *src1 = ring + at1[k] + ofs;
+      if (st == ST - 1) {
+        src = lh ? (const char*)fillers[0] : src;
+        src1 = lh ? (const char*)fillers[odd_in ? 0 : 1] : src1;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        even[st % 3][e] = ((const int*)src)[e];
+        odd[st % 3][e] = ((const int*)src1)[e];
+      }
+    };
+    read_step(0);
+    read_step(1);
+#pragma unroll
+    for (int st = 0; st < ST; ++st) {
+      if (st + 2 < ST) read_step(st + 2);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int fc = 0; fc < 2; ++fc) {
+        acc[0][fc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(stem_bf16x8, wf[st][fc]),
+                                                             __builtin_bit_cast(stem_bf16x8, even[st % 3]), acc[0][fc], 0, 0, 0);
+        acc[1][fc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(stem_bf16x8, wf[st][fc]),
+                                                             __builtin_bit_cast(stem_bf16x8, odd[st % 3]), acc[1][fc], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto write = [&](const stem_f32x16 (&v)[2], uint16_t* dst) __attribute__((always_inline)) {
+#pragma unroll
+    for (int fc = 0; fc < 2; ++fc) {
+      uint32_t o[8];
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
-        const float4 a4 = scale ? *(const float4*)(scale + co0 + 4 * q4) : float4{1.0f, 1.0f, 1.0f, 1.0f};
-        const float4 b4 = shift ? *(const float4*)(shift + co0 + 4 * q4) : float4{0.0f, 0.0f, 0.0f, 0.0f};
-        sc[4 * q4] = a4.x, sc[4 * q4 + 1] = a4.y, sc[4 * q4 + 2] = a4.z, sc[4 * q4 + 3] = a4.w;
-        sh[4 * q4] = b4.x, sh[4 * q4 + 1] = b4.y, sh[4 * q4 + 2] = b4.z, sh[4 * q4 + 3] = b4.w;
-      }
-      uint16_t out[16];
+        const float4 sc = *(const float4*)(tab + 32 * fc + 16 * lh + 4 * q4);
+        const float4 sh = *(const float4*)(tab + kCb + 32 * fc + 16 * lh + 4 * q4);
+        float r[4] = {fmaf(v[fc][4 * q4], sc.x, sh.x), fmaf(v[fc][4 * q4 + 1], sc.y, sh.y),
+                      fmaf(v[fc][4 * q4 + 2], sc.z, sh.z), fmaf(v[fc][4 * q4 + 3], sc.w, sh.w)};
+        if (a.relu) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        float v = acc[fp][fc][i] * sc[i] + sh[i];
-        if (relu) v = fmaxf(v, 0.0f);
-        out[i] = (POOL && !inside) ? (uint16_t)0xFF80 : float_to_bf16(v);     // 0xFF80 = -inf
-      }
-      uint4* dst = POOL ? (uint4*)(ol + ((2 * (2 * wave + fp) + (lj >> 4)) * TILE + (lj & 15)) * kCb + 32 * fc + 16 * lh)
-                        : (uint4*)(y + (((long long)img * ho + oy) * wo + ox) * c_out + co0);
-      dst[0] = *(const uint4*)(out);
-      dst[1] = *(const uint4*)(out + 8);
-    }
-  }
-  if constexpr (POOL) {
-    __syncthreads();
-    // pooled pixel (py, px) of the tile takes tile rows 2py .. 2py+2 and columns 2px .. 2px+2; a thread
-    // takes eight channels of one pooled pixel at a time
-    for (int it = tid; it < PT * PT * (kCb / 8); it += 256) {
-      const int c8 = it & 7, pp = it >> 3;
-      const int py = pp / PT, px = pp - py * PT;
-      const int gy = PT * th + py, gx = PT * tw + px;
-      if (gy >= pho || gx >= pwo) continue;
-      float m[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) m[i] = -__builtin_inff();
-#pragma unroll
-      for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          uint16_t v[8];
-          *(uint4*)v = *(const uint4*)(ol + ((2 * py + r) * TILE + 2 * px + c) * kCb + c8 * 8);
-#pragma unroll
-          for (int i = 0; i < 8; ++i) m[i] = fmaxf(m[i], bf16_to_float(v[i]));
+          for (int e = 0; e < 4; ++e) r[e] = fmaxf(r[e], 0.0f);
         }
-      uint16_t o8[8];
+        o[2 * q4] = bf16_pair(r[0], r[1]);
+        o[2 * q4 + 1] = bf16_pair(r[2], r[3]);
+      }
+      ((uint4*)(dst + 32 * fc))[0] = uint4{o[0], o[1], o[2], o[3]};
+      ((uint4*)(dst + 32 * fc))[1] = uint4{o[4], o[5], o[6], o[7]};
+    }
+  };
+  // MFMA results may be read by inline assembly some wait states after the last one
+  auto settle = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // the larger one of an odd column's sum and its left neighbour's (lane - 1; anything in lanes 0 and 32)
+  auto with_left = [&](float odd) __attribute__((always_inline)) {
+    float r;
+    asm("v_max_f32_dpp %0, %1, %1 wave_shr:1 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(odd));
+    return r;
+  };
+  auto max2 = [&](float u, float v) __attribute__((always_inline)) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(u), "v"(v));
+    return r;
+  };
+  auto max3 = [&](float u, float v, float w) __attribute__((always_inline)) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(u), "v"(v), "v"(w));
+    return r;
+  };
+
+  stem_f32x16 above[2];                          // the maxima of the row above the next pooled row's first own one
+  stem_f32x16 acc[2][2];
+  if constexpr (POOL) {
+    if (p0 > 0) {
+      row_sums(2 * p0 - 1, acc);
+      settle();
 #pragma unroll
-      for (int i = 0; i < 8; ++i) o8[i] = float_to_bf16(m[i]);
-      *(uint4*)(y + (((long long)img * pho + gy) * pwo + gx) * c_out + cb * kCb + c8 * 8) = *(const uint4*)o8;
+      for (int fc = 0; fc < 2; ++fc)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float even = acc[0][fc][i], odd = acc[1][fc][i];
+          above[fc][i] = max2(even, with_left(odd));
+        }
+    } else {
+#pragma unroll
+      for (int fc = 0; fc < 2; ++fc)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) above[fc][i] = -__builtin_inff();
     }
   }
-  }   // tiles of the row
+#pragma nounroll
+  for (int p = p0; p < p1; ++p) {
+    stem_i32x4 next[4];
+    const bool more = p + 1 < p1;
+    if (more) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) next[k] = load_piece(4 * p + 9 - a.pad + k);
+    }
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int r = 2 * p + half;
+      if (half == 1 && r >= a.ho) break;         // (the last pooled row of an odd height)
+      row_sums(r, acc);
+      if constexpr (POOL) {
+        settle();
+        const bool last = half == 1 || r + 1 >= a.ho;
+        stem_f32x16 here[2];
+#pragma unroll
+        for (int fc = 0; fc < 2; ++fc)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const float even = acc[0][fc][i], odd = acc[1][fc][i], up = above[fc][i];
+            if (half == 0) {
+              above[fc][i] = max3(up, even, with_left(odd));
+            } else {
+              const float m = max2(even, with_left(odd));
+              here[fc][i] = m;
+              above[fc][i] = max2(up, m);
+            }
+          }
+        if (last) {
+          if (mine) write(above, a.y + (((long long)img * a.oh + p) * a.ow + pc) * a.c_out + cb * kCb + 16 * lh);
+          if (half == 1) {
+#pragma unroll
+            for (int fc = 0; fc < 2; ++fc) above[fc] = here[fc];
+          }
+        }
+      } else {
+        uint16_t* dst = a.y + (((long long)img * a.ho + r) * a.wo + 2 * pc) * a.c_out + cb * kCb + 16 * lh;
+        if (mine) write(acc[0], dst);
+        if (mine && odd_in) write(acc[1], dst + a.c_out);
+      }
+    }
+    if (more) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) keep_piece(4 * p + 9 - a.pad + k, next[k]);
+      __syncthreads();
+    }
+  }
+}
+
+int launch_conv7x7s2c3(bool pool, const char* who, const void* x, const void* w, const float* scale, const float* shift,
+                       void* y, int n, int h, int wd, int c_out, int pad, int relu, hipStream_t s) {
+  StemArgs a{};
+  a.x = (const uint16_t*)x;
+  a.w = (const uint16_t*)w;
+  a.scale = scale;
+  a.shift = shift;
+  a.y = (uint16_t*)y;
+  a.h = h;
+  a.wd = wd;
+  a.c_out = c_out;
+  a.pad = pad;
+  a.relu = relu;
+  a.ho = (h + 2 * pad - 7) / 2 + 1;
+  a.wo = (wd + 2 * pad - 7) / 2 + 1;
+  a.oh = pool ? (a.ho - 1) / 2 + 1 : (a.ho + 1) / 2;
+  a.ow = pool ? (a.wo - 1) / 2 + 1 : (a.wo + 1) / 2;
+  const int frags = (a.ow + kStemCols - 1) / kStemCols;
+  a.cpf = (a.ow + frags - 1) / frags;
+  a.col_wgs = (frags + 1) / 2;
+  // Bands: a band computes one row more than it writes and lays out the weights anew, so long ones are better, as long as
+  // the chip is full: a compute unit holds four workgroups.
+  const long long per_row = (long long)n * a.col_wgs * (c_out / kCb), want = 4 * 256;
+  long long bands = (want + per_row - 1) / per_row;
+  if (bands > a.oh) bands = a.oh;
+  a.band = (int)((a.oh + bands - 1) / bands);
+  a.bands = (a.oh + a.band - 1) / a.band;
+  const long long blocks = (long long)n * a.bands * a.col_wgs;
+  if (blocks > 0x7fffffffll) return cg::set_error(CG_EUNSUPPORTED, "%s: too many tiles", who);
+  hipLaunchKernelGGL(pool ? conv7x7s2c3_kernel<true> : conv7x7s2c3_kernel<false>, dim3((unsigned)blocks, (unsigned)(c_out / kCb)),
+                     dim3(128), 0, s, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return cg::set_error(CG_EHIP, "%s: %s", who, hipGetErrorString(e));
+  return CG_OK;
 }
 
 // 1x1 convolution with stride (the ResNet shortcut) on the matrix cores: a GEMM of the strided
@@ -492,21 +677,8 @@ int cg_small_cin_conv(const void* x, const void* w, const float* scale, const fl
     return cg::set_error(CG_EINVAL, "cg_small_cin_conv: y, scale and shift must be 16-byte aligned");
   if (n == 0) return CG_OK;
   const int ho = (h + 2 * pad - k) / stride + 1, wo = (wd + 2 * pad - k) / stride + 1;
-  if (k == 7 && stride == 2 && c_in == 3) {      // the ImageNet input layer: the matrix-core kernel
-    // 16x16 tiles per block, along a row: a whole row of tiles (the weight layout is then done once
-    // per row) when that still leaves two blocks per CU
-    const int tiles_w16 = (wo + 15) / 16;
-    const long long rows16 = (long long)n * ((ho + 15) / 16) * (c_out / kCb);
-    const int tpb = rows16 >= 512 ? tiles_w16 : 1;
-    const long long t16 = (long long)n * ((ho + 15) / 16) * ((tiles_w16 + tpb - 1) / tpb);
-    if (t16 > 0x7fffffffll) return cg::set_error(CG_EUNSUPPORTED, "cg_small_cin_conv: too many tiles");
-    hipLaunchKernelGGL(conv7x7s2c3_mfma_kernel<false>, dim3((unsigned)t16, (unsigned)(c_out / kCb)), dim3(256), 0,
-                       (hipStream_t)hip_stream, (const uint16_t*)x, (const uint16_t*)w, scale, shift, (uint16_t*)y, n, h, wd,
-                       c_out, pad, ho, wo, relu, tpb);
-    const hipError_t e7 = hipGetLastError();
-    if (e7 != hipSuccess) return cg::set_error(CG_EHIP, "cg_small_cin_conv: %s", hipGetErrorString(e7));
-    return CG_OK;
-  }
+  if (k == 7 && stride == 2 && c_in == 3)        // the ImageNet input layer: the matrix-core kernel
+    return launch_conv7x7s2c3(false, "cg_small_cin_conv", x, w, scale, shift, y, n, h, wd, c_out, pad, relu, (hipStream_t)hip_stream);
   const long long tiles = (long long)n * ((ho + kTile - 1) / kTile) * ((wo + kTile - 1) / kTile);
   if (tiles > 0x7fffffffll) return cg::set_error(CG_EUNSUPPORTED, "cg_small_cin_conv: too many tiles");
   const int pe = (kTile - 1) * stride + k;
@@ -529,19 +701,7 @@ int cg_conv7x7s2_maxpool(const void* x, const void* w, const float* scale, const
   if ((((uintptr_t)y) | ((uintptr_t)scale) | ((uintptr_t)shift)) & 15)
     return cg::set_error(CG_EINVAL, "cg_conv7x7s2_maxpool: y, scale and shift must be 16-byte aligned");
   if (n == 0) return CG_OK;
-  const int ho = (h + 2 * pad - 7) / 2 + 1, wo = (wd + 2 * pad - 7) / 2 + 1;
-  const int pho = (ho - 1) / 2 + 1, pwo = (wo - 1) / 2 + 1;
-  const int tiles_w = (pwo + 6) / 7;
-  const long long rows = (long long)n * ((pho + 6) / 7) * (c_out / kCb);
-  const int tpb = rows >= 512 ? tiles_w : 1;
-  const long long blocks = (long long)n * ((pho + 6) / 7) * ((tiles_w + tpb - 1) / tpb);
-  if (blocks > 0x7fffffffll) return cg::set_error(CG_EUNSUPPORTED, "cg_conv7x7s2_maxpool: too many tiles");
-  hipLaunchKernelGGL(conv7x7s2c3_mfma_kernel<true>, dim3((unsigned)blocks, (unsigned)(c_out / kCb)), dim3(256), 0,
-                     (hipStream_t)hip_stream, (const uint16_t*)x, (const uint16_t*)w, scale, shift, (uint16_t*)y, n, h, wd,
-                     c_out, pad, ho, wo, relu, tpb);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return cg::set_error(CG_EHIP, "cg_conv7x7s2_maxpool: %s", hipGetErrorString(e));
-  return CG_OK;
+  return launch_conv7x7s2c3(true, "cg_conv7x7s2_maxpool", x, w, scale, shift, y, n, h, wd, c_out, pad, relu, (hipStream_t)hip_stream);
 }
 
 int cg_pointwise_conv(const void* x, const void* w, const float* scale, const float* shift, void* y, int32_t n,
