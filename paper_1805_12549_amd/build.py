@@ -14,7 +14,7 @@ ROOT = PKG.parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libcg_conv.so"
 
-SOURCES = ["cg_conv_api.hip", "kernels_naive.hip", "kernels_direct.hip", "kernels_mfma3.hip", "kernels_dense.hip",
+SOURCES = ["cg_conv_api.hip", "kernels_naive.hip", "kernels_direct.hip", "kernels_rows.hip", "kernels_counts.hip", "kernels_dense.hip",
            "kernels_tile.hip", "kernels_tile_bf16_k3.hip", "kernels_tile_bf16_k1.hip", "kernels_tile_i8_k3.hip",
            "kernels_tile_i8_k1.hip"]
 

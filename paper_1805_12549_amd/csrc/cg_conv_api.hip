@@ -77,7 +77,7 @@ enum Kernel { kNaive, kRows, kTile, kDirect };
 struct CallPlan {
   int n;
   Kernel kernel;
-  cg::Mfma3Plan rows;
+  cg::RowsPlan rows;
   cg::TilePlan tile;
   cg::DirectPlan direct;
 };
@@ -197,7 +197,7 @@ Layout make_layout(const cg_conv_desc& d, size_t wpk_base_bytes, size_t wpk_cond
 }
 
 struct Plans {
-  cg::Mfma3Plan v3;
+  cg::RowsPlan v3;
   cg::TilePlan v4;
   cg::DirectPlan vd;
   int variant;
@@ -221,7 +221,7 @@ int cu_count() {
 
 int resolve_variant(const cg_conv_desc& d, Plans* pl) {
   pl->v4 = cg::tile_plan(d, cu_count());
-  pl->v3 = cg::mfma3_plan(d, cu_count());
+  pl->v3 = cg::rows_plan(d, cu_count(), 0, 2);
   if (d.variant == CG_VARIANT_TILE && !pl->v4.ok)
     return fail(CG_EUNSUPPORTED, "the large-tile matrix-core kernel does not cover this shape/dtype");
   if (d.variant == CG_VARIANT_MFMA_ROWS && !pl->v3.ok)
@@ -242,10 +242,10 @@ int resolve_variant(const cg_conv_desc& d, Plans* pl) {
 void pick_kernel(const cg_conv* h, CallPlan* c) {
   c->kernel = h->variant == CG_VARIANT_MFMA_ROWS ? kRows : h->variant == CG_VARIANT_TILE ? kTile : kNaive;
   if (!h->direct_ok || !c->direct.ok) return;
-  // One round of tiles over the compute units (two where the tiled kernels start late: int8, 1x1) is where
-  // the small-tile kernel's time starts to grow; measured over one to 64 images of the ResNet-18 layers,
-  // e.g. 512 channels at 7x7 bf16: 10 against 22 us at one image, 17.5 / 24 at 16, 32 / 25 at 32.
-  const int rounds = h->d.in_dtype == CG_BF16 && h->d.kh == 3 ? 1 : 2;
+  // One round of tiles over the compute units (two for 1x1 layers) is where the small-tile kernel's time starts to
+  // grow; measured over one to 64 images of the ResNet-18 layers, e.g. 512 channels at 7x7, small-tile / row-tiled kernel:
+  // 15.3 / 19.1 us at eight images of bf16, 12.3 / 13.9 at eight of int8, 20.9 / 14.4 at 32 (two rounds).
+  const int rounds = h->d.kh == 3 ? 1 : 2;
   if (c->kernel == kNaive || c->direct.tiles <= rounds * cu_count()) c->kernel = kDirect;
 }
 
@@ -257,8 +257,8 @@ CallPlan plan_call(const cg_conv* h, int n) {
   cg_conv_desc dn = h->d;
   dn.n_max = n;
   if (h->variant == CG_VARIANT_MFMA_ROWS) {
-    const cg::Mfma3Plan q = cg::mfma3_plan(dn, cu_count());
-    if (q.ok && q.cps == c.rows.cps && q.grp_mode == c.rows.grp_mode && q.gsp == c.rows.gsp &&
+    const cg::RowsPlan q = cg::rows_plan(dn, cu_count(), c.rows.cps, 2);
+    if (q.ok && q.grp_mode == c.rows.grp_mode && q.gsp == c.rows.gsp &&
         q.stages[0] == c.rows.stages[0] && q.stages[1] == c.rows.stages[1])
       c.rows = q;
   } else if (h->variant == CG_VARIANT_TILE) {
@@ -305,6 +305,7 @@ cg::Params base_params(const cg_conv* h) {
   p.in_dtype = d.in_dtype;
   p.out_dtype = d.out_dtype;
   p.gated = h->c_cond > 0;
+  p.two_sided = d.delta_hi != nullptr;
   p.rq_shift = d.rq_shift;
   p.rq_res_mult = d.rq_res_mult;
   p.words = (d.c_out + 31) / 32;
@@ -418,7 +419,8 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
 
   // Host image of the per-channel tables.
   //   float path: 0 thr, 1 thr_hi, 2 sc0, 3 sh0, 4 sc1, 5 sh1
-  //   int path:   0 thr, 2 mult0, 3 mult1, 4 bias
+  //   int path:   0 thr, 2 mult0, 3 mult1, 4 bias; 5 and 6, of every 64 channels: (bias << shift) + half as 64-bit
+  //               words, 32 channels in table 5 and 32 in table 6
   const size_t tw = lay.table_stride / 4;
   try {
     h->staging.assign(tw * kTables, 0u);
@@ -435,6 +437,11 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
       t[2 * tw + c] = (uint32_t)(d.rq_mult0 ? d.rq_mult0[c] : 1);
       t[3 * tw + c] = (uint32_t)(d.rq_mult1 ? d.rq_mult1[c] : 1);
       t[4 * tw + c] = (uint32_t)(d.rq_bias ? d.rq_bias[c] : 0);
+      const uint64_t add = (uint64_t)((long long)(d.rq_bias ? d.rq_bias[c] : 0) * (1ll << d.rq_shift) +
+                                      (d.rq_shift > 0 ? 1ll << (d.rq_shift - 1) : 0ll));
+      uint32_t* pair = t + (5 + c % 64 / 32) * tw + c / 64 * 64 + 2 * (c % 32);
+      pair[0] = (uint32_t)add;
+      pair[1] = (uint32_t)(add >> 32);
     } else {
       float lo = -inf, hi = inf;
       if (gated) {
@@ -471,7 +478,7 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   if (e == hipSuccess && variant == CG_VARIANT_TILE)
     e = cg::launch_tile_pack(pl.v4, h->base, pk + lay.wpk_base_off, pk + lay.wpk_cond_off, s);
   if (e == hipSuccess && variant == CG_VARIANT_MFMA_ROWS)
-    e = cg::launch_mfma3_pack(pl.v3, h->base, pk + lay.wpk_base_off, pk + lay.wpk_cond_off, s);
+    e = cg::launch_rows_pack(pl.v3, h->base, pk + lay.wpk_base_off, pk + lay.wpk_cond_off, s);
   if (e == hipSuccess && pl.direct_ok)
     e = cg::launch_direct_pack(pl.vd, h->base, pk + lay.wpd_base_off, pk + lay.wpd_cond_off, s);
   if (e != hipSuccess) {
@@ -621,11 +628,21 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
   p.clear_total = counts && clear_total;
 
   if (cp.kernel == kDirect && !aligned) cp.kernel = kNaive;      // (only where the plain kernel is the layer's family)
+  if (cp.kernel == kRows && cp.rows.pf == 2 && residual) {
+    // Two fragments per wavefront write an output twice and read the residual after the first time.
+    const char *y0 = (const char*)y, *r0 = (const char*)residual;
+    const size_t len = (size_t)p.m_total * d.c_out * 2;
+    if (y0 < r0 + len && r0 < y0 + len) {
+      cg_conv_desc dn = d;
+      dn.n_max = n;
+      cp.rows = cg::rows_plan(dn, cu_count(), cp.rows.cps, 1);
+    }
+  }
   hipStream_t s = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
   auto launch = [&](const cg::Params& q) -> hipError_t {
     switch (cp.kernel) {
-      case kRows: return cg::launch_mfma3(cp.rows, q, pk + l.wpk_base_off, pk + l.wpk_cond_off, s);
+      case kRows: return cg::launch_rows(cp.rows, q, pk + l.wpk_base_off, pk + l.wpk_cond_off, s);
       case kTile: return cg::launch_tile(cp.tile, q, pk + l.wpk_base_off, pk + l.wpk_cond_off, s);
       case kDirect: return cg::launch_direct(cp.direct, q, pk + l.wpd_base_off, pk + l.wpd_cond_off, ws + wl.partial_off, s);
       default: return cg::launch_naive(q, s);

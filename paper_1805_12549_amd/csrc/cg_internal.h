@@ -18,6 +18,7 @@ struct Params {
   long long m_total;       // n*ho*wo
   unsigned epilogue;
   int in_dtype, out_dtype;
+  int two_sided;           // an upper gate threshold was given
   int gated;               // 0: dense layer, no gate, second affine pair applies
   int rq_shift, rq_res_mult;
   int words;               // bitmap words per pixel = ceil(c_out/32)
@@ -70,7 +71,7 @@ struct TilePlan {
   int pr;                  // patch rows, maximum over tiles
   int n16;                 // 16-byte positions of a stage's patch = pr * pitch * cps
   int xcd_cb;              // 1: blocks of one channel block share an XCD; 0: blocks of one tile do
-  int grp_mode, gsp;       // channel grouping, as in Mfma3Plan
+  int grp_mode, gsp;       // channel grouping, as in RowsPlan
   int stages[2];           // stages of the base / conditional phase
   int nb;                  // stage buffers in LDS (the loads run nb - 1 stages ahead)
   size_t lds_bytes;        // LDS of the kernel instantiation
@@ -101,43 +102,6 @@ hipError_t launch_tile_i8_k3(const TilePlan& g, const TileGeo& q, const Params& 
 hipError_t launch_tile_i8_k1(const TilePlan& g, const TileGeo& q, const Params& p, const void* w0, const void* w1,
                              hipStream_t s);
 
-// Geometry of the row-tiled matrix-core kernel (32x32 MFMA blocks, transposed product).
-//
-// Tiles are `tr` consecutive global output rows x 64 channels as above.  K is walked in super-stages
-// of `cps` 16-byte channel chunks per pixel; the LDS patch of a super-stage holds 16*cps bytes per
-// pixel slot, slot = patch_row * 2^logp + (wi + pad).
-struct Mfma3Plan {
-  int ok;
-  int elem_bytes, ch;      // bytes per element; channels per 16-byte chunk
-  int nwv;                 // wavefronts per workgroup: 4, or 8 for the 256-pixel tile
-  int nf;                  // 32-pixel fragments per wavefront in the base phase
-  int nc;                  // 32-channel fragments per wavefront: 2, or 1 when two wavefronts share a pixel fragment
-  int ldw;                 // wavefronts (of nwv) that only issue the LDS-direct loads: 0 or 4
-  int xcd_cb;              // 1: blocks of one channel block share an XCD (needs n_cb % 8 == 0); 0: blocks of one tile do
-  int bm;                  // 32*nf*nwv*nc/2 pixels per tile, padded
-  int n_cb;                // c_out / 64
-  int tr;                  // global output rows per tile
-  int hp;                  // h + 2*pad
-  unsigned magic_hp, magic_ho, magic_wo;
-  int logp;                // log2 of the patch row pitch in pixel slots (pitch >= 16, > w + pad - 1)
-  int pr;                  // patch rows, maximum over tiles
-  int cps;                 // chunks per pixel per super-stage: 4 or 2
-  int ni;                  // 1 KB load instructions per super-stage patch = ceil(pr * pitch * cps / 64)
-  int pkb;                 // LDS patch buffer class: 24 KB (two workgroups per CU) or 48 KB
-  // Channel grouping.  0: none.  1: a 64-channel block lies inside one output group; its base
-  // channels start at group*c_base and the conditional phase skips them.  2: a block covers
-  // `gsp` whole groups; its base phase walks the gsp*c_base base channels of all of them and its
-  // conditional phase all c_in channels, the packed weights holding zeros where a channel is not on
-  // that path for that output channel.
-  int grp_mode, gsp;
-  // set by the launcher for the call's grid: ceil(tiles / 8); the divisor that splits a block slot into
-  // (tile, channel block) and its multiplier (0: divide)
-  int tiles8, div_d;
-  unsigned div_magic;
-  int stages[2];           // super-stages of the base / conditional phase
-  size_t wpk_base_bytes, wpk_cond_bytes;
-};
-
 // Geometry of the small-tile matrix-core kernel (kernels_direct.hip): 16*pf output pixels x 32*cg
 // channels per tile, operands straight from global memory.
 struct DirectPlan {
@@ -167,10 +131,40 @@ hipError_t launch_direct_pack(const DirectPlan& plan, const Params& p, void* wpk
 hipError_t launch_direct(const DirectPlan& plan, const Params& p, const void* wpk_base, const void* wpk_cond, void* partial,
                          hipStream_t s);
 
-Mfma3Plan mfma3_plan(const cg_conv_desc& d, int n_cu);
-hipError_t launch_mfma3_pack(const Mfma3Plan& plan, const Params& p, void* wpk_base, void* wpk_cond, hipStream_t s);
-hipError_t launch_mfma3(const Mfma3Plan& plan, const Params& p, const void* wpk_base, const void* wpk_cond,
-                        hipStream_t s);
+// Geometry of the row-tiled matrix-core kernel (kernels_rows.hip): persistent workgroups of 64 output channels
+// that walk runs of output rows in tiles of at most 256 pixels; K in stages of `cps` 16-byte channel chunks
+// per pixel times nine taps; the LDS patch of a stage holds 16*cps bytes per pixel slot,
+// slot = patch_row * 2^logp + (wi + pad).
+struct RowsPlan {
+  int ok;
+  int elem_bytes, ch;      // bytes per element; channels per 16-byte chunk
+  int cps;                 // chunks per pixel per stage: 4 or 2
+  int stages[2];           // stages of the base / conditional phase
+  // Channel grouping.  0: none.  1: a 64-channel block lies inside one output group; its base
+  // channels start at group*c_base and the conditional phase skips them.  2: a block covers
+  // `gsp` whole groups; its base phase walks the gsp*c_base base channels of all of them and its
+  // conditional phase all c_in channels, the packed weights holding zeros where a channel is not on
+  // that path for that output channel.
+  int grp_mode, gsp;
+  int n_cb;                // c_out / 64
+  int n_slots;             // workgroups per channel block: the batch's rows are split evenly over them
+  int xcd_cb;              // 1: workgroups of one channel block share an XCD (needs n_cb % 8 == 0)
+  int hp;                  // h + 2*pad
+  int tr;                  // output rows per tile
+  int logp, pr, n_pl;      // log2 of the patch row pitch; patch rows, maximum over tiles; 1 KB loads per patch
+  int resident, nb;        // 1: all weights stay in LDS; stage buffers
+  int psz, pstr;           // bytes per patch; bytes between stage buffers
+  int pf;                  // fragments per wavefront: 1 or 2
+  int fwl, nfc;            // fragment of a wavefront: 2^fwl columns (-1: 32 pixels in a row), fragments per row group
+  int wres, shuf, shuf_bytes, tabs, lds_bytes;   // LDS offsets of resident weights (-1: none), shuffled rows, tables
+  size_t wpk_base_bytes, wpk_cond_bytes;
+};
+
+// cps: 0 = pick, 4 or 2 = that (for a handle whose weights are packed); max_pf: the most fragments per wavefront
+RowsPlan rows_plan(const cg_conv_desc& d, int n_cu, int cps, int max_pf);
+hipError_t launch_rows_pack(const RowsPlan& plan, const Params& p, void* wpk_base, void* wpk_cond, hipStream_t s);
+hipError_t launch_rows(const RowsPlan& plan, const Params& p, const void* wpk_base, const void* wpk_cond,
+                         hipStream_t s);
 // per-(image, channel) fired counts and their total (into p.counts / p.total) from a decision bitmap
 hipError_t launch_bitmap_counts(const Params& p, const uint32_t* bitmap, hipStream_t s);
 // channel-wise gate: mask[img][w] bit b = (fired count of channel 32*w + b in image img, from the bitmap) >= need

@@ -1,0 +1,1191 @@
+// Row-tiled matrix-core kernel of the gated convolution (bf16 and int8 MFMA, 32x32 blocks): persistent
+// workgroups whose wavefronts run free of each other, loads issued by wavefronts of their own.
+//
+// A workgroup of twelve wavefronts is alone on its compute unit and owns one block of 64 output
+// channels and a run of consecutive output rows of the batch (rows numbered R = img*Ho + ho), which it
+// walks in tiles of up to 256 pixels (whole rows, possibly straddling images).  K is walked in stages
+// of CPS 16-byte channel chunks x nine taps; a stage's input patch and its weights sit in one of NB
+// LDS buffers.  The sequence of stages runs through all tiles of the workgroup without a break.
+//
+//   loaders     wavefronts 8..11 issue every LDS-direct load and publish what has landed in LDS counters; the
+//               eight multiplying wavefronts publish what they are done with.  There is no barrier: a wavefront
+//               that has nothing to multiply in a stage (no gate of its pixels fired, no pixels in the tile's
+//               ragged end) passes it by, and one that writes its output does not hold up the others, so
+//               one wavefront's gate and output instructions run under another's matrix instructions.
+//               Where all stages' weights fit into LDS together (64 channels) they stay there and only the
+//               patches stream.
+//   base path   implicit GEMM over taps x base channels; a wavefront multiplies a fragment of 32 pixels of the
+//               tile (FH rows x 32/FH columns, or 32 in a row) by the 64 channels.  The product is taken
+//               transposed (weights are the row operand, their rows permuted), which leaves a lane with 16
+//               consecutive channels of one pixel per accumulator: gate and output work on registers.
+//   gate        accumulators against the per-channel thresholds (merged gate, Sec. 3.2 of the
+//               channel-gating paper); decision words leave straight from registers.
+//   cond. path  a wavefront with a fired gate adds the conditional channels on top of a copy of its base sums and
+//               picks per channel (Eq. 1).  The granule of skipping is the wavefront's fragment; a compact shape
+//               of it (4x8 pixels) is what keeps it close to the fired area: with clustered maps at a firing rate
+//               of 0.3, 0.64 of the 4x8 fragments of 56x56 maps hold a fired pixel, 0.90 of runs of 32.
+//               (Listing the fired pixels of a tile and dealing them out 32 at a time issues 0.42, but
+//               needs every wavefront at the gate at once, an exchange of sums and a second output pass; it measured
+//               1.3 to 2 times slower than this form at 64 channels and no faster at 256 and 512.)
+//   output      scale/shift by decision, residual, ReLU, convert (Eq. 1), stored from registers.
+//
+// PF = 2 (bf16 layers with many channels and pixels): a wavefront takes two fragments and reads a stage's weights from LDS once for
+// both, which is what bounds the loop there (one fragment: 3 KB of LDS reads for two products, i.e. 192 of 128 clocks).
+// Its registers do not hold two sets of sums per fragment; the outputs for an unfired gate are written first and
+// corrected where a gate fired.
+//
+// What bounds the kernel: at 64 and 128 channels the instructions of gate and output (a third of a wavefront's time each
+// side of the products), at 256 and 512 the LDS reads and, for few images, the start (arguments, tables and the first
+// stage: 2 us of 8 to 13).  Measured in a graph, before (barrier-coupled workgroups with the pixels listed anew for the
+// conditional path) and now, us:
+//   bf16  64 channels at 56x56, 64 images 31 -> 27, 256: 93 -> 79;  256 at 14x14, 8 images 14.7 -> 13.3, 256: 58.8 -> 59;
+//         512 at 7x7, 8: 23.8 -> 19.1, 256: 68 -> 62;  128>256 at 28x28 stride 2, 64: 19.3 -> 16.8, 256: 69 -> 53
+//   int8  128 at 28x28, 32 images 18.0 -> 11.6, 256: 70 -> 53;  512 at 7x7, 8: 20.9 -> 13.9, 256: 52 -> 39
+//
+// A patch is stored [pixel slot][CPS chunk positions]; chunk q of slot s sits at position q ^ f(s),
+// f(s) = (s >> 2) & 3 (CPS = 4) or (s >> 3) & 1 (CPS = 2), which spreads the operand reads over the LDS
+// banks.  Slot = patch_row * P + c with P a power of two >= max(16, W + pad) and c = wi + pad;
+// positions outside the image are out-of-range buffer loads, which write zeros.
+//
+// The vector-memory path serves a cache line every two clocks, whatever part of it is asked for (measured: 17, 35
+// and 65 bytes a clock in pieces of 32, 64 and 128+), which is why outputs are transposed between lanes before
+// they are stored and why stages of four chunks are preferred where the channel counts allow.
+#include <type_traits>
+#include <utility>
+
+#include "cg_mfma_common.h"
+
+namespace cg {
+
+namespace {
+
+constexpr int kBn = 64;                      // output channels per workgroup
+constexpr int kCw = 8;                       // wavefronts that multiply
+constexpr int kLw = 4;                       // wavefronts that load
+constexpr int kNt = 64 * (kCw + kLw);
+constexpr int kTabs = 8;                     // per-channel tables of `packed`
+constexpr int kTabBytes = kTabs * 256 + 64;  // ... of the block's 64 channels; progress counters
+constexpr int kShufRow = 144;                // bytes of a pixel's row in the shuffled store's LDS tile (128 + skew)
+constexpr int kLds = 160 * 1024;
+constexpr int kMaxPatchLoads = 12;           // 1 KB load instructions per loading wavefront and patch
+
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(16))) int i32x16;
+
+// 32x32 output block; lane l supplies row / column l%32 and the 16-byte K chunk l/32 of either
+// operand; it receives column l%32, rows 8*(i/4) + 4*(l/32) + i%4 in register i.
+struct Bf16Rows {
+  using Base = Bf16Traits;
+  using acc16 = f32x16;
+  using acc_t = float;
+  static __device__ __forceinline__ acc16 mfma(i32x4 rows, i32x4 cols, acc16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, rows), __builtin_bit_cast(bf16x8, cols),
+                                                   c, 0, 0, 0);
+  }
+  // d = 2*d + (v >= t)
+  static __device__ __forceinline__ void shift_in(unsigned& d, float v, int t) {
+    asm("v_cmp_ge_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(d) : "v"(v), "v"(t) : "vcc");
+  }
+};
+
+struct I8Rows {
+  using Base = I8Traits;
+  using acc16 = i32x16;
+  using acc_t = int32_t;
+  static __device__ __forceinline__ acc16 mfma(i32x4 rows, i32x4 cols, acc16 c) {
+    return __builtin_amdgcn_mfma_i32_32x32x32_i8(rows, cols, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ void shift_in(unsigned& d, int v, int t) {
+    asm("v_cmp_ge_i32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(d) : "v"(v), "v"(t) : "vcc");
+  }
+};
+
+__device__ __forceinline__ int as_bits(float f) { return __float_as_int(f); }
+__device__ __forceinline__ int as_bits(int v) { return v; }
+__device__ __forceinline__ void from_bits(int b, float& f) { f = __int_as_float(b); }
+__device__ __forceinline__ void from_bits(int b, int& v) { v = b; }
+
+// exact x / d for x, d < 65536 with magic = ceil(2^32 / d); magic 0 stands for d = 1 (2^32 does not fit)
+__device__ __forceinline__ int div16(int x, unsigned magic) { return magic ? (int)__umulhi((unsigned)x, magic) : x; }
+
+// 16-byte LDS read with a compile-time byte offset; the caller waits (lgkmcnt) before using the value
+template <int OFS>
+__device__ __forceinline__ i32x4 lds_read16(unsigned addr) {
+  static_assert(OFS >= 0 && OFS < 65536, "16-bit offset field");
+  i32x4 v;
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFS) : "memory");
+  return v;
+}
+
+// s_waitcnt vmcnt(n) for any LO <= n: the largest multiple of two below HI that is not above it (fewer in flight is safe)
+#define CG_VMCNT(n) (0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
+template <int LO, int HI>
+__device__ __forceinline__ void wait_vm(int n) {
+  if constexpr (HI - LO <= 2) {
+    __builtin_amdgcn_s_waitcnt(CG_VMCNT(LO));
+  } else {
+    constexpr int MID = LO + (HI - LO) / 4 * 2;
+    if (n >= MID)
+      wait_vm<MID, HI>(n);
+    else
+      wait_vm<LO, MID>(n);
+  }
+}
+
+// the larger one (fmaxf of values that are no signalling NaNs, without the instruction that would quiet those)
+__device__ __forceinline__ float max_of(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+// two floats as bf16 (round to nearest even), a in the low half
+__device__ __forceinline__ int bf16_pair(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(int, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+
+__device__ __forceinline__ int med3(int v, int lo, int hi) {
+  int r;
+  asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "v"(lo), "v"(hi));
+  return r;
+}
+
+// byte offset of chunk position (h ^ f(slot)) of pixel slot `slot`
+template <int CPS>
+__device__ __forceinline__ int slot_addr(int slot, int h) {
+  if constexpr (CPS == 4) return slot * 64 + ((h ^ (slot >> 2)) & 3) * 16;
+  return slot * 32 + ((h ^ (slot >> 3)) & 1) * 16;
+}
+
+// 4x4 transpose of 16-byte pieces over the four 16-lane groups of a wavefront: piece g of group j <-> piece j of group g
+__device__ __forceinline__ void transpose4(i32x4 (&v)[4]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v[j][e], (unsigned)v[j + 2][e], false, false);
+      v[j][e] = (int)r[0];
+      v[j + 2][e] = (int)r[1];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; j += 2) {
+      const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v[j][e], (unsigned)v[j + 1][e], false, false);
+      v[j][e] = (int)r[0];
+      v[j + 1][e] = (int)r[1];
+    }
+  }
+}
+
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(std::make_integer_sequence<int, N>{}, static_cast<F&&>(f));
+}
+
+__device__ __forceinline__ void wait_lds() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);        // lgkmcnt(0)
+  asm volatile("" ::: "memory");
+}
+
+// barrier without the drain of every memory operation that __syncthreads() implies
+__device__ __forceinline__ void bare_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// Waits until each of the N progress counters at LDS address `addr` is at least `need`; `have` caches their
+// minimum.  (Every counter is advanced by a wavefront that never waits for this one's next step; the bound on the
+// polls only turns a mistake into a wrong result instead of a hang.)
+template <int N>
+__device__ __forceinline__ void wait_counters(unsigned addr, int lane, int need, int& have) {
+  if (have >= need) return;
+  for (int spin = 0; spin < (1 << 22); ++spin) {
+    int v;
+    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(addr + (lane < N ? lane : 0) * 4) : "memory");
+    have = __builtin_amdgcn_readlane(v, 0);
+#pragma unroll
+    for (int i = 1; i < N; ++i) {
+      const int w = __builtin_amdgcn_readlane(v, i);
+      have = w < have ? w : have;
+    }
+    have = __builtin_amdgcn_readfirstlane(have);
+    if (have >= need) return;
+    __builtin_amdgcn_s_sleep(1);
+  }
+}
+
+// what is the same for the whole grid; the kernel reads each group with a few scalar loads, issued together
+struct RowsArgs {
+  // every wavefront
+  unsigned flags;                            // kGated ...
+  unsigned magic_ncb, magic_ho;
+  int n_cb, n_slots, xcd_cb, per_xcd;
+  int full, rows_per, rows_more;             // whole rounds of tiles; rows per workgroup after them (the first rows_more: one more)
+  int tr, logp;                              // rows per tile, patch pitch
+  int s0, s, nb, pstr, psz, wres, tabs;      // stages; buffers and LDS offsets (wres < 0: weights are in the ring)
+  int ho, hp, stride, tab_stride;
+  uint32_t* clear;                           // two words that the grid clears, or NULL
+  // loading wavefronts
+  const char* x;
+  const char *w0, *w1;
+  const char* tab;
+  unsigned magic_hp, x_bytes;
+  int n, h, w, pad, xps, pr, n_pl;           // patch rows, 1 KB patch loads
+  int base_chn, gap_chn, grp_mode, grp_step; // channel walk
+  // multiplying wavefronts
+  int fwl, nfc;                              // log2 columns of a fragment and fragments per row group; fwl < 0: 32 in a row
+  unsigned magic_wo, magic_nfc;
+  char* y;
+  const char* residual;
+  uint32_t* bitmap;
+  const uint32_t* chan_mask;
+  int wo, words, c_out, rq_shift, rq_res_mult, shuf, cpg, groups;
+};
+enum : unsigned {
+  kGated = 1u, kGateOnly = 2u, kTwoSided = 4u, kAffine = 8u, kRelu = 16u, kResidual = 32u,
+  kFast = 64u,                               // 2-byte (int8 layers: 1-byte) outputs in natural channel order
+  kShuf2 = 128u,                             // 2-byte outputs in shuffled channel order
+};
+
+constexpr int kParamsAt = (sizeof(RowsArgs) + alignof(Params) - 1) / alignof(Params) * alignof(Params);   // of the kernel's arguments
+
+template <typename Tr, int CPS, int PF>
+__global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params) {
+  using acc16 = typename Tr::acc16;
+  using acc_t = typename Tr::acc_t;
+  using Base = typename Tr::Base;
+  constexpr int KS = 9 * CPS / 2;              // K steps per stage
+  constexpr int PAIRS = CPS / 2;
+  constexpr int WB = KS * 2048;                // bytes of a stage's weights
+  constexpr int NWL = WB / 1024 / kLw;         // weight load instructions per loading wavefront (CPS = 2: one more for some)
+  constexpr int SB = 16 * CPS;                 // bytes per pixel slot
+  extern __shared__ __align__(1024) char lds[];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lj = lane & 31, lh = lane >> 5;
+  asm volatile("" ::"s"(a.flags), "s"(a.magic_ncb), "s"(a.magic_ho), "s"(a.n_cb), "s"(a.n_slots), "s"(a.xcd_cb), "s"(a.per_xcd),
+               "s"(a.full), "s"(a.rows_per), "s"(a.rows_more), "s"(a.tr), "s"(a.logp), "s"(a.s0), "s"(a.s), "s"(a.nb), "s"(a.pstr),
+               "s"(a.psz), "s"(a.wres), "s"(a.tabs), "s"(a.ho), "s"(a.hp), "s"(a.stride), "s"(a.tab_stride), "s"(a.clear));
+
+  // Block id mod 8 is the XCD.  Normally an XCD takes a contiguous run of rows with all channel blocks, so that a
+  // row is fetched into one L2 once; xcd_cb: the workgroups of a channel block sit on one XCD instead, so that each
+  // L2 holds an eighth of the weights (layers whose weights outweigh their input).
+  int slot, cbk;
+  {
+    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+    if (a.xcd_cb) {
+      const int ncb8 = a.n_cb >> 3;
+      slot = j / ncb8;
+      cbk = (j - slot * ncb8) * 8 + xcd;
+    } else {
+      const int rank = xcd * a.per_xcd + j;
+      slot = div16(rank, a.magic_ncb);
+      cbk = rank - slot * a.n_cb;
+    }
+  }
+  if (slot >= a.n_slots) return;
+  if (a.clear && blockIdx.x == 0 && tid < 2) a.clear[tid] = 0u;
+  // The workgroup's tiles: number slot, slot + n_slots, ... of the batch's tiles of tr rows (neighbours in time on an
+  // XCD are neighbours in the batch; one workgroup's tiles come from different images, whose shares of fired
+  // pixels differ), then an even share of the rows that do not make a whole round.
+  const int tail_a = a.full * a.n_slots * a.tr + slot * a.rows_per + (slot < a.rows_more ? slot : a.rows_more);
+  const int tail_rows = a.rows_per + (slot < a.rows_more ? 1 : 0);
+  const int tiles = a.full + (tail_rows > 0 ? 1 : 0);
+  auto tile_row = [&](int t) __attribute__((always_inline)) { return t < a.full ? (t * a.n_slots + slot) * a.tr : tail_a; };
+  const bool gated = (a.flags & kGated) != 0, gate_only = (a.flags & kGateOnly) != 0;
+  const unsigned lds0 = (unsigned)(uintptr_t)lds;
+  // progress counters: stages landed per loading wavefront, stages done with per multiplying wavefront
+  const unsigned landed = lds0 + a.tabs + kTabs * 256, done = landed + 4 * kLw;
+  auto publish = [&](unsigned addr, int value) __attribute__((always_inline)) {
+    if (lane == 0) asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(value) : "memory");
+  };
+  if (tid < kLw + kCw) *(int*)(lds + a.tabs + kTabs * 256 + tid * 4) = 0;
+
+  if (wave >= kCw) {
+    // ================================ loading wavefronts ============================================
+    // They share their SIMDs with the multiplying wavefronts and every instruction between two loads counts: buffer
+    // loads with a scalar offset (no address arithmetic, padding by the range check), positions formed once per tile.
+    __builtin_amdgcn_s_setprio(3);
+    asm volatile("" ::"s"(a.x), "s"(a.w0), "s"(a.w1), "s"(a.tab), "s"(a.magic_hp), "s"(a.x_bytes), "s"(a.n), "s"(a.h), "s"(a.w),
+                 "s"(a.pad), "s"(a.xps), "s"(a.pr), "s"(a.n_pl), "s"(a.base_chn), "s"(a.gap_chn), "s"(a.grp_mode), "s"(a.grp_step));
+    const int lw = wave - kCw;
+    const int V = tiles * a.s;
+    auto rsrc = [](const void* ptr, unsigned bytes) __attribute__((always_inline)) {
+      const unsigned long long q = (unsigned long long)ptr;
+      return i32x4{(int)q, (int)(q >> 32) & 0xffff, (int)bytes, 0x00027000};
+    };
+    const i32x4 xr = rsrc(a.x, a.x_bytes);
+    const i32x4 wr0 = rsrc(a.w0 + (size_t)cbk * a.s0 * WB, a.s0 * WB);
+    const i32x4 wr1 = rsrc(a.w1 + (size_t)cbk * (a.s - a.s0) * WB, (a.s - a.s0) * WB);
+    auto dma = [&](i32x4 r, int voff, int soff, unsigned dst) __attribute__((always_inline)) {
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(voff), "s"(r), "s"(soff) : "memory");
+    };
+    // the block's tables, four to a load; they land before its first stage does
+    if (lw == 0) {
+#pragma unroll
+      for (int k = 0; k < kTabs / 4; ++k)
+        dma(rsrc(a.tab, kTabs * a.tab_stride), (4 * k + (lane >> 4)) * a.tab_stride + (lane & 15) * 16, cbk * kBn * 4,
+            lds0 + a.tabs + k * 1024);
+    }
+    // byte offset of the channel of x at which stage s starts: the base phase starts at this block's first base channel;
+    // the conditional phase walks the channels in order and jumps over the base channels (without grouping these are
+    // the first c_base; with grouping, Sec. 3.3, those of the block's own group, or none when the block covers
+    // several groups and the packed weights carry zeros instead).
+    const int b0 = a.grp_mode ? (cbk * kBn / a.grp_step) * a.base_chn : 0;
+    // A position of the patch (16 bytes of a pixel) is load lw + 4k, lane `lane`; its row of the patch and its offset
+    // inside an image row do not depend on the tile.  kOut: past the end of any x (the plan keeps x below 2 GiB).
+    constexpr int kOut = (int)0x80000000;
+    int vcol[kMaxPatchLoads], voff[kMaxPatchLoads];
+    int np = 0;                              // patch loads of this wavefront
+#pragma unroll
+    for (int k = 0; k < kMaxPatchLoads; ++k) {
+      voff[k] = vcol[k] = kOut;
+      if (lw + kLw * k < a.n_pl) {
+        ++np;
+        const int pos = (lw + kLw * k) * 64 + lane;
+        const int sl = pos / CPS, cp = pos % CPS;
+        const int f = CPS == 4 ? (sl >> 2) & 3 : (sl >> 3) & 1;
+        const int wi = (sl & ((1 << a.logp) - 1)) - a.pad;
+        if ((unsigned)wi < (unsigned)a.w && (sl >> a.logp) < a.pr) vcol[k] = wi * a.xps + (cp ^ f) * 16;
+      }
+    }
+    const int rowx = a.w * a.xps;            // bytes per image row
+    // positions of this wavefront's patch loads for the tile that starts at row R0
+    auto tile_setup = [&](int R0) __attribute__((always_inline)) {
+      const int img0 = div16(R0, a.magic_ho);
+      const int rho0 = img0 * a.hp + (R0 - img0 * a.ho) * a.stride;     // stacked padded input row of patch row 0
+#pragma unroll
+      for (int k = 0; k < kMaxPatchLoads; ++k) {
+        if (k >= np) break;
+        const int rho = rho0 + ((((lw + kLw * k) * 64 + lane) / CPS) >> a.logp);
+        const int img = div16(rho, a.magic_hp);
+        const int hi = rho - img * a.hp - a.pad;
+        voff[k] = img < a.n && (unsigned)hi < (unsigned)a.h && vcol[k] != kOut ? (img * a.h + hi) * rowx + vcol[k] : kOut;
+      }
+    };
+    const int nwl = NWL + (lw < (WB / 1024) % kLw ? 1 : 0);       // weight loads of this wavefront per stage
+    const int lane16 = lane * 16 + lw * 1024;
+    int is = 0, ib = 0, iv = 0, itile = 0;   // the next stage to issue: stage of its tile, buffer, number
+    auto issue = [&]() __attribute__((always_inline)) {
+      const unsigned buf = lds0 + ib * a.pstr + lw * 1024;
+      if (is == 0) tile_setup(tile_row(itile));
+      if (a.wres < 0 || iv < a.s) {
+        const unsigned wd = a.wres < 0 ? buf + a.psz : lds0 + a.wres + is * WB + lw * 1024;
+        const i32x4 r = is < a.s0 ? wr0 : wr1;
+        const int so = (is < a.s0 ? is : is - a.s0) * WB;
+#pragma unroll
+        for (int k = 0; k < NWL; ++k) dma(r, lane16, so + k * (kLw * 1024), wd + k * (kLw * 1024));
+        if (nwl > NWL) dma(r, lane16, so + NWL * (kLw * 1024), wd + NWL * (kLw * 1024));
+      }
+      int c = is < a.s0 ? b0 + is * SB : (is - a.s0) * SB;
+      if (is >= a.s0 && c >= b0) c += a.gap_chn;
+#pragma unroll
+      for (int k = 0; k < kMaxPatchLoads; ++k) {
+        if (k >= np) break;
+        dma(xr, voff[k], c, buf + k * (kLw * 1024));
+      }
+      ++iv;
+      if (++is == a.s) {
+        is = 0;
+        ++itile;
+      }
+      if (++ib == a.nb) ib = 0;
+    };
+    auto n_loads = [&](int v) { return np + (a.wres < 0 || v < a.s ? nwl : 0); };
+    int out = 0;                             // stages published as landed
+    auto land = [&]() __attribute__((always_inline)) {
+      // stage `out` has landed once only the loads of the stages issued after it are in flight
+      int fly = 0;
+      for (int v = out + 1; v < iv; ++v) fly += n_loads(v);
+      wait_vm<0, 62>(fly);
+      ++out;
+      publish(landed + 4 * lw, out);
+    };
+    issue();
+    bare_barrier();                          // the counters are set up
+    int free_to = 0;
+    while (iv < V) {
+      // the buffer of stage iv is free when every multiplying wavefront is done with stage iv - nb
+      while (free_to < iv - a.nb + 1 && out < iv) {
+        land();
+        if (out < iv) {
+          int v;
+          asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(done + (lane < kCw ? lane : 0) * 4) : "memory");
+          if (__ballot(v < iv - a.nb + 1) == 0ull) free_to = iv - a.nb + 1;
+        }
+      }
+      wait_counters<kCw>(done, lane, iv - a.nb + 1, free_to);
+      issue();
+      if (iv - out > 2) land();
+    }
+    while (out < V) land();
+    return;
+  }
+
+  // ================================ multiplying wavefronts ==========================================
+  asm volatile("" ::"s"(a.fwl), "s"(a.nfc), "s"(a.magic_wo), "s"(a.magic_nfc), "s"(a.y), "s"(a.residual), "s"(a.bitmap),
+               "s"(a.chan_mask), "s"(a.wo), "s"(a.words), "s"(a.c_out), "s"(a.rq_shift), "s"(a.rq_res_mult));
+  acc_t* const tlo = (acc_t*)(lds + a.tabs);         // [64] thresholds, lower and upper
+  acc_t* const thi = tlo + 64;
+  float* const aff = (float*)(thi + 64);             // [4][64] scale0, shift0, scale1, shift1; int8: mult0, mult1
+  long long* const addends = (long long*)(aff + 192);// int8: what is added before the shift
+  bare_barrier();                                    // the counters are set up
+  const int rowb = SB << a.logp;                     // bytes per patch row
+  const unsigned wlane = lh * 1024 + lj * 16;        // lane's offset of its weight rows in a K step
+  acc16 accP[PF][2], accS[PF][2];                    // base sums; base and conditional sums (PF = 2: accP holds these too)
+
+  // One stage: the operand reads of K steps k+1 and k+2 are in flight while step k is multiplied.
+  auto mma_stage = [&](auto f0c, auto nfc_, unsigned pat, unsigned wgt, const int (&pa)[PF][3], acc16 (&acc)[PF][2])
+      __attribute__((always_inline)) {
+    constexpr int F0 = decltype(f0c)::value, NF = decltype(nfc_)::value;       // fragments F0 .. F0 + NF - 1
+    constexpr int PD = NF == 1 ? 2 : 1, NR = PD + 1;
+    i32x4 wa[NR][2], xb[NR][NF];
+    const unsigned wad = wgt + wlane;
+    auto read_step = [&](auto kc) __attribute__((always_inline)) {
+      constexpr int k = decltype(kc)::value, n = k % NR, tap = k / PAIRS, r = tap / 3, c = tap % 3;
+      wa[n][0] = lds_read16<k * 2048>(wad);
+      wa[n][1] = lds_read16<k * 2048 + 512>(wad);
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+        xb[n][f] = lds_read16<0>((unsigned)((pa[F0 + f][c] + (int)(pat + r * rowb)) ^ ((k % PAIRS) * 32)));
+    };
+    static_for<PD>([&](auto kc) __attribute__((always_inline)) { read_step(kc); });
+    static_for<KS>([&](auto kc) __attribute__((always_inline)) {
+      constexpr int k = decltype(kc)::value, n = k % NR;
+      constexpr int later = KS - 1 - k < PD - 1 ? KS - 1 - k : PD - 1;
+      __builtin_amdgcn_s_waitcnt(0xC07F | ((later * (2 + NF)) << 8));
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (k + PD < KS) read_step(std::integral_constant<int, k + PD>{});
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        acc[F0 + f][0] = Tr::mfma(wa[n][0], xb[n][f], acc[F0 + f][0]);
+        acc[F0 + f][1] = Tr::mfma(wa[n][1], xb[n][f], acc[F0 + f][1]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // MFMA results may be read by ordinary instructions some wait states after the last one
+  auto settle = [&]() __attribute__((always_inline)) {
+    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // The pixel's sums: with a fired gate the ones that hold the conditional channels.
+  auto pick = [&](unsigned dl) __attribute__((always_inline)) {
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int m = (int)(dl << (31 - 16 * f - i)) >> 31;
+        const acc_t pv = accP[0][f][i], sv = accS[0][f][i];
+        acc_t r;
+        from_bits((as_bits(sv) & m) | (as_bits(pv) & ~m), r);
+        accP[0][f][i] = r;
+      }
+  };
+  // bf16 accesses to y and the residual go in the transposed order of transpose4: access j is 16 pixels of one lane
+  // half, four lanes per pixel, i.e. half as many cache lines as a lane's own pieces would touch
+  auto px_of = [&](int px, int h) __attribute__((always_inline)) {   // pixel 16*h + lane % 16 of the fragment
+    return __builtin_amdgcn_ds_bpermute((lane & 15) * 4 + h * 64, px);
+  };
+  auto lane_bytes = [&]() __attribute__((always_inline)) {
+    int b = (lane & 32 ? 64 : 0) + (lane & 16 ? 16 : 0);
+    if constexpr (PF == 2) asm volatile("" : "+v"(b));        // (addresses formed from it are not kept across the K loops)
+    return b;
+  };
+  // Output of the lanes' pixels px (counted from pixel m0 of the batch; -1: none), 2 x 16 channels each, in three steps that
+  // whole wavefronts execute.  First the values, from sums and the decisions in dl (bit 16*f + i; UNI: all the same):
+  auto finish = [&](auto uni, const acc16 (&sum)[2], unsigned dl, long long m0, int px, i32x4 (&v)[4]) __attribute__((always_inline)) {
+    constexpr bool UNI = decltype(uni)::value;
+    const float relu_lo = (a.flags & kRelu) ? 0.0f : -__builtin_inff();
+    const int rowy = a.c_out * 2;
+    const int pxj[2] = {px_of(px, 0), px_of(px, 1)};
+    const long long first = m0 * rowy + cbk * (kBn * 2) + lane_bytes();
+    const float* const taken = aff + (dl ? 128 : 0);
+    i32x4 rs[4];                                     // the lane's four 16-byte pieces
+    if (a.flags & kResidual) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        rs[j] = i32x4{0, 0, 0, 0};
+        if (pxj[j & 1] >= 0) rs[j] = *(const i32x4*)(a.residual + first + (long long)pxj[j & 1] * rowy + (j >> 1) * 32);
+      }
+      transpose4(rs);
+    }
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {                  // eight channels at a time
+        const int cl = 32 * f + 16 * lh + 8 * h;
+        float r[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) r[i] = sum[f][8 * h + i];
+        if (a.flags & kAffine) {
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            if constexpr (UNI) {
+              const f32x4 at = *(const f32x4*)(taken + cl + 4 * q), bt = *(const f32x4*)(taken + 64 + cl + 4 * q);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) r[4 * q + e] = fmaf(at[e], r[4 * q + e], bt[e]);
+            } else {
+              const i32x4 a0 = *(const i32x4*)(aff + cl + 4 * q), b0 = *(const i32x4*)(aff + 64 + cl + 4 * q);
+              const i32x4 a1 = *(const i32x4*)(aff + 128 + cl + 4 * q), b1 = *(const i32x4*)(aff + 192 + cl + 4 * q);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const int m = (int)(dl << (31 - 16 * f - 8 * h - 4 * q - e)) >> 31;
+                r[4 * q + e] = fmaf(__int_as_float((a1[e] & m) | (a0[e] & ~m)), r[4 * q + e],
+                                    __int_as_float((b1[e] & m) | (b0[e] & ~m)));
+              }
+            }
+          }
+        }
+        if (a.flags & kResidual) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const unsigned w = (unsigned)rs[2 * f + h][i >> 1];
+            r[i] += __uint_as_float(i & 1 ? w & 0xffff0000u : w << 16);
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          v[2 * f + h][e] = bf16_pair(max_of(r[2 * e], relu_lo), max_of(r[2 * e + 1], relu_lo));
+        if constexpr (PF == 2) __builtin_amdgcn_sched_barrier(0);    // (one piece at a time: no registers for more)
+      }
+  };
+  // then, where y holds the values for an unfired gate already, each channel's own
+  auto choose = [&](unsigned dl, long long m0, int px, i32x4 (&v)[4]) __attribute__((always_inline)) {
+    const int rowy = a.c_out * 2;
+    const int pxj[2] = {px_of(px, 0), px_of(px, 1)};
+    const long long first = m0 * rowy + cbk * (kBn * 2) + lane_bytes();
+    i32x4 base[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      base[j] = i32x4{0, 0, 0, 0};
+      if (pxj[j & 1] >= 0) base[j] = *(const i32x4*)(a.y + first + (long long)pxj[j & 1] * rowy + (j >> 1) * 32);
+    }
+    transpose4(base);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned lo = (unsigned)((int)(dl << (31 - 8 * j - 2 * e)) >> 31), hi = (unsigned)((int)(dl << (30 - 8 * j - 2 * e)) >> 31);
+        const unsigned m = (lo & 0xffffu) | (hi & 0xffff0000u);
+        v[j][e] = (int)(((unsigned)v[j][e] & m) | ((unsigned)base[j][e] & ~m));
+      }
+  };
+  // and the stores
+  auto store = [&](i32x4 (&v)[4], long long m0, int px) __attribute__((always_inline)) {
+    const int rowy = a.c_out * 2;
+    const int pxj[2] = {px_of(px, 0), px_of(px, 1)};
+    const long long first = m0 * rowy + cbk * (kBn * 2) + lane_bytes();
+    transpose4(v);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (pxj[j & 1] >= 0) *(i32x4*)(a.y + first + (long long)pxj[j & 1] * rowy + (j >> 1) * 32) = v[j];
+  };
+  auto emit_fast = [&](unsigned dl, long long m0, int px) __attribute__((always_inline)) {
+    if constexpr (Base::kDtype != CG_I8) {
+      i32x4 v[4];
+      finish(std::false_type{}, accP[0], dl, m0, px, v);
+      if (a.flags & kShuf2) {
+        // Shuffled channel order (Sec. 3.3): channel j of group i goes to position j*groups + i of its pixel.  The
+        // block's 64 channels are `ng` groups x `nj` channels: an LDS row holds a pixel's in the order [j][group], so
+        // that a run of ng elements is contiguous in both, and consecutive lanes store consecutive j.
+        const int cpg = a.cpg, groups = a.groups;
+        const int njl = cpg >= kBn ? 6 : 31 - __clz(cpg), ngl = 6 - njl;  // (a group narrower than a block divides it)
+        const int ng = 1 << ngl, nj = 1 << njl;
+        const int g0 = cbk * kBn / cpg, j0 = cbk * kBn - g0 * cpg;      // first group; first channel in it (ng = 1)
+        uint16_t* row = (uint16_t*)(lds + a.shuf + wave * (32 * kShufRow) + lj * kShufRow);
+        int lane_ch = 16 * lh;                       // (opaque: 32 addresses formed once would not fit the registers)
+        asm volatile("" : "+v"(lane_ch));
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int c = 32 * f + lane_ch + i;
+            row[((c & (nj - 1)) << ngl) + (c >> njl)] = (uint16_t)((unsigned)v[2 * f + (i >> 3)][(i & 7) >> 1] >> (16 * (i & 1)));
+          }
+        wait_lds();
+        for (int id = lane; id < 32 * nj; id += 64) {
+          const int q = id >> njl, j = id & (nj - 1);                   // pixel of the fragment, channel of its group
+          const int pq = __shfl(px, q, 64);
+          const uint16_t* from = (const uint16_t*)(lds + a.shuf + wave * (32 * kShufRow) + q * kShufRow) + (j << ngl);
+          uint16_t* to = (uint16_t*)a.y + (m0 + pq) * a.c_out + (j0 + j) * groups + g0;
+          if (pq >= 0) {
+            if (ng == 2 && (groups & 1) == 0)
+              *(uint32_t*)to = *(const uint32_t*)from;                  // (g0 is even: blocks cover whole pairs)
+            else
+              for (int e = 0; e < ng; ++e) to[e] = from[e];
+          }
+        }
+        wait_lds();
+        return;
+      }
+      store(v, m0, px);
+    } else {
+      // requantised int8: t = (S * mult_d + bias + half + residual * res_mult) >> shift, clamped (exact in 64 bits;
+      // shifts of two and more: with the high word clamped to +-2^(shift-1) the shifted value fits 32 bits, and what was
+      // clamped still lies beyond the bytes' range).  Access h covers 16 pixels, four 16-lane groups per pixel.
+      const int lo = (a.flags & kRelu) ? 0 : -128;
+      const int h_hi = (1 << (a.rq_shift - 1)) - 1, h_lo = -1 - h_hi;
+      const int pxh[2] = {px_of(px, 0), px_of(px, 1)};
+      const long long first = m0 * a.c_out + cbk * kBn + (lane & 16) * 2 + (lane & 32) / 2;
+      auto swap_halves = [&](i32x4 (&u)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const auto r = __builtin_amdgcn_permlane16_swap((unsigned)u[0][e], (unsigned)u[1][e], false, false);
+          u[0][e] = (int)r[0];
+          u[1][e] = (int)r[1];
+        }
+      };
+      i32x4 v[2], rs[2];
+      if (a.flags & kResidual) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          rs[h] = i32x4{0, 0, 0, 0};
+          if (pxh[h] >= 0) rs[h] = *(const i32x4*)(a.residual + first + (long long)pxh[h] * a.c_out);
+        }
+        swap_halves(rs);
+      }
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        const int cl = 32 * f + 16 * lh;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const i32x4 m0_ = *(const i32x4*)(aff + cl + 4 * q), m1_ = *(const i32x4*)(aff + 64 + cl + 4 * q);
+          unsigned c[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int m = (int)(dl << (31 - 16 * f - 4 * q - e)) >> 31;
+            const int sv = accP[0][f][4 * q + e];
+            long long t = (long long)sv * ((m1_[e] & m) | (m0_[e] & ~m)) + addends[cl + 4 * q + e];
+            if (a.flags & kResidual) t += (long long)(int8_t)((unsigned)rs[f][q] >> (8 * e)) * a.rq_res_mult;
+            const int th = med3((int)(t >> 32), h_lo, h_hi);
+            c[e] = (unsigned)med3((int)__builtin_amdgcn_alignbit((unsigned)th, (unsigned)t, (unsigned)a.rq_shift), lo, 127);
+          }
+          // byte 0 of each of the four
+          const unsigned p01 = __builtin_amdgcn_perm(c[1], c[0], 0x0c0c0400u), p23 = __builtin_amdgcn_perm(c[3], c[2], 0x04000c0cu);
+          v[f][q] = (int)(p01 | p23);
+        }
+      }
+      swap_halves(v);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (pxh[h] >= 0) *(i32x4*)(a.y + first + (long long)pxh[h] * a.c_out) = v[h];
+    }
+  };
+  // every other output type and order, one lane's pixel at a time
+  auto emit_any = [&](unsigned dl, long long m) __attribute__((always_inline)) {
+    // The arguments it needs are read here, and its channel numbers formed here: kept in registers across the K loops
+    // (what the compiler does by itself) they would spill.
+    const auto* kernarg = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() + kParamsAt;
+    asm volatile("" : "+s"(kernarg));
+    const Params q = *(const Params*)kernarg;
+    int lane_ch = 16 * lh;
+    asm volatile("" : "+v"(lane_ch));
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      const int co0 = cbk * kBn + 32 * f + lane_ch;
+      const unsigned d16 = (dl >> (16 * f)) & 0xffffu;
+      if (q.shuffle) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int co = co0 + i, grp = co / q.cpg;
+          const long long o = m * q.c_out + (co - grp * q.cpg) * q.groups + grp;
+          const bool fired = ((d16 >> i) & 1u) != 0u;
+          const acc_t sv = accP[0][f][i];
+          if constexpr (Base::kDtype == CG_I8)
+            store_int(q, o, finish_int(q, sv, fired, co, o));
+          else
+            store_float(q, o, finish_float(q, sv, fired, co, o));
+        }
+        continue;
+      }
+      const long long o = m * q.c_out + co0;
+      i32x4 v[4];
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const acc_t sv = accP[0][f][4 * q4 + e];
+          v[q4][e] = as_bits(sv);
+        }
+      finish_store8<Base>(q, v[0], v[1], d16 & 0xffu, co0, o);
+      finish_store8<Base>(q, v[2], v[3], d16 >> 8, co0 + 8, o + 8);
+    }
+  };
+
+  int v = 0, b = 0, have = 0;                        // the next stage: its number and buffer; stages known to have landed
+#pragma nounroll
+  for (int t = 0; t < tiles; ++t) {
+    const int R0 = tile_row(t), rows_here = t < a.full ? a.tr : tail_rows;
+    const long long m0 = (long long)R0 * a.wo;       // the tile's first output pixel
+    // this lane's pixels, one in each of the wavefront's fragments `wave` and (PF = 2) wave + kCw: row and column in the tile
+    const int next = v + a.s;                        // first stage of the next tile
+    int px[PF], pimg[PF], pa[PF][3];
+    bool inside[PF], any[PF];                        // the pixel exists; any of the fragment does
+    int lp = lj;
+    if constexpr (PF == 2) asm volatile("" : "+v"(lp));       // (formed for each tile: no registers to keep them)
+#pragma unroll
+    for (int g = 0; g < PF; ++g) {
+      const int fr = wave + kCw * g;
+      int lr, wo_;
+      if (a.fwl < 0) {
+        const int i = fr * 32 + lp;
+        lr = div16(i, a.magic_wo);
+        wo_ = i - lr * a.wo;
+      } else {
+        const int fq = div16(fr, a.magic_nfc);
+        lr = (fq << (5 - a.fwl)) + (lp >> a.fwl);
+        wo_ = ((fr - fq * a.nfc) << a.fwl) + (lp & ((1 << a.fwl) - 1));
+      }
+      inside[g] = lr < rows_here && wo_ < a.wo;
+      any[g] = __ballot(inside[g]) != 0ull;
+      if (!inside[g]) lr = wo_ = 0;                  // lanes past the tile's end read pixel 0 and are dropped
+      const int img0 = div16(R0, a.magic_ho);
+      const int rho0 = img0 * a.hp + (R0 - img0 * a.ho) * a.stride;
+      const int R = R0 + lr;
+      pimg[g] = div16(R, a.magic_ho);
+      const int slot0 = ((pimg[g] * a.hp + (R - pimg[g] * a.ho) * a.stride - rho0) << a.logp) + wo_ * a.stride;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) pa[g][c] = slot_addr<CPS>(slot0 + c, lh);
+      px[g] = inside[g] ? lr * a.wo + wo_ : -1;
+    }
+    auto pass_by = [&]() __attribute__((always_inline)) {
+      publish(done + 4 * wave, next);
+      b += next - v;
+      v = next;
+      while (b >= a.nb) b -= a.nb;
+    };
+    if (!any[0]) {                                   // no pixel of this tile is this wavefront's
+      pass_by();
+      continue;
+    }
+#pragma unroll
+    for (int g = 0; g < PF; ++g)
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) accP[g][f][i] = 0;
+    // stages first .. last - 1 for fragments f0 .. f0 + nf - 1
+    auto stages = [&](auto f0, auto nf, int first, int last, acc16 (&acc)[PF][2]) __attribute__((always_inline)) {
+#pragma nounroll
+      for (int s = first; s < last; ++s) {
+        wait_counters<kLw>(landed, lane, v + 1, have);
+        const unsigned pat = lds0 + b * a.pstr;
+        mma_stage(f0, nf, pat, a.wres < 0 ? pat + a.psz : lds0 + a.wres + s * WB, pa, acc);
+        ++v;
+        publish(done + 4 * wave, v);
+        if (++b == a.nb) b = 0;
+      }
+      settle();
+    };
+    constexpr std::integral_constant<int, 0> zero{};
+    constexpr std::integral_constant<int, 1> one{};
+    if constexpr (PF == 2) {
+      if (any[1])
+        stages(zero, std::integral_constant<int, 2>{}, 0, a.s0, accP);
+      else
+        stages(zero, one, 0, a.s0, accP);
+    } else {
+      stages(zero, one, 0, a.s0, accP);
+    }
+
+    unsigned dl[PF];                                 // a dense layer takes the second pair everywhere
+    bool fired[PF];
+#pragma unroll
+    for (int g = 0; g < PF; ++g) {
+      dl[g] = ~0u;
+      fired[g] = false;
+      if (!gated || !any[g]) continue;
+      // ---- gate --------------------------------------------------------------------------------------
+      dl[g] = 0u;
+#pragma unroll
+      for (int f = 1; f >= 0; --f)
+#pragma unroll
+        for (int q4 = 3; q4 >= 0; --q4) {
+          const i32x4 lo4 = *(const i32x4*)(tlo + 32 * f + 16 * lh + 4 * q4);
+#pragma unroll
+          for (int e = 3; e >= 0; --e) Tr::shift_in(dl[g], accP[g][f][4 * q4 + e], lo4[e]);
+        }
+      if constexpr (Base::kDtype != CG_I8) {
+        if (a.flags & kTwoSided) {
+#pragma unroll
+          for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+              const f32x4 hi4 = *(const f32x4*)(thi + 32 * f + 16 * lh + 4 * q4);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const acc_t w = accP[g][f][4 * q4 + e];
+                if (!(w <= hi4[e])) dl[g] &= ~(1u << (16 * f + 4 * q4 + e));
+              }
+            }
+        }
+      }
+      if (!inside[g]) dl[g] = 0u;
+      if (a.chan_mask) {
+        // channel-wise gate (Sec. 3.2): only the channels that keep their conditional path in this image
+        const uint32_t* mw = a.chan_mask + (long long)pimg[g] * a.words + cbk * 2;
+        dl[g] &= ((mw[0] >> (16 * lh)) & 0xffffu) | (((mw[1] >> (16 * lh)) & 0xffffu) << 16);
+      }
+      if (a.bitmap) {
+        const unsigned other = (unsigned)__shfl_xor((int)dl[g], 32, 64);   // the pixel's other channels
+        if (lh == 0 && inside[g])
+          *(uint2*)(a.bitmap + (m0 + px[g]) * a.words + cbk * 2) =
+              uint2{(dl[g] & 0xffffu) | (other << 16), (dl[g] >> 16) | (other & 0xffff0000u)};
+      }
+      fired[g] = __ballot(dl[g] != 0u) != 0ull;
+    }
+    if (gate_only) continue;     // first pass of the channel-wise gate: the decisions are all it produces
+    // ---- conditional path, output ---------------------------------------------------------------------
+    if constexpr (PF == 1) {
+      if (fired[0]) {
+#pragma unroll
+        for (int f = 0; f < 2; ++f) accS[0][f] = accP[0][f];
+        stages(zero, one, a.s0, a.s, accS);
+        pick(dl[0]);
+      } else if (gated) {
+        pass_by();
+      }
+      if (a.flags & kFast)
+        emit_fast(dl[0], m0, px[0]);
+      else if (inside[0])
+        emit_any(dl[0], m0 + px[0]);
+    } else if constexpr (Base::kDtype != CG_I8) {
+      // No registers for two sets of sums: every fragment's outputs for an unfired gate are written first, and where it goes
+      // on the fired channels' replace them at the end.
+      i32x4 w[4];
+      if (gated) {
+#pragma unroll
+        for (int g = 0; g < PF; ++g) {
+          if (!any[g]) continue;
+          finish(std::true_type{}, accP[g], 0u, m0, px[g], w);
+          store(w, m0, px[g]);
+        }
+      }
+      if (fired[0] && fired[1])
+        stages(zero, std::integral_constant<int, 2>{}, a.s0, a.s, accP);
+      else if (fired[0])
+        stages(zero, one, a.s0, a.s, accP);
+      else if (fired[1])
+        stages(one, one, a.s0, a.s, accP);
+      else if (gated)
+        pass_by();
+#pragma unroll
+      for (int g = 0; g < PF; ++g) {
+        if (gated ? !fired[g] : !any[g]) continue;
+        finish(std::true_type{}, accP[g], 1u, m0, px[g], w);
+        if (gated) choose(dl[g], m0, px[g], w);
+        store(w, m0, px[g]);
+      }
+    }
+  }
+}
+
+// [c_out][9][c_phase] -> [column block][stage][kernel row r][K step k][chunk h][row][16 bytes]
+// with tap = 3r + k / (CPS/2) and chunk = CPS*sigma + 2*(k % (CPS/2)) + h; row rho of a 32-row
+// fragment holds channel 16*((rho/4)%2) + 4*(rho/8) + rho%4, which puts 16 consecutive channels in
+// one lane of the transposed product
+//
+// Channel grouping with blocks that cover several groups (multi != 0): the base phase (phase 0)
+// walks the base channels of all the block's groups, the conditional phase all c_in channels; a
+// chunk that is not on that path for the row's output channel is packed as zeros (a chunk never
+// straddles a group: c_base is a multiple of the chunk's channel count).
+__global__ void pack_rows_kernel(const char* __restrict__ w, char* __restrict__ out, int c_phase, int eb, int ch,
+                                 int cps, int stages, long long total, int multi, int phase, int c_base, int cpg) {
+  const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (id >= total) return;
+  const int gk = 3 * cps / 2, pairs = cps / 2;
+  const int rho = (int)(id & 63);
+  long long r_ = id >> 6;
+  const int h = (int)(r_ & 1);
+  r_ >>= 1;
+  const int k = (int)(r_ % gk);
+  r_ /= gk;
+  const int kr = (int)(r_ % 3);
+  r_ /= 3;
+  const int ss = (int)(r_ % stages);
+  const int cb = (int)(r_ / stages);
+  const int tap = 3 * kr + k / pairs;
+  const int chunk = cps * ss + 2 * (k % pairs) + h;
+  const int fc = rho >> 5, rr = rho & 31;
+  const int co = cb * kBn + 32 * fc + 16 * ((rr >> 2) & 1) + 4 * (rr >> 3) + (rr & 3);
+  int c_src = chunk * ch;          // first channel of the chunk in the row's w_base / w_cond
+  bool zero = false;
+  if (multi) {
+    const int grp = co / cpg;      // the row's output group = its base input group
+    if (phase == 0) {
+      const int blk_grp0 = (cb * kBn) / cpg;                 // first group of this column block
+      zero = blk_grp0 + c_src / c_base != grp;
+      c_src = c_src % c_base;
+    } else {
+      zero = c_src / c_base == grp;
+      if (c_src >= (grp + 1) * c_base) c_src -= c_base;
+    }
+  }
+  i32x4 v = {0, 0, 0, 0};
+  if (!zero) v = *(const i32x4*)(w + (((long long)co * 9 + tap) * c_phase + c_src) * eb);
+  *(i32x4*)(out + id * 16) = v;
+}
+
+
+template <typename Tr, int CPS, int PF>
+hipError_t launch_rows_one(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
+  const unsigned blocks = a.xcd_cb ? (unsigned)(g.n_slots * g.n_cb) : (unsigned)a.per_xcd * 8u;
+  // (a compute unit holds 160 KB; more than the default of a launch has to be asked for, once per kernel)
+  static const hipError_t attr = hipFuncSetAttribute((const void*)gated_conv_rows_kernel<Tr, CPS, PF>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL((gated_conv_rows_kernel<Tr, CPS, PF>), dim3(blocks), dim3(kNt), (size_t)g.lds_bytes, s, a, p);
+  return hipGetLastError();
+}
+
+unsigned magic16(int d) { return d == 1 ? 0u : (unsigned)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d); }
+
+// Plan with stages of `cps` chunks; ok = 0 where the shape does not allow them.  *cost: estimated clocks.
+RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* cost) {
+  RowsPlan g{};
+  g.elem_bytes = d.in_dtype == CG_BF16 ? 2 : 1;
+  g.ch = 16 / g.elem_bytes;
+  const long long xps = d.x_pixel_stride ? d.x_pixel_stride : d.c_in;
+  if (xps % g.ch) return g;
+  // channels the two phases walk
+  int base_k = d.c_base, c_cond = d.c_in - d.c_base;
+  g.gsp = 1;
+  if (d.groups > 1) {
+    const int cpg = d.c_out / d.groups;
+    if (cpg % kBn == 0) {
+      g.grp_mode = 1;                       // a 64-channel block lies inside one group
+    } else if (kBn % cpg == 0 && d.c_base % g.ch == 0) {
+      g.grp_mode = 2;                       // a block covers kBn/cpg whole groups
+      g.gsp = kBn / cpg;
+      base_k = g.gsp * d.c_base;
+      c_cond = d.c_in;
+    } else {
+      return g;
+    }
+  }
+  if (d.groups <= 1 && base_k % (2 * g.ch) != 0 && base_k % g.ch == 0 && base_k < d.c_in && d.c_in % (2 * g.ch) == 0) {
+    // A base group of one 16-byte chunk (16 int8 channels) is below the two-chunk K step: the base
+    // phase then walks two chunks with zero weights on the second, and the conditional phase all
+    // input channels with zero weights on the base ones - the packing of a block that covers
+    // several groups, with one group.
+    g.grp_mode = 2;
+    g.gsp = 2;
+    base_k = 2 * d.c_base;
+    c_cond = d.c_in;
+  }
+  if (base_k % (cps * g.ch) || c_cond % (cps * g.ch)) return g;
+  if (d.c_out % kBn) return g;
+  const int ho = (d.h + 2 * d.pad - 3) / d.stride + 1, wo = (d.w + 2 * d.pad - 3) / d.stride + 1;
+  // 32-bit byte offsets and 16-bit row numbers inside the kernel
+  if ((long long)d.n_max * d.h * d.w * xps * g.elem_bytes >= (1ll << 31)) return g;
+  if ((long long)d.n_max * ho * wo >= (1ll << 30)) return g;
+  if ((long long)d.n_max * (d.h + 2 * d.pad) >= 65536 || (long long)d.n_max * ho >= 65536) return g;
+  g.cps = cps;
+  g.n_cb = d.c_out / kBn;
+  g.hp = d.h + 2 * d.pad;
+  g.logp = 4;
+  while ((1 << g.logp) < d.w + d.pad) ++g.logp;
+  if ((1 << g.logp) == d.w + d.pad && d.pad) ++g.logp;   // keep a zero slot after the last column
+  if (g.logp > 8) return g;
+  g.stages[0] = base_k / (cps * g.ch);
+  g.stages[1] = c_cond / (cps * g.ch);
+  const int S = g.stages[0] + g.stages[1], ks = 9 * cps / 2, wb = ks * 2048;
+  const long long rows = (long long)d.n_max * ho;
+  // which operand an XCD's L2 should see whole: the heavier one
+  g.xcd_cb = (g.n_cb % 8 == 0 && 9ll * d.c_in * d.c_out > (long long)d.n_max * d.h * d.w * d.c_in) ? 1 : 0;
+  long long slots = n_cu / g.n_cb;
+  if (slots < 1) slots = 1;
+  if (slots > rows) slots = rows;
+  g.n_slots = (int)slots;
+  const int slot_rows = (int)((rows + slots - 1) / slots);
+  // patch rows of a tile of t output rows, maximum over the rows a tile may start at
+  auto patch_rows = [&](int t) {
+    int pr = 0;
+    for (int r0 = 0; r0 < ho; ++r0) {
+      const int r1 = r0 + t - 1;
+      const int here = (r1 / ho) * g.hp + (r1 % ho) * d.stride - r0 * d.stride + 3;
+      if (here > pr) pr = here;
+    }
+    return pr;
+  };
+  // Fragment shape, rows per tile and buffers: the choice with the least estimated time.  A K step costs 64 clocks of
+  // the matrix cores per fragment on one SIMD; a conditional stage costs the share of the fragments that hold a
+  // fired pixel (measured on clustered maps at a firing rate of 0.3, by the fragment's height); the
+  // vector-memory path serves a line every two clocks; with two buffers a stage's latency shows; the gate and
+  // the output are some 250 instructions a fragment.
+  const int shuf_bytes = d.shuffle && d.in_dtype == CG_BF16 && d.out_dtype == CG_BF16 && !(d.epilogue & CG_EPI_RESIDUAL) ? kCw * 32 * kShufRow : 0;
+  double best = 1e30;
+  // Two fragments per wavefront: 16 clocks of LDS reads per fragment and K step instead of 24 (a quarter of the K loop's
+  // time), for outputs that are formed and written twice (1500 clocks a fragment).
+  const bool wide = d.in_dtype == CG_BF16 && d.out_dtype == CG_BF16 && !d.shuffle && cps == 4;
+  for (int pf = 1; pf <= (wide ? max_pf : 1); ++pf)
+  for (int fwl = -1; fwl <= 5; ++fwl) {
+    if (fwl == 0 || fwl == 1) continue;                    // (16 and 32 rows of one or two columns: no better than a run)
+    const int fh = fwl < 0 ? 1 : 32 >> fwl, nfc = fwl < 0 ? 1 : (wo + (1 << fwl) - 1) >> fwl;
+    const int frags_max = kCw * pf;
+    if (nfc > frags_max) continue;
+    int tmax = fwl < 0 ? 32 * frags_max / wo : frags_max / nfc * fh;
+    if (tmax < 1) continue;
+    const double beta = fwl < 0 ? (wo >= 32 ? 0.90 : wo >= 16 ? 0.82 : 0.62) : fh == 1 ? 0.90 : fh == 2 ? 0.75 : 0.60;
+    const int step = fwl < 0 ? 1 : fh;
+    for (int t = tmax; t >= step && 4 * t >= tmax; t -= step) {
+      const int pr = patch_rows(t);
+      const long long psz = (((long long)pr << g.logp) * 16 * cps + 1023) / 1024 * 1024;
+      if (psz / 1024 > kMaxPatchLoads * kLw) continue;
+      for (int resident = 1; resident >= 0; --resident) {
+        const long long fixed = kTabBytes + shuf_bytes + (resident ? (long long)S * wb : 0);
+        const long long per = psz + (resident ? 0 : wb);
+        int nb = (int)((kLds - fixed) / per);
+        if (fixed > kLds || nb < 2) continue;
+        if (nb > 8) nb = 8;
+        const double lines = (double)(pr * (d.w < (1 << g.logp) ? d.w : (1 << g.logp))) + (resident ? 0 : wb / 128.0);
+        const double stream = 2.0 * lines + (nb == 2 ? 700.0 : nb == 3 ? 150.0 : 0.0);
+        auto tile = [&](int r) {
+          const int frags = fwl < 0 ? (r * wo + 31) / 32 : (r + fh - 1) / fh * nfc;
+          const double per_simd = (frags + 3) / 4;
+          const double mm = ks * 64.0 * per_simd * (per_simd < 2 ? 1.25 : 1.05) * (frags > kCw ? 0.75 : 1.0);
+          const double mc = mm * (beta < 1.0 ? (beta + 0.15 < 1.0 ? beta + 0.15 : 1.0) : 1.0);
+          return g.stages[0] * (mm > stream ? mm : stream) + g.stages[1] * (mc > stream ? mc : stream) + 900.0 + (pf == 2 ? per_simd * 1500.0 : 0.0);
+        };
+        const double c = (slot_rows / t) * tile(t) + (slot_rows % t ? tile(slot_rows % t) : 0.0) + 1500.0 +
+                         (resident ? S * wb / 60.0 : 0.0);
+        if (c < best) {
+          best = c;
+          g.pf = pf;
+          g.fwl = fwl;
+          g.nfc = nfc;
+          g.tr = t;
+          g.pr = pr;
+          g.n_pl = (int)(psz / 1024);
+          g.nb = nb;
+          g.resident = resident;
+          g.psz = (int)psz;
+          g.pstr = (int)per;
+          g.ok = 1;
+        }
+      }
+    }
+  }
+  if (!g.ok) return g;
+  int off = g.nb * g.pstr;
+  g.wres = g.resident ? off : -1;
+  if (g.resident) off += S * wb;
+  g.shuf = off;
+  g.shuf_bytes = shuf_bytes;
+  off += shuf_bytes;
+  g.tabs = off;
+  g.lds_bytes = off + kTabBytes;
+  g.wpk_base_bytes = (size_t)g.n_cb * g.stages[0] * wb;
+  g.wpk_cond_bytes = (size_t)g.n_cb * g.stages[1] * wb;
+  *cost = best;
+  return g;
+}
+
+}  // namespace
+
+RowsPlan rows_plan(const cg_conv_desc& d, int n_cu, int cps, int max_pf) {
+  RowsPlan none{};
+  if (d.in_dtype != CG_BF16 && d.in_dtype != CG_I8) return none;
+  if (d.kh != 3 || d.kw != 3 || d.stride < 1 || d.stride > 2 || d.pad > 1) return none;
+  double c4 = 1e30, c2 = 1e30;
+  const RowsPlan a = cps == 2 ? none : plan_cps(d, n_cu, 4, max_pf, &c4);
+  const RowsPlan b = cps == 4 ? none : plan_cps(d, n_cu, 2, max_pf, &c2);
+  return a.ok && (!b.ok || c4 <= c2) ? a : b;
+}
+
+hipError_t launch_rows_pack(const RowsPlan& g, const Params& p, void* wpk_base, void* wpk_cond, hipStream_t s) {
+  for (int ph = 0; ph < 2; ++ph) {
+    if (g.stages[ph] == 0) continue;
+    const long long total = (long long)g.n_cb * g.stages[ph] * 3 * (3 * g.cps / 2) * 2 * 64;
+    const unsigned blocks = (unsigned)((total + 255) / 256);
+    hipLaunchKernelGGL(pack_rows_kernel, dim3(blocks), dim3(256), 0, s, (const char*)(ph ? p.w_cond : p.w_base),
+                       (char*)(ph ? wpk_cond : wpk_base), ph ? p.c_cond : p.c_base, g.elem_bytes, g.ch, g.cps,
+                       g.stages[ph], total, g.grp_mode == 2 ? 1 : 0, ph, p.c_base, p.cpg);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_rows(const RowsPlan& g, const Params& p, const void* w0, const void* w1, hipStream_t s) {
+  RowsArgs a{};
+  a.x = (const char*)p.x;
+  a.w0 = (const char*)w0;
+  a.w1 = (const char*)w1;
+  a.tab = (const char*)p.thr_f;
+  a.y = (char*)p.y;
+  a.residual = (const char*)p.residual;
+  a.bitmap = p.bitmap;
+  a.chan_mask = p.chan_mask;
+  a.clear = p.clear_total ? p.total : nullptr;
+  a.magic_hp = magic16(g.hp);
+  a.magic_ho = magic16(p.ho);
+  a.magic_wo = magic16(p.wo);
+  a.magic_ncb = magic16(g.n_cb);
+  a.n = p.n;
+  a.h = p.h;
+  a.w = p.w;
+  a.ho = p.ho;
+  a.wo = p.wo;
+  a.hp = g.hp;
+  a.stride = p.stride;
+  a.pad = p.pad;
+  a.xps = (int)p.x_pixel_stride * g.elem_bytes;
+  a.x_bytes = (unsigned)((((long long)p.n * p.h * p.w - 1) * p.x_pixel_stride + p.c_in) * g.elem_bytes);
+  const int rows = p.n * p.ho;
+  a.full = rows / (g.n_slots * g.tr);
+  const int tail = rows - a.full * g.n_slots * g.tr;
+  a.rows_per = tail / g.n_slots;
+  a.rows_more = tail % g.n_slots;
+  a.tr = g.tr;
+  a.logp = g.logp;
+  a.pr = g.pr;
+  a.n_pl = g.n_pl;
+  a.s0 = g.stages[0];
+  a.s = g.stages[0] + (p.gated && !p.gate_only ? g.stages[1] : 0);
+  a.nb = g.nb;
+  a.pstr = g.pstr;
+  a.psz = g.psz;
+  a.wres = g.wres;
+  a.tabs = g.tabs;
+  a.shuf = g.shuf;
+  a.fwl = g.fwl;
+  a.nfc = g.nfc;
+  a.magic_nfc = magic16(g.nfc);
+  a.n_cb = g.n_cb;
+  a.n_slots = g.n_slots;
+  a.xcd_cb = g.xcd_cb;
+  a.per_xcd = (g.n_slots * g.n_cb + 7) / 8;
+  a.grp_mode = p.groups > 1 ? 1 : 0;
+  a.grp_step = p.cpg;
+  a.base_chn = p.c_base * g.elem_bytes;
+  a.gap_chn = g.grp_mode == 2 ? 0 : p.c_base * g.elem_bytes;
+  a.words = p.words;
+  a.tab_stride = (int)p.table_stride;
+  a.c_out = p.c_out;
+  a.cpg = p.cpg;
+  a.groups = p.groups;
+  a.rq_shift = p.rq_shift;
+  a.rq_res_mult = p.rq_res_mult;
+  const bool shuf2 = p.shuffle && g.shuf_bytes > 0;
+  a.flags = (p.gated ? kGated : 0u) | (p.gate_only ? kGateOnly : 0u) | (p.two_sided ? kTwoSided : 0u) |
+            ((p.epilogue & CG_EPI_AFFINE) && p.in_dtype != CG_I8 ? kAffine : 0u) | ((p.epilogue & CG_EPI_RELU) ? kRelu : 0u) |
+            ((p.epilogue & CG_EPI_RESIDUAL) ? kResidual : 0u) |
+            ((p.out_dtype == CG_BF16 || (p.out_dtype == CG_I8 && p.rq_shift >= 2)) && (!p.shuffle || shuf2) ? kFast : 0u) | (shuf2 ? kShuf2 : 0u);
+  if (p.in_dtype == CG_I8) return g.cps == 4 ? launch_rows_one<I8Rows, 4, 1>(g, p, a, s) : launch_rows_one<I8Rows, 2, 1>(g, p, a, s);
+  if (g.pf == 2)
+    return g.cps == 4 ? launch_rows_one<Bf16Rows, 4, 2>(g, p, a, s) : launch_rows_one<Bf16Rows, 2, 2>(g, p, a, s);
+  return g.cps == 4 ? launch_rows_one<Bf16Rows, 4, 1>(g, p, a, s) : launch_rows_one<Bf16Rows, 2, 1>(g, p, a, s);
+}
+
+}  // namespace cg

@@ -1,0 +1,71 @@
+"""GPU parity of the row-tiled matrix-core kernel at the edges of its tiles: every fragment shape, tiles that end inside an
+image or an image row, weights that stay in LDS or stream, the shuffled store, one and two fragments per wavefront."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1805_12549_amd import binding as B
+from paper_1805_12549_amd import workloads as W
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+def S(n, h, w, ci, co, **kw):
+    return W.LayerShape("%dx%dx%d_%d>%d" % (n, h, w, ci, co) + "".join("_%s%d" % i for i in sorted(kw.items())), n, h, w, ci, co, **kw)
+
+
+SHAPES = [
+    S(1, 3, 3, 64, 64),                        # one fragment, most of it past the image
+    S(3, 5, 250, 64, 64),                      # the widest rows
+    S(2, 20, 33, 64, 64),                      # last fragment of a row holds one column
+    S(5, 14, 14, 256, 256),
+    S(7, 27, 27, 192, 192),
+    S(2, 31, 9, 128, 64, stride=2),
+    S(4, 17, 40, 128, 128, groups=2),          # channel groups: a block inside one
+    S(3, 13, 21, 128, 128, groups=8),          # a block of several
+    S(130, 14, 14, 256, 256),                  # two fragments per wavefront, 32 x 14 pixel tiles
+    S(30, 14, 14, 256, 1024),                  # the same in runs of 32 pixels
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=[s.name for s in SHAPES])
+def test_rows_kernel_shapes(shape):
+    rng = np.random.default_rng(shape.n * 11 + shape.c_out)
+    c, big = shape.c_out, shape.n * shape.h * shape.w > 5000
+    aff = dict(scale0=rng.uniform(0.5, 1.5, c), shift0=rng.normal(0, 0.1, c),
+               scale1=rng.uniform(0.5, 1.5, c), shift1=rng.normal(0, 0.1, c))
+    res = rng.standard_normal((shape.n, shape.ho, shape.wo, c)).astype(np.float32)
+    full = B.CG_EPI_RELU | B.CG_EPI_AFFINE | B.CG_EPI_RESIDUAL
+    inp = W.make_inputs(shape, 9000 + c + shape.h, kind="coherent", rho=0.3, round_bf16=True, grouped=shape.groups != 4)
+    gate = W.calibrate_gate(inp, 0.3, sample_images=2)
+    kw = dict(variant=B.CG_VARIANT_MFMA_ROWS)
+    runs = [dict(out_dtype=B.CG_BF16, affine=aff, residual=res, epilogue=full, n_run=max(1, shape.n - 1))]
+    if not big:
+        runs += [dict(out_dtype=B.CG_BF16, affine=aff, epilogue=full & ~B.CG_EPI_RESIDUAL, shuffle=inp.grouped),
+                 dict(out_dtype=B.CG_F32, delta_hi=gate.delta + 0.8)]
+    for r in runs:
+        print("\n  " + str(P.run_float(inp, gate, name=shape.name, **kw, **r)), flush=True)
+    if not big:
+        q = W.quantize_int8(W.make_inputs(shape, 9100 + c + shape.h, kind="coherent", rho=0.35, grouped=inp.grouped))
+        thr = W.calibrate_gate_int8(q, 0.35, sample_images=None)
+        print("  " + str(P.run_int8(q, thr, name=shape.name + " int8", **kw)), flush=True)
+
+
+def test_residual_may_be_the_output():
+    """y written over the residual (two fragments per wavefront write y twice, which that must not see)."""
+    shape = S(130, 14, 14, 256, 256)
+    inp = W.make_inputs(shape, 9300, kind="coherent", rho=0.3, round_bf16=True)
+    gate = W.calibrate_gate(inp, 0.3, sample_images=2)
+    bf = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16)
+    layer = B.GatedConv(n_max=shape.n, h=14, w=14, c_in=256, c_out=256, c_base=inp.w_base.shape[-1], w_base=bf(inp.w_base),
+                        w_cond=bf(inp.w_cond), in_dtype=B.CG_BF16, out_dtype=B.CG_BF16,
+                        epilogue=B.CG_EPI_RELU | B.CG_EPI_RESIDUAL, gate_mean=gate.mean, gate_var=gate.var, delta=gate.delta)
+    x = bf(inp.x)
+    res = torch.randn(shape.n, 14, 14, 256, device="cuda").to(torch.bfloat16)
+    y, bits, counts = [t.clone() for t in layer.forward(x, residual=res)]
+    over = res.clone()
+    _, bits2, counts2 = layer.forward(x, residual=over, y=over)
+    torch.cuda.synchronize()
+    layer.close()
+    assert torch.equal(y, over) and torch.equal(bits, bits2) and torch.equal(counts, counts2)
