@@ -89,6 +89,7 @@ struct cg_conv {
   int ho, wo, c_cond;
   int variant;              // resolved CG_VARIANT_*: the kernel family that covers the shape
   bool direct_ok;           // the small-tile kernel's weights are packed too
+  bool point_ok;            // a 1x1 layer of the large-tile family that runs on the row-tiled kernel
   CallPlan first;           // plan for n_max
   Layout lay;
   cg::Params base;          // what is the same in every call
@@ -201,7 +202,7 @@ struct Plans {
   cg::TilePlan v4;
   cg::DirectPlan vd;
   int variant;
-  bool direct_ok;
+  bool direct_ok, point_ok;
   size_t wpk_base_bytes, wpk_cond_bytes, wpd_base_bytes, wpd_cond_bytes;
 };
 
@@ -229,23 +230,35 @@ int resolve_variant(const cg_conv_desc& d, Plans* pl) {
   int v = d.variant;
   if (v == CG_VARIANT_AUTO) v = pl->v3.ok ? CG_VARIANT_MFMA_ROWS : pl->v4.ok ? CG_VARIANT_TILE : CG_VARIANT_NAIVE;
   pl->variant = v;
+  // 1x1 layers of stride 1 whose channel walk is whole stages run on the row-tiled kernel (unless a family was asked for by
+  // name): 1024 channels at 14x14 x64, bf16 49 us against 89 on the large-tile kernel, int8 36 against 101
+  pl->point_ok = false;
+  if (d.variant == CG_VARIANT_AUTO && v != CG_VARIANT_MFMA_ROWS) {
+    const cg::RowsPlan q = cg::point_plan(d, cu_count());
+    pl->point_ok = q.ok != 0;
+    if (q.ok) pl->v3 = q;
+  }
   pl->vd = cg::direct_plan(d, d.n_max, cu_count());
   pl->direct_ok = d.variant == CG_VARIANT_AUTO && pl->vd.ok;      // (a family that was asked for by name is what runs)
   pl->wpd_base_bytes = pl->direct_ok ? pl->vd.wpk_bytes[0] : 0;
   pl->wpd_cond_bytes = pl->direct_ok ? pl->vd.wpk_bytes[1] : 0;
-  pl->wpk_base_bytes = v == CG_VARIANT_TILE ? pl->v4.wpk_base_bytes : v == CG_VARIANT_MFMA_ROWS ? pl->v3.wpk_base_bytes : 0;
-  pl->wpk_cond_bytes = v == CG_VARIANT_TILE ? pl->v4.wpk_cond_bytes : v == CG_VARIANT_MFMA_ROWS ? pl->v3.wpk_cond_bytes : 0;
+  const bool rows = v == CG_VARIANT_MFMA_ROWS || pl->point_ok;
+  pl->wpk_base_bytes = rows ? pl->v3.wpk_base_bytes : v == CG_VARIANT_TILE ? pl->v4.wpk_base_bytes : 0;
+  pl->wpk_cond_bytes = rows ? pl->v3.wpk_cond_bytes : v == CG_VARIANT_TILE ? pl->v4.wpk_cond_bytes : 0;
   return CG_OK;
 }
 
 // The kernel a batch runs on.  (Layers that neither tiled family covers: the small-tile kernel.)
 void pick_kernel(const cg_conv* h, CallPlan* c) {
-  c->kernel = h->variant == CG_VARIANT_MFMA_ROWS ? kRows : h->variant == CG_VARIANT_TILE ? kTile : kNaive;
+  c->kernel = h->variant == CG_VARIANT_MFMA_ROWS || h->point_ok ? kRows : h->variant == CG_VARIANT_TILE ? kTile : kNaive;
   if (!h->direct_ok || !c->direct.ok) return;
-  // One round of tiles over the compute units (two for 1x1 layers) is where the small-tile kernel's time starts to
-  // grow; measured over one to 64 images of the ResNet-18 layers, e.g. 512 channels at 7x7, small-tile / row-tiled kernel:
-  // 15.3 / 19.1 us at eight images of bf16, 12.3 / 13.9 at eight of int8, 20.9 / 14.4 at 32 (two rounds).
-  const int rounds = h->d.kh == 3 ? 1 : 2;
+  // One round of tiles over the compute units (two where the large-tile kernel is the other choice) is where the small-tile
+  // kernel's time starts to grow; measured over one to 64 images of the ResNet-18 layers, e.g. 512 channels at 7x7,
+  // small-tile / row-tiled kernel: 15.3 / 19.1 us at eight images of bf16, 12.3 / 13.9 at eight of int8, 20.9 / 14.4 at
+  // 32 (two rounds).  1x1 layers on the row-tiled kernel are too short below 512 channels for a split of K to pay: 64
+  // channels at 56x56, one image 7.7 / 5.5; 1024 at 14x14, one image 10.2 / 11.5, eight 13.2 / 13.1.
+  if (h->point_ok && h->d.c_in < 512) return;
+  const int rounds = h->d.kh == 3 || h->point_ok ? 1 : 2;
   if (c->kernel == kNaive || c->direct.tiles <= rounds * cu_count()) c->kernel = kDirect;
 }
 
@@ -256,8 +269,8 @@ CallPlan plan_call(const cg_conv* h, int n) {
   c.n = n;
   cg_conv_desc dn = h->d;
   dn.n_max = n;
-  if (h->variant == CG_VARIANT_MFMA_ROWS) {
-    const cg::RowsPlan q = cg::rows_plan(dn, cu_count(), c.rows.cps, 2);
+  if (h->variant == CG_VARIANT_MFMA_ROWS || h->point_ok) {
+    const cg::RowsPlan q = h->point_ok ? cg::point_plan(dn, cu_count()) : cg::rows_plan(dn, cu_count(), c.rows.cps, 2);
     if (q.ok && q.grp_mode == c.rows.grp_mode && q.gsp == c.rows.gsp &&
         q.stages[0] == c.rows.stages[0] && q.stages[1] == c.rows.stages[1])
       c.rows = q;
@@ -409,6 +422,7 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   h->c_cond = d.c_in - d.c_base;
   h->variant = variant;
   h->direct_ok = pl.direct_ok;
+  h->point_ok = pl.point_ok;
   h->lay = lay;
   h->first.n = d.n_max;
   h->first.rows = pl.v3;
@@ -475,9 +489,9 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
     e = hipMemcpyAsync(pk + lay.w_base_off, d.w_base, lay.w_base_bytes, hipMemcpyDeviceToDevice, s);
   if (e == hipSuccess && lay.w_cond_bytes)
     e = hipMemcpyAsync(pk + lay.w_cond_off, d.w_cond, lay.w_cond_bytes, hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess && variant == CG_VARIANT_TILE)
+  if (e == hipSuccess && variant == CG_VARIANT_TILE && !pl.point_ok)
     e = cg::launch_tile_pack(pl.v4, h->base, pk + lay.wpk_base_off, pk + lay.wpk_cond_off, s);
-  if (e == hipSuccess && variant == CG_VARIANT_MFMA_ROWS)
+  if (e == hipSuccess && (variant == CG_VARIANT_MFMA_ROWS || pl.point_ok))
     e = cg::launch_rows_pack(pl.v3, h->base, pk + lay.wpk_base_off, pk + lay.wpk_cond_off, s);
   if (e == hipSuccess && pl.direct_ok)
     e = cg::launch_direct_pack(pl.vd, h->base, pk + lay.wpd_base_off, pk + lay.wpd_cond_off, s);
@@ -627,7 +641,7 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
   p.total = total;
   p.clear_total = counts && clear_total;
 
-  if (cp.kernel == kDirect && !aligned) cp.kernel = kNaive;      // (only where the plain kernel is the layer's family)
+  if (!aligned) cp.kernel = kNaive;      // (the plain kernel is the layer's family: the others were turned away)
   if (cp.kernel == kRows && cp.rows.pf == 2 && residual) {
     // Two fragments per wavefront write an output twice and read the residual after the first time.
     const char *y0 = (const char*)y, *r0 = (const char*)residual;

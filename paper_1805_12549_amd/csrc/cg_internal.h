@@ -138,7 +138,8 @@ hipError_t launch_direct(const DirectPlan& plan, const Params& p, const void* wp
 struct RowsPlan {
   int ok;
   int elem_bytes, ch;      // bytes per element; channels per 16-byte chunk
-  int cps;                 // chunks per pixel per stage: 4 or 2
+  int taps;                // 9, or 1 for 1x1 layers: a row is then a pixel, and a patch the tile's pixels
+  int cps;                 // chunks per pixel per stage: 4 or 2 (1x1: 8)
   int stages[2];           // stages of the base / conditional phase
   // Channel grouping.  0: none.  1: a 64-channel block lies inside one output group; its base
   // channels start at group*c_base and the conditional phase skips them.  2: a block covers
@@ -162,6 +163,8 @@ struct RowsPlan {
 
 // cps: 0 = pick, 4 or 2 = that (for a handle whose weights are packed); max_pf: the most fragments per wavefront
 RowsPlan rows_plan(const cg_conv_desc& d, int n_cu, int cps, int max_pf);
+// the same kernel on 1x1 layers of stride 1
+RowsPlan point_plan(const cg_conv_desc& d, int n_cu);
 hipError_t launch_rows_pack(const RowsPlan& plan, const Params& p, void* wpk_base, void* wpk_cond, hipStream_t s);
 hipError_t launch_rows(const RowsPlan& plan, const Params& p, const void* wpk_base, const void* wpk_cond,
                          hipStream_t s);

@@ -34,6 +34,9 @@
 // Its registers do not hold two sets of sums per fragment; the outputs for an unfired gate are written first and
 // corrected where a gate fired.
 //
+// TAPS = 1 (1x1 layers of stride 1): a row is a pixel, a patch the tile's pixels (no halo), a stage up to eight chunks of one
+// tap.  1024 channels at 14x14, 64 images: bf16 49 us, int8 36; 89 and 101 on the large-tile kernel.
+//
 // What bounds the kernel: at 64 and 128 channels the instructions of gate and output (a third of a wavefront's time each
 // side of the products), at 256 and 512 the LDS reads and, for few images, the start (arguments, tables and the first
 // stage: 2 us of 8 to 13).  Measured in a graph, before (barrier-coupled workgroups with the pixels listed anew for the
@@ -154,6 +157,7 @@ __device__ __forceinline__ int med3(int v, int lo, int hi) {
 // byte offset of chunk position (h ^ f(slot)) of pixel slot `slot`
 template <int CPS>
 __device__ __forceinline__ int slot_addr(int slot, int h) {
+  if constexpr (CPS == 8) return slot * 128 + ((h ^ slot) & 7) * 16;
   if constexpr (CPS == 4) return slot * 64 + ((h ^ (slot >> 2)) & 3) * 16;
   return slot * 32 + ((h ^ (slot >> 3)) & 1) * 16;
 }
@@ -255,12 +259,12 @@ enum : unsigned {
 
 constexpr int kParamsAt = (sizeof(RowsArgs) + alignof(Params) - 1) / alignof(Params) * alignof(Params);   // of the kernel's arguments
 
-template <typename Tr, int CPS, int PF>
+template <typename Tr, int CPS, int PF, int TAPS>
 __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params) {
   using acc16 = typename Tr::acc16;
   using acc_t = typename Tr::acc_t;
   using Base = typename Tr::Base;
-  constexpr int KS = 9 * CPS / 2;              // K steps per stage
+  constexpr int KS = TAPS * CPS / 2;             // K steps per stage
   constexpr int PAIRS = CPS / 2;
   constexpr int WB = KS * 2048;                // bytes of a stage's weights
   constexpr int NWL = WB / 1024 / kLw;         // weight load instructions per loading wavefront (CPS = 2: one more for some)
@@ -351,14 +355,28 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
         ++np;
         const int pos = (lw + kLw * k) * 64 + lane;
         const int sl = pos / CPS, cp = pos % CPS;
-        const int f = CPS == 4 ? (sl >> 2) & 3 : (sl >> 3) & 1;
+        const int f = CPS == 8 ? sl & 7 : CPS == 4 ? (sl >> 2) & 3 : (sl >> 3) & 1;
+        if constexpr (TAPS == 1) {
+          vcol[k] = sl * a.xps + (cp ^ f) * 16;
+          continue;
+        }
         const int wi = (sl & ((1 << a.logp) - 1)) - a.pad;
         if ((unsigned)wi < (unsigned)a.w && (sl >> a.logp) < a.pr) vcol[k] = wi * a.xps + (cp ^ f) * 16;
       }
     }
     const int rowx = a.w * a.xps;            // bytes per image row
-    // positions of this wavefront's patch loads for the tile that starts at row R0
-    auto tile_setup = [&](int R0) __attribute__((always_inline)) {
+    // positions of this wavefront's patch loads for tile t
+    auto tile_setup = [&](int t) __attribute__((always_inline)) {
+      const int R0 = tile_row(t);
+      if constexpr (TAPS == 1) {
+        const int here = t < a.full ? a.tr : tail_rows;
+#pragma unroll
+        for (int k = 0; k < kMaxPatchLoads; ++k) {
+          if (k >= np) break;
+          voff[k] = ((lw + kLw * k) * 64 + lane) / CPS < here ? R0 * a.xps + vcol[k] : kOut;
+        }
+        return;
+      }
       const int img0 = div16(R0, a.magic_ho);
       const int rho0 = img0 * a.hp + (R0 - img0 * a.ho) * a.stride;     // stacked padded input row of patch row 0
 #pragma unroll
@@ -375,7 +393,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     int is = 0, ib = 0, iv = 0, itile = 0;   // the next stage to issue: stage of its tile, buffer, number
     auto issue = [&]() __attribute__((always_inline)) {
       const unsigned buf = lds0 + ib * a.pstr + lw * 1024;
-      if (is == 0) tile_setup(tile_row(itile));
+      if (is == 0) tile_setup(itile);
       if (a.wres < 0 || iv < a.s) {
         const unsigned wd = a.wres < 0 ? buf + a.psz : lds0 + a.wres + is * WB + lw * 1024;
         const i32x4 r = is < a.s0 ? wr0 : wr1;
@@ -445,7 +463,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   auto mma_stage = [&](auto f0c, auto nfc_, unsigned pat, unsigned wgt, const int (&pa)[PF][3], acc16 (&acc)[PF][2])
       __attribute__((always_inline)) {
     constexpr int F0 = decltype(f0c)::value, NF = decltype(nfc_)::value;       // fragments F0 .. F0 + NF - 1
-    constexpr int PD = NF == 1 ? 2 : 1, NR = PD + 1;
+    constexpr int PD = NF == 1 && KS > 1 ? 2 : 1, NR = PD + 1;
     i32x4 wa[NR][2], xb[NR][NF];
     const unsigned wad = wgt + wlane;
     auto read_step = [&](auto kc) __attribute__((always_inline)) {
@@ -737,6 +755,15 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     for (int g = 0; g < PF; ++g) {
       const int fr = wave + kCw * g;
       int lr, wo_;
+      if constexpr (TAPS == 1) {                     // a row is a pixel
+        const int i = fr * 32 + lp;
+        px[g] = i < rows_here ? i : -1;
+        inside[g] = i < rows_here;
+        any[g] = __ballot(inside[g]) != 0ull;
+        pa[g][0] = slot_addr<CPS>(inside[g] ? i : 0, lh);
+        pimg[g] = a.chan_mask ? (R0 + (inside[g] ? i : 0)) / a.hp : 0;
+        continue;
+      }
       if (a.fwl < 0) {
         const int i = fr * 32 + lp;
         lr = div16(i, a.magic_wo);
@@ -900,18 +927,18 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
 // chunk that is not on that path for the row's output channel is packed as zeros (a chunk never
 // straddles a group: c_base is a multiple of the chunk's channel count).
 __global__ void pack_rows_kernel(const char* __restrict__ w, char* __restrict__ out, int c_phase, int eb, int ch,
-                                 int cps, int stages, long long total, int multi, int phase, int c_base, int cpg) {
+                                 int cps, int stages, long long total, int multi, int phase, int c_base, int cpg, int taps) {
   const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= total) return;
-  const int gk = 3 * cps / 2, pairs = cps / 2;
+  const int gk = taps == 9 ? 3 * cps / 2 : cps / 2, pairs = cps / 2, rows = taps == 9 ? 3 : 1;
   const int rho = (int)(id & 63);
   long long r_ = id >> 6;
   const int h = (int)(r_ & 1);
   r_ >>= 1;
   const int k = (int)(r_ % gk);
   r_ /= gk;
-  const int kr = (int)(r_ % 3);
-  r_ /= 3;
+  const int kr = (int)(r_ % rows);
+  r_ /= rows;
   const int ss = (int)(r_ % stages);
   const int cb = (int)(r_ / stages);
   const int tap = 3 * kr + k / pairs;
@@ -932,33 +959,38 @@ __global__ void pack_rows_kernel(const char* __restrict__ w, char* __restrict__ 
     }
   }
   i32x4 v = {0, 0, 0, 0};
-  if (!zero) v = *(const i32x4*)(w + (((long long)co * 9 + tap) * c_phase + c_src) * eb);
+  if (!zero) v = *(const i32x4*)(w + (((long long)co * taps + tap) * c_phase + c_src) * eb);
   *(i32x4*)(out + id * 16) = v;
 }
 
 
-template <typename Tr, int CPS, int PF>
+template <typename Tr, int CPS, int PF, int TAPS>
 hipError_t launch_rows_one(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
   const unsigned blocks = a.xcd_cb ? (unsigned)(g.n_slots * g.n_cb) : (unsigned)a.per_xcd * 8u;
   // (a compute unit holds 160 KB; more than the default of a launch has to be asked for, once per kernel)
-  static const hipError_t attr = hipFuncSetAttribute((const void*)gated_conv_rows_kernel<Tr, CPS, PF>,
+  static const hipError_t attr = hipFuncSetAttribute((const void*)gated_conv_rows_kernel<Tr, CPS, PF, TAPS>,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((gated_conv_rows_kernel<Tr, CPS, PF>), dim3(blocks), dim3(kNt), (size_t)g.lds_bytes, s, a, p);
+  hipLaunchKernelGGL((gated_conv_rows_kernel<Tr, CPS, PF, TAPS>), dim3(blocks), dim3(kNt), (size_t)g.lds_bytes, s, a, p);
   return hipGetLastError();
+}
+
+template <typename Tr>
+hipError_t launch_point(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
+  if (g.cps == 8) return launch_rows_one<Tr, 8, 1, 1>(g, p, a, s);
+  return g.cps == 4 ? launch_rows_one<Tr, 4, 1, 1>(g, p, a, s) : launch_rows_one<Tr, 2, 1, 1>(g, p, a, s);
 }
 
 unsigned magic16(int d) { return d == 1 ? 0u : (unsigned)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d); }
 
-// Plan with stages of `cps` chunks; ok = 0 where the shape does not allow them.  *cost: estimated clocks.
-RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* cost) {
-  RowsPlan g{};
+// The channel walk of both phases in stages of `cps` chunks; false where the shape does not allow them.
+bool plan_walk(const cg_conv_desc& d, int cps, RowsPlan& g, int& base_k, int& c_cond) {
   g.elem_bytes = d.in_dtype == CG_BF16 ? 2 : 1;
   g.ch = 16 / g.elem_bytes;
   const long long xps = d.x_pixel_stride ? d.x_pixel_stride : d.c_in;
-  if (xps % g.ch) return g;
+  if (xps % g.ch) return false;
   // channels the two phases walk
-  int base_k = d.c_base, c_cond = d.c_in - d.c_base;
+  base_k = d.c_base, c_cond = d.c_in - d.c_base;
   g.gsp = 1;
   if (d.groups > 1) {
     const int cpg = d.c_out / d.groups;
@@ -970,7 +1002,7 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
       base_k = g.gsp * d.c_base;
       c_cond = d.c_in;
     } else {
-      return g;
+      return false;
     }
   }
   if (d.groups <= 1 && base_k % (2 * g.ch) != 0 && base_k % g.ch == 0 && base_k < d.c_in && d.c_in % (2 * g.ch) == 0) {
@@ -983,22 +1015,31 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
     base_k = 2 * d.c_base;
     c_cond = d.c_in;
   }
-  if (base_k % (cps * g.ch) || c_cond % (cps * g.ch)) return g;
-  if (d.c_out % kBn) return g;
+  if (base_k % (cps * g.ch) || c_cond % (cps * g.ch)) return false;
+  if (d.c_out % kBn) return false;
+  g.n_cb = d.c_out / kBn;
+  g.cps = cps;
+  g.stages[0] = base_k / (cps * g.ch);
+  g.stages[1] = c_cond / (cps * g.ch);
+  // 32-bit byte offsets inside the kernel
+  return (long long)d.n_max * d.h * d.w * xps * g.elem_bytes < (1ll << 31);
+}
+
+// Plan with stages of `cps` chunks; ok = 0 where the shape does not allow them.  *cost: estimated clocks.
+RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* cost) {
+  RowsPlan g{};
+  int base_k, c_cond;
+  if (!plan_walk(d, cps, g, base_k, c_cond)) return g;
   const int ho = (d.h + 2 * d.pad - 3) / d.stride + 1, wo = (d.w + 2 * d.pad - 3) / d.stride + 1;
-  // 32-bit byte offsets and 16-bit row numbers inside the kernel
-  if ((long long)d.n_max * d.h * d.w * xps * g.elem_bytes >= (1ll << 31)) return g;
+  // 16-bit row numbers inside the kernel
   if ((long long)d.n_max * ho * wo >= (1ll << 30)) return g;
   if ((long long)d.n_max * (d.h + 2 * d.pad) >= 65536 || (long long)d.n_max * ho >= 65536) return g;
-  g.cps = cps;
-  g.n_cb = d.c_out / kBn;
+  g.taps = 9;
   g.hp = d.h + 2 * d.pad;
   g.logp = 4;
   while ((1 << g.logp) < d.w + d.pad) ++g.logp;
   if ((1 << g.logp) == d.w + d.pad && d.pad) ++g.logp;   // keep a zero slot after the last column
   if (g.logp > 8) return g;
-  g.stages[0] = base_k / (cps * g.ch);
-  g.stages[1] = c_cond / (cps * g.ch);
   const int S = g.stages[0] + g.stages[1], ks = 9 * cps / 2, wb = ks * 2048;
   const long long rows = (long long)d.n_max * ho;
   // which operand an XCD's L2 should see whole: the heavier one
@@ -1103,14 +1144,63 @@ RowsPlan rows_plan(const cg_conv_desc& d, int n_cu, int cps, int max_pf) {
   return a.ok && (!b.ok || c4 <= c2) ? a : b;
 }
 
+RowsPlan point_plan(const cg_conv_desc& d, int n_cu) {
+  RowsPlan g{};
+  int base_k, c_cond;
+  if ((d.in_dtype != CG_BF16 && d.in_dtype != CG_I8) || d.kh != 1 || d.kw != 1 || d.stride != 1 || d.pad != 0) return g;
+  if (!plan_walk(d, 8, g, base_k, c_cond)) {
+    g = RowsPlan{};
+    if (!plan_walk(d, 4, g, base_k, c_cond)) {
+      g = RowsPlan{};
+      if (!plan_walk(d, 2, g, base_k, c_cond)) return g;
+    }
+  }
+  const int wb = g.cps / 2 * 2048;
+  g.taps = 1;
+  g.pf = g.nfc = g.hp = 1;
+  g.fwl = -1;
+  const long long px = (long long)d.n_max * d.h * d.w;
+  if (px >= (1ll << 30)) return g;
+  g.xcd_cb = g.n_cb % 8 == 0 && d.c_out > px ? 1 : 0;
+  long long slots = n_cu / g.n_cb;
+  if (slots < 1) slots = 1;
+  if (slots > (px + 31) / 32) slots = (px + 31) / 32;
+  g.n_slots = (int)slots;
+  // A workgroup's pixels in as few tiles of at most 256 as they take, all of the same size.
+  const long long each = (px + slots - 1) / slots, tiles = (each + 32 * kCw - 1) / (32 * kCw);
+  g.tr = (int)((each + tiles - 1) / tiles);
+  const int S = g.stages[0] + g.stages[1];
+  g.psz = (g.tr * 16 * g.cps + 1023) / 1024 * 1024;
+  g.n_pl = g.psz / 1024;
+  g.shuf_bytes = d.shuffle && d.in_dtype == CG_BF16 && d.out_dtype == CG_BF16 && !(d.epilogue & CG_EPI_RESIDUAL) ? kCw * 32 * kShufRow : 0;
+  const int room = kLds - kTabBytes - g.shuf_bytes;
+  // weights that leave room for four patches stay in LDS
+  g.resident = S * wb + 4 * g.psz <= room ? 1 : 0;
+  g.pstr = g.psz + (g.resident ? 0 : wb);
+  g.nb = (room - (g.resident ? S * wb : 0)) / g.pstr;
+  if (g.nb < 2) return g;
+  if (g.nb > 8) g.nb = 8;
+  int off = g.nb * g.pstr;
+  g.wres = g.resident ? off : -1;
+  if (g.resident) off += S * wb;
+  g.shuf = off;
+  off += g.shuf_bytes;
+  g.tabs = off;
+  g.lds_bytes = off + kTabBytes;
+  g.wpk_base_bytes = (size_t)g.n_cb * g.stages[0] * wb;
+  g.wpk_cond_bytes = (size_t)g.n_cb * g.stages[1] * wb;
+  g.ok = 1;
+  return g;
+}
+
 hipError_t launch_rows_pack(const RowsPlan& g, const Params& p, void* wpk_base, void* wpk_cond, hipStream_t s) {
   for (int ph = 0; ph < 2; ++ph) {
     if (g.stages[ph] == 0) continue;
-    const long long total = (long long)g.n_cb * g.stages[ph] * 3 * (3 * g.cps / 2) * 2 * 64;
+    const long long total = (long long)g.n_cb * g.stages[ph] * (g.taps * g.cps / 2) * 2 * 64;
     const unsigned blocks = (unsigned)((total + 255) / 256);
     hipLaunchKernelGGL(pack_rows_kernel, dim3(blocks), dim3(256), 0, s, (const char*)(ph ? p.w_cond : p.w_base),
                        (char*)(ph ? wpk_cond : wpk_base), ph ? p.c_cond : p.c_base, g.elem_bytes, g.ch, g.cps,
-                       g.stages[ph], total, g.grp_mode == 2 ? 1 : 0, ph, p.c_base, p.cpg);
+                       g.stages[ph], total, g.grp_mode == 2 ? 1 : 0, ph, p.c_base, p.cpg, g.taps);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -1136,13 +1226,13 @@ hipError_t launch_rows(const RowsPlan& g, const Params& p, const void* w0, const
   a.h = p.h;
   a.w = p.w;
   a.ho = p.ho;
-  a.wo = p.wo;
-  a.hp = g.hp;
+  a.wo = g.taps == 1 ? 1 : p.wo;
+  a.hp = g.taps == 1 ? p.ho * p.wo : g.hp;
   a.stride = p.stride;
   a.pad = p.pad;
   a.xps = (int)p.x_pixel_stride * g.elem_bytes;
   a.x_bytes = (unsigned)((((long long)p.n * p.h * p.w - 1) * p.x_pixel_stride + p.c_in) * g.elem_bytes);
-  const int rows = p.n * p.ho;
+  const int rows = g.taps == 1 ? p.n * p.ho * p.wo : p.n * p.ho;
   a.full = rows / (g.n_slots * g.tr);
   const int tail = rows - a.full * g.n_slots * g.tr;
   a.rows_per = tail / g.n_slots;
@@ -1182,10 +1272,11 @@ hipError_t launch_rows(const RowsPlan& g, const Params& p, const void* w0, const
             ((p.epilogue & CG_EPI_AFFINE) && p.in_dtype != CG_I8 ? kAffine : 0u) | ((p.epilogue & CG_EPI_RELU) ? kRelu : 0u) |
             ((p.epilogue & CG_EPI_RESIDUAL) ? kResidual : 0u) |
             ((p.out_dtype == CG_BF16 || (p.out_dtype == CG_I8 && p.rq_shift >= 2)) && (!p.shuffle || shuf2) ? kFast : 0u) | (shuf2 ? kShuf2 : 0u);
-  if (p.in_dtype == CG_I8) return g.cps == 4 ? launch_rows_one<I8Rows, 4, 1>(g, p, a, s) : launch_rows_one<I8Rows, 2, 1>(g, p, a, s);
-  if (g.pf == 2)
-    return g.cps == 4 ? launch_rows_one<Bf16Rows, 4, 2>(g, p, a, s) : launch_rows_one<Bf16Rows, 2, 2>(g, p, a, s);
-  return g.cps == 4 ? launch_rows_one<Bf16Rows, 4, 1>(g, p, a, s) : launch_rows_one<Bf16Rows, 2, 1>(g, p, a, s);
+  if (g.taps == 1)
+    return p.in_dtype == CG_I8 ? launch_point<I8Rows>(g, p, a, s) : launch_point<Bf16Rows>(g, p, a, s);
+  if (p.in_dtype == CG_I8) return g.cps == 4 ? launch_rows_one<I8Rows, 4, 1, 9>(g, p, a, s) : launch_rows_one<I8Rows, 2, 1, 9>(g, p, a, s);
+  if (g.pf == 2) return launch_rows_one<Bf16Rows, 4, 2, 9>(g, p, a, s);     // (planned for stages of four chunks only)
+  return g.cps == 4 ? launch_rows_one<Bf16Rows, 4, 1, 9>(g, p, a, s) : launch_rows_one<Bf16Rows, 2, 1, 9>(g, p, a, s);
 }
 
 }  // namespace cg

@@ -52,6 +52,34 @@ def test_rows_kernel_shapes(shape):
         print("  " + str(P.run_int8(q, thr, name=shape.name + " int8", **kw)), flush=True)
 
 
+POINT = [
+    S(24, 14, 14, 256, 512, k=1, pad=0),
+    S(23, 13, 11, 512, 1024, k=1, pad=0),               # last tile ends inside a fragment
+    S(70, 16, 16, 256, 64, k=1, pad=0),                 # weights stay in LDS
+    S(20, 15, 15, 256, 512, k=1, pad=0, groups=2),      # channel groups: a block inside one
+    S(20, 15, 15, 512, 256, k=1, pad=0, groups=8),      # a block of several
+]
+
+
+@pytest.mark.parametrize("shape", POINT, ids=[s.name for s in POINT])
+def test_point_wise_shapes(shape):
+    rng = np.random.default_rng(shape.n * 13 + shape.c_out)
+    c = shape.c_out
+    aff = dict(scale0=rng.uniform(0.5, 1.5, c), shift0=rng.normal(0, 0.1, c),
+               scale1=rng.uniform(0.5, 1.5, c), shift1=rng.normal(0, 0.1, c))
+    res = rng.standard_normal((shape.n, shape.ho, shape.wo, c)).astype(np.float32)
+    full = B.CG_EPI_RELU | B.CG_EPI_AFFINE | B.CG_EPI_RESIDUAL
+    inp = W.make_inputs(shape, 9400 + c + shape.h, kind="coherent", rho=0.3, round_bf16=True, grouped=shape.groups != 4)
+    gate = W.calibrate_gate(inp, 0.3, sample_images=2)
+    for r in (dict(out_dtype=B.CG_BF16, affine=aff, residual=res, epilogue=full, n_run=shape.n - 1),
+              dict(out_dtype=B.CG_BF16, affine=aff, epilogue=full & ~B.CG_EPI_RESIDUAL, shuffle=inp.grouped),
+              dict(out_dtype=B.CG_F32, tau_c=0.3)):
+        print("\n  " + str(P.run_float(inp, gate, name=shape.name, **r)), flush=True)
+    q = W.quantize_int8(W.make_inputs(shape, 9500 + c + shape.h, kind="coherent", rho=0.35, grouped=inp.grouped))
+    thr = W.calibrate_gate_int8(q, 0.35, sample_images=None)
+    print("  " + str(P.run_int8(q, thr, name=shape.name + " int8")), flush=True)
+
+
 def test_residual_may_be_the_output():
     """y written over the residual (two fragments per wavefront write y twice, which that must not see)."""
     shape = S(130, 14, 14, 256, 256)
