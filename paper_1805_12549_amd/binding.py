@@ -45,6 +45,8 @@ if len(_hip_runtimes_mapped()) > 1:
 
 # the current stream's address without building a Stream object per call
 _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+# torch's caching allocator without a tensor around the block: memory that belongs to one stream (bytes, stream's address)
+_raw_alloc, _raw_free = torch._C._cuda_cudaCachingAllocator_raw_alloc, torch._C._cuda_cudaCachingAllocator_raw_delete
 
 CG_OK, CG_EINVAL, CG_EUNSUPPORTED, CG_ENOMEM, CG_EHIP = 0, 1, 2, 3, 4
 CG_F32, CG_BF16, CG_I8, CG_I32 = 0, 1, 2, 3
@@ -108,6 +110,11 @@ _lib.cg_maxpool3x3s2.argtypes = [C.c_void_p, C.c_void_p] + [C.c_int32] * 4 + [C.
 _lib.cg_maxpool3x3s2.restype = C.c_int
 _lib.cg_avgpool_fc.argtypes = [C.c_void_p] * 4 + [C.c_int32] * 4 + [C.c_void_p]
 _lib.cg_avgpool_fc.restype = C.c_int
+
+
+def current_stream_ptr() -> int:
+    """Address of the current device's current stream."""
+    return _raw_stream(_current_device())
 
 
 class CGError(RuntimeError):
@@ -285,13 +292,12 @@ class GatedConv:
         self.n_max, self.c_out, self.out_dtype = n_max, c_out, out_dtype
         self.words = (c_out + 31) // 32
         self._y_dtype = getattr(torch, _TORCH_OUT[out_dtype])
-        self._ws = None
         self._ws_need = {}      # workspace bytes per batch size
 
     def _stream_ptr(self):
         if self.stream is not None:
             return self.stream.cuda_stream
-        return _raw_stream(_current_device())
+        return current_stream_ptr()
 
     def forward(self, x, residual=None, y=None, bitmap=True, counts=True):
         """x: torch device tensor [n,H,W,C_in] (contiguous NHWC).  Returns (y, bitmap, counts)."""
@@ -310,14 +316,19 @@ class GatedConv:
         need = self._ws_need.get(n)
         if need is None:
             need = self._ws_need[n] = cg_conv_workspace_bytes(self.handle, n)
-        ws_ptr = 0
-        if need:
-            if self._ws is None or self._ws.numel() < need + 256:
-                self._ws = empty(need + 256, dtype=self._torch.uint8, device=x.device)
-            ws_ptr = (self._ws.data_ptr() + 255) & ~255
-        rc = _lib.cg_conv_forward(self.handle, n, x.data_ptr(), 0 if residual is None else residual.data_ptr(), y.data_ptr(),
-                                  0 if bitmap is None else bitmap.data_ptr(), 0 if counts is None else counts.data_ptr(),
-                                  ws_ptr, need, self._stream_ptr())
+        stream = self._stream_ptr()
+        # The workspace belongs to this call: taken from the stream's share of the caching allocator and given back once
+        # the kernels are enqueued, it serves later work of the same stream only, and under capture it is the graph's own.
+        # (One kept by the layer was shared by its calls on all streams, and a graph held its address after a larger
+        # batch had replaced it.)
+        ws_ptr = _raw_alloc(need, stream) if need else 0
+        try:
+            rc = _lib.cg_conv_forward(self.handle, n, x.data_ptr(), 0 if residual is None else residual.data_ptr(), y.data_ptr(),
+                                      0 if bitmap is None else bitmap.data_ptr(), 0 if counts is None else counts.data_ptr(),
+                                      ws_ptr, need, stream)
+        finally:
+            if ws_ptr:
+                _raw_free(ws_ptr)
         if rc != CG_OK:
             raise CGError(rc, cg_last_error())
         return y, bitmap, counts

@@ -61,7 +61,7 @@ class _Shortcut:
         ho = (s.hw - 1) // 2 + 1
         y = torch.empty((n, ho, ho, s.c_out), dtype=torch.bfloat16, device=x.device)
         B.cg_pointwise_conv(x.data_ptr(), self.w.data_ptr(), self.scale.data_ptr(), self.shift.data_ptr(), y.data_ptr(),
-                            n, s.hw, s.hw, s.c_in, s.c_out, 2, False, torch.cuda.current_stream().cuda_stream)
+                            n, s.hw, s.hw, s.c_in, s.c_out, 2, False, B.current_stream_ptr())
         return y, None, None
 
     def close(self):
@@ -99,7 +99,7 @@ class GatedResNet18:
 
     # -- building blocks -------------------------------------------------------------------------
     def _stream(self):
-        return torch.cuda.current_stream().cuda_stream
+        return B.current_stream_ptr()
 
     def _input_layer(self, x, keep_conv=True):
         """The input convolution and the max pooling; keep_conv=False runs them fused (the pooled tensor only)."""
