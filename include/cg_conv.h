@@ -79,7 +79,10 @@ typedef struct cg_conv_desc {
                                 output group i takes input group i as x_p and the other input groups, in
                                 increasing channel order, as x_r.  The weight layouts stay as below: per
                                 output channel, w_base holds its c_base base-path weights and w_cond the
-                                weights of its c_in - c_base conditional channels in that order. */
+                                weights of its c_in - c_base conditional channels in that order.  Where a
+                                group has fewer than 64 output channels the two tiled kernels (see CG_VARIANT_*) walk the
+                                channels of several groups together, with zero weights between them: there an
+                                infinite or NaN input may turn sums of the neighbouring groups into NaN. */
   int64_t x_pixel_stride;    /* elements between pixels of x; 0 means c_in */
 
   const void* w_base;        /* DEVICE [c_out][kh][kw][c_base] */

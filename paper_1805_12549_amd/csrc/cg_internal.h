@@ -120,6 +120,7 @@ struct DirectPlan {
   // first group and walks chunks[0] of them; the conditional phase walks all chunks but the gap_len ones
   // from there on.  strad: bytes of the base group in its last, partly used chunk (ungrouped layers).
   int chunks[2], total_chunks, gap_len, strad;
+  int mixed;               // channel grouping: zero weights keep channels apart that a block walks together
   int ksteps[2];           // K steps (four chunks) per phase
   int n_grp;               // 32-channel groups of the packed weights
   size_t wpk_bytes[2];

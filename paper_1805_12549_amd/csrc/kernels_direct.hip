@@ -37,7 +37,9 @@ struct Bf16Direct {
   using Base = Bf16Traits;
   using acc4 = f32x4;
   using acc_t = float;
+  static constexpr int kCh = 8;
   static __device__ __forceinline__ acc4 mma(i32x4 rows, i32x4 cols, acc4 c) { return Bf16Traits::mfma(rows, cols, c); }
+  static __device__ __forceinline__ float element(i32x4 v, int e) { return __uint_as_float(e & 1 ? (unsigned)v[e >> 1] & 0xffff0000u : (unsigned)v[e >> 1] << 16); }
 };
 
 struct I8Direct {
@@ -58,6 +60,8 @@ struct F32Direct {
   using Base = F32Traits;
   using acc4 = f32x4;
   using acc_t = float;
+  static constexpr int kCh = 4;
+  static __device__ __forceinline__ float element(i32x4 v, int e) { return __int_as_float(v[e]); }
   static __device__ __forceinline__ acc4 mma(i32x4 rows, i32x4 cols, acc4 c) {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
@@ -280,7 +284,12 @@ __device__ __forceinline__ void finish_unit(const DirectArgs& a, acc_t (&s)[4], 
 // 8 wavefronts per workgroup at most
 constexpr int kMaxSplit = 8;
 
-template <typename Tr, int PF, int CG, bool SPLIT>
+// MIXED: float layers whose blocks cover several channel groups (Sec. 3.3) or whose groups share a chunk.  The packed
+// weights are zero where a channel is not on a row's path, which keeps its finite values out of the row's sum but turns
+// an infinity or a NaN into a NaN; a wavefront that ends up with a NaN forms its sums again, from the path's channels
+// alone.  (The look at the sums costs 1 to 2 %: 96 channels at 56x56 in four groups, 16 images 52.4 -> 52.9 us, 128 at 28x28,
+// two images 11.2 -> 11.4; one at every operand, as it is read, 5 to 7 %.)
+template <typename Tr, int PF, int CG, bool SPLIT, bool MIXED>
 __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, 2) void gated_conv_direct_kernel(DirectArgs p) {
   using Base = typename Tr::Base;
   using acc4 = typename Tr::acc4;
@@ -428,6 +437,62 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, 2) void gated_conv_di
       if (i + 1 < nb) {
         if (i + 2 < nb) fetch(B0{});
         mul(B1{});
+      }
+    }
+    if constexpr (MIXED) {
+      bool nan = false;
+#pragma unroll
+      for (int f = 0; f < PF; ++f)
+#pragma unroll
+        for (int c = 0; c < CG; ++c)
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) nan |= a[f][c][h][e] != a[f][c][h][e];
+      if (__ballot(nan) == 0ull) return;
+      // (a lane's rows are 8*lg .. 8*lg + 7 of each group; the unit, and with it the channel, is the same for all lanes)
+      int row_grp[CG][2][4];
+#pragma unroll
+      for (int c = 0; c < CG; ++c)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            row_grp[c][h][e] = ((grp0 + c) * 32 + 8 * lg + 4 * h + e) / p.cpg;
+#pragma unroll
+            for (int f = 0; f < PF; ++f) a[f][c][h][e] = 0.0f;
+          }
+#pragma nounroll
+      for (int u = 4 * k0; u < 4 * k1; ++u) {
+        const int t = u / nq, chunk = cfirst + u - t * nq, r = (t * 11) >> 5;
+        if (t >= p.taps || chunk >= p.total_chunks) continue;
+        i32x4 xv[PF];
+#pragma unroll
+        for (int f = 0; f < PF; ++f) {
+          const int off = xbase[f] + r * rowb + (t - 3 * r) * p.xps + chunk * 16;
+          xv[f] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, ((vmask[f] >> t) & 1u) ? off : -1, 0, 0));
+        }
+        int ch_grp[Tr::kCh];
+#pragma unroll
+        for (int i = 0; i < Tr::kCh; ++i) ch_grp[i] = (chunk * Tr::kCh + i) / p.c_base;
+        const char* wu = wp - lane * 16 + (size_t)(u >> 2) * 2048 + (u & 3) * 256 + lg * 64;
+#pragma unroll
+        for (int c = 0; c < CG; ++c)
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const i32x4 wv = *(const i32x4*)(wu + c * wgrp + h * 1024 + e * 16);
+#pragma unroll
+              for (int i = 0; i < Tr::kCh; ++i) {
+                const bool on = (ch_grp[i] == row_grp[c][h][e]) == (ph == 0);
+#pragma unroll
+                for (int f = 0; f < PF; ++f) {
+                  const float old = a[f][c][h][e];
+                  a[f][c][h][e] = on ? fmaf(Tr::element(xv[f], i), Tr::element(wv, i), old) : old;
+                }
+              }
+            }
       }
     }
   };
@@ -666,15 +731,23 @@ __global__ void pack_direct_kernel(const T* __restrict__ wb, const T* __restrict
   for (int e = 0; e < CH; ++e) out[id * CH + e] = v[e];
 }
 
+template <typename Tr, int PF, int CG, bool MIXED>
+hipError_t launch_direct_form(const DirectPlan& g, const DirectArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)a.per_xcd * 8u);
+  if (g.split == 1)
+    hipLaunchKernelGGL((gated_conv_direct_kernel<Tr, PF, CG, false, MIXED>), grid, dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL((gated_conv_direct_kernel<Tr, PF, CG, true, MIXED>), grid, dim3(64 * g.split), 0, s, a);
+  return hipGetLastError();
+}
+
 template <typename Tr, int PF, int CG>
 hipError_t launch_direct_tile(const DirectPlan& g, const DirectArgs& a, hipStream_t s) {
-  const dim3 grid((unsigned)a.per_xcd * 8u);
-  if (g.split == 1) {
-    hipLaunchKernelGGL((gated_conv_direct_kernel<Tr, PF, CG, false>), grid, dim3(256), 0, s, a);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL((gated_conv_direct_kernel<Tr, PF, CG, true>), grid, dim3(64 * g.split), 0, s, a);
-  const hipError_t e = hipGetLastError();
+  hipError_t e;
+  if constexpr (Tr::Base::kDtype == CG_I8)
+    e = launch_direct_form<Tr, PF, CG, false>(g, a, s);
+  else
+    e = g.mixed ? launch_direct_form<Tr, PF, CG, true>(g, a, s) : launch_direct_form<Tr, PF, CG, false>(g, a, s);
   if (e != hipSuccess || g.slices == 1) return e;
   hipLaunchKernelGGL((direct_finish_kernel<Tr, PF, CG>), dim3((unsigned)(g.px_wgs * g.n_cblk)), dim3(PF * CG * 128), 0, s, a);
   return hipGetLastError();
@@ -729,6 +802,7 @@ DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu) {
       if (ga != gb) single = false;
     }
     g.gap_len = single ? d.c_base / g.ch : 0;
+    g.mixed = single ? 0 : 1;
   }
   g.chunks[1] = gated ? g.total_chunks - g.gap_len : 0;
   for (int ph = 0; ph < 2; ++ph) {

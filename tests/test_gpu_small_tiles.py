@@ -85,3 +85,37 @@ def test_base_group_inside_a_chunk_keeps_the_paths_apart():
     assert int(bitmap.abs().sum()) == 0 and int(counts[0]) == 0
     assert float(y.max()) == 36.0 and float(y.min()) == 16.0
     layer.close()
+
+
+@pytest.mark.parametrize("in_dtype", [B.CG_F32, B.CG_BF16], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("n,h,w,cin,cout,groups", [(1, 9, 7, 64, 64, 4), (2, 8, 10, 96, 48, 4), (1, 8, 8, 32, 48, 16), (40, 33, 31, 16, 64, 4)],
+                         ids=["split", "one_group_a_fragment", "groups_inside_a_chunk", "one_wavefront_a_tile"])
+def test_grouped_layers_keep_infinities_in_their_group(in_dtype, n, h, w, cin, cout, groups):
+    """An infinite input reaches the base sums of its own group and the conditional sums of the others, and nothing else.
+    Weights are ones and finite inputs small whole numbers, so every sum is exact and the reference is a plain sum."""
+    import torch
+    dt = torch.float32 if in_dtype == B.CG_F32 else torch.bfloat16
+    cb, cpg = cin // groups, cout // groups
+    x = torch.ones((n, h, w, cin), dtype=torch.float64)
+    x[:, :, w // 2:, :] = 2.0
+    for g in range(groups):
+        x[g % n, (3 * g) % h, (5 * g) % w, g * cb + g % cb] = float("inf")
+    thr = 9.0 * cb + 0.5                                               # the left half's base sums stay below
+    layer = B.GatedConv(n_max=n, h=h, w=w, c_in=cin, c_out=cout, c_base=cb, groups=groups, in_dtype=in_dtype, out_dtype=B.CG_F32,
+                        w_base=torch.ones((cout, 3, 3, cb), dtype=dt, device="cuda"),
+                        w_cond=torch.ones((cout, 3, 3, cin - cb), dtype=dt, device="cuda"),
+                        gate_mean=np.zeros(cout), gate_var=np.ones(cout), delta=np.full(cout, thr))
+    y, bitmap, _ = layer.forward(x.to(dt).cuda())
+    torch.cuda.synchronize()
+    layer.close()
+    xp = torch.nn.functional.pad(x, (0, 0, 1, 1, 1, 1))
+    per_group = [sum(xp[:, r:r + h, c:c + w, g * cb:(g + 1) * cb].sum(-1) for r in range(3) for c in range(3)) for g in range(groups)]
+    want = torch.empty((n, h, w, cout), dtype=torch.float64)
+    for g in range(groups):
+        rest = sum(per_group[k] for k in range(groups) if k != g)
+        want[..., g * cpg:(g + 1) * cpg] = torch.where(per_group[g] >= thr, per_group[g] + rest, per_group[g])[..., None]
+    assert torch.isfinite(want).any() and torch.isinf(want).any()
+    assert torch.equal(y.cpu().double(), want)
+    fired = torch.from_numpy(W.unpack_bitmap(bitmap.cpu().numpy().view(np.uint32), cout)).reshape(n, h, w, cout).bool()
+    base = torch.stack(per_group, -1).repeat_interleave(cpg, -1)
+    assert torch.equal(fired, base >= thr)
