@@ -514,30 +514,36 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
 }
 
 namespace {
-// Workspace layout: [decision bitmap of the batch][channel mask][partial sums].  Fired gates are counted from a
-// decision bitmap; it goes to the workspace when the caller asks for counts without a bitmap, and so
+// Workspace layout: [decisions: the batch's bitmap, or (kCounting) its counts][channel mask][partial sums].  Fired gates
+// are counted from a decision bitmap; it goes to the workspace when the caller asks for counts without a bitmap, and so
 // does the first pass of the channel-wise gate.  The mask exists only with the channel-wise gate, the
 // partial sums only where several workgroups share a tile's K.
 struct WsLayout {
-  size_t bitmap_off, bitmap_bytes, mask_off, mask_bytes, partial_off, total;
+  size_t dec_off, dec_bytes, mask_off, mask_bytes, partial_off, total;
 };
-WsLayout ws_layout(const cg_conv* h, int32_t n, const CallPlan& c) {
+// What a call gets of it: what any call may need (the caller's workspace); what this call needs; or what the plain kernel
+// needs when it counts the fired gates itself (an image whose bitmap does not fit the scratch array).
+enum Scratch { kAnyCall, kThisCall, kCounting };
+WsLayout ws_layout(const cg_conv* h, int32_t n, const CallPlan& c, Scratch mode, bool counts_only) {
   WsLayout w{};
   const size_t words = (size_t)(h->d.c_out + 31) / 32;
-  const bool chan_gate = h->c_cond > 0 && h->d.tau_c > 0.0f;
-  if (h->c_cond > 0) w.bitmap_bytes = align256((size_t)n * h->ho * h->wo * words * 4);
+  const bool gated = h->c_cond > 0, chan_gate = gated && h->d.tau_c > 0.0f;
+  if (mode == kCounting)
+    w.dec_bytes = chan_gate ? align256((size_t)n * h->d.c_out * 4 + 8) : 0;
+  else if (gated && (mode == kAnyCall || chan_gate || counts_only))
+    w.dec_bytes = align256((size_t)n * h->ho * h->wo * words * 4);
   if (chan_gate) w.mask_bytes = align256((size_t)n * words * 4);
-  w.bitmap_off = 0;
-  w.mask_off = w.bitmap_bytes;
+  w.dec_off = 0;
+  w.mask_off = w.dec_bytes;
   w.partial_off = w.mask_off + w.mask_bytes;
-  w.total = w.partial_off + (c.kernel == kDirect ? align256(c.direct.partial_bytes) : 0);
+  w.total = w.partial_off + (c.kernel == kDirect && mode != kCounting ? align256(c.direct.partial_bytes) : 0);
   return w;
 }
 }  // namespace
 
 size_t cg_conv_workspace_bytes(const cg_conv* h, int32_t n) {
   if (!h || n <= 0) return 0;
-  return ws_layout(h, n, call_plan(h, n)).total;
+  return ws_layout(h, n, call_plan(h, n), kAnyCall, true).total;
 }
 
 int cg_conv_info(const cg_conv* h, int32_t* ho, int32_t* wo) {
@@ -553,7 +559,7 @@ namespace {
 
 // counts: [n][c_out] fired counts; total: their sum, cleared first if clear_total (both NULL or neither)
 int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap,
-                 uint32_t* counts, uint32_t* total, bool clear_total, void* workspace, size_t workspace_bytes,
+                 uint32_t* counts, uint32_t* total, bool clear_total, Scratch mode, void* workspace, size_t workspace_bytes,
                  void* hip_stream);
 
 }  // namespace
@@ -562,43 +568,51 @@ extern "C" {
 
 int cg_conv_forward(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap,
                     uint32_t* counts, void* workspace, size_t workspace_bytes, void* hip_stream) {
-  return forward_impl(h, n, x, residual, y, bitmap, counts ? counts + 2 : nullptr, counts, true, workspace, workspace_bytes,
-                      hip_stream);
+  return forward_impl(h, n, x, residual, y, bitmap, counts ? counts + 2 : nullptr, counts, true, kAnyCall, workspace,
+                      workspace_bytes, hip_stream);
 }
 
 int cg_conv_forward_noalloc(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap,
                             uint32_t* counts, void* hip_stream) {
   if (!h) return fail(CG_EINVAL, "handle is NULL");
   if (n < 0 || n > h->d.n_max) return fail(CG_EINVAL, "n = %d is outside [0, n_max = %d]", n, h->d.n_max);
-  const size_t need = n > 0 ? cg_conv_workspace_bytes(h, n) : 0;
-  if (need > kScratchBytes && h->variant == CG_VARIANT_NAIVE && cg_conv_workspace_bytes(h, 1) <= kScratchBytes && x && y) {
-    // layers of this family take any batch: as many images at a time as the scratch array serves
-    const cg_conv_desc& d = h->d;
-    const int step = (int)(kScratchBytes / cg_conv_workspace_bytes(h, 1));
-    void* ws = scratch_of_current_device();
-    if (!ws) return CG_EHIP;
-    const size_t xi = (size_t)d.h * d.w * d.x_pixel_stride * elem_bytes(d.in_dtype), px = (size_t)h->ho * h->wo;
-    const size_t yi = px * d.c_out * elem_bytes(d.out_dtype);
-    const size_t ri = px * d.c_out * elem_bytes(d.in_dtype == CG_I8 ? CG_I8 : d.out_dtype);
-    for (int i = 0; i < n; i += step) {
-      const int m = n - i < step ? n - i : step;
-      const int rc = forward_impl(h, m, (const char*)x + i * xi, residual ? (const char*)residual + i * ri : nullptr,
-                                  (char*)y + i * yi, bitmap ? bitmap + i * px * ((d.c_out + 31) / 32) : nullptr,
-                                  counts ? counts + 2 + (size_t)i * d.c_out : nullptr, counts, i == 0, ws, kScratchBytes,
-                                  hip_stream);
-      if (rc != CG_OK) return rc;
+  if (n == 0) return CG_OK;
+  Scratch mode = kAnyCall;
+  int step = n;                          // images at a time
+  if (h->variant == CG_VARIANT_NAIVE) {
+    // Layers of this family take any batch: as many images at a time as the scratch array serves, and one at a time,
+    // counted without a bitmap, where not even one image's bitmap fits.
+    const bool counts_only = counts && !bitmap;
+    mode = kThisCall;
+    if (ws_layout(h, n, call_plan(h, n), mode, counts_only).total > kScratchBytes) {
+      const size_t one = ws_layout(h, 1, call_plan(h, 1), mode, counts_only).total;
+      if (one > kScratchBytes) mode = kCounting;
+      step = one > kScratchBytes ? 1 : (int)(kScratchBytes / one);
     }
-    return CG_OK;
   }
+  const size_t need = mode == kAnyCall ? cg_conv_workspace_bytes(h, n) : 0;
   if (need > kScratchBytes)
     return fail(CG_EUNSUPPORTED, "this call needs %zu bytes of scratch; the library's fixed scratch array holds %zu",
                 need, kScratchBytes);
-  void* ws = nullptr;
-  if (need > 0) {
-    ws = scratch_of_current_device();
-    if (!ws) return CG_EHIP;
+  void* ws = scratch_of_current_device();
+  if (!ws) return CG_EHIP;
+  if (step == n)
+    return forward_impl(h, n, x, residual, y, bitmap, counts ? counts + 2 : nullptr, counts, true, mode, ws, kScratchBytes,
+                        hip_stream);
+  if (!x || !y) return fail(CG_EINVAL, "x and y must not be NULL");
+  const cg_conv_desc& d = h->d;
+  const size_t xi = (size_t)d.h * d.w * d.x_pixel_stride * elem_bytes(d.in_dtype), px = (size_t)h->ho * h->wo;
+  const size_t yi = px * d.c_out * elem_bytes(d.out_dtype);
+  const size_t ri = px * d.c_out * elem_bytes(d.in_dtype == CG_I8 ? CG_I8 : d.out_dtype);
+  for (int i = 0; i < n; i += step) {
+    const int m = n - i < step ? n - i : step;
+    const int rc = forward_impl(h, m, (const char*)x + i * xi, residual ? (const char*)residual + i * ri : nullptr,
+                                (char*)y + i * yi, bitmap ? bitmap + i * px * ((d.c_out + 31) / 32) : nullptr,
+                                counts ? counts + 2 + (size_t)i * d.c_out : nullptr, counts, i == 0, mode, ws, kScratchBytes,
+                                hip_stream);
+    if (rc != CG_OK) return rc;
   }
-  return forward_impl(h, n, x, residual, y, bitmap, counts ? counts + 2 : nullptr, counts, true, ws, need, hip_stream);
+  return CG_OK;
 }
 
 void cg_conv_destroy(cg_conv* h) { delete h; }
@@ -608,7 +622,7 @@ void cg_conv_destroy(cg_conv* h) { delete h; }
 namespace {
 
 int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap,
-                 uint32_t* counts, uint32_t* total, bool clear_total, void* workspace, size_t workspace_bytes,
+                 uint32_t* counts, uint32_t* total, bool clear_total, Scratch mode, void* workspace, size_t workspace_bytes,
                  void* hip_stream) {
   if (!h) return fail(CG_EINVAL, "handle is NULL");
   if (n < 0 || n > h->d.n_max) return fail(CG_EINVAL, "n = %d is outside [0, n_max = %d]", n, h->d.n_max);
@@ -621,7 +635,7 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
   if (h->variant != CG_VARIANT_NAIVE && !aligned)
     return fail(CG_EINVAL, "x, y, residual and bitmap must be 16-byte aligned");
   CallPlan cp = call_plan(h, n);
-  const WsLayout wl = ws_layout(h, n, cp);
+  const WsLayout wl = ws_layout(h, n, cp, mode, counts && !bitmap);
   const size_t need = wl.total;
   if (need > 0 && (!workspace || workspace_bytes < need))
     return fail(CG_EINVAL, "workspace of %zu bytes is smaller than the %zu required", workspace_bytes, need);
@@ -641,7 +655,7 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
   p.total = total;
   p.clear_total = counts && clear_total;
 
-  if (!aligned) cp.kernel = kNaive;      // (the plain kernel is the layer's family: the others were turned away)
+  if (!aligned || mode == kCounting) cp.kernel = kNaive;      // (the plain kernel is the layer's family: the others were turned away)
   if (cp.kernel == kRows && cp.rows.pf == 2 && residual) {
     // Two fragments per wavefront write an output twice and read the residual after the first time.
     const char *y0 = (const char*)y, *r0 = (const char*)residual;
@@ -675,24 +689,37 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
     q.y = nullptr;
     q.counts = q.total = nullptr;
     q.clear_total = 0;
-    q.bitmap = (uint32_t*)(ws + wl.bitmap_off);
-    e = launch(q);
-    if (e == hipSuccess) e = cg::launch_bitmap_chan_mask(q, q.bitmap, need_u, mask, s);
+    q.bitmap = nullptr;
+    if (mode == kCounting) {
+      q.total = (uint32_t*)(ws + wl.dec_off);
+      q.counts = q.total + 2;
+      q.count_here = 1;
+      e = cg::launch_zero_u32(q.total, 2 + (size_t)n * d.c_out, s);
+      if (e == hipSuccess) e = launch(q);
+      if (e == hipSuccess) e = cg::launch_counts_chan_mask(q, q.counts, need_u, mask, s);
+    } else {
+      q.bitmap = (uint32_t*)(ws + wl.dec_off);
+      e = launch(q);
+      if (e == hipSuccess) e = cg::launch_bitmap_chan_mask(q, q.bitmap, need_u, mask, s);
+    }
     p.chan_mask = mask;
   }
+  if (e == hipSuccess && counts && (!p.gated || mode == kCounting))       // (the first call's counts follow the total)
+    e = clear_total ? cg::launch_zero_u32(total, 2 + (size_t)n * d.c_out, s) : cg::launch_zero_u32(counts, (size_t)n * d.c_out, s);
   if (!p.gated) {
     // a dense layer has no decisions
-    if (e == hipSuccess && counts)       // (the first call's counts follow the total)
-      e = clear_total ? cg::launch_zero_u32(total, 2 + (size_t)n * d.c_out, s) : cg::launch_zero_u32(counts, (size_t)n * d.c_out, s);
     if (e == hipSuccess && bitmap) e = cg::launch_zero_u32(bitmap, (size_t)p.m_total * p.words, s);
     p.counts = p.total = nullptr;
     p.clear_total = 0;
     p.bitmap = nullptr;
+  } else if (counts && mode == kCounting) {
+    p.count_here = 1;
+    p.clear_total = 0;
   } else if (counts && !bitmap) {
-    p.bitmap = (uint32_t*)(ws + wl.bitmap_off);   // free again once the mask exists
+    p.bitmap = (uint32_t*)(ws + wl.dec_off);      // free again once the mask exists
   }
   if (e == hipSuccess) e = launch(p);
-  if (e == hipSuccess && counts && p.gated) e = cg::launch_bitmap_counts(p, p.bitmap, s);
+  if (e == hipSuccess && counts && p.gated && !p.count_here) e = cg::launch_bitmap_counts(p, p.bitmap, s);
   if (e != hipSuccess) return fail(CG_EHIP, "cg_conv_forward: %s", hipGetErrorString(e));
   return CG_OK;
 }

@@ -51,6 +51,7 @@ struct Params {
   uint32_t* counts;        // [n][c_out] fired counts, or NULL; counted from the bitmap after the layer kernel
   uint32_t* total;         // their 64-bit sum (two words), or NULL; counting adds to it
   int clear_total;         // the layer kernel zeroes the total
+  int count_here;          // plain kernel: adds to counts and total itself (both cleared before), no bitmap needed
 };
 
 // Geometry of the large-tile matrix-core kernel (kernels_tile.hip): four wavefronts per workgroup,
@@ -174,6 +175,8 @@ hipError_t launch_bitmap_counts(const Params& p, const uint32_t* bitmap, hipStre
 // channel-wise gate: mask[img][w] bit b = (fired count of channel 32*w + b in image img, from the bitmap) >= need
 hipError_t launch_bitmap_chan_mask(const Params& p, const uint32_t* bitmap, uint32_t need, uint32_t* mask,
                                    hipStream_t s);
+// the same from [n][c_out] fired counts
+hipError_t launch_counts_chan_mask(const Params& p, const uint32_t* counts, uint32_t need, uint32_t* mask, hipStream_t s);
 
 // launchers (return hipError_t from the last launch)
 hipError_t launch_naive(const Params& p, hipStream_t s);

@@ -85,6 +85,18 @@ __global__ void bitmap_counts_small_kernel(const uint32_t* __restrict__ bitmap, 
   }
 }
 
+// the channel mask from counts: one thread per word
+__global__ void counts_chan_mask_kernel(const uint32_t* __restrict__ counts, int words, int c_out, long long items, uint32_t need,
+                                        uint32_t* __restrict__ mask) {
+  const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (id >= items) return;
+  const int w = (int)(id % words);
+  const long long img = id / words;
+  uint32_t keep = 0u;
+  for (int b = 0; b < 32 && w * 32 + b < c_out; ++b) keep |= (counts[img * c_out + w * 32 + b] >= need ? 1u : 0u) << b;
+  mask[id] = keep;
+}
+
 }  // namespace
 
 namespace {
@@ -115,6 +127,14 @@ hipError_t launch_bitmap_chan_mask(const Params& p, const uint32_t* bitmap, uint
   }
   hipLaunchKernelGGL(bitmap_counts_kernel, dim3((unsigned)blocks), dim3(256), 0, s, bitmap, p.words, p.ho * p.wo,
                      p.c_out, (uint32_t*)nullptr, (unsigned long long*)nullptr, mask, need);
+  return hipGetLastError();
+}
+
+hipError_t launch_counts_chan_mask(const Params& p, const uint32_t* counts, uint32_t need, uint32_t* mask, hipStream_t s) {
+  const long long items = (long long)p.n * p.words;
+  if (items <= 0) return hipSuccess;
+  hipLaunchKernelGGL(counts_chan_mask_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, counts, p.words, p.c_out,
+                     items, need, mask);
   return hipGetLastError();
 }
 

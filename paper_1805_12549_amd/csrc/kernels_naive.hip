@@ -109,6 +109,10 @@ __global__ __launch_bounds__(256) void naive_kernel(Params p) {
   if (p.bitmap && (lane & 31) == 0 && m < p.m_total)
     p.bitmap[t >> 5] = (uint32_t)(lane ? (mask >> 32) : mask);
   if (p.clear_total && t < 2) p.total[t] = 0u;
+  if (p.count_here) {
+    if (fired) atomicAdd(p.counts + m / ((long long)p.ho * p.wo) * p.c_out + co, 1u);
+    if (lane == 0 && mask) atomicAdd((unsigned long long*)p.total, (unsigned long long)__popcll(mask));
+  }
 }
 
 __global__ void zero_u32_kernel(uint32_t* ptr, size_t words) {

@@ -80,3 +80,27 @@ def test_noalloc_refuses_what_does_not_fit():
     # zero weights and zero thresholds: every gate fires (0 >= 0)
     assert int(cnt[0]) == 2 * 112 * 112 * 256
     layer.close()
+
+
+@pytest.mark.parametrize("tau_c", [0.0, 0.3], ids=["plain_gate", "channel_gate"])
+def test_noalloc_takes_images_whose_bitmap_does_not_fit(tau_c):
+    """A layer outside the tiled families on images of 2100 x 2100 pixels: one image's bitmap (17.6 MB) is larger than the
+    array; the fired gates are then counted without one, an image at a time."""
+    shape = W.LayerShape("na_16@2100", 2, 2100, 2100, 16, 16)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    x = torch.randint(0, 60, (2, 2100, 2100, 16), generator=gen, device="cuda", dtype=torch.int8)
+    w = torch.randint(-60, 60, (16, 3, 3, 16), generator=gen, device="cuda", dtype=torch.int8)
+    thr = np.linspace(-30000, 30000, 16).astype(np.int32)             # from nearly all to nearly none
+    layer = B.GatedConv(n_max=2, h=2100, w=2100, c_in=16, c_out=16, c_base=4, w_base=w[..., :4].contiguous(),
+                        w_cond=w[..., 4:].contiguous(), in_dtype=B.CG_I8, out_dtype=B.CG_I32, gate_thr_i32=thr, tau_c=tau_c)
+    assert B.cg_conv_workspace_bytes(layer.handle, 1) > (16 << 20)
+    for n in (1, 2):
+        for want_bitmap in (True, False):
+            ref = _call(layer, x[:n], n, False, want_bitmap)
+            if tau_c and want_bitmap:
+                assert 0 < int((ref[1][2:] == 0).sum()) < n * 16      # the channel-wise gate closed some channels
+            got = _call(layer, x[:n], n, True, want_bitmap)
+            for u, v in zip(ref, got):
+                assert u is None or torch.equal(u, v)
+    layer.close()
