@@ -79,7 +79,8 @@ struct CallPlan {
   Kernel kernel;
   cg::RowsPlan rows;
   cg::TilePlan tile;
-  cg::DirectPlan direct;
+  cg::DirectPlan direct, direct_rest;    // for `piece` images at a time and for what is left (none where piece divides n)
+  int piece;
 };
 
 }  // namespace
@@ -88,7 +89,7 @@ struct cg_conv {
   cg_conv_desc d;           // copy of the descriptor (host pointers are dead after create)
   int ho, wo, c_cond;
   int variant;              // resolved CG_VARIANT_*: the kernel family that covers the shape
-  bool direct_ok;           // the small-tile kernel's weights are packed too
+  bool direct_ok;           // the small-tile kernel's weights are packed too: it takes the layer, if not every batch of it
   bool point_ok;            // a 1x1 layer of the large-tile family that runs on the row-tiled kernel
   CallPlan first;           // plan for n_max
   Layout lay;
@@ -238,7 +239,7 @@ int resolve_variant(const cg_conv_desc& d, Plans* pl) {
     pl->point_ok = q.ok != 0;
     if (q.ok) pl->v3 = q;
   }
-  pl->vd = cg::direct_plan(d, d.n_max, cu_count());
+  pl->vd = cg::direct_plan(d, 1, cu_count());          // (what is packed does not depend on the batch)
   pl->direct_ok = d.variant == CG_VARIANT_AUTO && pl->vd.ok;      // (a family that was asked for by name is what runs)
   pl->wpd_base_bytes = pl->direct_ok ? pl->vd.wpk_bytes[0] : 0;
   pl->wpd_cond_bytes = pl->direct_ok ? pl->vd.wpk_bytes[1] : 0;
@@ -246,6 +247,24 @@ int resolve_variant(const cg_conv_desc& d, Plans* pl) {
   pl->wpk_base_bytes = rows ? pl->v3.wpk_base_bytes : v == CG_VARIANT_TILE ? pl->v4.wpk_base_bytes : 0;
   pl->wpk_cond_bytes = rows ? pl->v3.wpk_cond_bytes : v == CG_VARIANT_TILE ? pl->v4.wpk_cond_bytes : 0;
   return CG_OK;
+}
+
+// The small-tile kernel's plan for a batch.  Its 32-bit offsets reach over 1 GiB of x and 2^30 pixels; where the plain kernel
+// would be the other choice, a larger batch runs in pieces (of whole images: every pointer stays aligned as the pixels are).
+// int8, 16 channels at 512x512, 300 images: 167 -> 9.0 ms.
+void plan_direct(const cg_conv* h, int n, CallPlan* c) {
+  c->direct = c->direct_rest = cg::DirectPlan{};
+  c->piece = n;
+  if (!h->direct_ok) return;
+  c->direct = cg::direct_plan(h->d, n, cu_count());
+  if (c->direct.ok || h->variant != CG_VARIANT_NAIVE || h->point_ok) return;
+  const long long limit = (1ll << 30) - 1, image = (long long)h->d.h * h->d.w * h->d.x_pixel_stride * elem_bytes(h->d.in_dtype);
+  const long long px = (long long)h->ho * h->wo, piece = limit / (image > px ? image : px);
+  if (piece < 1 || piece >= n) return;
+  c->direct = cg::direct_plan(h->d, (int)piece, cu_count());
+  if (n % piece) c->direct_rest = cg::direct_plan(h->d, (int)(n % piece), cu_count());
+  if (n % piece && !c->direct_rest.ok) c->direct.ok = 0;
+  c->piece = (int)piece;
 }
 
 // The kernel a batch runs on.  (Layers that neither tiled family covers: the small-tile kernel.)
@@ -280,7 +299,7 @@ CallPlan plan_call(const cg_conv* h, int n) {
         q.gsp == c.tile.gsp && q.stages[0] == c.tile.stages[0] && q.stages[1] == c.tile.stages[1])
       c.tile = q;
   }
-  if (h->direct_ok) c.direct = cg::direct_plan(dn, n, cu_count());
+  plan_direct(h, n, &c);
   pick_kernel(h, &c);
   return c;
 }
@@ -427,7 +446,7 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   h->first.n = d.n_max;
   h->first.rows = pl.v3;
   h->first.tile = pl.v4;
-  h->first.direct = pl.vd;
+  plan_direct(h, d.n_max, &h->first);
   pick_kernel(h, &h->first);
   h->base = base_params(h);
 
@@ -536,7 +555,8 @@ WsLayout ws_layout(const cg_conv* h, int32_t n, const CallPlan& c, Scratch mode,
   w.dec_off = 0;
   w.mask_off = w.dec_bytes;
   w.partial_off = w.mask_off + w.mask_bytes;
-  w.total = w.partial_off + (c.kernel == kDirect && mode != kCounting ? align256(c.direct.partial_bytes) : 0);
+  const size_t partial = c.direct.partial_bytes > c.direct_rest.partial_bytes ? c.direct.partial_bytes : c.direct_rest.partial_bytes;
+  w.total = w.partial_off + (c.kernel == kDirect && mode != kCounting ? align256(partial) : 0);
   return w;
 }
 }  // namespace
@@ -672,7 +692,24 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
     switch (cp.kernel) {
       case kRows: return cg::launch_rows(cp.rows, q, pk + l.wpk_base_off, pk + l.wpk_cond_off, s);
       case kTile: return cg::launch_tile(cp.tile, q, pk + l.wpk_base_off, pk + l.wpk_cond_off, s);
-      case kDirect: return cg::launch_direct(cp.direct, q, pk + l.wpd_base_off, pk + l.wpd_cond_off, ws + wl.partial_off, s);
+      case kDirect: {
+        hipError_t err = hipSuccess;
+        for (int i = 0; i < n && err == hipSuccess; i += cp.piece) {
+          const long long px = (long long)h->ho * h->wo, oi = i * px * d.c_out;
+          cg::Params r = q;
+          r.n = n - i < cp.piece ? n - i : cp.piece;
+          r.m_total = r.n * px;
+          r.x = (const char*)q.x + (long long)i * d.h * d.w * d.x_pixel_stride * elem_bytes(d.in_dtype);
+          r.residual = (const char*)q.residual + (q.residual ? oi * elem_bytes(d.in_dtype == CG_I8 ? CG_I8 : d.out_dtype) : 0);
+          r.y = (char*)q.y + (q.y ? oi * elem_bytes(d.out_dtype) : 0);
+          if (q.bitmap) r.bitmap = q.bitmap + i * px * q.words;
+          if (q.chan_mask) r.chan_mask = q.chan_mask + (long long)i * q.words;
+          r.clear_total = q.clear_total && i == 0;
+          err = cg::launch_direct(r.n == cp.piece ? cp.direct : cp.direct_rest, r, pk + l.wpd_base_off, pk + l.wpd_cond_off,
+                                  ws + wl.partial_off, s);
+        }
+        return err;
+      }
       default: return cg::launch_naive(q, s);
     }
   };

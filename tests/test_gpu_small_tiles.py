@@ -119,3 +119,28 @@ def test_grouped_layers_keep_infinities_in_their_group(in_dtype, n, h, w, cin, c
     fired = torch.from_numpy(W.unpack_bitmap(bitmap.cpu().numpy().view(np.uint32), cout)).reshape(n, h, w, cout).bool()
     base = torch.stack(per_group, -1).repeat_interleave(cpg, -1)
     assert torch.equal(fired, base >= thr)
+
+
+@pytest.mark.parametrize("tau_c", [0.0, 0.3], ids=["plain_gate", "channel_gate"])
+def test_batches_beyond_the_offsets_run_in_pieces(tau_c):
+    """x of 1.02 GiB: one piece of 255 images and a rest of six, against calls of 29 images at a time; whole numbers, so equal."""
+    import torch
+    n, c = 261, 16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(6)
+    x = torch.randint(0, 60, (n, 512, 512, c), generator=gen, device="cuda", dtype=torch.int8)
+    w = torch.randint(-60, 60, (c, 3, 3, c), generator=gen, device="cuda", dtype=torch.int8)
+    layer = B.GatedConv(n_max=n, h=512, w=512, c_in=c, c_out=c, c_base=4, w_base=w[..., :4].contiguous(), w_cond=w[..., 4:].contiguous(),
+                        in_dtype=B.CG_I8, out_dtype=B.CG_I8, gate_thr_i32=np.linspace(-30000, 30000, c).astype(np.int32), tau_c=tau_c,
+                        epilogue=B.CG_EPI_RELU | B.CG_EPI_RESIDUAL, rq_mult0=3, rq_mult1=2, rq_shift=10, rq_res_mult=900)
+    res = torch.randint(-128, 128, (n, 512, 512, c), generator=gen, device="cuda", dtype=torch.int8)
+    y, bitmap, counts = layer.forward(x, residual=res)
+    total = 0
+    for i in range(0, n, 29):
+        y2, bitmap2, counts2 = layer.forward(x[i:i + 29], residual=res[i:i + 29])
+        px = 512 * 512
+        assert torch.equal(y[i:i + 29], y2) and torch.equal(bitmap[i * px:(i + 29) * px], bitmap2)
+        assert torch.equal(counts[2 + i * c:2 + (i + 29) * c], counts2[2:])
+        total += int(counts2[0]) & 0xffffffff
+    assert (int(counts[0]) & 0xffffffff) + (int(counts[1]) << 32) == total and 0 < total < n * 512 * 512 * c
+    layer.close()
