@@ -166,7 +166,8 @@ size_t cg_conv_workspace_bytes(const cg_conv* h, int32_t n);
  *   workspace >= cg_conv_workspace_bytes(h, n) bytes, 256-byte aligned; may be NULL if that is 0.
  * Calls on one handle may overlap only if they use distinct y / bitmap / counts / workspace.
  * Errors: CG_EINVAL (NULL where not allowed, n out of range, workspace too small),
- * CG_EHIP (a launch failed).
+ * CG_EHIP (a launch failed; or a kernel of an earlier call, on any handle, came to the bound of an internal
+ * wait, which is a mistake in the library: that call's results are wrong, and no later call runs).
  */
 int cg_conv_forward(cg_conv* h, int32_t n, const void* x, const void* residual, void* y,
                     uint32_t* bitmap, uint32_t* counts, void* workspace, size_t workspace_bytes,

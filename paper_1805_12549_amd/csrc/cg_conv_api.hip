@@ -401,6 +401,24 @@ void* scratch_of_current_device() {
   return ptr;
 }
 
+// A word of pinned host memory that any GPU's kernels can write, held until the process ends: a kernel whose bounded wait
+// came to its end sets it (a mistake in this library: the pass's results are wrong).  NULL with the error text set on failure.
+std::mutex g_gave_up_lock;
+uint32_t* g_gave_up = nullptr;
+
+uint32_t* gave_up_word() {
+  std::lock_guard<std::mutex> g(g_gave_up_lock);
+  if (g_gave_up) return g_gave_up;
+  void* ptr = nullptr;
+  const hipError_t e = hipHostMalloc(&ptr, 64, hipHostMallocPortable | hipHostMallocMapped);
+  if (e != hipSuccess || !ptr) {
+    fail(CG_EHIP, "hipHostMalloc of the kernels' error word failed: %s", hipGetErrorString(e));
+    return nullptr;
+  }
+  memset(ptr, 0, 64);
+  return g_gave_up = (uint32_t*)ptr;
+}
+
 }  // namespace
 
 extern "C" {
@@ -520,9 +538,10 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
     return code;
   }
   h->d.w_base = h->d.w_cond = nullptr;
-  // set-up is the place to ask for this device's scratch address, so that a later
-  // cg_conv_forward_noalloc (possibly under graph capture) only reads it
-  if (!scratch_of_current_device()) {
+  // set-up is the place to ask for this device's scratch address and the kernels' error word, so that a later
+  // forward call (possibly under graph capture) only reads them
+  h->base.gave_up = gave_up_word();
+  if (!h->base.gave_up || !scratch_of_current_device()) {
     const std::string keep = g_err;
     delete h;
     g_err = keep;
@@ -647,6 +666,8 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
   if (!h) return fail(CG_EINVAL, "handle is NULL");
   if (n < 0 || n > h->d.n_max) return fail(CG_EINVAL, "n = %d is outside [0, n_max = %d]", n, h->d.n_max);
   if (n == 0) return CG_OK;
+  if (__atomic_load_n(h->base.gave_up, __ATOMIC_RELAXED))
+    return fail(CG_EHIP, "a kernel of an earlier call gave up waiting for its own loads; that call's results are wrong");
   if (!x || !y) return fail(CG_EINVAL, "x and y must not be NULL");
   if ((h->d.epilogue & CG_EPI_RESIDUAL) && !residual)
     return fail(CG_EINVAL, "residual is NULL but the layer was created with CG_EPI_RESIDUAL");

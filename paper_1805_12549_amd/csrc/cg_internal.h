@@ -41,6 +41,7 @@ struct Params {
   const void* w_base;
   const void* w_cond;
   size_t table_stride;     // bytes between the per-channel tables of `packed`; thr_f is table 0
+  uint32_t* gave_up;       // a word of host memory that a kernel sets when it gives up a wait (its results are then wrong)
   const void* zeros;       // at least 256 bytes of zeros (source of the padding in the LDS-direct loads)
 
   // call arguments

@@ -204,12 +204,14 @@ __device__ __forceinline__ void bare_barrier() {
 }
 
 // Waits until each of the N progress counters at LDS address `addr` is at least `need`; `have` caches their
-// minimum.  (Every counter is advanced by a wavefront that never waits for this one's next step; the bound on the
-// polls only turns a mistake into a wrong result instead of a hang.)
+// minimum.  Every counter is advanced by a wavefront that never waits for this one's next step; the bound on the
+// polls (near a second) only turns a mistake into a wrong result instead of a hang.  `have` is then kGaveUp, the wavefront
+// waits no more, and at its end it sets a word of host memory after which every call of the library fails.
+constexpr int kPolls = 1 << 22, kGaveUp = 0x7fffffff;
 template <int N>
 __device__ __forceinline__ void wait_counters(unsigned addr, int lane, int need, int& have) {
   if (have >= need) return;
-  for (int spin = 0; spin < (1 << 22); ++spin) {
+  for (int spin = 0; spin < kPolls; ++spin) {
     int v;
     asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(addr + (lane < N ? lane : 0) * 4) : "memory");
     have = __builtin_amdgcn_readlane(v, 0);
@@ -222,6 +224,10 @@ __device__ __forceinline__ void wait_counters(unsigned addr, int lane, int need,
     if (have >= need) return;
     __builtin_amdgcn_s_sleep(1);
   }
+  have = kGaveUp;
+}
+__device__ __forceinline__ void mark_if_gave_up(int have, int lane, uint32_t* gave_up) {
+  if (have == kGaveUp && lane == 0) __hip_atomic_store(gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // what is the same for the whole grid; the kernel reads each group with a few scalar loads, issued together
@@ -250,6 +256,7 @@ struct RowsArgs {
   uint32_t* bitmap;
   const uint32_t* chan_mask;
   int wo, words, c_out, rq_shift, rq_res_mult, shuf, cpg, groups;
+  uint32_t* gave_up;                         // host memory: set where a wait came to its bound
 };
 enum : unsigned {
   kGated = 1u, kGateOnly = 2u, kTwoSided = 4u, kAffine = 8u, kRelu = 16u, kResidual = 32u,
@@ -444,6 +451,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       if (iv - out > 2) land();
     }
     while (out < V) land();
+    mark_if_gave_up(free_to, lane, a.gave_up);
     return;
   }
 
@@ -915,6 +923,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       }
     }
   }
+  mark_if_gave_up(have, lane, a.gave_up);
 }
 
 // [c_out][9][c_phase] -> [column block][stage][kernel row r][K step k][chunk h][row][16 bytes]
@@ -1218,6 +1227,7 @@ hipError_t launch_rows(const RowsPlan& g, const Params& p, const void* w0, const
   a.bitmap = p.bitmap;
   a.chan_mask = p.chan_mask;
   a.clear = p.clear_total ? p.total : nullptr;
+  a.gave_up = p.gave_up;
   a.magic_hp = magic16(g.hp);
   a.magic_ho = magic16(p.ho);
   a.magic_wo = magic16(p.wo);
