@@ -42,6 +42,32 @@ int set_error(int code, const char* fmt, ...) {
   g_err = buf;
   return code;
 }
+
+int cu_count() {
+  static std::atomic<int> cached[64];
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) == hipSuccess && dev >= 0) {
+    if (dev < 64) n = cached[dev].load(std::memory_order_relaxed);
+    if (n > 0) return n;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) {
+      if (dev < 64) cached[dev].store(n, std::memory_order_relaxed);
+      return n;
+    }
+  }
+  (void)hipGetLastError();
+  return 256;
+}
+
+hipError_t allow_lds(const void* kernel, int bytes, std::atomic<uint64_t>& done) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev >= 0 && dev < 64 ? (uint64_t)1 << dev : 0;
+  if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
+  return e;
+}
 }  // namespace cg
 
 namespace {
@@ -207,23 +233,9 @@ struct Plans {
   size_t wpk_base_bytes, wpk_cond_bytes, wpd_base_bytes, wpd_cond_bytes;
 };
 
-// compute units of the current device (256 where no device answers: the plan is then the MI355X one)
-int cu_count() {
-  static int cached = 0;
-  if (cached > 0) return cached;
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) == hipSuccess &&
-      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) {
-    cached = n;
-    return n;
-  }
-  (void)hipGetLastError();
-  return 256;
-}
-
 int resolve_variant(const cg_conv_desc& d, Plans* pl) {
-  pl->v4 = cg::tile_plan(d, cu_count());
-  pl->v3 = cg::rows_plan(d, cu_count(), 0, 2);
+  pl->v4 = cg::tile_plan(d, cg::cu_count());
+  pl->v3 = cg::rows_plan(d, cg::cu_count(), 0, 2);
   if (d.variant == CG_VARIANT_TILE && !pl->v4.ok)
     return fail(CG_EUNSUPPORTED, "the large-tile matrix-core kernel does not cover this shape/dtype");
   if (d.variant == CG_VARIANT_MFMA_ROWS && !pl->v3.ok)
@@ -235,11 +247,11 @@ int resolve_variant(const cg_conv_desc& d, Plans* pl) {
   // name): 1024 channels at 14x14 x64, bf16 49 us against 89 on the large-tile kernel, int8 36 against 101
   pl->point_ok = false;
   if (d.variant == CG_VARIANT_AUTO && v != CG_VARIANT_MFMA_ROWS) {
-    const cg::RowsPlan q = cg::point_plan(d, cu_count());
+    const cg::RowsPlan q = cg::point_plan(d, cg::cu_count());
     pl->point_ok = q.ok != 0;
     if (q.ok) pl->v3 = q;
   }
-  pl->vd = cg::direct_plan(d, 1, cu_count());          // (what is packed does not depend on the batch)
+  pl->vd = cg::direct_plan(d, 1, cg::cu_count());          // (what is packed does not depend on the batch)
   pl->direct_ok = d.variant == CG_VARIANT_AUTO && pl->vd.ok;      // (a family that was asked for by name is what runs)
   pl->wpd_base_bytes = pl->direct_ok ? pl->vd.wpk_bytes[0] : 0;
   pl->wpd_cond_bytes = pl->direct_ok ? pl->vd.wpk_bytes[1] : 0;
@@ -256,13 +268,13 @@ void plan_direct(const cg_conv* h, int n, CallPlan* c) {
   c->direct = c->direct_rest = cg::DirectPlan{};
   c->piece = n;
   if (!h->direct_ok) return;
-  c->direct = cg::direct_plan(h->d, n, cu_count());
+  c->direct = cg::direct_plan(h->d, n, cg::cu_count());
   if (c->direct.ok || h->variant != CG_VARIANT_NAIVE || h->point_ok) return;
   const long long limit = (1ll << 30) - 1, image = (long long)h->d.h * h->d.w * h->d.x_pixel_stride * elem_bytes(h->d.in_dtype);
   const long long px = (long long)h->ho * h->wo, piece = limit / (image > px ? image : px);
   if (piece < 1 || piece >= n) return;
-  c->direct = cg::direct_plan(h->d, (int)piece, cu_count());
-  if (n % piece) c->direct_rest = cg::direct_plan(h->d, (int)(n % piece), cu_count());
+  c->direct = cg::direct_plan(h->d, (int)piece, cg::cu_count());
+  if (n % piece) c->direct_rest = cg::direct_plan(h->d, (int)(n % piece), cg::cu_count());
   if (n % piece && !c->direct_rest.ok) c->direct.ok = 0;
   c->piece = (int)piece;
 }
@@ -278,7 +290,7 @@ void pick_kernel(const cg_conv* h, CallPlan* c) {
   // channels at 56x56, one image 7.7 / 5.5; 1024 at 14x14, one image 10.2 / 11.5, eight 13.2 / 13.1.
   if (h->point_ok && h->d.c_in < 512) return;
   const int rounds = h->d.kh == 3 || h->point_ok ? 1 : 2;
-  if (c->kernel == kNaive || c->direct.tiles <= rounds * cu_count()) c->kernel = kDirect;
+  if (c->kernel == kNaive || c->direct.tiles <= rounds * cg::cu_count()) c->kernel = kDirect;
 }
 
 // The launch shape follows the batch of the call: a smaller batch than n_max is planned afresh and the
@@ -289,12 +301,12 @@ CallPlan plan_call(const cg_conv* h, int n) {
   cg_conv_desc dn = h->d;
   dn.n_max = n;
   if (h->variant == CG_VARIANT_MFMA_ROWS || h->point_ok) {
-    const cg::RowsPlan q = h->point_ok ? cg::point_plan(dn, cu_count()) : cg::rows_plan(dn, cu_count(), c.rows.cps, 2);
+    const cg::RowsPlan q = h->point_ok ? cg::point_plan(dn, cg::cu_count()) : cg::rows_plan(dn, cg::cu_count(), c.rows.cps, 2);
     if (q.ok && q.grp_mode == c.rows.grp_mode && q.gsp == c.rows.gsp &&
         q.stages[0] == c.rows.stages[0] && q.stages[1] == c.rows.stages[1])
       c.rows = q;
   } else if (h->variant == CG_VARIANT_TILE) {
-    const cg::TilePlan q = cg::tile_plan(dn, cu_count());
+    const cg::TilePlan q = cg::tile_plan(dn, cg::cu_count());
     if (q.ok && q.taps == c.tile.taps && q.cps == c.tile.cps && q.wn == c.tile.wn && q.grp_mode == c.tile.grp_mode &&
         q.gsp == c.tile.gsp && q.stages[0] == c.tile.stages[0] && q.stages[1] == c.tile.stages[1])
       c.tile = q;
@@ -704,7 +716,7 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
     if (y0 < r0 + len && r0 < y0 + len) {
       cg_conv_desc dn = d;
       dn.n_max = n;
-      cp.rows = cg::rows_plan(dn, cu_count(), cp.rows.cps, 1);
+      cp.rows = cg::rows_plan(dn, cg::cu_count(), cp.rows.cps, 1);
     }
   }
   hipStream_t s = (hipStream_t)hip_stream;

@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "cg_conv.h"
 
 namespace cg {
@@ -178,6 +180,12 @@ hipError_t launch_bitmap_chan_mask(const Params& p, const uint32_t* bitmap, uint
                                    hipStream_t s);
 // the same from [n][c_out] fired counts
 hipError_t launch_counts_chan_mask(const Params& p, const uint32_t* counts, uint32_t need, uint32_t* mask, hipStream_t s);
+
+// compute units of the current device (256 where no device answers: the plan is then the MI355X one)
+int cu_count();
+// Lets `kernel` use up to `bytes` of LDS on the current device, which has to be asked for beyond the default of a launch,
+// once per kernel and device; `done` is the kernel's own record of the devices that were asked.
+hipError_t allow_lds(const void* kernel, int bytes, std::atomic<uint64_t>& done);
 
 // launchers (return hipError_t from the last launch)
 hipError_t launch_naive(const Params& p, hipStream_t s);

@@ -479,7 +479,7 @@ int launch_conv7x7s2c3(bool pool, const char* who, const void* x, const void* w,
   a.col_wgs = (frags + 1) / 2;
   // Bands: a band computes one row more than it writes and lays out the weights anew, so long ones are better, as long as
   // the chip is full: a compute unit holds four workgroups.
-  const long long per_row = (long long)n * a.col_wgs * (c_out / kCb), want = 4 * 256;
+  const long long per_row = (long long)n * a.col_wgs * (c_out / kCb), want = 4ll * cg::cu_count();
   long long bands = (want + per_row - 1) / per_row;
   if (bands > a.oh) bands = a.oh;
   a.band = (int)((a.oh + bands - 1) / bands);
@@ -850,8 +850,8 @@ int cg_avgpool_fc(const void* x, const void* wfc, const float* bias, float* logi
   if (n == 0) return CG_OK;
   if (c % 32 == 0 && c <= kPoolMaxC && ((((uintptr_t)x) | ((uintptr_t)wfc)) & 15) == 0) {
     const size_t lds = 16 * ((size_t)c * 2 + 16) + (size_t)(1024 / (c / 8)) * c * sizeof(float);
-    static const hipError_t attr =
-        hipFuncSetAttribute((const void*)avgpool_fc_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    static std::atomic<uint64_t> asked{0};
+    const hipError_t attr = cg::allow_lds((const void*)avgpool_fc_mfma_kernel, 160 * 1024, asked);
     if (attr != hipSuccess) return cg::set_error(CG_EHIP, "cg_avgpool_fc: %s", hipGetErrorString(attr));
     hipLaunchKernelGGL(avgpool_fc_mfma_kernel, dim3((unsigned)((n + kPoolImgs - 1) / kPoolImgs), (unsigned)((classes + 255) / 256)),
                        dim3(1024), lds, (hipStream_t)hip_stream, (const uint16_t*)x, (const uint16_t*)wfc, bias, logits, n, hw, c,

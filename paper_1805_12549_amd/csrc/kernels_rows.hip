@@ -976,9 +976,8 @@ __global__ void pack_rows_kernel(const char* __restrict__ w, char* __restrict__ 
 template <typename Tr, int CPS, int PF, int TAPS>
 hipError_t launch_rows_one(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
   const unsigned blocks = a.xcd_cb ? (unsigned)(g.n_slots * g.n_cb) : (unsigned)a.per_xcd * 8u;
-  // (a compute unit holds 160 KB; more than the default of a launch has to be asked for, once per kernel)
-  static const hipError_t attr = hipFuncSetAttribute((const void*)gated_conv_rows_kernel<Tr, CPS, PF, TAPS>,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  static std::atomic<uint64_t> asked{0};
+  const hipError_t attr = allow_lds((const void*)gated_conv_rows_kernel<Tr, CPS, PF, TAPS>, kLds, asked);
   if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL((gated_conv_rows_kernel<Tr, CPS, PF, TAPS>), dim3(blocks), dim3(kNt), (size_t)g.lds_bytes, s, a, p);
   return hipGetLastError();

@@ -92,7 +92,36 @@ static void gave_up_wait_is_reported() {
   cg_conv_destroy(b);
 }
 
+// What a launch depends on is asked of the device it goes to: the LDS beyond the default, the compute units.
+static void devices_are_asked_one_by_one() {
+  const size_t first = launches.size();
+  unsigned blocks[2][2];
+  for (device = 0; device < 2; ++device) {
+    cg_conv* h = make(64);
+    size_t at = launches.size();
+    EXPECT(forward(h, 64) == CG_OK && launches.size() == at + 1);
+    blocks[device][0] = launches.back().blocks;
+    cg_conv_destroy(h);
+    at = launches.size();
+    EXPECT(cg_conv7x7s2_maxpool((void*)16, (void*)16, nullptr, nullptr, (void*)16, 16, 224, 224, 64, 3, 1, nullptr) == CG_OK);
+    EXPECT(launches.size() == at + 1);
+    blocks[device][1] = launches.back().blocks;
+    EXPECT(cg_avgpool_fc((void*)16, (void*)16, nullptr, (float*)16, 4, 49, 2048, 1000, nullptr) == CG_OK);
+  }
+  device = 0;
+  int large = 0;
+  for (size_t i = first; i < launches.size(); ++i) {
+    if (launches[i].lds <= 65536) continue;
+    ++large;
+    EXPECT(large_lds.count({launches[i].kernel, launches[i].device}) == 1);
+  }
+  EXPECT(large == 4);
+  EXPECT(blocks[0][0] == 256 && blocks[1][0] == 64);
+  EXPECT(blocks[0][1] == 896 && blocks[1][1] == 224);
+}
+
 int main() {
+  devices_are_asked_one_by_one();
   gave_up_wait_is_reported();
   if (failures) { std::printf("%d checks failed\n", failures); return 1; }
   std::printf("host calls driver: ok\n");
