@@ -103,7 +103,7 @@ enum Kernel { kNaive, kRows, kTile, kDirect };
 struct CallPlan {
   int n;
   Kernel kernel;
-  cg::RowsPlan rows;
+  cg::RowsPlan rows, rows_over;          // rows_over: for an output written over its residual
   cg::TilePlan tile;
   cg::DirectPlan direct, direct_rest;    // for `piece` images at a time and for what is left (none where piece divides n)
   int piece;
@@ -121,10 +121,12 @@ struct cg_conv {
   Layout lay;
   cg::Params base;          // what is the same in every call
   std::vector<uint32_t> staging;  // host image of the tables; kept alive for the async copy
-  // plans of other batch sizes, made on first use and kept (at most kKept of them)
-  static constexpr size_t kKept = 8;
+  // plans of other batch sizes, made on first use (7 us of host time) and kept, the last kKept of them
+  static constexpr int kKept = 64;
   mutable std::mutex lock;
-  mutable std::vector<CallPlan> kept;
+  mutable int kept_n[kKept] = {};          // their batch sizes; 0: none yet
+  mutable int kept_next = 0;
+  mutable std::vector<CallPlan> kept;      // (kKept of them from the start: a forward call allocates nothing)
 };
 
 namespace {
@@ -293,6 +295,15 @@ void pick_kernel(const cg_conv* h, CallPlan* c) {
   if (c->kernel == kNaive || c->direct.tiles <= rounds * cg::cu_count()) c->kernel = kDirect;
 }
 
+// Two fragments per wavefront write an output twice and read the residual after the first time: where the two may be the
+// same memory, a plan with one fragment is kept beside.
+void plan_over(const cg_conv* h, CallPlan* c) {
+  if (c->kernel != kRows || c->rows.pf != 2 || !(h->d.epilogue & CG_EPI_RESIDUAL)) return;
+  cg_conv_desc dn = h->d;
+  dn.n_max = c->n;
+  c->rows_over = cg::rows_plan(dn, cg::cu_count(), c->rows.cps, 1);
+}
+
 // The launch shape follows the batch of the call: a smaller batch than n_max is planned afresh and the
 // new plan is used if it reads the prepacked weights the same way.
 CallPlan plan_call(const cg_conv* h, int n) {
@@ -313,18 +324,20 @@ CallPlan plan_call(const cg_conv* h, int n) {
   }
   plan_direct(h, n, &c);
   pick_kernel(h, &c);
+  plan_over(h, &c);
   return c;
 }
 
 CallPlan call_plan(const cg_conv* h, int n) {
   if (n == h->first.n) return h->first;
   std::lock_guard<std::mutex> g(h->lock);
-  for (const CallPlan& c : h->kept)
-    if (c.n == n) return c;
-  const CallPlan c = plan_call(h, n);
-  if (h->kept.size() >= cg_conv::kKept) h->kept.erase(h->kept.begin());
-  h->kept.push_back(c);
-  return c;
+  for (int i = 0; i < cg_conv::kKept; ++i)
+    if (h->kept_n[i] == n) return h->kept[i];
+  const int at = h->kept_next;
+  h->kept_next = (at + 1) % cg_conv::kKept;
+  h->kept[at] = plan_call(h, n);
+  h->kept_n[at] = n;
+  return h->kept[at];
 }
 
 cg::Params base_params(const cg_conv* h) {
@@ -478,6 +491,7 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   h->first.tile = pl.v4;
   plan_direct(h, d.n_max, &h->first);
   pick_kernel(h, &h->first);
+  plan_over(h, &h->first);
   h->base = base_params(h);
 
   // Host image of the per-channel tables.
@@ -487,6 +501,7 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   const size_t tw = lay.table_stride / 4;
   try {
     h->staging.assign(tw * kTables, 0u);
+    h->kept.resize(cg_conv::kKept);
   } catch (...) {
     delete h;
     return fail(CG_ENOMEM, "out of host memory");
@@ -710,14 +725,10 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
 
   if (!aligned || mode == kCounting) cp.kernel = kNaive;      // (the plain kernel is the layer's family: the others were turned away)
   if (cp.kernel == kRows && cp.rows.pf == 2 && residual) {
-    // Two fragments per wavefront write an output twice and read the residual after the first time.
+    // (see plan_over)
     const char *y0 = (const char*)y, *r0 = (const char*)residual;
     const size_t len = (size_t)p.m_total * d.c_out * 2;
-    if (y0 < r0 + len && r0 < y0 + len) {
-      cg_conv_desc dn = d;
-      dn.n_max = n;
-      cp.rows = cg::rows_plan(dn, cg::cu_count(), cp.rows.cps, 1);
-    }
+    if (y0 < r0 + len && r0 < y0 + len) cp.rows = cp.rows_over;
   }
   hipStream_t s = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;

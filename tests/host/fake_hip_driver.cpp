@@ -11,7 +11,7 @@
 
 #include "cg_conv.h"
 
-static int device = 0, failures = 0;
+static int device = 0, failures = 0, device_asked = 0;
 static int compute_units[2] = {256, 64};
 static std::vector<void*> host_blocks;
 struct Launch { const void* kernel; int device; unsigned blocks; size_t lds; };
@@ -21,7 +21,7 @@ static Launch config;
 #define EXPECT(c) do { if (!(c)) { std::printf("FAILED line %d: %s  [%s]\n", __LINE__, #c, cg_last_error()); ++failures; } } while (0)
 
 extern "C" {
-hipError_t hipGetDevice(int* d) { *d = device; return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = device; ++device_asked; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int d) {
   *v = a == hipDeviceAttributeMultiprocessorCount ? compute_units[d] : 0;
   return hipSuccess;
@@ -92,6 +92,42 @@ static void gave_up_wait_is_reported() {
   cg_conv_destroy(b);
 }
 
+// Plans are made once per batch size (a plan asks for the device's compute units; a launch alone asks for the device once).
+static void plans_are_kept() {
+  cg_conv* h = make(64);
+  for (int round = 0; round < 2; ++round)
+    for (int n = 1; n <= 40; ++n) {
+      device_asked = 0;
+      EXPECT(forward(h, n) == CG_OK);
+      EXPECT(round == 0 || device_asked <= 1);
+    }
+  cg_conv_destroy(h);
+  // two fragments per wavefront, y over the residual: another plan, kept as well
+  static float stat[256], one[256];
+  for (float& v : one) v = 1.0f;
+  cg_conv_desc d;
+  std::memset(&d, 0, sizeof d);
+  d.struct_size = sizeof d;
+  d.n_max = 256; d.h = d.w = 14; d.c_in = d.c_out = 256; d.c_base = 64; d.kh = d.kw = 3; d.stride = d.pad = 1;
+  d.in_dtype = d.out_dtype = CG_BF16; d.epilogue = CG_EPI_RELU | CG_EPI_RESIDUAL; d.gate_mean = d.delta = stat; d.gate_var = one;
+  d.w_base = (const void*)0x1000; d.w_cond = (const void*)0x2000;
+  d.packed = (void*)0x100000; d.packed_bytes = cg_conv_packed_bytes(&d);
+  EXPECT(cg_conv_create(&h, &d, nullptr) == CG_OK);
+  const void* kernel[2];
+  for (int n = 256; n >= 200; n -= 56)
+    for (int round = 0; round < 2; ++round)
+      for (int over = 0; over < 2; ++over) {
+        device_asked = 0;
+        char *y = (char*)0x300000000ull, *res = over ? y : (char*)0x600000000ull;
+        EXPECT(cg_conv_forward(h, n, (void*)0x200000000ull, res, y, nullptr, nullptr, (void*)0x500000000ull,
+                               cg_conv_workspace_bytes(h, n), nullptr) == CG_OK);
+        EXPECT((round == 0 && !over) || device_asked <= 1);
+        kernel[over] = launches.back().kernel;
+        EXPECT(!over || kernel[0] != kernel[1]);
+      }
+  cg_conv_destroy(h);
+}
+
 // What a launch depends on is asked of the device it goes to: the LDS beyond the default, the compute units.
 static void devices_are_asked_one_by_one() {
   const size_t first = launches.size();
@@ -122,6 +158,7 @@ static void devices_are_asked_one_by_one() {
 
 int main() {
   devices_are_asked_one_by_one();
+  plans_are_kept();
   gave_up_wait_is_reported();
   if (failures) { std::printf("%d checks failed\n", failures); return 1; }
   std::printf("host calls driver: ok\n");
