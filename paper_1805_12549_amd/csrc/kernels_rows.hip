@@ -67,7 +67,7 @@ constexpr int kCw = 8;                       // wavefronts that multiply
 constexpr int kLw = 4;                       // wavefronts that load
 constexpr int kNt = 64 * (kCw + kLw);
 constexpr int kTabs = 8;                     // per-channel tables of `packed`
-constexpr int kTabBytes = kTabs * 256 + 64;  // ... of the block's 64 channels; progress counters
+constexpr int kTabBytes = kTabs * 256 + 64;  // ... of the block's 64 channels; progress counters (12) and gave_up
 constexpr int kShufRow = 144;                // bytes of a pixel's row in the shuffled store's LDS tile (128 + skew)
 constexpr int kLds = 160 * 1024;
 constexpr int kMaxPatchLoads = 12;           // 1 KB load instructions per loading wavefront and patch
@@ -226,10 +226,6 @@ __device__ __forceinline__ void wait_counters(unsigned addr, int lane, int need,
   }
   have = kGaveUp;
 }
-__device__ __forceinline__ void mark_if_gave_up(int have, int lane, uint32_t* gave_up) {
-  if (have == kGaveUp && lane == 0) __hip_atomic_store(gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 // what is the same for the whole grid; the kernel reads each group with a few scalar loads, issued together
 struct RowsArgs {
   // every wavefront
@@ -241,6 +237,7 @@ struct RowsArgs {
   int s0, s, nb, pstr, psz, wres, tabs;      // stages; buffers and LDS offsets (wres < 0: weights are in the ring)
   int ho, hp, stride, tab_stride;
   uint32_t* clear;                           // two words that the grid clears, or NULL
+  uint32_t* gave_up;                         // host memory: set where a wait came to its bound
   // loading wavefronts
   const char* x;
   const char *w0, *w1;
@@ -256,7 +253,6 @@ struct RowsArgs {
   uint32_t* bitmap;
   const uint32_t* chan_mask;
   int wo, words, c_out, rq_shift, rq_res_mult, shuf, cpg, groups;
-  uint32_t* gave_up;                         // host memory: set where a wait came to its bound
 };
 enum : unsigned {
   kGated = 1u, kGateOnly = 2u, kTwoSided = 4u, kAffine = 8u, kRelu = 16u, kResidual = 32u,
@@ -283,7 +279,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   const int lj = lane & 31, lh = lane >> 5;
   asm volatile("" ::"s"(a.flags), "s"(a.magic_ncb), "s"(a.magic_ho), "s"(a.n_cb), "s"(a.n_slots), "s"(a.xcd_cb), "s"(a.per_xcd),
                "s"(a.full), "s"(a.rows_per), "s"(a.rows_more), "s"(a.tr), "s"(a.logp), "s"(a.s0), "s"(a.s), "s"(a.nb), "s"(a.pstr),
-               "s"(a.psz), "s"(a.wres), "s"(a.tabs), "s"(a.ho), "s"(a.hp), "s"(a.stride), "s"(a.tab_stride), "s"(a.clear));
+               "s"(a.psz), "s"(a.wres), "s"(a.tabs), "s"(a.ho), "s"(a.hp), "s"(a.stride), "s"(a.tab_stride), "s"(a.clear), "s"(a.gave_up));
 
   // Block id mod 8 is the XCD.  Normally an XCD takes a contiguous run of rows with all channel blocks, so that a
   // row is fetched into one L2 once; xcd_cb: the workgroups of a channel block sit on one XCD instead, so that each
@@ -318,6 +314,14 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     if (lane == 0) asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(value) : "memory");
   };
   if (tid < kLw + kCw) *(int*)(lds + a.tabs + kTabs * 256 + tid * 4) = 0;
+  // (kept here: read from the arguments at the end of each wavefront it cost a launch 1.5 us)
+  if (tid == 0) *(uint32_t**)(lds + a.tabs + kTabs * 256 + 48) = a.gave_up;
+
+  auto mark_if_gave_up = [&](int have) __attribute__((always_inline)) {
+    if (have != kGaveUp) return;
+    uint32_t* const word = *(uint32_t* const*)(lds + a.tabs + kTabs * 256 + 48);
+    if (lane == 0) __hip_atomic_store(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  };
 
   if (wave >= kCw) {
     // ================================ loading wavefronts ============================================
@@ -451,7 +455,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       if (iv - out > 2) land();
     }
     while (out < V) land();
-    mark_if_gave_up(free_to, lane, a.gave_up);
+    mark_if_gave_up(free_to);
     return;
   }
 
@@ -923,7 +927,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       }
     }
   }
-  mark_if_gave_up(have, lane, a.gave_up);
+  mark_if_gave_up(have);
 }
 
 // [c_out][9][c_phase] -> [column block][stage][kernel row r][K step k][chunk h][row][16 bytes]
