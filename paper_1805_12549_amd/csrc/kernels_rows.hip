@@ -237,7 +237,6 @@ struct RowsArgs {
   int s0, s, nb, pstr, psz, wres, tabs;      // stages; buffers and LDS offsets (wres < 0: weights are in the ring)
   int ho, hp, stride, tab_stride;
   uint32_t* clear;                           // two words that the grid clears, or NULL
-  uint32_t* gave_up;                         // host memory: set where a wait came to its bound
   // loading wavefronts
   const char* x;
   const char *w0, *w1;
@@ -253,6 +252,7 @@ struct RowsArgs {
   uint32_t* bitmap;
   const uint32_t* chan_mask;
   int wo, words, c_out, rq_shift, rq_res_mult, shuf, cpg, groups;
+  uint32_t* gave_up;                         // host memory: set where a wait came to its bound
 };
 enum : unsigned {
   kGated = 1u, kGateOnly = 2u, kTwoSided = 4u, kAffine = 8u, kRelu = 16u, kResidual = 32u,
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   const int lj = lane & 31, lh = lane >> 5;
   asm volatile("" ::"s"(a.flags), "s"(a.magic_ncb), "s"(a.magic_ho), "s"(a.n_cb), "s"(a.n_slots), "s"(a.xcd_cb), "s"(a.per_xcd),
                "s"(a.full), "s"(a.rows_per), "s"(a.rows_more), "s"(a.tr), "s"(a.logp), "s"(a.s0), "s"(a.s), "s"(a.nb), "s"(a.pstr),
-               "s"(a.psz), "s"(a.wres), "s"(a.tabs), "s"(a.ho), "s"(a.hp), "s"(a.stride), "s"(a.tab_stride), "s"(a.clear), "s"(a.gave_up));
+               "s"(a.psz), "s"(a.wres), "s"(a.tabs), "s"(a.ho), "s"(a.hp), "s"(a.stride), "s"(a.tab_stride), "s"(a.clear));
 
   // Block id mod 8 is the XCD.  Normally an XCD takes a contiguous run of rows with all channel blocks, so that a
   // row is fetched into one L2 once; xcd_cb: the workgroups of a channel block sit on one XCD instead, so that each
@@ -314,8 +314,6 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     if (lane == 0) asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(value) : "memory");
   };
   if (tid < kLw + kCw) *(int*)(lds + a.tabs + kTabs * 256 + tid * 4) = 0;
-  // (kept here: read from the arguments at the end of each wavefront it cost a launch 1.5 us)
-  if (tid == 0) *(uint32_t**)(lds + a.tabs + kTabs * 256 + 48) = a.gave_up;
 
   auto mark_if_gave_up = [&](int have) __attribute__((always_inline)) {
     if (have != kGaveUp) return;
@@ -461,7 +459,9 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
 
   // ================================ multiplying wavefronts ==========================================
   asm volatile("" ::"s"(a.fwl), "s"(a.nfc), "s"(a.magic_wo), "s"(a.magic_nfc), "s"(a.y), "s"(a.residual), "s"(a.bitmap),
-               "s"(a.chan_mask), "s"(a.wo), "s"(a.words), "s"(a.c_out), "s"(a.rq_shift), "s"(a.rq_res_mult));
+               "s"(a.chan_mask), "s"(a.wo), "s"(a.words), "s"(a.c_out), "s"(a.rq_shift), "s"(a.rq_res_mult), "s"(a.gave_up));
+  // (the address waits in LDS: read from the arguments at the end of each wavefront it cost a launch 1.5 us)
+  if (tid == 0) *(uint32_t**)(lds + a.tabs + kTabs * 256 + 48) = a.gave_up;
   acc_t* const tlo = (acc_t*)(lds + a.tabs);         // [64] thresholds, lower and upper
   acc_t* const thi = tlo + 64;
   float* const aff = (float*)(thi + 64);             // [4][64] scale0, shift0, scale1, shift1; int8: mult0, mult1
