@@ -45,6 +45,7 @@ if len(_hip_runtimes_mapped()) > 1:
 
 # the current stream's address without building a Stream object per call
 _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+_empty, _int32 = torch.empty, torch.int32
 # torch's caching allocator without a tensor around the block: memory that belongs to one stream (bytes, stream's address)
 _raw_alloc, _raw_free = torch._C._cuda_cudaCachingAllocator_raw_alloc, torch._C._cuda_cudaCachingAllocator_raw_delete
 
@@ -297,20 +298,19 @@ class GatedConv:
     def _stream_ptr(self):
         if self.stream is not None:
             return self.stream.cuda_stream
-        return current_stream_ptr()
+        return _raw_stream(_current_device())
 
     def forward(self, x, residual=None, y=None, bitmap=True, counts=True):
         """x: torch device tensor [n,H,W,C_in] (contiguous NHWC).  Returns (y, bitmap, counts)."""
-        empty = self._torch.empty
-        n = x.shape[0]
+        n, dev = x.shape[0], x.device
         if y is None:
-            y = empty((n, self.ho, self.wo, self.c_out), dtype=self._y_dtype, device=x.device)
+            y = _empty((n, self.ho, self.wo, self.c_out), dtype=self._y_dtype, device=dev)
         if bitmap is True:
-            bitmap = empty((n * self.ho * self.wo, self.words), dtype=self._torch.int32, device=x.device)
+            bitmap = _empty((n * self.ho * self.wo, self.words), dtype=_int32, device=dev)
         elif bitmap is False:
             bitmap = None
         if counts is True:
-            counts = empty(2 + n * self.c_out, dtype=self._torch.int32, device=x.device)
+            counts = _empty(2 + n * self.c_out, dtype=_int32, device=dev)
         elif counts is False:
             counts = None
         need = self._ws_need.get(n)
