@@ -84,6 +84,31 @@ def test_conv7x7s2_maxpool_fused(n, h, w, c_out, pad):
             assert (np.abs(got - ref) <= tol).all(), float(np.abs(got - ref).max())
 
 
+@pytest.mark.parametrize("n,h,w,c_out,pad", [(24, 224, 224, 64, 3), (40, 131, 90, 128, 3), (300, 33, 40, 64, 2)])
+def test_conv7x7s2_single_images_equal_the_batch(n, h, w, c_out, pad):
+    """32 channels a workgroup (few images) and 64: every output is the same chain of products, so bit for bit the same."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    x = torch.randn((n, h, w, 3), generator=gen, device="cuda").to(torch.bfloat16)
+    wt = (torch.randn((c_out, 7, 7, 3), generator=gen, device="cuda") * 0.12).to(torch.bfloat16)
+    sc = torch.randn(c_out, generator=gen, device="cuda")              # negative ones among them
+    sh = torch.randn(c_out, generator=gen, device="cuda")
+    ho, wo = O.out_hw(h, w, 7, 7, 2, pad)
+    ph, pw = (ho - 1) // 2 + 1, (wo - 1) // 2 + 1
+    def run(k0, k1):
+        y = torch.empty((k1 - k0, ho, wo, c_out), dtype=torch.bfloat16, device="cuda")
+        p = torch.empty((k1 - k0, ph, pw, c_out), dtype=torch.bfloat16, device="cuda")
+        B.cg_small_cin_conv(x[k0:k1].data_ptr(), wt.data_ptr(), sc.data_ptr(), sh.data_ptr(), y.data_ptr(), k1 - k0, h, w, 3, c_out,
+                            7, 2, pad, True, _stream())
+        B.cg_conv7x7s2_maxpool(x[k0:k1].data_ptr(), wt.data_ptr(), sc.data_ptr(), sh.data_ptr(), p.data_ptr(), k1 - k0, h, w, c_out,
+                               pad, True, _stream())
+        return y, p
+    y, p = run(0, n)
+    for k in (0, n // 2, n - 1):
+        y1, p1 = run(k, k + 1)
+        assert torch.equal(y[k:k + 1], y1) and torch.equal(p[k:k + 1], p1)
+
+
 @pytest.mark.parametrize("n,h,w,c", [(2, 112, 112, 64), (3, 9, 7, 8), (1, 1, 1, 16), (2, 6, 5, 72)])
 def test_maxpool_bit_exact(n, h, w, c):
     rng = np.random.default_rng(h * 10 + c)
