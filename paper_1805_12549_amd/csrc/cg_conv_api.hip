@@ -103,7 +103,7 @@ enum Kernel { kNaive, kRows, kTile, kDirect };
 struct CallPlan {
   int n;
   Kernel kernel;
-  cg::RowsPlan rows;
+  cg::RowsPlan rows, rows_over;          // rows_over: for an output written over its residual
   cg::TilePlan tile;
   cg::DirectPlan direct, direct_rest;    // for `piece` images at a time and for what is left (none where piece divides n)
   int piece;
@@ -126,7 +126,7 @@ struct cg_conv {
   mutable std::mutex lock;
   mutable int kept_n[kKept] = {};          // their batch sizes; 0: none yet
   mutable int kept_next = 0;
-  mutable std::vector<CallPlan> kept;      // (room for kKept from the start: a forward call allocates nothing)
+  mutable std::vector<CallPlan> kept;      // (kKept of them from the start: a forward call allocates nothing)
 };
 
 namespace {
@@ -237,7 +237,7 @@ struct Plans {
 
 int resolve_variant(const cg_conv_desc& d, Plans* pl) {
   pl->v4 = cg::tile_plan(d, cg::cu_count());
-  pl->v3 = cg::rows_plan(d, cg::cu_count(), 0);
+  pl->v3 = cg::rows_plan(d, cg::cu_count(), 0, 2);
   if (d.variant == CG_VARIANT_TILE && !pl->v4.ok)
     return fail(CG_EUNSUPPORTED, "the large-tile matrix-core kernel does not cover this shape/dtype");
   if (d.variant == CG_VARIANT_MFMA_ROWS && !pl->v3.ok)
@@ -295,6 +295,15 @@ void pick_kernel(const cg_conv* h, CallPlan* c) {
   if (c->kernel == kNaive || c->direct.tiles <= rounds * cg::cu_count()) c->kernel = kDirect;
 }
 
+// Two fragments per wavefront write an output twice and read the residual after the first time: where the two may be the
+// same memory, a plan with one fragment is kept beside.
+void plan_over(const cg_conv* h, CallPlan* c) {
+  if (c->kernel != kRows || c->rows.pf != 2 || !(h->d.epilogue & CG_EPI_RESIDUAL)) return;
+  cg_conv_desc dn = h->d;
+  dn.n_max = c->n;
+  c->rows_over = cg::rows_plan(dn, cg::cu_count(), c->rows.cps, 1);
+}
+
 // The launch shape follows the batch of the call: a smaller batch than n_max is planned afresh and the
 // new plan is used if it reads the prepacked weights the same way.
 CallPlan plan_call(const cg_conv* h, int n) {
@@ -303,7 +312,7 @@ CallPlan plan_call(const cg_conv* h, int n) {
   cg_conv_desc dn = h->d;
   dn.n_max = n;
   if (h->variant == CG_VARIANT_MFMA_ROWS || h->point_ok) {
-    const cg::RowsPlan q = h->point_ok ? cg::point_plan(dn, cg::cu_count()) : cg::rows_plan(dn, cg::cu_count(), c.rows.cps);
+    const cg::RowsPlan q = h->point_ok ? cg::point_plan(dn, cg::cu_count()) : cg::rows_plan(dn, cg::cu_count(), c.rows.cps, 2);
     if (q.ok && q.grp_mode == c.rows.grp_mode && q.gsp == c.rows.gsp &&
         q.stages[0] == c.rows.stages[0] && q.stages[1] == c.rows.stages[1])
       c.rows = q;
@@ -315,6 +324,7 @@ CallPlan plan_call(const cg_conv* h, int n) {
   }
   plan_direct(h, n, &c);
   pick_kernel(h, &c);
+  plan_over(h, &c);
   return c;
 }
 
@@ -325,13 +335,9 @@ CallPlan call_plan(const cg_conv* h, int n) {
     if (h->kept_n[i] == n) return h->kept[i];
   const int at = h->kept_next;
   h->kept_next = (at + 1) % cg_conv::kKept;
-  const CallPlan c = plan_call(h, n);
-  if (at < (int)h->kept.size())
-    h->kept[at] = c;
-  else
-    h->kept.push_back(c);
+  h->kept[at] = plan_call(h, n);
   h->kept_n[at] = n;
-  return c;
+  return h->kept[at];
 }
 
 cg::Params base_params(const cg_conv* h) {
@@ -485,6 +491,7 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   h->first.tile = pl.v4;
   plan_direct(h, d.n_max, &h->first);
   pick_kernel(h, &h->first);
+  plan_over(h, &h->first);
   h->base = base_params(h);
 
   // Host image of the per-channel tables.
@@ -494,7 +501,7 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   const size_t tw = lay.table_stride / 4;
   try {
     h->staging.assign(tw * kTables, 0u);
-    h->kept.reserve(cg_conv::kKept);
+    h->kept.resize(cg_conv::kKept);
   } catch (...) {
     delete h;
     return fail(CG_ENOMEM, "out of host memory");
@@ -717,6 +724,12 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
   p.clear_total = counts && clear_total;
 
   if (!aligned || mode == kCounting) cp.kernel = kNaive;      // (the plain kernel is the layer's family: the others were turned away)
+  if (cp.kernel == kRows && cp.rows.pf == 2 && residual) {
+    // (see plan_over)
+    const char *y0 = (const char*)y, *r0 = (const char*)residual;
+    const size_t len = (size_t)p.m_total * d.c_out * 2;
+    if (y0 < r0 + len && r0 < y0 + len) cp.rows = cp.rows_over;
+  }
   hipStream_t s = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
   auto launch = [&](const cg::Params& q) -> hipError_t {

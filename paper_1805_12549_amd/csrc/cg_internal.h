@@ -160,13 +160,14 @@ struct RowsPlan {
   int logp, pr, n_pl;      // log2 of the patch row pitch; patch rows, maximum over tiles; 1 KB loads per patch
   int resident, nb;        // 1: all weights stay in LDS; stage buffers
   int psz, pstr;           // bytes per patch; bytes between stage buffers
+  int pf;                  // fragments per wavefront: 1 or 2
   int fwl, nfc;            // fragment of a wavefront: 2^fwl columns (-1: 32 pixels in a row), fragments per row group
   int wres, shuf, shuf_bytes, tabs, lds_bytes;   // LDS offsets of resident weights (-1: none), shuffled rows, tables
   size_t wpk_base_bytes, wpk_cond_bytes;
 };
 
-// cps: 0 = pick, 4 or 2 = that (for a handle whose weights are packed)
-RowsPlan rows_plan(const cg_conv_desc& d, int n_cu, int cps);
+// cps: 0 = pick, 4 or 2 = that (for a handle whose weights are packed); max_pf: the most fragments per wavefront
+RowsPlan rows_plan(const cg_conv_desc& d, int n_cu, int cps, int max_pf);
 // the same kernel on 1x1 layers of stride 1
 RowsPlan point_plan(const cg_conv_desc& d, int n_cu);
 hipError_t launch_rows_pack(const RowsPlan& plan, const Params& p, void* wpk_base, void* wpk_cond, hipStream_t s);

@@ -29,9 +29,10 @@
 //               1.3 to 2 times slower than this form at 64 channels and no faster at 256 and 512.)
 //   output      scale/shift by decision, residual, ReLU, convert (Eq. 1), stored from registers.
 //
-// Two fragments per wavefront, which read a stage's weights from LDS once for both, leave no registers for two sets of sums
-// each: outputs for an unfired gate were written first and corrected where a gate fired.  Over 60 layers that was at most
-// 2 % faster than one fragment with its best tiles, and mostly slower.
+// PF = 2 (bf16 layers with many channels and pixels): a wavefront takes two fragments and reads a stage's weights from LDS once for
+// both, which is what bounds the loop there (one fragment: 3 KB of LDS reads for two products, i.e. 192 of 128 clocks).
+// Its registers do not hold two sets of sums per fragment; the outputs for an unfired gate are written first and
+// corrected where a gate fired.
 //
 // TAPS = 1 (1x1 layers of stride 1): a row is a pixel, a patch the tile's pixels (no halo), a stage up to eight chunks of one
 // tap.  1024 channels at 14x14, 64 images: bf16 49 us, int8 36; 89 and 101 on the large-tile kernel.
@@ -261,7 +262,7 @@ enum : unsigned {
 
 constexpr int kParamsAt = (sizeof(RowsArgs) + alignof(Params) - 1) / alignof(Params) * alignof(Params);   // of the kernel's arguments
 
-template <typename Tr, int CPS, int TAPS>
+template <typename Tr, int CPS, int PF, int TAPS>
 __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params) {
   using acc16 = typename Tr::acc16;
   using acc_t = typename Tr::acc_t;
@@ -468,29 +469,36 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   bare_barrier();                                    // the counters are set up
   const int rowb = SB << a.logp;                     // bytes per patch row
   const unsigned wlane = lh * 1024 + lj * 16;        // lane's offset of its weight rows in a K step
-  acc16 accP[2], accS[2];                            // base sums; base and conditional sums
+  acc16 accP[PF][2], accS[PF][2];                    // base sums; base and conditional sums (PF = 2: accP holds these too)
 
   // One stage: the operand reads of K steps k+1 and k+2 are in flight while step k is multiplied.
-  auto mma_stage = [&](unsigned pat, unsigned wgt, const int (&pa)[3], acc16 (&acc)[2]) __attribute__((always_inline)) {
-    constexpr int PD = KS > 1 ? 2 : 1, NR = PD + 1;
-    i32x4 wa[NR][2], xb[NR];
+  auto mma_stage = [&](auto f0c, auto nfc_, unsigned pat, unsigned wgt, const int (&pa)[PF][3], acc16 (&acc)[PF][2])
+      __attribute__((always_inline)) {
+    constexpr int F0 = decltype(f0c)::value, NF = decltype(nfc_)::value;       // fragments F0 .. F0 + NF - 1
+    constexpr int PD = NF == 1 && KS > 1 ? 2 : 1, NR = PD + 1;
+    i32x4 wa[NR][2], xb[NR][NF];
     const unsigned wad = wgt + wlane;
     auto read_step = [&](auto kc) __attribute__((always_inline)) {
       constexpr int k = decltype(kc)::value, n = k % NR, tap = k / PAIRS, r = tap / 3, c = tap % 3;
       wa[n][0] = lds_read16<k * 2048>(wad);
       wa[n][1] = lds_read16<k * 2048 + 512>(wad);
-      xb[n] = lds_read16<0>((unsigned)((pa[c] + (int)(pat + r * rowb)) ^ ((k % PAIRS) * 32)));
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+        xb[n][f] = lds_read16<0>((unsigned)((pa[F0 + f][c] + (int)(pat + r * rowb)) ^ ((k % PAIRS) * 32)));
     };
     static_for<PD>([&](auto kc) __attribute__((always_inline)) { read_step(kc); });
     static_for<KS>([&](auto kc) __attribute__((always_inline)) {
       constexpr int k = decltype(kc)::value, n = k % NR;
       constexpr int later = KS - 1 - k < PD - 1 ? KS - 1 - k : PD - 1;
-      __builtin_amdgcn_s_waitcnt(0xC07F | ((later * 3) << 8));
+      __builtin_amdgcn_s_waitcnt(0xC07F | ((later * (2 + NF)) << 8));
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (k + PD < KS) read_step(std::integral_constant<int, k + PD>{});
       __builtin_amdgcn_sched_barrier(0);
-      acc[0] = Tr::mfma(wa[n][0], xb[n], acc[0]);
-      acc[1] = Tr::mfma(wa[n][1], xb[n], acc[1]);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        acc[F0 + f][0] = Tr::mfma(wa[n][0], xb[n][f], acc[F0 + f][0]);
+        acc[F0 + f][1] = Tr::mfma(wa[n][1], xb[n][f], acc[F0 + f][1]);
+      }
       __builtin_amdgcn_sched_barrier(0);
     });
   };
@@ -507,10 +515,10 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int m = (int)(dl << (31 - 16 * f - i)) >> 31;
-        const acc_t pv = accP[f][i], sv = accS[f][i];
+        const acc_t pv = accP[0][f][i], sv = accS[0][f][i];
         acc_t r;
         from_bits((as_bits(sv) & m) | (as_bits(pv) & ~m), r);
-        accP[f][i] = r;
+        accP[0][f][i] = r;
       }
   };
   // bf16 accesses to y and the residual go in the transposed order of transpose4: access j is 16 pixels of one lane
@@ -518,14 +526,20 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   auto px_of = [&](int px, int h) __attribute__((always_inline)) {   // pixel 16*h + lane % 16 of the fragment
     return __builtin_amdgcn_ds_bpermute((lane & 15) * 4 + h * 64, px);
   };
-  auto lane_bytes = [&]() __attribute__((always_inline)) { return (lane & 32 ? 64 : 0) + (lane & 16 ? 16 : 0); };
-  // Output of the lanes' pixels px (counted from pixel m0 of the batch; -1: none), 2 x 16 channels each, in two steps that
-  // whole wavefronts execute.  First the values, from sums and the decisions in dl (bit 16*f + i):
-  auto finish = [&](const acc16 (&sum)[2], unsigned dl, long long m0, int px, i32x4 (&v)[4]) __attribute__((always_inline)) {
+  auto lane_bytes = [&]() __attribute__((always_inline)) {
+    int b = (lane & 32 ? 64 : 0) + (lane & 16 ? 16 : 0);
+    if constexpr (PF == 2) asm volatile("" : "+v"(b));        // (addresses formed from it are not kept across the K loops)
+    return b;
+  };
+  // Output of the lanes' pixels px (counted from pixel m0 of the batch; -1: none), 2 x 16 channels each, in three steps that
+  // whole wavefronts execute.  First the values, from sums and the decisions in dl (bit 16*f + i; UNI: all the same):
+  auto finish = [&](auto uni, const acc16 (&sum)[2], unsigned dl, long long m0, int px, i32x4 (&v)[4]) __attribute__((always_inline)) {
+    constexpr bool UNI = decltype(uni)::value;
     const float relu_lo = (a.flags & kRelu) ? 0.0f : -__builtin_inff();
     const int rowy = a.c_out * 2;
     const int pxj[2] = {px_of(px, 0), px_of(px, 1)};
     const long long first = m0 * rowy + cbk * (kBn * 2) + lane_bytes();
+    const float* const taken = aff + (dl ? 128 : 0);
     i32x4 rs[4];                                     // the lane's four 16-byte pieces
     if (a.flags & kResidual) {
 #pragma unroll
@@ -546,13 +560,19 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
         if (a.flags & kAffine) {
 #pragma unroll
           for (int q = 0; q < 2; ++q) {
-            const i32x4 a0 = *(const i32x4*)(aff + cl + 4 * q), b0 = *(const i32x4*)(aff + 64 + cl + 4 * q);
-            const i32x4 a1 = *(const i32x4*)(aff + 128 + cl + 4 * q), b1 = *(const i32x4*)(aff + 192 + cl + 4 * q);
+            if constexpr (UNI) {
+              const f32x4 at = *(const f32x4*)(taken + cl + 4 * q), bt = *(const f32x4*)(taken + 64 + cl + 4 * q);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int m = (int)(dl << (31 - 16 * f - 8 * h - 4 * q - e)) >> 31;
-              r[4 * q + e] = fmaf(__int_as_float((a1[e] & m) | (a0[e] & ~m)), r[4 * q + e],
-                                  __int_as_float((b1[e] & m) | (b0[e] & ~m)));
+              for (int e = 0; e < 4; ++e) r[4 * q + e] = fmaf(at[e], r[4 * q + e], bt[e]);
+            } else {
+              const i32x4 a0 = *(const i32x4*)(aff + cl + 4 * q), b0 = *(const i32x4*)(aff + 64 + cl + 4 * q);
+              const i32x4 a1 = *(const i32x4*)(aff + 128 + cl + 4 * q), b1 = *(const i32x4*)(aff + 192 + cl + 4 * q);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const int m = (int)(dl << (31 - 16 * f - 8 * h - 4 * q - e)) >> 31;
+                r[4 * q + e] = fmaf(__int_as_float((a1[e] & m) | (a0[e] & ~m)), r[4 * q + e],
+                                    __int_as_float((b1[e] & m) | (b0[e] & ~m)));
+              }
             }
           }
         }
@@ -566,6 +586,28 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           v[2 * f + h][e] = bf16_pair(max_of(r[2 * e], relu_lo), max_of(r[2 * e + 1], relu_lo));
+        if constexpr (PF == 2) __builtin_amdgcn_sched_barrier(0);    // (one piece at a time: no registers for more)
+      }
+  };
+  // then, where y holds the values for an unfired gate already, each channel's own
+  auto choose = [&](unsigned dl, long long m0, int px, i32x4 (&v)[4]) __attribute__((always_inline)) {
+    const int rowy = a.c_out * 2;
+    const int pxj[2] = {px_of(px, 0), px_of(px, 1)};
+    const long long first = m0 * rowy + cbk * (kBn * 2) + lane_bytes();
+    i32x4 base[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      base[j] = i32x4{0, 0, 0, 0};
+      if (pxj[j & 1] >= 0) base[j] = *(const i32x4*)(a.y + first + (long long)pxj[j & 1] * rowy + (j >> 1) * 32);
+    }
+    transpose4(base);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned lo = (unsigned)((int)(dl << (31 - 8 * j - 2 * e)) >> 31), hi = (unsigned)((int)(dl << (30 - 8 * j - 2 * e)) >> 31);
+        const unsigned m = (lo & 0xffffu) | (hi & 0xffff0000u);
+        v[j][e] = (int)(((unsigned)v[j][e] & m) | ((unsigned)base[j][e] & ~m));
       }
   };
   // and the stores
@@ -581,7 +623,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   auto emit_fast = [&](unsigned dl, long long m0, int px) __attribute__((always_inline)) {
     if constexpr (Base::kDtype != CG_I8) {
       i32x4 v[4];
-      finish(accP, dl, m0, px, v);
+      finish(std::false_type{}, accP[0], dl, m0, px, v);
       if (a.flags & kShuf2) {
         // Shuffled channel order (Sec. 3.3): channel j of group i goes to position j*groups + i of its pixel.  The
         // block's 64 channels are `ng` groups x `nj` channels: an LDS row holds a pixel's in the order [j][group], so
@@ -652,7 +694,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const int m = (int)(dl << (31 - 16 * f - 4 * q - e)) >> 31;
-            const int sv = accP[f][4 * q + e];
+            const int sv = accP[0][f][4 * q + e];
             long long t = (long long)sv * ((m1_[e] & m) | (m0_[e] & ~m)) + addends[cl + 4 * q + e];
             if (a.flags & kResidual) t += (long long)(int8_t)((unsigned)rs[f][q] >> (8 * e)) * a.rq_res_mult;
             const int th = med3((int)(t >> 32), h_lo, h_hi);
@@ -688,7 +730,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
           const int co = co0 + i, grp = co / q.cpg;
           const long long o = m * q.c_out + (co - grp * q.cpg) * q.groups + grp;
           const bool fired = ((d16 >> i) & 1u) != 0u;
-          const acc_t sv = accP[f][i];
+          const acc_t sv = accP[0][f][i];
           if constexpr (Base::kDtype == CG_I8)
             store_int(q, o, finish_int(q, sv, fired, co, o));
           else
@@ -702,7 +744,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const acc_t sv = accP[f][4 * q4 + e];
+          const acc_t sv = accP[0][f][4 * q4 + e];
           v[q4][e] = as_bits(sv);
         }
       finish_store8<Base>(q, v[0], v[1], d16 & 0xffu, co0, o);
@@ -715,37 +757,45 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   for (int t = 0; t < tiles; ++t) {
     const int R0 = tile_row(t), rows_here = t < a.full ? a.tr : tail_rows;
     const long long m0 = (long long)R0 * a.wo;       // the tile's first output pixel
-    // this lane's pixel of the wavefront's fragment: row and column in the tile
+    // this lane's pixels, one in each of the wavefront's fragments `wave` and (PF = 2) wave + kCw: row and column in the tile
     const int next = v + a.s;                        // first stage of the next tile
-    int px, pimg, pa[3];
-    bool inside;                                     // the pixel exists
-    if constexpr (TAPS == 1) {                       // a row is a pixel
-      const int i = wave * 32 + lj;
-      inside = i < rows_here;
-      px = inside ? i : -1;
-      pa[0] = slot_addr<CPS>(inside ? i : 0, lh);
-      pimg = a.chan_mask ? (R0 + (inside ? i : 0)) / a.hp : 0;
-    } else {
+    int px[PF], pimg[PF], pa[PF][3];
+    bool inside[PF], any[PF];                        // the pixel exists; any of the fragment does
+    int lp = lj;
+    if constexpr (PF == 2) asm volatile("" : "+v"(lp));       // (formed for each tile: no registers to keep them)
+#pragma unroll
+    for (int g = 0; g < PF; ++g) {
+      const int fr = wave + kCw * g;
       int lr, wo_;
+      if constexpr (TAPS == 1) {                     // a row is a pixel
+        const int i = fr * 32 + lp;
+        px[g] = i < rows_here ? i : -1;
+        inside[g] = i < rows_here;
+        any[g] = __ballot(inside[g]) != 0ull;
+        pa[g][0] = slot_addr<CPS>(inside[g] ? i : 0, lh);
+        pimg[g] = a.chan_mask ? (R0 + (inside[g] ? i : 0)) / a.hp : 0;
+        continue;
+      }
       if (a.fwl < 0) {
-        const int i = wave * 32 + lj;
+        const int i = fr * 32 + lp;
         lr = div16(i, a.magic_wo);
         wo_ = i - lr * a.wo;
       } else {
-        const int fq = div16(wave, a.magic_nfc);
-        lr = (fq << (5 - a.fwl)) + (lj >> a.fwl);
-        wo_ = ((wave - fq * a.nfc) << a.fwl) + (lj & ((1 << a.fwl) - 1));
+        const int fq = div16(fr, a.magic_nfc);
+        lr = (fq << (5 - a.fwl)) + (lp >> a.fwl);
+        wo_ = ((fr - fq * a.nfc) << a.fwl) + (lp & ((1 << a.fwl) - 1));
       }
-      inside = lr < rows_here && wo_ < a.wo;
-      if (!inside) lr = wo_ = 0;                     // lanes past the tile's end read pixel 0 and are dropped
+      inside[g] = lr < rows_here && wo_ < a.wo;
+      any[g] = __ballot(inside[g]) != 0ull;
+      if (!inside[g]) lr = wo_ = 0;                  // lanes past the tile's end read pixel 0 and are dropped
       const int img0 = div16(R0, a.magic_ho);
       const int rho0 = img0 * a.hp + (R0 - img0 * a.ho) * a.stride;
       const int R = R0 + lr;
-      pimg = div16(R, a.magic_ho);
-      const int slot0 = ((pimg * a.hp + (R - pimg * a.ho) * a.stride - rho0) << a.logp) + wo_ * a.stride;
+      pimg[g] = div16(R, a.magic_ho);
+      const int slot0 = ((pimg[g] * a.hp + (R - pimg[g] * a.ho) * a.stride - rho0) << a.logp) + wo_ * a.stride;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) pa[c] = slot_addr<CPS>(slot0 + c, lh);
-      px = inside ? lr * a.wo + wo_ : -1;
+      for (int c = 0; c < 3; ++c) pa[g][c] = slot_addr<CPS>(slot0 + c, lh);
+      px[g] = inside[g] ? lr * a.wo + wo_ : -1;
     }
     auto pass_by = [&]() __attribute__((always_inline)) {
       publish(done + 4 * wave, next);
@@ -753,41 +803,56 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       v = next;
       while (b >= a.nb) b -= a.nb;
     };
-    if (__ballot(inside) == 0ull) {                  // no pixel of this tile is this wavefront's
+    if (!any[0]) {                                   // no pixel of this tile is this wavefront's
       pass_by();
       continue;
     }
 #pragma unroll
-    for (int f = 0; f < 2; ++f)
+    for (int g = 0; g < PF; ++g)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) accP[f][i] = 0;
-    // stages first .. last - 1
-    auto stages = [&](int first, int last, acc16 (&acc)[2]) __attribute__((always_inline)) {
+      for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) accP[g][f][i] = 0;
+    // stages first .. last - 1 for fragments f0 .. f0 + nf - 1
+    auto stages = [&](auto f0, auto nf, int first, int last, acc16 (&acc)[PF][2]) __attribute__((always_inline)) {
 #pragma nounroll
       for (int s = first; s < last; ++s) {
         wait_counters<kLw>(landed, lane, v + 1, have);
         const unsigned pat = lds0 + b * a.pstr;
-        mma_stage(pat, a.wres < 0 ? pat + a.psz : lds0 + a.wres + s * WB, pa, acc);
+        mma_stage(f0, nf, pat, a.wres < 0 ? pat + a.psz : lds0 + a.wres + s * WB, pa, acc);
         ++v;
         publish(done + 4 * wave, v);
         if (++b == a.nb) b = 0;
       }
       settle();
     };
-    stages(0, a.s0, accP);
+    constexpr std::integral_constant<int, 0> zero{};
+    constexpr std::integral_constant<int, 1> one{};
+    if constexpr (PF == 2) {
+      if (any[1])
+        stages(zero, std::integral_constant<int, 2>{}, 0, a.s0, accP);
+      else
+        stages(zero, one, 0, a.s0, accP);
+    } else {
+      stages(zero, one, 0, a.s0, accP);
+    }
 
-    unsigned dl = ~0u;                               // a dense layer takes the second pair everywhere
-    bool fired = false;
-    if (gated) {
+    unsigned dl[PF];                                 // a dense layer takes the second pair everywhere
+    bool fired[PF];
+#pragma unroll
+    for (int g = 0; g < PF; ++g) {
+      dl[g] = ~0u;
+      fired[g] = false;
+      if (!gated || !any[g]) continue;
       // ---- gate --------------------------------------------------------------------------------------
-      dl = 0u;
+      dl[g] = 0u;
 #pragma unroll
       for (int f = 1; f >= 0; --f)
 #pragma unroll
         for (int q4 = 3; q4 >= 0; --q4) {
           const i32x4 lo4 = *(const i32x4*)(tlo + 32 * f + 16 * lh + 4 * q4);
 #pragma unroll
-          for (int e = 3; e >= 0; --e) Tr::shift_in(dl, accP[f][4 * q4 + e], lo4[e]);
+          for (int e = 3; e >= 0; --e) Tr::shift_in(dl[g], accP[g][f][4 * q4 + e], lo4[e]);
         }
       if constexpr (Base::kDtype != CG_I8) {
         if (a.flags & kTwoSided) {
@@ -798,40 +863,69 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
               const f32x4 hi4 = *(const f32x4*)(thi + 32 * f + 16 * lh + 4 * q4);
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
-                const acc_t w = accP[f][4 * q4 + e];
-                if (!(w <= hi4[e])) dl &= ~(1u << (16 * f + 4 * q4 + e));
+                const acc_t w = accP[g][f][4 * q4 + e];
+                if (!(w <= hi4[e])) dl[g] &= ~(1u << (16 * f + 4 * q4 + e));
               }
             }
         }
       }
-      if (!inside) dl = 0u;
+      if (!inside[g]) dl[g] = 0u;
       if (a.chan_mask) {
         // channel-wise gate (Sec. 3.2): only the channels that keep their conditional path in this image
-        const uint32_t* mw = a.chan_mask + (long long)pimg * a.words + cbk * 2;
-        dl &= ((mw[0] >> (16 * lh)) & 0xffffu) | (((mw[1] >> (16 * lh)) & 0xffffu) << 16);
+        const uint32_t* mw = a.chan_mask + (long long)pimg[g] * a.words + cbk * 2;
+        dl[g] &= ((mw[0] >> (16 * lh)) & 0xffffu) | (((mw[1] >> (16 * lh)) & 0xffffu) << 16);
       }
       if (a.bitmap) {
-        const unsigned other = (unsigned)__shfl_xor((int)dl, 32, 64);      // the pixel's other channels
-        if (lh == 0 && inside)
-          *(uint2*)(a.bitmap + (m0 + px) * a.words + cbk * 2) =
-              uint2{(dl & 0xffffu) | (other << 16), (dl >> 16) | (other & 0xffff0000u)};
+        const unsigned other = (unsigned)__shfl_xor((int)dl[g], 32, 64);   // the pixel's other channels
+        if (lh == 0 && inside[g])
+          *(uint2*)(a.bitmap + (m0 + px[g]) * a.words + cbk * 2) =
+              uint2{(dl[g] & 0xffffu) | (other << 16), (dl[g] >> 16) | (other & 0xffff0000u)};
       }
-      fired = __ballot(dl != 0u) != 0ull;
+      fired[g] = __ballot(dl[g] != 0u) != 0ull;
     }
     if (gate_only) continue;     // first pass of the channel-wise gate: the decisions are all it produces
     // ---- conditional path, output ---------------------------------------------------------------------
-    if (fired) {
+    if constexpr (PF == 1) {
+      if (fired[0]) {
 #pragma unroll
-      for (int f = 0; f < 2; ++f) accS[f] = accP[f];
-      stages(a.s0, a.s, accS);
-      pick(dl);
-    } else if (gated) {
-      pass_by();
+        for (int f = 0; f < 2; ++f) accS[0][f] = accP[0][f];
+        stages(zero, one, a.s0, a.s, accS);
+        pick(dl[0]);
+      } else if (gated) {
+        pass_by();
+      }
+      if (a.flags & kFast)
+        emit_fast(dl[0], m0, px[0]);
+      else if (inside[0])
+        emit_any(dl[0], m0 + px[0]);
+    } else if constexpr (Base::kDtype != CG_I8) {
+      // No registers for two sets of sums: every fragment's outputs for an unfired gate are written first, and where it goes
+      // on the fired channels' replace them at the end.
+      i32x4 w[4];
+      if (gated) {
+#pragma unroll
+        for (int g = 0; g < PF; ++g) {
+          if (!any[g]) continue;
+          finish(std::true_type{}, accP[g], 0u, m0, px[g], w);
+          store(w, m0, px[g]);
+        }
+      }
+      if (fired[0] && fired[1])
+        stages(zero, std::integral_constant<int, 2>{}, a.s0, a.s, accP);
+      else if (fired[0])
+        stages(zero, one, a.s0, a.s, accP);
+      else if (fired[1])
+        stages(one, one, a.s0, a.s, accP);
+      else if (gated)
+        pass_by();
+#pragma unroll
+      for (int g = 0; g < PF; ++g) {
+        if (gated ? !fired[g] : !any[g]) continue;
+        finish(std::true_type{}, accP[g], 1u, m0, px[g], w);
+        if (gated) choose(dl[g], m0, px[g], w);
+        store(w, m0, px[g]);
+      }
     }
-    if (a.flags & kFast)
-      emit_fast(dl, m0, px);
-    else if (inside)
-      emit_any(dl, m0 + px);
   }
   mark_if_gave_up(have);
 }
@@ -883,20 +977,20 @@ __global__ void pack_rows_kernel(const char* __restrict__ w, char* __restrict__ 
 }
 
 
-template <typename Tr, int CPS, int TAPS>
+template <typename Tr, int CPS, int PF, int TAPS>
 hipError_t launch_rows_one(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
   const unsigned blocks = a.xcd_cb ? (unsigned)(g.n_slots * g.n_cb) : (unsigned)a.per_xcd * 8u;
   static std::atomic<uint64_t> asked{0};
-  const hipError_t attr = allow_lds((const void*)gated_conv_rows_kernel<Tr, CPS, TAPS>, kLds, asked);
+  const hipError_t attr = allow_lds((const void*)gated_conv_rows_kernel<Tr, CPS, PF, TAPS>, kLds, asked);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((gated_conv_rows_kernel<Tr, CPS, TAPS>), dim3(blocks), dim3(kNt), (size_t)g.lds_bytes, s, a, p);
+  hipLaunchKernelGGL((gated_conv_rows_kernel<Tr, CPS, PF, TAPS>), dim3(blocks), dim3(kNt), (size_t)g.lds_bytes, s, a, p);
   return hipGetLastError();
 }
 
 template <typename Tr>
 hipError_t launch_point(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
-  if (g.cps == 8) return launch_rows_one<Tr, 8, 1>(g, p, a, s);
-  return g.cps == 4 ? launch_rows_one<Tr, 4, 1>(g, p, a, s) : launch_rows_one<Tr, 2, 1>(g, p, a, s);
+  if (g.cps == 8) return launch_rows_one<Tr, 8, 1, 1>(g, p, a, s);
+  return g.cps == 4 ? launch_rows_one<Tr, 4, 1, 1>(g, p, a, s) : launch_rows_one<Tr, 2, 1, 1>(g, p, a, s);
 }
 
 unsigned magic16(int d) { return d == 1 ? 0u : (unsigned)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d); }
@@ -944,7 +1038,7 @@ bool plan_walk(const cg_conv_desc& d, int cps, RowsPlan& g, int& base_k, int& c_
 }
 
 // Plan with stages of `cps` chunks; ok = 0 where the shape does not allow them.  *cost: estimated clocks.
-RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, double* cost) {
+RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* cost) {
   RowsPlan g{};
   int base_k, c_cond;
   if (!plan_walk(d, cps, g, base_k, c_cond)) return g;
@@ -1020,6 +1114,7 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, double* cost) {
                          (resident ? S * wb / 60.0 : 0.0);
         if (c < best) {
           best = c;
+          g.pf = 1;
           g.fwl = fwl;
           g.nfc = nfc;
           g.tr = t;
@@ -1051,13 +1146,13 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, double* cost) {
 
 }  // namespace
 
-RowsPlan rows_plan(const cg_conv_desc& d, int n_cu, int cps) {
+RowsPlan rows_plan(const cg_conv_desc& d, int n_cu, int cps, int max_pf) {
   RowsPlan none{};
   if (d.in_dtype != CG_BF16 && d.in_dtype != CG_I8) return none;
   if (d.kh != 3 || d.kw != 3 || d.stride < 1 || d.stride > 2 || d.pad > 1) return none;
   double c4 = 1e30, c2 = 1e30;
-  const RowsPlan a = cps == 2 ? none : plan_cps(d, n_cu, 4, &c4);
-  const RowsPlan b = cps == 4 ? none : plan_cps(d, n_cu, 2, &c2);
+  const RowsPlan a = cps == 2 ? none : plan_cps(d, n_cu, 4, max_pf, &c4);
+  const RowsPlan b = cps == 4 ? none : plan_cps(d, n_cu, 2, max_pf, &c2);
   return a.ok && (!b.ok || c4 <= c2) ? a : b;
 }
 
@@ -1074,7 +1169,7 @@ RowsPlan point_plan(const cg_conv_desc& d, int n_cu) {
   }
   const int wb = g.cps / 2 * 2048;
   g.taps = 1;
-  g.nfc = g.hp = 1;
+  g.pf = g.nfc = g.hp = 1;
   g.fwl = -1;
   const long long px = (long long)d.n_max * d.h * d.w;
   if (px >= (1ll << 30)) return g;
@@ -1192,8 +1287,9 @@ hipError_t launch_rows(const RowsPlan& g, const Params& p, const void* w0, const
             ((p.out_dtype == CG_BF16 || (p.out_dtype == CG_I8 && p.rq_shift >= 2)) && (!p.shuffle || shuf2) ? kFast : 0u) | (shuf2 ? kShuf2 : 0u);
   if (g.taps == 1)
     return p.in_dtype == CG_I8 ? launch_point<I8Rows>(g, p, a, s) : launch_point<Bf16Rows>(g, p, a, s);
-  if (p.in_dtype == CG_I8) return g.cps == 4 ? launch_rows_one<I8Rows, 4, 9>(g, p, a, s) : launch_rows_one<I8Rows, 2, 9>(g, p, a, s);
-  return g.cps == 4 ? launch_rows_one<Bf16Rows, 4, 9>(g, p, a, s) : launch_rows_one<Bf16Rows, 2, 9>(g, p, a, s);
+  if (p.in_dtype == CG_I8) return g.cps == 4 ? launch_rows_one<I8Rows, 4, 1, 9>(g, p, a, s) : launch_rows_one<I8Rows, 2, 1, 9>(g, p, a, s);
+  if (g.pf == 2) return launch_rows_one<Bf16Rows, 4, 2, 9>(g, p, a, s);     // (planned for stages of four chunks only)
+  return g.cps == 4 ? launch_rows_one<Bf16Rows, 4, 1, 9>(g, p, a, s) : launch_rows_one<Bf16Rows, 2, 1, 9>(g, p, a, s);
 }
 
 }  // namespace cg

@@ -1,5 +1,5 @@
 """GPU parity of the row-tiled matrix-core kernel at the edges of its tiles: every fragment shape, tiles that end inside an
-image or an image row, weights that stay in LDS or stream, the shuffled store."""
+image or an image row, weights that stay in LDS or stream, the shuffled store, one and two fragments per wavefront."""
 import numpy as np
 import pytest
 import torch
@@ -24,8 +24,8 @@ SHAPES = [
     S(2, 31, 9, 128, 64, stride=2),
     S(4, 17, 40, 128, 128, groups=2),          # channel groups: a block inside one
     S(3, 13, 21, 128, 128, groups=8),          # a block of several
-    S(130, 14, 14, 256, 256),                  # several tiles per workgroup that straddle images
-    S(30, 14, 14, 256, 1024),                  # more channel blocks than XCDs
+    S(130, 14, 14, 256, 256),                  # two fragments per wavefront, 32 x 14 pixel tiles
+    S(30, 14, 14, 256, 1024),                  # the same in runs of 32 pixels
 ]
 
 
@@ -81,7 +81,7 @@ def test_point_wise_shapes(shape):
 
 
 def test_residual_may_be_the_output():
-    """y written over the residual."""
+    """y written over the residual (two fragments per wavefront write y twice, which that must not see)."""
     shape = S(130, 14, 14, 256, 256)
     inp = W.make_inputs(shape, 9300, kind="coherent", rho=0.3, round_bf16=True)
     gate = W.calibrate_gate(inp, 0.3, sample_images=2)
