@@ -1071,25 +1071,32 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
     }
     return pr;
   };
-  // Fragment shape, rows per tile and buffers: the choice with the least estimated time, in clocks.  The estimate follows what
-  // was measured for 3000 plans of 200 layers (bf16 and int8, 64 to 512 channels, firing rates of 0.1 to 0.6, clustered and
-  // not): the plan it picks takes 0.6 % longer than the best one in the mean and 6 % at most.  (Constants fitted to half of
-  // the layers: 0.9 % and 8 % on the other half.  With constants that left most of what an output costs to two fragments per
-  // wavefront: 3.3 % and 20 %.)
-  //   a K step costs 64 clocks of the matrix cores per fragment on one SIMD, a third more where a lone wavefront has to wait
-  //   for its LDS reads; as wavefronts run free, a SIMD with fewer fragments than the fullest one helps by a quarter;
+  // Fragments per wavefront and their shape, rows per tile and buffers: the choice with the least estimated time, in clocks.
+  // The estimate follows what was measured for 4000 plans of 257 layers (bf16 and int8, 64 to 512 channels, firing rates of
+  // 0.1 to 0.6, clustered and not): the plan it picks takes 0.5 % longer than the best one in the mean and 6 % at most.
+  // (Constants fitted to half of the layers: 0.7 % and 10 % on the other half.  The ones before, which counted too little
+  // for an output: 3.0 % and 32 %.)
+  //   A K step costs 64 clocks of the matrix cores per fragment on one SIMD, half as much again where a lone wavefront has to
+  //   wait for its LDS reads, and an eighth less where a wavefront reads the weights for two fragments; as wavefronts run
+  //   free, a SIMD with fewer fragments than the fullest one helps by a third;
   //   a conditional stage costs the share of the fragments that hold a fired pixel, by the fragment's height, and some;
   //   the vector-memory path serves a line every two clocks; with two or three buffers a stage's latency shows;
-  //   gate and output cost 3200 clocks a fragment, fragments of four columns a little more (more lines), and a tile 4000.
+  //   gate and output cost 2800 clocks a fragment, 5800 where it is written twice (two fragments to a wavefront), fragments
+  //   of four columns a little more (more lines), and a tile 3500.
+  // Two fragments pay with many channels and tiles that fill them: 512 at 28x28, 12 images 43 us against 50; 256 at 14x14, 256
+  // images 61 and 61; 128 at 28x28, 128 images 47 and 41.
   const int shuf_bytes = d.shuffle && d.in_dtype == CG_BF16 && d.out_dtype == CG_BF16 && !(d.epilogue & CG_EPI_RESIDUAL) ? kCw * 32 * kShufRow : 0;
   double best = 1e30;
+  const bool wide = d.in_dtype == CG_BF16 && d.out_dtype == CG_BF16 && !d.shuffle && cps == 4;
+  for (int pf = 1; pf <= (wide ? max_pf : 1); ++pf)
   for (int fwl = -1; fwl <= 5; ++fwl) {
     if (fwl == 0 || fwl == 1) continue;                    // (16 and 32 rows of one or two columns: no better than a run)
     const int fh = fwl < 0 ? 1 : 32 >> fwl, nfc = fwl < 0 ? 1 : (wo + (1 << fwl) - 1) >> fwl;
-    if (nfc > kCw) continue;
-    const int tmax = fwl < 0 ? 32 * kCw / wo : kCw / nfc * fh;
+    const int frags_max = kCw * pf;
+    if (nfc > frags_max) continue;
+    const int tmax = fwl < 0 ? 32 * frags_max / wo : frags_max / nfc * fh;
     if (tmax < 1) continue;
-    const double beta = fwl < 0 ? (wo >= 32 ? 0.80 : wo >= 16 ? 0.72 : 0.63) : fh == 1 || fh == 8 ? 0.70 : 0.61;
+    const double beta = fwl < 0 ? (wo >= 32 ? 0.85 : wo >= 16 ? 0.72 : 0.53) : fh == 1 ? 0.67 : fh == 8 ? 0.64 : 0.59;
     const int step = fwl < 0 ? 1 : fh;
     for (int t = tmax; t >= step && 4 * t >= tmax; t -= step) {
       const int pr = patch_rows(t);
@@ -1102,19 +1109,19 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
         if (fixed > kLds || nb < 2) continue;
         if (nb > 8) nb = 8;
         const double lines = (double)(pr * (d.w < (1 << g.logp) ? d.w : (1 << g.logp))) + (resident ? 0 : wb / 128.0);
-        const double stream = 2.0 * lines + (nb == 2 ? 940.0 : nb == 3 ? 230.0 : 0.0);
+        const double stream = 2.0 * lines + (nb == 2 ? 910.0 : nb == 3 ? 150.0 : 0.0);
         auto tile = [&](int r) {
           const int frags = fwl < 0 ? (r * wo + 31) / 32 : (r + fh - 1) / fh * nfc;
-          const double per_simd = 0.75 * ((frags + 3) / 4) + 0.25 * frags / 4.0;
-          const double mm = ks * 64.0 * per_simd * (frags <= 4 ? 1.38 : 1.05), mc = mm * (beta + 0.15);
-          return g.stages[0] * ((mm > stream ? mm : stream) + 60.0) + g.stages[1] * ((mc > stream ? mc : stream) + 60.0) + 4000.0 +
-                 per_simd * 3200.0 * (fwl == 2 ? 1.05 : 1.0);
+          const double per_simd = 0.67 * ((frags + 3) / 4) + 0.33 * frags / 4.0;
+          const double mm = ks * 64.0 * per_simd * (frags <= 4 ? 1.55 : 1.10) * (frags > kCw ? 0.87 : 1.0), mc = mm * (beta + 0.15);
+          return g.stages[0] * (mm > stream ? mm : stream) + g.stages[1] * (mc > stream ? mc : stream) + 3500.0 +
+                 per_simd * (pf == 2 ? 5800.0 : 2800.0) * (fwl == 2 ? 1.07 : 1.0);
         };
         const double c = (slot_rows / t) * tile(t) + (slot_rows % t ? tile(slot_rows % t) : 0.0) + 1500.0 +
                          (resident ? S * wb / 60.0 : 0.0);
         if (c < best) {
           best = c;
-          g.pf = 1;
+          g.pf = pf;
           g.fwl = fwl;
           g.nfc = nfc;
           g.tr = t;

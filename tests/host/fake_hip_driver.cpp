@@ -102,7 +102,7 @@ static void plans_are_kept() {
       EXPECT(round == 0 || device_asked <= 1);
     }
   cg_conv_destroy(h);
-  // also where y is written over the residual
+  // two fragments per wavefront, y over the residual: another plan, kept as well
   static float stat[256], one[256];
   for (float& v : one) v = 1.0f;
   cg_conv_desc d;
@@ -113,6 +113,7 @@ static void plans_are_kept() {
   d.w_base = (const void*)0x1000; d.w_cond = (const void*)0x2000;
   d.packed = (void*)0x100000; d.packed_bytes = cg_conv_packed_bytes(&d);
   EXPECT(cg_conv_create(&h, &d, nullptr) == CG_OK);
+  const void* kernel[2];
   for (int n = 256; n >= 200; n -= 56)
     for (int round = 0; round < 2; ++round)
       for (int over = 0; over < 2; ++over) {
@@ -121,6 +122,8 @@ static void plans_are_kept() {
         EXPECT(cg_conv_forward(h, n, (void*)0x200000000ull, res, y, nullptr, nullptr, (void*)0x500000000ull,
                                cg_conv_workspace_bytes(h, n), nullptr) == CG_OK);
         EXPECT((round == 0 && !over) || device_asked <= 1);
+        kernel[over] = launches.back().kernel;
+        EXPECT(!over || kernel[0] != kernel[1]);
       }
   cg_conv_destroy(h);
 }

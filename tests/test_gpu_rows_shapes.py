@@ -24,8 +24,10 @@ SHAPES = [
     S(2, 31, 9, 128, 64, stride=2),
     S(4, 17, 40, 128, 128, groups=2),          # channel groups: a block inside one
     S(3, 13, 21, 128, 128, groups=8),          # a block of several
-    S(130, 14, 14, 256, 256),                  # two fragments per wavefront, 32 x 14 pixel tiles
-    S(30, 14, 14, 256, 1024),                  # the same in runs of 32 pixels
+    S(130, 14, 14, 256, 256),                  # several tiles per workgroup that straddle images
+    S(100, 14, 14, 256, 256),                  # two fragments per wavefront, in runs of 32 pixels
+    S(30, 14, 14, 256, 1024),                  # the same, more channel blocks
+    S(16, 28, 28, 384, 384),                   # the same in fragments of 4 x 8 pixels
 ]
 
 
@@ -80,9 +82,10 @@ def test_point_wise_shapes(shape):
     print("  " + str(P.run_int8(q, thr, name=shape.name + " int8")), flush=True)
 
 
-def test_residual_may_be_the_output():
+@pytest.mark.parametrize("n", [100, 130], ids=["two_fragments", "one_fragment"])
+def test_residual_may_be_the_output(n):
     """y written over the residual (two fragments per wavefront write y twice, which that must not see)."""
-    shape = S(130, 14, 14, 256, 256)
+    shape = S(n, 14, 14, 256, 256)
     inp = W.make_inputs(shape, 9300, kind="coherent", rho=0.3, round_bf16=True)
     gate = W.calibrate_gate(inp, 0.3, sample_images=2)
     bf = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16)
