@@ -126,7 +126,7 @@ struct cg_conv {
   mutable std::mutex lock;
   mutable int kept_n[kKept] = {};          // their batch sizes; 0: none yet
   mutable int kept_next = 0;
-  mutable std::vector<CallPlan> kept;      // (kKept of them from the start: a forward call allocates nothing)
+  mutable std::vector<CallPlan> kept;      // (room for kKept from the start: a forward call allocates nothing)
 };
 
 namespace {
@@ -335,9 +335,13 @@ CallPlan call_plan(const cg_conv* h, int n) {
     if (h->kept_n[i] == n) return h->kept[i];
   const int at = h->kept_next;
   h->kept_next = (at + 1) % cg_conv::kKept;
-  h->kept[at] = plan_call(h, n);
+  const CallPlan c = plan_call(h, n);
+  if (at < (int)h->kept.size())
+    h->kept[at] = c;
+  else
+    h->kept.push_back(c);
   h->kept_n[at] = n;
-  return h->kept[at];
+  return c;
 }
 
 cg::Params base_params(const cg_conv* h) {
@@ -501,7 +505,7 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   const size_t tw = lay.table_stride / 4;
   try {
     h->staging.assign(tw * kTables, 0u);
-    h->kept.resize(cg_conv::kKept);
+    h->kept.reserve(cg_conv::kKept);
   } catch (...) {
     delete h;
     return fail(CG_ENOMEM, "out of host memory");
