@@ -177,7 +177,10 @@ class Layer:
         self.rho = fired / (s.m * s.c_out)
         d = W.unpack_bitmap(bm[: min(s.m, 8 * s.ho * s.wo)].cpu().numpy().view(np.uint32), s.c_out)
         self.beta_16x16 = W.occupancy(d, 16, 16)
-        self.beta_px64 = W.occupancy(d, 1, 64)          # the kernels' granule: one pixel x one 64-channel block
+        # The row-tiled kernel skips whole fragments of 32 pixels x one 64-channel block; runs of 32 pixels in a row are its
+        # coarsest ones (blocks of 4 x 8 and 8 x 4 pixels lie between these and single pixels).
+        self.beta_run = W.occupancy(d, 32, 64)
+        self.beta_px64 = W.occupancy(d, 1, 64)
         self.beta_px = W.occupancy(d, 1, s.c_out)
 
     def time_us(self, which):
@@ -223,13 +226,13 @@ def run_sweep(args, shapes, variant):
                         us_dense = L.time_us("dense")
                     us_g.append(L.time_us("gated"))
                     rho_meas.append(round(L.rho, 3))
-                    beta.append(round(L.beta_px64, 3))
+                    beta.append(round(L.beta_run, 3))
                     kname = KERNEL_OF.get(L.gated.variant, "?")
                     L.close()
                     del L
                     torch.cuda.empty_cache()
                 rows.append(dict(layer=s.name, maps=kind, base_fraction="1/%d" % G, kernel=kname, rho_target=rhos,
-                                 rho=rho_meas, beta_pixel_x_64ch=beta, us_gated=[round(v, 2) for v in us_g],
+                                 rho=rho_meas, beta_32px_run_x_64ch=beta, us_gated=[round(v, 2) for v in us_g],
                                  us_dense=round(us_dense, 2), crossover_rho=crossover(rho_meas, us_g, us_dense)))
                 print("sweep %-9s %-13s 1/G=1/%d dense %6.2f us  gated %s  crossover %s" %
                       (kind, s.name, G, us_dense, " ".join("%6.2f" % v for v in us_g), rows[-1]["crossover_rho"]),
@@ -392,7 +395,7 @@ def main():
         s = L.shape
         row = dict(layer=s.name, kernel=KERNEL_OF.get(L.gated.variant, "?"), us_gated=round(L.us_gated, 2),
                    rho=round(L.rho, 4), beta_16px_x_16ch=round(L.beta_16x16, 3), beta_pixel_x_64ch=round(L.beta_px64, 3),
-                   beta_pixel=round(L.beta_px, 3), eff_tops_gated=round(2 * s.dense_macs / L.us_gated / 1e6, 1))
+                   beta_32px_run_x_64ch=round(L.beta_run, 3), beta_pixel=round(L.beta_px, 3), eff_tops_gated=round(2 * s.dense_macs / L.us_gated / 1e6, 1))
         if L.us_dense is not None:
             row.update(us_dense=round(L.us_dense, 2), tops_dense=round(2 * s.dense_macs / L.us_dense / 1e6, 1),
                        speedup=round(L.us_dense / L.us_gated, 3))
@@ -404,7 +407,7 @@ def main():
         "value": round(value, 2), "unit": "TOP/s", "n_gpus": 1, "steps": steps, "warmup": warm,
         "ms_per_step": round(ms_per_step, 5), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": args.dtype, "data": "synthetic",
-        "config": {"workload": "ImageNet-shaped ResNet-18 gated 3x3 convs (configs[2]): batch %d, %s NHWC, G=4, "
+        "config": {"workload": "ImageNet-shaped ResNet-18 gated 3x3 convs: batch %d, %s NHWC, G=4, "
                                "%s gate maps, target firing %.2f%s; step = all %d layers" %
                                (args.batch, args.dtype, args.kind, args.rho,
                                 (", channel grouping" if args.grouped else "") +

@@ -270,7 +270,7 @@ def main():
     torch.cuda.set_device(0)
     out = {}
     for tag, rho in (("gated", args.rho), ("dense", 0.0)):
-        net = GatedResNet18(args.batch, args.size, rho=rho, grouped=args.grouped and rho > 0)
+        net = GatedResNet18(max(args.batch, 4), args.size, rho=rho, grouped=args.grouped and rho > 0)    # (calibrates on four)
         rng = np.random.default_rng(1)
         x = _t(np.tile(net.calib_input, (-(-args.batch // net.calib_input.shape[0]), 1, 1, 1))[:args.batch])
         for _ in range(3):
