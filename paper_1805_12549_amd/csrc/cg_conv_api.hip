@@ -90,6 +90,7 @@ struct Layout {
   size_t w_cond_off, w_cond_bytes;
   size_t wpk_base_off, wpk_cond_off;       // prepacked weights of the tiled kernel, if one covers the layer
   size_t wpd_base_off, wpd_cond_off;       // prepacked weights of the small-tile kernel, if it may be picked
+  size_t wpt_base_off;                     // prepacked weights of the large-tile kernel beside the row-tiled one's (tile_too)
   size_t total;
 };
 
@@ -117,6 +118,7 @@ struct cg_conv {
   int variant;              // resolved CG_VARIANT_*: the kernel family that covers the shape
   bool direct_ok;           // the small-tile kernel's weights are packed too: it takes the layer, if not every batch of it
   bool point_ok;            // a 1x1 layer of the large-tile family that runs on the row-tiled kernel
+  bool tile_too;            // ... and on the large-tile kernel where that suits the batch
   CallPlan first;           // plan for n_max
   Layout lay;
   cg::Params base;          // what is the same in every call
@@ -202,7 +204,7 @@ int validate(const cg_conv_desc* d, int* ho, int* wo) {
 }
 
 Layout make_layout(const cg_conv_desc& d, size_t wpk_base_bytes, size_t wpk_cond_bytes, size_t wpd_base_bytes,
-                   size_t wpd_cond_bytes) {
+                   size_t wpd_cond_bytes, size_t wpt_base_bytes) {
   Layout l{};
   const size_t eb = (size_t)elem_bytes(d.in_dtype);
   const size_t taps = (size_t)d.kh * d.kw;
@@ -222,6 +224,8 @@ Layout make_layout(const cg_conv_desc& d, size_t wpk_base_bytes, size_t wpk_cond
   off += align256(wpd_base_bytes);
   l.wpd_cond_off = off;
   off += align256(wpd_cond_bytes);
+  l.wpt_base_off = off;
+  off += align256(wpt_base_bytes);
   l.total = off;
   return l;
 }
@@ -231,8 +235,8 @@ struct Plans {
   cg::TilePlan v4;
   cg::DirectPlan vd;
   int variant;
-  bool direct_ok, point_ok;
-  size_t wpk_base_bytes, wpk_cond_bytes, wpd_base_bytes, wpd_cond_bytes;
+  bool direct_ok, point_ok, tile_too;
+  size_t wpk_base_bytes, wpk_cond_bytes, wpd_base_bytes, wpd_cond_bytes, wpt_base_bytes;
 };
 
 int resolve_variant(const cg_conv_desc& d, Plans* pl) {
@@ -246,13 +250,14 @@ int resolve_variant(const cg_conv_desc& d, Plans* pl) {
   if (v == CG_VARIANT_AUTO) v = pl->v3.ok ? CG_VARIANT_MFMA_ROWS : pl->v4.ok ? CG_VARIANT_TILE : CG_VARIANT_NAIVE;
   pl->variant = v;
   // 1x1 layers of stride 1 whose channel walk is whole stages run on the row-tiled kernel (unless a family was asked for by
-  // name): 1024 channels at 14x14 x64, bf16 49 us against 89 on the large-tile kernel, int8 36 against 101
+  // name): 1024 channels at 14x14 x64, bf16 50 us against 99 on the large-tile kernel, int8 38 against 105
   pl->point_ok = false;
   if (d.variant == CG_VARIANT_AUTO && v != CG_VARIANT_MFMA_ROWS) {
     const cg::RowsPlan q = cg::point_plan(d, cg::cu_count());
     pl->point_ok = q.ok != 0;
     if (q.ok) pl->v3 = q;
   }
+  pl->tile_too = pl->point_ok && pl->v4.ok && d.in_dtype == CG_BF16 && d.c_base == d.c_in && d.c_in >= 2048;    // (see pick_kernel)
   pl->vd = cg::direct_plan(d, 1, cg::cu_count());          // (what is packed does not depend on the batch)
   pl->direct_ok = d.variant == CG_VARIANT_AUTO && pl->vd.ok;      // (a family that was asked for by name is what runs)
   pl->wpd_base_bytes = pl->direct_ok ? pl->vd.wpk_bytes[0] : 0;
@@ -260,6 +265,7 @@ int resolve_variant(const cg_conv_desc& d, Plans* pl) {
   const bool rows = v == CG_VARIANT_MFMA_ROWS || pl->point_ok;
   pl->wpk_base_bytes = rows ? pl->v3.wpk_base_bytes : v == CG_VARIANT_TILE ? pl->v4.wpk_base_bytes : 0;
   pl->wpk_cond_bytes = rows ? pl->v3.wpk_cond_bytes : v == CG_VARIANT_TILE ? pl->v4.wpk_cond_bytes : 0;
+  pl->wpt_base_bytes = pl->tile_too ? pl->v4.wpk_base_bytes : 0;
   return CG_OK;
 }
 
@@ -284,6 +290,14 @@ void plan_direct(const cg_conv* h, int n, CallPlan* c) {
 // The kernel a batch runs on.  (Layers that neither tiled family covers: the small-tile kernel.)
 void pick_kernel(const cg_conv* h, CallPlan* c) {
   c->kernel = h->variant == CG_VARIANT_MFMA_ROWS || h->point_ok ? kRows : h->variant == CG_VARIANT_TILE ? kTile : kNaive;
+  // Dense bf16 1x1 layers with a deep K, which reads the operands of a product in larger pieces on the large-tile kernel: as
+  // long as its tiles are whole rounds over the compute units, large-tile / row-tiled kernel, us: 4096 channels to 4096,
+  // 8192 pixels 336 / 394, 2048 86 / 101; 2048 to 2048, 4096 pixels 51 / 58.  Rounds that are not: 4096 to 4096, 700
+  // pixels 65 / 44; 2048 to 512, 12544 57 / 50.  At 1024 channels the two are equal.
+  if (h->tile_too && c->tile.ok) {
+    const int cu = cg::cu_count(), rounds = (c->tile.wgs + cu - 1) / cu;
+    if ((long long)c->tile.wgs * 100 >= 97ll * rounds * cu) c->kernel = kTile;
+  }
   if (!h->direct_ok || !c->direct.ok) return;
   // One round of tiles over the compute units (two where the large-tile kernel is the other choice) is where the small-tile
   // kernel's time starts to grow; measured over one to 64 images of the ResNet-18 layers, e.g. 512 channels at 7x7,
@@ -316,11 +330,14 @@ CallPlan plan_call(const cg_conv* h, int n) {
     if (q.ok && q.grp_mode == c.rows.grp_mode && q.gsp == c.rows.gsp &&
         q.stages[0] == c.rows.stages[0] && q.stages[1] == c.rows.stages[1])
       c.rows = q;
-  } else if (h->variant == CG_VARIANT_TILE) {
+  }
+  if (h->tile_too || (h->variant == CG_VARIANT_TILE && !h->point_ok)) {
     const cg::TilePlan q = cg::tile_plan(dn, cg::cu_count());
     if (q.ok && q.taps == c.tile.taps && q.cps == c.tile.cps && q.wn == c.tile.wn && q.grp_mode == c.tile.grp_mode &&
         q.gsp == c.tile.gsp && q.stages[0] == c.tile.stages[0] && q.stages[1] == c.tile.stages[1])
       c.tile = q;
+    else if (h->tile_too)
+      c.tile.ok = 0;
   }
   plan_direct(h, n, &c);
   pick_kernel(h, &c);
@@ -459,7 +476,7 @@ size_t cg_conv_packed_bytes(const cg_conv_desc* desc) {
   if (validate(desc, &ho, &wo) != CG_OK) return 0;
   Plans pl;
   if (resolve_variant(*desc, &pl) != CG_OK) return 0;
-  return make_layout(*desc, pl.wpk_base_bytes, pl.wpk_cond_bytes, pl.wpd_base_bytes, pl.wpd_cond_bytes).total;
+  return make_layout(*desc, pl.wpk_base_bytes, pl.wpk_cond_bytes, pl.wpd_base_bytes, pl.wpd_cond_bytes, pl.wpt_base_bytes).total;
 }
 
 int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
@@ -473,7 +490,7 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   rc = resolve_variant(d, &pl);
   if (rc != CG_OK) return rc;
   const int variant = pl.variant;
-  const Layout lay = make_layout(d, pl.wpk_base_bytes, pl.wpk_cond_bytes, pl.wpd_base_bytes, pl.wpd_cond_bytes);
+  const Layout lay = make_layout(d, pl.wpk_base_bytes, pl.wpk_cond_bytes, pl.wpd_base_bytes, pl.wpd_cond_bytes, pl.wpt_base_bytes);
   if (!d.packed) return fail(CG_EINVAL, "packed is NULL");
   if (((uintptr_t)d.packed & 255) != 0) return fail(CG_EINVAL, "packed must be 256-byte aligned");
   if (d.packed_bytes < lay.total)
@@ -489,6 +506,7 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   h->variant = variant;
   h->direct_ok = pl.direct_ok;
   h->point_ok = pl.point_ok;
+  h->tile_too = pl.tile_too;
   h->lay = lay;
   h->first.n = d.n_max;
   h->first.rows = pl.v3;
@@ -561,6 +579,8 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
     e = cg::launch_tile_pack(pl.v4, h->base, pk + lay.wpk_base_off, pk + lay.wpk_cond_off, s);
   if (e == hipSuccess && (variant == CG_VARIANT_MFMA_ROWS || pl.point_ok))
     e = cg::launch_rows_pack(pl.v3, h->base, pk + lay.wpk_base_off, pk + lay.wpk_cond_off, s);
+  if (e == hipSuccess && pl.tile_too)
+    e = cg::launch_tile_pack(pl.v4, h->base, pk + lay.wpt_base_off, nullptr, s);
   if (e == hipSuccess && pl.direct_ok)
     e = cg::launch_direct_pack(pl.vd, h->base, pk + lay.wpd_base_off, pk + lay.wpd_cond_off, s);
   if (e != hipSuccess) {
@@ -739,7 +759,7 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
   auto launch = [&](const cg::Params& q) -> hipError_t {
     switch (cp.kernel) {
       case kRows: return cg::launch_rows(cp.rows, q, pk + l.wpk_base_off, pk + l.wpk_cond_off, s);
-      case kTile: return cg::launch_tile(cp.tile, q, pk + l.wpk_base_off, pk + l.wpk_cond_off, s);
+      case kTile: return cg::launch_tile(cp.tile, q, pk + (h->tile_too ? l.wpt_base_off : l.wpk_base_off), pk + l.wpk_cond_off, s);
       case kDirect: {
         hipError_t err = hipSuccess;
         for (int i = 0; i < n && err == hipSuccess; i += cp.piece) {

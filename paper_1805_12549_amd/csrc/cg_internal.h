@@ -77,6 +77,7 @@ struct TilePlan {
   int xcd_cb;              // 1: blocks of one channel block share an XCD; 0: blocks of one tile do
   int grp_mode, gsp;       // channel grouping, as in RowsPlan
   int stages[2];           // stages of the base / conditional phase
+  int wgs;                 // workgroups of a launch
   int nb;                  // stage buffers in LDS (the loads run nb - 1 stages ahead)
   size_t lds_bytes;        // LDS of the kernel instantiation
   size_t wpk_stage_bytes;  // bytes of one (channel block, stage) slab of prepacked weights

@@ -35,7 +35,7 @@
 // corrected where a gate fired.
 //
 // TAPS = 1 (1x1 layers of stride 1): a row is a pixel, a patch the tile's pixels (no halo), a stage up to eight chunks of one
-// tap.  1024 channels at 14x14, 64 images: bf16 49 us, int8 36; 89 and 101 on the large-tile kernel.
+// tap.  1024 channels at 14x14, 64 images: bf16 50 us, int8 38; 99 and 105 on the large-tile kernel.
 //
 // What bounds the kernel: at 64 and 128 channels the instructions of gate and output (a third of a wavefront's time each
 // side of the products), at 256 and 512 the LDS reads and, for few images, the start (arguments, tables and the first

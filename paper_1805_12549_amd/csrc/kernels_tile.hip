@@ -220,6 +220,7 @@ TilePlan plan_wn(const cg_conv_desc& d, int n_cu, int wn) {
     }
     g.fp = fp;
     g.tr = t;
+    g.wgs = (int)wgs;
     g.pr = patch_rows(t);
     g.n16 = g.pr * P * g.cps;
     g.hp = hp;

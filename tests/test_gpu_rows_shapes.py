@@ -100,3 +100,15 @@ def test_residual_may_be_the_output(n):
     torch.cuda.synchronize()
     layer.close()
     assert torch.equal(y, over) and torch.equal(bits, bits2) and torch.equal(counts, counts2)
+
+
+@pytest.mark.parametrize("n", [2048, 1900, 5], ids=["large_tile", "row_tiled", "small_tile"])
+def test_dense_deep_point_wise_layers(n):
+    """A dense bf16 layer of 2048 channels runs on three kernels, by the batch: whole rounds of large tiles, others, few pixels."""
+    shape = S(2048, 1, 1, 2048, 1024, k=1, pad=0, groups=1)
+    inp = W.make_inputs(shape, 9800, kind="iid", round_bf16=True)
+    rng = np.random.default_rng(98)
+    aff = dict(scale0=rng.uniform(0.5, 1.5, 1024), shift0=rng.normal(0, 0.1, 1024), scale1=rng.uniform(0.5, 1.5, 1024),
+               shift1=rng.normal(0, 0.1, 1024))
+    print("\n  " + str(P.run_float(inp, None, out_dtype=B.CG_BF16, affine=aff, epilogue=B.CG_EPI_RELU | B.CG_EPI_AFFINE, n_run=n,
+                                    name=shape.name)), flush=True)
