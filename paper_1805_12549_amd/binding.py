@@ -46,6 +46,7 @@ if len(_hip_runtimes_mapped()) > 1:
 # the current stream's address without building a Stream object per call
 _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
 _empty, _int32 = torch.empty, torch.int32
+_strided = torch.empty_strided     # (contiguous tensors of several dimensions: 1.3 us against 1.7 for empty)
 # torch's caching allocator without a tensor around the block: memory that belongs to one stream (bytes, stream's address)
 _raw_alloc, _raw_free = torch._C._cuda_cudaCachingAllocator_raw_alloc, torch._C._cuda_cudaCachingAllocator_raw_delete
 
@@ -304,9 +305,10 @@ class GatedConv:
         """x: torch device tensor [n,H,W,C_in] (contiguous NHWC).  Returns (y, bitmap, counts)."""
         n, dev = x.shape[0], x.device
         if y is None:
-            y = _empty((n, self.ho, self.wo, self.c_out), dtype=self._y_dtype, device=dev)
+            ho, wo, c = self.ho, self.wo, self.c_out
+            y = _strided((n, ho, wo, c), (ho * wo * c, wo * c, c, 1), dtype=self._y_dtype, device=dev)
         if bitmap is True:
-            bitmap = _empty((n * self.ho * self.wo, self.words), dtype=_int32, device=dev)
+            bitmap = _strided((n * self.ho * self.wo, self.words), (self.words, 1), dtype=_int32, device=dev)
         elif bitmap is False:
             bitmap = None
         if counts is True:
