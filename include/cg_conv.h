@@ -45,14 +45,16 @@ typedef struct cg_conv cg_conv; /* opaque */
 enum { CG_OK = 0, CG_EINVAL = 1, CG_EUNSUPPORTED = 2, CG_ENOMEM = 3, CG_EHIP = 4 };
 enum { CG_F32 = 0, CG_BF16 = 1, CG_I8 = 2, CG_I32 = 3 };
 enum { CG_EPI_RELU = 1u, CG_EPI_AFFINE = 2u, CG_EPI_RESIDUAL = 4u };
-/* Kernel family.  AUTO picks the row-tiled pixel-compacting matrix-core kernel (3x3 layers whose
+/* Kernel family.  AUTO picks the row-tiled matrix-core kernel (3x3 layers whose
  * channel groups are whole 32-byte runs) when the shape allows, else the large-tile matrix-core
  * kernel (3x3 and 1x1 layers, fully connected layers as 1x1 layers on a 1x1 image, channel groups of
  * whole 16-byte runs), else the plain one-thread-per-activation kernel.  All of them compute the
- * same layer.  A handle made with AUTO runs a batch of few output pixels, and every layer outside the two
+ * same layer.  A handle made with AUTO runs 1x1 layers of stride 1 on the row-tiled kernel as well (dense ones with
+ * many channels on either, by the batch), and a batch of few output pixels, and every layer outside the two
  * tiled families whose pixels are whole 16-byte runs of channels, on a small-tile matrix-core kernel (any
  * float or int8 type); cg_conv_info still names the family that covers the shape.  A family asked for by
- * name is what runs. */
+ * name is what runs.  The kernels add a float sum in different orders: a decision whose sum lies within rounding of
+ * its threshold, and the last bits of an output, may depend on the batch that an image is in. */
 enum {
   CG_VARIANT_AUTO = 0,
   CG_VARIANT_NAIVE = 1,
@@ -163,7 +165,8 @@ size_t cg_conv_workspace_bytes(const cg_conv* h, int32_t n);
  *   counts    nullable, 8-byte aligned.  2 + n*c_out words, fully overwritten: words 0,1 = number of fired gates
  *             (low, high half of a 64-bit count); word 2 + img*c_out + co = fired gates of that
  *             image and output channel (the sum the channel-wise gate of Sec. 3.2 thresholds).
- *   workspace >= cg_conv_workspace_bytes(h, n) bytes, 256-byte aligned; may be NULL if that is 0.
+ *   workspace >= cg_conv_workspace_bytes(h, n) bytes, 256-byte aligned; may be NULL if that is 0.  A captured
+ *             call keeps its address: it must stay the graph's own as long as the graph is replayed.
  * Calls on one handle may overlap only if they use distinct y / bitmap / counts / workspace.
  * Errors: CG_EINVAL (NULL where not allowed, n out of range, workspace too small),
  * CG_EHIP (a launch failed; or a kernel of an earlier call, on any handle, came to the bound of an internal

@@ -1,8 +1,7 @@
 // The dense pieces of a ResNet around the gated layers (the paper evaluates ResNet-18, Sec. 5):
 // the input convolution on few channels (7x7 stride 2 on RGB), 3x3 stride-2 max pooling and global
 // average pooling followed by the fully connected layer.  None of them is gated.  bf16 activations
-// and weights, fp32 accumulation.  (The 1x1 stride-2 shortcut convolutions run through
-// cg_conv_create / cg_conv_forward as dense layers, c_base == c_in.)
+// and weights, fp32 accumulation.  Also the 1x1 stride-2 shortcut convolutions (cg_pointwise_conv), which are dense too.
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -146,7 +145,7 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
 //
 // What bounds it: the matrix cores (44 instructions of 32 clocks per output row and 28 pooled columns; half of the time with
 // two wavefronts to a SIMD) and as often the LDS reads of the pixel operands.  Images of 224x224 with pooling: 256 in
-// 98 us, 64 in 36, 16 in 18; 240, 66 and 22 in the form before (16x16 tiles gathered as single elements, 1.31 times
+// 98 us, 64 in 33, 16 in 16; 240, 66 and 22 in the form before (16x16 tiles gathered as single elements, 1.31 times
 // the products, outputs exchanged through LDS for the pooling).
 constexpr int kStemPitch = 1664;                 // bytes of a ring row: 63 pooled columns' input and the window's rest
 constexpr int kStemRing = 16;

@@ -1,6 +1,7 @@
 // Plain kernel: one thread per output activation, direct convolution.
-// Covers every shape and dtype the API accepts (fp32 layers, channel counts
-// the matrix-core kernels cannot tile, any kernel size).  Follows Eq. 1 of
+// Covers every shape and dtype the API accepts; what comes here are layers
+// whose pixels are not whole 16-byte runs, unaligned pointers, and counting
+// without a bitmap where none fits the scratch.  Follows Eq. 1 of
 // the channel-gating paper step by step: base sum, gate, conditional sum only
 // where the gate fired, output function.  With channel grouping (Sec. 3.3) the
 // base channels of output group i are input group i and the conditional

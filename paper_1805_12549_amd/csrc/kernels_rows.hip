@@ -39,11 +39,16 @@
 //
 // What bounds the kernel: at 64 and 128 channels the instructions of gate and output (a third of a wavefront's time each
 // side of the products), at 256 and 512 the LDS reads and, for few images, the start (arguments, tables and the first
-// stage: 2 us of 8 to 13).  Measured in a graph, before (barrier-coupled workgroups with the pixels listed anew for the
-// conditional path) and now, us:
-//   bf16  64 channels at 56x56, 64 images 31 -> 27, 256: 93 -> 79;  256 at 14x14, 8 images 14.7 -> 13.3, 256: 58.8 -> 59;
-//         512 at 7x7, 8: 23.8 -> 19.1, 256: 68 -> 62;  128>256 at 28x28 stride 2, 64: 19.3 -> 16.8, 256: 69 -> 53
-//   int8  128 at 28x28, 32 images 18.0 -> 11.6, 256: 70 -> 53;  512 at 7x7, 8: 20.9 -> 13.9, 256: 52 -> 39
+// stage: 2 us of 8 to 13).  The matrix cores are busy for 15 to 26 % of a layer at 64 images.  Measured in a graph with
+// rotated buffers, clustered maps at a firing rate of 0.3, before (barrier-coupled workgroups with the pixels listed anew for
+// the conditional path) and now, us:
+//   bf16, scale/shift, residual and ReLU
+//         64 channels at 56x56, 64 images 36.4 -> 28.9, 256: 116 -> 95;  128 at 28x28, 64: 25.1 -> 25.2, 128: 45.4 -> 41.3,
+//         256: 74.4 -> 70.6;  256 at 14x14, 64: 24.2 -> 20.5, 128: 33.5 -> 34.8, 256: 56.4 -> 60.5;  512 at 7x7, 64: 29.6 ->
+//         23.6, 256: 74.0 -> 61.3;  128>256 at 28x28 stride 2, 64: 22.8 -> 19.0, 256: 83 -> 56
+//   int8  128 at 28x28, 32 images 17.6 -> 11.2, 256: 71 -> 48;  512 at 7x7, 256: 53 -> 35
+// Where it is not faster, skipping whole fragments is what it loses against single pixels: 256 at 14x14, 256 images, by firing
+// rate 0.05: 47.6 -> 49.9, 0.1: 49.6 -> 50.4, 0.3: 55.7 -> 56.6, 0.6: 62.4 -> 60.9.
 //
 // A patch is stored [pixel slot][CPS chunk positions]; chunk q of slot s sits at position q ^ f(s),
 // f(s) = (s >> 2) & 3 (CPS = 4) or (s >> 3) & 1 (CPS = 2), which spreads the operand reads over the LDS
