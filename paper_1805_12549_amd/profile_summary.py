@@ -76,10 +76,10 @@ def traffic(fetch_csv: str, write_csv: str, copy_bytes: int = 256 << 20, kernel:
     n = max(1, min(len(f_layer), len(w_layer)))
     out.append("bytes_per_launch: %.0f" % (tot / n))
     out += ["commands (each in its own run, after cd /tmp && export TMPDIR=/tmp, from the repository root):",
-            "  rocprofv3 --pmc FETCH_SIZE --output-format csv -d gpurun_out/prof_fetch -o r -- python3 -m paper_1805_12549_amd.traffic_probe",
-            "  rocprofv3 --pmc WRITE_SIZE --output-format csv -d gpurun_out/prof_write -o r -- python3 -m paper_1805_12549_amd.traffic_probe",
-            "  python -m paper_1805_12549_amd.profile_summary --traffic gpurun_out/prof_fetch/r_counter_collection.csv "
-            "gpurun_out/prof_write/r_counter_collection.csv",
+            "  rocprofv3 --pmc FETCH_SIZE --output-format csv -d out/prof_fetch -o r -- python3 -m paper_1805_12549_amd.traffic_probe",
+            "  rocprofv3 --pmc WRITE_SIZE --output-format csv -d out/prof_write -o r -- python3 -m paper_1805_12549_amd.traffic_probe",
+            "  python -m paper_1805_12549_amd.profile_summary --traffic out/prof_fetch/r_counter_collection.csv "
+            "out/prof_write/r_counter_collection.csv",
             "launches 0..6 = the 7 ImageNet-shaped ResNet-18 gated 3x3 layers (64@56, 128@28, 256@14, 512@7, 64>128 s2, "
             "128>256 s2, 256>512 s2), batch 64, bf16, one cold-cache forward each"]
     return "\n".join(out) + "\n"
@@ -103,9 +103,9 @@ def mfma_busy(counter_csv: str, trace_us, kernel: str = "gated_conv") -> str:
         out.append("all launches: executed %.1f GFLOP in %.1f us -> %.3f of the bf16 MFMA peak" % (
             tot / 1e9, sum(trace_us[:len(vals)]), tot / (sum(trace_us[:len(vals)]) * 1e-6) / 2.5e15))
     out += ["commands (after cd /tmp && export TMPDIR=/tmp, from the repository root):",
-            "  rocprofv3 --pmc SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CYCLES GRBM_GUI_ACTIVE --output-format csv -d gpurun_out/prof_mfma -o r "
+            "  rocprofv3 --pmc SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CYCLES GRBM_GUI_ACTIVE --output-format csv -d out/prof_mfma -o r "
             "-- python3 -m paper_1805_12549_amd.traffic_probe",
-            "  python -m paper_1805_12549_amd.profile_summary --mfma gpurun_out/prof_mfma/r_counter_collection.csv <us_gated of the 7 layers>",
+            "  python -m paper_1805_12549_amd.profile_summary --mfma out/prof_mfma/r_counter_collection.csv <us_gated of the 7 layers>",
             "launches 0..6 = the 7 ImageNet-shaped ResNet-18 gated 3x3 layers, batch 64, bf16, one cold-cache forward each"]
     return "\n".join(out) + "\n"
 
