@@ -50,9 +50,9 @@ enum { CG_EPI_RELU = 1u, CG_EPI_AFFINE = 2u, CG_EPI_RESIDUAL = 4u };
  * kernel (3x3 and 1x1 layers, fully connected layers as 1x1 layers on a 1x1 image, channel groups of
  * whole 16-byte runs), else the plain one-thread-per-activation kernel.  All of them compute the
  * same layer.  A handle made with AUTO runs 1x1 layers of stride 1 on the row-tiled kernel as well (dense ones with
- * many channels on either, by the batch), and a batch of few output pixels, and every layer outside the two
- * tiled families whose pixels are whole 16-byte runs of channels, on a small-tile matrix-core kernel (any
- * float or int8 type); cg_conv_info still names the family that covers the shape.  A family asked for by
+ * many channels on either, by the batch), and a batch that is estimated to be faster there (few output pixels, strided
+ * 1x1 layers), and every layer outside the two tiled families whose pixels are whole 16-byte runs of channels, on a
+ * small-tile matrix-core kernel (any float or int8 type); cg_conv_info still names the family that covers the shape.  A family asked for by
  * name is what runs.  The kernels add a float sum in different orders: a decision whose sum lies within rounding of
  * its threshold, and the last bits of an output, may depend on the batch that an image is in. */
 enum {
@@ -148,8 +148,7 @@ size_t cg_conv_packed_bytes(const cg_conv_desc* desc);
  * must be ordered after that stream's work.  On failure *out is NULL. */
 int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream);
 
-/* Device scratch a forward call of batch n needs (may be 0; not monotonic in n: a small batch may share its
- * tiles' sums through it). */
+/* Device scratch a forward call of batch n needs (may be 0). */
 size_t cg_conv_workspace_bytes(const cg_conv* h, int32_t n);
 
 /*
@@ -181,7 +180,7 @@ int cg_conv_forward(cg_conv* h, int32_t n, const void* x, const void* residual, 
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and results
  * as cg_conv_forward without `workspace`: the scratch the call needs (the batch's decision bitmap when
  * counts are asked for without a bitmap; with the channel-wise gate also the first pass's bitmap
- * and channel mask; on small batches partial sums) lives in a fixed 16 MiB array inside the library, one
+ * and channel mask) lives in a fixed 16 MiB array inside the library, one
  * copy per GPU, held until the process ends.  The call allocates nothing (no hipMalloc / hipFree, no
  * allocating library routine) and relies on no previous contents of the array.  A call of a tiled family that
  * needs more scratch than the array holds (cg_conv_workspace_bytes(h, n) > 16 MiB) fails with

@@ -299,14 +299,25 @@ void pick_kernel(const cg_conv* h, CallPlan* c) {
     if ((long long)c->tile.wgs * 100 >= 97ll * rounds * cu) c->kernel = kTile;
   }
   if (!h->direct_ok || !c->direct.ok) return;
-  // One round of tiles over the compute units (two where the large-tile kernel is the other choice) is where the small-tile
-  // kernel's time starts to grow; measured over one to 64 images of the ResNet-18 layers, e.g. 512 channels at 7x7,
-  // small-tile / row-tiled kernel: 15.3 / 19.1 us at eight images of bf16, 12.3 / 13.9 at eight of int8, 20.9 / 14.4 at
-  // 32 (two rounds).  1x1 layers on the row-tiled kernel are too short below 512 channels for a split of K to pay: 64
-  // channels at 56x56, one image 7.7 / 5.5; 1024 at 14x14, one image 10.2 / 11.5, eight 13.2 / 13.1.
-  if (h->point_ok && h->d.c_in < 512) return;
-  const int rounds = h->d.kh == 3 || h->point_ok ? 1 : 2;
-  if (c->kernel == kNaive || c->direct.tiles <= rounds * cg::cu_count()) c->kernel = kDirect;
+  if (c->kernel == kNaive) {
+    c->kernel = kDirect;
+    return;
+  }
+  // The estimated times of the two, in clocks.  Over 427 layers of one to 100000 output pixels (3x3 and 1x1, strides one and
+  // two, grouped and not) what is picked takes 1 % longer than the better of the two in the mean.  Small-tile kernel / other, us:
+  // 512 channels at 7x7, one image 8.9 / 18.9, eight 13.6 / 19.8; 64 at 56x56, one 5.7 / 8.5, four 9.8 / 9.0, eight 15.2 /
+  // 10.0; int8 256 at 14x14, eight 8.3 / 10.9.  Strided 1x1 layers, where the other is the large-tile kernel: 256 to 448 at
+  // 20x20, 193 images 34 / 188.  Fully connected, 448 to 3968, 49 images 5.4 / 17.8, 2816 to 3776, 378 images 40 / 30.
+  double other, mine = c->direct.cost;
+  if (c->kernel == kRows) {
+    other = h->point_ok ? c->rows.cost : 4900.0 + 1.52 * c->rows.cost;
+  } else {
+    const cg::TilePlan& t = c->tile;
+    const int rounds = (t.wgs + cg::cu_count() - 1) / cg::cu_count();
+    other = 7200.0 + rounds * (7900.0 + (t.stages[0] + 0.29 * t.stages[1]) * (1200.0 + 2.3 * t.cps * t.fp * t.bn));
+  }
+  if (mine > 33000.0) mine += 0.25 * (mine - 33000.0);      // (its estimate is low where tiles are many)
+  if (mine < other) c->kernel = kDirect;
 }
 
 // Two fragments per wavefront write an output twice and read the residual after the first time: where the two may be the
@@ -603,12 +614,11 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
 }
 
 namespace {
-// Workspace layout: [decisions: the batch's bitmap, or (kCounting) its counts][channel mask][partial sums].  Fired gates
+// Workspace layout: [decisions: the batch's bitmap, or (kCounting) its counts][channel mask].  Fired gates
 // are counted from a decision bitmap; it goes to the workspace when the caller asks for counts without a bitmap, and so
-// does the first pass of the channel-wise gate.  The mask exists only with the channel-wise gate, the
-// partial sums only where several workgroups share a tile's K.
+// does the first pass of the channel-wise gate.  The mask exists only with the channel-wise gate.
 struct WsLayout {
-  size_t dec_off, dec_bytes, mask_off, mask_bytes, partial_off, total;
+  size_t dec_off, dec_bytes, mask_off, mask_bytes, total;
 };
 // What a call gets of it: what any call may need (the caller's workspace); what this call needs; or what the plain kernel
 // needs when it counts the fired gates itself (an image whose bitmap does not fit the scratch array).
@@ -624,9 +634,7 @@ WsLayout ws_layout(const cg_conv* h, int32_t n, const CallPlan& c, Scratch mode,
   if (chan_gate) w.mask_bytes = align256((size_t)n * words * 4);
   w.dec_off = 0;
   w.mask_off = w.dec_bytes;
-  w.partial_off = w.mask_off + w.mask_bytes;
-  const size_t partial = c.direct.partial_bytes > c.direct_rest.partial_bytes ? c.direct.partial_bytes : c.direct_rest.partial_bytes;
-  w.total = w.partial_off + (c.kernel == kDirect && mode != kCounting ? align256(partial) : 0);
+  w.total = w.mask_off + w.mask_bytes;
   return w;
 }
 }  // namespace
@@ -773,8 +781,7 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
           if (q.bitmap) r.bitmap = q.bitmap + i * px * q.words;
           if (q.chan_mask) r.chan_mask = q.chan_mask + (long long)i * q.words;
           r.clear_total = q.clear_total && i == 0;
-          err = cg::launch_direct(r.n == cp.piece ? cp.direct : cp.direct_rest, r, pk + l.wpd_base_off, pk + l.wpd_cond_off,
-                                  ws + wl.partial_off, s);
+          err = cg::launch_direct(r.n == cp.piece ? cp.direct : cp.direct_rest, r, pk + l.wpd_base_off, pk + l.wpd_cond_off, s);
         }
         return err;
       }

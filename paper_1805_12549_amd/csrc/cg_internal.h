@@ -107,18 +107,16 @@ hipError_t launch_tile_i8_k3(const TilePlan& g, const TileGeo& q, const Params& 
 hipError_t launch_tile_i8_k1(const TilePlan& g, const TileGeo& q, const Params& p, const void* w0, const void* w1,
                              hipStream_t s);
 
-// Geometry of the small-tile matrix-core kernel (kernels_direct.hip): 16*pf output pixels x 32*cg
+// Geometry of the small-tile matrix-core kernel (kernels_direct.hip): 16*pf output pixels x 16*nh
 // channels per tile, operands straight from global memory.
 struct DirectPlan {
   int ok;
   int elem_bytes, ch;      // bytes per element; channels per 16-byte chunk
   int taps;                // 9 or 1
-  int pf, cg;              // 16-pixel fragments and 32-channel groups per tile
+  int pf, nh;              // 16-pixel fragments and 16-channel halves of the packed groups per tile
   int split;               // wavefronts of a workgroup that share a tile's K; 1: a wavefront walks all of it
   int nwb;                 // of which walk the base path
-  int slices;              // workgroups that share a tile's K (their sums meet in the workspace)
   int n_cblk;              // tiles across the channels
-  int tiles;               // tiles in all
   int px_wgs;              // workgroups across the pixels
   unsigned x_bytes;        // size of x
   // Channel chunks per tap and phase.  The base phase starts at the first chunk of the 64-channel block's
@@ -129,13 +127,12 @@ struct DirectPlan {
   int ksteps[2];           // K steps (four chunks) per phase
   int n_grp;               // 32-channel groups of the packed weights
   size_t wpk_bytes[2];
-  size_t partial_bytes;    // workspace for the slices' sums
+  double cost;             // estimated time, in clocks
 };
 
 DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu);
 hipError_t launch_direct_pack(const DirectPlan& plan, const Params& p, void* wpk_base, void* wpk_cond, hipStream_t s);
-hipError_t launch_direct(const DirectPlan& plan, const Params& p, const void* wpk_base, const void* wpk_cond, void* partial,
-                         hipStream_t s);
+hipError_t launch_direct(const DirectPlan& plan, const Params& p, const void* wpk_base, const void* wpk_cond, hipStream_t s);
 
 // Geometry of the row-tiled matrix-core kernel (kernels_rows.hip): persistent workgroups of 64 output channels
 // that walk runs of output rows in tiles of at most 256 pixels; K in stages of `cps` 16-byte channel chunks
@@ -165,6 +162,7 @@ struct RowsPlan {
   int fwl, nfc;            // fragment of a wavefront: 2^fwl columns (-1: 32 pixels in a row), fragments per row group
   int wres, shuf, shuf_bytes, tabs, lds_bytes;   // LDS offsets of resident weights (-1: none), shuffled rows, tables
   size_t wpk_base_bytes, wpk_cond_bytes;
+  double cost;             // estimated time, in clocks
 };
 
 // cps: 0 = pick, 4 or 2 = that (for a handle whose weights are packed); max_pf: the most fragments per wavefront

@@ -58,6 +58,7 @@
 // The vector-memory path serves a cache line every two clocks, whatever part of it is asked for (measured: 17, 35
 // and 65 bytes a clock in pieces of 32, 64 and 128+), which is why outputs are transposed between lanes before
 // they are stored and why stages of four chunks are preferred where the channel counts allow.
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -1152,6 +1153,7 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
   g.lds_bytes = off + kTabBytes;
   g.wpk_base_bytes = (size_t)g.n_cb * g.stages[0] * wb;
   g.wpk_cond_bytes = (size_t)g.n_cb * g.stages[1] * wb;
+  g.cost = best;
   *cost = best;
   return g;
 }
@@ -1213,6 +1215,16 @@ RowsPlan point_plan(const cg_conv_desc& d, int n_cu) {
   g.lds_bytes = off + kTabBytes;
   g.wpk_base_bytes = (size_t)g.n_cb * g.stages[0] * wb;
   g.wpk_cond_bytes = (size_t)g.n_cb * g.stages[1] * wb;
+  // The estimated time, fitted to 67 layers of 2 to 50000 pixels: a stage takes its products, its lines of memory or, where it
+  // is short, 950 clocks of latency.
+  g.cost = 4400.0 + (g.resident ? S * wb / 60.0 : 0.0);
+  for (long long left = each; left > 0; left -= g.tr) {
+    const long long here = left < g.tr ? left : g.tr, frags = (here + 31) / 32;
+    const double per_simd = 0.67 * ((frags + 3) / 4) + 0.33 * frags / 4.0;
+    const double mm = g.cps / 2 * 64.0 * per_simd * (frags <= 4 ? 1.55 : 1.10);
+    const double stream = 6.8 * (here * 16 * g.cps + (g.resident ? 0 : wb)) / 128.0;
+    g.cost += S * std::max(950.0, std::max(mm, stream)) + 3450.0 + 4500.0 * per_simd;
+  }
   g.ok = 1;
   return g;
 }

@@ -144,3 +144,30 @@ def test_batches_beyond_the_offsets_run_in_pieces(tau_c):
         total += int(counts2[0]) & 0xffffffff
     assert (int(counts[0]) & 0xffffffff) + (int(counts[1]) << 32) == total and 0 < total < n * 512 * 512 * c
     layer.close()
+
+
+# Edges of the tiles of 16 or 32 pixels by 16, 32 or 64 channels: pixels around multiples of 16, channels that end inside a
+# sixteen (the bitmap's other half word is written as well), K of one step and of many, wavefronts without a K step of their own.
+FORMS = [
+    S(1, 1, 1, 16, 16, k=1, pad=0), S(3, 1, 5, 48, 17, k=1, pad=0), S(1, 4, 4, 32, 48), S(1, 1, 17, 64, 40),
+    S(2, 3, 11, 128, 72, k=1, pad=0, stride=2), S(1, 7, 7, 128, 128), S(33, 2, 2, 96, 33), S(5, 9, 9, 64, 144, stride=2),
+    S(1, 1, 1, 1344, 208, k=1, pad=0, groups=2), S(3, 13, 13, 192, 96, groups=8), S(60, 12, 12, 32, 80), S(16, 40, 40, 16, 32, k=1, pad=0),
+]
+
+
+@pytest.mark.parametrize("shape", FORMS, ids=[s.name for s in FORMS])
+@pytest.mark.parametrize("grouped", [False, True], ids=["plain", "grouped"])
+def test_tile_edges(shape, grouped):
+    if grouped and (shape.c_out % shape.groups or shape.k != 3):
+        pytest.skip("no such grouping")
+    kind = "iid"
+    inp = W.make_inputs(shape, 7300 + shape.c_out + shape.h, kind=kind, rho=0.3, round_bf16=True, grouped=grouped)
+    gate = W.calibrate_gate(inp, 0.3, sample_images=None)
+    kw = dict(shuffle=grouped)
+    for dtype in (B.CG_F32, B.CG_BF16):
+        if shape.c_in % (4 if dtype == B.CG_F32 else 8) == 0:
+            _say(P.run_float(inp, gate, in_dtype=dtype, out_dtype=dtype, name=shape.name + " %d" % dtype, **kw))
+    if shape.c_in % 16 == 0:
+        q = W.quantize_int8(W.make_inputs(shape, 7400 + shape.c_out + shape.h, kind=kind, rho=0.35, grouped=grouped))
+        thr = W.calibrate_gate_int8(q, 0.35, sample_images=None)
+        _say(P.run_int8(q, thr, name=shape.name + " int8", **kw))
