@@ -38,8 +38,10 @@
 // tap.  1024 channels at 14x14, 64 images: bf16 50 us, int8 38; 99 and 105 on the large-tile kernel.
 //
 // What bounds the kernel: at 64 and 128 channels the instructions of gate and output (a third of a wavefront's time each
-// side of the products), at 256 and 512 the LDS reads and, for few images, the start (arguments, tables and the first
-// stage: 2 us of 8 to 13).  The matrix cores are busy for 15 to 26 % of a layer at 64 images.  Measured in a graph with
+// side of the products), at 256 and 512 the LDS reads and, for few images, the start: the first stage of all workgroups
+// (some 40 KB each, 10 MB for the chip) lands 2.7 us after the first instruction.  Arguments asked for at once and a column
+// that is formed once per wavefront have the loads out after 1.1 us instead of 1.9: 64 channels at 56x56, 64 images 22.9 -> 22.3
+// us, 128 to 256 at 28x28 stride 2 16.1 -> 15.6, int8 128 at 28x28, 32 images 10.4 -> 10.1.  The matrix cores are busy for 15 to 26 % of a layer at 64 images.  Measured in a graph with
 // rotated buffers, clustered maps at a firing rate of 0.3, before (barrier-coupled workgroups with the pixels listed anew for
 // the conditional path) and now, us:
 //   bf16, scale/shift, residual and ReLU
@@ -248,7 +250,7 @@ struct RowsArgs {
   const char *w0, *w1;
   const char* tab;
   unsigned magic_hp, x_bytes;
-  int n, h, w, pad, xps, pr, n_pl;           // patch rows, 1 KB patch loads
+  int n, h, w, pad, xps, n_pl;               // 1 KB patch loads
   int base_chn, gap_chn, grp_mode, grp_step; // channel walk
   // multiplying wavefronts
   int fwl, nfc;                              // log2 columns of a fragment and fragments per row group; fwl < 0: 32 in a row
@@ -283,9 +285,13 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lj = lane & 31, lh = lane >> 5;
+  // All arguments in one go: each further wait for some of them is 500 clocks of a start that nothing overlaps.
   asm volatile("" ::"s"(a.flags), "s"(a.magic_ncb), "s"(a.magic_ho), "s"(a.n_cb), "s"(a.n_slots), "s"(a.xcd_cb), "s"(a.per_xcd),
                "s"(a.full), "s"(a.rows_per), "s"(a.rows_more), "s"(a.tr), "s"(a.logp), "s"(a.s0), "s"(a.s), "s"(a.nb), "s"(a.pstr),
-               "s"(a.psz), "s"(a.wres), "s"(a.tabs), "s"(a.ho), "s"(a.hp), "s"(a.stride), "s"(a.tab_stride), "s"(a.clear));
+               "s"(a.psz), "s"(a.wres), "s"(a.tabs), "s"(a.ho), "s"(a.hp), "s"(a.stride), "s"(a.tab_stride), "s"(a.clear), "s"(a.x),
+               "s"(a.w0), "s"(a.w1), "s"(a.tab), "s"(a.magic_hp), "s"(a.x_bytes), "s"(a.n), "s"(a.h), "s"(a.w), "s"(a.pad), "s"(a.xps),
+               "s"(a.n_pl), "s"(a.base_chn), "s"(a.gap_chn), "s"(a.grp_mode), "s"(a.grp_step), "s"(a.fwl), "s"(a.nfc), "s"(a.magic_wo),
+               "s"(a.magic_nfc), "s"(a.y), "s"(a.residual), "s"(a.bitmap), "s"(a.wo), "s"(a.gave_up));
 
   // Block id mod 8 is the XCD.  Normally an XCD takes a contiguous run of rows with all channel blocks, so that a
   // row is fetched into one L2 once; xcd_cb: the workgroups of a channel block sit on one XCD instead, so that each
@@ -332,8 +338,6 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     // They share their SIMDs with the multiplying wavefronts and every instruction between two loads counts: buffer
     // loads with a scalar offset (no address arithmetic, padding by the range check), positions formed once per tile.
     __builtin_amdgcn_s_setprio(3);
-    asm volatile("" ::"s"(a.x), "s"(a.w0), "s"(a.w1), "s"(a.tab), "s"(a.magic_hp), "s"(a.x_bytes), "s"(a.n), "s"(a.h), "s"(a.w),
-                 "s"(a.pad), "s"(a.xps), "s"(a.pr), "s"(a.n_pl), "s"(a.base_chn), "s"(a.gap_chn), "s"(a.grp_mode), "s"(a.grp_step));
     const int lw = wave - kCw;
     const int V = tiles * a.s;
     auto rsrc = [](const void* ptr, unsigned bytes) __attribute__((always_inline)) {
@@ -358,57 +362,46 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     // the first c_base; with grouping, Sec. 3.3, those of the block's own group, or none when the block covers
     // several groups and the packed weights carry zeros instead).
     const int b0 = a.grp_mode ? (cbk * kBn / a.grp_step) * a.base_chn : 0;
-    // A position of the patch (16 bytes of a pixel) is load lw + 4k, lane `lane`; its row of the patch and its offset
-    // inside an image row do not depend on the tile.  kOut: past the end of any x (the plan keeps x below 2 GiB).
-    constexpr int kOut = (int)0x80000000;
-    int vcol[kMaxPatchLoads], voff[kMaxPatchLoads];
-    int np = 0;                              // patch loads of this wavefront
-#pragma unroll
-    for (int k = 0; k < kMaxPatchLoads; ++k) {
-      voff[k] = vcol[k] = kOut;
-      if (lw + kLw * k < a.n_pl) {
-        ++np;
-        const int pos = (lw + kLw * k) * 64 + lane;
-        const int sl = pos / CPS, cp = pos % CPS;
-        const int f = CPS == 8 ? sl & 7 : CPS == 4 ? (sl >> 2) & 3 : (sl >> 3) & 1;
-        if constexpr (TAPS == 1) {
-          vcol[k] = sl * a.xps + (cp ^ f) * 16;
-          continue;
-        }
-        const int wi = (sl & ((1 << a.logp) - 1)) - a.pad;
-        if ((unsigned)wi < (unsigned)a.w && (sl >> a.logp) < a.pr) vcol[k] = wi * a.xps + (cp ^ f) * 16;
-      }
-    }
+    // A position of the patch (16 bytes of a pixel) is load lw + 4k, lane `lane`.  From one load to the next of a wavefront it
+    // is kStep slots on, whole periods of the chunks' permutation, and whole rows where the pitch is not above that: the chunk
+    // and the column are then the same in all loads.  (Positions behind the patch's last row read some row of x or zeros.)  kOut: past the end of any x (the plan keeps x below 2 GiB).
+    constexpr int kOut = (int)0x80000000, kStep = kLw * 64 / CPS;
+    const int sl0 = lw * (64 / CPS) + lane / CPS;
+    const int chunk = ((lane % CPS) ^ (CPS == 8 ? sl0 & 7 : CPS == 4 ? (sl0 >> 2) & 3 : (sl0 >> 3) & 1)) * 16;
+    const int np = (a.n_pl - lw + kLw - 1) / kLw;            // patch loads of this wavefront
     const int rowx = a.w * a.xps;            // bytes per image row
-    // positions of this wavefront's patch loads for tile t
+    auto column = [&](int sl) __attribute__((always_inline)) {
+      const int wi = (sl & ((1 << a.logp) - 1)) - a.pad;
+      return (unsigned)wi < (unsigned)a.w ? wi * a.xps + chunk : kOut;
+    };
+    const bool one_col = TAPS == 9 && (kStep >> a.logp) != 0;
+    const int col0 = TAPS == 9 ? column(sl0) : sl0 * a.xps + chunk;
+    int voff[kMaxPatchLoads];
+    int R0 = 0, here = 0, rho0 = 0;          // of the tile: first row, rows, stacked padded input row of patch row 0
     auto tile_setup = [&](int t) __attribute__((always_inline)) {
-      const int R0 = tile_row(t);
-      if constexpr (TAPS == 1) {
-        const int here = t < a.full ? a.tr : tail_rows;
-#pragma unroll
-        for (int k = 0; k < kMaxPatchLoads; ++k) {
-          if (k >= np) break;
-          voff[k] = ((lw + kLw * k) * 64 + lane) / CPS < here ? R0 * a.xps + vcol[k] : kOut;
-        }
-        return;
+      R0 = tile_row(t);
+      here = t < a.full ? a.tr : tail_rows;
+      if constexpr (TAPS == 9) {
+        const int img0 = div16(R0, a.magic_ho);
+        rho0 = img0 * a.hp + (R0 - img0 * a.ho) * a.stride;
       }
-      const int img0 = div16(R0, a.magic_ho);
-      const int rho0 = img0 * a.hp + (R0 - img0 * a.ho) * a.stride;     // stacked padded input row of patch row 0
-#pragma unroll
-      for (int k = 0; k < kMaxPatchLoads; ++k) {
-        if (k >= np) break;
-        const int rho = rho0 + ((((lw + kLw * k) * 64 + lane) / CPS) >> a.logp);
-        const int img = div16(rho, a.magic_hp);
-        const int hi = rho - img * a.hp - a.pad;
-        voff[k] = img < a.n && (unsigned)hi < (unsigned)a.h && vcol[k] != kOut ? (img * a.h + hi) * rowx + vcol[k] : kOut;
-      }
+    };
+    // position of this wavefront's patch load k for the tile
+    auto position = [&](int k) __attribute__((always_inline)) {
+      const int sl = sl0 + kStep * k;
+      if constexpr (TAPS == 1) return sl < here ? R0 * a.xps + kStep * k * a.xps + col0 : kOut;
+      const int rho = rho0 + (sl >> a.logp), img = div16(rho, a.magic_hp), hi = rho - (int)__umul24(img, a.hp) - a.pad;
+      const int col = one_col ? col0 : column(sl);
+      return img < a.n && (unsigned)hi < (unsigned)a.h && col != kOut ? ((int)__umul24(img, a.h) + hi) * rowx + col : kOut;
     };
     const int nwl = NWL + (lw < (WB / 1024) % kLw ? 1 : 0);       // weight loads of this wavefront per stage
     const int lane16 = lane * 16 + lw * 1024;
     int is = 0, ib = 0, iv = 0, itile = 0;   // the next stage to issue: stage of its tile, buffer, number
+    // (weights first: their addresses need nothing of the tile)
     auto issue = [&]() __attribute__((always_inline)) {
       const unsigned buf = lds0 + ib * a.pstr + lw * 1024;
-      if (is == 0) tile_setup(itile);
+      int c = is < a.s0 ? b0 + is * SB : (is - a.s0) * SB;
+      if (is >= a.s0 && c >= b0) c += a.gap_chn;
       if (a.wres < 0 || iv < a.s) {
         const unsigned wd = a.wres < 0 ? buf + a.psz : lds0 + a.wres + is * WB + lw * 1024;
         const i32x4 r = is < a.s0 ? wr0 : wr1;
@@ -417,12 +410,20 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
         for (int k = 0; k < NWL; ++k) dma(r, lane16, so + k * (kLw * 1024), wd + k * (kLw * 1024));
         if (nwl > NWL) dma(r, lane16, so + NWL * (kLw * 1024), wd + NWL * (kLw * 1024));
       }
-      int c = is < a.s0 ? b0 + is * SB : (is - a.s0) * SB;
-      if (is >= a.s0 && c >= b0) c += a.gap_chn;
+      if (is == 0) {                         // (each load goes out as soon as its position is known)
+        tile_setup(itile);
 #pragma unroll
-      for (int k = 0; k < kMaxPatchLoads; ++k) {
-        if (k >= np) break;
-        dma(xr, voff[k], c, buf + k * (kLw * 1024));
+        for (int k = 0; k < kMaxPatchLoads; ++k) {
+          if (k >= np) break;
+          voff[k] = position(k);
+          dma(xr, voff[k], c, buf + k * (kLw * 1024));
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < kMaxPatchLoads; ++k) {
+          if (k >= np) break;
+          dma(xr, voff[k], c, buf + k * (kLw * 1024));
+        }
       }
       ++iv;
       if (++is == a.s) {
@@ -464,8 +465,6 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   }
 
   // ================================ multiplying wavefronts ==========================================
-  asm volatile("" ::"s"(a.fwl), "s"(a.nfc), "s"(a.magic_wo), "s"(a.magic_nfc), "s"(a.y), "s"(a.residual), "s"(a.bitmap),
-               "s"(a.chan_mask), "s"(a.wo), "s"(a.words), "s"(a.c_out), "s"(a.rq_shift), "s"(a.rq_res_mult), "s"(a.gave_up));
   // (the address waits in LDS: read from the arguments at the end of each wavefront it cost a launch 1.5 us)
   if (tid == 0) *(uint32_t**)(lds + a.tabs + kTabs * 256 + 48) = a.gave_up;
   acc_t* const tlo = (acc_t*)(lds + a.tabs);         // [64] thresholds, lower and upper
@@ -537,22 +536,28 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     if constexpr (PF == 2) asm volatile("" : "+v"(b));        // (addresses formed from it are not kept across the K loops)
     return b;
   };
-  // Output of the lanes' pixels px (counted from pixel m0 of the batch; -1: none), 2 x 16 channels each, in three steps that
-  // whole wavefronts execute.  First the values, from sums and the decisions in dl (bit 16*f + i; UNI: all the same):
+  // The residual of the lanes' pixels px (counted from pixel m0 of the batch; -1: none), 2 x 16 channels each, as it is read:
+  // the lane's 16-byte pieces in the transposed order, four of bf16, two of int8.
+  auto load_residual = [&](long long m0, int px, auto& rs) __attribute__((always_inline)) {
+    constexpr int kPieces = Base::kDtype == CG_I8 ? 2 : 4;
+    const int pxj[2] = {px_of(px, 0), px_of(px, 1)};
+    const int rowy = Base::kDtype == CG_I8 ? a.c_out : a.c_out * 2;
+    const long long first = m0 * rowy + (Base::kDtype == CG_I8 ? cbk * kBn + (lane & 16) * 2 + (lane & 32) / 2 : cbk * (kBn * 2) + lane_bytes());
+#pragma unroll
+    for (int j = 0; j < kPieces; ++j) {
+      rs[j] = i32x4{0, 0, 0, 0};
+      if (pxj[j & 1] >= 0) rs[j] = *(const i32x4*)(a.residual + first + (long long)pxj[j & 1] * rowy + (j >> 1) * 32);
+    }
+  };
+  // Output of those pixels in three steps that whole wavefronts execute.  First the values, from sums, the residual and the
+  // decisions in dl (bit 16*f + i; UNI: all the same):
   auto finish = [&](auto uni, const acc16 (&sum)[2], unsigned dl, long long m0, int px, i32x4 (&v)[4]) __attribute__((always_inline)) {
     constexpr bool UNI = decltype(uni)::value;
     const float relu_lo = (a.flags & kRelu) ? 0.0f : -__builtin_inff();
-    const int rowy = a.c_out * 2;
-    const int pxj[2] = {px_of(px, 0), px_of(px, 1)};
-    const long long first = m0 * rowy + cbk * (kBn * 2) + lane_bytes();
     const float* const taken = aff + (dl ? 128 : 0);
-    i32x4 rs[4];                                     // the lane's four 16-byte pieces
+    i32x4 rs[4];
     if (a.flags & kResidual) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        rs[j] = i32x4{0, 0, 0, 0};
-        if (pxj[j & 1] >= 0) rs[j] = *(const i32x4*)(a.residual + first + (long long)pxj[j & 1] * rowy + (j >> 1) * 32);
-      }
+      load_residual(m0, px, rs);
       transpose4(rs);
     }
 #pragma unroll
@@ -683,11 +688,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       };
       i32x4 v[2], rs[2];
       if (a.flags & kResidual) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          rs[h] = i32x4{0, 0, 0, 0};
-          if (pxh[h] >= 0) rs[h] = *(const i32x4*)(a.residual + first + (long long)pxh[h] * a.c_out);
-        }
+        load_residual(m0, px, rs);
         swap_halves(rs);
       }
 #pragma unroll
@@ -1276,7 +1277,6 @@ hipError_t launch_rows(const RowsPlan& g, const Params& p, const void* w0, const
   a.rows_more = tail % g.n_slots;
   a.tr = g.tr;
   a.logp = g.logp;
-  a.pr = g.pr;
   a.n_pl = g.n_pl;
   a.s0 = g.stages[0];
   a.s = g.stages[0] + (p.gated && !p.gate_only ? g.stages[1] : 0);
