@@ -97,6 +97,10 @@ struct Bf16Rows {
   static __device__ __forceinline__ void shift_in(unsigned& d, float v, int t) {
     asm("v_cmp_ge_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(d) : "v"(v), "v"(t) : "vcc");
   }
+  // ... (v <= t)
+  static __device__ __forceinline__ void shift_in_le(unsigned& d, float v, int t) {
+    asm("v_cmp_le_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(d) : "v"(v), "v"(t) : "vcc");
+  }
 };
 
 struct I8Rows {
@@ -260,6 +264,7 @@ struct RowsArgs {
   uint32_t* bitmap;
   const uint32_t* chan_mask;
   int wo, words, c_out, rq_shift, rq_res_mult, shuf, cpg, groups;
+  int spg;                                   // stages per channel group where a block covers several, else 0
   uint32_t* gave_up;                         // host memory: set where a wait came to its bound
 };
 enum : unsigned {
@@ -270,7 +275,16 @@ enum : unsigned {
 
 constexpr int kParamsAt = (sizeof(RowsArgs) + alignof(Params) - 1) / alignof(Params) * alignof(Params);   // of the kernel's arguments
 
-template <typename Tr, int CPS, int PF, int TAPS>
+// What a launch can do beside the common part; what it cannot is not in its code, whose registers and spilled scalars every
+// wavefront pays for (all in one, the natural order cost 160 registers instead of 128 and 1 to 5 % of the time).
+enum RowsOut {
+  kNatural,                                  // fast outputs (kFast) in natural channel order
+  kHalves,                                   // the same, blocks that cover several channel groups
+  kShuffled,                                 // fast outputs in shuffled order
+  kAnyOut,                                   // every other output type and order
+};
+
+template <typename Tr, int CPS, int PF, int TAPS, int OUT>
 __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params) {
   using acc16 = typename Tr::acc16;
   using acc_t = typename Tr::acc_t;
@@ -476,17 +490,19 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   const unsigned wlane = lh * 1024 + lj * 16;        // lane's offset of its weight rows in a K step
   acc16 accP[PF][2], accS[PF][2];                    // base sums; base and conditional sums (PF = 2: accP holds these too)
 
-  // One stage: the operand reads of K steps k+1 and k+2 are in flight while step k is multiplied.
-  auto mma_stage = [&](auto f0c, auto nfc_, unsigned pat, unsigned wgt, const int (&pa)[PF][3], acc16 (&acc)[PF][2])
+  // One stage: the operand reads of K steps k+1 and k+2 are in flight while step k is multiplied.  HALVES: bit c, the block's
+  // channels 32c .. 32c + 31 take part.
+  auto mma_stage = [&](auto f0c, auto nfc_, auto halves_c, unsigned pat, unsigned wgt, const int (&pa)[PF][3], acc16 (&acc)[PF][2])
       __attribute__((always_inline)) {
     constexpr int F0 = decltype(f0c)::value, NF = decltype(nfc_)::value;       // fragments F0 .. F0 + NF - 1
     constexpr int PD = NF == 1 && KS > 1 ? 2 : 1, NR = PD + 1;
+    constexpr int HALVES = decltype(halves_c)::value, NC = HALVES == 3 ? 2 : 1;
     i32x4 wa[NR][2], xb[NR][NF];
     const unsigned wad = wgt + wlane;
     auto read_step = [&](auto kc) __attribute__((always_inline)) {
       constexpr int k = decltype(kc)::value, n = k % NR, tap = k / PAIRS, r = tap / 3, c = tap % 3;
-      wa[n][0] = lds_read16<k * 2048>(wad);
-      wa[n][1] = lds_read16<k * 2048 + 512>(wad);
+      if constexpr (HALVES & 1) wa[n][0] = lds_read16<k * 2048>(wad);
+      if constexpr (HALVES & 2) wa[n][1] = lds_read16<k * 2048 + 512>(wad);
 #pragma unroll
       for (int f = 0; f < NF; ++f)
         xb[n][f] = lds_read16<0>((unsigned)((pa[F0 + f][c] + (int)(pat + r * rowb)) ^ ((k % PAIRS) * 32)));
@@ -495,14 +511,14 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     static_for<KS>([&](auto kc) __attribute__((always_inline)) {
       constexpr int k = decltype(kc)::value, n = k % NR;
       constexpr int later = KS - 1 - k < PD - 1 ? KS - 1 - k : PD - 1;
-      __builtin_amdgcn_s_waitcnt(0xC07F | ((later * (2 + NF)) << 8));
+      __builtin_amdgcn_s_waitcnt(0xC07F | ((later * (NC + NF)) << 8));
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (k + PD < KS) read_step(std::integral_constant<int, k + PD>{});
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int f = 0; f < NF; ++f) {
-        acc[F0 + f][0] = Tr::mfma(wa[n][0], xb[n][f], acc[F0 + f][0]);
-        acc[F0 + f][1] = Tr::mfma(wa[n][1], xb[n][f], acc[F0 + f][1]);
+        if constexpr (HALVES & 1) acc[F0 + f][0] = Tr::mfma(wa[n][0], xb[n][f], acc[F0 + f][0]);
+        if constexpr (HALVES & 2) acc[F0 + f][1] = Tr::mfma(wa[n][1], xb[n][f], acc[F0 + f][1]);
       }
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -631,42 +647,113 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     for (int j = 0; j < 4; ++j)
       if (pxj[j & 1] >= 0) *(i32x4*)(a.y + first + (long long)pxj[j & 1] * rowy + (j >> 1) * 32) = v[j];
   };
+  // Shuffled channel order (Sec. 3.3): channel j of group i goes to position j*groups + i of its pixel.  The block's 64 channels
+  // are `ng` groups x `nj` channels: an LDS row holds a pixel's in the order [j][group], so that a run of ng elements is
+  // contiguous in both, and consecutive lanes store consecutive j.  A lane's sixteen words of a row are formed in registers
+  // for one, two and four groups (four: from the exchanged halves of two lanes) and the runs of several pixels are under way
+  // together.  (One element and one run after the other, as it was and as other numbers of groups still are, a fragment's output
+  // took 11000 clocks.)  With the products with zeros left out, in four groups, 64 images, us: 128 channels at 28x28, counts too
+  // 42.0 -> 31.4, 64 at 56x56 51.7 -> 36.6; eight groups of 128 at 28x28, natural order 27.7 -> 26.0.
+  auto shuffled_store = [&](i32x4 (&v)[4], long long m0, int px) __attribute__((always_inline)) {
+    const int cpg = a.cpg, groups = a.groups;
+    const int njl = cpg >= kBn ? 6 : 31 - __clz(cpg), ngl = 6 - njl;    // (a group narrower than a block divides it)
+    const int ng = 1 << ngl, nj = 1 << njl;
+    const int g0 = cbk * kBn / cpg, j0 = cbk * kBn - g0 * cpg;          // first group; first channel in it (ng = 1)
+    char* const rows = lds + a.shuf + wave * (32 * kShufRow);
+    int at = lane;                                   // (opaque: addresses formed from it are not kept across the K loops)
+    asm volatile("" : "+v"(at));
+    auto runs = [&](auto nglc) __attribute__((always_inline)) {
+      constexpr int NGL = decltype(nglc)::value, NG = 1 << NGL, NJ = 64 >> NGL, PX = 64 / NJ;      // PX pixels per store
+      using run_t = std::conditional_t<NG == 1, uint16_t, std::conditional_t<NG == 2, uint32_t, uint2>>;
+      i32x4* const mine = (i32x4*)(rows + (at & 31) * kShufRow + (at >> 5) * (NG == 1 ? 32 : 64));
+      if constexpr (NG == 1) {                       // channels 16*lh + i and 32 + 16*lh + i
+        mine[0] = v[0];
+        mine[1] = v[1];
+        mine[4] = v[2];
+        mine[5] = v[3];
+      } else {
+        i32x4 w[4];
+        if constexpr (NG == 2) {                     // j = 16*lh + i: the pairs (v[0..1], v[2..3]) of elements
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const unsigned lo = (unsigned)v[q >> 1][2 * (q & 1) + (e >> 1)], hi = (unsigned)v[2 + (q >> 1)][2 * (q & 1) + (e >> 1)];
+              w[q][e] = (int)__builtin_amdgcn_perm(hi, lo, e & 1 ? 0x07060302u : 0x05040100u);
+            }
+        } else {                                     // j = 8*lh + i: groups 2f + lh; lane halves exchange eight of their sixteen j
+#pragma unroll
+          for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v[2 * f][e], (unsigned)v[2 * f + 1][e], false, false);
+              v[2 * f][e] = (int)r[0];               // group 2f, then group 2f + 1, of j = 8*lh + 2e, 2e + 1
+              v[2 * f + 1][e] = (int)r[1];
+            }
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+              for (int f = 0; f < 2; ++f)
+                w[e][2 * h + f] = (int)__builtin_amdgcn_perm((unsigned)v[2 * f + 1][e], (unsigned)v[2 * f][e], h ? 0x07060302u : 0x05040100u);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) mine[q] = w[q];
+      }
+      wait_lds();
+      const int j = at & (NJ - 1), sub = at / NJ;    // run of the pixel, pixel of the store
+      char* const to = a.y + (m0 * a.c_out + (long long)(j0 + j) * groups + g0) * 2;
+#pragma unroll
+      for (int p0 = 0; p0 < 32; p0 += 8 * PX) {
+        run_t r[8];
+        int pq[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const int q = p0 + k * PX + sub;
+          pq[k] = __builtin_amdgcn_ds_bpermute(q * 4, px);
+          r[k] = *(const run_t*)(rows + q * kShufRow + j * (int)sizeof(run_t));
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (pq[k] >= 0) *(run_t*)(to + (long long)pq[k] * (a.c_out * 2)) = r[k];
+      }
+      wait_lds();
+    };
+    if (ng == 1) {
+      runs(std::integral_constant<int, 0>{});
+    } else if (ng == 2 && (groups & 1) == 0) {       // (g0 is a multiple of ng: runs lie on their own size)
+      runs(std::integral_constant<int, 1>{});
+    } else if (ng == 4 && (groups & 3) == 0) {
+      runs(std::integral_constant<int, 2>{});
+    } else {
+      uint16_t* const row = (uint16_t*)(rows + (at & 31) * kShufRow);
+      const int lane_ch = 16 * (at >> 5);
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int c = 32 * f + lane_ch + i;
+          row[((c & (nj - 1)) << ngl) + (c >> njl)] = (uint16_t)((unsigned)v[2 * f + (i >> 3)][(i & 7) >> 1] >> (16 * (i & 1)));
+        }
+      wait_lds();
+      for (int id = lane; id < 32 * nj; id += 64) {
+        const int q = id >> njl, j = id & (nj - 1);                     // pixel of the fragment, channel of its group
+        const int pq = __shfl(px, q, 64);
+        const uint16_t* const from = (const uint16_t*)(rows + q * kShufRow) + (j << ngl);
+        uint16_t* const to = (uint16_t*)a.y + (m0 + pq) * a.c_out + (j0 + j) * groups + g0;
+        if (pq >= 0)
+          for (int e = 0; e < ng; ++e) to[e] = from[e];
+      }
+      wait_lds();
+    }
+  };
   auto emit_fast = [&](unsigned dl, long long m0, int px) __attribute__((always_inline)) {
     if constexpr (Base::kDtype != CG_I8) {
       i32x4 v[4];
       finish(std::false_type{}, accP[0], dl, m0, px, v);
-      if (a.flags & kShuf2) {
-        // Shuffled channel order (Sec. 3.3): channel j of group i goes to position j*groups + i of its pixel.  The
-        // block's 64 channels are `ng` groups x `nj` channels: an LDS row holds a pixel's in the order [j][group], so
-        // that a run of ng elements is contiguous in both, and consecutive lanes store consecutive j.
-        const int cpg = a.cpg, groups = a.groups;
-        const int njl = cpg >= kBn ? 6 : 31 - __clz(cpg), ngl = 6 - njl;  // (a group narrower than a block divides it)
-        const int ng = 1 << ngl, nj = 1 << njl;
-        const int g0 = cbk * kBn / cpg, j0 = cbk * kBn - g0 * cpg;      // first group; first channel in it (ng = 1)
-        uint16_t* row = (uint16_t*)(lds + a.shuf + wave * (32 * kShufRow) + lj * kShufRow);
-        int lane_ch = 16 * lh;                       // (opaque: 32 addresses formed once would not fit the registers)
-        asm volatile("" : "+v"(lane_ch));
-#pragma unroll
-        for (int f = 0; f < 2; ++f)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int c = 32 * f + lane_ch + i;
-            row[((c & (nj - 1)) << ngl) + (c >> njl)] = (uint16_t)((unsigned)v[2 * f + (i >> 3)][(i & 7) >> 1] >> (16 * (i & 1)));
-          }
-        wait_lds();
-        for (int id = lane; id < 32 * nj; id += 64) {
-          const int q = id >> njl, j = id & (nj - 1);                   // pixel of the fragment, channel of its group
-          const int pq = __shfl(px, q, 64);
-          const uint16_t* from = (const uint16_t*)(lds + a.shuf + wave * (32 * kShufRow) + q * kShufRow) + (j << ngl);
-          uint16_t* to = (uint16_t*)a.y + (m0 + pq) * a.c_out + (j0 + j) * groups + g0;
-          if (pq >= 0) {
-            if (ng == 2 && (groups & 1) == 0)
-              *(uint32_t*)to = *(const uint32_t*)from;                  // (g0 is even: blocks cover whole pairs)
-            else
-              for (int e = 0; e < ng; ++e) to[e] = from[e];
-          }
-        }
-        wait_lds();
+      if constexpr (OUT == kShuffled) {
+        shuffled_store(v, m0, px);
         return;
       }
       store(v, m0, px);
@@ -820,13 +907,14 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       for (int f = 0; f < 2; ++f)
 #pragma unroll
         for (int i = 0; i < 16; ++i) accP[g][f][i] = 0;
-    // stages first .. last - 1 for fragments f0 .. f0 + nf - 1
-    auto stages = [&](auto f0, auto nf, int first, int last, acc16 (&acc)[PF][2]) __attribute__((always_inline)) {
+    // stages first .. last - 1 for fragments f0 .. f0 + nf - 1 and the halves of the block's channels
+    auto stages = [&](auto f0, auto nf, auto hv, int first, int last, acc16 (&acc)[PF][2]) __attribute__((always_inline)) {
 #pragma nounroll
       for (int s = first; s < last; ++s) {
         wait_counters<kLw>(landed, lane, v + 1, have);
         const unsigned pat = lds0 + b * a.pstr;
-        mma_stage(f0, nf, pat, a.wres < 0 ? pat + a.psz : lds0 + a.wres + s * WB, pa, acc);
+        const unsigned wgt = a.wres < 0 ? pat + a.psz : lds0 + a.wres + s * WB;
+        mma_stage(f0, nf, hv, pat, wgt, pa, acc);
         ++v;
         publish(done + 4 * wave, v);
         if (++b == a.nb) b = 0;
@@ -835,13 +923,26 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     };
     constexpr std::integral_constant<int, 0> zero{};
     constexpr std::integral_constant<int, 1> one{};
+    constexpr std::integral_constant<int, 2> two{};
+    constexpr std::integral_constant<int, 3> both{};
     if constexpr (PF == 2) {
       if (any[1])
-        stages(zero, std::integral_constant<int, 2>{}, 0, a.s0, accP);
+        stages(zero, two, both, 0, a.s0, accP);
       else
-        stages(zero, one, 0, a.s0, accP);
+        stages(zero, one, both, 0, a.s0, accP);
+    } else if constexpr (OUT == kHalves || OUT == kShuffled) {
+      // Where a block covers several channel groups and a stage lies inside one (spg), its products with a half of the block's
+      // channels may be products with zeros throughout; they are left out, a run of such stages by a loop of its own (chosen stage
+      // by stage inside one loop the sums moved between registers: 160 of them, and a third of the gain).  A base stage belongs to one group, i.e. to one half: the first half of
+      // the stages to the first.
+      if (a.spg) {
+        stages(zero, one, one, 0, a.s0 >> 1, accP);
+        stages(zero, one, two, a.s0 >> 1, a.s0, accP);
+      } else {
+        stages(zero, one, both, 0, a.s0, accP);
+      }
     } else {
-      stages(zero, one, 0, a.s0, accP);
+      stages(zero, one, both, 0, a.s0, accP);
     }
 
     unsigned dl[PF];                                 // a dense layer takes the second pair everywhere
@@ -863,17 +964,16 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
         }
       if constexpr (Base::kDtype != CG_I8) {
         if (a.flags & kTwoSided) {
+          unsigned below = 0u;                       // bit by bit as above, upper thresholds
 #pragma unroll
-          for (int f = 0; f < 2; ++f)
+          for (int f = 1; f >= 0; --f)
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-              const f32x4 hi4 = *(const f32x4*)(thi + 32 * f + 16 * lh + 4 * q4);
+            for (int q4 = 3; q4 >= 0; --q4) {
+              const i32x4 hi4 = *(const i32x4*)(thi + 32 * f + 16 * lh + 4 * q4);
 #pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const acc_t w = accP[g][f][4 * q4 + e];
-                if (!(w <= hi4[e])) dl[g] &= ~(1u << (16 * f + 4 * q4 + e));
-              }
+              for (int e = 3; e >= 0; --e) Tr::shift_in_le(below, accP[g][f][4 * q4 + e], hi4[e]);
             }
+          dl[g] &= below;
         }
       }
       if (!inside[g]) dl[g] = 0u;
@@ -896,12 +996,26 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       if (fired[0]) {
 #pragma unroll
         for (int f = 0; f < 2; ++f) accS[0][f] = accP[0][f];
-        stages(zero, one, a.s0, a.s, accS);
+        if constexpr (OUT == kHalves || OUT == kShuffled) {
+          // ... and a conditional one to all groups but its own, a half where groups have 32 channels.
+          int at = a.s0, to = a.spg && a.cpg == 32 ? a.s0 + 2 * cbk * a.spg : a.s;
+#pragma nounroll
+          for (;;) {
+            stages(zero, one, both, at, to, accS);
+            if (to == a.s) break;
+            stages(zero, one, two, to, to + a.spg, accS);
+            stages(zero, one, one, to + a.spg, to + 2 * a.spg, accS);
+            at = to + 2 * a.spg;
+            to = a.s;
+          }
+        } else {
+          stages(zero, one, both, a.s0, a.s, accS);
+        }
         pick(dl[0]);
       } else if (gated) {
         pass_by();
       }
-      if (a.flags & kFast)
+      if constexpr (OUT != kAnyOut)
         emit_fast(dl[0], m0, px[0]);
       else if (inside[0])
         emit_any(dl[0], m0 + px[0]);
@@ -918,11 +1032,11 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
         }
       }
       if (fired[0] && fired[1])
-        stages(zero, std::integral_constant<int, 2>{}, a.s0, a.s, accP);
+        stages(zero, two, both, a.s0, a.s, accP);
       else if (fired[0])
-        stages(zero, one, a.s0, a.s, accP);
+        stages(zero, one, both, a.s0, a.s, accP);
       else if (fired[1])
-        stages(one, one, a.s0, a.s, accP);
+        stages(one, one, both, a.s0, a.s, accP);
       else if (gated)
         pass_by();
 #pragma unroll
@@ -984,20 +1098,34 @@ __global__ void pack_rows_kernel(const char* __restrict__ w, char* __restrict__ 
 }
 
 
-template <typename Tr, int CPS, int PF, int TAPS>
+template <typename Tr, int CPS, int PF, int TAPS, int OUT>
 hipError_t launch_rows_one(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
   const unsigned blocks = a.xcd_cb ? (unsigned)(g.n_slots * g.n_cb) : (unsigned)a.per_xcd * 8u;
   static std::atomic<uint64_t> asked{0};
-  const hipError_t attr = allow_lds((const void*)gated_conv_rows_kernel<Tr, CPS, PF, TAPS>, kLds, asked);
+  const hipError_t attr = allow_lds((const void*)gated_conv_rows_kernel<Tr, CPS, PF, TAPS, OUT>, kLds, asked);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((gated_conv_rows_kernel<Tr, CPS, PF, TAPS>), dim3(blocks), dim3(kNt), (size_t)g.lds_bytes, s, a, p);
+  hipLaunchKernelGGL((gated_conv_rows_kernel<Tr, CPS, PF, TAPS, OUT>), dim3(blocks), dim3(kNt), (size_t)g.lds_bytes, s, a, p);
   return hipGetLastError();
 }
 
+template <typename Tr, int OUT>
+hipError_t launch_rows_out(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
+  if constexpr (OUT != kHalves) if (g.taps == 1) {
+    if (g.cps == 8) return launch_rows_one<Tr, 8, 1, 1, OUT>(g, p, a, s);
+    return g.cps == 4 ? launch_rows_one<Tr, 4, 1, 1, OUT>(g, p, a, s) : launch_rows_one<Tr, 2, 1, 1, OUT>(g, p, a, s);
+  }
+  if constexpr (Tr::Base::kDtype == CG_BF16 && OUT == kNatural)
+    if (g.pf == 2) return launch_rows_one<Tr, 4, 2, 9, OUT>(g, p, a, s);      // (planned for stages of four chunks only)
+  return g.cps == 4 ? launch_rows_one<Tr, 4, 1, 9, OUT>(g, p, a, s) : launch_rows_one<Tr, 2, 1, 9, OUT>(g, p, a, s);
+}
+
 template <typename Tr>
-hipError_t launch_point(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
-  if (g.cps == 8) return launch_rows_one<Tr, 8, 1, 1>(g, p, a, s);
-  return g.cps == 4 ? launch_rows_one<Tr, 4, 1, 1>(g, p, a, s) : launch_rows_one<Tr, 2, 1, 1>(g, p, a, s);
+hipError_t launch_rows_type(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
+  if (!(a.flags & kFast)) return launch_rows_out<Tr, kAnyOut>(g, p, a, s);
+  if constexpr (Tr::Base::kDtype == CG_BF16)
+    if (a.flags & kShuf2) return launch_rows_out<Tr, kShuffled>(g, p, a, s);
+  if (g.pf == 1 && g.taps == 9 && a.spg) return launch_rows_out<Tr, kHalves>(g, p, a, s);
+  return launch_rows_out<Tr, kNatural>(g, p, a, s);
 }
 
 unsigned magic16(int d) { return d == 1 ? 0u : (unsigned)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d); }
@@ -1093,6 +1221,10 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
   // Two fragments pay with many channels and tiles that fill them: 512 at 28x28, 12 images 43 us against 50; 256 at 14x14, 256
   // images 61 and 61; 128 at 28x28, 128 images 47 and 41.
   const int shuf_bytes = d.shuffle && d.in_dtype == CG_BF16 && d.out_dtype == CG_BF16 && !(d.epilogue & CG_EPI_RESIDUAL) ? kCw * 32 * kShufRow : 0;
+  // stages that are walked with one half of the block's channels of several groups
+  const int cpg = d.groups > 1 ? d.c_out / d.groups : 0;
+  const bool halved = g.grp_mode == 2 && cpg > 0 && cpg <= 32 && d.c_base % (cps * g.ch) == 0;
+  const double h0 = halved ? 0.55 : 1.0, h1 = halved && cpg == 32 ? 1.0 - 0.9 / d.groups : 1.0;
   double best = 1e30;
   const bool wide = d.in_dtype == CG_BF16 && d.out_dtype == CG_BF16 && !d.shuffle && cps == 4;
   for (int pf = 1; pf <= (wide ? max_pf : 1); ++pf)
@@ -1121,7 +1253,7 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
           const int frags = fwl < 0 ? (r * wo + 31) / 32 : (r + fh - 1) / fh * nfc;
           const double per_simd = 0.67 * ((frags + 3) / 4) + 0.33 * frags / 4.0;
           const double mm = ks * 64.0 * per_simd * (frags <= 4 ? 1.55 : 1.10) * (frags > kCw ? 0.87 : 1.0), mc = mm * (beta + 0.15);
-          return g.stages[0] * (mm > stream ? mm : stream) + g.stages[1] * (mc > stream ? mc : stream) + 3500.0 +
+          return g.stages[0] * (mm * h0 > stream ? mm * h0 : stream) + g.stages[1] * (mc * h1 > stream ? mc * h1 : stream) + 3500.0 +
                  per_simd * (pf == 2 ? 5800.0 : 2800.0) * (fwl == 2 ? 1.07 : 1.0);
         };
         const double c = (slot_rows / t) * tile(t) + (slot_rows % t ? tile(slot_rows % t) : 0.0) + 1500.0 +
@@ -1302,6 +1434,8 @@ hipError_t launch_rows(const RowsPlan& g, const Params& p, const void* w0, const
   a.c_out = p.c_out;
   a.cpg = p.cpg;
   a.groups = p.groups;
+  // (without grouping a padded base group is the only case of zero weights, and both halves of the channels share it)
+  a.spg = g.grp_mode == 2 && p.groups > 1 && p.cpg <= 32 && p.c_base % (g.cps * g.ch) == 0 ? p.c_base / (g.cps * g.ch) : 0;
   a.rq_shift = p.rq_shift;
   a.rq_res_mult = p.rq_res_mult;
   const bool shuf2 = p.shuffle && g.shuf_bytes > 0;
@@ -1309,11 +1443,7 @@ hipError_t launch_rows(const RowsPlan& g, const Params& p, const void* w0, const
             ((p.epilogue & CG_EPI_AFFINE) && p.in_dtype != CG_I8 ? kAffine : 0u) | ((p.epilogue & CG_EPI_RELU) ? kRelu : 0u) |
             ((p.epilogue & CG_EPI_RESIDUAL) ? kResidual : 0u) |
             ((p.out_dtype == CG_BF16 || (p.out_dtype == CG_I8 && p.rq_shift >= 2)) && (!p.shuffle || shuf2) ? kFast : 0u) | (shuf2 ? kShuf2 : 0u);
-  if (g.taps == 1)
-    return p.in_dtype == CG_I8 ? launch_point<I8Rows>(g, p, a, s) : launch_point<Bf16Rows>(g, p, a, s);
-  if (p.in_dtype == CG_I8) return g.cps == 4 ? launch_rows_one<I8Rows, 4, 1, 9>(g, p, a, s) : launch_rows_one<I8Rows, 2, 1, 9>(g, p, a, s);
-  if (g.pf == 2) return launch_rows_one<Bf16Rows, 4, 2, 9>(g, p, a, s);     // (planned for stages of four chunks only)
-  return g.cps == 4 ? launch_rows_one<Bf16Rows, 4, 1, 9>(g, p, a, s) : launch_rows_one<Bf16Rows, 2, 1, 9>(g, p, a, s);
+  return p.in_dtype == CG_I8 ? launch_rows_type<I8Rows>(g, p, a, s) : launch_rows_type<Bf16Rows>(g, p, a, s);
 }
 
 }  // namespace cg

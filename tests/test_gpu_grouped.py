@@ -134,3 +134,30 @@ def test_grouped_kernels_agree_bit_for_bit_int8():
         for other in outs[1:]:
             for u, v in zip(outs[0], other):
                 assert torch.equal(u, v)
+
+
+# The row-tiled kernel's forms for blocks that cover several groups: runs of stages that take part with one half of the block's
+# channels (groups of 32, 16 and 8 output channels, stages of one group and of less), shuffled rows of one, two, four and eight
+# groups to a block, and group counts that leave the runs of a pixel unaligned.
+SEVERAL = [
+    W.LayerShape("s_64_g2", 3, 9, 11, 64, 64, groups=2), W.LayerShape("s_64_g4", 2, 12, 7, 64, 64, groups=4),
+    W.LayerShape("s_64_g8", 2, 10, 10, 64, 64, groups=8), W.LayerShape("s_128_g2", 2, 9, 9, 128, 128, groups=2),
+    W.LayerShape("s_128_g8", 5, 8, 6, 128, 128, groups=8), W.LayerShape("s_192_g3", 2, 7, 9, 192, 192, groups=3),
+    W.LayerShape("s_192_g6s2", 2, 13, 15, 192, 192, groups=6, stride=2), W.LayerShape("s_192_g12", 1, 9, 9, 192, 192, groups=12),
+    W.LayerShape("s_256_g16", 1, 8, 8, 256, 256, groups=16), W.LayerShape("s_256>64_g2", 2, 9, 9, 256, 64, groups=2),
+]
+
+
+@pytest.mark.parametrize("shape", SEVERAL, ids=[s.name for s in SEVERAL])
+def test_rows_blocks_of_several_groups(shape):
+    inp = W.make_inputs(shape, 6100 + shape.c_out + shape.groups, kind="coherent", rho=0.3, round_bf16=True, grouped=True)
+    gate = W.calibrate_gate(inp, 0.30, sample_images=None)
+    for kw in (dict(), dict(shuffle=True), dict(shuffle=True, delta_hi=gate.delta + 0.8), dict(tau_c=0.3, n_run=1)):
+        rep = _say(P.run_float(inp, gate, in_dtype=B.CG_BF16, out_dtype=B.CG_BF16, variant=B.CG_VARIANT_MFMA_ROWS, name=shape.name, **kw))
+        assert rep.variant == B.CG_VARIANT_MFMA_ROWS
+    if shape.c_base % 16 == 0:
+        rng = np.random.default_rng(shape.c_in)
+        q = W.quantize_int8(W.make_inputs(shape, 6200 + shape.c_out, kind="coherent", rho=0.35, grouped=True))
+        thr = W.calibrate_gate_int8(q, 0.35, sample_images=None)
+        for shuffle in (False, True):
+            _say(P.run_int8(q, thr, out_i8=True, rq=W.requant_params(q, rng), shuffle=shuffle, variant=B.CG_VARIANT_MFMA_ROWS, name=shape.name))
