@@ -573,6 +573,8 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
       t[5 * tw + c] = f2u(d.shift1 ? d.shift1[c] : 0.0f);
     }
   }
+  h->base.one_pair = d.in_dtype != CG_I8 && memcmp(t + 2 * tw, t + 4 * tw, (size_t)d.c_out * 4) == 0 &&
+                     memcmp(t + 3 * tw, t + 5 * tw, (size_t)d.c_out * 4) == 0;
   // host pointers must not be used after create
   h->d.gate_mean = h->d.gate_var = h->d.delta = h->d.delta_hi = nullptr;
   h->d.gate_thr_i32 = nullptr;

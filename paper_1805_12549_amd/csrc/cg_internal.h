@@ -22,6 +22,7 @@ struct Params {
   int in_dtype, out_dtype;
   int two_sided;           // an upper gate threshold was given
   int gated;               // 0: dense layer, no gate, second affine pair applies
+  int one_pair;            // float layers: the two scale/shift pairs are equal in every channel
   int rq_shift, rq_res_mult;
   int words;               // bitmap words per pixel = ceil(c_out/32)
   int groups;              // >= 1; > 1: channel grouping (Sec. 3.3), output group i has input group i as base

@@ -271,6 +271,7 @@ enum : unsigned {
   kGated = 1u, kGateOnly = 2u, kTwoSided = 4u, kAffine = 8u, kRelu = 16u, kResidual = 32u,
   kFast = 64u,                               // 2-byte (int8 layers: 1-byte) outputs in natural channel order
   kShuf2 = 128u,                             // 2-byte outputs in shuffled channel order
+  kOnePair = 256u,                           // the two scale/shift pairs are the same
 };
 
 constexpr int kParamsAt = (sizeof(RowsArgs) + alignof(Params) - 1) / alignof(Params) * alignof(Params);   // of the kernel's arguments
@@ -748,10 +749,16 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       wait_lds();
     }
   };
-  auto emit_fast = [&](unsigned dl, long long m0, int px) __attribute__((always_inline)) {
+  // one_pair: the whole fragment takes the same scale/shift pair (nothing fired, a dense layer, or the pairs are equal, as in
+  // a network that was trained with one normalisation): half the table reads and a quarter of the instructions of a choice
+  // per value.  ResNet-18 with equal pairs, 64 images 426 -> 413 us, 256 images 1120 -> 1091.
+  auto emit_fast = [&](unsigned dl, bool one_pair, long long m0, int px) __attribute__((always_inline)) {
     if constexpr (Base::kDtype != CG_I8) {
       i32x4 v[4];
-      finish(std::false_type{}, accP[0], dl, m0, px, v);
+      if (one_pair)
+        finish(std::true_type{}, accP[0], dl, m0, px, v);
+      else
+        finish(std::false_type{}, accP[0], dl, m0, px, v);
       if constexpr (OUT == kShuffled) {
         shuffled_store(v, m0, px);
         return;
@@ -1016,7 +1023,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
         pass_by();
       }
       if constexpr (OUT != kAnyOut)
-        emit_fast(dl[0], m0, px[0]);
+        emit_fast(dl[0], !fired[0] || (a.flags & kOnePair) != 0u, m0, px[0]);
       else if (inside[0])
         emit_any(dl[0], m0 + px[0]);
     } else if constexpr (Base::kDtype != CG_I8) {
@@ -1441,7 +1448,7 @@ hipError_t launch_rows(const RowsPlan& g, const Params& p, const void* w0, const
   const bool shuf2 = p.shuffle && g.shuf_bytes > 0;
   a.flags = (p.gated ? kGated : 0u) | (p.gate_only ? kGateOnly : 0u) | (p.two_sided ? kTwoSided : 0u) |
             ((p.epilogue & CG_EPI_AFFINE) && p.in_dtype != CG_I8 ? kAffine : 0u) | ((p.epilogue & CG_EPI_RELU) ? kRelu : 0u) |
-            ((p.epilogue & CG_EPI_RESIDUAL) ? kResidual : 0u) |
+            ((p.epilogue & CG_EPI_RESIDUAL) ? kResidual : 0u) | (p.one_pair || !(p.epilogue & CG_EPI_AFFINE) ? kOnePair : 0u) |
             ((p.out_dtype == CG_BF16 || (p.out_dtype == CG_I8 && p.rq_shift >= 2)) && (!p.shuffle || shuf2) ? kFast : 0u) | (shuf2 ? kShuf2 : 0u);
   return p.in_dtype == CG_I8 ? launch_rows_type<I8Rows>(g, p, a, s) : launch_rows_type<Bf16Rows>(g, p, a, s);
 }

@@ -112,3 +112,20 @@ def test_dense_deep_point_wise_layers(n):
                shift1=rng.normal(0, 0.1, 1024))
     print("\n  " + str(P.run_float(inp, None, out_dtype=B.CG_BF16, affine=aff, epilogue=B.CG_EPI_RELU | B.CG_EPI_AFFINE, n_run=n,
                                     name=shape.name)), flush=True)
+
+
+@pytest.mark.parametrize("pairs", ["equal", "differ_in_one_shift", "none"])
+def test_one_scale_shift_pair(pairs):
+    """Fragments that take one pair throughout: nothing fired, a dense layer, equal pairs, no scale/shift at all."""
+    rng = np.random.default_rng(5)
+    c = 128
+    scale, shift = rng.uniform(0.5, 1.5, c), rng.normal(0, 0.1, c)
+    other = shift.copy()
+    other[c - 1] += 0.0 if pairs == "equal" else 0.5
+    aff = None if pairs == "none" else dict(scale0=scale, shift0=shift, scale1=scale, shift1=other)
+    epi = B.CG_EPI_RELU | (0 if aff is None else B.CG_EPI_AFFINE)
+    for groups in (4, 1):
+        inp = W.make_inputs(S(3, 13, 18, c, c, groups=groups), 8800, kind="coherent", rho=0.3, round_bf16=True)
+        gate = W.calibrate_gate(inp, 0.3, sample_images=None) if groups > 1 else None
+        rep = P.run_float(inp, gate, out_dtype=B.CG_BF16, affine=aff, epilogue=epi, variant=B.CG_VARIANT_MFMA_ROWS, name=pairs)
+        assert rep.variant == B.CG_VARIANT_MFMA_ROWS
