@@ -10,6 +10,25 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 
+// 4x4 transpose of 16-byte pieces over the four 16-lane groups of a wavefront: piece g of group j <-> piece j of group g
+__device__ __forceinline__ void transpose4(i32x4 (&v)[4]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v[j][e], (unsigned)v[j + 2][e], false, false);
+      v[j][e] = (int)r[0];
+      v[j + 2][e] = (int)r[1];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; j += 2) {
+      const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v[j][e], (unsigned)v[j + 1][e], false, false);
+      v[j][e] = (int)r[0];
+      v[j + 1][e] = (int)r[1];
+    }
+  }
+}
+
 struct Bf16Traits {
   using acc4 = f32x4;
   using acc_t = float;

@@ -6,7 +6,7 @@
 #include <cstdarg>
 #include <cstdio>
 
-#include "cg_device.h"
+#include "cg_mfma_common.h"
 
 namespace cg {
 int set_error(int code, const char* fmt, ...);   // defined with the host API
@@ -498,7 +498,77 @@ int launch_conv7x7s2c3(bool pool, const char* who, const void* x, const void* w,
   return CG_OK;
 }
 
-// 1x1 convolution with stride (the ResNet shortcut) on the matrix cores: a GEMM of the strided
+// 1x1 convolution with stride (the ResNet shortcut) on the matrix cores.
+struct PointArgs {
+  const char* x;
+  const char* w;
+  const float* scale;
+  const float* shift;
+  char* y;
+  int m_total, h, wd, c_in, c_out, stride, ho, wo, relu;
+  cg::Div d_wo, d_ho;
+};
+
+// byte offset of the input pixel of output pixel m
+__device__ __forceinline__ long long point_pixel(const PointArgs& a, unsigned m) {
+  const unsigned q = cg::quot(m, a.d_wo), img = cg::quot(q, a.d_ho);
+  const long long row = (long long)img * a.h + (q - img * (unsigned)a.ho) * (unsigned)a.stride;
+  return (row * a.wd + (m - q * (unsigned)a.wo) * (unsigned)a.stride) * (a.c_in * 2);
+}
+
+// Few pixels: a workgroup of one wavefront owns 16 pixels x 32 channels and takes both operands straight from memory in 64-byte
+// pieces, all of up to eight K steps (256 channels) at once: what bounds it is one latency.  ResNet-18's three shortcuts of one
+// image 5.2, 6.4 and 9.0 us in the kernel below, whose blocks there are 14, 8 and 8; 3.6, 4.2 and 5.1 us here.
+__global__ __launch_bounds__(64) void pointwise_small_kernel(PointArgs a) {
+  constexpr int U = 8;
+  const int lane = threadIdx.x, lj = lane & 15, lg = lane >> 4;
+  const int c0 = blockIdx.y * 32, nq = a.c_in >> 3, steps = (nq + 3) >> 2;
+  const unsigned m = blockIdx.x * 16 + lj;
+  const bool valid = m < (unsigned)a.m_total;
+  const char* const wr = a.w + (long long)(c0 + lj) * (a.c_in * 2) + lg * 16;
+  const int w16 = 16 * a.c_in * 2;
+  stem_i32x4 wv[U][2], xv[U];
+  cg::f32x4 acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}}, sc[2], sh[2];
+  const char* const xr = a.x + point_pixel(a, valid ? m : 0u) + lg * 16;
+  for (int s0 = 0; s0 < steps; s0 += U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool on = 4 * (s0 + u) + lg < nq;        // (a last step of two chunks)
+      xv[u] = wv[u][0] = wv[u][1] = stem_i32x4{0, 0, 0, 0};
+      if (on) {
+        wv[u][0] = *(const stem_i32x4*)(wr + (s0 + u) * 64);
+        wv[u][1] = *(const stem_i32x4*)(wr + w16 + (s0 + u) * 64);
+        xv[u] = *(const stem_i32x4*)(xr + (s0 + u) * 64);
+      }
+    }
+    if (s0 == 0) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        sc[i] = a.scale ? *(const cg::f32x4*)(a.scale + c0 + 16 * i + 4 * lg) : cg::f32x4{1.0f, 1.0f, 1.0f, 1.0f};
+        sh[i] = a.shift ? *(const cg::f32x4*)(a.shift + c0 + 16 * i + 4 * lg) : cg::f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(stem_bf16x8, wv[u][i]), __builtin_bit_cast(stem_bf16x8, xv[u]),
+                                                         acc[i], 0, 0, 0);
+  }
+  if (!valid) return;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = acc[i][e] * sc[i][e] + sh[i][e];
+      if (a.relu) v[e] = fmaxf(v[e], 0.0f);
+    }
+    *(uint2*)(a.y + ((long long)m * a.c_out + c0 + 16 * i + 4 * lg) * 2) = uint2{bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3])};
+  }
+}
+
+// Many pixels: a GEMM of the strided
 // pixels (column operand, 16 bytes per lane and K step straight from global memory: a pixel's
 // channels are contiguous) with the weights of a 64-channel block (row operand, laid out once
 // per block in LDS, rows permuted as in the kernel above).  Block = 128 output pixels x 64
@@ -606,31 +676,33 @@ __global__ __launch_bounds__(256) void maxpool3x3s2_kernel(const uint16_t* __res
 }
 
 // Global average pooling and the fully connected layer for channel counts in multiples of 32: a workgroup of sixteen
-// wavefronts takes up to four images and 256 classes, a wavefront 16 of them.
+// wavefronts takes up to four images and 32 to 256 classes, a wavefront 16 of them (and a share of the K steps).
 //
 // The means are fp32; each is split into three bf16 numbers that add up to it exactly (8 bits of its 24 each), and the
 // three parts of four images are twelve of the sixteen columns of one 16x16x32 product with the weights: as exact as fp32
 // products, at a third of a percent of their instructions.  What bounds it is the latency of three dependent steps
-// (read the map, meet in LDS, multiply), so a wavefront's first weights are requested before the map is read.
-// ResNet-18's head (512 channels of 7x7, 1000 classes): 11.6 us for one image and 13.6 us for 256; 23.5 and 75 us as one
-// wavefront per class with a butterfly sum for each image.
+// (read the map, meet in LDS, multiply), so a wavefront's first weights are requested before the map is read, and with few images
+// the weights of a workgroup, read at 23 bytes a clock: then it takes fewer classes, 32 at least, and its wavefronts share the
+// K steps.  ResNet-18's head (512 channels of 7x7, 1000 classes): one image 11.9 -> 7.1 us, 16 images 14.2 -> 8.2, 256 images 14.9.
 constexpr int kPoolImgs = 4;
 constexpr int kPoolSteps = 16;                   // K steps whose weights a wavefront holds at a time
 constexpr int kPoolMaxC = 2048;
 
 __global__ __launch_bounds__(1024) void avgpool_fc_mfma_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ wfc,
                                                                const float* __restrict__ bias, float* __restrict__ logits,
-                                                               int n, int hw, int c, int classes) {
+                                                               int n, int hw, int c, int classes, int cls_log) {
   typedef __attribute__((ext_vector_type(4))) float f32x4;
   extern __shared__ __align__(16) char pool_lds[];
   const int rowb = c * 2 + 16;                   // bytes of a column of the product's right operand, skewed
   float* part = (float*)(pool_lds + 16 * rowb);  // [groups][c] partial sums
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int img0 = blockIdx.x * kPoolImgs, imgs = n - img0 < kPoolImgs ? n - img0 : kPoolImgs;
-  const int k0 = blockIdx.y * 256 + wave * 16;   // this wavefront's classes
-  const int steps = c >> 5;
+  // 16 << cls_log classes to a workgroup; 16 >> cls_log wavefronts share the K steps of 16 of them
+  const int k0 = (int)(blockIdx.y << (4 + cls_log)) + (wave & ((1 << cls_log) - 1)) * 16;   // this wavefront's classes
+  const int share = wave >> cls_log, shares = 16 >> cls_log;
+  const int first = (c >> 5) * share / shares, steps = (c >> 5) * (share + 1) / shares - first;
   const int cls = k0 + (lane & 15) < classes ? k0 + (lane & 15) : classes - 1;
-  const char* wrow = (const char*)(wfc + (long long)cls * c + (lane >> 4) * 8);
+  const char* wrow = (const char*)(wfc + (long long)cls * c + (lane >> 4) * 8) + first * 64;
   stem_i32x4 wv[kPoolSteps];
 #pragma unroll
   for (int st = 0; st < kPoolSteps; ++st)
@@ -676,10 +748,10 @@ __global__ __launch_bounds__(1024) void avgpool_fc_mfma_kernel(const uint16_t* _
     *(uint16_t*)(pool_lds + (12 + im) * rowb + cc * 2) = 0;
   }
   __syncthreads();
-  if (k0 >= classes) return;
+  if (shares == 1 && k0 >= classes) return;
   // ---- product: rows = classes
   f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-  const char* col = pool_lds + (lane & 15) * rowb + (lane >> 4) * 16;
+  const char* col = pool_lds + (lane & 15) * rowb + (lane >> 4) * 16 + first * 64;
   for (int s0 = 0; s0 < steps; s0 += kPoolSteps) {
     if (s0 > 0) {
 #pragma unroll
@@ -692,6 +764,13 @@ __global__ __launch_bounds__(1024) void avgpool_fc_mfma_kernel(const uint16_t* _
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(stem_bf16x8, wv[st]),
                                                       __builtin_bit_cast(stem_bf16x8, *(const stem_i32x4*)(col + (s0 + st) * 64)),
                                                       acc, 0, 0, 0);
+  }
+  if (shares > 1) {                              // the wavefronts' sums meet where the partial sums of the map were
+    f32x4* const sums = (f32x4*)part;
+    sums[wave * 64 + lane] = acc;
+    __syncthreads();
+    if (share > 0 || k0 >= classes) return;
+    for (int s = 1; s < shares; ++s) acc += sums[((s << cls_log) + wave) * 64 + lane];
   }
   const int im = lane & 15, r0 = k0 + (lane >> 4) * 4;
 #pragma unroll
@@ -822,9 +901,18 @@ int cg_pointwise_conv(const void* x, const void* w, const float* scale, const fl
   const long long m_total = (long long)n * ho * wo;
   const long long blocks = (m_total + 127) / 128;
   if (blocks > 0x7fffffffll) return cg::set_error(CG_EUNSUPPORTED, "cg_pointwise_conv: too large");
-  hipLaunchKernelGGL(pointwise_conv_kernel, dim3((unsigned)blocks, (unsigned)(c_out / kCb)), dim3(256),
-                     (size_t)c_in * kCb * 2, (hipStream_t)hip_stream, (const uint16_t*)x, (const uint16_t*)w, scale, shift,
-                     (uint16_t*)y, m_total, h, wd, c_in, c_out, stride, ho, wo, relu);
+  // Small tiles below a quarter of a block per compute unit.  Small / large tiles, us: 64 to 128 channels, 784 pixels 3.6 / 5.2 and
+  // 12544 (196 blocks) 10.2 / 6.5; 128 to 256, 3136 pixels (100) 6.8 / 5.8; 256 to 512, 784 pixels (56) 5.5 / 9.0.
+  if (blocks * (c_out / kCb) * 4 < cg::cu_count()) {
+    const PointArgs a{(const char*)x, (const char*)w, scale, shift, (char*)y, (int)m_total, h, wd, c_in, c_out, stride, ho, wo, relu,
+                      cg::div_of(wo), cg::div_of(ho)};
+    hipLaunchKernelGGL(pointwise_small_kernel, dim3((unsigned)((m_total + 15) / 16), (unsigned)(c_out / 32)), dim3(64), 0,
+                       (hipStream_t)hip_stream, a);
+  } else {
+    hipLaunchKernelGGL(pointwise_conv_kernel, dim3((unsigned)blocks, (unsigned)(c_out / kCb)), dim3(256), (size_t)c_in * kCb * 2,
+                       (hipStream_t)hip_stream, (const uint16_t*)x, (const uint16_t*)w, scale, shift, (uint16_t*)y, m_total, h, wd,
+                       c_in, c_out, stride, ho, wo, relu);
+  }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return cg::set_error(CG_EHIP, "cg_pointwise_conv: %s", hipGetErrorString(e));
   return CG_OK;
@@ -858,9 +946,13 @@ int cg_avgpool_fc(const void* x, const void* wfc, const float* bias, float* logi
     static std::atomic<uint64_t> asked{0};
     const hipError_t attr = cg::allow_lds((const void*)avgpool_fc_mfma_kernel, 160 * 1024, asked);
     if (attr != hipSuccess) return cg::set_error(CG_EHIP, "cg_avgpool_fc: %s", hipGetErrorString(attr));
-    hipLaunchKernelGGL(avgpool_fc_mfma_kernel, dim3((unsigned)((n + kPoolImgs - 1) / kPoolImgs), (unsigned)((classes + 255) / 256)),
+    // classes to a workgroup: as few as give every compute unit one, 32 at least (each workgroup averages its images again)
+    const int groups = (n + kPoolImgs - 1) / kPoolImgs;
+    int cls_log = 1;
+    while (cls_log < 4 && (long long)groups * ((classes + (16 << cls_log) - 1) >> (4 + cls_log)) > cg::cu_count()) ++cls_log;
+    hipLaunchKernelGGL(avgpool_fc_mfma_kernel, dim3((unsigned)groups, (unsigned)((classes + (16 << cls_log) - 1) >> (4 + cls_log))),
                        dim3(1024), lds, (hipStream_t)hip_stream, (const uint16_t*)x, (const uint16_t*)wfc, bias, logits, n, hw, c,
-                       classes);
+                       classes, cls_log);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return cg::set_error(CG_EHIP, "cg_avgpool_fc: %s", hipGetErrorString(e));
     return CG_OK;

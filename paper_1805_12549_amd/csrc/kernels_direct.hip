@@ -82,15 +82,6 @@ __device__ __forceinline__ int bits_of(int v) { return v; }
 __device__ __forceinline__ void set_bits(int b, float& f) { f = __int_as_float(b); }
 __device__ __forceinline__ void set_bits(int b, int& v) { v = b; }
 
-// x / d for x < 2^31: (2x * m) >> (32 + s) with s = ceil(log2 d), m = ceil(2^(31+s) / d) < 2^32; exact, as m*d exceeds 2^(31+s)
-// by less than d <= 2^s.  (Three instructions and no branch; a division takes some 35, i.e. 180 clocks of a wavefront that
-// has nothing else to do.)
-struct Div {
-  unsigned m;
-  int s;
-};
-__device__ __forceinline__ unsigned quot(unsigned x, Div d) { return __umulhi(x << 1, d.m) >> d.s; }
-
 // What the kernels read, in one piece: a wavefront's first instructions load what its addresses are made of and wait once
 // (argument by argument, in the order of use, the waits alone took over a microsecond of a six-microsecond kernel); what
 // the end of the layer needs is loaded behind the first operands (load_rest).
@@ -759,13 +750,6 @@ hipError_t launch_direct_dtype(const DirectPlan& g, const DirectArgs& a, hipStre
     case 1 * 8 + 1: return launch_direct_tile<Tr, 1, 1>(g, a, s);
     default: return hipErrorInvalidValue;
   }
-}
-
-Div div_of(int d) {
-  Div v{0u, 0};
-  while ((1ll << v.s) < d) ++v.s;
-  v.m = (unsigned)(((1ull << (31 + v.s)) + (unsigned)d - 1) / (unsigned)d);
-  return v;
 }
 
 }  // namespace

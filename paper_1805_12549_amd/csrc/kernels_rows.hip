@@ -174,25 +174,6 @@ __device__ __forceinline__ int slot_addr(int slot, int h) {
   return slot * 32 + ((h ^ (slot >> 3)) & 1) * 16;
 }
 
-// 4x4 transpose of 16-byte pieces over the four 16-lane groups of a wavefront: piece g of group j <-> piece j of group g
-__device__ __forceinline__ void transpose4(i32x4 (&v)[4]) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v[j][e], (unsigned)v[j + 2][e], false, false);
-      v[j][e] = (int)r[0];
-      v[j + 2][e] = (int)r[1];
-    }
-#pragma unroll
-    for (int j = 0; j < 4; j += 2) {
-      const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v[j][e], (unsigned)v[j + 1][e], false, false);
-      v[j][e] = (int)r[0];
-      v[j + 1][e] = (int)r[1];
-    }
-  }
-}
-
 template <int... I, typename F>
 __device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
   (f(std::integral_constant<int, I>{}), ...);

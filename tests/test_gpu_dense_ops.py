@@ -246,3 +246,32 @@ def test_dense_ops_on_random_shapes(seed):
     B.cg_avgpool_fc(xd.data_ptr(), wd_.data_ptr(), bd.data_ptr(), out.data_ptr(), n, hw, c, classes, _stream())
     torch.cuda.synchronize()
     np.testing.assert_allclose(out.cpu().numpy(), O.avgpool_fc(x, wfc, b), rtol=P.RTOL, atol=P.ATOL)
+
+
+@pytest.mark.parametrize("n,h,w,c_in,c_out,stride", [
+    (1, 4, 4, 16, 64, 1), (1, 1, 17, 48, 64, 1), (3, 9, 7, 272, 128, 2), (1, 31, 33, 512, 192, 2),      # few pixels: 16 x 32 tiles
+    (70, 56, 57, 64, 128, 2), (19, 43, 41, 16, 64, 1), (64, 28, 28, 512, 64, 1), (130, 30, 29, 208, 256, 2)])    # many: runs of 128
+def test_pointwise_conv_forms(n, h, w, c_in, c_out, stride):
+    gen = torch.Generator(device="cuda").manual_seed(c_in + h)
+    x = torch.randn((n, h, w, c_in), generator=gen, device="cuda").to(torch.bfloat16)
+    wt = (torch.randn((c_out, c_in), generator=gen, device="cuda") * (2.0 / c_in) ** 0.5).to(torch.bfloat16)
+    sc, sh = torch.rand(c_out, generator=gen, device="cuda") + 0.5, torch.randn(c_out, generator=gen, device="cuda") * 0.1
+    y = torch.empty((n, (h - 1) // stride + 1, (w - 1) // stride + 1, c_out), dtype=torch.bfloat16, device="cuda")
+    B.cg_pointwise_conv(x.data_ptr(), wt.data_ptr(), sc.data_ptr(), sh.data_ptr(), y.data_ptr(), n, h, w, c_in, c_out, stride, True, _stream())
+    xs = x[:, ::stride, ::stride].reshape(-1, c_in).double().cpu()
+    ref = torch.relu(xs @ wt.double().cpu().t() * sc.double().cpu() + sh.double().cpu()).reshape(y.shape)
+    _check(y.double().cpu().numpy(), ref.numpy())
+
+
+@pytest.mark.parametrize("n,hw,c,classes", [(1, 49, 512, 1000), (1, 3, 32, 33), (5, 49, 2048, 40), (17, 16, 96, 1000), (70, 9, 352, 257),
+                                              (300, 4, 64, 700)])
+def test_avgpool_fc_splits(n, hw, c, classes):
+    """32 to 256 classes to a workgroup, whose K steps up to eight wavefronts share."""
+    gen = torch.Generator(device="cuda").manual_seed(n + c)
+    x = torch.relu(torch.randn((n, hw, c), generator=gen, device="cuda")).to(torch.bfloat16)
+    wfc = (torch.randn((classes, c), generator=gen, device="cuda") / c ** 0.5).to(torch.bfloat16)
+    b = torch.randn(classes, generator=gen, device="cuda")
+    out = torch.empty((n, classes), dtype=torch.float32, device="cuda")
+    B.cg_avgpool_fc(x.data_ptr(), wfc.data_ptr(), b.data_ptr(), out.data_ptr(), n, hw, c, classes, _stream())
+    ref = x.double().cpu().mean(1) @ wfc.double().cpu().t() + b.double().cpu()
+    np.testing.assert_allclose(out.cpu().numpy(), ref.numpy(), rtol=P.RTOL, atol=P.ATOL)
