@@ -372,6 +372,24 @@ CallPlan call_plan(const cg_conv* h, int n) {
   return c;
 }
 
+// Whether the requantisation of channel c fits 32 bits once its sum is clamped to [lo, hi] (sums beyond give the value that
+// the last one gives): every factor below 2^23, every sum below 2^31.  t = S*mult_d + addend + residual*res_mult lies beyond the
+// bytes' range on either side at the bounds, whichever mult is taken and whatever the residual is.
+bool fits_32_bits(const cg_conv_desc& d, int c, int32_t* addend, int32_t* lo, int32_t* hi) {
+  const long long m0 = d.rq_mult0 ? d.rq_mult0[c] : 1, m1 = d.rq_mult1 ? d.rq_mult1[c] : 1, limit = 1ll << 23;
+  const long long least = m0 < m1 ? m0 : m1, most = m0 < m1 ? m1 : m0;
+  const long long a = (long long)(d.rq_bias ? d.rq_bias[c] : 0) * (1ll << d.rq_shift) + (d.rq_shift > 0 ? 1ll << (d.rq_shift - 1) : 0ll);
+  const long long res = (d.epilogue & CG_EPI_RESIDUAL) ? 128ll * (d.rq_res_mult < 0 ? -(long long)d.rq_res_mult : d.rq_res_mult) : 0;
+  const long long range = 128ll << d.rq_shift, span = range + (a < 0 ? -a : a) + res;
+  if (least <= 0 || most >= limit || res >= 128 * limit || span >= (1ll << 31)) return false;
+  const long long bound = span / least + 1;                // at +-bound: |S * mult| > span for either mult
+  if (bound >= limit || bound * most + (a < 0 ? -a : a) + res >= (1ll << 31)) return false;
+  *addend = (int32_t)a;
+  *lo = (int32_t)-bound;
+  *hi = (int32_t)bound;
+  return true;
+}
+
 cg::Params base_params(const cg_conv* h) {
   const cg_conv_desc& d = h->d;
   const char* pk = (const char*)d.packed;
@@ -530,7 +548,8 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   // Host image of the per-channel tables.
   //   float path: 0 thr, 1 thr_hi, 2 sc0, 3 sh0, 4 sc1, 5 sh1
   //   int path:   0 thr, 2 mult0, 3 mult1, 4 bias; 5 and 6, of every 64 channels: (bias << shift) + half as 64-bit
-  //               words, 32 channels in table 5 and 32 in table 6
+  //               words, 32 channels in table 5 and 32 in table 6; where 32 bits are enough (fits_32_bits, all channels):
+  //               1 and 6 the bounds of the sum, 5 the same addend in 32 bits
   const size_t tw = lay.table_stride / 4;
   try {
     h->staging.assign(tw * kTables, 0u);
@@ -542,6 +561,10 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
   uint32_t* t = h->staging.data();
   const bool gated = d.c_base < d.c_in;
   const float inf = std::numeric_limits<float>::infinity();
+  int32_t fit_add, fit_lo, fit_hi;
+  bool fits = d.in_dtype == CG_I8 && d.out_dtype == CG_I8;
+  for (int c = 0; fits && c < d.c_out; ++c) fits = fits_32_bits(d, c, &fit_add, &fit_lo, &fit_hi);
+  h->base.fit32 = fits;
   for (int c = 0; c < d.c_out; ++c) {
     if (d.in_dtype == CG_I8) {
       t[0 * tw + c] = (uint32_t)(gated ? d.gate_thr_i32[c] : std::numeric_limits<int32_t>::min());
@@ -550,6 +573,12 @@ int cg_conv_create(cg_conv** out, const cg_conv_desc* desc, void* hip_stream) {
       t[4 * tw + c] = (uint32_t)(d.rq_bias ? d.rq_bias[c] : 0);
       const uint64_t add = (uint64_t)((long long)(d.rq_bias ? d.rq_bias[c] : 0) * (1ll << d.rq_shift) +
                                       (d.rq_shift > 0 ? 1ll << (d.rq_shift - 1) : 0ll));
+      if (fits && fits_32_bits(d, c, &fit_add, &fit_lo, &fit_hi)) {
+        t[1 * tw + c] = (uint32_t)fit_lo;
+        t[5 * tw + c] = (uint32_t)fit_add;
+        t[6 * tw + c] = (uint32_t)fit_hi;
+        continue;
+      }
       uint32_t* pair = t + (5 + c % 64 / 32) * tw + c / 64 * 64 + 2 * (c % 32);
       pair[0] = (uint32_t)add;
       pair[1] = (uint32_t)(add >> 32);

@@ -23,6 +23,7 @@ struct Params {
   int two_sided;           // an upper gate threshold was given
   int gated;               // 0: dense layer, no gate, second affine pair applies
   int one_pair;            // float layers: the two scale/shift pairs are equal in every channel
+  int fit32;               // int8 -> int8 layers: the requantisation fits 32 bits (tables 1, 5 and 6 are laid out for that)
   int rq_shift, rq_res_mult;
   int words;               // bitmap words per pixel = ceil(c_out/32)
   int groups;              // >= 1; > 1: channel grouping (Sec. 3.3), output group i has input group i as base

@@ -111,6 +111,7 @@ enum : unsigned {
   kGated = 8u, kGateOnly = 16u, kClear = 32u, kShuffle = 64u,
   kOut4 = 128u,                                   // 4-byte outputs (CG_F32 / CG_I32)
   kUni0 = 256u, kUni1 = 512u,                     // a K step of the phase lies inside one tap
+  kFit32 = 1024u,                                 // int8 -> int8: the requantisation fits 32 bits
 };
 
 __device__ __forceinline__ void load_args(const DirectArgs& a) {
@@ -126,7 +127,8 @@ __device__ __forceinline__ void load_rest(const DirectArgs& a) {
                "s"(a.words), "s"(a.rq_shift), "s"(a.rq_res_mult));
 }
 
-// The per-channel tables of four channels, fetched ahead of the sums they are needed for.
+// The per-channel tables of four channels, fetched ahead of the sums they are needed for.  (int8 layers whose requantisation
+// fits 32 bits: hi and h1 = bounds of the sum, s1 = what is added.)
 template <typename Base>
 struct Tab4 {
   i32x4 lo, hi, s0, h0, s1, h1;                  // int8 layers: s0 = mult0, h0 = mult1, s1 = bias
@@ -138,10 +140,15 @@ struct Tab4 {
       lo = *(const i32x4*)t;
       if constexpr (Base::kDtype != CG_I8) hi = *(const i32x4*)(t + a.tab_stride);
     }
+    if (Base::kDtype == CG_I8 && (a.flags & kFit32)) {
+      hi = *(const i32x4*)(t + a.tab_stride);
+      s1 = *(const i32x4*)(t + 5 * a.tab_stride);
+      h1 = *(const i32x4*)(t + 6 * a.tab_stride);
+    }
     if (Base::kDtype == CG_I8 ? !(a.flags & kOut4) : (a.flags & kAffine) != 0) {
       s0 = *(const i32x4*)(t + 2 * a.tab_stride);
       h0 = *(const i32x4*)(t + 3 * a.tab_stride);
-      s1 = *(const i32x4*)(t + 4 * a.tab_stride);
+      if (!(Base::kDtype == CG_I8 && (a.flags & kFit32))) s1 = *(const i32x4*)(t + 4 * a.tab_stride);
       if constexpr (Base::kDtype != CG_I8) h1 = *(const i32x4*)(t + 5 * a.tab_stride);
     }
   }
@@ -217,7 +224,15 @@ __device__ __forceinline__ void finish4(const DirectArgs& a, const acc_t (&s)[4]
     int32_t v[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const long long r = (long long)(int8_t)((uint32_t)res[0] >> (8 * e)) * a.rq_res_mult;
+      const int rb = (int8_t)((uint32_t)res[0] >> (8 * e));
+      if (a.flags & kFit32) {                    // (as in the row-tiled kernel)
+        const int sv = s[e] < t.hi[e] ? t.hi[e] : s[e] > t.h1[e] ? t.h1[e] : s[e];
+        int q = (__mul24(sv, ((d >> e) & 1u) ? t.h0[e] : t.s0[e]) + t.s1[e] + __mul24(rb, a.rq_res_mult)) >> a.rq_shift;
+        const int low = (a.flags & kRelu) ? 0 : -128;
+        v[e] = q < low ? low : q > 127 ? 127 : q;
+        continue;
+      }
+      const long long r = (long long)rb * a.rq_res_mult;
       long long q;
       if (a.flags & kOut4) {
         q = (long long)s[e] + r;
@@ -924,7 +939,7 @@ hipError_t launch_direct(const DirectPlan& g, const Params& p, const void* w0, c
   a.rq_res_mult = p.rq_res_mult;
   static_assert(kRelu == CG_EPI_RELU && kAffine == CG_EPI_AFFINE && kResidual == CG_EPI_RESIDUAL, "the epilogue flags pass through");
   a.flags = p.epilogue | (p.gated ? kGated : 0u) | (p.gate_only ? kGateOnly : 0u) | (p.clear_total ? kClear : 0u) |
-            (p.shuffle ? kShuffle : 0u) | (p.out_dtype == CG_F32 || p.out_dtype == CG_I32 ? kOut4 : 0u);
+            (p.shuffle ? kShuffle : 0u) | (p.out_dtype == CG_F32 || p.out_dtype == CG_I32 ? kOut4 : 0u) | (p.fit32 ? kFit32 : 0u);
   // a block's base channels start at a multiple of c_base; one that is no multiple of four chunks leaves the general walk
   const bool aligned = g.total_chunks % 4 == 0 && (p.groups <= 1 || p.c_base % (4 * g.ch) == 0) && g.gap_len % 4 == 0;
   if (aligned && g.chunks[0] % 4 == 0) a.flags |= kUni0;
