@@ -52,9 +52,21 @@
 // Where it is not faster, skipping whole fragments is what it loses against single pixels: 256 at 14x14, 256 images, by firing
 // rate 0.05: 47.6 -> 49.9, 0.1: 49.6 -> 50.4, 0.3: 55.7 -> 56.6, 0.6: 62.4 -> 60.9.
 //
+// kPaired (tiles of at most four fragments, which would leave four of the multiplying wavefronts idle): two wavefronts, on the same
+// SIMD, take a fragment, each with 32 of the block's channels, and one's LDS reads, gate and output run under the other's
+// products.  Alone on its SIMD a wavefront took half as long again as its products.  us before and after: 256 channels at 8x8, 128 images 15.7 ->
+// 15.1, 64 at 56x56, 8 images 8.1 -> 7.6, 128 at 16x16, 32 images 9.1 -> 8.6, int8 256 at 14x14, 32 images 10.5 -> 9.8, 512 at
+// 7x7, 64 images 15.3 -> 14.6; slower 256 at 14x14, 32 images 13.5 -> 13.8.  A stage still takes 1100 clocks at 256 channels where its
+// products take 576, its loads 710 (a 1 KB load is 20 clocks of the memory path, 32 where it is made of pieces of 32 bytes)
+// and its LDS accesses 800.
+//
 // A patch is stored [pixel slot][CPS chunk positions]; chunk q of slot s sits at position q ^ f(s),
 // f(s) = (s >> 2) & 3 (CPS = 4) or (s >> 3) & 1 (CPS = 2), which spreads the operand reads over the LDS
-// banks.  Slot = patch_row * P + c with P a power of two >= max(16, W + pad) and c = wi + pad;
+// banks.  (A 16-byte read is served in four groups of lanes, {0-3, 12-15, 20-27}, the rest of the first 32, and the same
+// again 32 lanes on.)  Where a group covers several patch rows, i.e. on narrow maps, the lowest bit of the row takes the place of f's highest
+// bit: 8x8 maps 1 pass to a group instead of 2, 7x7 2 instead of 3, fragments of 8 columns 1 to 1.5 instead of 2.  That costs an
+// instruction in every third read and pays only where two wavefronts share a fragment (256 channels at 8x8 3 %; with one each
+// 128 channels at 28x28 lost 1 %).  Slot = patch_row * P + c with P a power of two >= max(16, W + pad) and c = wi + pad;
 // positions outside the image are out-of-range buffer loads, which write zeros.
 //
 // The vector-memory path serves a cache line every two clocks, whatever part of it is asked for (measured: 17, 35
@@ -166,12 +178,16 @@ __device__ __forceinline__ int med3(int v, int lo, int hi) {
   return r;
 }
 
-// byte offset of chunk position (h ^ f(slot)) of pixel slot `slot`
+// f(slot), and the byte offset of chunk position (h ^ f(slot)) of pixel slot `slot`; `bit`: the slot's bit that is f's highest
 template <int CPS>
-__device__ __forceinline__ int slot_addr(int slot, int h) {
-  if constexpr (CPS == 8) return slot * 128 + ((h ^ slot) & 7) * 16;
-  if constexpr (CPS == 4) return slot * 64 + ((h ^ (slot >> 2)) & 3) * 16;
-  return slot * 32 + ((h ^ (slot >> 3)) & 1) * 16;
+__device__ __forceinline__ int slot_perm(int slot, int bit) {
+  if constexpr (CPS == 8) return slot & 7;
+  if constexpr (CPS == 4) return ((slot >> 2) & 1) | (((slot >> bit) & 1) << 1);
+  return (slot >> bit) & 1;
+}
+template <int CPS>
+__device__ __forceinline__ int slot_addr(int slot, int h, int bit) {
+  return slot * (16 * CPS) + (h ^ slot_perm<CPS>(slot, bit)) * 16;
 }
 
 template <int... I, typename F>
@@ -226,7 +242,7 @@ struct RowsArgs {
   unsigned magic_ncb, magic_ho;
   int n_cb, n_slots, xcd_cb, per_xcd;
   int full, rows_per, rows_more;             // whole rounds of tiles; rows per workgroup after them (the first rows_more: one more)
-  int tr, logp;                              // rows per tile, patch pitch
+  int tr, logp, bit;                         // rows per tile, patch pitch, chunk permutation
   int s0, s, nb, pstr, psz, wres, tabs;      // stages; buffers and LDS offsets (wres < 0: weights are in the ring)
   int ho, hp, stride, tab_stride;
   uint32_t* clear;                           // two words that the grid clears, or NULL
@@ -254,6 +270,7 @@ enum : unsigned {
   kShuf2 = 128u,                             // 2-byte outputs in shuffled channel order
   kOnePair = 256u,                           // the two scale/shift pairs are the same
   kFit32 = 512u,                             // int8: the requantisation fits 32 bits
+  kPairs = 1024u,                            // two wavefronts to a fragment
 };
 
 constexpr int kParamsAt = (sizeof(RowsArgs) + alignof(Params) - 1) / alignof(Params) * alignof(Params);   // of the kernel's arguments
@@ -262,6 +279,7 @@ constexpr int kParamsAt = (sizeof(RowsArgs) + alignof(Params) - 1) / alignof(Par
 // wavefront pays for (all in one, the natural order cost 160 registers instead of 128 and 1 to 5 % of the time).
 enum RowsOut {
   kNatural,                                  // fast outputs (kFast) in natural channel order
+  kPaired,                                   // the same, tiles of at most four fragments: two wavefronts to one, 32 channels each
   kHalves,                                   // the same, blocks that cover several channel groups
   kShuffled,                                 // fast outputs in shuffled order
   kAnyOut,                                   // every other output type and order
@@ -282,9 +300,12 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lj = lane & 31, lh = lane >> 5;
+  // fragments of 32 channels that a wavefront multiplies, and the first channel of them in the block
+  constexpr int kF = OUT == kPaired ? 1 : 2;
+  const int ch0 = OUT == kPaired && wave < kCw ? (wave >> 2) * 32 : 0;
   // All arguments in one go: each further wait for some of them is 500 clocks of a start that nothing overlaps.
   asm volatile("" ::"s"(a.flags), "s"(a.magic_ncb), "s"(a.magic_ho), "s"(a.n_cb), "s"(a.n_slots), "s"(a.xcd_cb), "s"(a.per_xcd),
-               "s"(a.full), "s"(a.rows_per), "s"(a.rows_more), "s"(a.tr), "s"(a.logp), "s"(a.s0), "s"(a.s), "s"(a.nb), "s"(a.pstr),
+               "s"(a.full), "s"(a.rows_per), "s"(a.rows_more), "s"(a.tr), "s"(a.logp), "s"(a.bit), "s"(a.s0), "s"(a.s), "s"(a.nb), "s"(a.pstr),
                "s"(a.psz), "s"(a.wres), "s"(a.tabs), "s"(a.ho), "s"(a.hp), "s"(a.stride), "s"(a.tab_stride), "s"(a.clear), "s"(a.x),
                "s"(a.w0), "s"(a.w1), "s"(a.tab), "s"(a.magic_hp), "s"(a.x_bytes), "s"(a.n), "s"(a.h), "s"(a.w), "s"(a.pad), "s"(a.xps),
                "s"(a.n_pl), "s"(a.base_chn), "s"(a.gap_chn), "s"(a.grp_mode), "s"(a.grp_step), "s"(a.fwl), "s"(a.nfc), "s"(a.magic_wo),
@@ -364,7 +385,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     // and the column are then the same in all loads.  (Positions behind the patch's last row read some row of x or zeros.)  kOut: past the end of any x (the plan keeps x below 2 GiB).
     constexpr int kOut = (int)0x80000000, kStep = kLw * 64 / CPS;
     const int sl0 = lw * (64 / CPS) + lane / CPS;
-    const int chunk = ((lane % CPS) ^ (CPS == 8 ? sl0 & 7 : CPS == 4 ? (sl0 >> 2) & 3 : (sl0 >> 3) & 1)) * 16;
+    const int chunk = ((lane % CPS) ^ slot_perm<CPS>(sl0, a.bit)) * 16;
     const int np = (a.n_pl - lw + kLw - 1) / kLw;            // patch loads of this wavefront
     const int rowx = a.w * a.xps;            // bytes per image row
     auto column = [&](int sl) __attribute__((always_inline)) {
@@ -464,13 +485,14 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   // ================================ multiplying wavefronts ==========================================
   // (the address waits in LDS: read from the arguments at the end of each wavefront it cost a launch 1.5 us)
   if (tid == 0) *(uint32_t**)(lds + a.tabs + kTabs * 256 + 48) = a.gave_up;
-  acc_t* const tlo = (acc_t*)(lds + a.tabs);         // [64] thresholds, lower and upper
+  acc_t* const tlo = (acc_t*)(lds + a.tabs) + ch0;   // [64] thresholds, lower and upper
   acc_t* const thi = tlo + 64;
   float* const aff = (float*)(thi + 64);             // [4][64] scale0, shift0, scale1, shift1; int8: mult0, mult1
-  long long* const addends = (long long*)(aff + 192);// int8: what is added before the shift
+  long long* const addends = (long long*)(aff + 192 - ch0) + ch0;      // int8: what is added before the shift
   bare_barrier();                                    // the counters are set up
   const int rowb = SB << a.logp;                     // bytes per patch row
-  const unsigned wlane = lh * 1024 + lj * 16;        // lane's offset of its weight rows in a K step
+  const int flip = OUT != kPaired || a.bit < a.logp ? 0 : CPS * 8;     // what a patch row more changes in the chunk permutation
+  const unsigned wlane = lh * 1024 + (lj + ch0) * 16;// lane's offset of its weight rows in a K step
   acc16 accP[PF][2], accS[PF][2];                    // base sums; base and conditional sums (PF = 2: accP holds these too)
 
   // One stage: the operand reads of K steps k+1 and k+2 are in flight while step k is multiplied.  HALVES: bit c, the block's
@@ -488,7 +510,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       if constexpr (HALVES & 2) wa[n][1] = lds_read16<k * 2048 + 512>(wad);
 #pragma unroll
       for (int f = 0; f < NF; ++f)
-        xb[n][f] = lds_read16<0>((unsigned)((pa[F0 + f][c] + (int)(pat + r * rowb)) ^ ((k % PAIRS) * 32)));
+        xb[n][f] = lds_read16<0>((unsigned)((pa[F0 + f][c] + (int)(pat + r * rowb)) ^ (r == 1 ? (k % PAIRS) * 32 ^ flip : (k % PAIRS) * 32)));
     };
     static_for<PD>([&](auto kc) __attribute__((always_inline)) { read_step(kc); });
     static_for<KS>([&](auto kc) __attribute__((always_inline)) {
@@ -515,7 +537,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   // The pixel's sums: with a fired gate the ones that hold the conditional channels.
   auto pick = [&](unsigned dl) __attribute__((always_inline)) {
 #pragma unroll
-    for (int f = 0; f < 2; ++f)
+    for (int f = 0; f < kF; ++f)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int m = (int)(dl << (31 - 16 * f - i)) >> 31;
@@ -531,17 +553,38 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     return __builtin_amdgcn_ds_bpermute((lane & 15) * 4 + h * 64, px);
   };
   auto lane_bytes = [&]() __attribute__((always_inline)) {
+    if constexpr (kF == 1) return lane & 48;
     int b = (lane & 32 ? 64 : 0) + (lane & 16 ? 16 : 0);
     if constexpr (PF == 2) asm volatile("" : "+v"(b));        // (addresses formed from it are not kept across the K loops)
     return b;
   };
+  // pieces of a lane's own pixel <-> pieces in that order; two pieces: access j is 16 pixels, again four lanes per pixel
+  auto swap_halves = [&](auto& u) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const auto r = __builtin_amdgcn_permlane16_swap((unsigned)u[0][e], (unsigned)u[1][e], false, false);
+      u[0][e] = (int)r[0];
+      u[1][e] = (int)r[1];
+    }
+  };
+  auto transpose = [&](i32x4 (&u)[2 * kF]) __attribute__((always_inline)) {
+    if constexpr (kF == 1)
+      swap_halves(u);
+    else
+      transpose4(u);
+  };
   // The residual of the lanes' pixels px (counted from pixel m0 of the batch; -1: none), 2 x 16 channels each, as it is read:
   // the lane's 16-byte pieces in the transposed order, four of bf16, two of int8.
   auto load_residual = [&](long long m0, int px, auto& rs) __attribute__((always_inline)) {
-    constexpr int kPieces = Base::kDtype == CG_I8 ? 2 : 4;
+    if constexpr (Base::kDtype == CG_I8 && kF == 1) {
+      rs[0] = i32x4{0, 0, 0, 0};
+      if (px >= 0) rs[0] = *(const i32x4*)(a.residual + (m0 + px) * a.c_out + cbk * kBn + ch0 + 16 * lh);
+      return;
+    }
+    constexpr int kPieces = Base::kDtype == CG_I8 ? 2 : 2 * kF;
     const int pxj[2] = {px_of(px, 0), px_of(px, 1)};
     const int rowy = Base::kDtype == CG_I8 ? a.c_out : a.c_out * 2;
-    const long long first = m0 * rowy + (Base::kDtype == CG_I8 ? cbk * kBn + (lane & 16) * 2 + (lane & 32) / 2 : cbk * (kBn * 2) + lane_bytes());
+    const long long first = m0 * rowy + (Base::kDtype == CG_I8 ? cbk * kBn + (lane & 16) * 2 + (lane & 32) / 2 : (cbk * kBn + ch0) * 2 + lane_bytes());
 #pragma unroll
     for (int j = 0; j < kPieces; ++j) {
       rs[j] = i32x4{0, 0, 0, 0};
@@ -550,17 +593,17 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   };
   // Output of those pixels in three steps that whole wavefronts execute.  First the values, from sums, the residual and the
   // decisions in dl (bit 16*f + i; UNI: all the same):
-  auto finish = [&](auto uni, const acc16 (&sum)[2], unsigned dl, long long m0, int px, i32x4 (&v)[4]) __attribute__((always_inline)) {
+  auto finish = [&](auto uni, const acc16 (&sum)[2], unsigned dl, long long m0, int px, i32x4 (&v)[2 * kF]) __attribute__((always_inline)) {
     constexpr bool UNI = decltype(uni)::value;
     const float relu_lo = (a.flags & kRelu) ? 0.0f : -__builtin_inff();
     const float* const taken = aff + (dl ? 128 : 0);
-    i32x4 rs[4];
+    i32x4 rs[2 * kF];
     if (a.flags & kResidual) {
       load_residual(m0, px, rs);
-      transpose4(rs);
+      transpose(rs);
     }
 #pragma unroll
-    for (int f = 0; f < 2; ++f)
+    for (int f = 0; f < kF; ++f)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {                  // eight channels at a time
         const int cl = 32 * f + 16 * lh + 8 * h;
@@ -621,13 +664,13 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       }
   };
   // and the stores
-  auto store = [&](i32x4 (&v)[4], long long m0, int px) __attribute__((always_inline)) {
+  auto store = [&](i32x4 (&v)[2 * kF], long long m0, int px) __attribute__((always_inline)) {
     const int rowy = a.c_out * 2;
     const int pxj[2] = {px_of(px, 0), px_of(px, 1)};
-    const long long first = m0 * rowy + cbk * (kBn * 2) + lane_bytes();
-    transpose4(v);
+    const long long first = m0 * rowy + (cbk * kBn + ch0) * 2 + lane_bytes();
+    transpose(v);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 2 * kF; ++j)
       if (pxj[j & 1] >= 0) *(i32x4*)(a.y + first + (long long)pxj[j & 1] * rowy + (j >> 1) * 32) = v[j];
   };
   // Shuffled channel order (Sec. 3.3): channel j of group i goes to position j*groups + i of its pixel.  The block's 64 channels
@@ -666,7 +709,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
             }
         } else {                                     // j = 8*lh + i: groups 2f + lh; lane halves exchange eight of their sixteen j
 #pragma unroll
-          for (int f = 0; f < 2; ++f)
+          for (int f = 0; f < kF; ++f)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v[2 * f][e], (unsigned)v[2 * f + 1][e], false, false);
@@ -678,7 +721,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-              for (int f = 0; f < 2; ++f)
+              for (int f = 0; f < kF; ++f)
                 w[e][2 * h + f] = (int)__builtin_amdgcn_perm((unsigned)v[2 * f + 1][e], (unsigned)v[2 * f][e], h ? 0x07060302u : 0x05040100u);
         }
 #pragma unroll
@@ -713,7 +756,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       uint16_t* const row = (uint16_t*)(rows + (at & 31) * kShufRow);
       const int lane_ch = 16 * (at >> 5);
 #pragma unroll
-      for (int f = 0; f < 2; ++f)
+      for (int f = 0; f < kF; ++f)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int c = 32 * f + lane_ch + i;
@@ -736,7 +779,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   // per value.  ResNet-18 with equal pairs, 64 images 426 -> 413 us, 256 images 1120 -> 1091.
   auto emit_fast = [&](unsigned dl, bool one_pair, long long m0, int px) __attribute__((always_inline)) {
     if constexpr (Base::kDtype != CG_I8) {
-      i32x4 v[4];
+      i32x4 v[2 * kF];
       if (one_pair)
         finish(std::true_type{}, accP[0], dl, m0, px, v);
       else
@@ -754,18 +797,10 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       const int h_hi = (1 << (a.rq_shift - 1)) - 1, h_lo = -1 - h_hi;
       const int pxh[2] = {px_of(px, 0), px_of(px, 1)};
       const long long first = m0 * a.c_out + cbk * kBn + (lane & 16) * 2 + (lane & 32) / 2;
-      auto swap_halves = [&](i32x4 (&u)[2]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const auto r = __builtin_amdgcn_permlane16_swap((unsigned)u[0][e], (unsigned)u[1][e], false, false);
-          u[0][e] = (int)r[0];
-          u[1][e] = (int)r[1];
-        }
-      };
       i32x4 v[2], rs[2];
       if (a.flags & kResidual) {
         load_residual(m0, px, rs);
-        swap_halves(rs);
+        if constexpr (kF == 2) swap_halves(rs);
       }
       // four values, clamped to the bytes' range, as bytes
       auto pack4 = [&](const unsigned (&c)[4]) __attribute__((always_inline)) {
@@ -780,7 +815,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
         const int* const mult = (const int*)aff + (UNI && dl ? 64 : 0);
         const int *const s_lo = (const int*)thi, *const add = (const int*)aff + 192, *const s_hi = (const int*)aff + 256;
 #pragma unroll
-        for (int f = 0; f < 2; ++f) {
+        for (int f = 0; f < kF; ++f) {
           const int cl = 32 * f + 16 * lh;
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
@@ -808,7 +843,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
           narrow(std::false_type{});
       } else {
 #pragma unroll
-      for (int f = 0; f < 2; ++f) {
+      for (int f = 0; f < kF; ++f) {
         const int cl = 32 * f + 16 * lh;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -827,6 +862,10 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
         }
       }
       }
+      if constexpr (kF == 1) {
+        if (px >= 0) *(i32x4*)(a.y + (m0 + px) * a.c_out + cbk * kBn + ch0 + 16 * lh) = v[0];
+        return;
+      }
       swap_halves(v);
 #pragma unroll
       for (int h = 0; h < 2; ++h)
@@ -843,7 +882,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     int lane_ch = 16 * lh;
     asm volatile("" : "+v"(lane_ch));
 #pragma unroll
-    for (int f = 0; f < 2; ++f) {
+    for (int f = 0; f < kF; ++f) {
       const int co0 = cbk * kBn + 32 * f + lane_ch;
       const unsigned d16 = (dl >> (16 * f)) & 0xffffu;
       if (q.shuffle) {
@@ -887,14 +926,14 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     if constexpr (PF == 2) asm volatile("" : "+v"(lp));       // (formed for each tile: no registers to keep them)
 #pragma unroll
     for (int g = 0; g < PF; ++g) {
-      const int fr = wave + kCw * g;
+      const int fr = (OUT == kPaired ? wave & 3 : wave) + kCw * g;
       int lr, wo_;
       if constexpr (TAPS == 1) {                     // a row is a pixel
         const int i = fr * 32 + lp;
         px[g] = i < rows_here ? i : -1;
         inside[g] = i < rows_here;
         any[g] = __ballot(inside[g]) != 0ull;
-        pa[g][0] = slot_addr<CPS>(inside[g] ? i : 0, lh);
+        pa[g][0] = slot_addr<CPS>(inside[g] ? i : 0, lh, a.bit);
         pimg[g] = a.chan_mask ? (R0 + (inside[g] ? i : 0)) / a.hp : 0;
         continue;
       }
@@ -916,7 +955,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       pimg[g] = div16(R, a.magic_ho);
       const int slot0 = ((pimg[g] * a.hp + (R - pimg[g] * a.ho) * a.stride - rho0) << a.logp) + wo_ * a.stride;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) pa[g][c] = slot_addr<CPS>(slot0 + c, lh);
+      for (int c = 0; c < 3; ++c) pa[g][c] = slot_addr<CPS>(slot0 + c, lh, a.bit);
       px[g] = inside[g] ? lr * a.wo + wo_ : -1;
     }
     auto pass_by = [&]() __attribute__((always_inline)) {
@@ -932,7 +971,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
 #pragma unroll
     for (int g = 0; g < PF; ++g)
 #pragma unroll
-      for (int f = 0; f < 2; ++f)
+      for (int f = 0; f < kF; ++f)
 #pragma unroll
         for (int i = 0; i < 16; ++i) accP[g][f][i] = 0;
     // stages first .. last - 1 for fragments f0 .. f0 + nf - 1 and the halves of the block's channels
@@ -953,6 +992,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     constexpr std::integral_constant<int, 1> one{};
     constexpr std::integral_constant<int, 2> two{};
     constexpr std::integral_constant<int, 3> both{};
+    constexpr std::integral_constant<int, (1 << kF) - 1> mine{};
     if constexpr (PF == 2) {
       if (any[1])
         stages(zero, two, both, 0, a.s0, accP);
@@ -970,7 +1010,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
         stages(zero, one, both, 0, a.s0, accP);
       }
     } else {
-      stages(zero, one, both, 0, a.s0, accP);
+      stages(zero, one, mine, 0, a.s0, accP);
     }
 
     unsigned dl[PF];                                 // a dense layer takes the second pair everywhere
@@ -983,7 +1023,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       // ---- gate --------------------------------------------------------------------------------------
       dl[g] = 0u;
 #pragma unroll
-      for (int f = 1; f >= 0; --f)
+      for (int f = kF - 1; f >= 0; --f)
 #pragma unroll
         for (int q4 = 3; q4 >= 0; --q4) {
           const i32x4 lo4 = *(const i32x4*)(tlo + 32 * f + 16 * lh + 4 * q4);
@@ -994,7 +1034,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
         if (a.flags & kTwoSided) {
           unsigned below = 0u;                       // bit by bit as above, upper thresholds
 #pragma unroll
-          for (int f = 1; f >= 0; --f)
+          for (int f = kF - 1; f >= 0; --f)
 #pragma unroll
             for (int q4 = 3; q4 >= 0; --q4) {
               const i32x4 hi4 = *(const i32x4*)(thi + 32 * f + 16 * lh + 4 * q4);
@@ -1008,11 +1048,16 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       if (a.chan_mask) {
         // channel-wise gate (Sec. 3.2): only the channels that keep their conditional path in this image
         const uint32_t* mw = a.chan_mask + (long long)pimg[g] * a.words + cbk * 2;
-        dl[g] &= ((mw[0] >> (16 * lh)) & 0xffffu) | (((mw[1] >> (16 * lh)) & 0xffffu) << 16);
+        if constexpr (kF == 1)
+          dl[g] &= mw[ch0 >> 5] >> (16 * lh);
+        else
+          dl[g] &= ((mw[0] >> (16 * lh)) & 0xffffu) | (((mw[1] >> (16 * lh)) & 0xffffu) << 16);
       }
       if (a.bitmap) {
         const unsigned other = (unsigned)__shfl_xor((int)dl[g], 32, 64);   // the pixel's other channels
-        if (lh == 0 && inside[g])
+        if constexpr (kF == 1) {
+          if (lh == 0 && inside[g]) a.bitmap[(m0 + px[g]) * a.words + cbk * 2 + (ch0 >> 5)] = dl[g] | (other << 16);
+        } else if (lh == 0 && inside[g])
           *(uint2*)(a.bitmap + (m0 + px[g]) * a.words + cbk * 2) =
               uint2{(dl[g] & 0xffffu) | (other << 16), (dl[g] >> 16) | (other & 0xffff0000u)};
       }
@@ -1023,7 +1068,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     if constexpr (PF == 1) {
       if (fired[0]) {
 #pragma unroll
-        for (int f = 0; f < 2; ++f) accS[0][f] = accP[0][f];
+        for (int f = 0; f < kF; ++f) accS[0][f] = accP[0][f];
         if constexpr (OUT == kHalves || OUT == kShuffled) {
           // ... and a conditional one to all groups but its own, a half where groups have 32 channels.
           int at = a.s0, to = a.spg && a.cpg == 32 ? a.s0 + 2 * cbk * a.spg : a.s;
@@ -1037,7 +1082,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
             to = a.s;
           }
         } else {
-          stages(zero, one, both, a.s0, a.s, accS);
+          stages(zero, one, mine, a.s0, a.s, accS);
         }
         pick(dl[0]);
       } else if (gated) {
@@ -1138,7 +1183,7 @@ hipError_t launch_rows_one(const RowsPlan& g, const Params& p, const RowsArgs& a
 
 template <typename Tr, int OUT>
 hipError_t launch_rows_out(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
-  if constexpr (OUT != kHalves) if (g.taps == 1) {
+  if constexpr (OUT != kHalves && OUT != kPaired) if (g.taps == 1) {
     if (g.cps == 8) return launch_rows_one<Tr, 8, 1, 1, OUT>(g, p, a, s);
     return g.cps == 4 ? launch_rows_one<Tr, 4, 1, 1, OUT>(g, p, a, s) : launch_rows_one<Tr, 2, 1, 1, OUT>(g, p, a, s);
   }
@@ -1147,12 +1192,19 @@ hipError_t launch_rows_out(const RowsPlan& g, const Params& p, const RowsArgs& a
   return g.cps == 4 ? launch_rows_one<Tr, 4, 1, 9, OUT>(g, p, a, s) : launch_rows_one<Tr, 2, 1, 9, OUT>(g, p, a, s);
 }
 
+// fragments of a tile of r rows of wo pixels
+int tile_fragments(int r, int fwl, int nfc, int wo) {
+  const int fh = 32 >> (fwl < 0 ? 0 : fwl);
+  return fwl < 0 ? (r * wo + 31) / 32 : (r + fh - 1) / fh * nfc;
+}
+
 template <typename Tr>
 hipError_t launch_rows_type(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
   if (!(a.flags & kFast)) return launch_rows_out<Tr, kAnyOut>(g, p, a, s);
   if constexpr (Tr::Base::kDtype == CG_BF16)
     if (a.flags & kShuf2) return launch_rows_out<Tr, kShuffled>(g, p, a, s);
   if (g.pf == 1 && g.taps == 9 && a.spg) return launch_rows_out<Tr, kHalves>(g, p, a, s);
+  if (a.flags & kPairs) return launch_rows_out<Tr, kPaired>(g, p, a, s);
   return launch_rows_out<Tr, kNatural>(g, p, a, s);
 }
 
@@ -1253,6 +1305,7 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
   const int cpg = d.groups > 1 ? d.c_out / d.groups : 0;
   const bool halved = g.grp_mode == 2 && cpg > 0 && cpg <= 32 && d.c_base % (cps * g.ch) == 0;
   const double h0 = halved ? 0.55 : 1.0, h1 = halved && cpg == 32 ? 1.0 - 0.9 / d.groups : 1.0;
+  const bool pairs = !halved && !d.shuffle && (d.out_dtype == CG_BF16 || (d.out_dtype == CG_I8 && d.rq_shift >= 2));
   double best = 1e30;
   const bool wide = d.in_dtype == CG_BF16 && d.out_dtype == CG_BF16 && !d.shuffle && cps == 4;
   for (int pf = 1; pf <= (wide ? max_pf : 1); ++pf)
@@ -1267,6 +1320,7 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
     const int step = fwl < 0 ? 1 : fh;
     for (int t = tmax; t >= step && 4 * t >= tmax; t -= step) {
       const int pr = patch_rows(t);
+      const bool paired = pairs && pf == 1 && tile_fragments(t, fwl, nfc, wo) <= kCw / 2;
       const long long psz = (((long long)pr << g.logp) * 16 * cps + 1023) / 1024 * 1024;
       if (psz / 1024 > kMaxPatchLoads * kLw) continue;
       for (int resident = 1; resident >= 0; --resident) {
@@ -1277,12 +1331,13 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
         if (nb > 8) nb = 8;
         const double lines = (double)(pr * (d.w < (1 << g.logp) ? d.w : (1 << g.logp))) + (resident ? 0 : wb / 128.0);
         const double stream = 2.0 * lines + (nb == 2 ? 910.0 : nb == 3 ? 150.0 : 0.0);
+        // (two wavefronts to a fragment hide some of each other's waits)
         auto tile = [&](int r) {
-          const int frags = fwl < 0 ? (r * wo + 31) / 32 : (r + fh - 1) / fh * nfc;
+          const int frags = tile_fragments(r, fwl, nfc, wo);
           const double per_simd = 0.67 * ((frags + 3) / 4) + 0.33 * frags / 4.0;
-          const double mm = ks * 64.0 * per_simd * (frags <= 4 ? 1.55 : 1.10) * (frags > kCw ? 0.87 : 1.0), mc = mm * (beta + 0.15);
+          const double mm = ks * 64.0 * per_simd * (frags > 4 ? 1.10 : paired ? 1.30 : 1.55) * (frags > kCw ? 0.87 : 1.0), mc = mm * (beta + 0.15);
           return g.stages[0] * (mm * h0 > stream ? mm * h0 : stream) + g.stages[1] * (mc * h1 > stream ? mc * h1 : stream) + 3500.0 +
-                 per_simd * (pf == 2 ? 5800.0 : 2800.0) * (fwl == 2 ? 1.07 : 1.0);
+                 per_simd * (pf == 2 ? 5800.0 : paired ? 1700.0 : 2800.0) * (fwl == 2 ? 1.07 : 1.0);
         };
         const double c = (slot_rows / t) * tile(t) + (slot_rows % t ? tile(slot_rows % t) : 0.0) + 1500.0 +
                          (resident ? S * wb / 60.0 : 0.0);
@@ -1471,6 +1526,12 @@ hipError_t launch_rows(const RowsPlan& g, const Params& p, const void* w0, const
             ((p.epilogue & CG_EPI_AFFINE) && p.in_dtype != CG_I8 ? kAffine : 0u) | ((p.epilogue & CG_EPI_RELU) ? kRelu : 0u) |
             ((p.epilogue & CG_EPI_RESIDUAL) ? kResidual : 0u) | (p.in_dtype != CG_I8 && (p.one_pair || !(p.epilogue & CG_EPI_AFFINE)) ? kOnePair : 0u) | (p.fit32 ? kFit32 : 0u) |
             ((p.out_dtype == CG_BF16 || (p.out_dtype == CG_I8 && p.rq_shift >= 2)) && (!p.shuffle || shuf2) ? kFast : 0u) | (shuf2 ? kShuf2 : 0u);
+  const bool pairs = (a.flags & kFast) && !p.shuffle && !a.spg && g.pf == 1 && g.taps == 9 && tile_fragments(g.tr, g.fwl, g.nfc, p.wo) <= kCw / 2;
+  if (pairs) a.flags |= kPairs;
+  // rows of the patch lie in the banks of others: runs of 32 pixels over several of them, fragments of up to 8 columns (counted for widths of 2
+  // to 56: never more passes than with the fixed bit; from 32 columns on and at stride 2 there are)
+  const bool narrow = p.stride == 1 && (g.fwl < 0 ? p.wo < 32 : g.fwl <= 3);
+  a.bit = pairs && narrow && (2 << g.logp) <= kLw * 64 / g.cps ? g.logp : 3;
   return p.in_dtype == CG_I8 ? launch_rows_type<I8Rows>(g, p, a, s) : launch_rows_type<Bf16Rows>(g, p, a, s);
 }
 

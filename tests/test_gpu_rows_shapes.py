@@ -129,3 +129,43 @@ def test_one_scale_shift_pair(pairs):
         gate = W.calibrate_gate(inp, 0.3, sample_images=None) if groups > 1 else None
         rep = P.run_float(inp, gate, out_dtype=B.CG_BF16, affine=aff, epilogue=epi, variant=B.CG_VARIANT_MFMA_ROWS, name=pairs)
         assert rep.variant == B.CG_VARIANT_MFMA_ROWS
+
+
+PAIRED = [
+    S(128, 8, 8, 256, 256),                    # full fragments of four rows
+    S(40, 7, 7, 512, 512),                     # runs of 32 pixels over five rows and images, stages of four chunks
+    S(2, 3, 4, 64, 128),                       # part of one fragment
+    S(9, 13, 13, 64, 192),
+    S(3, 17, 31, 128, 128),                    # the widest rows whose number goes into the chunk permutation
+    S(3, 12, 33, 64, 64),                      # fragments of eight columns or runs, the fixed permutation
+    S(11, 17, 15, 64, 128, stride=2),
+    S(6, 12, 18, 64, 128, groups=1),           # dense
+]
+
+
+@pytest.mark.parametrize("shape", PAIRED, ids=[s.name for s in PAIRED])
+def test_two_wavefronts_to_a_fragment(shape):
+    """Tiles of at most four fragments: each wavefront has 32 of the block's 64 channels.  Every gate and output option."""
+    c, full = shape.c_out, B.CG_EPI_RELU | B.CG_EPI_AFFINE | B.CG_EPI_RESIDUAL
+    rng = np.random.default_rng(c + shape.w)
+    aff = dict(scale0=rng.uniform(0.5, 1.5, c), shift0=rng.normal(0, 0.1, c), scale1=rng.uniform(0.5, 1.5, c), shift1=rng.normal(0, 0.1, c))
+    res = rng.standard_normal((shape.n, shape.ho, shape.wo, c)).astype(np.float32)
+    inp = W.make_inputs(shape, 9600 + shape.h, kind="coherent", rho=0.3, round_bf16=True)
+    gate = W.calibrate_gate(inp, 0.3, sample_images=2) if shape.groups > 1 else None
+    runs = [dict(epilogue=B.CG_EPI_RELU), dict(affine=aff, residual=res, epilogue=full, n_run=max(1, shape.n - 1))]
+    if gate:
+        runs += [dict(affine=aff, epilogue=full & ~B.CG_EPI_RESIDUAL, delta_hi=gate.delta + 0.8), dict(epilogue=0, tau_c=0.3)]
+    for r in runs:
+        rep = P.run_float(inp, gate, out_dtype=B.CG_BF16, variant=B.CG_VARIANT_MFMA_ROWS, name=shape.name, **r)
+        assert rep.variant == B.CG_VARIANT_MFMA_ROWS
+    if not gate or c * shape.n > 12000:
+        return
+    q = W.quantize_int8(W.make_inputs(shape, 9700 + shape.h, kind="coherent", rho=0.35))
+    thr = W.calibrate_gate_int8(q, 0.35, sample_images=None)
+    r8 = rng.integers(-128, 128, (shape.n, shape.ho, shape.wo, c)).astype(np.int8)
+    for hi, shift in ((200, 14), (1 << 20, 24)):                     # the requantisation in 32 bits and in 64
+        rq = dict(rq_mult0=rng.integers(-hi, hi, c).astype(np.int32), rq_mult1=rng.integers(-hi, hi, c).astype(np.int32),
+                  rq_bias=rng.integers(-hi, hi, c).astype(np.int32), rq_shift=shift)
+        P.run_int8(q, thr, out_i8=True, rq=rq, epilogue=B.CG_EPI_RELU, variant=B.CG_VARIANT_MFMA_ROWS, name=shape.name)
+        P.run_int8(q, thr, out_i8=True, rq=rq, residual=r8, rq_res_mult=hi // 2, epilogue=B.CG_EPI_RESIDUAL, variant=B.CG_VARIANT_MFMA_ROWS,
+                   name=shape.name)
