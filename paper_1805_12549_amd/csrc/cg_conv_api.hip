@@ -1,6 +1,7 @@
 // Host side of the C ABI: argument validation, threshold folding (merged gate of
 // Sec. 3.2 of the channel-gating paper), layout of the caller's `packed` buffer,
 // kernel-family choice and launch sequencing.  No device memory is allocated here.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -303,21 +304,23 @@ void pick_kernel(const cg_conv* h, CallPlan* c) {
     c->kernel = kDirect;
     return;
   }
-  // The estimated times of the two, in clocks.  Over 427 layers of one to 100000 output pixels (3x3 and 1x1, strides one and
-  // two, grouped and not) what is picked takes 1 % longer than the better of the two in the mean.  Small-tile kernel / other, us:
+  // The estimated times of the two, in clocks.  Over 123 layers of 50 to 250000 output pixels (3x3 and 1x1, strides one and
+  // two) what is picked takes 0.2 % longer than the better of the two in the mean and 8 % at most.  Small-tile kernel / other, us:
   // 512 channels at 7x7, one image 8.9 / 18.9, eight 13.6 / 19.8; 64 at 56x56, one 5.7 / 8.5, four 9.8 / 9.0, eight 15.2 /
   // 10.0; int8 256 at 14x14, eight 8.3 / 10.9.  Strided 1x1 layers, where the other is the large-tile kernel: 256 to 448 at
   // 20x20, 193 images 34 / 188.  Fully connected, 448 to 3968, 49 images 5.4 / 17.8, 2816 to 3776, 378 images 40 / 30.
-  double other, mine = c->direct.cost;
-  if (c->kernel == kRows) {
-    other = h->point_ok ? c->rows.cost : 4900.0 + 1.52 * c->rows.cost;
+  // 1x1, 128 to 128 at 28x28, 64 images 18.6 / 11.0; int8 64 to 128 at 56x56 stride 2, 32 images 16.1 / 10.6.
+  double other;
+  if (h->point_ok) {
+    other = c->rows.cost;                                 // (the large-tile kernel is taken above where it is faster than that)
+  } else if (c->kernel == kRows) {
+    other = 3900.0 + 1.45 * std::min(c->rows.cost, 22000.0) + 1.05 * std::max(c->rows.cost - 22000.0, 0.0);
   } else {
     const cg::TilePlan& t = c->tile;
     const int rounds = (t.wgs + cg::cu_count() - 1) / cg::cu_count();
     other = 7200.0 + rounds * (7900.0 + (t.stages[0] + 0.29 * t.stages[1]) * (1200.0 + 2.3 * t.cps * t.fp * t.bn));
   }
-  if (mine > 33000.0) mine += 0.25 * (mine - 33000.0);      // (its estimate is low where tiles are many)
-  if (mine < other) c->kernel = kDirect;
+  if (c->direct.est < other) c->kernel = kDirect;
 }
 
 // Two fragments per wavefront write an output twice and read the residual after the first time: where the two may be the

@@ -129,7 +129,7 @@ struct DirectPlan {
   int ksteps[2];           // K steps (four chunks) per phase
   int n_grp;               // 32-channel groups of the packed weights
   size_t wpk_bytes[2];
-  double cost;             // estimated time, in clocks
+  double cost, est;        // estimated time, in clocks: what plans were compared by; what the kernel is chosen by
 };
 
 DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu);
@@ -164,7 +164,7 @@ struct RowsPlan {
   int fwl, nfc;            // fragment of a wavefront: 2^fwl columns (-1: 32 pixels in a row), fragments per row group
   int wres, shuf, shuf_bytes, tabs, lds_bytes;   // LDS offsets of resident weights (-1: none), shuffled rows, tables
   size_t wpk_base_bytes, wpk_cond_bytes;
-  double cost;             // estimated time, in clocks
+  double cost, est;        // estimated time, in clocks: what plans were compared by; what the kernel is chosen by
 };
 
 // cps: 0 = pick, 4 or 2 = that (for a handle whose weights are packed); max_pf: the most fragments per wavefront

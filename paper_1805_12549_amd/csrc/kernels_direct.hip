@@ -812,7 +812,8 @@ DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu) {
 
   // Tile and split with the least estimated time, in clocks, fitted to 4500 measured plans of 277 layers (bf16 and int8, fp32
   // by itself; one to 31000 output pixels, 16 to 4000 channels).  What it picks takes 2.6 % longer than the best plan in
-  // the mean, 13 % at the 95th percentile.
+  // the mean, 13 % at the 95th percentile.  (That is what plans are compared by.  `est`, by which the kernel is chosen, counts the output of many
+  // tiles more: over 123 layers it is 9 % off.)
   //   A K step costs the vector-memory path 50 clocks for 16 pixels (64-byte pieces) and 12 (fp32: 32) for 16 channels of
   //   weights; the matrix cores take 16 (175) for a product, and a wavefront 450 (80) for the latency of a batch of
   //   steps.  Workgroups on a compute unit at the same time overlap in their latencies only.
@@ -846,6 +847,7 @@ DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu) {
         const double c = start + rounds * (each0 + each1 * nu) + wave0 * turns + std::max(busy, chain) + 0.35 * std::min(busy, chain) + (whole ? 2500.0 : 0.0);
         if (c >= g.cost) continue;
         g.cost = c;
+        g.est = 500.0 + 1.03 * c + nu * (100.0 * (rounds - 1.0) * (whole ? 4.0 : 1.0) + (whole ? 480.0 : 0.0));
         g.pf = pf;
         g.nh = nh;
         g.split = split;

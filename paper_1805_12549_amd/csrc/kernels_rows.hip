@@ -1431,15 +1431,15 @@ RowsPlan point_plan(const cg_conv_desc& d, int n_cu) {
   g.lds_bytes = off + kTabBytes;
   g.wpk_base_bytes = (size_t)g.n_cb * g.stages[0] * wb;
   g.wpk_cond_bytes = (size_t)g.n_cb * g.stages[1] * wb;
-  // The estimated time, fitted to 67 layers of 2 to 50000 pixels: a stage takes its products, its lines of memory or, where it
-  // is short, 950 clocks of latency.
-  g.cost = 4400.0 + (g.resident ? S * wb / 60.0 : 0.0);
+  // The estimated time, with the call's host part, in clocks of 2.25 GHz, fitted to 40 layers of 100 to 100000 pixels (4 % off, 10 % at most): a stage
+  // takes its products, its lines of memory or, where it is short, 980 clocks of latency; a conditional one half of that.
+  g.cost = 8450.0 + (g.resident ? S * wb / 60.0 : 0.0);
   for (long long left = each; left > 0; left -= g.tr) {
     const long long here = left < g.tr ? left : g.tr, frags = (here + 31) / 32;
     const double per_simd = 0.67 * ((frags + 3) / 4) + 0.33 * frags / 4.0;
-    const double mm = g.cps / 2 * 64.0 * per_simd * (frags <= 4 ? 1.55 : 1.10);
-    const double stream = 6.8 * (here * 16 * g.cps + (g.resident ? 0 : wb)) / 128.0;
-    g.cost += S * std::max(950.0, std::max(mm, stream)) + 3450.0 + 4500.0 * per_simd;
+    const double mm = g.cps / 2 * 102.0 * per_simd * (frags <= 4 ? 1.55 : 1.10);
+    const double stream = 7.86 * (here * 16 * g.cps + (g.resident ? 0 : wb)) / 128.0;
+    g.cost += (g.stages[0] + 0.51 * g.stages[1]) * std::max(984.0, std::max(mm, stream)) + 2180.0 + 2075.0 * per_simd;
   }
   g.ok = 1;
   return g;
