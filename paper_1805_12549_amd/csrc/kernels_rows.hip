@@ -1320,7 +1320,7 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
     const int step = fwl < 0 ? 1 : fh;
     for (int t = tmax; t >= step && 4 * t >= tmax; t -= step) {
       const int pr = patch_rows(t);
-      const bool paired = pairs && pf == 1 && tile_fragments(t, fwl, nfc, wo) <= kCw / 2;
+      const bool paired = pairs && pf == 1 && t >= slot_rows && tile_fragments(t, fwl, nfc, wo) <= kCw / 2;
       const long long psz = (((long long)pr << g.logp) * 16 * cps + 1023) / 1024 * 1024;
       if (psz / 1024 > kMaxPatchLoads * kLw) continue;
       for (int resident = 1; resident >= 0; --resident) {
@@ -1331,7 +1331,7 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
         if (nb > 8) nb = 8;
         const double lines = (double)(pr * (d.w < (1 << g.logp) ? d.w : (1 << g.logp))) + (resident ? 0 : wb / 128.0);
         const double stream = 2.0 * lines + (nb == 2 ? 910.0 : nb == 3 ? 150.0 : 0.0);
-        // (two wavefronts to a fragment hide some of each other's waits)
+        // (two wavefronts to a fragment hide some of each other's waits; counted for one tile, since of several the next ones hide them)
         auto tile = [&](int r) {
           const int frags = tile_fragments(r, fwl, nfc, wo);
           const double per_simd = 0.67 * ((frags + 3) / 4) + 0.33 * frags / 4.0;
