@@ -397,6 +397,48 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
   const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc((void*)p.x, (short)0, p.x_bytes, 0x00027000);
   constexpr unsigned kOut = 0x80000000u;            // an offset beyond any x (the plan keeps x below 1 GiB)
 
+  // The sums of a split in blocks of four K steps, which are added up in this wavefront's part of `ex`: a sum is rounded by the more
+  // the more sums it passes through.  Against 64 bits, rms: fp32 512 to 256 channels at 20x20 stride 2 4.2e-7 as one chain, 1.3e-7 in blocks
+  // (1.4e-7 with K split over workgroups as well, as it was); bf16 512 to 64 at 14x14 1.4e-7, 0.84e-7 (0.86e-7).  That costs 1 to 3 % of a layer.
+  // The largest tiles, whose waves have few steps each, have no registers for it (96 to 80 at 45x33 8.6 -> 11.2 us).
+  constexpr bool kBlocks = SPLIT && Base::kDtype != CG_I8 && NU < 8;
+  constexpr bool kTwo = kBlocks && (kU == 4 || NH == 2);     // two sums at a time, of the even and of the odd steps (where registers allow)
+  acc4 odd[PF][NH];
+  if constexpr (kTwo) {
+#pragma unroll
+    for (int f = 0; f < PF; ++f)
+#pragma unroll
+      for (int i = 0; i < NH; ++i) odd[f][i] = acc4{0, 0, 0, 0};
+  }
+  auto join = [&](acc4 (&a)[PF][NH]) __attribute__((always_inline)) {
+    if constexpr (kTwo) {
+#pragma unroll
+      for (int f = 0; f < PF; ++f)
+#pragma unroll
+        for (int i = 0; i < NH; ++i) {
+          a[f][i] += odd[f][i];
+          odd[f][i] = acc4{0, 0, 0, 0};
+        }
+    }
+  };
+  bool carried = false;
+  auto carry = [&](int batch, acc4 (&a)[PF][NH]) __attribute__((always_inline)) {
+    if constexpr (kBlocks) {
+      if (kU == 1 && (batch & 2) == 0) return;
+      join(a);
+#pragma unroll
+      for (int f = 0; f < PF; ++f)
+#pragma unroll
+        for (int i = 0; i < NH; ++i) {
+          i32x4* const at = &ex[(wave * NU + f * NH + i) * 64 + lane];
+          if (carried) a[f][i] += __builtin_bit_cast(acc4, *at);
+          *at = __builtin_bit_cast(i32x4, a[f][i]);
+          a[f][i] = acc4{0, 0, 0, 0};
+          if constexpr (NU == 4) __builtin_amdgcn_sched_barrier(0);      // (one unit at a time: no registers for more)
+        }
+      carried = true;
+    }
+  };
   // K steps [k0, k1) of phase ph into a.  `meanwhile` runs once the first operands are on their way.
   auto walk = [&](int ph, int k0, int k1, acc4 (&a)[PF][NH], auto meanwhile) __attribute__((always_inline)) {
     const int nq = ph ? p.chunks1 : p.chunks0;
@@ -491,7 +533,10 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
 #pragma unroll
           for (int f = 0; f < PF; ++f)
 #pragma unroll
-            for (int i = 0; i < NH; ++i) a[f][i] = Tr::mma(part, w[b][u][i], x[b][u][f], a[f][i]);
+            for (int i = 0; i < NH; ++i) {
+              acc4& to = kTwo && (u & 1) ? odd[f][i] : a[f][i];
+              to = Tr::mma(part, w[b][u][i], x[b][u][f], to);
+            }
     };
     using B0 = std::integral_constant<int, 0>;
     using B1 = std::integral_constant<int, 1>;
@@ -507,12 +552,26 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
         fetch_x(B1{});
       }
       mul(B0{});
+      if (kU == 4 && i + 1 < nb) carry(i, a);
       if (i + 1 < nb) {
         if (i + 2 < nb) {
           fetch_w(B0{});
           fetch_x(B0{});
         }
         mul(B1{});
+      }
+      if (i + 2 < nb) carry(i, a);
+    }
+    if constexpr (kBlocks) {
+      join(a);
+      if (carried) {
+#pragma unroll
+        for (int f = 0; f < PF; ++f)
+#pragma unroll
+          for (int i = 0; i < NH; ++i) {
+            a[f][i] += __builtin_bit_cast(acc4, ex[(wave * NU + f * NH + i) * 64 + lane]);
+            if constexpr (NU == 4) __builtin_amdgcn_sched_barrier(0);
+          }
       }
     }
     if constexpr (MIXED) {

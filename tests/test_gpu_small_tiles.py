@@ -3,6 +3,7 @@ oracle, through the C ABI: channel counts that are multiples of nothing large, b
 inside a 16-byte chunk, single images, fp32, both forms (K split over wavefronts / one wavefront per tile)."""
 import numpy as np
 import pytest
+import torch
 
 from paper_1805_12549_amd import binding as B
 from paper_1805_12549_amd import workloads as W
@@ -171,3 +172,28 @@ def test_tile_edges(shape, grouped):
         q = W.quantize_int8(W.make_inputs(shape, 7400 + shape.c_out + shape.h, kind=kind, rho=0.35, grouped=grouped))
         thr = W.calibrate_gate_int8(q, 0.35, sample_images=None)
         _say(P.run_int8(q, thr, name=shape.name + " int8", **kw))
+
+
+@pytest.mark.parametrize("dtype,shape", [("f32", (1, 20, 512, 256, 2)), ("f32", (1, 9, 128, 80, 1)), ("bf16", (1, 14, 512, 64, 1)),
+                                         ("bf16", (4, 4, 512, 128, 1))])
+def test_sums_of_a_split_against_64_bits(dtype, shape):
+    """A deep dense layer of few pixels: K is split over eight wavefronts, each adding up blocks of four K steps.
+
+    A rounding is at most 2^-24 of the sum it makes and 0.58 of that in the rms.  On its way a product passes through those of
+    its half block (two steps; fp32: four products each), of the wavefront's blocks and of the eight wavefronts' sums, none of which
+    is larger than the result in the rms.  (As one chain to a wavefront the fp32 errors were 1.3 and 2.4 times the bound.)"""
+    n, h, c, co, s = shape
+    g = torch.Generator().manual_seed(c + co)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    x = torch.randn(n, h, h, c, generator=g).to(tdt)
+    w = (torch.randn(co, 3, 3, c, generator=g) / (9 * c) ** 0.5).to(tdt)
+    layer = B.GatedConv(n_max=n, h=h, w=h, c_in=c, c_out=co, c_base=c, w_base=w.cuda(), w_cond=None,
+                        in_dtype=B.CG_F32 if dtype == "f32" else B.CG_BF16, out_dtype=B.CG_F32, kh=3, kw=3, stride=s, pad=1, epilogue=0)
+    y = layer.forward(x.cuda(), bitmap=False, counts=False)[0].cpu().double()
+    ref = torch.nn.functional.conv2d(x.double().permute(0, 3, 1, 2), w.double().permute(0, 3, 1, 2), stride=s, padding=1).permute(0, 2, 3, 1)
+    steps = 9 * c // (16 if dtype == "f32" else 32)                  # K steps of the layer
+    roundings = (8 if dtype == "f32" else 2) + -(-steps // 32) + 8
+    rms = (y - ref).pow(2).mean().sqrt().item()
+    bound = 0.58 * 2.0 ** -24 * roundings ** 0.5 * ref.pow(2).mean().sqrt().item()
+    print("%s %s: %.3g of %.3g" % (dtype, shape, rms, bound))
+    assert rms <= bound
