@@ -347,7 +347,8 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
   // K steps whose operands are fetched together; two such batches are in flight.  (Two steps instead of one for tiles of four
   // units and more: 133 to 181 registers, one workgroup on a compute unit instead of two, 1 to 7 % slower.)
   constexpr int kU = NU == 1 ? 4 : NU == 2 ? 2 : 1;
-  __shared__ __align__(16) i32x4 ex[SPLIT ? kMaxSplit * NU * 64 : 1];     // [wavefront][unit][lane]
+  constexpr bool kBlocks = SPLIT ? Base::kDtype != CG_I8 && NU < 8 : Base::kDtype == CG_F32;      // (see `carry`)
+  __shared__ __align__(16) i32x4 ex[SPLIT ? kMaxSplit * NU * 64 : kBlocks ? 4 * NU * 64 : 1];     // [wavefront][unit][lane]
 
   load_args(p);
   const int tid = threadIdx.x, lane = tid & 63;
@@ -397,12 +398,14 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
   const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc((void*)p.x, (short)0, p.x_bytes, 0x00027000);
   constexpr unsigned kOut = 0x80000000u;            // an offset beyond any x (the plan keeps x below 1 GiB)
 
-  // The sums of a split in blocks of four K steps, which are added up in this wavefront's part of `ex`: a sum is rounded by the more
-  // the more sums it passes through.  Against 64 bits, rms: fp32 512 to 256 channels at 20x20 stride 2 4.2e-7 as one chain, 1.3e-7 in blocks
-  // (1.4e-7 with K split over workgroups as well, as it was); bf16 512 to 64 at 14x14 1.4e-7, 0.84e-7 (0.86e-7).  That costs 1 to 3 % of a layer.
-  // The largest tiles, whose waves have few steps each, have no registers for it (96 to 80 at 45x33 8.6 -> 11.2 us).
-  constexpr bool kBlocks = SPLIT && Base::kDtype != CG_I8 && NU < 8;
-  constexpr bool kTwo = kBlocks && (kU == 4 || NH == 2);     // two sums at a time, of the even and of the odd steps (where registers allow)
+  // Float sums in blocks of two K steps to an accumulator (32 x 16 tiles of a split: four), which are added up in this wavefront's
+  // part of `ex`: a sum is rounded the more, the more sums it passes through.  Error against 64 bits, rms, relative, as one chain and in
+  // blocks: fp32 1x1, 192 to 64 channels at 42x45 stride 2, 67 images (whole) 1.43e-7 and 0.88e-7; 256 to 1664, 1011 pixels (whole) 1.82e-7 and
+  // 0.94e-7; 192 to 192 at 3x3, 6x62, 3 images (split) 1.20e-7 in blocks of four, 1.05e-7 of two.  Over 1350 layers it is at most 1.03
+  // (fp32) and 1.07 (bf16, K of a few steps) times that of the form that split K over workgroups as well, 0.81 and 0.96 in the mean.  It costs the
+  // whole form 1 to 4 % (17.0 -> 17.5 us, 18.7 -> 20.0), a split 1 to 3 %.  Not where it would cost more: bf16 sums of the whole form, whose K steps
+  // are one product each, and a split's tiles of eight units, which have no registers for it (96 to 80 at 45x33 8.6 -> 11.2 us) and few steps each.
+  constexpr bool kTwo = kBlocks && SPLIT && (kU == 4 || (kU == 2 && NH == 2));     // two sums at a time, of the even and of the odd steps
   acc4 odd[PF][NH];
   if constexpr (kTwo) {
 #pragma unroll
@@ -422,9 +425,8 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
     }
   };
   bool carried = false;
-  auto carry = [&](int batch, acc4 (&a)[PF][NH]) __attribute__((always_inline)) {
+  auto carry = [&](acc4 (&a)[PF][NH]) __attribute__((always_inline)) {
     if constexpr (kBlocks) {
-      if (kU == 1 && (batch & 2) == 0) return;
       join(a);
 #pragma unroll
       for (int f = 0; f < PF; ++f)
@@ -434,7 +436,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
           if (carried) a[f][i] += __builtin_bit_cast(acc4, *at);
           *at = __builtin_bit_cast(i32x4, a[f][i]);
           a[f][i] = acc4{0, 0, 0, 0};
-          if constexpr (NU == 4) __builtin_amdgcn_sched_barrier(0);      // (one unit at a time: no registers for more)
+          if constexpr (NU >= 4 || !SPLIT) __builtin_amdgcn_sched_barrier(0);      // (one unit at a time: no registers for more)
         }
       carried = true;
     }
@@ -456,6 +458,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
     const int dt = nq > 4 ? 0 : nq >= 3 ? 1 : nq == 2 ? 2 : 4, di = 4 - dt * nq;    // a K step on: so many taps and chunks on
     const int q0 = ph ? 0 : nq - 1;
     int k = k0;
+    carried = false;
     i32x4 x[2][kU][PF], w[2][kU][NH];
     bool cut[2][kU];                                // the step's unit is the straddling chunk (the mask is applied where the
                                                     // operand is used: at the load it would wait for it)
@@ -552,7 +555,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
         fetch_x(B1{});
       }
       mul(B0{});
-      if (kU == 4 && i + 1 < nb) carry(i, a);
+      if (kU == 4 && i + 1 < nb) carry(a);
       if (i + 1 < nb) {
         if (i + 2 < nb) {
           fetch_w(B0{});
@@ -560,7 +563,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
         }
         mul(B1{});
       }
-      if (i + 2 < nb) carry(i, a);
+      if (i + 2 < nb) carry(a);
     }
     if constexpr (kBlocks) {
       join(a);
@@ -570,7 +573,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
 #pragma unroll
           for (int i = 0; i < NH; ++i) {
             a[f][i] += __builtin_bit_cast(acc4, ex[(wave * NU + f * NH + i) * 64 + lane]);
-            if constexpr (NU == 4) __builtin_amdgcn_sched_barrier(0);
+            if constexpr (NU >= 4 || !SPLIT) __builtin_amdgcn_sched_barrier(0);
           }
       }
     }

@@ -197,3 +197,31 @@ def test_sums_of_a_split_against_64_bits(dtype, shape):
     bound = 0.58 * 2.0 ** -24 * roundings ** 0.5 * ref.pow(2).mean().sqrt().item()
     print("%s %s: %.3g of %.3g" % (dtype, shape, rms, bound))
     assert rms <= bound
+
+
+@pytest.mark.parametrize("shape,chain,sums", [
+    ((67, 42, 45, 192, 64, 1, 2, 4), 8, 5), ((27, 30, 31, 128, 64, 1, 1, 4), 8, 3), ((1011, 1, 1, 256, 1664, 1, 1, 8), 8, 7),
+    ((23, 27, 27, 32, 80, 3, 1, 2), 8, 5), ((89, 11, 11, 128, 256, 3, 2, 2), 36, 4)],
+    ids=["whole_192>64s2", "whole_128>64", "whole_fc", "whole_3x3", "split_of_eight_units"])
+def test_sums_of_gated_fp32_layers_against_64_bits(shape, chain, sums):
+    """The whole form adds up blocks of two K steps (eight 16x16x4 products); a split's tiles of eight units take a wavefront's share in
+    one chain (nine steps here).
+
+    A rounding is at most 2^-24 of the sum it makes and 0.58 of that in the rms.  In a chain of m additions of equal terms the sum grows with
+    them, so that they come to (m + 1) / 2 roundings of the last sum: those of a block, of the `sums` blocks or wavefronts of the
+    conditional path, and one for base and conditional sum.  (With one chain over K the whole form's errors were 1.45, 1.20, 1.71 and 1.52 times the bound.)"""
+    n, h, w_, c, co, k, s, groups = shape
+    cb = c // groups
+    g = torch.Generator().manual_seed(c + co)
+    x = torch.relu(torch.randn(n, h, w_, c, generator=g))
+    w = torch.randn(co, k, k, c, generator=g) * (2.0 / (k * k * c)) ** 0.5
+    layer = B.GatedConv(n_max=n, h=h, w=w_, c_in=c, c_out=co, c_base=cb, w_base=w[..., :cb].contiguous().cuda(), w_cond=w[..., cb:].contiguous().cuda(),
+                        in_dtype=B.CG_F32, out_dtype=B.CG_F32, kh=k, kw=k, stride=s, pad=k // 2, epilogue=0, gate_mean=np.zeros(co),
+                        gate_var=np.ones(co), delta=np.full(co, -np.inf))
+    y = layer.forward(x.cuda(), bitmap=False, counts=False)[0].cpu().double()
+    layer.close()
+    ref = torch.nn.functional.conv2d(x.double().permute(0, 3, 1, 2), w.double().permute(0, 3, 1, 2), stride=s, padding=k // 2).permute(0, 2, 3, 1)
+    rms = (y - ref).pow(2).mean().sqrt().item()
+    bound = 0.58 * 2.0 ** -24 * ((chain + 1) / 2 + (sums + 1) / 2 + 1) ** 0.5 * ref.pow(2).mean().sqrt().item()
+    print("%s: %.3g of %.3g" % (shape, rms, bound))
+    assert rms <= bound
