@@ -403,7 +403,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
   // blocks: fp32 1x1, 192 to 64 channels at 42x45 stride 2, 67 images (whole) 1.43e-7 and 0.88e-7; 256 to 1664, 1011 pixels (whole) 1.82e-7 and
   // 0.94e-7; 192 to 192 at 3x3, 6x62, 3 images (split) 1.20e-7 in blocks of four, 1.05e-7 of two.  Over 1350 layers it is at most 1.03
   // (fp32) and 1.07 (bf16, K of a few steps) times that of the form that split K over workgroups as well, 0.81 and 0.96 in the mean.  It costs the
-  // whole form 1 to 4 % (17.0 -> 17.5 us, 18.7 -> 20.0), a split 1 to 3 %.  Not where it would cost more: bf16 sums of the whole form, whose K steps
+  // whole form 2 % in the mean of 46 layers (16.9 -> 17.4 us, 18.9 -> 19.6; two of them, tiles of eight units, 24.4 -> 26.9), a split 1 to 3 %.  Not where it would cost more: bf16 sums of the whole form, whose K steps
   // are one product each, and a split's tiles of eight units, which have no registers for it (96 to 80 at 45x33 8.6 -> 11.2 us) and few steps each.
   constexpr bool kTwo = kBlocks && SPLIT && (kU == 4 || (kU == 2 && NH == 2));     // two sums at a time, of the even and of the odd steps
   acc4 odd[PF][NH];
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
           if (carried) a[f][i] += __builtin_bit_cast(acc4, *at);
           *at = __builtin_bit_cast(i32x4, a[f][i]);
           a[f][i] = acc4{0, 0, 0, 0};
-          if constexpr (NU >= 4 || !SPLIT) __builtin_amdgcn_sched_barrier(0);      // (one unit at a time: no registers for more)
+          if (SPLIT ? NU >= 4 : (f * NH + i) % 2 != 0) __builtin_amdgcn_sched_barrier(0);      // (one or two units at a time: no registers for more)
         }
       carried = true;
     }
@@ -573,7 +573,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
 #pragma unroll
           for (int i = 0; i < NH; ++i) {
             a[f][i] += __builtin_bit_cast(acc4, ex[(wave * NU + f * NH + i) * 64 + lane]);
-            if constexpr (NU >= 4 || !SPLIT) __builtin_amdgcn_sched_barrier(0);
+            if (SPLIT ? NU >= 4 : (f * NH + i) % 2 != 0) __builtin_amdgcn_sched_barrier(0);
           }
       }
     }
