@@ -595,7 +595,8 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   // decisions in dl (bit 16*f + i; UNI: all the same):
   auto finish = [&](auto uni, const acc16 (&sum)[2], unsigned dl, long long m0, int px, i32x4 (&v)[2 * kF]) __attribute__((always_inline)) {
     constexpr bool UNI = decltype(uni)::value;
-    const float relu_lo = (a.flags & kRelu) ? 0.0f : -__builtin_inff();
+    // (the larger of a number and a NaN is the number: without ReLU every value stays what it is, a NaN included)
+    const float relu_lo = (a.flags & kRelu) ? 0.0f : __builtin_nanf("");
     const float* const taken = aff + (dl ? 128 : 0);
     i32x4 rs[2 * kF];
     if (a.flags & kResidual) {

@@ -687,7 +687,7 @@ __global__ __launch_bounds__(kNT) void gated_conv_tile_kernel(Params p, TilePlan
     const bool lean = Base::kDtype != CG_I8 && p.out_dtype == CG_BF16 &&
                       !(p.epilogue & (CG_EPI_AFFINE | CG_EPI_RESIDUAL));
     const bool fastaff = Base::kDtype != CG_I8 && p.out_dtype == CG_BF16 && (p.epilogue & CG_EPI_AFFINE);
-    const float relu_lo = (p.epilogue & CG_EPI_RELU) ? 0.0f : -__builtin_inff();
+    const float relu_lo = (p.epilogue & CG_EPI_RELU) ? 0.0f : __builtin_nanf("");      // (as in the row-tiled kernel)
     char* const wtile = buf0 + wave * (32 * (64 * 2 + 16));
 #pragma unroll
     for (int fp = 0; fp < FP; ++fp) {
