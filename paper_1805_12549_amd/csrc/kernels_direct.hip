@@ -348,6 +348,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
   // units and more: 133 to 181 registers, one workgroup on a compute unit instead of two, 1 to 7 % slower.)
   constexpr int kU = NU == 1 ? 4 : NU == 2 ? 2 : 1;
   constexpr bool kBlocks = SPLIT ? Base::kDtype != CG_I8 && NU < 8 : Base::kDtype == CG_F32;      // (see `carry`)
+  constexpr bool kPair = !SPLIT && Base::kDtype == CG_BF16;                                        // (the same)
   __shared__ __align__(16) i32x4 ex[SPLIT ? kMaxSplit * NU * 64 : kBlocks ? 4 * NU * 64 : 1];     // [wavefront][unit][lane]
 
   load_args(p);
@@ -398,23 +399,24 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
   const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc((void*)p.x, (short)0, p.x_bytes, 0x00027000);
   constexpr unsigned kOut = 0x80000000u;            // an offset beyond any x (the plan keeps x below 1 GiB)
 
-  // Float sums in blocks of two K steps to an accumulator (32 x 16 tiles of a split: four), which are added up in this wavefront's
-  // part of `ex`: a sum is rounded the more, the more sums it passes through.  Error against 64 bits, rms, relative, as one chain and in
-  // blocks: fp32 1x1, 192 to 64 channels at 42x45 stride 2, 67 images (whole) 1.43e-7 and 0.88e-7; 256 to 1664, 1011 pixels (whole) 1.82e-7 and
-  // 0.94e-7; 192 to 192 at 3x3, 6x62, 3 images (split) 1.20e-7 in blocks of four, 1.05e-7 of two.  Over 1350 layers it is at most 1.03
-  // (fp32) and 1.07 (bf16, K of a few steps) times that of the form that split K over workgroups as well, 0.81 and 0.96 in the mean.  It costs the
-  // whole form 2 % in the mean of 46 layers (16.9 -> 17.4 us, 18.9 -> 19.6; two of them, tiles of eight units, 24.4 -> 26.9), a split 1 to 3 %.  Not where it would cost more: bf16 sums of the whole form, whose K steps
-  // are one product each, and a split's tiles of eight units, which have no registers for it (96 to 80 at 45x33 8.6 -> 11.2 us) and few steps each.
+  // How float sums are added up: a sum is rounded the more, the more sums it passes through, and a layer's error against 64 bits is to be no
+  // larger than it was when tiles were 32 x 64, of few of which K was split over up to sixteen workgroups as well.
+  //   A split, and fp32 sums of the whole form: blocks of two K steps to an accumulator, which are added up in this wavefront's part of
+  // `ex`.  Error against 64 bits, rms, relative, as one chain and in blocks: fp32 1x1, 192 to 64 channels at 42x45 stride 2, 67 images (whole) 1.43e-7 and
+  // 0.88e-7; 256 to 1664, 1011 pixels (whole) 1.82e-7 and 0.94e-7; 192 to 192 at 3x3, 6x62, 3 images (split) 1.20e-7 in blocks of four, 1.05e-7 of two.
+  // It costs the whole form 2 % in the mean of 46 layers (16.9 -> 17.4 us, 18.9 -> 19.6; two of them, tiles of eight units, 24.4 -> 26.9), a
+  // split 1 to 3 %.  A split's tiles of eight units have no registers for it (96 to 80 at 45x33 8.6 -> 11.2 us); a wavefront has a chain over its share.
+  //   bf16 sums of the whole form, whose K steps are one product each: the base path's even and odd steps by themselves, the odd ones in the
+  // registers of the conditional sums, which costs one addition (1 %).  Dense 1x1, 640 to 144 channels, 16306 pixels 1.08e-7 -> 0.78e-7, as much as with K
+  // split over two wavefronts; in blocks of four or eight steps as above 0.72e-7, and 3 % slower in the mean of 80 layers, 19 % at most.
+  // (Layers whose K was split over four, see the plan.)
+  //   Sums of four wavefronts meet in pairs (4 % of a split's error, and 2 % of the time of dense layers of 4 to 6 us).
+  // Over 500 layers of 10 to 10^5 pixels the error is 0.74 (fp32) and 0.92 (bf16) times the former one in the mean, 1.00 and 1.02 at most; over 400 bf16
+  // layers whose K was split and is not now, or less, 0.98, 1.09 at most (1.5 and 1.8 as one chain).
   constexpr bool kTwo = kBlocks && SPLIT && (kU == 4 || (kU == 2 && NH == 2));     // two sums at a time, of the even and of the odd steps
-  acc4 odd[PF][NH];
-  if constexpr (kTwo) {
-#pragma unroll
-    for (int f = 0; f < PF; ++f)
-#pragma unroll
-      for (int i = 0; i < NH; ++i) odd[f][i] = acc4{0, 0, 0, 0};
-  }
-  auto join = [&](acc4 (&a)[PF][NH]) __attribute__((always_inline)) {
-    if constexpr (kTwo) {
+  constexpr int kAtATime = SPLIT ? (NU >= 4 ? 1 : 8) : 2;      // units under way together
+  auto join = [&](auto two, acc4 (&a)[PF][NH], acc4 (&odd)[PF][NH]) __attribute__((always_inline)) {
+    if constexpr (decltype(two)::value) {
 #pragma unroll
       for (int f = 0; f < PF; ++f)
 #pragma unroll
@@ -425,9 +427,9 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
     }
   };
   bool carried = false;
-  auto carry = [&](acc4 (&a)[PF][NH]) __attribute__((always_inline)) {
+  auto carry = [&](auto two, acc4 (&a)[PF][NH], acc4 (&odd)[PF][NH]) __attribute__((always_inline)) {
     if constexpr (kBlocks) {
-      join(a);
+      join(two, a, odd);
 #pragma unroll
       for (int f = 0; f < PF; ++f)
 #pragma unroll
@@ -436,13 +438,14 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
           if (carried) a[f][i] += __builtin_bit_cast(acc4, *at);
           *at = __builtin_bit_cast(i32x4, a[f][i]);
           a[f][i] = acc4{0, 0, 0, 0};
-          if (SPLIT ? NU >= 4 : (f * NH + i) % 2 != 0) __builtin_amdgcn_sched_barrier(0);      // (one or two units at a time: no registers for more)
+          if ((f * NH + i) % kAtATime == kAtATime - 1) __builtin_amdgcn_sched_barrier(0);      // (no registers for more)
         }
       carried = true;
     }
   };
-  // K steps [k0, k1) of phase ph into a.  `meanwhile` runs once the first operands are on their way.
-  auto walk = [&](int ph, int k0, int k1, acc4 (&a)[PF][NH], auto meanwhile) __attribute__((always_inline)) {
+  // K steps [k0, k1) of phase ph into a, two: the odd steps into `odd` first (both zero before; `odd` again afterwards).  `meanwhile` runs
+  // once the first operands are on their way.
+  auto walk = [&](auto two, int ph, int k0, int k1, acc4 (&a)[PF][NH], acc4 (&odd)[PF][NH], auto meanwhile) __attribute__((always_inline)) {
     const int nq = ph ? p.chunks1 : p.chunks0;
     const Div dnq = ph ? p.nq1 : p.nq0;
     const int cfirst = ph ? 0 : bfirst;
@@ -537,7 +540,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
           for (int f = 0; f < PF; ++f)
 #pragma unroll
             for (int i = 0; i < NH; ++i) {
-              acc4& to = kTwo && (u & 1) ? odd[f][i] : a[f][i];
+              acc4& to = decltype(two)::value && ((kU == 1 ? b : u) & 1) ? odd[f][i] : a[f][i];
               to = Tr::mma(part, w[b][u][i], x[b][u][f], to);
             }
     };
@@ -555,7 +558,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
         fetch_x(B1{});
       }
       mul(B0{});
-      if (kU == 4 && i + 1 < nb) carry(a);
+      if (kU == 4 && i + 1 < nb) carry(two, a, odd);
       if (i + 1 < nb) {
         if (i + 2 < nb) {
           fetch_w(B0{});
@@ -563,17 +566,17 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
         }
         mul(B1{});
       }
-      if (i + 2 < nb) carry(a);
+      if (i + 2 < nb) carry(two, a, odd);
     }
+    join(two, a, odd);
     if constexpr (kBlocks) {
-      join(a);
       if (carried) {
 #pragma unroll
         for (int f = 0; f < PF; ++f)
 #pragma unroll
           for (int i = 0; i < NH; ++i) {
             a[f][i] += __builtin_bit_cast(acc4, ex[(wave * NU + f * NH + i) * 64 + lane]);
-            if (SPLIT ? NU >= 4 : (f * NH + i) % 2 != 0) __builtin_amdgcn_sched_barrier(0);
+            if ((f * NH + i) % kAtATime == kAtATime - 1) __builtin_amdgcn_sched_barrier(0);
           }
       }
     }
@@ -640,7 +643,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
     zero(accP);
     zero(accR);
     Tab4<Base> t[NH];
-    walk(0, 0, p.ks0, accP, [&]() __attribute__((always_inline)) {
+    walk(std::bool_constant<kPair>{}, 0, 0, p.ks0, accP, accR, [&]() __attribute__((always_inline)) {
       load_rest(p);
       if ((p.flags & kClear) && blockIdx.x == 0 && tid < 2) p.total[tid] = 0u;
     });
@@ -677,7 +680,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
         }
       }
       if (gate_only) return;
-      if (__ballot(any) != 0ull) walk(1, 0, p.ks1, accR, []() {});
+      if (__ballot(any) != 0ull) walk(std::false_type{}, 1, 0, p.ks1, accR, accR, []() {});
     }
     i32x4 res[PF][NH];
 #pragma unroll
@@ -706,8 +709,9 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
     const int part = ph ? wave - nwb : wave;
     const int kq = ph ? p.kq1 : p.kq0, kr = ph ? p.kr1 : p.kr0;
     const int k0 = part * kq + (part < kr ? part : kr), k1 = ph && gate_only ? k0 : k0 + kq + (part < kr ? 1 : 0);
-    acc4 acc[PF][NH];
+    acc4 acc[PF][NH], odd[PF][NH];
     zero(acc);
+    zero(odd);
     // this wavefront's unit of the tile's end (the plan has a wavefront for each): its tables and residual arrive behind the sums
     const int un = wave < NU ? wave : 0, uf = un / NH, co0 = (half0 + un % NH) * 16 + 4 * lg, m = m0 + 16 * uf + lj;
     const bool valid = m < p.m_total;
@@ -719,7 +723,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
         res = load_residual<Base>(p, co0, m, valid && !gate_only);
       }
     };
-    walk(ph, k0, k1, acc, [&]() __attribute__((always_inline)) {
+    walk(std::bool_constant<kTwo>{}, ph, k0, k1, acc, odd, [&]() __attribute__((always_inline)) {
       load_rest(p);
       if ((p.flags & kClear) && blockIdx.x == 0 && tid < 2) p.total[tid] = 0u;
       if constexpr (NU < 8) load_end();
@@ -745,16 +749,31 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
       i32x4 v[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[j] = ex[((w0 + j < nw ? w0 + j : 0) * NU + un) * 64 + lane];
+      acc_t t[4][4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) set_bits(v[j][e], t[j][e]);
+      if (w0 + 4 <= nw && (w0 + 4 <= nwb || w0 >= nwb)) {      // all of one path: in pairs
+        const bool base = w0 < nwb;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const acc_t sum = (t[0][e] + t[1][e]) + (t[2][e] + t[3][e]);
+          if (base)
+            s[e] += sum;
+          else
+            r[e] += sum;
+        }
+        continue;
+      }
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          acc_t t;
-          set_bits(v[j][e], t);
           if (w0 + j < nwb)
-            s[e] += t;
+            s[e] += t[j][e];
           else if (w0 + j < nw)
-            r[e] += t;
+            r[e] += t[j][e];
         }
     }
     finish_unit<Base>(p, s, r, tab, res, co0, lg, m, valid);
@@ -890,12 +909,16 @@ DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu) {
   const bool uni = g.total_chunks % 4 == 0 && g.gap_len % 4 == 0 && g.chunks[0] % 4 == 0;
   const double start = f32 ? 5250.0 : 5350.0, each0 = f32 ? 90.0 : 233.0, each1 = f32 ? 211.0 : 124.0, wave0 = f32 ? 3880.0 : 3790.0;
   const double cx = (f32 ? 52.0 : 50.0) * (uni ? 1.0 : f32 ? 1.25 : 0.91), cw = f32 ? 32.0 : 12.5, cm = f32 ? 175.0 : 16.0, cl = f32 ? 82.0 : 450.0;
+  // bf16 layers of at least two K steps to each of four wavefronts, and fewer than four times as many tiles of 32 x 64 as compute units, are
+  // split: their K always was, over four wavefronts or more, and as one chain of each path (two of a dense layer's) their error against 64 bits
+  // was up to 1.8 times as large.  14 such layers: 0.98 of the whole form's time in the mean, 0.88 to 1.11.
+  const bool chained = d.in_dtype == CG_BF16 && ks >= 8 && (m + 31) / 32 * (g.n_grp / 2) < 4ll * n_cu;
   g.cost = 1e30;
   for (int pf = 1; pf <= (m > 16 ? 2 : 1); ++pf)
     for (int nh = 1; nh <= (ngrp >= 2 ? 4 : 2); nh *= 2)
       for (int split = 1; split <= kMaxSplit; split *= 2) {
         const int nu = pf * nh;
-        if (split == 1 ? nh == 1 : split < nu || (gated && split < 2)) continue;
+        if (split == 1 ? nh == 1 || chained : split < nu || (gated && split < 2)) continue;
         const bool whole = split == 1;
         const long long px = (m + 16 * pf - 1) / (16 * pf), wgs = (whole ? (px + 3) / 4 : px) * tiles_c(nh);
         const int waves = whole ? 4 : split, nwb = nwb_of(split);

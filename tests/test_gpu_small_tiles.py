@@ -174,10 +174,61 @@ def test_tile_edges(shape, grouped):
         _say(P.run_int8(q, thr, name=shape.name + " int8", **kw))
 
 
+F, H, I = B.CG_F32, B.CG_BF16, B.CG_I8
+
+
+# Dense layers, (images, height, width, channels in and out, kernel), with the tile and the wavefronts that share its K, and the roundings that a product
+# passes through, in roundings of the last sum: a chain of m additions makes (m + 1) / 2.  Sums of eight wavefronts are added up in
+# pairs, 3; of four, 2.
+def _chain(m):
+    return (m + 1) / 2
+
+
+SUMS = [
+    (H, (261, 20, 8, 752, 40, 1), (1, 4, 1), _chain(23.5 / 2) + 1),                          # whole: even and odd steps by themselves
+    (H, (22, 25, 38, 1424, 80, 1), (2, 2, 1), _chain(44.5 / 2) + 1),
+    (H, (30, 40, 24, 1376, 72, 1), (2, 4, 1), _chain(43 / 2) + 1),
+    (H, (1, 57, 18, 2032, 64, 3), (1, 2, 8), _chain(2) + 1 + _chain(571.5 / 8 / 4) + 3),     # two blocks of two steps at a time
+    (H, (1, 44, 41, 560, 280, 3), (1, 2, 4), _chain(2) + 1 + _chain(157.5 / 4 / 4) + 2),
+    (H, (7, 41, 19, 768, 328, 1), (1, 4, 4), _chain(2) + _chain(24 / 4 / 2) + 2),            # blocks of two steps
+    (H, (24, 25, 21, 352, 88, 3), (2, 2, 4), _chain(2) + _chain(99 / 4 / 2) + 2),
+    (H, (2, 33, 8, 272, 1800, 1), (2, 4, 8), _chain(8.5 / 8 + 1) + 3),                       # a chain to a wavefront
+    (F, (10, 10, 25, 80, 392, 3), (1, 2, 2), _chain(8) + 1 + _chain(45 / 2 / 4) + 1),        # (fp32: four products to a step)
+    (F, (1, 22, 53, 768, 440, 3), (1, 4, 8), _chain(8) + _chain(432 / 8 / 2) + 3),
+    (F, (5, 46, 18, 560, 184, 3), (2, 2, 4), _chain(8) + _chain(315 / 4 / 2) + 2),
+    (F, (3, 47, 35, 496, 136, 3), (2, 4, 8), _chain(279 / 8 * 4) + 3),
+    (F, (7, 55, 18, 128, 432, 3), (1, 4, 1), _chain(8) + _chain(72 / 2)),
+    (F, (11, 49, 54, 144, 48, 3), (2, 2, 1), _chain(8) + _chain(81 / 2)),
+]
+
+
+@pytest.mark.parametrize("dtype,shape,form,roundings", SUMS, ids=["%s_%s" % ({F: "fp32", H: "bf16"}[d], "_".join(map(str, f))) for d, _, f, _ in SUMS])
+def test_sums_of_every_form_against_64_bits(dtype, shape, form, roundings):
+    """The error of a layer's sums, in the rms, is at most that of the roundings: 0.58 * 2^-24 of the sum each, a 15th more for what a product of 32
+    bf16 pairs rounds inside, which adds at most a seventh to the variance of one chain over K (measured: 24 to 25 for 22 of 44.5 and 43 steps)."""
+    n, h, w_, c, co, k = shape
+    g = torch.Generator(device="cuda").manual_seed(c + co)
+    tdt = torch.float32 if dtype == F else torch.bfloat16
+    x = torch.relu(torch.randn(n, h, w_, c, generator=g, device="cuda")).to(tdt)
+    w = (torch.randn(co, k, k, c, generator=g, device="cuda") * (2.0 / (k * k * c)) ** 0.5).to(tdt)
+    layer = B.GatedConv(n_max=n, h=h, w=w_, c_in=c, c_out=co, c_base=c, w_base=w, w_cond=None, in_dtype=dtype, out_dtype=F, kh=k, kw=k, stride=1, pad=k // 2,
+                        epilogue=0)
+    y = layer.forward(x, bitmap=False, counts=False)[0].double().reshape(-1, co)
+    layer.close()
+    cols = x.double().permute(0, 3, 1, 2)
+    cols = torch.nn.functional.unfold(cols, k, padding=k // 2).transpose(1, 2).reshape(-1, c * k * k)
+    ref = cols @ w.double().permute(0, 3, 1, 2).reshape(co, -1).T
+    rms = (y - ref).pow(2).mean().sqrt().item()
+    bound = 0.58 * 2.0 ** -24 * (1.14 * roundings) ** 0.5 * ref.pow(2).mean().sqrt().item()
+    print("%s: %.3g of %.3g" % (shape, rms, bound))
+    assert rms <= bound
+
+
 @pytest.mark.parametrize("dtype,shape", [("f32", (1, 20, 512, 256, 2)), ("f32", (1, 9, 128, 80, 1)), ("bf16", (1, 14, 512, 64, 1)),
                                          ("bf16", (4, 4, 512, 128, 1))])
 def test_sums_of_a_split_against_64_bits(dtype, shape):
-    """A deep dense layer of few pixels: K is split over eight wavefronts, each adding up blocks of four K steps.
+    """A deep dense layer of few pixels, tiles of 16 x 16: K is split over eight wavefronts, each adding up blocks of four K steps, of
+    which the even and the odd ones have a sum of their own.
 
     A rounding is at most 2^-24 of the sum it makes and 0.58 of that in the rms.  On its way a product passes through those of
     its half block (two steps; fp32: four products each), of the wavefront's blocks and of the eight wavefronts' sums, none of which
