@@ -413,7 +413,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
   //   Sums of four wavefronts meet in pairs (4 % of a split's error, and 2 % of the time of dense layers of 4 to 6 us).
   // Over 500 layers of 10 to 10^5 pixels the error is 0.74 (fp32) and 0.92 (bf16) times the former one in the mean, 1.00 and 1.02 at most; over 400 bf16
   // layers whose K was split and is not now, or less, 0.98, 1.09 at most (1.5 and 1.8 as one chain).
-  constexpr bool kTwo = kBlocks && SPLIT && (kU == 4 || (kU == 2 && NH == 2));     // two sums at a time, of the even and of the odd steps
+  constexpr bool kTwo = kBlocks && SPLIT && kU > 1;     // two sums at a time, of the even and of the odd steps
   constexpr int kAtATime = SPLIT ? (NU >= 4 ? 1 : 8) : 2;      // units under way together
   auto join = [&](auto two, acc4 (&a)[PF][NH], acc4 (&odd)[PF][NH]) __attribute__((always_inline)) {
     if constexpr (decltype(two)::value) {
@@ -840,7 +840,6 @@ hipError_t launch_direct_dtype(const DirectPlan& g, const DirectArgs& a, hipStre
   switch (g.pf * 8 + g.nh) {
     case 2 * 8 + 4: return launch_direct_tile<Tr, 2, 4>(g, a, s);
     case 2 * 8 + 2: return launch_direct_tile<Tr, 2, 2>(g, a, s);
-    case 2 * 8 + 1: return launch_direct_tile<Tr, 2, 1>(g, a, s);
     case 1 * 8 + 4: return launch_direct_tile<Tr, 1, 4>(g, a, s);
     case 1 * 8 + 2: return launch_direct_tile<Tr, 1, 2>(g, a, s);
     case 1 * 8 + 1: return launch_direct_tile<Tr, 1, 1>(g, a, s);
@@ -915,7 +914,7 @@ DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu) {
   const bool chained = d.in_dtype == CG_BF16 && ks >= 8 && (m + 31) / 32 * (g.n_grp / 2) < 4ll * n_cu;
   g.cost = 1e30;
   for (int pf = 1; pf <= (m > 16 ? 2 : 1); ++pf)
-    for (int nh = 1; nh <= (ngrp >= 2 ? 4 : 2); nh *= 2)
+    for (int nh = pf; nh <= (ngrp >= 2 ? 4 : 2); nh *= 2)           // (32 x 16 pixels and channels were never the least)
       for (int split = 1; split <= kMaxSplit; split *= 2) {
         const int nu = pf * nh;
         if (split == 1 ? nh == 1 || chained : split < nu || (gated && split < 2)) continue;
