@@ -1,0 +1,106 @@
+// Which kernel a forward call launches, without a GPU: this program defines the HIP runtime calls the library makes, which the
+// loader finds before the runtime's own, keeps the kernels' names as they are registered and "launches" nothing.
+// One layer a line on standard input: in_dtype out_dtype n_max n h w c_in c_out c_base k stride pad groups shuffle epilogue
+// variant rq_shift; a line with the kernel's name and its threads to a workgroup for each.  Run by tests/test_kernels_of_calls_cpu.py.
+#include <cxxabi.h>
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <limits>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "cg_conv.h"
+
+static std::map<const void*, std::string>& names() {      // (the library registers its kernels before main)
+  static std::map<const void*, std::string> m;
+  return m;
+}
+struct Launch { const void* kernel; unsigned threads; };
+static std::vector<Launch> launches;
+static dim3 config_block;
+
+extern "C" {
+void** __hipRegisterFatBinary(const void*) {
+  static void* handle[16];
+  return handle;
+}
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* device, unsigned, void*, void*, void*, void*, int*) {
+  int status = 0;
+  char* d = abi::__cxa_demangle(device, nullptr, nullptr, &status);
+  names()[host] = status == 0 && d ? d : device;
+  std::free(d);
+}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
+  *v = a == hipDeviceAttributeMultiprocessorCount ? 256 : 0;
+  return hipSuccess;
+}
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void*) { *p = (void*)0x700000000000ull; return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) { *p = std::calloc(1, bytes); return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3, dim3 block, size_t, hipStream_t) {
+  config_block = block;
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* s) {
+  *grid = *block = dim3(1);
+  *lds = 0;
+  *s = nullptr;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t) {
+  launches.push_back({f, config_block.x});
+  return hipSuccess;
+}
+}
+
+int main() {
+  int in_dtype, out_dtype, n_max, n, h, w, c_in, c_out, c_base, k, stride, pad, groups, shuffle, variant, rq_shift;
+  unsigned epilogue;
+  while (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %u %d %d", &in_dtype, &out_dtype, &n_max, &n, &h, &w, &c_in, &c_out, &c_base, &k,
+                    &stride, &pad, &groups, &shuffle, &epilogue, &variant, &rq_shift) == 17) {
+    const std::vector<float> zero(c_out, 0.0f), one(c_out, 1.0f);
+    const std::vector<int32_t> thr(c_out, 0);
+    cg_conv_desc d;
+    std::memset(&d, 0, sizeof d);
+    d.struct_size = sizeof d;
+    d.n_max = n_max; d.h = h; d.w = w; d.c_in = c_in; d.c_out = c_out; d.c_base = c_base; d.kh = d.kw = k; d.stride = stride; d.pad = pad;
+    d.in_dtype = in_dtype; d.out_dtype = out_dtype; d.epilogue = epilogue; d.variant = variant; d.groups = groups; d.shuffle = shuffle;
+    d.rq_shift = rq_shift;
+    if (in_dtype == CG_I8) {
+      d.gate_thr_i32 = thr.data();
+    } else {
+      d.gate_mean = d.delta = zero.data();
+      d.gate_var = one.data();
+    }
+    d.w_base = (const void*)0x1000;
+    d.w_cond = c_base < c_in ? (const void*)0x2000 : nullptr;
+    d.packed = (void*)0x100000;
+    d.packed_bytes = cg_conv_packed_bytes(&d);
+    cg_conv* layer = nullptr;
+    const char* said = "";
+    launches.clear();
+    if (cg_conv_create(&layer, &d, nullptr) != CG_OK) {
+      said = cg_last_error();
+    } else {
+      launches.clear();
+      if (cg_conv_forward(layer, n, (void*)0x200000000ull, (epilogue & CG_EPI_RESIDUAL) ? (void*)0x600000000ull : nullptr, (void*)0x300000000ull,
+                          nullptr, nullptr, (void*)0x500000000ull, cg_conv_workspace_bytes(layer, n), nullptr) != CG_OK)
+        said = cg_last_error();
+      cg_conv_destroy(layer);
+    }
+    if (launches.empty())
+      std::printf("none: %s\n", said);
+    else
+      std::printf("%s %u\n", names()[launches[0].kernel].c_str(), launches[0].threads);
+  }
+  return 0;
+}

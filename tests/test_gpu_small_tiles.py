@@ -174,7 +174,42 @@ def test_tile_edges(shape, grouped):
         _say(P.run_int8(q, thr, name=shape.name + " int8", **kw))
 
 
+# The forms that the layers above do not run in, a layer for up to three types: tile (16 pixels, 16 channels), whether K is split.  Pixels and
+# channels end inside a tile.  (tests/test_kernels_of_calls_cpu.py checks that they run in these forms.)
 F, H, I = B.CG_F32, B.CG_BF16, B.CG_I8
+TILES = [
+    (S(1, 28, 39, 16, 35, k=1, pad=0, groups=2), False, {F: (1, 2, True), H: (1, 2, True), I: (1, 2, True)}),
+    (S(173, 15, 1, 48, 33, k=1, pad=0, groups=2), False, {F: (1, 4, True), H: (1, 4, True), I: (1, 4, True)}),
+    (S(904, 1, 19, 16, 39, k=1, pad=0, groups=2), False, {F: (1, 2, False), H: (2, 4, False), I: (2, 4, False)}),
+    (S(1269, 1, 13, 16, 72, k=1, pad=0), False, {F: (2, 2, False), H: (2, 2, False), I: (2, 2, False)}),
+    (S(62, 9, 39, 16, 83, k=1, pad=0, groups=2), False, {H: (1, 2, False), I: (1, 2, False)}),
+    (S(19, 39, 27, 16, 133, k=1, pad=0, groups=2), False, {F: (2, 4, False)}),
+    (S(11, 38, 36, 96, 35, k=1, pad=0, groups=2), False, {F: (2, 4, True)}),
+    (S(40, 33, 31, 16, 64), False, {F: (1, 4, False), H: (1, 4, False), I: (1, 4, False)}),
+    (S(60, 12, 12, 32, 80), False, {F: (2, 2, True), H: (2, 2, True), I: (2, 2, True)}),
+    (S(5, 45, 33, 96, 80), False, {H: (2, 4, True), I: (2, 4, True)}),
+    (S(19, 4, 27, 16, 18, groups=2), True, {F: (1, 2, True), H: (1, 2, True)}),
+    (S(3, 12, 19, 16, 692, stride=2), True, {F: (1, 4, True), H: (1, 4, True)}),
+    (S(158, 38, 3, 16, 74, groups=2), True, {F: (2, 2, False), H: (2, 2, False)}),
+    (S(45, 40, 15, 16, 100), True, {F: (2, 4, False), H: (2, 4, False)}),
+    (S(13, 40, 34, 16, 172, stride=2), True, {F: (2, 4, True)}),
+    (S(527, 6, 4, 16, 100), True, {F: (1, 4, False)}),
+    (S(49, 15, 6, 16, 344), True, {F: (1, 2, False)}),
+    (S(1698, 1, 52, 8, 10, k=1, pad=0, stride=2, groups=2), True, {H: (1, 2, False)}),
+]
+
+
+@pytest.mark.parametrize("shape,grouped,forms", TILES, ids=[t[0].name + ("_grouped" if t[1] else "") for t in TILES])
+def test_every_tile(shape, grouped, forms):
+    inp = W.make_inputs(shape, 7500 + shape.c_out + shape.h, kind="iid", rho=0.3, round_bf16=True, grouped=grouped)
+    gate = W.calibrate_gate(inp, 0.3, sample_images=None)
+    for dtype in (F, H):
+        if dtype in forms:
+            _say(P.run_float(inp, gate, in_dtype=dtype, out_dtype=dtype, shuffle=grouped, name="%s %s" % (shape.name, forms[dtype])))
+    if I in forms:
+        q = W.quantize_int8(W.make_inputs(shape, 7600 + shape.c_out + shape.h, kind="iid", rho=0.35, grouped=grouped))
+        thr = W.calibrate_gate_int8(q, 0.35, sample_images=None)
+        _say(P.run_int8(q, thr, shuffle=grouped, name="%s int8 %s" % (shape.name, forms[I])))
 
 
 # Dense layers, (images, height, width, channels in and out, kernel), with the tile and the wavefronts that share its K, and the roundings that a product

@@ -1,0 +1,62 @@
+"""That the layers of the GPU tests run on the kernels, and in the forms, which those tests are there for: the choice of kernel and plan is the
+library's own, asked for through forward calls without a GPU."""
+import pytest
+
+from paper_1805_12549_amd import binding as B
+from tests import kernels_of_calls as K
+from tests import test_gpu_nan_outputs as nan_outputs
+from tests import test_gpu_small_tiles as small_tiles
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    path = K.build(tmp_path_factory.mktemp("driver"))
+    if path is None:
+        pytest.skip("needs hipcc and the built library")
+    return path
+
+
+def _layer(dtype, s, grouped=False):
+    return K.layer(dtype, s.n, s.h, s.w, s.c_in, s.c_out, c_base=s.c_base, k=s.k, stride=s.stride, pad=s.pad, groups=s.groups if grouped else 0,
+                   shuffle=grouped, out_dtype=dtype if dtype != B.CG_I8 else None)
+
+
+TYPE = {B.CG_F32: "F32Direct", B.CG_BF16: "Bf16Direct", B.CG_I8: "I8Direct"}
+
+
+def test_small_tile_forms(exe):
+    seen = set()
+    for shape, grouped, forms in small_tiles.TILES:
+        for dtype, (pf, nh, split) in forms.items():
+            kernel, args, _ = K.ask(exe, [_layer(dtype, shape, grouped)])[0]
+            assert (kernel, args) == ("gated_conv_direct_kernel", (TYPE[dtype], str(pf), str(nh), str(split).lower(), str(grouped).lower())), shape
+            seen.add(args)
+    for shape in small_tiles.FORMS + small_tiles.SHAPES:
+        for dtype, ch in ((B.CG_F32, 4), (B.CG_BF16, 8), (B.CG_I8, 16)):
+            for grouped in (False, True):
+                if shape.c_in % ch == 0 and not (grouped and (shape.c_out % shape.groups or shape.k != 3)):
+                    seen.add(K.ask(exe, [_layer(dtype, shape, grouped)])[0][1])
+    tiles = [("1", "1", "true")] + [(pf, nh, split) for pf, nh in (("1", "2"), ("1", "4"), ("2", "2"), ("2", "4")) for split in ("true", "false")]
+    missing = [(TYPE[d],) + t + (mixed,) for d in TYPE for t in tiles for mixed in ("false", "true")
+               if (TYPE[d],) + t + (mixed,) not in seen and not (mixed == "true" and d == B.CG_I8)]
+    assert not missing
+
+
+def test_forms_of_the_sums(exe):
+    for dtype, (n, h, w, c, co, k), (pf, nh, waves), _ in small_tiles.SUMS:
+        kernel, args, threads = K.ask(exe, [K.layer(dtype, n, h, w, c, co, k=k)])[0]
+        assert (kernel, args[:4]) == ("gated_conv_direct_kernel", (TYPE[dtype], str(pf), str(nh), str(waves > 1).lower())), (dtype, n, h, w, c, co, k)
+        assert threads == (64 * waves if waves > 1 else 256), (dtype, n, h, w, c, co, k)
+
+
+def test_layers_of_the_nan_test(exe):
+    want = [("gated_conv_rows_kernel", ("1", "9", "0")), ("gated_conv_rows_kernel", ("1", "9", "1")), ("gated_conv_rows_kernel", ("2", "9", "0")),
+            ("gated_conv_rows_kernel", ("1", "1", "0")), ("gated_conv_tile_kernel", None), ("gated_conv_tile_kernel", None),
+            ("gated_conv_direct_kernel", ("true",)), ("gated_conv_direct_kernel", ("false",)), ("naive_kernel", None)]
+    for (variant, n, hw, c, k), (kernel, args) in zip(nan_outputs.LAYERS, want):
+        got = K.ask(exe, [K.layer(B.CG_BF16, n, hw, hw, c, c, c_base=c // 4, k=k, out_dtype=B.CG_BF16, variant=variant)])[0]
+        assert got[0] == kernel, (variant, n, hw, c, k)
+        if kernel == "gated_conv_rows_kernel":
+            assert got[1][2:] == args, (variant, n, hw, c, k)
+        elif kernel == "gated_conv_direct_kernel":
+            assert got[1][3] == args[0], (variant, n, hw, c, k)
