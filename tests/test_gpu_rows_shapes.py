@@ -7,6 +7,7 @@ import torch
 from paper_1805_12549_amd import binding as B
 from paper_1805_12549_amd import workloads as W
 from tests import parity as P
+from tests.test_gpu_requantise import fits_32_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -163,9 +164,10 @@ def test_two_wavefronts_to_a_fragment(shape):
     q = W.quantize_int8(W.make_inputs(shape, 9700 + shape.h, kind="coherent", rho=0.35))
     thr = W.calibrate_gate_int8(q, 0.35, sample_images=None)
     r8 = rng.integers(-128, 128, (shape.n, shape.ho, shape.wo, c)).astype(np.int8)
-    for hi, shift in ((200, 14), (1 << 20, 24)):                     # the requantisation in 32 bits and in 64
-        rq = dict(rq_mult0=rng.integers(-hi, hi, c).astype(np.int32), rq_mult1=rng.integers(-hi, hi, c).astype(np.int32),
+    for lo, hi, shift, fits in ((-200, 200, 14, False), (-(1 << 20), 1 << 20, 24, False), (20, 200, 14, True)):      # in 64 bits and in 32
+        rq = dict(rq_mult0=rng.integers(lo, hi, c).astype(np.int32), rq_mult1=rng.integers(lo, hi, c).astype(np.int32),
                   rq_bias=rng.integers(-hi, hi, c).astype(np.int32), rq_shift=shift)
+        assert fits_32_bits(rq, hi // 2, True) == fits_32_bits(rq, 0, False) == fits
         P.run_int8(q, thr, out_i8=True, rq=rq, epilogue=B.CG_EPI_RELU, variant=B.CG_VARIANT_MFMA_ROWS, name=shape.name)
         P.run_int8(q, thr, out_i8=True, rq=rq, residual=r8, rq_res_mult=hi // 2, epilogue=B.CG_EPI_RESIDUAL, variant=B.CG_VARIANT_MFMA_ROWS,
                    name=shape.name)
