@@ -46,7 +46,7 @@ __device__ __forceinline__ unsigned long long sum32(uint32_t v) {
 }
 
 // x / d with magic = ceil(2^32 / d), or 0: divide
-__device__ __forceinline__ unsigned quot(unsigned x, unsigned d, unsigned magic) { return magic ? __umulhi(x, magic) : x / d; }
+__device__ __forceinline__ unsigned divide(unsigned x, unsigned d, unsigned magic) { return magic ? __umulhi(x, magic) : x / d; }
 
 // `wpi` wavefronts share an item (1: no exchange needed, WIDE = false); G groups of 64 pixels at a time
 template <int G, bool WIDE>
@@ -63,7 +63,7 @@ __global__ void bitmap_counts_kernel(const uint32_t* __restrict__ bitmap, int wo
   __syncthreads();
   unsigned long long total = 0ull;
   for (unsigned i0 = blockIdx.x * per; i0 < items; i0 += gridDim.x * per) {      // (items < 2^31: see launch_count)
-    const unsigned item = i0 + mine, img = quot(item, words, magic), w = item - img * words;
+    const unsigned item = i0 + mine, img = divide(item, words, magic), w = item - img * words;
     uint32_t n = 0u;
     if (item < items) {
       const uint32_t* const src = bitmap + (size_t)img * hw * words + w;

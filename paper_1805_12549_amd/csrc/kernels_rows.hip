@@ -56,7 +56,7 @@
 // SIMD, take a fragment, each with 32 of the block's channels, and one's LDS reads, gate and output run under the other's
 // products.  Alone on its SIMD a wavefront took half as long again as its products.  us before and after: 256 channels at 8x8, 128 images 15.7 ->
 // 15.1, 64 at 56x56, 8 images 8.1 -> 7.6, 128 at 16x16, 32 images 9.1 -> 8.6, int8 256 at 14x14, 32 images 10.5 -> 9.8, 512 at
-// 7x7, 64 images 15.3 -> 14.6; slower 256 at 14x14, 32 images 13.5 -> 13.8.  A stage still takes 1100 clocks at 256 channels where its
+// 7x7, 64 images 15.3 -> 14.6; 256 at 14x14 by the images, 16 12.0 -> 11.4, 24 12.4 -> 12.2, slower 28 to 40 (32 13.1 -> 13.3, 40 13.7 -> 14.1).  A stage still takes 1100 clocks at 256 channels where its
 // products take 576, its loads 710 (a 1 KB load is 20 clocks of the memory path, 32 where it is made of pieces of 32 bytes)
 // and its LDS accesses 800.
 //
