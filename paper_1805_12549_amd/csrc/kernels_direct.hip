@@ -408,10 +408,10 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
   // split 1 to 3 %.  A split's tiles of eight units have no registers for it (96 to 80 at 45x33 8.6 -> 11.2 us); a wavefront has a chain over its share.
   //   bf16 sums of the whole form, whose K steps are one product each: the base path's even and odd steps by themselves, the odd ones in the
   // registers of the conditional sums, which costs one addition (1 %).  Dense 1x1, 640 to 144 channels, 16306 pixels 1.08e-7 -> 0.78e-7, as much as with K
-  // split over two wavefronts; in blocks of four or eight steps as above 0.72e-7, and 3 % slower in the mean of 80 layers, 19 % at most.
+  // split over two wavefronts.  (In blocks of four or eight steps as above 2 to 3 % slower in the mean of 80 layers, 19 % at most.)
   // (Layers whose K was split over four, see the plan.)
   //   Sums of four wavefronts meet in pairs (4 % of a split's error, and 2 % of the time of dense layers of 4 to 6 us).
-  // Over 500 layers of 10 to 10^5 pixels the error is 0.74 (fp32) and 0.92 (bf16) times the former one in the mean, 1.00 and 1.02 at most; over 400 bf16
+  // Over 1300 layers of 10 to 10^5 pixels the error is 0.75 (fp32) and 0.94 (bf16) times the former one in the mean, 1.01 and 1.02 at most; over 400 bf16
   // layers whose K was split and is not now, or less, 0.98, 1.09 at most (1.5 and 1.8 as one chain).
   constexpr bool kTwo = kBlocks && SPLIT && kU > 1;     // two sums at a time, of the even and of the odd steps
   constexpr int kAtATime = SPLIT ? (NU >= 4 ? 1 : 8) : 2;      // units under way together
