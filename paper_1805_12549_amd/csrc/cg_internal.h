@@ -123,9 +123,11 @@ struct DirectPlan {
   unsigned x_bytes;        // size of x
   // Channel chunks per tap and phase.  The base phase starts at the first chunk of the 64-channel block's
   // first group and walks chunks[0] of them; the conditional phase walks all chunks but the gap_len ones
-  // from there on.  strad: bytes of the base group in its last, partly used chunk (ungrouped layers).
-  int chunks[2], total_chunks, gap_len, strad;
+  // from there on.
+  int chunks[2], total_chunks, gap_len;
   int mixed;               // channel grouping: zero weights keep channels apart that a block walks together
+  int straddle;            // no grouping: so do they in the chunk in which the base group ends
+  int uniform;             // every K step lies inside one tap and on one side of the base group
   int ksteps[2];           // K steps (four chunks) per phase
   int n_grp;               // 32-channel groups of the packed weights
   size_t wpk_bytes[2];

@@ -82,9 +82,8 @@ __device__ __forceinline__ int bits_of(int v) { return v; }
 __device__ __forceinline__ void set_bits(int b, float& f) { f = __int_as_float(b); }
 __device__ __forceinline__ void set_bits(int b, int& v) { v = b; }
 
-// What the kernels read, in one piece: a wavefront's first instructions load what its addresses are made of and wait once
-// (argument by argument, in the order of use, the waits alone took over a microsecond of a six-microsecond kernel); what
-// the end of the layer needs is loaded behind the first operands (load_rest).
+// What the kernels read, in one piece: a wavefront's first instructions load all of it and wait once (argument by argument, in the
+// order of use, the waits alone took over a microsecond of a six-microsecond kernel).
 struct DirectArgs {
   const void* x;             // less x_bias: the offset of tap (0,0) of a pixel on the image's edge is not negative
   const char *w0, *w1;
@@ -92,8 +91,8 @@ struct DirectArgs {
   int m_total, h, w, xps, rowb;
   Div wo, ho, cblk, nq0, nq1, cpg;
   int n_wo, n_ho, n_cblk, n_cpg;
-  int stride, pad, taps, chunks0, chunks1, total_chunks, gap_len, strad, groups, c_base, ch_log;
-  int ks0, ks1, nwb, per_xcd, n_wgs;
+  int stride, pad, taps, chunks0, chunks1, total_chunks, gap_len, groups, c_base, ch_log;
+  int ks0, ks1, waves, nwb, per_xcd, n_wgs;
   int kq0, kr0, kq1, kr1;    // K steps of a part of either phase: kq, the first kr parts one more
   unsigned flags;
   // the end of the layer
@@ -110,7 +109,7 @@ enum : unsigned {
   kRelu = 1u, kAffine = 2u, kResidual = 4u,       // as CG_EPI_*
   kGated = 8u, kGateOnly = 16u, kClear = 32u, kShuffle = 64u,
   kOut4 = 128u,                                   // 4-byte outputs (CG_F32 / CG_I32)
-  kUni0 = 256u, kUni1 = 512u,                     // a K step of the phase lies inside one tap
+  kStraddle = 256u,                               // the base group ends inside a chunk
   kFit32 = 1024u,                                 // int8 -> int8: the requantisation fits 32 bits
 };
 
@@ -119,7 +118,7 @@ __device__ __forceinline__ void load_args(const DirectArgs& a) {
                "s"(a.rowb), "s"(a.wo.m), "s"(a.wo.s), "s"(a.ho.m), "s"(a.ho.s), "s"(a.cblk.m), "s"(a.cblk.s),
                "s"(a.n_wo), "s"(a.n_ho), "s"(a.n_cblk), "s"(a.stride), "s"(a.pad), "s"(a.taps));
   asm volatile("" ::"s"(a.nq0.m), "s"(a.nq0.s), "s"(a.nq1.m), "s"(a.nq1.s), "s"(a.chunks0), "s"(a.chunks1), "s"(a.total_chunks),
-               "s"(a.gap_len), "s"(a.strad), "s"(a.ks0), "s"(a.ks1), "s"(a.nwb), "s"(a.per_xcd), "s"(a.n_wgs), "s"(a.kq0), "s"(a.kr0),
+               "s"(a.gap_len), "s"(a.ks0), "s"(a.ks1), "s"(a.waves), "s"(a.nwb), "s"(a.per_xcd), "s"(a.n_wgs), "s"(a.kq0), "s"(a.kr0),
                "s"(a.kq1), "s"(a.kr1), "s"(a.flags));
 }
 __device__ __forceinline__ void load_rest(const DirectArgs& a) {
@@ -127,48 +126,60 @@ __device__ __forceinline__ void load_rest(const DirectArgs& a) {
                "s"(a.words), "s"(a.rq_shift), "s"(a.rq_res_mult));
 }
 
+constexpr int kTabs = 7;                         // tables that a layer's end reads
+
 // The per-channel tables of four channels, fetched ahead of the sums they are needed for.  (int8 layers whose requantisation
 // fits 32 bits: hi and h1 = bounds of the sum, s1 = what is added.)
 template <typename Base>
 struct Tab4 {
   i32x4 lo, hi, s0, h0, s1, h1;                  // int8 layers: s0 = mult0, h0 = mult1, s1 = bias
-  __device__ __forceinline__ void load(const DirectArgs& a, int co0) {
-    lo = hi = s0 = h0 = s1 = h1 = i32x4{0, 0, 0, 0};
-    if (co0 >= a.c_out) return;                  // (a table is padded to a multiple of 64 entries)
-    const char* t = a.tab + co0 * 4;
-    if (a.flags & kGated) {
-      lo = *(const i32x4*)t;
-      if constexpr (Base::kDtype != CG_I8) hi = *(const i32x4*)(t + a.tab_stride);
-    }
-    if (Base::kDtype == CG_I8 && (a.flags & kFit32)) {
-      hi = *(const i32x4*)(t + a.tab_stride);
-      s1 = *(const i32x4*)(t + 5 * a.tab_stride);
-      h1 = *(const i32x4*)(t + 6 * a.tab_stride);
-    }
-    if (Base::kDtype == CG_I8 ? !(a.flags & kOut4) : (a.flags & kAffine) != 0) {
-      s0 = *(const i32x4*)(t + 2 * a.tab_stride);
-      h0 = *(const i32x4*)(t + 3 * a.tab_stride);
-      if (!(Base::kDtype == CG_I8 && (a.flags & kFit32))) s1 = *(const i32x4*)(t + 4 * a.tab_stride);
-      if constexpr (Base::kDtype != CG_I8) h1 = *(const i32x4*)(t + 5 * a.tab_stride);
-    }
+  // from a copy of the tables' sixteen channels, four pieces a table; what a flag leaves out is not used
+  __device__ __forceinline__ void take(const DirectArgs& a, const i32x4* q) {
+    const bool fit = Base::kDtype == CG_I8 && (a.flags & kFit32);
+    lo = q[0];
+    hi = q[4];
+    s0 = q[8];
+    h0 = q[12];
+    s1 = q[fit ? 20 : 16];
+    h1 = q[fit ? 24 : 20];
   }
 };
 
+// The end of the layer is one wavefront's instructions with nothing beside them, so it is written without a branch on a lane's value: choices
+// by decision are selections of bits, and a flag of the layer is a branch that all lanes take.  (As conditional expressions and stores the
+// sums of eight wavefronts alone took 2400 clocks, a store to a channel 1500.)
+
+// the bits of a where m has ones, of b elsewhere
+__device__ __forceinline__ int select_bits(int m, int a, int b) { return (a & m) | (b & ~m); }
+// all ones where bit e of d is set
+__device__ __forceinline__ int ones_if(unsigned d, int e) { return (int)(d << (31 - e)) >> 31; }
+
+// the larger one; NaN as the second: the first
+__device__ __forceinline__ float max_of(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ int med3(int v, int lo, int hi) {
+  int r;
+  asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "v"(lo), "v"(hi));
+  return r;
+}
+
 // decisions of four consecutive channels from their base sums
 template <typename Base, typename acc_t>
-__device__ __forceinline__ unsigned gate4(const DirectArgs& a, const acc_t (&s)[4], const Tab4<Base>& t, int co0) {
+__device__ __forceinline__ unsigned gate4(const DirectArgs& a, const acc_t (&s)[4], i32x4 lo, i32x4 hi, int co0) {
   unsigned d = 0u;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     bool f;
     if constexpr (Base::kDtype == CG_I8)
-      f = Base::fires(s[e], t.lo[e], 0);
+      f = Base::fires(s[e], lo[e], 0);
     else
-      f = Base::fires(s[e], __int_as_float(t.lo[e]), __int_as_float(t.hi[e]));
-    d |= (f ? 1u : 0u) << e;
+      f = Base::fires(s[e], __int_as_float(lo[e]), __int_as_float(hi[e]));
+    d |= f ? 1u << e : 0u;
   }
-  const int left = a.c_out - co0;                // channels past the last one never fire
-  return left >= 4 ? d : left > 0 ? d & ((1u << left) - 1u) : 0u;
+  return d & ((1u << med3(a.c_out - co0, 0, 4)) - 1u);     // channels past the last one never fire
 }
 
 // Four consecutive channels co0.. of an output pixel are read and stored in one piece where c_out allows, else one by one.
@@ -212,87 +223,96 @@ __device__ __forceinline__ i32x4 load_residual(const DirectArgs& a, int co0, lon
   return r;
 }
 
-// Output function (f of Eq. 1) for four consecutive channels co0.. of output pixel m, decisions in d.
+// Output function (f of Eq. 1) for four consecutive channels co0.. of output pixel m: base and conditional sums, decisions in d; nothing is
+// stored where the pixel or the channels are past the end (live).
 template <typename Base, typename acc_t>
-__device__ __forceinline__ void finish4(const DirectArgs& a, const acc_t (&s)[4], const Tab4<Base>& t, i32x4 res, unsigned d, int co0,
-                                        long long m) {
-  if (co0 >= a.c_out) return;
-  const bool whole = one_piece(a);
+__device__ __forceinline__ void finish4(const DirectArgs& a, const acc_t (&base)[4], const acc_t (&cond)[4], const Tab4<Base>& t, i32x4 res, unsigned d,
+                                        int co0, long long m, bool live) {
   const long long o = m * a.c_out + co0;
-  if (!(a.flags & kGated)) d = 0xfu;             // (a dense layer takes the second pair)
-  if constexpr (Base::kDtype == CG_I8) {
-    int32_t v[4];
+  acc_t s[4];
+  int on[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int rb = (int8_t)((uint32_t)res[0] >> (8 * e));
-      if (a.flags & kFit32) {                    // (as in the row-tiled kernel)
-        const int sv = s[e] < t.hi[e] ? t.hi[e] : s[e] > t.h1[e] ? t.h1[e] : s[e];
-        int q = (__mul24(sv, ((d >> e) & 1u) ? t.h0[e] : t.s0[e]) + t.s1[e] + __mul24(rb, a.rq_res_mult)) >> a.rq_shift;
-        const int low = (a.flags & kRelu) ? 0 : -128;
-        v[e] = q < low ? low : q > 127 ? 127 : q;
-        continue;
-      }
-      const long long r = (long long)rb * a.rq_res_mult;
-      long long q;
-      if (a.flags & kOut4) {
-        q = (long long)s[e] + r;
-        if ((a.flags & kRelu) && q < 0) q = 0;
-        q = q > 2147483647ll ? 2147483647ll : q;
-        q = q < -2147483648ll ? -2147483648ll : q;
-      } else {
-        q = (long long)s[e] * (((d >> e) & 1u) ? t.h0[e] : t.s0[e]);
-        q += (long long)t.s1[e] * (1ll << a.rq_shift) + r;
-        if (a.rq_shift > 0) q = (q + (1ll << (a.rq_shift - 1))) >> a.rq_shift;
-        const long long lo = (a.flags & kRelu) ? 0 : -128;
-        q = q < lo ? lo : q > 127 ? 127 : q;
-      }
-      v[e] = (int32_t)q;
-    }
-    if (!whole) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (co0 + e < a.c_out) {
-          const long long oe = element_at(a, m, co0 + e);
-          if (a.flags & kOut4)
-            ((int32_t*)a.y)[oe] = v[e];
-          else
-            ((int8_t*)a.y)[oe] = (int8_t)v[e];
-        }
-    } else if (a.flags & kOut4) {
-      *(i32x4*)((int32_t*)a.y + o) = i32x4{v[0], v[1], v[2], v[3]};
-    } else {
-      *(int32_t*)((int8_t*)a.y + o) = (v[0] & 0xff) | ((v[1] & 0xff) << 8) | ((v[2] & 0xff) << 16) | ((v[3] & 0xff) << 24);
-    }
-  } else {
-    float v[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float q = s[e];
-      if (a.flags & kAffine)
-        q = ((d >> e) & 1u) ? fmaf(__int_as_float(t.s1[e]), q, __int_as_float(t.h1[e]))
-                            : fmaf(__int_as_float(t.s0[e]), q, __int_as_float(t.h0[e]));
-      if (a.flags & kResidual)
-        q += (a.flags & kOut4) ? __int_as_float(res[e]) : __uint_as_float(e & 1 ? (unsigned)res[e >> 1] & 0xffff0000u : (unsigned)res[e >> 1] << 16);
-      if (a.flags & kRelu) q = fmaxf(q, 0.0f);
-      v[e] = q;
-    }
-    if (!whole) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (co0 + e < a.c_out) {
-          const long long oe = element_at(a, m, co0 + e);
-          if (a.flags & kOut4)
-            ((float*)a.y)[oe] = v[e];
-          else
-            ((uint16_t*)a.y)[oe] = float_to_bf16(v[e]);
-        }
-    } else if (a.flags & kOut4) {
-      *(f32x4*)((float*)a.y + o) = f32x4{v[0], v[1], v[2], v[3]};
-    } else {
-      *(uint2*)((uint16_t*)a.y + o) = uint2{(uint32_t)float_to_bf16(v[0]) | ((uint32_t)float_to_bf16(v[1]) << 16),
-                                            (uint32_t)float_to_bf16(v[2]) | ((uint32_t)float_to_bf16(v[3]) << 16)};
-    }
+  for (int e = 0; e < 4; ++e) {
+    on[e] = ones_if(d, e);
+    acc_t c;
+    set_bits(bits_of(cond[e]) & on[e], c);
+    s[e] = base[e] + c;
   }
+  if (!(a.flags & kGated)) on[0] = on[1] = on[2] = on[3] = -1;             // (a dense layer takes the second pair)
+  i32x4 v;                                       // what is stored, 4-byte outputs
+  int packed[2] = {0, 0};                        // narrow ones
+  if constexpr (Base::kDtype == CG_I8) {
+    const int low = (a.flags & kRelu) ? 0 : -128;
+    if (a.flags & kFit32) {                      // (as in the row-tiled kernel)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int q = __mul24(med3(s[e], t.hi[e], t.h1[e]), select_bits(on[e], t.h0[e], t.s0[e])) + t.s1[e] +
+                      __mul24((int)(int8_t)((uint32_t)res[0] >> (8 * e)), a.rq_res_mult);
+        v[e] = med3(q >> a.rq_shift, low, 127);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const long long r = (long long)(int8_t)((uint32_t)res[0] >> (8 * e)) * a.rq_res_mult;
+        long long q;
+        if (a.flags & kOut4) {
+          q = (long long)s[e] + r;
+          if ((a.flags & kRelu) && q < 0) q = 0;
+          q = q > 2147483647ll ? 2147483647ll : q;
+          q = q < -2147483648ll ? -2147483648ll : q;
+        } else {
+          q = (long long)s[e] * select_bits(on[e], t.h0[e], t.s0[e]);
+          q += (long long)t.s1[e] * (1ll << a.rq_shift) + r;
+          if (a.rq_shift > 0) q = (q + (1ll << (a.rq_shift - 1))) >> a.rq_shift;
+          q = q < low ? low : q > 127 ? 127 : q;
+        }
+        v[e] = (int32_t)q;
+      }
+    }
+    packed[0] = (v[0] & 0xff) | ((v[1] & 0xff) << 8) | ((v[2] & 0xff) << 16) | ((v[3] & 0xff) << 24);
+  } else {
+    const float relu_lo = (a.flags & kRelu) ? 0.0f : __builtin_nanf("");
+    if (a.flags & kAffine) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        s[e] = fmaf(__int_as_float(select_bits(on[e], t.s1[e], t.s0[e])), s[e], __int_as_float(select_bits(on[e], t.h1[e], t.h0[e])));
+    }
+    if (a.flags & kResidual) {
+      if (a.flags & kOut4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] += __int_as_float(res[e]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] += __uint_as_float(e & 1 ? (unsigned)res[e >> 1] & 0xffff0000u : (unsigned)res[e >> 1] << 16);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = __float_as_int(max_of(s[e], relu_lo));
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      packed[e] = (int)((uint32_t)float_to_bf16(__int_as_float(v[2 * e])) | ((uint32_t)float_to_bf16(__int_as_float(v[2 * e + 1])) << 16));
+  }
+  if (one_piece(a)) {
+    if (a.flags & kOut4) {
+      if (live) *(i32x4*)((int32_t*)a.y + o) = v;
+    } else if constexpr (Base::kDtype == CG_I8) {
+      if (live) *(int32_t*)((int8_t*)a.y + o) = packed[0];
+    } else {
+      if (live) *(int2*)((uint16_t*)a.y + o) = int2{packed[0], packed[1]};
+    }
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (live && co0 + e < a.c_out) {
+      const long long oe = element_at(a, m, co0 + e);
+      if (a.flags & kOut4)
+        ((int32_t*)a.y)[oe] = v[e];
+      else if constexpr (Base::kDtype == CG_I8)
+        ((int8_t*)a.y)[oe] = (int8_t)v[e];
+      else
+        ((uint16_t*)a.y)[oe] = (uint16_t)((unsigned)packed[e >> 1] >> (16 * (e & 1)));
+    }
 }
 
 // or of a value over the four lane groups, in all of them
@@ -311,35 +331,34 @@ __device__ __forceinline__ unsigned masked(const DirectArgs& a, unsigned d, int 
 
 // The end of the layer for one unit of a tile (16 pixels x 16 channels, four channels a lane): decisions, output.
 template <typename Base, typename acc_t>
-__device__ __forceinline__ void finish_unit(const DirectArgs& a, acc_t (&s)[4], const acc_t (&r)[4], const Tab4<Base>& t, i32x4 res,
+__device__ __forceinline__ void finish_unit(const DirectArgs& a, const acc_t (&s)[4], const acc_t (&r)[4], const Tab4<Base>& t, i32x4 res,
                                             int co0, int lg, long long m, bool valid) {
   unsigned d = 0u;
   if (a.flags & kGated) {
-    d = gate4<Base>(a, s, t, co0);
-    if (!valid) d = 0u;
-    d = masked(a, d, co0, m);
+    d = gate4<Base>(a, s, t.lo, t.hi, co0) & (valid ? ~0u : 0u);
+    if (a.chan_mask) d = masked(a, d, co0, m);
     if (a.bitmap) {
       const unsigned half = or_groups(d << (4 * lg));
       const int at = (co0 - 4 * lg) >> 4;         // half word of the pixel
       if (lg == 0 && valid && at < 2 * a.words) ((uint16_t*)a.bitmap)[m * (2 * a.words) + at] = (uint16_t)half;
     }
   }
-  if (valid && !(a.flags & kGateOnly)) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) s[e] += ((d >> e) & 1u) ? r[e] : (acc_t)0;
-    finish4<Base>(a, s, t, res, d, co0, m);
-  }
+  if (!(a.flags & kGateOnly)) finish4<Base>(a, s, r, t, res, d, co0, m, valid && co0 < a.c_out);
 }
 
 // 8 wavefronts per workgroup at most
 constexpr int kMaxSplit = 8;
 
-// MIXED: float layers whose blocks cover several channel groups (Sec. 3.3) or whose groups share a chunk.  The packed
+// UNIFORM: every K step lies inside one tap and on one side of the base group, so that its place in x is the same for all lanes but for the
+// chunk (a scalar offset, changed by an addition; the general walk forms each lane group's own with some twenty vector instructions a step).
+//
+// MIXED: float layers whose blocks cover several channel groups (Sec. 3.3) or whose groups share a chunk; kStraddle: those whose base group ends
+// inside a chunk.  The packed
 // weights are zero where a channel is not on a row's path, which keeps its finite values out of the row's sum but turns
 // an infinity or a NaN into a NaN; a wavefront that ends up with a NaN forms its sums again, from the path's channels
 // alone.  (The look at the sums costs 1 to 2 %, one at every operand, as it is read, 5 to 7 %.)
-template <typename Tr, int PF, int NH, bool SPLIT, bool MIXED>
-__global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void gated_conv_direct_kernel(DirectArgs p) {
+template <typename Tr, int PF, int NH, bool SPLIT, bool MIXED, bool UNIFORM>
+__device__ __forceinline__ void direct_layer(const DirectArgs& p) {
   using Base = typename Tr::Base;
   using acc4 = typename Tr::acc4;
   using acc_t = typename Tr::acc_t;
@@ -349,11 +368,13 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
   constexpr int kU = NU == 1 ? 4 : NU == 2 ? 2 : 1;
   constexpr bool kBlocks = SPLIT ? Base::kDtype != CG_I8 && NU < 8 : Base::kDtype == CG_F32;      // (see `carry`)
   constexpr bool kPair = !SPLIT && Base::kDtype == CG_BF16;                                        // (the same)
-  __shared__ __align__(16) i32x4 ex[SPLIT ? kMaxSplit * NU * 64 : kBlocks ? 4 * NU * 64 : 1];     // [wavefront][unit][lane]
+  __shared__ __align__(16) i32x4 ex[SPLIT ? kMaxSplit * NU * 64 + (NU < 8 ? 1 : 0) : 1];     // [wavefront][unit][lane]; zeros
+  __shared__ __align__(16) i32x4 tab_at[SPLIT ? (NU < 8 ? NU * 4 * kTabs : 1) : 4 * NH * 4 * kTabs];    // [wavefront][(whole: sixteen channels)][table][four channels]
 
   load_args(p);
+  load_rest(p);
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = (int)blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = p.waves;
   const int lj = lane & 15, lg = lane >> 4;
 
   // block -> (pixel tile, channel tile): an XCD (block id mod 8) takes a contiguous run of them, so the
@@ -414,7 +435,6 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
   // Over 1300 layers of 10 to 10^5 pixels the error is 0.75 (fp32) and 0.94 (bf16) times the former one in the mean, 1.01 and 1.02 at most; over 400 bf16
   // layers whose K was split and is not now, or less, 0.98, 1.09 at most (1.5 and 1.8 as one chain).
   constexpr bool kTwo = kBlocks && SPLIT && kU > 1;     // two sums at a time, of the even and of the odd steps
-  constexpr int kAtATime = SPLIT ? (NU >= 4 ? 1 : 8) : 2;      // units under way together
   auto join = [&](auto two, acc4 (&a)[PF][NH], acc4 (&odd)[PF][NH]) __attribute__((always_inline)) {
     if constexpr (decltype(two)::value) {
 #pragma unroll
@@ -426,112 +446,89 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
         }
     }
   };
-  bool carried = false;
-  auto carry = [&](auto two, acc4 (&a)[PF][NH], acc4 (&odd)[PF][NH]) __attribute__((always_inline)) {
-    if constexpr (kBlocks) {
-      join(two, a, odd);
-#pragma unroll
-      for (int f = 0; f < PF; ++f)
-#pragma unroll
-        for (int i = 0; i < NH; ++i) {
-          i32x4* const at = &ex[(wave * NU + f * NH + i) * 64 + lane];
-          if (carried) a[f][i] += __builtin_bit_cast(acc4, *at);
-          *at = __builtin_bit_cast(i32x4, a[f][i]);
-          a[f][i] = acc4{0, 0, 0, 0};
-          if ((f * NH + i) % kAtATime == kAtATime - 1) __builtin_amdgcn_sched_barrier(0);      // (no registers for more)
-        }
-      carried = true;
-    }
-  };
-  // K steps [k0, k1) of phase ph into a, two: the odd steps into `odd` first (both zero before; `odd` again afterwards).  `meanwhile` runs
-  // once the first operands are on their way.
-  auto walk = [&](auto two, int ph, int k0, int k1, acc4 (&a)[PF][NH], acc4 (&odd)[PF][NH], auto meanwhile) __attribute__((always_inline)) {
+  // K steps k0 .. k0 + n - 1 of phase ph into a, two: the odd ones into `odd` first (both zero before; `odd` again afterwards).
+  // `meanwhile` runs once the first operands are on their way.
+  //   Two batches of kU steps are in flight.  Every way through the loop has the same loads in flight at the same line, and what is left
+  // at the end of K leaves it: the compiler's waits are then for the operands that are used and no others.  (With a
+  // branch around the fetches the wait before each product was for every load in flight, and where a step's offset was chosen between
+  // a scalar and the lanes' own each pixel load stood in a loop over the lanes.)  Steps past the end are loads out of range.
+  auto walk = [&](auto two, int ph, int k0, int n, acc4 (&a)[PF][NH], acc4 (&odd)[PF][NH], auto meanwhile) __attribute__((always_inline)) {
     const int nq = ph ? p.chunks1 : p.chunks0;
-    const Div dnq = ph ? p.nq1 : p.nq0;
+    const Div dnq{ph ? p.nq1.m : p.nq0.m, ph ? p.nq1.s : p.nq0.s};
     const int cfirst = ph ? 0 : bfirst;
+    const int gap_at = ph ? gap_s : 0x7fffffff;     // the chunk from which on the gap is jumped
     const unsigned wgrp = (unsigned)(ph ? p.ks1 : p.ks0) * 2048u;
     const char* const wp = (ph ? p.w1 : p.w0) + (size_t)(half0 >> 1) * wgrp + (NH == 1 ? (half0 & 1) * 1024 : 0);
-    const bool uni = (p.flags & (ph ? kUni1 : kUni0)) != 0;     // nq and the gap are multiples of four: a K step has one tap
-    int tap, ci;                                    // this lane group's unit of the next step (uni: the step's first)
-    {
-      const unsigned u = 4u * (unsigned)k0 + (uni ? 0u : (unsigned)lg);
-      tap = (int)quot(u, dnq);
-      ci = (int)u - tap * nq;
-    }
-    const int dt = nq > 4 ? 0 : nq >= 3 ? 1 : nq == 2 ? 2 : 4, di = 4 - dt * nq;    // a K step on: so many taps and chunks on
-    const int q0 = ph ? 0 : nq - 1;
-    int k = k0;
-    carried = false;
+    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc((void*)wp, (short)0, NH == 4 ? 2 * wgrp : wgrp, 0x00027000);
     i32x4 x[2][kU][PF], w[2][kU][NH];
-    bool cut[2][kU];                                // the step's unit is the straddling chunk (the mask is applied where the
-                                                    // operand is used: at the load it would wait for it)
+    int kw = k0, kx = k0;                           // the next step whose weights, pixels are fetched
+    const int k1 = k0 + n;
     auto fetch_w = [&](auto bt) __attribute__((always_inline)) {
       constexpr int b = decltype(bt)::value;
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
-        const int kk = k + u < k1 ? k + u : k1 - 1;
-        const char* const wk = wp + (size_t)((unsigned)kk * 2048u) + lane * 16;
+        const int at = kU == 1 || kw < k1 ? lane * 16 : (int)kOut, sw = kU == 1 || kw < k1 ? kw * 2048 : 0;
 #pragma unroll
-        for (int i = 0; i < NH; ++i) w[b][u][i] = *(const i32x4*)(wk + (size_t)(i >> 1) * wgrp + (i & 1) * 1024);
+        for (int i = 0; i < NH; ++i)
+          w[b][u][i] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, at + (i & 1) * 1024, sw + (i >> 1) * (int)wgrp, 0));
+        ++kw;
+      }
+    };
+    // the walk's place: UNIFORM: the step's tap and first chunk, else the unit of this lane group
+    int tap = 0, ci = 0, so = 0;                    // so (UNIFORM): offset of the step from its pixel's first tap
+    unsigned vo[PF];                                // (UNIFORM) the lanes' offsets at this tap
+    const int gap16 = p.gap_len * 16, first16 = (cfirst * 16) + (gap_at <= 0 ? gap16 : 0);
+    const int dt = nq > 4 ? 0 : nq >= 3 ? 1 : nq == 2 ? 2 : 4, di = 4 - dt * nq;    // (otherwise) a step on: so many taps and chunks on
+    auto enter_tap = [&]() __attribute__((always_inline)) {
+      const int r = (tap * 11) >> 5, s = tap - 3 * r;
+      so = r * p.rowb + s * p.xps + first16;
+#pragma unroll
+      for (int f = 0; f < PF; ++f) vo[f] = (vmask[f] >> tap) & 1u ? xbase[f] + (unsigned)lg * 16u : kOut;
+    };
+    auto start = [&]() __attribute__((always_inline)) {
+      const unsigned u = 4u * (unsigned)k0 + (UNIFORM ? 0u : (unsigned)lg);
+      tap = (int)quot(u, dnq);
+      ci = (int)u - tap * nq;
+      if constexpr (UNIFORM) {
+        enter_tap();
+        so += ci * 16 + (gap_at > 0 && ci >= gap_at ? gap16 : 0);
       }
     };
     auto fetch_x = [&](auto bt) __attribute__((always_inline)) {
       constexpr int b = decltype(bt)::value;
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
-        int so = 0;
-        unsigned vo[PF];
-        if (uni) {
-          const int c = cfirst + ci + (ph && ci >= gap_s ? p.gap_len : 0);
-          const int r = (tap * 11) >> 5, s = tap - 3 * r;
-          const unsigned on = k < k1 && c < p.total_chunks ? 1u << tap : 0u;     // (taps past the last are not in vmask)
-          so = r * p.rowb + s * p.xps + c * 16;
+        const bool on = kU == 1 || kx < k1;
+        ++kx;
+        if constexpr (UNIFORM) {
 #pragma unroll
-          for (int f = 0; f < PF; ++f) vo[f] = (vmask[f] & on) ? xbase[f] + (unsigned)lg * 16u : kOut;
-          cut[b][u] = ci + lg == q0;
+          for (int f = 0; f < PF; ++f) x[b][u][f] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, on ? (int)vo[f] : (int)kOut, on ? so : 0, 0));
+          so += 64;
           ci += 4;
-          if (ci >= nq) {
+          so += ci == gap_at ? gap16 : 0;
+          if (ci == nq) {
             ci = 0;
             ++tap;
+            enter_tap();
           }
         } else {
-          int c = cfirst + ci;
-          if (ph) c += c >= gap_s ? p.gap_len : 0;
-          const int t = tap < 9 ? tap : 9;          // (bit 9 and up of the validity mask are zero)
-          const int r = (t * 11) >> 5, s = t - 3 * r;
-          const bool on = k < k1 && c < p.total_chunks;
-          const unsigned off = (unsigned)(__mul24(r, p.rowb) + __mul24(s, p.xps) + c * 16);
+          const int c = cfirst + ci + (ci >= gap_at ? p.gap_len : 0);
+          const int t = on && c < p.total_chunks ? tap : 31;              // (bit 9 and up of the validity mask are zero)
+          const int r = (int)__umul24(tap, 11) >> 5;
+          const unsigned off = (unsigned)(__mul24(r, p.rowb - 3 * p.xps) + __mul24(tap, p.xps) + c * 16);
 #pragma unroll
-          for (int f = 0; f < PF; ++f) vo[f] = on && ((vmask[f] >> t) & 1u) ? xbase[f] + off : kOut;
-          cut[b][u] = ci == q0;
-          tap += dt;
-          ci += di;
-          if (ci >= nq) {
-            ci -= nq;
-            ++tap;
+          for (int f = 0; f < PF; ++f) {
+            const unsigned vof = (vmask[f] >> t) & 1u ? xbase[f] + off : kOut;
+            x[b][u][f] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)vof, 0, 0));
           }
+          const int next = ci + di;
+          tap += dt + (next >= nq ? 1 : 0);
+          ci = next - (next >= nq ? nq : 0);
         }
-        ++k;
-#pragma unroll
-        for (int f = 0; f < PF; ++f) x[b][u][f] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)vo[f], so, 0));
       }
     };
     auto mul = [&](auto bt) __attribute__((always_inline)) {
       constexpr int b = decltype(bt)::value;
-      if (p.strad) {
-        i32x4 bmask;                                // bytes of the chunk that straddles the end of the base group that belong to it
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int n = p.strad - 4 * e;
-          bmask[e] = n >= 4 ? -1 : n <= 0 ? 0 : (int)((1u << (8 * n)) - 1u);
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u)
-#pragma unroll
-          for (int f = 0; f < PF; ++f)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[b][u][f][e] &= cut[b][u] ? (ph ? ~bmask[e] : bmask[e]) : -1;
-      }
 #pragma unroll
       for (int u = 0; u < kU; ++u)
 #pragma unroll
@@ -543,44 +540,72 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
               acc4& to = decltype(two)::value && ((kU == 1 ? b : u) & 1) ? odd[f][i] : a[f][i];
               to = Tr::mma(part, w[b][u][i], x[b][u][f], to);
             }
+      __builtin_amdgcn_sched_barrier(0);
     };
-    using B0 = std::integral_constant<int, 0>;
-    using B1 = std::integral_constant<int, 1>;
-    const int nb = (k1 - k0 + kU - 1) / kU;
-    if (nb > 0) fetch_w(B0{});                      // (their addresses need nothing of the pixels)
-    pixels();
-    if (nb > 0) fetch_x(B0{});
-    meanwhile();
-#pragma nounroll
-    for (int i = 0; i < nb; i += 2) {
-      if (i + 1 < nb) {
-        fetch_w(B1{});
-        fetch_x(B1{});
-      }
-      mul(B0{});
-      if (kU == 4 && i + 1 < nb) carry(two, a, odd);
-      if (i + 1 < nb) {
-        if (i + 2 < nb) {
-          fetch_w(B0{});
-          fetch_x(B0{});
-        }
-        mul(B1{});
-      }
-      if (i + 2 < nb) carry(two, a, odd);
-    }
-    join(two, a, odd);
+    acc4 tot[PF][NH];                               // the blocks so far
     if constexpr (kBlocks) {
-      if (carried) {
+#pragma unroll
+      for (int f = 0; f < PF; ++f)
+#pragma unroll
+        for (int i = 0; i < NH; ++i) tot[f][i] = acc4{0, 0, 0, 0};
+    }
+    auto carry = [&]() __attribute__((always_inline)) {
+      if constexpr (kBlocks) {
+        join(two, a, odd);
 #pragma unroll
         for (int f = 0; f < PF; ++f)
 #pragma unroll
           for (int i = 0; i < NH; ++i) {
-            a[f][i] += __builtin_bit_cast(acc4, ex[(wave * NU + f * NH + i) * 64 + lane]);
-            if ((f * NH + i) % kAtATime == kAtATime - 1) __builtin_amdgcn_sched_barrier(0);
+            tot[f][i] += a[f][i];
+            a[f][i] = acc4{0, 0, 0, 0};
           }
       }
+    };
+    constexpr std::integral_constant<int, 0> B0{};
+    constexpr std::integral_constant<int, 1> B1{};
+    const int nb = (n + kU - 1) / kU;
+    if (nb > 0) {
+      fetch_w(B0);                                  // (their addresses need nothing of the pixels)
+      pixels();
+      start();
+      fetch_x(B0);
     }
-    if constexpr (MIXED) {
+    meanwhile();
+    if (nb > 1) {
+      fetch_w(B1);
+      fetch_x(B1);
+#pragma nounroll
+      for (int i = 2;; i += 2) {
+        mul(B0);
+        if (kU == 4) carry();
+        if (i >= nb) {
+          mul(B1);
+          break;
+        }
+        fetch_w(B0);
+        fetch_x(B0);
+        mul(B1);
+        carry();
+        if (i + 1 >= nb) {
+          mul(B0);
+          break;
+        }
+        fetch_w(B1);
+        fetch_x(B1);
+      }
+    } else if (nb > 0) {
+      mul(B0);
+    }
+    carry();
+    join(two, a, odd);
+    if constexpr (kBlocks) {
+#pragma unroll
+      for (int f = 0; f < PF; ++f)
+#pragma unroll
+        for (int i = 0; i < NH; ++i) a[f][i] = tot[f][i];
+    }
+    if constexpr (Base::kDtype != CG_I8 && !UNIFORM) {
+      if (!MIXED && !(p.flags & kStraddle)) return;
       bool nan = false;
 #pragma unroll
       for (int f = 0; f < PF; ++f)
@@ -600,8 +625,8 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
           for (int f = 0; f < PF; ++f) a[f][i][e] = 0.0f;
         }
 #pragma nounroll
-      for (int u = 4 * k0; u < 4 * k1; ++u) {
-        const int t = u / nq, chunk = cfirst + u - t * nq, r = (t * 11) >> 5;
+      for (int u = 4 * k0; u < 4 * (k0 + n); ++u) {
+        const int t = u / nq, i = u - t * nq, chunk = cfirst + i + (i >= gap_at ? p.gap_len : 0), r = (t * 11) >> 5;
         if (t >= p.taps || chunk >= p.total_chunks) continue;
         i32x4 xv[PF];
 #pragma unroll
@@ -642,20 +667,33 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
     acc4 accP[PF][NH], accR[PF][NH];
     zero(accP);
     zero(accR);
-    Tab4<Base> t[NH];
+    i32x4 tabs[NH];                                 // as of a split, of each sixteen channels
     walk(std::bool_constant<kPair>{}, 0, 0, p.ks0, accP, accR, [&]() __attribute__((always_inline)) {
-      load_rest(p);
       if ((p.flags & kClear) && blockIdx.x == 0 && tid < 2) p.total[tid] = 0u;
+      if (lane < 4 * kTabs) {
+#pragma unroll
+        for (int i = 0; i < NH; ++i) tabs[i] = *(const i32x4*)(p.tab + (lane >> 2) * p.tab_stride + (half0 + i) * 64 + (lane & 3) * 16);
+      }
     });
+    i32x4* const mine = tab_at + wave * (NH * 4 * kTabs);
+    if (lane < 4 * kTabs) {
+#pragma unroll
+      for (int i = 0; i < NH; ++i) mine[i * (4 * kTabs) + lane] = tabs[i];
+    }
+    __builtin_amdgcn_wave_barrier();                // (other lanes of this wavefront read them)
     unsigned d[PF][NH];                             // bit e: channel 16*(half0 + i) + 4*lg + e
 #pragma unroll
     for (int f = 0; f < PF; ++f)
 #pragma unroll
       for (int i = 0; i < NH; ++i) d[f][i] = 0u;
-#pragma unroll
-    for (int i = 0; i < NH; ++i) t[i].load(p, (half0 + i) * 16 + 4 * lg);
     if (gated) {
       bool any = false;
+      i32x4 lo[NH], hi[NH];
+#pragma unroll
+      for (int i = 0; i < NH; ++i) {
+        lo[i] = mine[i * (4 * kTabs) + lg];
+        hi[i] = mine[i * (4 * kTabs) + 4 + lg];
+      }
 #pragma unroll
       for (int f = 0; f < PF; ++f) {
         const long long m = m0 + 16 * f + lj;
@@ -665,7 +703,7 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
           acc_t s[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) s[e] = accP[f][i][e];
-          unsigned dd = gate4<Base>(p, s, t[i], co0);
+          unsigned dd = gate4<Base>(p, s, lo[i], hi[i], co0);
           if (m >= p.m_total) dd = 0u;
           dd = masked(p, dd, co0, m);
           d[f][i] = dd;
@@ -688,18 +726,20 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
 #pragma unroll
       for (int i = 0; i < NH; ++i) res[f][i] = load_residual<Base>(p, (half0 + i) * 16 + 4 * lg, m0 + 16 * f + lj, m0 + 16 * f + lj < p.m_total);
 #pragma unroll
-    for (int f = 0; f < PF; ++f) {
-      const long long m = m0 + 16 * f + lj;
-      if (m >= p.m_total) continue;
+    for (int i = 0; i < NH; ++i) {
+      Tab4<Base> t;
+      t.take(p, mine + i * (4 * kTabs) + lg);
 #pragma unroll
-      for (int i = 0; i < NH; ++i) {
-        acc_t s[4];
+      for (int f = 0; f < PF; ++f) {
+        const long long m = m0 + 16 * f + lj;
+        const int co0 = (half0 + i) * 16 + 4 * lg;
+        acc_t s[4], r[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const acc_t pv = accP[f][i][e], rv = accR[f][i][e];
-          s[e] = pv + (((d[f][i] >> e) & 1u) ? rv : (acc_t)0);
+          s[e] = accP[f][i][e];
+          r[e] = accR[f][i][e];
         }
-        finish4<Base>(p, s, t[i], res[f][i], d[f][i], (half0 + i) * 16 + 4 * lg, m);
+        finish4<Base>(p, s, r, t, res[f][i], d[f][i], co0, m, m < p.m_total && co0 < p.c_out);
       }
     }
   } else {
@@ -708,27 +748,25 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
     const int ph = wave >= nwb ? 1 : 0;
     const int part = ph ? wave - nwb : wave;
     const int kq = ph ? p.kq1 : p.kq0, kr = ph ? p.kr1 : p.kr0;
-    const int k0 = part * kq + (part < kr ? part : kr), k1 = ph && gate_only ? k0 : k0 + kq + (part < kr ? 1 : 0);
+    const int k0 = part * kq + (part < kr ? part : kr), n = ph && gate_only ? 0 : kq + (part < kr ? 1 : 0);
     acc4 acc[PF][NH], odd[PF][NH];
     zero(acc);
     zero(odd);
     // this wavefront's unit of the tile's end (the plan has a wavefront for each): its tables and residual arrive behind the sums
     const int un = wave < NU ? wave : 0, uf = un / NH, co0 = (half0 + un % NH) * 16 + 4 * lg, m = m0 + 16 * uf + lj;
     const bool valid = m < p.m_total;
-    Tab4<Base> tab;
-    i32x4 res;
+    i32x4 tabs = {0, 0, 0, 0}, res = {0, 0, 0, 0};  // (a lane's share of the tables: each lane's own four channels of all of them are 20 registers more)
     auto load_end = [&]() __attribute__((always_inline)) {
       if (wave < NU) {
-        tab.load(p, co0);
+        if (lane < 4 * kTabs) tabs = *(const i32x4*)(p.tab + (lane >> 2) * p.tab_stride + (half0 + un % NH) * 64 + (lane & 3) * 16);
         res = load_residual<Base>(p, co0, m, valid && !gate_only);
       }
     };
-    walk(std::bool_constant<kTwo>{}, ph, k0, k1, acc, odd, [&]() __attribute__((always_inline)) {
-      load_rest(p);
+    walk(std::bool_constant<kTwo>{}, ph, k0, n, acc, odd, [&]() __attribute__((always_inline)) {
       if ((p.flags & kClear) && blockIdx.x == 0 && tid < 2) p.total[tid] = 0u;
       if constexpr (NU < 8) load_end();
     });
-    if constexpr (NU == 8) load_end();              // (its 28 registers would leave room for one workgroup on a compute unit)
+    if constexpr (NU == 8) load_end();              // (its 8 registers would be spilled)
 #pragma unroll
     for (int f = 0; f < PF; ++f)
 #pragma unroll
@@ -741,43 +779,66 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
         }
         ex[(wave * NU + f * NH + i) * 64 + lane] = v;
       }
+    if (NU < 8 && tid == 0) ex[kMaxSplit * NU * 64] = i32x4{0, 0, 0, 0};
+    if (NU < 8 && wave < NU && lane < 4 * kTabs) tab_at[wave * (4 * kTabs) + lane] = tabs;
     __syncthreads();
     if (wave >= NU) return;
-    acc_t s[4] = {0, 0, 0, 0}, r[4] = {0, 0, 0, 0};
-#pragma nounroll
-    for (int w0 = 0; w0 < nw; w0 += 4) {            // four wavefronts' sums at a time
-      i32x4 v[4];
+    // The sums of the base and of the conditional wavefronts, in pairs.  Those of the other path, and past the last wavefront, are zeros:
+    // read as such from LDS, or (tiles of eight units, which leave no LDS) made so.
+    acc_t s[4], r[4];
+    auto add_up = [&](auto waves, int first, int end, acc_t (&sum)[4]) __attribute__((always_inline)) {
+      constexpr int N = decltype(waves)::value;
+      i32x4 v[N];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = ex[((w0 + j < nw ? w0 + j : 0) * NU + un) * 64 + lane];
-      acc_t t[4][4];
+      for (int j = 0; j < N; ++j) {
+        const bool in = j >= first && j < end;
+        if constexpr (NU < 8) {
+          v[j] = ex[in ? (j * NU + un) * 64 + lane : kMaxSplit * NU * 64];
+        } else {
+          v[j] = ex[(j * NU + un) * 64 + lane];
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+          for (int e = 0; e < 4; ++e) v[j][e] &= in ? -1 : 0;
+        }
+      }
+      acc_t t[N][4];
+#pragma unroll
+      for (int j = 0; j < N; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e) set_bits(v[j][e], t[j][e]);
-      if (w0 + 4 <= nw && (w0 + 4 <= nwb || w0 >= nwb)) {      // all of one path: in pairs
-        const bool base = w0 < nwb;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const acc_t sum = (t[0][e] + t[1][e]) + (t[2][e] + t[3][e]);
-          if (base)
-            s[e] += sum;
-          else
-            r[e] += sum;
-        }
-        continue;
-      }
+      for (int step = 1; step < N; step *= 2)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < N; j += 2 * step)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (w0 + j < nwb)
-            s[e] += t[j][e];
-          else if (w0 + j < nw)
-            r[e] += t[j][e];
-        }
+          for (int e = 0; e < 4; ++e) t[j][e] += t[j + step][e];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum[e] = t[0][e];
+    };
+    if (NU == 8 || nw > 4) {
+      add_up(std::integral_constant<int, 8>{}, 0, nwb, s);
+      add_up(std::integral_constant<int, 8>{}, nwb, nw, r);
+    } else {
+      add_up(std::integral_constant<int, 4>{}, 0, nwb, s);
+      add_up(std::integral_constant<int, 4>{}, nwb, nw, r);
     }
+    // (tiles of eight units leave no LDS: their tables lie where this wavefront has read the first one's sums of its unit)
+    i32x4* const mine = NU < 8 ? tab_at + wave * (4 * kTabs) : ex + un * 64;
+    if (NU == 8 && lane < 4 * kTabs) mine[lane] = tabs;
+    __builtin_amdgcn_wave_barrier();
+    Tab4<Base> tab;
+    tab.take(p, mine + lg);
     finish_unit<Base>(p, s, r, tab, res, co0, lg, m, valid);
   }
+}
+
+template <typename Tr, int PF, int NH, bool SPLIT, bool MIXED>
+__global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void gated_conv_direct_kernel(DirectArgs p) {
+  direct_layer<Tr, PF, NH, SPLIT, MIXED, false>(p);
+}
+struct UniformArgs : DirectArgs {};
+template <typename Tr, int PF, int NH, bool SPLIT, bool MIXED>
+__global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void gated_conv_direct_kernel(UniformArgs p) {
+  direct_layer<Tr, PF, NH, SPLIT, MIXED, true>(p);
 }
 
 // [c_out][taps][c] in the caller's two weight arrays -> [32-channel group][K step][half][lane][16 bytes] of
@@ -814,22 +875,27 @@ __global__ void pack_direct_kernel(const T* __restrict__ wb, const T* __restrict
   for (int e = 0; e < CH; ++e) out[id * CH + e] = v[e];
 }
 
-template <typename Tr, int PF, int NH, bool MIXED>
-hipError_t launch_direct_form(const DirectPlan& g, const DirectArgs& a, hipStream_t s) {
+template <typename Tr, int PF, int NH, bool MIXED, typename Args>
+hipError_t launch_direct_form(const DirectPlan& g, const Args& a, hipStream_t s) {
+  using Kernel = void (*)(Args);
   const dim3 grid((unsigned)a.per_xcd * 8u);
   if (g.split > 1) {
-    hipLaunchKernelGGL((gated_conv_direct_kernel<Tr, PF, NH, true, MIXED>), grid, dim3(64 * g.split), 0, s, a);
+    const Kernel k = gated_conv_direct_kernel<Tr, PF, NH, true, MIXED>;
+    hipLaunchKernelGGL(k, grid, dim3(64 * g.split), 0, s, a);
   } else {
-    if constexpr (NH == 1)
+    if constexpr (NH == 1) {
       return hipErrorInvalidValue;
-    else
-      hipLaunchKernelGGL((gated_conv_direct_kernel<Tr, PF, NH, false, MIXED>), grid, dim3(256), 0, s, a);
+    } else {
+      const Kernel k = gated_conv_direct_kernel<Tr, PF, NH, false, MIXED>;
+      hipLaunchKernelGGL(k, grid, dim3(256), 0, s, a);
+    }
   }
   return hipGetLastError();
 }
 
 template <typename Tr, int PF, int NH>
 hipError_t launch_direct_tile(const DirectPlan& g, const DirectArgs& a, hipStream_t s) {
+  if (g.uniform) return launch_direct_form<Tr, PF, NH, false>(g, UniformArgs{a}, s);
   if constexpr (Tr::Base::kDtype != CG_I8)
     if (g.mixed) return launch_direct_form<Tr, PF, NH, true>(g, a, s);
   return launch_direct_form<Tr, PF, NH, false>(g, a, s);
@@ -866,10 +932,11 @@ DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu) {
   const int ngrp = (d.c_out + 31) / 32;
   g.n_grp = (ngrp + 1) / 2 * 2;
   g.total_chunks = d.c_in / g.ch;
+  int last_end = 0;                                              // of the last block's base phase
   if (groups == 1) {
     g.chunks[0] = (d.c_base + g.ch - 1) / g.ch;
     g.gap_len = d.c_base / g.ch;
-    g.strad = (d.c_base % g.ch) * g.elem_bytes;
+    g.straddle = d.c_base % g.ch ? 1 : 0;
   } else {
     // a 64-channel block walks the base channels of every group it touches; the other groups' weights are zeros
     bool single = d.c_base % g.ch == 0;
@@ -882,6 +949,7 @@ DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu) {
     }
     g.gap_len = single ? d.c_base / g.ch : 0;
     g.mixed = single ? 0 : 1;
+    last_end = ((d.c_out - 1) / 64 * 64 / cpg) * d.c_base / g.ch + g.chunks[0];
   }
   g.chunks[1] = gated ? g.total_chunks - g.gap_len : 0;
   for (int ph = 0; ph < 2; ++ph) {
@@ -905,7 +973,9 @@ DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu) {
     const int b = (split * g.ksteps[0] + ks / 2) / ks;
     return b < 1 ? 1 : b > split - 1 ? split - 1 : b;
   };
+  // K steps of one tap, on one side of the base group, that end with the input's channels in every block
   const bool uni = g.total_chunks % 4 == 0 && g.gap_len % 4 == 0 && g.chunks[0] % 4 == 0;
+  g.uniform = uni && g.straddle == 0 && (groups == 1 || d.c_base % (4 * g.ch) == 0) && last_end <= g.total_chunks && (g.mixed == 0 || d.in_dtype == CG_I8);
   const double start = f32 ? 5250.0 : 5350.0, each0 = f32 ? 90.0 : 233.0, each1 = f32 ? 211.0 : 124.0, wave0 = f32 ? 3880.0 : 3790.0;
   const double cx = (f32 ? 52.0 : 50.0) * (uni ? 1.0 : f32 ? 1.25 : 0.91), cw = f32 ? 32.0 : 12.5, cm = f32 ? 175.0 : 16.0, cl = f32 ? 82.0 : 450.0;
   // bf16 layers of at least two K steps to each of four wavefronts, and fewer than four times as many tiles of 32 x 64 as compute units, are
@@ -996,10 +1066,10 @@ hipError_t launch_direct(const DirectPlan& g, const Params& p, const void* w0, c
   a.chunks1 = g.chunks[1];
   a.total_chunks = g.total_chunks;
   a.gap_len = g.gap_len;
-  a.strad = g.strad;
   a.ks0 = g.ksteps[0];
   a.ks1 = g.ksteps[1];
   a.n_cblk = g.n_cblk;
+  a.waves = g.split > 1 ? g.split : 4;
   a.nwb = g.nwb;
   a.c_out = p.c_out;
   a.words = p.words;
@@ -1025,11 +1095,7 @@ hipError_t launch_direct(const DirectPlan& g, const Params& p, const void* w0, c
   a.rq_res_mult = p.rq_res_mult;
   static_assert(kRelu == CG_EPI_RELU && kAffine == CG_EPI_AFFINE && kResidual == CG_EPI_RESIDUAL, "the epilogue flags pass through");
   a.flags = p.epilogue | (p.gated ? kGated : 0u) | (p.gate_only ? kGateOnly : 0u) | (p.clear_total ? kClear : 0u) |
-            (p.shuffle ? kShuffle : 0u) | (p.out_dtype == CG_F32 || p.out_dtype == CG_I32 ? kOut4 : 0u) | (p.fit32 ? kFit32 : 0u);
-  // a block's base channels start at a multiple of c_base; one that is no multiple of four chunks leaves the general walk
-  const bool aligned = g.total_chunks % 4 == 0 && (p.groups <= 1 || p.c_base % (4 * g.ch) == 0) && g.gap_len % 4 == 0;
-  if (aligned && g.chunks[0] % 4 == 0) a.flags |= kUni0;
-  if (aligned && g.chunks[1] % 4 == 0) a.flags |= kUni1;
+            (p.shuffle ? kShuffle : 0u) | (p.out_dtype == CG_F32 || p.out_dtype == CG_I32 ? kOut4 : 0u) | (p.fit32 ? kFit32 : 0u) | (g.straddle ? kStraddle : 0u);
   switch (p.in_dtype) {
     case CG_BF16: return launch_direct_dtype<Bf16Direct>(g, a, s);
     case CG_I8: return launch_direct_dtype<I8Direct>(g, a, s);
