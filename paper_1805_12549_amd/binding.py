@@ -9,6 +9,7 @@ reduced to raw device pointers before they cross the boundary.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 from pathlib import Path
 from typing import Optional
 
@@ -42,6 +43,14 @@ def _hip_runtimes_mapped():
 if len(_hip_runtimes_mapped()) > 1:
     raise ImportError("two HIP runtimes are mapped into this process (%s); import torch before anything "
                       "that loads libamdhip64" % ", ".join(_hip_runtimes_mapped()))
+
+_CALLS_PATH = _LIB_PATH.with_name("_calls.so")
+if not _CALLS_PATH.exists():
+    raise ImportError("%s is missing: build it with the library (python paper_1805_12549_amd/build.py or __graft_entry__.build())" % _CALLS_PATH)
+_spec = importlib.util.spec_from_file_location("paper_1805_12549_amd._calls", str(_CALLS_PATH))
+_calls = importlib.util.module_from_spec(_spec)
+_spec.loader.exec_module(_calls)
+_native_forward = _calls.forward
 
 # the current stream's address without building a Stream object per call
 _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
@@ -175,30 +184,36 @@ def _check(rc: int) -> None:
 def cg_small_cin_conv(x: int, w: int, scale: int, shift: int, y: int, n: int, h: int, wd: int, c_in: int,
                       c_out: int, k: int, stride: int, pad: int, relu: bool, hip_stream: int = 0) -> None:
     """Raw device addresses (0 = NULL for scale / shift)."""
-    _check(_lib.cg_small_cin_conv(C.c_void_p(x), C.c_void_p(w), C.c_void_p(scale), C.c_void_p(shift), C.c_void_p(y),
-                                  n, h, wd, c_in, c_out, k, stride, pad, int(bool(relu)), C.c_void_p(hip_stream)))
+    _check(_lib.cg_small_cin_conv(x, w, scale, shift, y,
+                                  n, h, wd, c_in, c_out, k, stride, pad, int(bool(relu)), hip_stream))
 
 
 def cg_conv7x7s2_maxpool(x: int, w: int, scale: int, shift: int, y: int, n: int, h: int, wd: int, c_out: int,
                          pad: int, relu: bool, hip_stream: int = 0) -> None:
-    _check(_lib.cg_conv7x7s2_maxpool(C.c_void_p(x), C.c_void_p(w), C.c_void_p(scale), C.c_void_p(shift), C.c_void_p(y),
-                                     n, h, wd, c_out, pad, int(bool(relu)), C.c_void_p(hip_stream)))
+    _check(_lib.cg_conv7x7s2_maxpool(x, w, scale, shift, y,
+                                     n, h, wd, c_out, pad, int(bool(relu)), hip_stream))
 
 
 def cg_pointwise_conv(x: int, w: int, scale: int, shift: int, y: int, n: int, h: int, wd: int, c_in: int, c_out: int,
                       stride: int, relu: bool, hip_stream: int = 0) -> None:
-    _check(_lib.cg_pointwise_conv(C.c_void_p(x), C.c_void_p(w), C.c_void_p(scale), C.c_void_p(shift), C.c_void_p(y),
-                                  n, h, wd, c_in, c_out, stride, int(bool(relu)), C.c_void_p(hip_stream)))
+    _check(_lib.cg_pointwise_conv(x, w, scale, shift, y,
+                                  n, h, wd, c_in, c_out, stride, int(bool(relu)), hip_stream))
 
 
 def cg_maxpool3x3s2(x: int, y: int, n: int, h: int, wd: int, c: int, hip_stream: int = 0) -> None:
-    _check(_lib.cg_maxpool3x3s2(C.c_void_p(x), C.c_void_p(y), n, h, wd, c, C.c_void_p(hip_stream)))
+    _check(_lib.cg_maxpool3x3s2(x, y, n, h, wd, c, hip_stream))
 
 
 def cg_avgpool_fc(x: int, wfc: int, bias: int, logits: int, n: int, hw: int, c: int, classes: int,
                   hip_stream: int = 0) -> None:
-    _check(_lib.cg_avgpool_fc(C.c_void_p(x), C.c_void_p(wfc), C.c_void_p(bias), C.c_void_p(logits), n, hw, c, classes,
-                              C.c_void_p(hip_stream)))
+    _check(_lib.cg_avgpool_fc(x, wfc, bias, logits, n, hw, c, classes,
+                              hip_stream))
+
+
+def empty_beside(x, bf16: bool, *sizes):
+    """A contiguous tensor of that shape (bf16, else fp32) on x's device."""
+    t = _calls.empty(x, bf16, *sizes)
+    return t if t is not None else torch.empty(sizes, dtype=torch.bfloat16 if bf16 else torch.float32, device=x.device)
 
 
 def cg_conv_info(handle: int):
@@ -237,6 +252,8 @@ class GatedConv:
     groups > 1 selects channel grouping, shuffle the channel-shuffled store, tau_c > 0 the
     channel-wise gate (see cg_conv.h).
     """
+
+    _native = None              # the layer as _calls.forward takes it, as long as it is open
 
     def __init__(self, *, n_max, h, w, c_in, c_out, c_base, w_base, w_cond, in_dtype, out_dtype,
                  kh=3, kw=3, stride=1, pad=1, epilogue=CG_EPI_RELU, variant=CG_VARIANT_AUTO,
@@ -295,6 +312,7 @@ class GatedConv:
         self.words = (c_out + 31) // 32
         self._y_dtype = getattr(torch, _TORCH_OUT[out_dtype])
         self._ws_need = {}      # workspace bytes per batch size
+        self._native = _calls.Layer(self.handle, self.ho, self.wo, c_out, out_dtype)
 
     def _stream_ptr(self):
         if self.stream is not None:
@@ -303,6 +321,13 @@ class GatedConv:
 
     def forward(self, x, residual=None, y=None, bitmap=True, counts=True):
         """x: torch device tensor [n,H,W,C_in] (contiguous NHWC).  Returns (y, bitmap, counts)."""
+        if self._native is not None:
+            out = _native_forward(self._native, self.stream, x, residual, y, bitmap, counts)
+            if out.__class__ is tuple:
+                return out
+            if out is not None:
+                raise CGError(out, cg_last_error())
+        # (arguments that are not plain tensors)
         n, dev = x.shape[0], x.device
         if y is None:
             ho, wo, c = self.ho, self.wo, self.c_out
@@ -337,6 +362,7 @@ class GatedConv:
 
     def close(self):
         if self.handle:
+            self._native = None
             cg_conv_destroy(self.handle)
             self.handle = None
 

@@ -1,10 +1,11 @@
-"""Build the C-ABI library ``libcg_conv.so`` from ``csrc/`` with hipcc for gfx950."""
+"""Build the C-ABI library ``libcg_conv.so`` from ``csrc/`` with hipcc for gfx950, and the binding's ``_calls.so`` (host code) with g++."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 from pathlib import Path
@@ -13,6 +14,7 @@ PKG = Path(__file__).resolve().parent
 ROOT = PKG.parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libcg_conv.so"
+CALLS = PKG / "_calls.so"
 
 SOURCES = ["cg_conv_api.hip", "kernels_naive.hip", "kernels_direct.hip", "kernels_rows.hip", "kernels_counts.hip", "kernels_dense.hip",
            "kernels_tile.hip", "kernels_tile_bf16_k3.hip", "kernels_tile_bf16_k1.hip", "kernels_tile_i8_k3.hip",
@@ -33,6 +35,19 @@ def hipcc() -> str:
         if cand and (os.path.sep not in cand or os.path.exists(cand)):
             return cand
     raise RuntimeError("hipcc not found")
+
+
+def calls_command(out) -> list:
+    """g++ on the Python extension of the calls (csrc/py_calls.cpp), against torch's C++ interface and the built library."""
+    import torch
+    home = Path(torch.__file__).resolve().parent
+    rocm = Path(hipcc()).resolve().parent.parent
+    rocm = rocm if (rocm / "include" / "hip").is_dir() else Path("/opt/rocm")
+    return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-isystem", str(home / "include"),
+            "-isystem", str(home / "include" / "torch" / "csrc" / "api" / "include"), "-isystem", str(rocm / "include"),
+            "-isystem", sysconfig.get_paths()["include"], "-I", str(ROOT / "include"), "-I", str(CSRC), str(CSRC / "py_calls.cpp"), "-o", str(out),
+            "-L", str(home / "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-L", str(PKG), "-lcg_conv", "-Wl,-rpath,$ORIGIN"]
 
 
 def build(verbose: bool = False, extra=(), jobs: int = 6) -> Path:
@@ -58,6 +73,12 @@ def build(verbose: bool = False, extra=(), jobs: int = 6) -> Path:
             print(" ".join(link), flush=True)
         subprocess.check_call(link)
         os.replace(tmp, LIB)
+        tmp = CALLS.with_name(CALLS.name + ".tmp%d" % os.getpid())
+        link = calls_command(tmp)
+        if verbose:
+            print(" ".join(link), flush=True)
+        subprocess.check_call(link)
+        os.replace(tmp, CALLS)
     finally:
         shutil.rmtree(work, ignore_errors=True)
     return LIB

@@ -657,7 +657,7 @@ struct WsLayout {
 // What a call gets of it: what any call may need (the caller's workspace); what this call needs; or what the plain kernel
 // needs when it counts the fired gates itself (an image whose bitmap does not fit the scratch array).
 enum Scratch { kAnyCall, kThisCall, kCounting };
-WsLayout ws_layout(const cg_conv* h, int32_t n, const CallPlan& c, Scratch mode, bool counts_only) {
+WsLayout ws_layout(const cg_conv* h, int32_t n, Scratch mode, bool counts_only) {
   WsLayout w{};
   const size_t words = (size_t)(h->d.c_out + 31) / 32;
   const bool gated = h->c_cond > 0, chan_gate = gated && h->d.tau_c > 0.0f;
@@ -675,7 +675,7 @@ WsLayout ws_layout(const cg_conv* h, int32_t n, const CallPlan& c, Scratch mode,
 
 size_t cg_conv_workspace_bytes(const cg_conv* h, int32_t n) {
   if (!h || n <= 0) return 0;
-  return ws_layout(h, n, call_plan(h, n), kAnyCall, true).total;
+  return ws_layout(h, n, kAnyCall, true).total;
 }
 
 int cg_conv_info(const cg_conv* h, int32_t* ho, int32_t* wo) {
@@ -704,6 +704,16 @@ int cg_conv_forward(cg_conv* h, int32_t n, const void* x, const void* residual, 
                       workspace_bytes, hip_stream);
 }
 
+size_t cg_conv_call_scratch_bytes(const cg_conv* h, int32_t n, int has_bitmap, int has_counts) {
+  if (!h || n <= 0) return 0;
+  return ws_layout(h, n, kThisCall, has_counts && !has_bitmap).total;
+}
+
+int cg_conv_call(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap, uint32_t* counts, void* workspace,
+                 size_t workspace_bytes, void* hip_stream) {
+  return forward_impl(h, n, x, residual, y, bitmap, counts ? counts + 2 : nullptr, counts, true, kThisCall, workspace, workspace_bytes, hip_stream);
+}
+
 int cg_conv_forward_noalloc(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap,
                             uint32_t* counts, void* hip_stream) {
   if (!h) return fail(CG_EINVAL, "handle is NULL");
@@ -716,8 +726,8 @@ int cg_conv_forward_noalloc(cg_conv* h, int32_t n, const void* x, const void* re
     // counted without a bitmap, where not even one image's bitmap fits.
     const bool counts_only = counts && !bitmap;
     mode = kThisCall;
-    if (ws_layout(h, n, call_plan(h, n), mode, counts_only).total > kScratchBytes) {
-      const size_t one = ws_layout(h, 1, call_plan(h, 1), mode, counts_only).total;
+    if (ws_layout(h, n, mode, counts_only).total > kScratchBytes) {
+      const size_t one = ws_layout(h, 1, mode, counts_only).total;
       if (one > kScratchBytes) mode = kCounting;
       step = one > kScratchBytes ? 1 : (int)(kScratchBytes / one);
     }
@@ -769,7 +779,7 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
   if (h->variant != CG_VARIANT_NAIVE && !aligned)
     return fail(CG_EINVAL, "x, y, residual and bitmap must be 16-byte aligned");
   CallPlan cp = call_plan(h, n);
-  const WsLayout wl = ws_layout(h, n, cp, mode, counts && !bitmap);
+  const WsLayout wl = ws_layout(h, n, mode, counts && !bitmap);
   const size_t need = wl.total;
   if (need > 0 && (!workspace || workspace_bytes < need))
     return fail(CG_EINVAL, "workspace of %zu bytes is smaller than the %zu required", workspace_bytes, need);
