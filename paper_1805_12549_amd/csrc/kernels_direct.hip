@@ -168,7 +168,7 @@ __device__ __forceinline__ int med3(int v, int lo, int hi) {
 
 // decisions of four consecutive channels from their base sums
 template <typename Base, typename acc_t>
-__device__ __forceinline__ unsigned gate4(const DirectArgs& a, const acc_t (&s)[4], i32x4 lo, i32x4 hi, int co0) {
+__device__ __forceinline__ unsigned gate4(const acc_t (&s)[4], i32x4 lo, i32x4 hi) {
   unsigned d = 0u;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -179,7 +179,11 @@ __device__ __forceinline__ unsigned gate4(const DirectArgs& a, const acc_t (&s)[
       f = Base::fires(s[e], __int_as_float(lo[e]), __int_as_float(hi[e]));
     d |= f ? 1u << e : 0u;
   }
-  return d & ((1u << med3(a.c_out - co0, 0, 4)) - 1u);     // channels past the last one never fire
+  return d;
+}
+// the decisions that there are: of channels before the last one, of pixels before the last one
+__device__ __forceinline__ unsigned there_are(const DirectArgs& a, int co0, bool pixel) {
+  return pixel ? (1u << med3(a.c_out - co0, 0, 4)) - 1u : 0u;
 }
 
 // Four consecutive channels co0.. of an output pixel are read and stored in one piece where c_out allows, else one by one.
@@ -223,12 +227,16 @@ __device__ __forceinline__ i32x4 load_residual(const DirectArgs& a, int co0, lon
   return r;
 }
 
-// Output function (f of Eq. 1) for four consecutive channels co0.. of output pixel m: base and conditional sums, decisions in d; nothing is
-// stored where the pixel or the channels are past the end (live).
+template <typename Base>
+__device__ __forceinline__ char* y_at(const DirectArgs& a, int co0, long long m) {
+  return (char*)a.y + ((m * a.c_out + co0) << ((a.flags & kOut4) ? 2 : Base::kDtype == CG_I8 ? 0 : 1));
+}
+
+// Output function (f of Eq. 1) for four consecutive channels co0.. of output pixel m: base and conditional sums, decisions in d; to `at` (y_at)
+// where they are stored in one piece; nothing is stored where the pixel or the channels are past the end (live).
 template <typename Base, typename acc_t>
 __device__ __forceinline__ void finish4(const DirectArgs& a, const acc_t (&base)[4], const acc_t (&cond)[4], const Tab4<Base>& t, i32x4 res, unsigned d,
-                                        int co0, long long m, bool live) {
-  const long long o = m * a.c_out + co0;
+                                        int co0, long long m, char* at, bool live) {
   acc_t s[4];
   int on[4];
 #pragma unroll
@@ -250,6 +258,10 @@ __device__ __forceinline__ void finish4(const DirectArgs& a, const acc_t (&base)
                       __mul24((int)(int8_t)((uint32_t)res[0] >> (8 * e)), a.rq_res_mult);
         v[e] = med3(q >> a.rq_shift, low, 127);
       }
+    } else if ((a.flags & (kOut4 | kResidual)) == kOut4) {
+      const int floor = (a.flags & kRelu) ? 0 : -2147483647 - 1;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = s[e] < floor ? floor : s[e];
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -294,11 +306,11 @@ __device__ __forceinline__ void finish4(const DirectArgs& a, const acc_t (&base)
   }
   if (one_piece(a)) {
     if (a.flags & kOut4) {
-      if (live) *(i32x4*)((int32_t*)a.y + o) = v;
+      if (live) *(i32x4*)at = v;
     } else if constexpr (Base::kDtype == CG_I8) {
-      if (live) *(int32_t*)((int8_t*)a.y + o) = packed[0];
+      if (live) *(int32_t*)at = packed[0];
     } else {
-      if (live) *(int2*)((uint16_t*)a.y + o) = int2{packed[0], packed[1]};
+      if (live) *(int2*)at = int2{packed[0], packed[1]};
     }
     return;
   }
@@ -329,23 +341,6 @@ __device__ __forceinline__ unsigned masked(const DirectArgs& a, unsigned d, int 
   return d;
 }
 
-// The end of the layer for one unit of a tile (16 pixels x 16 channels, four channels a lane): decisions, output.
-template <typename Base, typename acc_t>
-__device__ __forceinline__ void finish_unit(const DirectArgs& a, const acc_t (&s)[4], const acc_t (&r)[4], const Tab4<Base>& t, i32x4 res,
-                                            int co0, int lg, long long m, bool valid) {
-  unsigned d = 0u;
-  if (a.flags & kGated) {
-    d = gate4<Base>(a, s, t.lo, t.hi, co0) & (valid ? ~0u : 0u);
-    if (a.chan_mask) d = masked(a, d, co0, m);
-    if (a.bitmap) {
-      const unsigned half = or_groups(d << (4 * lg));
-      const int at = (co0 - 4 * lg) >> 4;         // half word of the pixel
-      if (lg == 0 && valid && at < 2 * a.words) ((uint16_t*)a.bitmap)[m * (2 * a.words) + at] = (uint16_t)half;
-    }
-  }
-  if (!(a.flags & kGateOnly)) finish4<Base>(a, s, r, t, res, d, co0, m, valid && co0 < a.c_out);
-}
-
 // 8 wavefronts per workgroup at most
 constexpr int kMaxSplit = 8;
 
@@ -368,7 +363,7 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
   constexpr int kU = NU == 1 ? 4 : NU == 2 ? 2 : 1;
   constexpr bool kBlocks = SPLIT ? Base::kDtype != CG_I8 && NU < 8 : Base::kDtype == CG_F32;      // (see `carry`)
   constexpr bool kPair = !SPLIT && Base::kDtype == CG_BF16;                                        // (the same)
-  __shared__ __align__(16) i32x4 ex[SPLIT ? kMaxSplit * NU * 64 + (NU < 8 ? 1 : 0) : 1];     // [wavefront][unit][lane]; zeros
+  __shared__ __align__(16) i32x4 ex[SPLIT ? kMaxSplit * NU * 64 : 1];     // [wavefront][unit][lane]
   __shared__ __align__(16) i32x4 tab_at[SPLIT ? (NU < 8 ? NU * 4 * kTabs : 1) : 4 * NH * 4 * kTabs];    // [wavefront][(whole: sixteen channels)][table][four channels]
 
   load_args(p);
@@ -459,20 +454,20 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
     const int gap_at = ph ? gap_s : 0x7fffffff;     // the chunk from which on the gap is jumped
     const unsigned wgrp = (unsigned)(ph ? p.ks1 : p.ks0) * 2048u;
     const char* const wp = (ph ? p.w1 : p.w0) + (size_t)(half0 >> 1) * wgrp + (NH == 1 ? (half0 & 1) * 1024 : 0);
-    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc((void*)wp, (short)0, NH == 4 ? 2 * wgrp : wgrp, 0x00027000);
-    i32x4 x[2][kU][PF], w[2][kU][NH];
-    int kw = k0, kx = k0;                           // the next step whose weights, pixels are fetched
     const int k1 = k0 + n;
+    // (to the end of this wavefront's last step, so that a batch's steps past it are zeros; tiles of 64 channels have no such steps)
+    const __amdgpu_buffer_rsrc_t wr =
+        __builtin_amdgcn_make_buffer_rsrc((void*)wp, (short)0, NH == 4 ? 2 * (int)wgrp : k1 * 2048 - (NH == 1 ? 1024 : 0), 0x00027000);
+    i32x4 x[2][kU][PF], w[2][kU][NH];
+    int vw = lane * 16 + k0 * 2048, kx = k0;        // offset of the next step's weights; the next step whose pixels are fetched
     auto fetch_w = [&](auto bt) __attribute__((always_inline)) {
       constexpr int b = decltype(bt)::value;
 #pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int at = kU == 1 || kw < k1 ? lane * 16 : (int)kOut, sw = kU == 1 || kw < k1 ? kw * 2048 : 0;
+      for (int u = 0; u < kU; ++u)
 #pragma unroll
         for (int i = 0; i < NH; ++i)
-          w[b][u][i] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, at + (i & 1) * 1024, sw + (i >> 1) * (int)wgrp, 0));
-        ++kw;
-      }
+          w[b][u][i] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, vw + u * 2048 + (i & 1) * 1024, (i >> 1) * (int)wgrp, 0));
+      vw += kU * 2048;
     };
     // the walk's place: UNIFORM: the step's tap and first chunk, else the unit of this lane group
     int tap = 0, ci = 0, so = 0;                    // so (UNIFORM): offset of the step from its pixel's first tap
@@ -498,11 +493,10 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
       constexpr int b = decltype(bt)::value;
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
-        const bool on = kU == 1 || kx < k1;
-        ++kx;
+        const bool on = u == 0 || kx + u < k1;
         if constexpr (UNIFORM) {
 #pragma unroll
-          for (int f = 0; f < PF; ++f) x[b][u][f] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, on ? (int)vo[f] : (int)kOut, on ? so : 0, 0));
+          for (int f = 0; f < PF; ++f) x[b][u][f] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, on ? (int)vo[f] : (int)kOut, so, 0));
           so += 64;
           ci += 4;
           so += ci == gap_at ? gap16 : 0;
@@ -526,6 +520,7 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
           ci = next - (next >= nq ? nq : 0);
         }
       }
+      kx += kU;
     };
     auto mul = [&](auto bt) __attribute__((always_inline)) {
       constexpr int b = decltype(bt)::value;
@@ -703,9 +698,7 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
           acc_t s[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) s[e] = accP[f][i][e];
-          unsigned dd = gate4<Base>(p, s, lo[i], hi[i], co0);
-          if (m >= p.m_total) dd = 0u;
-          dd = masked(p, dd, co0, m);
+          const unsigned dd = masked(p, gate4<Base>(s, lo[i], hi[i]) & there_are(p, co0, m < p.m_total), co0, m);
           d[f][i] = dd;
           any |= dd != 0u;
         }
@@ -739,7 +732,7 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
           s[e] = accP[f][i][e];
           r[e] = accR[f][i][e];
         }
-        finish4<Base>(p, s, r, t, res[f][i], d[f][i], co0, m, m < p.m_total && co0 < p.c_out);
+        finish4<Base>(p, s, r, t, res[f][i], d[f][i], co0, m, y_at<Base>(p, co0, m), m < p.m_total && co0 < p.c_out);
       }
     }
   } else {
@@ -756,17 +749,26 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
     const int un = wave < NU ? wave : 0, uf = un / NH, co0 = (half0 + un % NH) * 16 + 4 * lg, m = m0 + 16 * uf + lj;
     const bool valid = m < p.m_total;
     i32x4 tabs = {0, 0, 0, 0}, res = {0, 0, 0, 0};  // (a lane's share of the tables: each lane's own four channels of all of them are 20 registers more)
-    auto load_end = [&]() __attribute__((always_inline)) {
+    // ... and what the end needs of its place is formed while the first operands are on their way
+    char* y_here = nullptr;
+    uint16_t* bits_here = nullptr;                  // the half word of the unit's pixel (of lanes that store one)
+    unsigned there = 0u;
+    auto prepare_end = [&]() __attribute__((always_inline)) {
       if (wave < NU) {
         if (lane < 4 * kTabs) tabs = *(const i32x4*)(p.tab + (lane >> 2) * p.tab_stride + (half0 + un % NH) * 64 + (lane & 3) * 16);
         res = load_residual<Base>(p, co0, m, valid && !gate_only);
+        there = there_are(p, co0, valid);
+        y_here = y_at<Base>(p, co0, m);
+        const int at = half0 + un % NH;
+        if (p.bitmap && lg == 0 && valid && at < 2 * p.words) bits_here = (uint16_t*)p.bitmap + ((long long)m * (2 * p.words) + at);
+        asm volatile("" : "+v"(there), "+v"(y_here), "+v"(bits_here));
       }
     };
     walk(std::bool_constant<kTwo>{}, ph, k0, n, acc, odd, [&]() __attribute__((always_inline)) {
       if ((p.flags & kClear) && blockIdx.x == 0 && tid < 2) p.total[tid] = 0u;
-      if constexpr (NU < 8) load_end();
+      if constexpr (NU < 8) prepare_end();
     });
-    if constexpr (NU == 8) load_end();              // (its 8 registers would be spilled)
+    if constexpr (NU == 8) prepare_end();           // (its 13 registers would be spilled)
 #pragma unroll
     for (int f = 0; f < PF; ++f)
 #pragma unroll
@@ -779,55 +781,65 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
         }
         ex[(wave * NU + f * NH + i) * 64 + lane] = v;
       }
-    if (NU < 8 && tid == 0) ex[kMaxSplit * NU * 64] = i32x4{0, 0, 0, 0};
     if (NU < 8 && wave < NU && lane < 4 * kTabs) tab_at[wave * (4 * kTabs) + lane] = tabs;
     __syncthreads();
     if (wave >= NU) return;
-    // The sums of the base and of the conditional wavefronts, in pairs.  Those of the other path, and past the last wavefront, are zeros:
-    // read as such from LDS, or (tiles of eight units, which leave no LDS) made so.
+    // The sums of the base and of the conditional wavefronts, each added up in pairs; a way of its own for every split.
     acc_t s[4], r[4];
-    auto add_up = [&](auto waves, int first, int end, acc_t (&sum)[4]) __attribute__((always_inline)) {
-      constexpr int N = decltype(waves)::value;
-      i32x4 v[N];
+    auto add_up = [&](auto first, auto waves, acc_t (&sum)[4]) __attribute__((always_inline)) {
+      constexpr int F = decltype(first)::value, N = decltype(waves)::value;
+      if constexpr (N == 0) {
 #pragma unroll
-      for (int j = 0; j < N; ++j) {
-        const bool in = j >= first && j < end;
-        if constexpr (NU < 8) {
-          v[j] = ex[in ? (j * NU + un) * 64 + lane : kMaxSplit * NU * 64];
-        } else {
-          v[j] = ex[(j * NU + un) * 64 + lane];
+        for (int e = 0; e < 4; ++e) sum[e] = 0;
+      } else {
+        acc_t t[N][4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[j][e] &= in ? -1 : 0;
+        for (int j = 0; j < N; ++j) {
+          const i32x4 v = ex[((F + j) * NU + un) * 64 + lane];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) set_bits(v[e], t[j][e]);
         }
+#pragma unroll
+        for (int step = 1; step < N; step *= 2)
+#pragma unroll
+          for (int j = 0; j + step < N; j += 2 * step)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t[j][e] += t[j + step][e];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] = t[0][e];
       }
-      acc_t t[N][4];
-#pragma unroll
-      for (int j = 0; j < N; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) set_bits(v[j][e], t[j][e]);
-#pragma unroll
-      for (int step = 1; step < N; step *= 2)
-#pragma unroll
-        for (int j = 0; j < N; j += 2 * step)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) t[j][e] += t[j + step][e];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sum[e] = t[0][e];
     };
-    if (NU == 8 || nw > 4) {
-      add_up(std::integral_constant<int, 8>{}, 0, nwb, s);
-      add_up(std::integral_constant<int, 8>{}, nwb, nw, r);
-    } else {
-      add_up(std::integral_constant<int, 4>{}, 0, nwb, s);
-      add_up(std::integral_constant<int, 4>{}, nwb, nw, r);
-    }
+    auto meet = [&](auto self, auto waves, auto base) __attribute__((always_inline)) -> void {
+      constexpr int N = decltype(waves)::value, B = decltype(base)::value;
+      if constexpr (B < N) {
+        if (nwb > B) return self(self, waves, std::integral_constant<int, B + 1>{});
+      }
+      add_up(std::integral_constant<int, 0>{}, base, s);
+      add_up(base, std::integral_constant<int, N - B>{}, r);
+    };
+    constexpr std::integral_constant<int, 1> one{};
+    if (NU == 8 || nw == 8)
+      meet(meet, std::integral_constant<int, 8>{}, one);
+    else if (NU == 4 || nw == 4)
+      meet(meet, std::integral_constant<int, 4>{}, one);
+    else
+      meet(meet, std::integral_constant<int, 2>{}, one);
     // (tiles of eight units leave no LDS: their tables lie where this wavefront has read the first one's sums of its unit)
     i32x4* const mine = NU < 8 ? tab_at + wave * (4 * kTabs) : ex + un * 64;
     if (NU == 8 && lane < 4 * kTabs) mine[lane] = tabs;
     __builtin_amdgcn_wave_barrier();
     Tab4<Base> tab;
     tab.take(p, mine + lg);
-    finish_unit<Base>(p, s, r, tab, res, co0, lg, m, valid);
+    unsigned d = 0u;
+    if (gated) {
+      d = gate4<Base>(s, tab.lo, tab.hi) & there;
+      if (p.chan_mask) d = masked(p, d, co0, m);
+      if (p.bitmap) {
+        const unsigned half = or_groups(d << (4 * lg));
+        if (bits_here) *bits_here = (uint16_t)half;
+      }
+    }
+    if (!gate_only) finish4<Base>(p, s, r, tab, res, d, co0, m, y_here, there != 0u);
   }
 }
 
