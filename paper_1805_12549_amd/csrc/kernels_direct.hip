@@ -126,28 +126,42 @@ __device__ __forceinline__ void load_rest(const DirectArgs& a) {
                "s"(a.words), "s"(a.rq_shift), "s"(a.rq_res_mult));
 }
 
+// The end of the layer is a few wavefronts' instructions with nothing beside them, each of them some 6 clocks, and the first time through also the
+// instruction cache's misses (700 of 2100 clocks).  So it is short code without a branch on a lane's value: a lane has Q = 1, 2 or 4 consecutive
+// channels of a pixel, as few as there are wavefronts for; choices by decision are selections of bits; a flag of the layer is a branch that all lanes
+// take.  (As conditional expressions and stores the sums of eight wavefronts alone took 2400 clocks, a store to a channel 1500.)
+
+typedef __attribute__((ext_vector_type(2))) int i32x2;
+template <int Q>
+using ints = std::conditional_t<Q == 1, int, std::conditional_t<Q == 2, i32x2, i32x4>>;
+template <int Q>
+__device__ __forceinline__ void take(const void* from, int (&v)[Q]) {
+  const ints<Q> t = *(const ints<Q>*)from;
+  if constexpr (Q == 1) {
+    v[0] = t;
+  } else {
+#pragma unroll
+    for (int e = 0; e < Q; ++e) v[e] = t[e];
+  }
+}
+
 constexpr int kTabs = 7;                         // tables that a layer's end reads
 
-// The per-channel tables of four channels, fetched ahead of the sums they are needed for.  (int8 layers whose requantisation
-// fits 32 bits: hi and h1 = bounds of the sum, s1 = what is added.)
-template <typename Base>
-struct Tab4 {
-  i32x4 lo, hi, s0, h0, s1, h1;                  // int8 layers: s0 = mult0, h0 = mult1, s1 = bias
-  // from a copy of the tables' sixteen channels, four pieces a table; what a flag leaves out is not used
-  __device__ __forceinline__ void take(const DirectArgs& a, const i32x4* q) {
+// The per-channel tables of a lane's channels.  (int8 layers whose requantisation fits 32 bits: hi and h1 = bounds of the sum, s1 = what is added.)
+template <typename Base, int Q>
+struct Tab {
+  int lo[Q], hi[Q], s0[Q], h0[Q], s1[Q], h1[Q];  // int8 layers: s0 = mult0, h0 = mult1, s1 = bias
+  // from a copy of the tables' sixteen channels, 64 bytes a table; what a flag leaves out is not used
+  __device__ __forceinline__ void take_all(const DirectArgs& a, const char* q) {
     const bool fit = Base::kDtype == CG_I8 && (a.flags & kFit32);
-    lo = q[0];
-    hi = q[4];
-    s0 = q[8];
-    h0 = q[12];
-    s1 = q[fit ? 20 : 16];
-    h1 = q[fit ? 24 : 20];
+    take(q, lo);
+    take(q + 64, hi);
+    take(q + 128, s0);
+    take(q + 192, h0);
+    take(q + (fit ? 320 : 256), s1);
+    take(q + (fit ? 384 : 320), h1);
   }
 };
-
-// The end of the layer is one wavefront's instructions with nothing beside them, so it is written without a branch on a lane's value: choices
-// by decision are selections of bits, and a flag of the layer is a branch that all lanes take.  (As conditional expressions and stores the
-// sums of eight wavefronts alone took 2400 clocks, a store to a channel 1500.)
 
 // the bits of a where m has ones, of b elsewhere
 __device__ __forceinline__ int select_bits(int m, int a, int b) { return (a & m) | (b & ~m); }
@@ -166,12 +180,12 @@ __device__ __forceinline__ int med3(int v, int lo, int hi) {
   return r;
 }
 
-// decisions of four consecutive channels from their base sums
-template <typename Base, typename acc_t>
-__device__ __forceinline__ unsigned gate4(const acc_t (&s)[4], i32x4 lo, i32x4 hi) {
+// decisions of a lane's channels from their base sums
+template <typename Base, int Q, typename acc_t>
+__device__ __forceinline__ unsigned gate_of(const acc_t (&s)[Q], const int (&lo)[Q], const int (&hi)[Q]) {
   unsigned d = 0u;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
+  for (int e = 0; e < Q; ++e) {
     bool f;
     if constexpr (Base::kDtype == CG_I8)
       f = Base::fires(s[e], lo[e], 0);
@@ -182,12 +196,14 @@ __device__ __forceinline__ unsigned gate4(const acc_t (&s)[4], i32x4 lo, i32x4 h
   return d;
 }
 // the decisions that there are: of channels before the last one, of pixels before the last one
+template <int Q>
 __device__ __forceinline__ unsigned there_are(const DirectArgs& a, int co0, bool pixel) {
-  return pixel ? (1u << med3(a.c_out - co0, 0, 4)) - 1u : 0u;
+  return pixel ? (1u << med3(a.c_out - co0, 0, Q)) - 1u : 0u;
 }
 
-// Four consecutive channels co0.. of an output pixel are read and stored in one piece where c_out allows, else one by one.
-__device__ __forceinline__ bool one_piece(const DirectArgs& a) { return !((a.c_out & 3) || (a.flags & kShuffle)); }
+// Consecutive channels co0.. of an output pixel are read and stored in one piece where c_out allows, else one by one.
+template <int Q>
+__device__ __forceinline__ bool one_piece(const DirectArgs& a) { return !((a.c_out & (Q - 1)) || (a.flags & kShuffle)); }
 __device__ __forceinline__ long long element_at(const DirectArgs& a, long long m, int co) {
   if (!(a.flags & kShuffle)) return m * a.c_out + co;
   const int grp = (int)quot(co, a.cpg);
@@ -195,26 +211,31 @@ __device__ __forceinline__ long long element_at(const DirectArgs& a, long long m
 }
 
 // the residual of those channels, as it lies in memory (fetched ahead of the sums: its latency is 0.5 us of a finish)
-template <typename Base>
+template <typename Base, int Q>
 __device__ __forceinline__ i32x4 load_residual(const DirectArgs& a, int co0, long long m, bool valid) {
   i32x4 r = {0, 0, 0, 0};
   if (!(a.flags & kResidual) || !valid || co0 >= a.c_out) return r;
   constexpr bool I8 = Base::kDtype == CG_I8;
-  if (one_piece(a)) {
+  if (Q > 1 && one_piece<Q>(a)) {
     const long long o = m * a.c_out + co0;
     if constexpr (I8) {
-      r[0] = *(const int*)((const int8_t*)a.residual + o);
+      if constexpr (Q == 4)
+        r[0] = *(const int*)((const int8_t*)a.residual + o);
+      else
+        r[0] = *(const uint16_t*)((const int8_t*)a.residual + o);
     } else if (a.flags & kOut4) {
-      r = *(const i32x4*)((const float*)a.residual + o);
+      int v[Q];
+      take((const float*)a.residual + o, v);
+#pragma unroll
+      for (int e = 0; e < Q; ++e) r[e] = v[e];
     } else {
-      const uint2 q = *(const uint2*)((const uint16_t*)a.residual + o);
-      r[0] = (int)q.x;
-      r[1] = (int)q.y;
+      r[0] = *(const int*)((const uint16_t*)a.residual + o);
+      if constexpr (Q == 4) r[1] = *(const int*)((const uint16_t*)a.residual + o + 2);
     }
     return r;
   }
 #pragma unroll
-  for (int e = 0; e < 4; ++e)
+  for (int e = 0; e < Q; ++e)
     if (co0 + e < a.c_out) {
       const long long o = element_at(a, m, co0 + e);
       if constexpr (I8)
@@ -227,33 +248,37 @@ __device__ __forceinline__ i32x4 load_residual(const DirectArgs& a, int co0, lon
   return r;
 }
 
+// where those channels are stored in one piece
 template <typename Base>
 __device__ __forceinline__ char* y_at(const DirectArgs& a, int co0, long long m) {
   return (char*)a.y + ((m * a.c_out + co0) << ((a.flags & kOut4) ? 2 : Base::kDtype == CG_I8 ? 0 : 1));
 }
 
-// Output function (f of Eq. 1) for four consecutive channels co0.. of output pixel m: base and conditional sums, decisions in d; to `at` (y_at)
+// Output function (f of Eq. 1) for consecutive channels co0.. of output pixel m: base and conditional sums, decisions in d; to `at` (y_at)
 // where they are stored in one piece; nothing is stored where the pixel or the channels are past the end (live).
-template <typename Base, typename acc_t>
-__device__ __forceinline__ void finish4(const DirectArgs& a, const acc_t (&base)[4], const acc_t (&cond)[4], const Tab4<Base>& t, i32x4 res, unsigned d,
-                                        int co0, long long m, char* at, bool live) {
-  acc_t s[4];
-  int on[4];
+template <typename Base, int Q, typename acc_t>
+__device__ __forceinline__ void finish(const DirectArgs& a, const acc_t (&base)[Q], const acc_t (&cond)[Q], const Tab<Base, Q>& t, i32x4 res, unsigned d,
+                                       int co0, long long m, char* at, bool live) {
+  acc_t s[Q];
+  int on[Q];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
+  for (int e = 0; e < Q; ++e) {
     on[e] = ones_if(d, e);
     acc_t c;
     set_bits(bits_of(cond[e]) & on[e], c);
     s[e] = base[e] + c;
   }
-  if (!(a.flags & kGated)) on[0] = on[1] = on[2] = on[3] = -1;             // (a dense layer takes the second pair)
-  i32x4 v;                                       // what is stored, 4-byte outputs
+  if (!(a.flags & kGated)) {                     // (a dense layer takes the second pair)
+#pragma unroll
+    for (int e = 0; e < Q; ++e) on[e] = -1;
+  }
+  int v[Q];                                      // what is stored, 4-byte outputs
   int packed[2] = {0, 0};                        // narrow ones
   if constexpr (Base::kDtype == CG_I8) {
     const int low = (a.flags & kRelu) ? 0 : -128;
     if (a.flags & kFit32) {                      // (as in the row-tiled kernel)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
+      for (int e = 0; e < Q; ++e) {
         const int q = __mul24(med3(s[e], t.hi[e], t.h1[e]), select_bits(on[e], t.h0[e], t.s0[e])) + t.s1[e] +
                       __mul24((int)(int8_t)((uint32_t)res[0] >> (8 * e)), a.rq_res_mult);
         v[e] = med3(q >> a.rq_shift, low, 127);
@@ -261,10 +286,10 @@ __device__ __forceinline__ void finish4(const DirectArgs& a, const acc_t (&base)
     } else if ((a.flags & (kOut4 | kResidual)) == kOut4) {
       const int floor = (a.flags & kRelu) ? 0 : -2147483647 - 1;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = s[e] < floor ? floor : s[e];
+      for (int e = 0; e < Q; ++e) v[e] = s[e] < floor ? floor : s[e];
     } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
+      for (int e = 0; e < Q; ++e) {
         const long long r = (long long)(int8_t)((uint32_t)res[0] >> (8 * e)) * a.rq_res_mult;
         long long q;
         if (a.flags & kOut4) {
@@ -281,41 +306,54 @@ __device__ __forceinline__ void finish4(const DirectArgs& a, const acc_t (&base)
         v[e] = (int32_t)q;
       }
     }
-    packed[0] = (v[0] & 0xff) | ((v[1] & 0xff) << 8) | ((v[2] & 0xff) << 16) | ((v[3] & 0xff) << 24);
+#pragma unroll
+    for (int e = 0; e < Q; ++e) packed[0] |= (v[e] & 0xff) << (8 * e);
   } else {
     const float relu_lo = (a.flags & kRelu) ? 0.0f : __builtin_nanf("");
     if (a.flags & kAffine) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int e = 0; e < Q; ++e)
         s[e] = fmaf(__int_as_float(select_bits(on[e], t.s1[e], t.s0[e])), s[e], __int_as_float(select_bits(on[e], t.h1[e], t.h0[e])));
     }
     if (a.flags & kResidual) {
       if (a.flags & kOut4) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s[e] += __int_as_float(res[e]);
+        for (int e = 0; e < Q; ++e) s[e] += __int_as_float(res[e]);
       } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s[e] += __uint_as_float(e & 1 ? (unsigned)res[e >> 1] & 0xffff0000u : (unsigned)res[e >> 1] << 16);
+        for (int e = 0; e < Q; ++e) s[e] += __uint_as_float(e & 1 ? (unsigned)res[e >> 1] & 0xffff0000u : (unsigned)res[e >> 1] << 16);
       }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = __float_as_int(max_of(s[e], relu_lo));
+    for (int e = 0; e < Q; ++e) v[e] = __float_as_int(max_of(s[e], relu_lo));
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
-      packed[e] = (int)((uint32_t)float_to_bf16(__int_as_float(v[2 * e])) | ((uint32_t)float_to_bf16(__int_as_float(v[2 * e + 1])) << 16));
+    for (int e = 0; e < Q; ++e) packed[e >> 1] |= (int)((uint32_t)float_to_bf16(__int_as_float(v[e])) << (16 * (e & 1)));
   }
-  if (one_piece(a)) {
+  if (one_piece<Q>(a)) {
     if (a.flags & kOut4) {
-      if (live) *(i32x4*)at = v;
-    } else if constexpr (Base::kDtype == CG_I8) {
-      if (live) *(int32_t*)at = packed[0];
+      if constexpr (Q == 1) {
+        if (live) *(int*)at = v[0];
+      } else if constexpr (Q == 2) {
+        if (live) *(i32x2*)at = i32x2{v[0], v[1]};
+      } else {
+        if (live) *(i32x4*)at = i32x4{v[0], v[1], v[2], v[3]};
+      }
     } else {
-      if (live) *(int2*)at = int2{packed[0], packed[1]};
+      constexpr int kBytes = Q * (Base::kDtype == CG_I8 ? 1 : 2);
+      if constexpr (kBytes == 1) {
+        if (live) *(uint8_t*)at = (uint8_t)packed[0];
+      } else if constexpr (kBytes == 2) {
+        if (live) *(uint16_t*)at = (uint16_t)packed[0];
+      } else if constexpr (kBytes == 4) {
+        if (live) *(int*)at = packed[0];
+      } else {
+        if (live) *(i32x2*)at = i32x2{packed[0], packed[1]};
+      }
     }
     return;
   }
 #pragma unroll
-  for (int e = 0; e < 4; ++e)
+  for (int e = 0; e < Q; ++e)
     if (live && co0 + e < a.c_out) {
       const long long oe = element_at(a, m, co0 + e);
       if (a.flags & kOut4)
@@ -335,7 +373,18 @@ __device__ __forceinline__ unsigned or_groups(unsigned v) {
   return (unsigned)r[0] | (unsigned)r[1];
 }
 
-// The decisions of four channels of pixel m as the channel-wise gate (Sec. 3.2) leaves them
+// The sixteen decisions of a pixel from its lanes' (16/Q of them, side by side, the first channels first): in all of them.
+template <int Q>
+__device__ __forceinline__ unsigned sixteen(unsigned d, int lane) {
+  if constexpr (Q == 1) return (unsigned)(__ballot(d != 0u) >> (lane & 48)) & 0xffffu;
+  unsigned v = d << ((lane & (16 / Q - 1)) * Q);
+  v |= (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, true);       // quad_perm [1,0,3,2]
+  v |= (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x4e, 0xf, 0xf, true);       // quad_perm [2,3,0,1]
+  if constexpr (Q == 2) v |= (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xf, 0xf, true);      // row_half_mirror
+  return v;
+}
+
+// The decisions of a lane's channels of pixel m as the channel-wise gate (Sec. 3.2) leaves them
 __device__ __forceinline__ unsigned masked(const DirectArgs& a, unsigned d, int co0, long long m) {
   if (a.chan_mask && d) d &= a.chan_mask[(long long)quot((unsigned)m, a.hw) * a.words + (co0 >> 5)] >> (co0 & 31);
   return d;
@@ -363,8 +412,8 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
   constexpr int kU = NU == 1 ? 4 : NU == 2 ? 2 : 1;
   constexpr bool kBlocks = SPLIT ? Base::kDtype != CG_I8 && NU < 8 : Base::kDtype == CG_F32;      // (see `carry`)
   constexpr bool kPair = !SPLIT && Base::kDtype == CG_BF16;                                        // (the same)
-  __shared__ __align__(16) i32x4 ex[SPLIT ? kMaxSplit * NU * 64 : 1];     // [wavefront][unit][lane]
-  __shared__ __align__(16) i32x4 tab_at[SPLIT ? (NU < 8 ? NU * 4 * kTabs : 1) : 4 * NH * 4 * kTabs];    // [wavefront][(whole: sixteen channels)][table][four channels]
+  __shared__ __align__(16) i32x4 ex[SPLIT ? kMaxSplit * NU * 64 : 1];     // [wavefront][unit][pixel][four channels, rotated against bank conflicts]
+  __shared__ __align__(16) i32x4 tab_at[SPLIT ? (NU < 8 ? (NU == 1 ? 4 : kMaxSplit) * 4 * kTabs : 1) : 4 * NH * 4 * kTabs];    // [wavefront][(whole: sixteen channels)][table][four channels]
 
   load_args(p);
   load_rest(p);
@@ -683,11 +732,11 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
       for (int i = 0; i < NH; ++i) d[f][i] = 0u;
     if (gated) {
       bool any = false;
-      i32x4 lo[NH], hi[NH];
+      int lo[NH][4], hi[NH][4];
 #pragma unroll
       for (int i = 0; i < NH; ++i) {
-        lo[i] = mine[i * (4 * kTabs) + lg];
-        hi[i] = mine[i * (4 * kTabs) + 4 + lg];
+        take(&mine[i * (4 * kTabs) + lg], lo[i]);
+        take(&mine[i * (4 * kTabs) + 4 + lg], hi[i]);
       }
 #pragma unroll
       for (int f = 0; f < PF; ++f) {
@@ -698,7 +747,7 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
           acc_t s[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) s[e] = accP[f][i][e];
-          const unsigned dd = masked(p, gate4<Base>(s, lo[i], hi[i]) & there_are(p, co0, m < p.m_total), co0, m);
+          const unsigned dd = masked(p, gate_of<Base>(s, lo[i], hi[i]) & there_are<4>(p, co0, m < p.m_total), co0, m);
           d[f][i] = dd;
           any |= dd != 0u;
         }
@@ -717,11 +766,11 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
 #pragma unroll
     for (int f = 0; f < PF; ++f)
 #pragma unroll
-      for (int i = 0; i < NH; ++i) res[f][i] = load_residual<Base>(p, (half0 + i) * 16 + 4 * lg, m0 + 16 * f + lj, m0 + 16 * f + lj < p.m_total);
+      for (int i = 0; i < NH; ++i) res[f][i] = load_residual<Base, 4>(p, (half0 + i) * 16 + 4 * lg, m0 + 16 * f + lj, m0 + 16 * f + lj < p.m_total);
 #pragma unroll
     for (int i = 0; i < NH; ++i) {
-      Tab4<Base> t;
-      t.take(p, mine + i * (4 * kTabs) + lg);
+      Tab<Base, 4> t;
+      t.take_all(p, (const char*)(mine + i * (4 * kTabs) + lg));
 #pragma unroll
       for (int f = 0; f < PF; ++f) {
         const long long m = m0 + 16 * f + lj;
@@ -732,7 +781,7 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
           s[e] = accP[f][i][e];
           r[e] = accR[f][i][e];
         }
-        finish4<Base>(p, s, r, t, res[f][i], d[f][i], co0, m, y_at<Base>(p, co0, m), m < p.m_total && co0 < p.c_out);
+        finish<Base>(p, s, r, t, res[f][i], d[f][i], co0, m, y_at<Base>(p, co0, m), m < p.m_total && co0 < p.c_out);
       }
     }
   } else {
@@ -745,24 +794,41 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
     acc4 acc[PF][NH], odd[PF][NH];
     zero(acc);
     zero(odd);
-    // this wavefront's unit of the tile's end (the plan has a wavefront for each): its tables and residual arrive behind the sums
-    const int un = wave < NU ? wave : 0, uf = un / NH, co0 = (half0 + un % NH) * 16 + 4 * lg, m = m0 + 16 * uf + lj;
-    const bool valid = m < p.m_total;
+    // The tile's end: wavefront `wave` has the unit un of it, in shares of 4*Q pixels where there are several wavefronts to a unit (the plan has at least
+    // one); its tables, residual and places arrive behind the first operands.
+    auto with_q = [&](auto f) __attribute__((always_inline)) {
+      constexpr auto q_of = [](int waves) { return waves >= 4 * NU ? 1 : waves >= 2 * NU ? 2 : 4; };
+      if (NU == 8 || nw == 8)
+        f(std::integral_constant<int, q_of(8)>{}, std::integral_constant<int, 8>{});
+      else if (NU == 4 || nw == 4)
+        f(std::integral_constant<int, q_of(4)>{}, std::integral_constant<int, 4>{});
+      else
+        f(std::integral_constant<int, q_of(2)>{}, std::integral_constant<int, 2>{});
+    };
+    const int un = wave % NU, sub = wave / NU, uf = un / NH, half = half0 + un % NH;
+    const bool ends = NU == 1 ? wave < 4 : true;    // (a unit has four shares at most)
     i32x4 tabs = {0, 0, 0, 0}, res = {0, 0, 0, 0};  // (a lane's share of the tables: each lane's own four channels of all of them are 20 registers more)
-    // ... and what the end needs of its place is formed while the first operands are on their way
     char* y_here = nullptr;
-    uint16_t* bits_here = nullptr;                  // the half word of the unit's pixel (of lanes that store one)
+    uint16_t* bits_here = nullptr;                  // the half word of the lane's pixel (of lanes that store one)
     unsigned there = 0u;
+    int m = 0, co0 = 0, ex_here = 0, tab_here = 0;
     auto prepare_end = [&]() __attribute__((always_inline)) {
-      if (wave < NU) {
-        if (lane < 4 * kTabs) tabs = *(const i32x4*)(p.tab + (lane >> 2) * p.tab_stride + (half0 + un % NH) * 64 + (lane & 3) * 16);
-        res = load_residual<Base>(p, co0, m, valid && !gate_only);
-        there = there_are(p, co0, valid);
+      if (!ends) return;
+      with_q([&](auto qc, auto) __attribute__((always_inline)) {
+        constexpr int Q = decltype(qc)::value, L = 16 / Q;      // lanes to a pixel
+        const int ch = (lane & (L - 1)) * Q, px = sub * 4 * Q + lane / L;
+        if (lane < 4 * kTabs) tabs = *(const i32x4*)(p.tab + (lane >> 2) * p.tab_stride + half * 64 + (lane & 3) * 16);
+        m = m0 + 16 * uf + px;
+        co0 = half * 16 + ch;
+        const bool valid = m < p.m_total;
+        res = load_residual<Base, Q>(p, co0, m, valid && !gate_only);
+        there = there_are<Q>(p, co0, valid);
         y_here = y_at<Base>(p, co0, m);
-        const int at = half0 + un % NH;
-        if (p.bitmap && lg == 0 && valid && at < 2 * p.words) bits_here = (uint16_t*)p.bitmap + ((long long)m * (2 * p.words) + at);
-        asm volatile("" : "+v"(there), "+v"(y_here), "+v"(bits_here));
-      }
+        if (p.bitmap && ch == 0 && valid && half < 2 * p.words) bits_here = (uint16_t*)p.bitmap + ((long long)m * (2 * p.words) + half);
+        ex_here = un * 1024 + px * 64 + ((ch >> 2) ^ (px >> 2)) * 16 + (ch & 3) * 4;
+        tab_here = ch * 4;
+        asm volatile("" : "+v"(there), "+v"(y_here), "+v"(bits_here), "+v"(ex_here), "+v"(tab_here));
+      });
     };
     walk(std::bool_constant<kTwo>{}, ph, k0, n, acc, odd, [&]() __attribute__((always_inline)) {
       if ((p.flags & kClear) && blockIdx.x == 0 && tid < 2) p.total[tid] = 0u;
@@ -779,67 +845,64 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
           const acc_t sv = acc[f][i][e];
           v[e] = bits_of(sv);
         }
-        ex[(wave * NU + f * NH + i) * 64 + lane] = v;
+        ex[(wave * NU + f * NH + i) * 64 + lj * 4 + (lg ^ (lj >> 2))] = v;
       }
-    if (NU < 8 && wave < NU && lane < 4 * kTabs) tab_at[wave * (4 * kTabs) + lane] = tabs;
+    if (NU < 8 && ends && lane < 4 * kTabs) tab_at[wave * (4 * kTabs) + lane] = tabs;
     __syncthreads();
-    if (wave >= NU) return;
-    // The sums of the base and of the conditional wavefronts, each added up in pairs; a way of its own for every split.
-    acc_t s[4], r[4];
-    auto add_up = [&](auto first, auto waves, acc_t (&sum)[4]) __attribute__((always_inline)) {
-      constexpr int F = decltype(first)::value, N = decltype(waves)::value;
-      if constexpr (N == 0) {
+    if (!ends) return;
+    with_q([&](auto qc, auto wavesc) __attribute__((always_inline)) {
+      constexpr int Q = decltype(qc)::value, N = decltype(wavesc)::value;
+      // The sums of the base and of the conditional wavefronts, each added up in pairs; a way of its own for every split.
+      acc_t s[Q], r[Q];
+      auto add_up = [&](auto first, auto count, acc_t (&sum)[Q]) __attribute__((always_inline)) {
+        constexpr int F = decltype(first)::value, C = decltype(count)::value;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum[e] = 0;
-      } else {
-        acc_t t[N][4];
+        for (int e = 0; e < Q; ++e) sum[e] = 0;
+        if constexpr (C > 0) {
+          acc_t t[C][Q];
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-          const i32x4 v = ex[((F + j) * NU + un) * 64 + lane];
+          for (int j = 0; j < C; ++j) {
+            int v[Q];
+            take((const char*)ex + ex_here + (F + j) * (NU * 1024), v);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) set_bits(v[e], t[j][e]);
+            for (int e = 0; e < Q; ++e) set_bits(v[e], t[j][e]);
+          }
+#pragma unroll
+          for (int step = 1; step < C; step *= 2)
+#pragma unroll
+            for (int j = 0; j + step < C; j += 2 * step)
+#pragma unroll
+              for (int e = 0; e < Q; ++e) t[j][e] += t[j + step][e];
+#pragma unroll
+          for (int e = 0; e < Q; ++e) sum[e] = t[0][e];
         }
-#pragma unroll
-        for (int step = 1; step < N; step *= 2)
-#pragma unroll
-          for (int j = 0; j + step < N; j += 2 * step)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) t[j][e] += t[j + step][e];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sum[e] = t[0][e];
+      };
+      auto meet = [&](auto self, auto base) __attribute__((always_inline)) -> void {
+        constexpr int B = decltype(base)::value;
+        if constexpr (B < N) {
+          if (nwb > B) return self(self, std::integral_constant<int, B + 1>{});
+        }
+        add_up(std::integral_constant<int, 0>{}, base, s);
+        add_up(base, std::integral_constant<int, N - B>{}, r);
+      };
+      meet(meet, std::integral_constant<int, 1>{});
+      // (tiles of eight units leave no LDS: their tables lie where this wavefront has read the first one's sums of its unit)
+      i32x4* const mine = NU < 8 ? tab_at + wave * (4 * kTabs) : ex + un * 64;
+      if (NU == 8 && lane < 4 * kTabs) mine[lane] = tabs;
+      __builtin_amdgcn_wave_barrier();
+      Tab<Base, Q> tab;
+      tab.take_all(p, (const char*)mine + tab_here);
+      unsigned d = 0u;
+      if (gated) {
+        d = gate_of<Base>(s, tab.lo, tab.hi) & there;
+        if (p.chan_mask) d = masked(p, d, co0, m);
+        if (p.bitmap) {
+          const unsigned word = sixteen<Q>(d, lane);
+          if (bits_here) *bits_here = (uint16_t)word;
+        }
       }
-    };
-    auto meet = [&](auto self, auto waves, auto base) __attribute__((always_inline)) -> void {
-      constexpr int N = decltype(waves)::value, B = decltype(base)::value;
-      if constexpr (B < N) {
-        if (nwb > B) return self(self, waves, std::integral_constant<int, B + 1>{});
-      }
-      add_up(std::integral_constant<int, 0>{}, base, s);
-      add_up(base, std::integral_constant<int, N - B>{}, r);
-    };
-    constexpr std::integral_constant<int, 1> one{};
-    if (NU == 8 || nw == 8)
-      meet(meet, std::integral_constant<int, 8>{}, one);
-    else if (NU == 4 || nw == 4)
-      meet(meet, std::integral_constant<int, 4>{}, one);
-    else
-      meet(meet, std::integral_constant<int, 2>{}, one);
-    // (tiles of eight units leave no LDS: their tables lie where this wavefront has read the first one's sums of its unit)
-    i32x4* const mine = NU < 8 ? tab_at + wave * (4 * kTabs) : ex + un * 64;
-    if (NU == 8 && lane < 4 * kTabs) mine[lane] = tabs;
-    __builtin_amdgcn_wave_barrier();
-    Tab4<Base> tab;
-    tab.take(p, mine + lg);
-    unsigned d = 0u;
-    if (gated) {
-      d = gate4<Base>(s, tab.lo, tab.hi) & there;
-      if (p.chan_mask) d = masked(p, d, co0, m);
-      if (p.bitmap) {
-        const unsigned half = or_groups(d << (4 * lg));
-        if (bits_here) *bits_here = (uint16_t)half;
-      }
-    }
-    if (!gate_only) finish4<Base>(p, s, r, tab, res, d, co0, m, y_here, there != 0u);
+      if (!gate_only) finish<Base>(p, s, r, tab, res, d, co0, m, y_here, there != 0u);
+    });
   }
 }
 
