@@ -41,9 +41,12 @@
 // side of the products), at 256 and 512 the LDS reads and, for few images, the start: the first stage of all workgroups
 // (some 40 KB each, 10 MB for the chip) lands 2.7 us after the first instruction.  Arguments asked for at once and a column
 // that is formed once per wavefront have the loads out after 1.1 us instead of 1.9: 64 channels at 56x56, 64 images 22.9 -> 22.3
-// us, 128 to 256 at 28x28 stride 2 16.1 -> 15.6, int8 128 at 28x28, 32 images 10.4 -> 10.1.  The matrix cores are busy for 15 to 26 % of a layer at 64 images.  Measured in a graph with
-// rotated buffers, clustered maps at a firing rate of 0.3, before (barrier-coupled workgroups with the pixels listed anew for
-// the conditional path) and now, us:
+// us, 128 to 256 at 28x28 stride 2 16.1 -> 15.6, int8 128 at 28x28, 32 images 10.4 -> 10.1.  The matrix cores are busy for 15 to 26 % of a layer at 64 images.
+// Outputs: addresses of 32 bits in buffer accesses (the range check drops lanes without a pixel), one bit-field instruction to a decision, scale and shift
+// read ahead, one question instead of four for whether there are any: 64 channels at 56x56, 256 images 94.4 -> 86.5 us, 128 at 28x28 74.1 -> 68.9,
+// 256 at 14x14 61.5 -> 58.7, int8 128 at 28x28, 32 images 9.8 -> 9.4, 1x1 of 192 to 128 channels 12.3 -> 11.6.  Measured in a graph with
+// rotated buffers, clustered maps at a firing rate of 0.3, this form against an earlier one (barrier-coupled workgroups with the pixels listed anew for
+// the conditional path), before and after, us:
 //   bf16, scale/shift, residual and ReLU
 //         64 channels at 56x56, 64 images 36.4 -> 28.9, 256: 116 -> 95;  128 at 28x28, 64: 25.1 -> 25.2, 128: 45.4 -> 41.3,
 //         256: 74.4 -> 70.6;  256 at 14x14, 64: 24.2 -> 20.5, 128: 33.5 -> 34.8, 256: 56.4 -> 60.5;  512 at 7x7, 64: 29.6 ->
@@ -58,7 +61,8 @@
 // 15.1, 64 at 56x56, 8 images 8.1 -> 7.6, 128 at 16x16, 32 images 9.1 -> 8.6, int8 256 at 14x14, 32 images 10.5 -> 9.8, 512 at
 // 7x7, 64 images 15.3 -> 14.6; 256 at 14x14 by the images, 16 12.0 -> 11.4, 24 12.4 -> 12.2, slower 28 to 40 (32 13.1 -> 13.3, 40 13.7 -> 14.1).  A stage still takes 1100 clocks at 256 channels where its
 // products take 576, its loads 710 (a 1 KB load is 20 clocks of the memory path, 32 where it is made of pieces of 32 bytes)
-// and its LDS accesses 800.
+// and its LDS accesses 800.  (The other way to share a fragment, every second K step for all 64 channels, a quarter fewer LDS reads, and sums that
+// meet in LDS: 1.1 to 1.6 us slower throughout.  The loads stay, and both meetings and two more stage loops are met cold.)
 //
 // A patch is stored [pixel slot][CPS chunk positions]; chunk q of slot s sits at position q ^ f(s),
 // f(s) = (s >> 2) & 3 (CPS = 4) or (s >> 3) & 1 (CPS = 2), which spreads the operand reads over the LDS
@@ -95,6 +99,18 @@ constexpr int kMaxPatchLoads = 12;           // 1 KB load instructions per loadi
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(16))) int i32x16;
 
+// d = 2*d + (v >= t) for v3, v2, v1, v0 in turn: int8 as one statement (between two the compiler puts a wait), bf16 as four
+// (1x1 layers of 192 channels 11.5 us against 11.8: the table's next entries arrive in between).
+#define CG_SHIFT_IN1(cmp, v, t) cmp " vcc, " v ", " t "\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+#define CG_SHIFT_IN4_APART(cmp)                                                             \
+  asm(CG_SHIFT_IN1(cmp, "%1", "%2") : "+v"(d) : "v"(v3), "v"(t[3]) : "vcc"); \
+  asm(CG_SHIFT_IN1(cmp, "%1", "%2") : "+v"(d) : "v"(v2), "v"(t[2]) : "vcc"); \
+  asm(CG_SHIFT_IN1(cmp, "%1", "%2") : "+v"(d) : "v"(v1), "v"(t[1]) : "vcc"); \
+  asm(CG_SHIFT_IN1(cmp, "%1", "%2") : "+v"(d) : "v"(v0), "v"(t[0]) : "vcc")
+#define CG_SHIFT_IN4(cmp)                                                                                                  \
+  asm(CG_SHIFT_IN1(cmp, "%4", "%8") CG_SHIFT_IN1(cmp, "%3", "%7") CG_SHIFT_IN1(cmp, "%2", "%6") CG_SHIFT_IN1(cmp, "%1", "%5") \
+      : "+v"(d) : "v"(v0), "v"(v1), "v"(v2), "v"(v3), "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]) : "vcc")
+
 // 32x32 output block; lane l supplies row / column l%32 and the 16-byte K chunk l/32 of either
 // operand; it receives column l%32, rows 8*(i/4) + 4*(l/32) + i%4 in register i.
 struct Bf16Rows {
@@ -105,13 +121,12 @@ struct Bf16Rows {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, rows), __builtin_bit_cast(bf16x8, cols),
                                                    c, 0, 0, 0);
   }
-  // d = 2*d + (v >= t)
-  static __device__ __forceinline__ void shift_in(unsigned& d, float v, int t) {
-    asm("v_cmp_ge_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(d) : "v"(v), "v"(t) : "vcc");
+  static __device__ __forceinline__ void shift_in4(unsigned& d, float v0, float v1, float v2, float v3, i32x4 t) {
+    CG_SHIFT_IN4_APART("v_cmp_ge_f32");
   }
-  // ... (v <= t)
-  static __device__ __forceinline__ void shift_in_le(unsigned& d, float v, int t) {
-    asm("v_cmp_le_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(d) : "v"(v), "v"(t) : "vcc");
+  // (v <= t)
+  static __device__ __forceinline__ void shift_in4_le(unsigned& d, float v0, float v1, float v2, float v3, i32x4 t) {
+    CG_SHIFT_IN4_APART("v_cmp_le_f32");
   }
 };
 
@@ -122,10 +137,11 @@ struct I8Rows {
   static __device__ __forceinline__ acc16 mfma(i32x4 rows, i32x4 cols, acc16 c) {
     return __builtin_amdgcn_mfma_i32_32x32x32_i8(rows, cols, c, 0, 0, 0);
   }
-  static __device__ __forceinline__ void shift_in(unsigned& d, int v, int t) {
-    asm("v_cmp_ge_i32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(d) : "v"(v), "v"(t) : "vcc");
-  }
+  static __device__ __forceinline__ void shift_in4(unsigned& d, int v0, int v1, int v2, int v3, i32x4 t) { CG_SHIFT_IN4("v_cmp_ge_i32"); }
 };
+#undef CG_SHIFT_IN4
+#undef CG_SHIFT_IN4_APART
+#undef CG_SHIFT_IN1
 
 __device__ __forceinline__ int as_bits(float f) { return __float_as_int(f); }
 __device__ __forceinline__ int as_bits(int v) { return v; }
@@ -171,6 +187,16 @@ __device__ __forceinline__ int bf16_pair(float a, float b) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
   return __builtin_bit_cast(int, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
+
+// all ones where bit I + e of d is set, e = 0 .. 3 (as expressions they become a comparison for every use: three instructions and a wait
+// instead of one; one to an asm statement, each is waited for)
+template <int I>
+__device__ __forceinline__ void ones_if4(unsigned d, int (&m)[4]) {
+  asm("v_bfe_i32 %0, %4, %5, 1\n\tv_bfe_i32 %1, %4, %6, 1\n\tv_bfe_i32 %2, %4, %7, 1\n\tv_bfe_i32 %3, %4, %8, 1"
+      : "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=v"(m[3])
+      : "v"(d), "n"(I), "n"(I + 1), "n"(I + 2), "n"(I + 3));
+}
+__device__ __forceinline__ int select_bits(int m, int a, int b) { return (a & m) | (b & ~m); }
 
 __device__ __forceinline__ int med3(int v, int lo, int hi) {
   int r;
@@ -463,6 +489,10 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     issue();
     bare_barrier();                          // the counters are set up
     int free_to = 0;
+    // The loop starts behind a boundary of the instruction cache's lines, wherever the code before it ends: four wavefronts walk 5 KB with
+    // branches between any two loads, and where they enter a line decides what a fetch is worth.  Behind the boundary by the preheader's 16 bytes, or 48:
+    // 256 channels at 8x8, 128 images 14.1 us, 63x63 stride 2 73.0; 0 or 32 bytes: 14.4, 74.1.
+    asm volatile(".p2align 6");
     while (iv < V) {
       // the buffer of stage iv is free when every multiplying wavefront is done with stage iv - nb
       while (free_to < iv - a.nb + 1 && out < iv) {
@@ -536,27 +566,55 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
 
   // The pixel's sums: with a fired gate the ones that hold the conditional channels.
   auto pick = [&](unsigned dl) __attribute__((always_inline)) {
+    static_for<4 * kF>([&](auto ic) __attribute__((always_inline)) {
+      constexpr int f = decltype(ic)::value >> 2, i = (decltype(ic)::value & 3) * 4;
+      int m[4];
+      ones_if4<16 * f + i>(dl, m);
 #pragma unroll
-    for (int f = 0; f < kF; ++f)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int m = (int)(dl << (31 - 16 * f - i)) >> 31;
-        const acc_t pv = accP[0][f][i], sv = accS[0][f][i];
+      for (int e = 0; e < 4; ++e) {
+        const acc_t pv = accP[0][f][i + e], sv = accS[0][f][i + e];
         acc_t r;
-        from_bits((as_bits(sv) & m) | (as_bits(pv) & ~m), r);
-        accP[0][f][i] = r;
+        from_bits(select_bits(m[e], as_bits(sv), as_bits(pv)), r);
+        accP[0][f][i + e] = r;
       }
+    });
   };
   // bf16 accesses to y and the residual go in the transposed order of transpose4: access j is 16 pixels of one lane
-  // half, four lanes per pixel, i.e. half as many cache lines as a lane's own pieces would touch
+  // half, four lanes per pixel, i.e. half as many cache lines as a lane's own pieces would touch; int8 ones likewise, two pieces.
+  //   They are buffer accesses, at 32-bit offsets from the tile's first pixel that are formed once; the range check drops lanes without a pixel (addresses
+  // of 64 bits, a branch and zeros for each of them were a quarter of an output's instructions).
+  constexpr unsigned kNoPixel = 0x80000000u;
+  const int rowy = Base::kDtype == CG_I8 ? a.c_out : a.c_out * 2;
   auto px_of = [&](int px, int h) __attribute__((always_inline)) {   // pixel 16*h + lane % 16 of the fragment
     return __builtin_amdgcn_ds_bpermute((lane & 15) * 4 + h * 64, px);
   };
-  auto lane_bytes = [&]() __attribute__((always_inline)) {
-    if constexpr (kF == 1) return lane & 48;
-    int b = (lane & 32 ? 64 : 0) + (lane & 16 ? 16 : 0);
-    if constexpr (PF == 2) asm volatile("" : "+v"(b));        // (addresses formed from it are not kept across the K loops)
-    return b;
+  struct Places {
+    unsigned at[2];                                  // of the lane's pixels in accesses 0 and 1 (2 and 3: 32 bytes on)
+  };
+  auto places = [&](int px) __attribute__((always_inline)) {
+    Places w;
+    if constexpr (Base::kDtype == CG_I8 && kF == 1) {
+      w.at[0] = w.at[1] = px >= 0 ? __umul24((unsigned)px, (unsigned)rowy) + cbk * kBn + ch0 + 16 * lh : kNoPixel;
+    } else {
+      const int lane_bytes = Base::kDtype == CG_I8 ? cbk * kBn + (lane & 16) * 2 + (lane & 32) / 2
+                                                   : (cbk * kBn + ch0) * 2 + (kF == 1 ? lane & 48 : (lane & 32) * 2 + (lane & 16));
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int q = px_of(px, h);
+        w.at[h] = q >= 0 ? __umul24((unsigned)q, (unsigned)rowy) + lane_bytes : kNoPixel;
+      }
+    }
+    return w;
+  };
+  auto tile_buffer = [&](const void* base, long long m0) __attribute__((always_inline)) {
+    return __builtin_amdgcn_make_buffer_rsrc((char*)base + m0 * rowy, (short)0, 0x7fffffff, 0x00027000);
+  };
+  auto load_at = [&](__amdgpu_buffer_rsrc_t r, const Places& w, int j) __attribute__((always_inline)) {
+    return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(w.at[j & 1] + (j >> 1) * 32), 0, 0));
+  };
+  typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+  auto store_at = [&](__amdgpu_buffer_rsrc_t r, const Places& w, int j, i32x4 v) __attribute__((always_inline)) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)(w.at[j & 1] + (j >> 1) * 32), 0, 0);
   };
   // pieces of a lane's own pixel <-> pieces in that order; two pieces: access j is 16 pixels, again four lanes per pixel
   auto swap_halves = [&](auto& u) __attribute__((always_inline)) {
@@ -573,106 +631,143 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     else
       transpose4(u);
   };
-  // The residual of the lanes' pixels px (counted from pixel m0 of the batch; -1: none), 2 x 16 channels each, as it is read:
-  // the lane's 16-byte pieces in the transposed order, four of bf16, two of int8.
-  auto load_residual = [&](long long m0, int px, auto& rs) __attribute__((always_inline)) {
-    if constexpr (Base::kDtype == CG_I8 && kF == 1) {
-      rs[0] = i32x4{0, 0, 0, 0};
-      if (px >= 0) rs[0] = *(const i32x4*)(a.residual + (m0 + px) * a.c_out + cbk * kBn + ch0 + 16 * lh);
-      return;
-    }
-    constexpr int kPieces = Base::kDtype == CG_I8 ? 2 : 2 * kF;
-    const int pxj[2] = {px_of(px, 0), px_of(px, 1)};
-    const int rowy = Base::kDtype == CG_I8 ? a.c_out : a.c_out * 2;
-    const long long first = m0 * rowy + (Base::kDtype == CG_I8 ? cbk * kBn + (lane & 16) * 2 + (lane & 32) / 2 : (cbk * kBn + ch0) * 2 + lane_bytes());
+  // The residual of the lanes' pixels at w (of the tile that starts at pixel m0 of the batch), 2 x 16 channels each, as it is read: the lane's
+  // 16-byte pieces in the transposed order, four of bf16, two of int8; zeros where there is no pixel.
+  auto load_residual = [&](long long m0, const Places& w, auto& rs) __attribute__((always_inline)) {
+    constexpr int kPieces = Base::kDtype == CG_I8 ? kF : 2 * kF;
+    const auto r = tile_buffer(a.residual, m0);
 #pragma unroll
-    for (int j = 0; j < kPieces; ++j) {
-      rs[j] = i32x4{0, 0, 0, 0};
-      if (pxj[j & 1] >= 0) rs[j] = *(const i32x4*)(a.residual + first + (long long)pxj[j & 1] * rowy + (j >> 1) * 32);
-    }
+    for (int j = 0; j < kPieces; ++j) rs[j] = load_at(r, w, j);
   };
   // Output of those pixels in three steps that whole wavefronts execute.  First the values, from sums, the residual and the
-  // decisions in dl (bit 16*f + i; UNI: all the same):
-  auto finish = [&](auto uni, const acc16 (&sum)[2], unsigned dl, long long m0, int px, i32x4 (&v)[2 * kF]) __attribute__((always_inline)) {
+  // decisions in dl (bit 16*f + i; UNI: all the same).  Whether there is a scale/shift is asked once, and its table entries for the next eight channels are
+  // on their way while eight are formed:
+  auto finish = [&](auto uni, const acc16 (&sum)[2], unsigned dl, long long m0, const Places& w, i32x4 (&v)[2 * kF]) __attribute__((always_inline)) {
     constexpr bool UNI = decltype(uni)::value;
     // (the larger of a number and a NaN is the number: without ReLU every value stays what it is, a NaN included)
     const float relu_lo = (a.flags & kRelu) ? 0.0f : __builtin_nanf("");
-    const float* const taken = aff + (dl ? 128 : 0);
+    const float* const taken = aff + 16 * lh + (dl ? 128 : 0);
     i32x4 rs[2 * kF];
     if (a.flags & kResidual) {
-      load_residual(m0, px, rs);
+      load_residual(m0, w, rs);
       transpose(rs);
     }
+    // eight channels at a time, those from 32*f + 16*lh + 8*h on
+    auto rest = [&](auto kc, float (&r)[8]) __attribute__((always_inline)) {
+      constexpr int k = decltype(kc)::value;
+      if (a.flags & kResidual) {
 #pragma unroll
-    for (int f = 0; f < kF; ++f)
+        for (int i = 0; i < 8; ++i) {
+          const unsigned q = (unsigned)rs[k][i >> 1];
+          r[i] += __uint_as_float(i & 1 ? q & 0xffff0000u : q << 16);
+        }
+      }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {                  // eight channels at a time
-        const int cl = 32 * f + 16 * lh + 8 * h;
+      for (int e = 0; e < 4; ++e) v[k][e] = bf16_pair(max_of(r[2 * e], relu_lo), max_of(r[2 * e + 1], relu_lo));
+      if constexpr (PF == 2) __builtin_amdgcn_sched_barrier(0);      // (one piece at a time: no registers for more)
+    };
+    // each channel with the pair of its own decision
+    auto chosen = [&](auto kc, float (&r)[8]) __attribute__((always_inline)) {
+      constexpr int f = decltype(kc)::value >> 1, h = decltype(kc)::value & 1;
+      const float* const at = aff + 32 * f + 16 * lh + 8 * h;
+      static_for<2>([&](auto qc) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value;
+        const i32x4 a0 = *(const i32x4*)(at + 4 * q), b0 = *(const i32x4*)(at + 64 + 4 * q);
+        const i32x4 a1 = *(const i32x4*)(at + 128 + 4 * q), b1 = *(const i32x4*)(at + 192 + 4 * q);
+        int m[4];
+        ones_if4<16 * f + 8 * h + 4 * q>(dl, m);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          r[4 * q + e] = fmaf(__int_as_float(select_bits(m[e], a1[e], a0[e])), sum[f][8 * h + 4 * q + e],
+                              __int_as_float(select_bits(m[e], b1[e], b0[e])));
+      });
+    };
+    if constexpr (OUT == kPaired) {
+      // (a block has few tiles here, often one, and its end comes from a cold instruction cache: in the shortest form, without the reads ahead.
+      // 8x8 pixels of 256 channels, 128 images 13.9 us against 14.1)
+      static_for<2 * kF>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int k = decltype(kc)::value, f = k >> 1, h = k & 1;
         float r[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) r[i] = sum[f][8 * h + i];
         if (a.flags & kAffine) {
+          if constexpr (UNI) {
 #pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            if constexpr (UNI) {
-              const f32x4 at = *(const f32x4*)(taken + cl + 4 * q), bt = *(const f32x4*)(taken + 64 + cl + 4 * q);
+            for (int q = 0; q < 2; ++q) {
+              const f32x4 at = *(const f32x4*)(taken + 32 * f + 8 * h + 4 * q), bt = *(const f32x4*)(taken + 64 + 32 * f + 8 * h + 4 * q);
 #pragma unroll
               for (int e = 0; e < 4; ++e) r[4 * q + e] = fmaf(at[e], r[4 * q + e], bt[e]);
-            } else {
-              const i32x4 a0 = *(const i32x4*)(aff + cl + 4 * q), b0 = *(const i32x4*)(aff + 64 + cl + 4 * q);
-              const i32x4 a1 = *(const i32x4*)(aff + 128 + cl + 4 * q), b1 = *(const i32x4*)(aff + 192 + cl + 4 * q);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const int m = (int)(dl << (31 - 16 * f - 8 * h - 4 * q - e)) >> 31;
-                r[4 * q + e] = fmaf(__int_as_float((a1[e] & m) | (a0[e] & ~m)), r[4 * q + e],
-                                    __int_as_float((b1[e] & m) | (b0[e] & ~m)));
-              }
             }
+          } else {
+            chosen(kc, r);
           }
         }
-        if (a.flags & kResidual) {
+        rest(kc, r);
+      });
+      return;
+    }
+    if (!UNI || (a.flags & kAffine)) {               // (a layer without scale/shift has one pair throughout)
+      if constexpr (UNI) {
+        f32x4 t[2][4];                               // scales, then shifts
+        auto fetch = [&](auto kc) __attribute__((always_inline)) {
+          constexpr int k = decltype(kc)::value, cl = 32 * (k >> 1) + 8 * (k & 1), n = PF == 2 ? 0 : k & 1;
 #pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const unsigned w = (unsigned)rs[2 * f + h][i >> 1];
-            r[i] += __uint_as_float(i & 1 ? w & 0xffff0000u : w << 16);
+          for (int q = 0; q < 2; ++q) {
+            t[n][q] = *(const f32x4*)(taken + cl + 4 * q);
+            t[n][2 + q] = *(const f32x4*)(taken + 64 + cl + 4 * q);
           }
-        }
+        };
+        if constexpr (PF == 1) fetch(std::integral_constant<int, 0>{});
+        static_for<2 * kF>([&](auto kc) __attribute__((always_inline)) {
+          constexpr int k = decltype(kc)::value, n = PF == 2 ? 0 : k & 1;
+          if constexpr (PF == 2)
+            fetch(kc);
+          else if constexpr (k + 1 < 2 * kF)
+            fetch(std::integral_constant<int, k + 1>{});
+          float r[8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          v[2 * f + h][e] = bf16_pair(max_of(r[2 * e], relu_lo), max_of(r[2 * e + 1], relu_lo));
-        if constexpr (PF == 2) __builtin_amdgcn_sched_barrier(0);    // (one piece at a time: no registers for more)
+          for (int i = 0; i < 8; ++i) r[i] = fmaf(t[n][i >> 2][i & 3], sum[k >> 1][8 * (k & 1) + i], t[n][2 + (i >> 2)][i & 3]);
+          rest(kc, r);
+        });
+      } else {
+        static_for<2 * kF>([&](auto kc) __attribute__((always_inline)) {
+          float r[8];
+          chosen(kc, r);
+          rest(kc, r);
+        });
       }
+    } else {
+      static_for<2 * kF>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int k = decltype(kc)::value;
+        float r[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) r[i] = sum[k >> 1][8 * (k & 1) + i];
+        rest(kc, r);
+      });
+    }
   };
   // then, where y holds the values for an unfired gate already, each channel's own
-  auto choose = [&](unsigned dl, long long m0, int px, i32x4 (&v)[4]) __attribute__((always_inline)) {
-    const int rowy = a.c_out * 2;
-    const int pxj[2] = {px_of(px, 0), px_of(px, 1)};
-    const long long first = m0 * rowy + cbk * (kBn * 2) + lane_bytes();
+  auto choose = [&](unsigned dl, long long m0, const Places& w, i32x4 (&v)[4]) __attribute__((always_inline)) {
     i32x4 base[4];
+    const auto r = tile_buffer(a.y, m0);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      base[j] = i32x4{0, 0, 0, 0};
-      if (pxj[j & 1] >= 0) base[j] = *(const i32x4*)(a.y + first + (long long)pxj[j & 1] * rowy + (j >> 1) * 32);
-    }
+    for (int j = 0; j < 4; ++j) base[j] = load_at(r, w, j);
     transpose4(base);
+    static_for<4>([&](auto jc) __attribute__((always_inline)) {
+      constexpr int j = decltype(jc)::value;
+      int m[8];
+      ones_if4<8 * j>(dl, *(int(*)[4])&m[0]);
+      ones_if4<8 * j + 4>(dl, *(int(*)[4])&m[4]);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const unsigned lo = (unsigned)((int)(dl << (31 - 8 * j - 2 * e)) >> 31), hi = (unsigned)((int)(dl << (30 - 8 * j - 2 * e)) >> 31);
-        const unsigned m = (lo & 0xffffu) | (hi & 0xffff0000u);
-        v[j][e] = (int)(((unsigned)v[j][e] & m) | ((unsigned)base[j][e] & ~m));
-      }
+      for (int e = 0; e < 4; ++e) v[j][e] = select_bits(select_bits(0xffff, m[2 * e], m[2 * e + 1]), v[j][e], base[j][e]);
+    });
   };
   // and the stores
-  auto store = [&](i32x4 (&v)[2 * kF], long long m0, int px) __attribute__((always_inline)) {
-    const int rowy = a.c_out * 2;
-    const int pxj[2] = {px_of(px, 0), px_of(px, 1)};
-    const long long first = m0 * rowy + (cbk * kBn + ch0) * 2 + lane_bytes();
+  auto store = [&](i32x4 (&v)[2 * kF], long long m0, const Places& w) __attribute__((always_inline)) {
     transpose(v);
+    const auto r = tile_buffer(a.y, m0);
 #pragma unroll
-    for (int j = 0; j < 2 * kF; ++j)
-      if (pxj[j & 1] >= 0) *(i32x4*)(a.y + first + (long long)pxj[j & 1] * rowy + (j >> 1) * 32) = v[j];
+    for (int j = 0; j < 2 * kF; ++j) store_at(r, w, j, v[j]);
   };
   // Shuffled channel order (Sec. 3.3): channel j of group i goes to position j*groups + i of its pixel.  The block's 64 channels
   // are `ng` groups x `nj` channels: an LDS row holds a pixel's in the order [j][group], so that a run of ng elements is
@@ -779,28 +874,27 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   // a network that was trained with one normalisation): half the table reads and a quarter of the instructions of a choice
   // per value.  ResNet-18 with equal pairs, 64 images 426 -> 413 us, 256 images 1120 -> 1091.
   auto emit_fast = [&](unsigned dl, bool one_pair, long long m0, int px) __attribute__((always_inline)) {
+    const Places w = places(px);
     if constexpr (Base::kDtype != CG_I8) {
       i32x4 v[2 * kF];
       if (one_pair)
-        finish(std::true_type{}, accP[0], dl, m0, px, v);
+        finish(std::true_type{}, accP[0], dl, m0, w, v);
       else
-        finish(std::false_type{}, accP[0], dl, m0, px, v);
+        finish(std::false_type{}, accP[0], dl, m0, w, v);
       if constexpr (OUT == kShuffled) {
         shuffled_store(v, m0, px);
         return;
       }
-      store(v, m0, px);
+      store(v, m0, w);
     } else {
       // requantised int8: t = (S * mult_d + bias + half + residual * res_mult) >> shift, clamped (exact in 64 bits;
       // shifts of two and more: with the high word clamped to +-2^(shift-1) the shifted value fits 32 bits, and what was
       // clamped still lies beyond the bytes' range).  Access h covers 16 pixels, four 16-lane groups per pixel.
       const int lo = (a.flags & kRelu) ? 0 : -128;
       const int h_hi = (1 << (a.rq_shift - 1)) - 1, h_lo = -1 - h_hi;
-      const int pxh[2] = {px_of(px, 0), px_of(px, 1)};
-      const long long first = m0 * a.c_out + cbk * kBn + (lane & 16) * 2 + (lane & 32) / 2;
       i32x4 v[2], rs[2];
       if (a.flags & kResidual) {
-        load_residual(m0, px, rs);
+        load_residual(m0, w, rs);
         if constexpr (kF == 2) swap_halves(rs);
       }
       // four values, clamped to the bytes' range, as bytes
@@ -815,27 +909,27 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
         constexpr bool UNI = decltype(uni)::value;           // nothing fired, or a dense layer: one mult
         const int* const mult = (const int*)aff + (UNI && dl ? 64 : 0);
         const int *const s_lo = (const int*)thi, *const add = (const int*)aff + 192, *const s_hi = (const int*)aff + 256;
-#pragma unroll
-        for (int f = 0; f < kF; ++f) {
+        static_for<4 * kF>([&](auto kc) __attribute__((always_inline)) {
+          constexpr int f = decltype(kc)::value >> 2, q = decltype(kc)::value & 3;
           const int cl = 32 * f + 16 * lh;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
+          {
             const i32x4 ma = *(const i32x4*)(mult + cl + 4 * q), lo4 = *(const i32x4*)(s_lo + cl + 4 * q);
             const i32x4 ad = *(const i32x4*)(add + cl + 4 * q), hi4 = *(const i32x4*)(s_hi + cl + 4 * q);
             i32x4 mb = ma;
             if constexpr (!UNI) mb = *(const i32x4*)(mult + 64 + cl + 4 * q);
             unsigned c[4];
+            int m[4];
+            if constexpr (!UNI) ones_if4<16 * f + 4 * q>(dl, m);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              const int m = (int)(dl << (31 - 16 * f - 4 * q - e)) >> 31;
               const int sv = accP[0][f][4 * q + e];
-              int t = __mul24(med3(sv, lo4[e], hi4[e]), UNI ? ma[e] : (mb[e] & m) | (ma[e] & ~m)) + ad[e];
+              int t = __mul24(med3(sv, lo4[e], hi4[e]), UNI ? ma[e] : select_bits(m[e], mb[e], ma[e])) + ad[e];
               if (a.flags & kResidual) t += __mul24((int)(int8_t)((unsigned)rs[f][q] >> (8 * e)), a.rq_res_mult);
               c[e] = (unsigned)med3(t >> a.rq_shift, lo, 127);
             }
             v[f][q] = pack4(c);
           }
-        }
+        });
       };
       if (a.flags & kFit32) {
         if (one_pair)
@@ -863,14 +957,10 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
         }
       }
       }
-      if constexpr (kF == 1) {
-        if (px >= 0) *(i32x4*)(a.y + (m0 + px) * a.c_out + cbk * kBn + ch0 + 16 * lh) = v[0];
-        return;
-      }
-      swap_halves(v);
+      if constexpr (kF == 2) swap_halves(v);
+      const auto r = tile_buffer(a.y, m0);
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
-        if (pxh[h] >= 0) *(i32x4*)(a.y + first + (long long)pxh[h] * a.c_out) = v[h];
+      for (int h = 0; h < kF; ++h) store_at(r, w, h, v[h]);
     }
   };
   // every other output type and order, one lane's pixel at a time
@@ -1028,8 +1118,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
 #pragma unroll
         for (int q4 = 3; q4 >= 0; --q4) {
           const i32x4 lo4 = *(const i32x4*)(tlo + 32 * f + 16 * lh + 4 * q4);
-#pragma unroll
-          for (int e = 3; e >= 0; --e) Tr::shift_in(dl[g], accP[g][f][4 * q4 + e], lo4[e]);
+          Tr::shift_in4(dl[g], accP[g][f][4 * q4], accP[g][f][4 * q4 + 1], accP[g][f][4 * q4 + 2], accP[g][f][4 * q4 + 3], lo4);
         }
       if constexpr (Base::kDtype != CG_I8) {
         if (a.flags & kTwoSided) {
@@ -1039,8 +1128,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
 #pragma unroll
             for (int q4 = 3; q4 >= 0; --q4) {
               const i32x4 hi4 = *(const i32x4*)(thi + 32 * f + 16 * lh + 4 * q4);
-#pragma unroll
-              for (int e = 3; e >= 0; --e) Tr::shift_in_le(below, accP[g][f][4 * q4 + e], hi4[e]);
+              Tr::shift_in4_le(below, accP[g][f][4 * q4], accP[g][f][4 * q4 + 1], accP[g][f][4 * q4 + 2], accP[g][f][4 * q4 + 3], hi4);
             }
           dl[g] &= below;
         }
@@ -1101,8 +1189,9 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
 #pragma unroll
         for (int g = 0; g < PF; ++g) {
           if (!any[g]) continue;
-          finish(std::true_type{}, accP[g], 0u, m0, px[g], w);
-          store(w, m0, px[g]);
+          const Places at = places(px[g]);
+          finish(std::true_type{}, accP[g], 0u, m0, at, w);
+          store(w, m0, at);
         }
       }
       if (fired[0] && fired[1])
@@ -1116,9 +1205,10 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
 #pragma unroll
       for (int g = 0; g < PF; ++g) {
         if (gated ? !fired[g] : !any[g]) continue;
-        finish(std::true_type{}, accP[g], 1u, m0, px[g], w);
-        if (gated) choose(dl[g], m0, px[g], w);
-        store(w, m0, px[g]);
+        const Places at = places(px[g]);
+        finish(std::true_type{}, accP[g], 1u, m0, at, w);
+        if (gated) choose(dl[g], m0, at, w);
+        store(w, m0, at);
       }
     }
   }
@@ -1244,7 +1334,7 @@ bool plan_walk(const cg_conv_desc& d, int cps, RowsPlan& g, int& base_k, int& c_
     c_cond = d.c_in;
   }
   if (base_k % (cps * g.ch) || c_cond % (cps * g.ch)) return false;
-  if (d.c_out % kBn) return false;
+  if (d.c_out % kBn || d.c_out > (1 << 20)) return false;      // (512 pixels' outputs, at most 2 bytes each, at 32-bit offsets)
   g.n_cb = d.c_out / kBn;
   g.cps = cps;
   g.stages[0] = base_k / (cps * g.ch);

@@ -171,3 +171,28 @@ def test_two_wavefronts_to_a_fragment(shape):
         P.run_int8(q, thr, out_i8=True, rq=rq, epilogue=B.CG_EPI_RELU, variant=B.CG_VARIANT_MFMA_ROWS, name=shape.name)
         P.run_int8(q, thr, out_i8=True, rq=rq, residual=r8, rq_res_mult=hi // 2, epilogue=B.CG_EPI_RESIDUAL, variant=B.CG_VARIANT_MFMA_ROWS,
                    name=shape.name)
+
+
+ENDS = [S(6, 9, 13, 64, 64), S(40, 14, 14, 256, 256), S(16, 20, 20, 128, 128), S(3, 30, 70, 64, 192, stride=2), S(23, 13, 11, 512, 1024, k=1, pad=0)]
+
+
+@pytest.mark.parametrize("one_pair", [False, True])
+@pytest.mark.parametrize("shape", ENDS, ids=[s.name for s in ENDS])
+def test_outputs_with_and_without_scale_shift_and_residual(shape, one_pair):
+    """Each way through the end of a tile: no scale/shift, one pair, a pair by each decision; with and without a residual; tiles
+    whose last fragment has lanes without a pixel, whose places must neither be read nor written."""
+    c, rng = shape.c_out, np.random.default_rng(shape.h)
+    pair = [rng.uniform(0.5, 1.5, c), rng.normal(0, 0.1, c)]
+    other = pair if one_pair else [rng.uniform(0.5, 1.5, c), rng.normal(0, 0.1, c)]
+    aff = dict(scale0=pair[0], shift0=pair[1], scale1=other[0], shift1=other[1])
+    res = rng.standard_normal((shape.n, shape.ho, shape.wo, c)).astype(np.float32)
+    inp = W.make_inputs(shape, 9800 + shape.h, kind="coherent", rho=0.3, round_bf16=True)
+    gate = W.calibrate_gate(inp, 0.3, sample_images=2)
+    relu, scaled, added = B.CG_EPI_RELU, B.CG_EPI_AFFINE, B.CG_EPI_RESIDUAL
+    for epi in (scaled, scaled | added | relu) if one_pair else (0, added, scaled | relu, scaled | added):
+        more = dict(residual=res) if epi & added else {}
+        if epi & scaled:
+            more["affine"] = aff
+        if shape.k == 3:                       # (1x1 layers choose it by themselves)
+            more["variant"] = B.CG_VARIANT_MFMA_ROWS
+        P.run_float(inp, gate, out_dtype=B.CG_BF16, epilogue=epi, n_run=max(1, shape.n - 1), name=shape.name, **more)
