@@ -44,7 +44,10 @@
 // us, 128 to 256 at 28x28 stride 2 16.1 -> 15.6, int8 128 at 28x28, 32 images 10.4 -> 10.1.  The matrix cores are busy for 15 to 26 % of a layer at 64 images.
 // Outputs: addresses of 32 bits in buffer accesses (the range check drops lanes without a pixel), one bit-field instruction to a decision, scale and shift
 // read ahead, one question instead of four for whether there are any: 64 channels at 56x56, 256 images 94.4 -> 86.5 us, 128 at 28x28 74.1 -> 68.9,
-// 256 at 14x14 61.5 -> 58.7, int8 128 at 28x28, 32 images 9.8 -> 9.4, 1x1 of 192 to 128 channels 12.3 -> 11.6.  Measured in a graph with
+// 256 at 14x14 61.5 -> 58.7, int8 128 at 28x28, 32 images 9.8 -> 9.4, 1x1 of 192 to 128 channels 12.3 -> 11.6.
+// Layers with a residual have kernels of their own (kAdded): it is on its way while the tile's stages are multiplied, and the others have no branch
+// for it at every piece of an output.  With: int8 384 to 512 at 40x40 stride 2, 42 images 54.8 -> 53.0, 1x1 of 192 to 128 channels 11.7 -> 11.1; without:
+// 64 at 56x56, 64 images 22.3 -> 21.5, int8 128 at 28x28, 32 images 9.9 -> 9.4, 64 at 16x16, 216 images 8.9 -> 8.4.  Measured in a graph with
 // rotated buffers, clustered maps at a firing rate of 0.3, this form against an earlier one (barrier-coupled workgroups with the pixels listed anew for
 // the conditional path), before and after, us:
 //   bf16, scale/shift, residual and ReLU
@@ -309,6 +312,7 @@ enum RowsOut {
   kHalves,                                   // the same, blocks that cover several channel groups
   kShuffled,                                 // fast outputs in shuffled order
   kAnyOut,                                   // every other output type and order
+  kAdded, kPairedAdded,                      // kNatural and kPaired of layers with a residual, which is read before a tile's stages
 };
 
 template <typename Tr, int CPS, int PF, int TAPS, int OUT>
@@ -327,8 +331,12 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lj = lane & 31, lh = lane >> 5;
   // fragments of 32 channels that a wavefront multiplies, and the first channel of them in the block
-  constexpr int kF = OUT == kPaired ? 1 : 2;
-  const int ch0 = OUT == kPaired && wave < kCw ? (wave >> 2) * 32 : 0;
+  constexpr bool PAIR = OUT == kPaired || OUT == kPairedAdded;
+  constexpr int kF = PAIR ? 1 : 2;
+  // a residual: asked for (kHalves, kAnyOut), none, or one that is read before the tile's stages (PF = 2: no registers for it)
+  constexpr bool kAsk = OUT == kHalves || OUT == kAnyOut, kAhead = PF == 1 && (OUT == kAdded || OUT == kPairedAdded);
+  const bool added = kAsk ? (a.flags & kResidual) != 0 : OUT == kAdded || OUT == kPairedAdded;
+  const int ch0 = PAIR && wave < kCw ? (wave >> 2) * 32 : 0;
   // All arguments in one go: each further wait for some of them is 500 clocks of a start that nothing overlaps.
   asm volatile("" ::"s"(a.flags), "s"(a.magic_ncb), "s"(a.magic_ho), "s"(a.n_cb), "s"(a.n_slots), "s"(a.xcd_cb), "s"(a.per_xcd),
                "s"(a.full), "s"(a.rows_per), "s"(a.rows_more), "s"(a.tr), "s"(a.logp), "s"(a.bit), "s"(a.s0), "s"(a.s), "s"(a.nb), "s"(a.pstr),
@@ -521,7 +529,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   long long* const addends = (long long*)(aff + 192 - ch0) + ch0;      // int8: what is added before the shift
   bare_barrier();                                    // the counters are set up
   const int rowb = SB << a.logp;                     // bytes per patch row
-  const int flip = OUT != kPaired || a.bit < a.logp ? 0 : CPS * 8;     // what a patch row more changes in the chunk permutation
+  const int flip = !PAIR || a.bit < a.logp ? 0 : CPS * 8;     // what a patch row more changes in the chunk permutation
   const unsigned wlane = lh * 1024 + (lj + ch0) * 16;// lane's offset of its weight rows in a K step
   acc16 accP[PF][2], accS[PF][2];                    // base sums; base and conditional sums (PF = 2: accP holds these too)
 
@@ -642,20 +650,25 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   // Output of those pixels in three steps that whole wavefronts execute.  First the values, from sums, the residual and the
   // decisions in dl (bit 16*f + i; UNI: all the same).  Whether there is a scale/shift is asked once, and its table entries for the next eight channels are
   // on their way while eight are formed:
-  auto finish = [&](auto uni, const acc16 (&sum)[2], unsigned dl, long long m0, const Places& w, i32x4 (&v)[2 * kF]) __attribute__((always_inline)) {
+  auto finish = [&](auto uni, const acc16 (&sum)[2], unsigned dl, long long m0, const Places& w, i32x4 (&early)[2 * kF], i32x4 (&v)[2 * kF]) __attribute__((always_inline)) {
     constexpr bool UNI = decltype(uni)::value;
     // (the larger of a number and a NaN is the number: without ReLU every value stays what it is, a NaN included)
     const float relu_lo = (a.flags & kRelu) ? 0.0f : __builtin_nanf("");
     const float* const taken = aff + 16 * lh + (dl ? 128 : 0);
     i32x4 rs[2 * kF];
-    if (a.flags & kResidual) {
-      load_residual(m0, w, rs);
+    if (added) {
+      if constexpr (kAhead) {
+#pragma unroll
+        for (int j = 0; j < 2 * kF; ++j) rs[j] = early[j];
+      } else {
+        load_residual(m0, w, rs);
+      }
       transpose(rs);
     }
     // eight channels at a time, those from 32*f + 16*lh + 8*h on
     auto rest = [&](auto kc, float (&r)[8]) __attribute__((always_inline)) {
       constexpr int k = decltype(kc)::value;
-      if (a.flags & kResidual) {
+      if (added) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const unsigned q = (unsigned)rs[k][i >> 1];
@@ -682,7 +695,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
                               __int_as_float(select_bits(m[e], b1[e], b0[e])));
       });
     };
-    if constexpr (OUT == kPaired) {
+    if constexpr (PAIR) {
       // (a block has few tiles here, often one, and its end comes from a cold instruction cache: in the shortest form, without the reads ahead.
       // 8x8 pixels of 256 channels, 128 images 13.9 us against 14.1)
       static_for<2 * kF>([&](auto kc) __attribute__((always_inline)) {
@@ -873,14 +886,13 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
   // one_pair: the whole fragment takes the same scale/shift pair (nothing fired, a dense layer, or the pairs are equal, as in
   // a network that was trained with one normalisation): half the table reads and a quarter of the instructions of a choice
   // per value.  ResNet-18 with equal pairs, 64 images 426 -> 413 us, 256 images 1120 -> 1091.
-  auto emit_fast = [&](unsigned dl, bool one_pair, long long m0, int px) __attribute__((always_inline)) {
-    const Places w = places(px);
+  auto emit_fast = [&](unsigned dl, bool one_pair, long long m0, int px, const Places& w, i32x4 (&rs)[2 * kF]) __attribute__((always_inline)) {
     if constexpr (Base::kDtype != CG_I8) {
       i32x4 v[2 * kF];
       if (one_pair)
-        finish(std::true_type{}, accP[0], dl, m0, w, v);
+        finish(std::true_type{}, accP[0], dl, m0, w, rs, v);
       else
-        finish(std::false_type{}, accP[0], dl, m0, w, v);
+        finish(std::false_type{}, accP[0], dl, m0, w, rs, v);
       if constexpr (OUT == kShuffled) {
         shuffled_store(v, m0, px);
         return;
@@ -892,9 +904,9 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       // clamped still lies beyond the bytes' range).  Access h covers 16 pixels, four 16-lane groups per pixel.
       const int lo = (a.flags & kRelu) ? 0 : -128;
       const int h_hi = (1 << (a.rq_shift - 1)) - 1, h_lo = -1 - h_hi;
-      i32x4 v[2], rs[2];
-      if (a.flags & kResidual) {
-        load_residual(m0, w, rs);
+      i32x4 v[2];
+      if (added) {
+        if constexpr (!kAhead) load_residual(m0, w, rs);
         if constexpr (kF == 2) swap_halves(rs);
       }
       // four values, clamped to the bytes' range, as bytes
@@ -924,7 +936,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
             for (int e = 0; e < 4; ++e) {
               const int sv = accP[0][f][4 * q + e];
               int t = __mul24(med3(sv, lo4[e], hi4[e]), UNI ? ma[e] : select_bits(m[e], mb[e], ma[e])) + ad[e];
-              if (a.flags & kResidual) t += __mul24((int)(int8_t)((unsigned)rs[f][q] >> (8 * e)), a.rq_res_mult);
+              if (added) t += __mul24((int)(int8_t)((unsigned)rs[f][q] >> (8 * e)), a.rq_res_mult);
               c[e] = (unsigned)med3(t >> a.rq_shift, lo, 127);
             }
             v[f][q] = pack4(c);
@@ -949,7 +961,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
             const int m = (int)(dl << (31 - 16 * f - 4 * q - e)) >> 31;
             const int sv = accP[0][f][4 * q + e];
             long long t = (long long)sv * ((m1_[e] & m) | (m0_[e] & ~m)) + addends[cl + 4 * q + e];
-            if (a.flags & kResidual) t += (long long)(int8_t)((unsigned)rs[f][q] >> (8 * e)) * a.rq_res_mult;
+            if (added) t += (long long)(int8_t)((unsigned)rs[f][q] >> (8 * e)) * a.rq_res_mult;
             const int th = med3((int)(t >> 32), h_lo, h_hi);
             c[e] = (unsigned)med3((int)__builtin_amdgcn_alignbit((unsigned)th, (unsigned)t, (unsigned)a.rq_shift), lo, 127);
           }
@@ -1017,7 +1029,7 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     if constexpr (PF == 2) asm volatile("" : "+v"(lp));       // (formed for each tile: no registers to keep them)
 #pragma unroll
     for (int g = 0; g < PF; ++g) {
-      const int fr = (OUT == kPaired ? wave & 3 : wave) + kCw * g;
+      const int fr = (PAIR ? wave & 3 : wave) + kCw * g;
       int lr, wo_;
       if constexpr (TAPS == 1) {                     // a row is a pixel
         const int i = fr * 32 + lp;
@@ -1058,6 +1070,18 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     if (!any[0]) {                                   // no pixel of this tile is this wavefront's
       pass_by();
       continue;
+    }
+    // The residual is on its way while the stages are multiplied.
+    [[maybe_unused]] Places at_early;
+    [[maybe_unused]] i32x4 rs_early[2 * kF];
+    if constexpr (kAhead) {
+      at_early = places(px[0]);
+      if (!gate_only) {
+        load_residual(m0, at_early, rs_early);
+      } else {                               // (defined: else copies of the last tile's are waited for)
+#pragma unroll
+        for (int j = 0; j < 2 * kF; ++j) rs_early[j] = i32x4{0, 0, 0, 0};
+      }
     }
 #pragma unroll
     for (int g = 0; g < PF; ++g)
@@ -1177,10 +1201,15 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       } else if (gated) {
         pass_by();
       }
-      if constexpr (OUT != kAnyOut)
-        emit_fast(dl[0], !fired[0] || (a.flags & kOnePair) != 0u, m0, px[0]);
-      else if (inside[0])
+      if constexpr (kAhead) {
+        emit_fast(dl[0], !fired[0] || (a.flags & kOnePair) != 0u, m0, px[0], at_early, rs_early);
+      } else if constexpr (OUT != kAnyOut) {
+        const Places at = places(px[0]);
+        i32x4 rs[2 * kF];
+        emit_fast(dl[0], !fired[0] || (a.flags & kOnePair) != 0u, m0, px[0], at, rs);
+      } else if (inside[0]) {
         emit_any(dl[0], m0 + px[0]);
+      }
     } else if constexpr (Base::kDtype != CG_I8) {
       // No registers for two sets of sums: every fragment's outputs for an unfired gate are written first, and where it goes
       // on the fired channels' replace them at the end.
@@ -1190,7 +1219,8 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
         for (int g = 0; g < PF; ++g) {
           if (!any[g]) continue;
           const Places at = places(px[g]);
-          finish(std::true_type{}, accP[g], 0u, m0, at, w);
+          i32x4 rs[4];
+          finish(std::true_type{}, accP[g], 0u, m0, at, rs, w);
           store(w, m0, at);
         }
       }
@@ -1206,7 +1236,8 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       for (int g = 0; g < PF; ++g) {
         if (gated ? !fired[g] : !any[g]) continue;
         const Places at = places(px[g]);
-        finish(std::true_type{}, accP[g], 1u, m0, at, w);
+        i32x4 rs[4];
+        finish(std::true_type{}, accP[g], 1u, m0, at, rs, w);
         if (gated) choose(dl[g], m0, at, w);
         store(w, m0, at);
       }
@@ -1274,11 +1305,11 @@ hipError_t launch_rows_one(const RowsPlan& g, const Params& p, const RowsArgs& a
 
 template <typename Tr, int OUT>
 hipError_t launch_rows_out(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
-  if constexpr (OUT != kHalves && OUT != kPaired) if (g.taps == 1) {
+  if constexpr (OUT != kHalves && OUT != kPaired && OUT != kPairedAdded) if (g.taps == 1) {
     if (g.cps == 8) return launch_rows_one<Tr, 8, 1, 1, OUT>(g, p, a, s);
     return g.cps == 4 ? launch_rows_one<Tr, 4, 1, 1, OUT>(g, p, a, s) : launch_rows_one<Tr, 2, 1, 1, OUT>(g, p, a, s);
   }
-  if constexpr (Tr::Base::kDtype == CG_BF16 && OUT == kNatural)
+  if constexpr (Tr::Base::kDtype == CG_BF16 && (OUT == kNatural || OUT == kAdded))
     if (g.pf == 2) return launch_rows_one<Tr, 4, 2, 9, OUT>(g, p, a, s);      // (planned for stages of four chunks only)
   return g.cps == 4 ? launch_rows_one<Tr, 4, 1, 9, OUT>(g, p, a, s) : launch_rows_one<Tr, 2, 1, 9, OUT>(g, p, a, s);
 }
@@ -1295,8 +1326,9 @@ hipError_t launch_rows_type(const RowsPlan& g, const Params& p, const RowsArgs& 
   if constexpr (Tr::Base::kDtype == CG_BF16)
     if (a.flags & kShuf2) return launch_rows_out<Tr, kShuffled>(g, p, a, s);
   if (g.pf == 1 && g.taps == 9 && a.spg) return launch_rows_out<Tr, kHalves>(g, p, a, s);
-  if (a.flags & kPairs) return launch_rows_out<Tr, kPaired>(g, p, a, s);
-  return launch_rows_out<Tr, kNatural>(g, p, a, s);
+  const bool added = (a.flags & kResidual) != 0u;
+  if (a.flags & kPairs) return added ? launch_rows_out<Tr, kPairedAdded>(g, p, a, s) : launch_rows_out<Tr, kPaired>(g, p, a, s);
+  return added ? launch_rows_out<Tr, kAdded>(g, p, a, s) : launch_rows_out<Tr, kNatural>(g, p, a, s);
 }
 
 unsigned magic16(int d) { return d == 1 ? 0u : (unsigned)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d); }
