@@ -196,3 +196,25 @@ def test_outputs_with_and_without_scale_shift_and_residual(shape, one_pair):
         if shape.k == 3:                       # (1x1 layers choose it by themselves)
             more["variant"] = B.CG_VARIANT_MFMA_ROWS
         P.run_float(inp, gate, out_dtype=B.CG_BF16, epilogue=epi, n_run=max(1, shape.n - 1), name=shape.name, **more)
+
+
+@pytest.mark.parametrize("shape", ENDS, ids=[s.name for s in ENDS])
+def test_outputs_of_four_bytes(shape):
+    """Float and 32-bit outputs, 16 channels of a pixel by four lanes: the same ways through the end, and sums that a residual
+    takes past 32 bits (the sums of 128 to 512 channels times nine taps stay below 2^27, a residual of 2^30 each way does not)."""
+    c, rng = shape.c_out, np.random.default_rng(shape.w)
+    aff = dict(scale0=rng.uniform(0.5, 1.5, c), shift0=rng.normal(0, 0.1, c), scale1=rng.uniform(0.5, 1.5, c), shift1=rng.normal(0, 0.1, c))
+    one = dict(aff, scale1=aff["scale0"], shift1=aff["shift0"])
+    res = rng.standard_normal((shape.n, shape.ho, shape.wo, c)).astype(np.float32)
+    inp = W.make_inputs(shape, 9900 + shape.h, kind="coherent", rho=0.3, round_bf16=True)
+    gate = W.calibrate_gate(inp, 0.3, sample_images=2)
+    relu, scaled, added, n = B.CG_EPI_RELU, B.CG_EPI_AFFINE, B.CG_EPI_RESIDUAL, max(1, shape.n - 1)
+    rows = dict(variant=B.CG_VARIANT_MFMA_ROWS) if shape.k == 3 else {}
+    for epi, more in ((0, {}), (added, dict(residual=res)), (scaled | relu, dict(affine=aff)), (scaled | added, dict(affine=aff, residual=res)),
+                      (scaled | added | relu, dict(affine=one, residual=res))):
+        P.run_float(inp, gate, epilogue=epi, n_run=n, name=shape.name, **more, **rows)
+    q = W.quantize_int8(W.make_inputs(shape, 9950 + shape.h, kind="coherent", rho=0.35))
+    thr = W.calibrate_gate_int8(q, 0.35, sample_images=None)
+    r8 = rng.integers(-128, 128, (shape.n, shape.ho, shape.wo, c)).astype(np.int8)
+    for epi, more in ((relu, {}), (added, dict(residual=r8, rq_res_mult=-(1 << 25))), (added | relu, dict(residual=r8, rq_res_mult=1 << 23))):
+        P.run_int8(q, thr, epilogue=epi, n_run=n, name=shape.name, **more, **rows)
