@@ -143,9 +143,10 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
 // Maxima of sums instead of outputs: the output function is monotone in the sum, rising where the scale is not negative;
 // channels with a negative scale take negated weights and the scale's magnitude (both exact).
 //
-// What bounds it: the matrix cores (44 instructions of 32 clocks per output row and 28 pooled columns; half of the time with
-// two wavefronts to a SIMD) and as often the LDS reads of the pixel operands.  Images of 224x224 with pooling: 256 in
-// 98 us, 64 in 33, 16 in 16; 240, 66 and 22 in the form before (16x16 tiles gathered as single elements, 1.31 times
+// What bounds it: two wavefronts to a SIMD are not enough to keep anything busy: the matrix cores (44 instructions of 32 clocks per output row
+// and 28 pooled columns) are for 41 % of the time, LDS for 43 % (a quarter of that conflicts), and a wavefront waits for operands or the other
+// one's products for the rest; its 250 registers, half of them weights and sums, allow no third.  Images of 224x224 with pooling: 256 in
+// 84 us, 64 in 35, 16 in 17; 240, 66 and 22 in the form before (16x16 tiles gathered as single elements, 1.31 times
 // the products, outputs exchanged through LDS for the pooling).
 constexpr int kStemPitch = 1664;                 // bytes of a ring row: 63 pooled columns' input and the window's rest
 constexpr int kStemRing = 16;
@@ -168,7 +169,8 @@ struct __attribute__((packed, aligned(2))) StemPiece {
   stem_i32x4 v;
 };
 
-template <bool POOL, int NFC>
+// RAGGED: rows that are not whole 16-byte pieces (the others have no instruction for it: one image of 224x224 6.6 us with, 6.1 without)
+template <bool POOL, int NFC, bool RAGGED>
 __global__ __launch_bounds__(128, 2) void conv7x7s2c3_kernel(StemArgs a) {
   constexpr int K = 7, CI = 3, TAPS = K * K * CI, ST = 11, CB = 32 * NFC;
   __shared__ __align__(16) char ring[kStemRing * kStemPitch];   // first the weights, then input rows
@@ -191,16 +193,21 @@ __global__ __launch_bounds__(128, 2) void conv7x7s2c3_kernel(StemArgs a) {
   const int piece0 = (el0 & ~7) + tid * 8;       // first element of this thread's piece
   const uint16_t* const ximg = a.x + (long long)img * a.h * row_els;
   const bool in_row = tid < kStemPieces && piece0 >= 0 && piece0 + 8 <= row_els;
-  const bool cut = tid < kStemPieces && piece0 < row_els && piece0 + 8 > row_els;    // (rows of whole pieces have none)
+  // The piece that a row ends in (rows of whole pieces have none) is taken from the row's last eight elements and moved down when it is kept; rows of
+  // fewer are put together from single ones.  (Every such piece from single ones, each waited for, us: 64 images of 223x223 47.8, now 35.4; 140 of
+  // 201x201 98.4, now 68.4; 8 of 97x97 11.4, now 8.3.)
+  const bool cut = RAGGED && tid < kStemPieces && piece0 < row_els && piece0 + 8 > row_els;
+  const bool whole = in_row || (cut && row_els >= 8);
+  const int from = cut ? row_els - 8 : piece0, down = cut && row_els >= 8 ? 8 - (row_els & 7) : 0;
   auto load_piece = [&](int hi) __attribute__((always_inline)) {
     stem_i32x4 v = {0, 0, 0, 0};
     if ((unsigned)hi < (unsigned)a.h) {
-      const uint16_t* src = ximg + (long long)hi * row_els + piece0;
-      if (in_row) v = ((const StemPiece*)src)->v;
-      if ((row_els & 7) && cut) {
+      const uint16_t* const row = ximg + (long long)hi * row_els;
+      if (whole) v = ((const StemPiece*)(row + from))->v;
+      if (RAGGED && row_els < 8 && cut) {
 #pragma nounroll
-        for (int e = 0; e < (row_els & 7); ++e) {
-          const int bits = (int)((uint32_t)src[e] << (16 * (e & 1)));
+        for (int e = 0; e < row_els; ++e) {
+          const int bits = (int)((uint32_t)row[e] << (16 * (e & 1)));
 #pragma unroll
           for (int d = 0; d < 4; ++d) v[d] |= e >> 1 == d ? bits : 0;
         }
@@ -209,6 +216,14 @@ __global__ __launch_bounds__(128, 2) void conv7x7s2c3_kernel(StemArgs a) {
     return v;
   };
   auto keep_piece = [&](int hi, stem_i32x4 v) __attribute__((always_inline)) {
+    if constexpr (RAGGED) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = down & 4 ? (e < 2 ? v[e + 2] : 0) : v[e];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = down & 2 ? (e < 3 ? v[e + 1] : 0) : v[e];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = down & 1 ? (int)__builtin_amdgcn_alignbit(e < 3 ? (uint32_t)v[e + 1] : 0u, (uint32_t)v[e], 16) : v[e];
+    }
     if (tid < kStemPieces) {                     // (el0 is even)
       int* dst = (int*)(ring + ((hi + 64) & (kStemRing - 1)) * kStemPitch + 16 + (piece0 - el0) * 2);
 #pragma unroll
@@ -405,6 +420,10 @@ __global__ __launch_bounds__(128, 2) void conv7x7s2c3_kernel(StemArgs a) {
         for (int i = 0; i < 16; ++i) above[fc][i] = -__builtin_inff();
     }
   }
+  // No load is in flight from here on nor at the end of a step, as far as the compiler knows: those that only some of the threads keep were to it, and
+  // it waited for the next rows' loads, or for a step's stores, before a step's first product.
+  constexpr int kVmcnt0 = 0x0f70;
+  __builtin_amdgcn_s_waitcnt(kVmcnt0);
 #pragma nounroll
   for (int p = p0; p < p1; ++p) {
     stem_i32x4 next[4];
@@ -418,6 +437,15 @@ __global__ __launch_bounds__(128, 2) void conv7x7s2c3_kernel(StemArgs a) {
       const int r = 2 * p + half;
       if (half == 1 && r >= a.ho) break;         // (the last pooled row of an odd height)
       row_sums(r, acc);
+      // The next step's rows are kept here, ahead of this step's outputs, whose stores a wait for the loads would wait for too; their places are those
+      // of rows 7 to 4 above this step's first, which nothing reads any more.
+      if (half == 0) {
+        __builtin_amdgcn_s_waitcnt(kVmcnt0);
+        if (more) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) keep_piece(4 * p + 9 - a.pad + k, next[k]);
+        }
+      }
       if constexpr (POOL) {
         settle();
         const bool last = half == 1 || r + 1 >= a.ho;
@@ -448,11 +476,7 @@ __global__ __launch_bounds__(128, 2) void conv7x7s2c3_kernel(StemArgs a) {
         if (mine && odd_in) write(acc[1], dst + a.c_out);
       }
     }
-    if (more) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) keep_piece(4 * p + 9 - a.pad + k, next[k]);
-      __syncthreads();
-    }
+    if (more) __syncthreads();
   }
 }
 
@@ -487,12 +511,12 @@ int launch_conv7x7s2c3(bool pool, const char* who, const void* x, const void* w,
   if (blocks > 0x7fffffffll) return cg::set_error(CG_EUNSUPPORTED, "%s: too many tiles", who);
   // 32 channels a workgroup instead of 64, half of the products for a wavefront, where 64 would leave half of the chip idle:
   // images of 224x224 with pooling, one 8.8 -> 6.2 us, four 9.0 -> 8.0, eight 11.8 -> 11.1 (twelve are past the line).
-  if (2 * blocks * (c_out / kCb) <= want)
-    hipLaunchKernelGGL((pool ? conv7x7s2c3_kernel<true, 1> : conv7x7s2c3_kernel<false, 1>), dim3((unsigned)blocks, (unsigned)(c_out / 32)),
-                       dim3(128), 0, s, a);
-  else
-    hipLaunchKernelGGL((pool ? conv7x7s2c3_kernel<true, 2> : conv7x7s2c3_kernel<false, 2>), dim3((unsigned)blocks, (unsigned)(c_out / kCb)),
-                       dim3(128), 0, s, a);
+  const bool narrow = 2 * blocks * (c_out / kCb) <= want, ragged = wd * 3 % 8 != 0;
+  const auto kernel = narrow ? (pool ? (ragged ? conv7x7s2c3_kernel<true, 1, true> : conv7x7s2c3_kernel<true, 1, false>)
+                                     : (ragged ? conv7x7s2c3_kernel<false, 1, true> : conv7x7s2c3_kernel<false, 1, false>))
+                             : (pool ? (ragged ? conv7x7s2c3_kernel<true, 2, true> : conv7x7s2c3_kernel<true, 2, false>)
+                                     : (ragged ? conv7x7s2c3_kernel<false, 2, true> : conv7x7s2c3_kernel<false, 2, false>));
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks, (unsigned)(c_out / (narrow ? 32 : kCb))), dim3(128), 0, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return cg::set_error(CG_EHIP, "%s: %s", who, hipGetErrorString(e));
   return CG_OK;

@@ -109,6 +109,31 @@ def test_conv7x7s2_single_images_equal_the_batch(n, h, w, c_out, pad):
         assert torch.equal(y[k:k + 1], y1) and torch.equal(p[k:k + 1], p1)
 
 
+@pytest.mark.parametrize("w", [1, 2, 3, 5, 8, 9, 12, 14, 23, 47, 86, 127])
+@pytest.mark.parametrize("pad", [2, 3])
+def test_conv7x7s2_rows_that_end_inside_a_piece(w, pad):
+    """Widths whose rows end at every place of a 16-byte piece of the input, rows shorter than one among them; odd numbers of output rows."""
+    n, h, c_out = 2, 25, 64
+    rng = np.random.default_rng(w + pad)
+    if w + 2 * pad < 7:
+        pytest.skip("no output column")
+    x = _bf16(rng.standard_normal((n, h, w, 3)))
+    wt = _bf16(rng.standard_normal((c_out, 7, 7, 3)) * np.sqrt(2.0 / 147))
+    sc = rng.uniform(-0.5, 1.5, c_out).astype(np.float32)
+    sh = (rng.standard_normal(c_out) * 0.3).astype(np.float32)
+    ho, wo = O.out_hw(h, w, 7, 7, 2, pad)
+    xd, wd_, scd, shd = _dev(x), _dev(wt), _dev(sc, torch.float32), _dev(sh, torch.float32)
+    y = torch.empty((n, ho, wo, c_out), dtype=torch.bfloat16, device="cuda")
+    p = torch.empty((n, (ho - 1) // 2 + 1, (wo - 1) // 2 + 1, c_out), dtype=torch.bfloat16, device="cuda")
+    B.cg_small_cin_conv(xd.data_ptr(), wd_.data_ptr(), scd.data_ptr(), shd.data_ptr(), y.data_ptr(), n, h, w, 3, c_out, 7, 2, pad, True, _stream())
+    B.cg_conv7x7s2_maxpool(xd.data_ptr(), wd_.data_ptr(), scd.data_ptr(), shd.data_ptr(), p.data_ptr(), n, h, w, c_out, pad, True, _stream())
+    torch.cuda.synchronize()
+    dense = O.dense_conv(x, wt, stride=2, pad=pad, scale=sc, shift=sh, relu=True)
+    for got, ref in ((y, dense), (p, O.maxpool3x3s2(dense))):
+        tol = P.ATOL + P.RTOL * np.abs(ref) + P.bf16_ulp(ref)
+        assert (np.abs(got.float().cpu().numpy().astype(np.float64) - ref) <= tol).all()
+
+
 @pytest.mark.parametrize("n,h,w,c", [(2, 112, 112, 64), (3, 9, 7, 8), (1, 1, 1, 16), (2, 6, 5, 72)])
 def test_maxpool_bit_exact(n, h, w, c):
     rng = np.random.default_rng(h * 10 + c)
