@@ -28,11 +28,15 @@
 // 4 to 40 % slower than eight (128 registers to a wavefront are not enough for the larger tiles), K split over two or four
 // workgroups as well 20 to 50 % slower at one to four images.
 //
+// (Those are with an end of branches on lanes' values and a K loop whose waits were for every load in flight.  Scalar offsets where a K step lies inside
+// one tap, waits for one batch at a time, sums that meet in straight code and an end shared by up to four wavefronts a unit take 60 layers of
+// 3.4 to 28 us to 0.81 of that time: int8 256 at 14x14 through the binding 5.3 -> 3.9, 96 to 80 at 45x33 7.9 -> 6.6.)
+//
 // K is walked in steps of four units, unit u = tap * chunks + chunk, a unit being one 16-byte channel
 // chunk of one tap; lane group l/16 supplies unit 4k + l/16.  Padding (taps outside the image, units past
-// the last) is an out-of-range buffer load, which returns zeros.  A base group that ends inside a chunk is
-// masked in registers on both paths, so that a channel never meets a weight of the other path (0 * inf
-// would otherwise reach the sum).
+// the last) is an out-of-range buffer load, which returns zeros.  In the chunk in which a base group ends the
+// packed weights are zero for the other path's channels; where a float sum is a NaN there, it is formed again from the path's own channels
+// (0 * inf would otherwise reach it).
 #include <algorithm>
 #include <type_traits>
 
