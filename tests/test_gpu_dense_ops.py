@@ -109,14 +109,11 @@ def test_conv7x7s2_single_images_equal_the_batch(n, h, w, c_out, pad):
         assert torch.equal(y[k:k + 1], y1) and torch.equal(p[k:k + 1], p1)
 
 
-@pytest.mark.parametrize("w", [1, 2, 3, 5, 8, 9, 12, 14, 23, 47, 86, 127])
-@pytest.mark.parametrize("pad", [2, 3])
+@pytest.mark.parametrize("w,pad", [(w, 3) for w in (1, 2, 3, 5, 8, 9, 12, 14, 23, 47, 86, 127)] + [(w, 2) for w in (3, 5, 8, 9, 12, 14, 23, 47, 86, 127)])
 def test_conv7x7s2_rows_that_end_inside_a_piece(w, pad):
     """Widths whose rows end at every place of a 16-byte piece of the input, rows shorter than one among them; odd numbers of output rows."""
     n, h, c_out = 2, 25, 64
     rng = np.random.default_rng(w + pad)
-    if w + 2 * pad < 7:
-        pytest.skip("no output column")
     x = _bf16(rng.standard_normal((n, h, w, 3)))
     wt = _bf16(rng.standard_normal((c_out, 7, 7, 3)) * np.sqrt(2.0 / 147))
     sc = rng.uniform(-0.5, 1.5, c_out).astype(np.float32)
