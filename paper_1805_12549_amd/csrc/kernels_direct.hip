@@ -59,7 +59,7 @@ struct I8Direct {
   using Base = I8Traits;
   using acc4 = i32x4;
   using acc_t = int32_t;
-  static constexpr int kParts = 1;
+  static constexpr int kCh = 16, kParts = 1;
   static __device__ __forceinline__ acc4 mma(int, i32x4 rows, i32x4 cols, acc4 c) { return I8Traits::mfma(rows, cols, c); }
 };
 
@@ -403,8 +403,8 @@ constexpr int kMaxSplit = 8;
 // MIXED: float layers whose blocks cover several channel groups (Sec. 3.3) or whose groups share a chunk; kStraddle: those whose base group ends
 // inside a chunk.  The packed
 // weights are zero where a channel is not on a row's path, which keeps its finite values out of the row's sum but turns
-// an infinity or a NaN into a NaN; a wavefront that ends up with a NaN forms its sums again, from the path's channels
-// alone.  (The look at the sums costs 1 to 2 %, one at every operand, as it is read, 5 to 7 %.)
+// an infinity or a NaN into a NaN; a wavefront that ends up with one forms the sum again, from the path's channels
+// alone.  No other sum changes by it: pixels beside it, of other images among them, keep their bits.  (The look at the sums costs 1 to 2 %, one at every operand, as it is read, 5 to 7 %.)
 template <typename Tr, int PF, int NH, bool SPLIT, bool MIXED, bool UNIFORM>
 __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
   using Base = typename Tr::Base;
@@ -590,6 +590,69 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
             }
       __builtin_amdgcn_sched_barrier(0);
     };
+    // the place in x of unit u of K for this lane's pixel of fragment f: its offset or kOut
+    auto unit_at = [&](int f, int t, int chunk) __attribute__((always_inline)) {
+      const int r = (t * 11) >> 5;
+      const bool on = t < p.taps && chunk < p.total_chunks && ((vmask[f] >> (t & 31)) & 1u);
+      return on ? xbase[f] + (unsigned)(r * p.rowb + (t - 3 * r) * p.xps + chunk * 16) : kOut;
+    };
+    // A layer whose base group ends inside a chunk: the same products in the same order once more, the other path's channels of that chunk
+    // left out of x, so that a pixel has the sum that it would have if they were finite (zero weights add nothing to it), to the bit.
+    [[maybe_unused]] auto products_again = [&](int f, int h, acc4& all) __attribute__((always_inline)) {
+      const int own = p.c_base & (Tr::kCh - 1), at = ph ? 0 : nq - 1;      // base channels of that chunk, and where it is
+      const int ln = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));      // (the lane, in no register until here)
+      acc4 sum[2] = {acc4{0, 0, 0, 0}, acc4{0, 0, 0, 0}};
+      auto step = [&](auto to, int k) __attribute__((always_inline)) {
+        const unsigned u = 4u * (unsigned)k + (unsigned)(ln >> 4);
+        const int t = (int)quot(u, dnq), i = (int)u - t * nq, chunk = cfirst + i + (i >= gap_at ? p.gap_len : 0);
+        i32x4 xv = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)unit_at(f, t, chunk), 0, 0));
+        const i32x4 wv = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, ln * 16 + k * 2048 + (h & 1) * 1024, (h >> 1) * (int)wgrp, 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int bytes = own * (16 / Tr::kCh) - 4 * e;                  // of the word, base channels
+          const int base = bytes >= 4 ? -1 : bytes <= 0 ? 0 : (1 << (8 * bytes)) - 1;
+          xv[e] &= i == at ? (ph ? ~base : base) : -1;
+        }
+#pragma unroll
+        for (int part = 0; part < Tr::kParts; ++part) sum[decltype(to)::value] = Tr::mma(part, wv, xv, sum[decltype(to)::value]);
+      };
+      constexpr int kBlock = kU == 1 ? 2 : 4;       // (two batches of one or two steps, or one of four)
+#pragma nounroll
+      for (int k = 0; k < n; ++k) {
+        step(std::integral_constant<int, 0>{}, k0 + k);
+        if constexpr (decltype(two)::value)
+          if (++k < n) step(std::integral_constant<int, 1>{}, k0 + k);
+        if (k + 1 >= n || (kBlocks && k % kBlock == kBlock - 1)) {
+          all += decltype(two)::value ? sum[0] + sum[1] : sum[0];
+          sum[0] = sum[1] = acc4{0, 0, 0, 0};
+        }
+      }
+    };
+    // Blocks of several groups: each row's products one by one.  (A lane's rows are 4*lg .. 4*lg + 3 of the 16 channels; the unit, and with it the channel, is
+    // the same for all lanes.)
+    [[maybe_unused]] auto rows_again = [&](int f, int h, acc4& sum) __attribute__((always_inline)) {
+      if constexpr (MIXED) {
+        int row_grp[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) row_grp[e] = (int)quot((half0 + h) * 16 + 4 * lg + e, p.cpg);
+#pragma nounroll
+        for (int u = 4 * k0; u < 4 * (k0 + n); ++u) {
+          const int t = u / nq, i = u - t * nq, chunk = cfirst + i + (i >= gap_at ? p.gap_len : 0);
+          if (t >= p.taps || chunk >= p.total_chunks) continue;
+          const i32x4 xv = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)unit_at(f, t, chunk), 0, 0));
+          const char* const wu = wp + (size_t)(h >> 1) * wgrp + (size_t)(u >> 2) * 2048 + (h & 1) * 1024 + (u & 3) * 256 + lg * 64;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const i32x4 wv = *(const i32x4*)(wu + e * 16);
+#pragma unroll
+            for (int c = 0; c < Tr::kCh; ++c) {
+              const bool on = ((chunk * Tr::kCh + c) / p.c_base == row_grp[e]) == (ph == 0);
+              sum[e] = on ? fmaf(Tr::element(xv, c), Tr::element(wv, c), sum[e]) : sum[e];
+            }
+          }
+        }
+      }
+    };
     acc4 tot[PF][NH];                               // the blocks so far
     if constexpr (kBlocks) {
 #pragma unroll
@@ -652,56 +715,40 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
 #pragma unroll
         for (int i = 0; i < NH; ++i) a[f][i] = tot[f][i];
     }
+    // Sums that are a NaN are formed again without the other path's channels, 16 pixels by 16 channels at a time (there are no registers for more
+    // beside those that the first pass left); no other sum changes.
     if constexpr (Base::kDtype != CG_I8 && !UNIFORM) {
       if (!MIXED && !(p.flags & kStraddle)) return;
+      auto any_nan = [](const acc4& v) __attribute__((always_inline)) {
+        bool nan = false;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) nan |= v[e] != v[e];
+        return nan;
+      };
       bool nan = false;
 #pragma unroll
       for (int f = 0; f < PF; ++f)
 #pragma unroll
-        for (int i = 0; i < NH; ++i)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) nan |= a[f][i][e] != a[f][i][e];
+        for (int i = 0; i < NH; ++i) nan |= any_nan(a[f][i]);
       if (__ballot(nan) == 0ull) return;
-      // (a lane's rows are 4*lg .. 4*lg + 3 of each 16 channels; the unit, and with it the channel, is the same for all lanes)
-      int row_grp[NH][4];
 #pragma unroll
-      for (int i = 0; i < NH; ++i)
+      for (int f = 0; f < PF; ++f)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          row_grp[i][e] = (int)quot((half0 + i) * 16 + 4 * lg + e, p.cpg);
-#pragma unroll
-          for (int f = 0; f < PF; ++f) a[f][i][e] = 0.0f;
-        }
-#pragma nounroll
-      for (int u = 4 * k0; u < 4 * (k0 + n); ++u) {
-        const int t = u / nq, i = u - t * nq, chunk = cfirst + i + (i >= gap_at ? p.gap_len : 0), r = (t * 11) >> 5;
-        if (t >= p.taps || chunk >= p.total_chunks) continue;
-        i32x4 xv[PF];
-#pragma unroll
-        for (int f = 0; f < PF; ++f) {
-          const unsigned off = xbase[f] + (unsigned)(r * p.rowb + (t - 3 * r) * p.xps + chunk * 16);
-          xv[f] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(((vmask[f] >> t) & 1u) ? off : kOut), 0, 0));
-        }
-        int ch_grp[Tr::kCh];
-#pragma unroll
-        for (int i = 0; i < Tr::kCh; ++i) ch_grp[i] = (chunk * Tr::kCh + i) / p.c_base;
-        const char* const wu = wp + (size_t)(u >> 2) * 2048 + (u & 3) * 256 + lg * 64;
-#pragma unroll
-        for (int h = 0; h < NH; ++h)
+        for (int h = 0; h < NH; ++h) {
+          if (__ballot(any_nan(a[f][h])) == 0ull) continue;
+          acc4 again{0, 0, 0, 0};
+          if constexpr (MIXED)
+            rows_again(f, h, again);
+          else
+            products_again(f, h, again);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const i32x4 wv = *(const i32x4*)(wu + (size_t)(h >> 1) * wgrp + (h & 1) * 1024 + e * 16);
-#pragma unroll
-            for (int i = 0; i < Tr::kCh; ++i) {
-              const bool on = (ch_grp[i] == row_grp[h][e]) == (ph == 0);
-#pragma unroll
-              for (int f = 0; f < PF; ++f) {
-                const float old = a[f][h][e];
-                a[f][h][e] = on ? fmaf(Tr::element(xv[f], i), Tr::element(wv, i), old) : old;
-              }
-            }
+            float v = again[e];
+            asm volatile("" : "+v"(v));             // (one by one into the first pass's registers: tiles of eight units are spilled otherwise)
+            const float old = a[f][h][e];
+            a[f][h][e] = old != old ? v : old;
           }
-      }
+        }
     }
   };
   auto zero = [&](acc4 (&a)[PF][NH]) __attribute__((always_inline)) {

@@ -122,6 +122,50 @@ def test_grouped_layers_keep_infinities_in_their_group(in_dtype, n, h, w, cin, c
     assert torch.equal(fired, base >= thr)
 
 
+# Layers whose base group ends inside a chunk, (type, images, size, channels in and out, base channels) with the tile and the wavefronts that share
+# its K; and grouped ones.  (tests/test_kernels_of_calls_cpu.py checks the forms.)
+INSIDE = [
+    (B.CG_F32, (1, 20, 40, 40, 10, 1), (1, 1, True)), (B.CG_F32, (4, 20, 40, 40, 10, 1), (1, 2, True)), (B.CG_F32, (8, 64, 16, 16, 3, 1), (2, 2, True)),
+    (B.CG_F32, (16, 28, 48, 48, 10, 1), (2, 4, True)), (B.CG_F32, (90, 28, 16, 40, 3, 1), (2, 2, False)), (B.CG_F32, (200, 28, 16, 40, 3, 1), (2, 4, False)),
+    (B.CG_BF16, (1, 20, 40, 40, 12, 1), (1, 1, True)), (B.CG_BF16, (4, 20, 40, 40, 12, 1), (1, 2, True)), (B.CG_BF16, (8, 64, 16, 16, 4, 1), (2, 2, True)),
+    (B.CG_BF16, (16, 28, 48, 48, 12, 1), (2, 4, True)), (B.CG_BF16, (40, 32, 16, 64, 4, 1), (1, 4, False)), (B.CG_BF16, (200, 28, 16, 40, 4, 1), (2, 4, False)),
+    (B.CG_F32, (1, 20, 48, 48, 6, 8), (1, 1, True)), (B.CG_BF16, (200, 28, 16, 80, 4, 4), (2, 4, False)),
+]
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")], ids=["inf", "nan"])
+@pytest.mark.parametrize("dtype,shape,form", INSIDE, ids=["%s_%s%s" % ({0: "fp32", 1: "bf16"}[d], "_".join(map(str, f)), "_grouped" if s[5] > 1 else "")
+                                                          for d, s, f in INSIDE])
+def test_a_value_that_is_not_finite_changes_no_other_sum(dtype, shape, form, bad):
+    """Inputs of any size, so that a sum in another order is another sum.  A bad value in a channel of the conditional path next to the last base channel: no
+    decision changes, and no output but those of fired gates that it reaches.  In the last base channel: nothing outside its window
+    changes.  Both to the bit.  Grouped: outside the window."""
+    n, h, c, co, cb, groups = shape
+    tdt = torch.float32 if dtype == B.CG_F32 else torch.bfloat16
+    g = torch.Generator().manual_seed(c + co)
+    x = torch.randn((n, h, h, c), generator=g).relu().to(tdt).cuda()
+    w = (torch.randn((co, 3, 3, c), generator=g) / (9 * c) ** 0.5).to(tdt).cuda()
+    kw = dict(groups=groups) if groups > 1 else {}
+    layer = B.GatedConv(n_max=n, h=h, w=h, c_in=c, c_out=co, c_base=cb, w_base=w[..., :cb].contiguous(), w_cond=w[..., cb:].contiguous(), in_dtype=dtype,
+                        out_dtype=B.CG_F32, epilogue=0, gate_mean=np.zeros(co), gate_var=np.ones(co), delta=np.full(co, 0.2), **kw)
+    y0, bits0 = [t.clone() for t in layer.forward(x, counts=False)[:2]]
+    fired = torch.from_numpy(W.unpack_bitmap(bits0.cpu().numpy().view(np.uint32), co)).reshape(n, h, h, co).bool().cuda()
+    assert 0.05 < fired.float().mean() < 0.7 and torch.isfinite(y0).all()
+    for channel in (cb, cb - 1):
+        bad_x, near = x.clone(), torch.zeros((n, h, h, 1), dtype=torch.bool, device="cuda")
+        for img, r, s in ((0, 3, 4), (0, h - 1, 0), (n - 1, h // 2, h - 2)):
+            bad_x[img, r, s, channel] = bad
+            near[img, max(0, r - 1):r + 2, max(0, s - 1):s + 2] = True
+        y, bits = layer.forward(bad_x, counts=False)[:2]
+        own = groups == 1 and channel == cb                        # only fired gates may see it
+        same_bits = torch.ones_like(near) if own else ~near
+        assert torch.equal(bits.reshape(n, h, h, -1)[same_bits[..., 0]], bits0.reshape(n, h, h, -1)[same_bits[..., 0]])
+        same = ~(near & fired) if own else (~near).expand_as(fired)
+        assert torch.equal(y[same], y0[same])
+        assert not torch.isfinite(y).all()
+    layer.close()
+
+
 @pytest.mark.parametrize("tau_c", [0.0, 0.3], ids=["plain_gate", "channel_gate"])
 def test_batches_beyond_the_offsets_run_in_pieces(tau_c):
     """x of 1.02 GiB: one piece of 255 images and a rest of six, against calls of 29 images at a time; whole numbers, so equal."""

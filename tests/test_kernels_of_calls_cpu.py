@@ -42,6 +42,12 @@ def test_small_tile_forms(exe):
     assert not missing
 
 
+def test_layers_with_a_base_group_that_ends_inside_a_chunk(exe):
+    for dtype, (n, h, c, co, cb, groups), (pf, nh, split) in small_tiles.INSIDE:
+        kernel, args, _ = K.ask(exe, [K.layer(dtype, n, h, h, c, co, c_base=cb, groups=groups if groups > 1 else 0)])[0]
+        assert (kernel, args) == ("gated_conv_direct_kernel", (TYPE[dtype], str(pf), str(nh), str(split).lower(), str(groups > 1).lower())), (dtype, n, h, c, co)
+
+
 def test_forms_of_the_sums(exe):
     for dtype, (n, h, w, c, co, k), (pf, nh, waves), _ in small_tiles.SUMS:
         kernel, args, threads = K.ask(exe, [K.layer(dtype, n, h, w, c, co, k=k)])[0]
