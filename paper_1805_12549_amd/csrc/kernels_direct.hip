@@ -525,6 +525,7 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
     // the walk's place: UNIFORM: the step's tap and first chunk, else the unit of this lane group
     int tap = 0, ci = 0, so = 0;                    // so (UNIFORM): offset of the step from its pixel's first tap
     unsigned vo[PF];                                // (UNIFORM) the lanes' offsets at this tap
+    const int row16 = p.rowb >> 4, px16 = p.xps >> 4;                               // (otherwise) in chunks: 24 bits hold them and their differences
     const int gap16 = p.gap_len * 16, first16 = (cfirst * 16) + (gap_at <= 0 ? gap16 : 0);
     const int dt = nq > 4 ? 0 : nq >= 3 ? 1 : nq == 2 ? 2 : 4, di = 4 - dt * nq;    // (otherwise) a step on: so many taps and chunks on
     auto enter_tap = [&]() __attribute__((always_inline)) {
@@ -562,10 +563,10 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
           const int c = cfirst + ci + (ci >= gap_at ? p.gap_len : 0);
           const int t = on && c < p.total_chunks ? tap : 31;              // (bit 9 and up of the validity mask are zero)
           const int r = (int)__umul24(tap, 11) >> 5;
-          const unsigned off = (unsigned)(__mul24(r, p.rowb - 3 * p.xps) + __mul24(tap, p.xps) + c * 16);
+          const int off16 = __mul24(r, row16 - 3 * px16) + __mul24(tap, px16) + c;
 #pragma unroll
           for (int f = 0; f < PF; ++f) {
-            const unsigned vof = (vmask[f] >> t) & 1u ? xbase[f] + off : kOut;
+            const unsigned vof = (vmask[f] >> t) & 1u ? xbase[f] + ((unsigned)off16 << 4) : kOut;
             x[b][u][f] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)vof, 0, 0));
           }
           const int next = ci + di;

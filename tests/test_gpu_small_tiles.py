@@ -166,6 +166,29 @@ def test_a_value_that_is_not_finite_changes_no_other_sum(dtype, shape, form, bad
     layer.close()
 
 
+# Images one pixel wide whose pixels are of more than 4 MiB: the difference of a row and three pixels is beyond 24 bits of bytes.
+LONG_PIXELS = [(B.CG_F32, (1 << 20) + 4), (B.CG_BF16, (1 << 21) + 8), (B.CG_I8, (1 << 22) + 16)]
+
+
+@pytest.mark.parametrize("dtype,c", LONG_PIXELS, ids=["fp32", "bf16", "int8"])
+def test_long_pixels(dtype, c):
+    """Whole numbers, whose sums stay below 2^24: exact."""
+    g = torch.Generator(device="cuda").manual_seed(c)
+    tdt = {B.CG_F32: torch.float32, B.CG_BF16: torch.bfloat16, B.CG_I8: torch.int8}[dtype]
+    x = torch.randint(0, 2, (1, 3, 1, c), generator=g, device="cuda", dtype=torch.int8).to(tdt)
+    w = torch.randint(-1, 2, (8, 3, 3, c), generator=g, device="cuda", dtype=torch.int8).to(tdt)
+    layer = B.GatedConv(n_max=1, h=3, w=1, c_in=c, c_out=8, c_base=c, w_base=w, w_cond=None, in_dtype=dtype,
+                        out_dtype=B.CG_I32 if dtype == B.CG_I8 else B.CG_F32, epilogue=0)
+    y = layer.forward(x, bitmap=False, counts=False)[0].double().reshape(3, 8)
+    layer.close()
+    want = torch.zeros((3, 8), dtype=torch.float64, device="cuda")
+    for r in range(3):
+        column = w[:, r, 1].double()
+        for row in range(max(0, 1 - r), min(3, 4 - r)):
+            want[row] += column @ x[0, row + r - 1, 0].double()
+    assert want.abs().max() > 100 and torch.equal(y, want)
+
+
 @pytest.mark.parametrize("tau_c", [0.0, 0.3], ids=["plain_gate", "channel_gate"])
 def test_batches_beyond_the_offsets_run_in_pieces(tau_c):
     """x of 1.02 GiB: one piece of 255 images and a rest of six, against calls of 29 images at a time; whole numbers, so equal."""

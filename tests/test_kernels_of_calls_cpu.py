@@ -48,6 +48,11 @@ def test_layers_with_a_base_group_that_ends_inside_a_chunk(exe):
         assert (kernel, args) == ("gated_conv_direct_kernel", (TYPE[dtype], str(pf), str(nh), str(split).lower(), str(groups > 1).lower())), (dtype, n, h, c, co)
 
 
+def test_layers_of_long_pixels(exe):
+    for dtype, c in small_tiles.LONG_PIXELS:
+        assert K.ask(exe, [K.layer(dtype, 1, 3, 1, c, 8)])[0][0] == "gated_conv_direct_kernel"
+
+
 def test_forms_of_the_sums(exe):
     for dtype, (n, h, w, c, co, k), (pf, nh, waves), _ in small_tiles.SUMS:
         kernel, args, threads = K.ask(exe, [K.layer(dtype, n, h, w, c, co, k=k)])[0]
