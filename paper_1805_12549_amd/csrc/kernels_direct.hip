@@ -510,16 +510,17 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
     const int k1 = k0 + n;
     // (to the end of this wavefront's last step, so that a batch's steps past it are zeros; tiles of 64 channels have no such steps)
     const __amdgpu_buffer_rsrc_t wr =
-        __builtin_amdgcn_make_buffer_rsrc((void*)wp, (short)0, NH == 4 ? 2 * (int)wgrp : k1 * 2048 - (NH == 1 ? 1024 : 0), 0x00027000);
+        __builtin_amdgcn_make_buffer_rsrc((void*)wp, (short)0, (int)(NH == 4 ? 2 * wgrp : (unsigned)k1 * 2048u - (NH == 1 ? 1024u : 0u)), 0x00027000);
     i32x4 x[2][kU][PF], w[2][kU][NH];
-    int vw = lane * 16 + k0 * 2048, kx = k0;        // offset of the next step's weights; the next step whose pixels are fetched
+    unsigned vw = (unsigned)lane * 16u + (unsigned)k0 * 2048u;      // offset of the next step's weights
+    int kx = k0;                                    // the next step whose pixels are fetched
     auto fetch_w = [&](auto bt) __attribute__((always_inline)) {
       constexpr int b = decltype(bt)::value;
 #pragma unroll
       for (int u = 0; u < kU; ++u)
 #pragma unroll
         for (int i = 0; i < NH; ++i)
-          w[b][u][i] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, vw + u * 2048 + (i & 1) * 1024, (i >> 1) * (int)wgrp, 0));
+          w[b][u][i] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, (int)(vw + u * 2048 + (i & 1) * 1024), (i >> 1) * (int)wgrp, 0));
       vw += kU * 2048;
     };
     // the walk's place: UNIFORM: the step's tap and first chunk, else the unit of this lane group
@@ -607,7 +608,7 @@ __device__ __forceinline__ void direct_layer(const DirectArgs& p) {
         const unsigned u = 4u * (unsigned)k + (unsigned)(ln >> 4);
         const int t = (int)quot(u, dnq), i = (int)u - t * nq, chunk = cfirst + i + (i >= gap_at ? p.gap_len : 0);
         i32x4 xv = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)unit_at(f, t, chunk), 0, 0));
-        const i32x4 wv = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, ln * 16 + k * 2048 + (h & 1) * 1024, (h >> 1) * (int)wgrp, 0));
+        const i32x4 wv = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, (int)((unsigned)ln * 16u + (unsigned)k * 2048u + (h & 1) * 1024), (h >> 1) * (int)wgrp, 0));
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int bytes = own * (16 / Tr::kCh) - 4 * e;                  // of the word, base channels
@@ -1109,11 +1110,13 @@ DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu) {
   // split: their K always was, over four wavefronts or more, and as one chain of each path (two of a dense layer's) their error against 64 bits
   // was up to 1.8 times as large.  14 such layers: 0.98 of the whole form's time in the mean, 0.88 to 1.11.
   const bool chained = d.in_dtype == CG_BF16 && ks >= 8 && (m + 31) / 32 * (g.n_grp / 2) < 4ll * n_cu;
+  const bool two_in_4g = std::max(g.ksteps[0], g.ksteps[1]) < (1 << 20);        // (tiles of 64 channels: two groups' weights, 2048 bytes a step, at 32-bit offsets)
   g.cost = 1e30;
   for (int pf = 1; pf <= (m > 16 ? 2 : 1); ++pf)
     for (int nh = pf; nh <= (ngrp >= 2 ? 4 : 2); nh *= 2)           // (32 x 16 pixels and channels were never the least)
       for (int split = 1; split <= kMaxSplit; split *= 2) {
         const int nu = pf * nh;
+        if (nh == 4 && !two_in_4g) continue;
         if (split == 1 ? nh == 1 || chained : split < nu || (gated && split < 2)) continue;
         const bool whole = split == 1;
         const long long px = (m + 16 * pf - 1) / (16 * pf), wgs = (whole ? (px + 3) / 4 : px) * tiles_c(nh);

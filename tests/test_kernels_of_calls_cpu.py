@@ -53,6 +53,14 @@ def test_layers_of_long_pixels(exe):
         assert K.ask(exe, [K.layer(dtype, 1, 3, 1, c, 8)])[0][0] == "gated_conv_direct_kernel"
 
 
+@pytest.mark.parametrize("dtype,c", [(B.CG_F32, 1900004), (B.CG_BF16, 3800008), (B.CG_I8, 7600016)], ids=["fp32", "bf16", "int8"])
+def test_weights_of_a_tile_are_within_32_bits(exe, dtype, c):
+    """K of 2^20 steps and more: 2 GiB of weights to 32 channels, so no tiles of 64."""
+    for c_out in (512, 2048, 4096):
+        kernel, args, _ = K.ask(exe, [K.layer(dtype, 1, 100, 1, c, c_out)])[0]
+        assert kernel == "gated_conv_direct_kernel" and args[2] in ("1", "2"), args
+
+
 def test_forms_of_the_sums(exe):
     for dtype, (n, h, w, c, co, k), (pf, nh, waves), _ in small_tiles.SUMS:
         kernel, args, threads = K.ask(exe, [K.layer(dtype, n, h, w, c, co, k=k)])[0]
