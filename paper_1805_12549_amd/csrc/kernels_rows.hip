@@ -295,12 +295,12 @@ struct RowsArgs {
 };
 enum : unsigned {
   kGated = 1u, kGateOnly = 2u, kTwoSided = 4u, kAffine = 8u, kRelu = 16u, kResidual = 32u,
-  kFast = 64u,                               // 2-byte (int8 layers: 1-byte) outputs in natural channel order
+  kFast = 64u,                               // 2-byte (int8 layers: 1-byte) outputs in natural channel order (or kShuf2), within 32-bit offsets (near_outputs)
   kShuf2 = 128u,                             // 2-byte outputs in shuffled channel order
   kOnePair = 256u,                           // the two scale/shift pairs are the same
   kFit32 = 512u,                             // int8: the requantisation fits 32 bits
   kPairs = 1024u,                            // two wavefronts to a fragment
-  kFourBytes = 2048u,                        // float (int8 layers: 32-bit) outputs in natural channel order
+  kFourBytes = 2048u,                        // float (int8 layers: 32-bit) outputs in natural channel order, within 32-bit offsets
 };
 
 constexpr int kParamsAt = (sizeof(RowsArgs) + alignof(Params) - 1) / alignof(Params) * alignof(Params);   // of the kernel's arguments
@@ -312,7 +312,8 @@ enum RowsOut {
   kPaired,                                   // the same, tiles of at most four fragments: two wavefronts to one, 32 channels each
   kHalves,                                   // the same, blocks that cover several channel groups
   kShuffled,                                 // fast outputs in shuffled order
-  kAnyOut,                                   // every other output type and order: one lane's pixel at a time
+  kAnyOut,                                   // the rest, one lane's pixel at a time: shuffled orders without LDS for them, int8 outputs of shifts below two,
+                                             // more channels than 32-bit offsets reach over (near_outputs)
   kWide,                                     // float and 32-bit outputs in natural order
   kAdded, kPairedAdded,                      // kNatural and kPaired of layers with a residual, which is read before a tile's stages
 };
@@ -1431,6 +1432,19 @@ hipError_t launch_rows_type(const RowsPlan& g, const Params& p, const RowsArgs& 
 
 unsigned magic16(int d) { return d == 1 ? 0u : (unsigned)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d); }
 
+// Whether the outputs and the residual of a tile of pf fragments to a wavefront are within 31-bit offsets of its first pixel (a pixel's bytes are then
+// within the 24 bits of the products that form them): up to 2^21 channels of four bytes, 2^22 of two (2^21 with two fragments), 2^23 of one.
+// The others' outputs take 64-bit addresses (kAnyOut).
+bool near_outputs(int c_out, int out_dtype, int pf) {
+  const int bytes = out_dtype == CG_BF16 ? 2 : out_dtype == CG_I8 ? 1 : 4;
+  return 32ll * kCw * pf * bytes * c_out < (1ll << 31);
+}
+// LDS for the shuffled order's rows: bf16 outputs without a residual
+int shuffle_bytes(const cg_conv_desc& d) {
+  return d.shuffle && d.in_dtype == CG_BF16 && d.out_dtype == CG_BF16 && !(d.epilogue & CG_EPI_RESIDUAL) && near_outputs(d.c_out, CG_BF16, 1)
+             ? kCw * 32 * kShufRow : 0;
+}
+
 // The channel walk of both phases in stages of `cps` chunks; false where the shape does not allow them.
 bool plan_walk(const cg_conv_desc& d, int cps, RowsPlan& g, int& base_k, int& c_cond) {
   g.elem_bytes = d.in_dtype == CG_BF16 ? 2 : 1;
@@ -1464,7 +1478,7 @@ bool plan_walk(const cg_conv_desc& d, int cps, RowsPlan& g, int& base_k, int& c_
     c_cond = d.c_in;
   }
   if (base_k % (cps * g.ch) || c_cond % (cps * g.ch)) return false;
-  if (d.c_out % kBn || d.c_out > (1 << 20)) return false;      // (512 pixels' outputs, at most 2 bytes each, at 32-bit offsets)
+  if (d.c_out % kBn) return false;
   g.n_cb = d.c_out / kBn;
   g.cps = cps;
   g.stages[0] = base_k / (cps * g.ch);
@@ -1492,6 +1506,7 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
   const long long rows = (long long)d.n_max * ho;
   // which operand an XCD's L2 should see whole: the heavier one
   g.xcd_cb = (g.n_cb % 8 == 0 && 9ll * d.c_in * d.c_out > (long long)d.n_max * d.h * d.w * d.c_in) ? 1 : 0;
+  if (g.n_cb > 65536 && !g.xcd_cb) return g;             // (div16)
   long long slots = n_cu / g.n_cb;
   if (slots < 1) slots = 1;
   if (slots > rows) slots = rows;
@@ -1521,14 +1536,14 @@ RowsPlan plan_cps(const cg_conv_desc& d, int n_cu, int cps, int max_pf, double* 
   //   of four columns a little more (more lines), and a tile 3500.
   // Two fragments pay with many channels and tiles that fill them: 512 at 28x28, 12 images 43 us against 50; 256 at 14x14, 256
   // images 61 and 61; 128 at 28x28, 128 images 47 and 41.
-  const int shuf_bytes = d.shuffle && d.in_dtype == CG_BF16 && d.out_dtype == CG_BF16 && !(d.epilogue & CG_EPI_RESIDUAL) ? kCw * 32 * kShufRow : 0;
+  const int shuf_bytes = shuffle_bytes(d);
   // stages that are walked with one half of the block's channels of several groups
   const int cpg = d.groups > 1 ? d.c_out / d.groups : 0;
   const bool halved = g.grp_mode == 2 && cpg > 0 && cpg <= 32 && d.c_base % (cps * g.ch) == 0;
   const double h0 = halved ? 0.55 : 1.0, h1 = halved && cpg == 32 ? 1.0 - 0.9 / d.groups : 1.0;
-  const bool pairs = !halved && !d.shuffle && (d.out_dtype == CG_BF16 || (d.out_dtype == CG_I8 && d.rq_shift >= 2));
+  const bool pairs = !halved && !d.shuffle && near_outputs(d.c_out, d.out_dtype, 1) && (d.out_dtype == CG_BF16 || (d.out_dtype == CG_I8 && d.rq_shift >= 2));
   double best = 1e30;
-  const bool wide = d.in_dtype == CG_BF16 && d.out_dtype == CG_BF16 && !d.shuffle && cps == 4;
+  const bool wide = d.in_dtype == CG_BF16 && d.out_dtype == CG_BF16 && !d.shuffle && cps == 4 && near_outputs(d.c_out, CG_BF16, 2);
   for (int pf = 1; pf <= (wide ? max_pf : 1); ++pf)
   for (int fwl = -1; fwl <= 5; ++fwl) {
     if (fwl == 0 || fwl == 1) continue;                    // (16 and 32 rows of one or two columns: no better than a run)
@@ -1625,6 +1640,7 @@ RowsPlan point_plan(const cg_conv_desc& d, int n_cu) {
   const long long px = (long long)d.n_max * d.h * d.w;
   if (px >= (1ll << 30)) return g;
   g.xcd_cb = g.n_cb % 8 == 0 && d.c_out > px ? 1 : 0;
+  if (g.n_cb > 65536 && !g.xcd_cb) return g;
   long long slots = n_cu / g.n_cb;
   if (slots < 1) slots = 1;
   if (slots > (px + 31) / 32) slots = (px + 31) / 32;
@@ -1635,7 +1651,7 @@ RowsPlan point_plan(const cg_conv_desc& d, int n_cu) {
   const int S = g.stages[0] + g.stages[1];
   g.psz = (g.tr * 16 * g.cps + 1023) / 1024 * 1024;
   g.n_pl = g.psz / 1024;
-  g.shuf_bytes = d.shuffle && d.in_dtype == CG_BF16 && d.out_dtype == CG_BF16 && !(d.epilogue & CG_EPI_RESIDUAL) ? kCw * 32 * kShufRow : 0;
+  g.shuf_bytes = shuffle_bytes(d);
   const int room = kLds - kTabBytes - g.shuf_bytes;
   // weights that leave room for four patches stay in LDS
   g.resident = S * wb + 4 * g.psz <= room ? 1 : 0;
@@ -1742,12 +1758,12 @@ hipError_t launch_rows(const RowsPlan& g, const Params& p, const void* w0, const
   a.spg = g.grp_mode == 2 && p.groups > 1 && p.cpg <= 32 && p.c_base % (g.cps * g.ch) == 0 ? p.c_base / (g.cps * g.ch) : 0;
   a.rq_shift = p.rq_shift;
   a.rq_res_mult = p.rq_res_mult;
-  const bool shuf2 = p.shuffle && g.shuf_bytes > 0;
+  const bool shuf2 = p.shuffle && g.shuf_bytes > 0, near = near_outputs(p.c_out, p.out_dtype, g.pf);
   a.flags = (p.gated ? kGated : 0u) | (p.gate_only ? kGateOnly : 0u) | (p.two_sided ? kTwoSided : 0u) |
             ((p.epilogue & CG_EPI_AFFINE) && p.in_dtype != CG_I8 ? kAffine : 0u) | ((p.epilogue & CG_EPI_RELU) ? kRelu : 0u) |
             ((p.epilogue & CG_EPI_RESIDUAL) ? kResidual : 0u) | (p.in_dtype != CG_I8 && (p.one_pair || !(p.epilogue & CG_EPI_AFFINE)) ? kOnePair : 0u) | (p.fit32 ? kFit32 : 0u) |
-            ((p.out_dtype == CG_BF16 || (p.out_dtype == CG_I8 && p.rq_shift >= 2)) && (!p.shuffle || shuf2) ? kFast : 0u) | (shuf2 ? kShuf2 : 0u) |
-            (!p.shuffle && (p.out_dtype == CG_F32 || p.out_dtype == CG_I32) ? kFourBytes : 0u);
+            (near && (p.out_dtype == CG_BF16 || (p.out_dtype == CG_I8 && p.rq_shift >= 2)) && (!p.shuffle || shuf2) ? kFast : 0u) | (shuf2 ? kShuf2 : 0u) |
+            (near && !p.shuffle && (p.out_dtype == CG_F32 || p.out_dtype == CG_I32) ? kFourBytes : 0u);
   const bool pairs = (a.flags & kFast) && !p.shuffle && !a.spg && g.pf == 1 && g.taps == 9 && tile_fragments(g.tr, g.fwl, g.nfc, p.wo) <= kCw / 2;
   if (pairs) a.flags |= kPairs;
   // rows of the patch lie in the banks of others: runs of 32 pixels over several of them, fragments of up to 8 columns (counted for widths of 2

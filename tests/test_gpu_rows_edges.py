@@ -64,3 +64,32 @@ def test_strided_input_pixels_and_repeatability():
     _say(P.compare_float("strided input", a[0].cpu().numpy().astype(np.float64), a[1].cpu().numpy().view(np.uint32),
                          a[2].cpu().numpy().view(np.uint32), ref, 128, B.CG_F32, layer.variant))
     layer.close()
+
+
+# More output channels than a tile's outputs have 32-bit offsets for, and as many as they just do: (type, output type, channels, shuffled, the kernel's
+# form, which tests/test_kernels_of_calls_cpu.py checks).
+F, H, I = B.CG_F32, B.CG_BF16, B.CG_I8
+MANY_CHANNELS = [(H, H, (1 << 20) + 128, False, "1"), (H, H, (1 << 20) + 128, True, "3"), (H, F, (1 << 20) + 128, False, "5"), (H, F, (1 << 21) + 128, False, "4"),
+                 (H, H, (1 << 22) + 512, False, "4"), (H, H, (1 << 22) + 512, True, "4"), (I, I, (1 << 20) + 128, False, "1")]
+
+
+@pytest.mark.parametrize("dtype,out,c,shuffle,form", MANY_CHANNELS, ids=["%d_%d_%d_%s" % (d, o, c, f) for d, o, c, _, f in MANY_CHANNELS])
+def test_many_output_channels(dtype, out, c, shuffle, form):
+    """Small whole numbers against the plain kernel: equal."""
+    g = torch.Generator(device="cuda").manual_seed(c)
+    tdt = torch.int8 if dtype == I else torch.bfloat16
+    odt = {F: torch.float32, H: torch.bfloat16, I: torch.int8}[out]
+    x = torch.randint(0, 4, (1, 2, 2, 32), generator=g, device="cuda", dtype=torch.int8).to(tdt)
+    w_b, w_c = (torch.randint(-2, 3, (c, 3, 3, 16), generator=g, device="cuda", dtype=torch.int8).to(tdt) for _ in range(2))
+    res = torch.randint(-9, 10, (1, 2, 2, c), generator=g, device="cuda", dtype=torch.int8).to(odt)
+    kw = dict(gate_thr_i32=np.full(c, 5, np.int32), rq_mult0=3, rq_mult1=2, rq_shift=8, rq_res_mult=100) if dtype == I else dict(
+        gate_mean=np.zeros(c), gate_var=np.ones(c), delta=np.full(c, 5.0))
+    got = []
+    for variant in (B.CG_VARIANT_MFMA_ROWS, B.CG_VARIANT_NAIVE):
+        layer = B.GatedConv(n_max=1, h=2, w=2, c_in=32, c_out=c, c_base=16, w_base=w_b, w_cond=w_c, in_dtype=dtype, out_dtype=out, variant=variant,
+                            epilogue=B.CG_EPI_RELU | (0 if shuffle else B.CG_EPI_RESIDUAL), **kw, **(dict(groups=2, shuffle=True) if shuffle else {}))
+        assert layer.variant == variant
+        got.append(layer.forward(x, residual=None if shuffle else res))
+        torch.cuda.synchronize()
+        layer.close()
+    assert all(torch.equal(a, b) for a, b in zip(*got)) and int(got[0][2][0]) > c

@@ -5,6 +5,7 @@ import pytest
 from paper_1805_12549_amd import binding as B
 from tests import kernels_of_calls as K
 from tests import test_gpu_nan_outputs as nan_outputs
+from tests import test_gpu_rows_edges as rows_edges
 from tests import test_gpu_small_tiles as small_tiles
 
 
@@ -59,6 +60,14 @@ def test_weights_of_a_tile_are_within_32_bits(exe, dtype, c):
     for c_out in (512, 2048, 4096):
         kernel, args, _ = K.ask(exe, [K.layer(dtype, 1, 100, 1, c, c_out)])[0]
         assert kernel == "gated_conv_direct_kernel" and args[2] in ("1", "2"), args
+
+
+def test_row_tiled_outputs_of_many_channels(exe):
+    """The row-tiled kernel takes as many channels as before its outputs were at 32-bit offsets, beyond them in the form for any output."""
+    for dtype, out, c_out, shuffle, form in rows_edges.MANY_CHANNELS:
+        kernel, args, _ = K.ask(exe, [K.layer(dtype, 1, 2, 2, 32, c_out, c_base=16, groups=2 if shuffle else 0, shuffle=shuffle, out_dtype=out, rq_shift=8,
+                                              variant=B.CG_VARIANT_MFMA_ROWS)])[0]
+        assert (kernel, args[4]) == ("gated_conv_rows_kernel", form), (dtype, out, c_out)
 
 
 def test_forms_of_the_sums(exe):
