@@ -37,8 +37,8 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def calls_command(out) -> list:
-    """g++ on the Python extension of the calls (csrc/py_calls.cpp), against torch's C++ interface and the built library."""
+def calls_command(out, lib_dir) -> list:
+    """g++ on the Python extension of the calls (csrc/py_calls.cpp), against torch's C++ interface and the library in lib_dir."""
     import torch
     home = Path(torch.__file__).resolve().parent
     rocm = Path(hipcc()).resolve().parent.parent
@@ -47,12 +47,12 @@ def calls_command(out) -> list:
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-isystem", str(home / "include"),
             "-isystem", str(home / "include" / "torch" / "csrc" / "api" / "include"), "-isystem", str(rocm / "include"),
             "-isystem", sysconfig.get_paths()["include"], "-I", str(ROOT / "include"), "-I", str(CSRC), str(CSRC / "py_calls.cpp"), "-o", str(out),
-            "-L", str(home / "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-L", str(PKG), "-lcg_conv", "-Wl,-rpath,$ORIGIN"]
+            "-L", str(home / "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-L", str(lib_dir), "-lcg_conv", "-Wl,-rpath,$ORIGIN"]
 
 
 def build(verbose: bool = False, extra=(), jobs: int = 6) -> Path:
     """Compile every source every time it is called (the 'does it build' check): one object per
-    source, compiled side by side, then one link."""
+    source, compiled side by side, then the two links."""
     cc = hipcc()
     work = Path(tempfile.mkdtemp(prefix="cg_build_"))
     try:
@@ -67,18 +67,17 @@ def build(verbose: bool = False, extra=(), jobs: int = 6) -> Path:
 
         with ThreadPoolExecutor(max_workers=max(1, jobs)) as pool:
             objs = list(pool.map(compile_one, SOURCES))
-        tmp = LIB.with_name(LIB.name + ".tmp%d" % os.getpid())
-        link = [cc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", str(tmp)]
-        if verbose:
-            print(" ".join(link), flush=True)
-        subprocess.check_call(link)
-        os.replace(tmp, LIB)
-        tmp = CALLS.with_name(CALLS.name + ".tmp%d" % os.getpid())
-        link = calls_command(tmp)
-        if verbose:
-            print(" ".join(link), flush=True)
-        subprocess.check_call(link)
-        os.replace(tmp, CALLS)
+        # both are linked before either is put in place: a library beside an extension of another build would be called with other arguments
+        lib, calls = work / LIB.name, work / CALLS.name
+        for link in ([cc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", str(lib)], calls_command(calls, work)):
+            if verbose:
+                print(" ".join(link), flush=True)
+            subprocess.check_call(link)
+        placed = [(to.with_name(to.name + ".tmp%d" % os.getpid()), to) for to in (LIB, CALLS)]
+        for built, (tmp, _) in zip((lib, calls), placed):
+            shutil.copy(built, tmp)
+        for tmp, to in placed:
+            os.replace(tmp, to)
     finally:
         shutil.rmtree(work, ignore_errors=True)
     return LIB
