@@ -1,15 +1,18 @@
-"""ctypes binding of the C-ABI library (``include/cg_conv.h``), same names.
+"""Binding of the C-ABI library (``include/cg_conv.h``), same names.
 
 Argument marshalling only: every step of the layer runs in the HIP kernels of
 ``libcg_conv.so``.  There is no CPU fallback; importing this module raises if the
 library has not been built (``python paper_1805_12549_amd/build.py``).
-PyTorch appears only as the owner of device memory and streams: tensors are
-reduced to raw device pointers before they cross the boundary.
+PyTorch appears only as the owner of device memory and streams.  ctypes takes raw
+device pointers; a forward call of plain tensors goes through ``_calls.so``
+(``csrc/py_calls.cpp``), which takes the tensors, allocates the outputs asked for
+and passes the library raw pointers too.
 """
 from __future__ import annotations
 
 import ctypes as C
 import importlib.util
+import warnings
 from pathlib import Path
 from typing import Optional
 
@@ -44,13 +47,28 @@ if len(_hip_runtimes_mapped()) > 1:
     raise ImportError("two HIP runtimes are mapped into this process (%s); import torch before anything "
                       "that loads libamdhip64" % ", ".join(_hip_runtimes_mapped()))
 
-_CALLS_PATH = _LIB_PATH.with_name("_calls.so")
-if not _CALLS_PATH.exists():
-    raise ImportError("%s is missing: build it with the library (python paper_1805_12549_amd/build.py or __graft_entry__.build())" % _CALLS_PATH)
-_spec = importlib.util.spec_from_file_location("paper_1805_12549_amd._calls", str(_CALLS_PATH))
-_calls = importlib.util.module_from_spec(_spec)
-_spec.loader.exec_module(_calls)
-_native_forward = _calls.forward
+
+def _load_calls(path):
+    """The extension of the calls (csrc/py_calls.cpp), or None where it is not there or not for this torch, whose objects it reads directly: every call
+    then goes through ctypes, to the same kernels with some microseconds more of host time."""
+    if not path.exists():
+        why = "is missing"
+    else:
+        spec = importlib.util.spec_from_file_location("paper_1805_12549_amd._calls", str(path))
+        try:
+            module = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(module)
+        except ImportError as e:
+            why = "does not load (%s)" % e
+        else:
+            if module.torch_version == torch.__version__:
+                return module
+            why = "was built for torch %s, not %s" % (module.torch_version, torch.__version__)
+    warnings.warn("%s %s: calls take more host time until it is built again (python paper_1805_12549_amd/build.py)" % (path, why), stacklevel=2)
+    return None
+
+
+_calls = _load_calls(_LIB_PATH.with_name("_calls.so"))
 
 # the current stream's address without building a Stream object per call
 _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
@@ -212,7 +230,7 @@ def cg_avgpool_fc(x: int, wfc: int, bias: int, logits: int, n: int, hw: int, c: 
 
 def empty_beside(x, bf16: bool, *sizes):
     """A contiguous tensor of that shape (bf16, else fp32) on x's device."""
-    t = _calls.empty(x, bf16, *sizes)
+    t = _calls.empty(x, bf16, *sizes) if _calls is not None else None
     return t if t is not None else torch.empty(sizes, dtype=torch.bfloat16 if bf16 else torch.float32, device=x.device)
 
 
@@ -312,7 +330,8 @@ class GatedConv:
         self.words = (c_out + 31) // 32
         self._y_dtype = getattr(torch, _TORCH_OUT[out_dtype])
         self._ws_need = {}      # workspace bytes per batch size
-        self._native = _calls.Layer(self.handle, self.ho, self.wo, c_out, out_dtype)
+        if _calls is not None:
+            self._native = _calls.Layer(self.handle, self.ho, self.wo, c_out, out_dtype)
 
     def _stream_ptr(self):
         if self.stream is not None:
@@ -322,7 +341,7 @@ class GatedConv:
     def forward(self, x, residual=None, y=None, bitmap=True, counts=True):
         """x: torch device tensor [n,H,W,C_in] (contiguous NHWC).  Returns (y, bitmap, counts)."""
         if self._native is not None:
-            out = _native_forward(self._native, self.stream, x, residual, y, bitmap, counts)
+            out = _calls.forward(self._native, self.stream, x, residual, y, bitmap, counts)
             if out.__class__ is tuple:
                 return out
             if out is not None:

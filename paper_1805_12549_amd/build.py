@@ -44,7 +44,7 @@ def calls_command(out, lib_dir) -> list:
     rocm = Path(hipcc()).resolve().parent.parent
     rocm = rocm if (rocm / "include" / "hip").is_dir() else Path("/opt/rocm")
     return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-isystem", str(home / "include"),
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DCG_TORCH_VERSION="%s"' % torch.__version__, "-isystem", str(home / "include"),
             "-isystem", str(home / "include" / "torch" / "csrc" / "api" / "include"), "-isystem", str(rocm / "include"),
             "-isystem", sysconfig.get_paths()["include"], "-I", str(ROOT / "include"), "-I", str(CSRC), str(CSRC / "py_calls.cpp"), "-o", str(out),
             "-L", str(home / "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-L", str(lib_dir), "-lcg_conv", "-Wl,-rpath,$ORIGIN"]

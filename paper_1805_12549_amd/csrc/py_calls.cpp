@@ -175,6 +175,11 @@ PyMODINIT_FUNC PyInit__calls() {
   if (PyType_Ready(&layer_type) < 0) return nullptr;
   PyObject* const m = PyModule_Create(&module);
   if (!m) return nullptr;
+  // (torch's objects are read as this version lays them out)
+  if (PyModule_AddStringConstant(m, "torch_version", CG_TORCH_VERSION) < 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
   Py_INCREF(&layer_type);
   if (PyModule_AddObject(m, "Layer", (PyObject*)&layer_type) < 0) {
     Py_DECREF(&layer_type);

@@ -73,3 +73,14 @@ def test_errors_and_streams():
     layer.close()
     with pytest.raises(B.CGError):
         layer.forward(x, residual=res)
+
+
+def test_calls_without_the_extension():
+    """The extension is what a built tree runs on; without it the same call goes through ctypes."""
+    assert B._calls is not None
+    layer, x, res = _layer()
+    assert layer._native is not None
+    want = layer.forward(x, residual=res)
+    layer._native = None
+    assert all(torch.equal(p, q) for p, q in zip(want, layer.forward(x, residual=res)))
+    layer.close()
