@@ -44,6 +44,8 @@ struct WithoutGil {
   ~WithoutGil() { PyEval_RestoreThread(state); }
 };
 
+extern PyTypeObject layer_type;
+
 bool plain_tensor(PyObject* o) { return THPVariable_CheckExact(o); }
 
 // an output argument: True (allocate), False / None (leave out), a tensor; anything else: false
@@ -62,6 +64,10 @@ PyObject* forward(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
   HANDLE_TH_ERRORS
   if (n_args != 7) {
     PyErr_SetString(PyExc_TypeError, "forward takes seven arguments");
+    return nullptr;
+  }
+  if (Py_TYPE(args[0]) != &layer_type) {
+    PyErr_SetString(PyExc_TypeError, "forward's first argument is a Layer");
     return nullptr;
   }
   const Layer* const l = (const Layer*)args[0];

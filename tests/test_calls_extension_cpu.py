@@ -35,3 +35,12 @@ def test_import(tmp_path, case, starts):
     r = subprocess.run([sys.executable, "-c", CHECK.format(other=case == "other_torch", package=PKG.name)], cwd=tmp_path, capture_output=True, text=True,
                        timeout=300)
     assert r.returncode == 0 and r.stdout.startswith(starts), (r.stdout, r.stderr[-2000:])
+
+
+@pytest.mark.skipif(not (PKG / "libcg_conv.so").exists() or not (PKG / "_calls.so").exists(), reason="needs the built library")
+def test_forward_takes_a_layer_only():
+    """(an object of another type was read as a layer)"""
+    from paper_1805_12549_amd import binding as B
+    for other in (None, 0, object(), "layer"):
+        with pytest.raises(TypeError, match="Layer"):
+            B._calls.forward(other, None, None, None, None, False, False)
