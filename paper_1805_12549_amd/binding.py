@@ -228,10 +228,10 @@ def cg_avgpool_fc(x: int, wfc: int, bias: int, logits: int, n: int, hw: int, c: 
                               hip_stream))
 
 
-def empty_beside(x, bf16: bool, *sizes):
-    """A contiguous tensor of that shape (bf16, else fp32) on x's device."""
-    t = _calls.empty(x, bf16, *sizes) if _calls is not None else None
-    return t if t is not None else torch.empty(sizes, dtype=torch.bfloat16 if bf16 else torch.float32, device=x.device)
+def empty_beside(x, *sizes):
+    """A contiguous bf16 tensor of that shape on x's device."""
+    t = _calls.empty_bf16(x, *sizes) if _calls is not None else None
+    return t if t is not None else torch.empty(sizes, dtype=torch.bfloat16, device=x.device)
 
 
 def cg_conv_info(handle: int):

@@ -121,24 +121,24 @@ PyObject* forward(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
   END_HANDLE_TH_ERRORS
 }
 
-// empty(like, bf16, sizes ...): a contiguous bf16 or fp32 tensor on the device of `like`; None: not a plain tensor
-PyObject* empty(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
+// empty_bf16(like, sizes ...): a contiguous bf16 tensor on the device of `like`; None: not a plain tensor
+PyObject* empty_bf16(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
   HANDLE_TH_ERRORS
-  if (n_args < 3 || n_args > 6) {
-    PyErr_SetString(PyExc_TypeError, "empty takes a tensor, a truth value and one to four sizes");
+  if (n_args < 2 || n_args > 5) {
+    PyErr_SetString(PyExc_TypeError, "empty_bf16 takes a tensor and one to four sizes");
     return nullptr;
   }
   if (at::impl::torch_function_mode_enabled() || !plain_tensor(args[0])) Py_RETURN_NONE;
   const at::Tensor& like = THPVariable_Unpack(args[0]);
   int64_t sizes[4];
-  for (Py_ssize_t i = 2; i < n_args; ++i) {
-    sizes[i - 2] = PyLong_AsLongLong(args[i]);
-    if (sizes[i - 2] == -1 && PyErr_Occurred()) return nullptr;
+  for (Py_ssize_t i = 1; i < n_args; ++i) {
+    sizes[i - 1] = PyLong_AsLongLong(args[i]);
+    if (sizes[i - 1] == -1 && PyErr_Occurred()) return nullptr;
   }
   at::Tensor t;
   {
     const WithoutGil released;
-    t = at::empty(at::IntArrayRef(sizes, n_args - 2), at::TensorOptions().device(like.device()).dtype(args[1] == Py_True ? at::kBFloat16 : at::kFloat));
+    t = at::empty(at::IntArrayRef(sizes, n_args - 1), at::TensorOptions().device(like.device()).dtype(at::kBFloat16));
   }
   return THPVariable_Wrap(t);
   END_HANDLE_TH_ERRORS
@@ -163,7 +163,7 @@ PyTypeObject layer_type = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
 PyMethodDef methods[] = {
     {"forward", (PyCFunction)(void (*)(void))forward, METH_FASTCALL, "forward(layer, stream, x, residual, y, bitmap, counts)"},
-    {"empty", (PyCFunction)(void (*)(void))empty, METH_FASTCALL, "empty(like, bf16, *sizes)"},
+    {"empty_bf16", (PyCFunction)(void (*)(void))empty_bf16, METH_FASTCALL, "empty_bf16(like, *sizes)"},
     {nullptr, nullptr, 0, nullptr},
 };
 

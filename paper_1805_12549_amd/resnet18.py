@@ -59,7 +59,7 @@ class _Shortcut:
         s = self.spec
         n = x.shape[0]
         ho = (s.hw - 1) // 2 + 1
-        y = B.empty_beside(x, True, n, ho, ho, s.c_out)
+        y = B.empty_beside(x, n, ho, ho, s.c_out)
         B.cg_pointwise_conv(x.data_ptr(), self.w.data_ptr(), self.scale.data_ptr(), self.shift.data_ptr(), y.data_ptr(),
                             n, s.hw, s.hw, s.c_in, s.c_out, 2, False, B.current_stream_ptr())
         return y, None, None
