@@ -32,15 +32,16 @@ def layer(in_dtype, n, h, w, c_in, c_out, *, c_base=None, k=3, stride=1, pad=Non
 
 
 def ask(exe, layers):
-    """(kernel, template arguments, threads to a workgroup) of each layer's first launch."""
+    """(kernel, template arguments, threads to a workgroup, types of its arguments) of each layer's first launch.  (Small-tile kernels of the same template
+    arguments differ in the last: UniformArgs where every K step lies inside one tap, else DirectArgs.)"""
     text = "\n".join(" ".join(str(v) for v in line) for line in layers) + "\n"
     r = subprocess.run([str(exe)], input=text, capture_output=True, text=True, timeout=120)
     lines = r.stdout.splitlines()
     assert r.returncode == 0 and len(lines) == len(layers), r.stderr[-2000:]
     out = []
     for line in lines:
-        m = re.search(r"(\w+)(?:<([^()]*)>)?\([^()]*\) (\d+)$", line.replace("(anonymous namespace)", "anonymous"))
+        m = re.search(r"(\w+)(?:<([^()]*)>)?\(([^()]*)\) (\d+)$", line.replace("(anonymous namespace)", "anonymous"))
         assert m, line
-        args = tuple(a.strip().split("::")[-1] for a in (m.group(2) or "").split(","))
-        out.append((m.group(1), args, int(m.group(3))))
+        names = lambda text: tuple(a.strip().split("::")[-1] for a in text.split(","))
+        out.append((m.group(1), names(m.group(2) or ""), int(m.group(4)), names(m.group(3))))
     return out

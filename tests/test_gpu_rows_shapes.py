@@ -173,14 +173,17 @@ def test_two_wavefronts_to_a_fragment(shape):
                    name=shape.name)
 
 
-ENDS = [S(6, 9, 13, 64, 64), S(40, 14, 14, 256, 256), S(16, 20, 20, 128, 128), S(3, 30, 70, 64, 192, stride=2), S(23, 13, 11, 512, 1024, k=1, pad=0)]
+# (the first four: two wavefronts to a fragment; the next three: one, stages of two chunks and of four)
+ENDS = [S(6, 9, 13, 64, 64), S(40, 14, 14, 256, 256), S(16, 20, 20, 128, 128), S(3, 30, 70, 64, 192, stride=2),
+        S(2, 6, 141, 128, 64), S(31, 18, 45, 64, 64, groups=2), S(17, 33, 44, 128, 64, groups=2), S(23, 13, 11, 512, 1024, k=1, pad=0)]
 
 
 @pytest.mark.parametrize("one_pair", [False, True])
 @pytest.mark.parametrize("shape", ENDS, ids=[s.name for s in ENDS])
 def test_outputs_with_and_without_scale_shift_and_residual(shape, one_pair):
-    """Each way through the end of a tile: no scale/shift, one pair, a pair by each decision; with and without a residual; tiles
-    whose last fragment has lanes without a pixel, whose places must neither be read nor written."""
+    """Each way through the end of a tile: no scale/shift, one pair, a pair by each decision; with and without a residual; one and two wavefronts to
+    a fragment (tests/test_kernels_of_calls_cpu.py checks the forms); tiles whose last fragment has lanes without a pixel, whose places must neither be
+    read nor written."""
     c, rng = shape.c_out, np.random.default_rng(shape.h)
     pair = [rng.uniform(0.5, 1.5, c), rng.normal(0, 0.1, c)]
     other = pair if one_pair else [rng.uniform(0.5, 1.5, c), rng.normal(0, 0.1, c)]
@@ -201,7 +204,7 @@ def test_outputs_with_and_without_scale_shift_and_residual(shape, one_pair):
 @pytest.mark.parametrize("shape", ENDS, ids=[s.name for s in ENDS])
 def test_outputs_of_four_bytes(shape):
     """Float and 32-bit outputs, 16 channels of a pixel by four lanes: the same ways through the end, and sums that a residual
-    takes past 32 bits (the sums of 128 to 512 channels times nine taps stay below 2^27, a residual of 2^30 each way does not)."""
+    takes past 32 bits either way (the sums of 64 to 512 channels times nine taps stay below 2^27, residuals go to 2^32), with ReLU too."""
     c, rng = shape.c_out, np.random.default_rng(shape.w)
     aff = dict(scale0=rng.uniform(0.5, 1.5, c), shift0=rng.normal(0, 0.1, c), scale1=rng.uniform(0.5, 1.5, c), shift1=rng.normal(0, 0.1, c))
     one = dict(aff, scale1=aff["scale0"], shift1=aff["shift0"])
@@ -216,5 +219,20 @@ def test_outputs_of_four_bytes(shape):
     q = W.quantize_int8(W.make_inputs(shape, 9950 + shape.h, kind="coherent", rho=0.35))
     thr = W.calibrate_gate_int8(q, 0.35, sample_images=None)
     r8 = rng.integers(-128, 128, (shape.n, shape.ho, shape.wo, c)).astype(np.int8)
-    for epi, more in ((relu, {}), (added, dict(residual=r8, rq_res_mult=-(1 << 25))), (added | relu, dict(residual=r8, rq_res_mult=1 << 23))):
+    for epi, more in ((relu, {}), (added, dict(residual=r8, rq_res_mult=-(1 << 25))), (added | relu, dict(residual=r8, rq_res_mult=1 << 25))):
         P.run_int8(q, thr, epilogue=epi, n_run=n, name=shape.name, **more, **rows)
+
+
+@pytest.mark.parametrize("shape", ENDS, ids=[s.name for s in ENDS])
+def test_int8_outputs_with_and_without_residual(shape):
+    c, rng = shape.c_out, np.random.default_rng(shape.n)
+    q = W.quantize_int8(W.make_inputs(shape, 9960 + shape.h, kind="coherent", rho=0.35))
+    thr = W.calibrate_gate_int8(q, 0.35, sample_images=None)
+    r8 = rng.integers(-128, 128, (shape.n, shape.ho, shape.wo, c)).astype(np.int8)
+    rows = dict(variant=B.CG_VARIANT_MFMA_ROWS) if shape.k == 3 else {}
+    for lo, hi, shift, fits in ((-200, 200, 14, False), (20, 200, 14, True)):      # in 64 bits and in 32
+        rq = dict(rq_mult0=rng.integers(lo, hi, c).astype(np.int32), rq_mult1=rng.integers(lo, hi, c).astype(np.int32),
+                  rq_bias=rng.integers(-hi, hi, c).astype(np.int32), rq_shift=shift)
+        assert fits_32_bits(rq, hi // 2, True) == fits_32_bits(rq, 0, False) == fits
+        P.run_int8(q, thr, out_i8=True, rq=rq, epilogue=B.CG_EPI_RELU, n_run=max(1, shape.n - 1), name=shape.name, **rows)
+        P.run_int8(q, thr, out_i8=True, rq=rq, residual=r8, rq_res_mult=hi // 2, epilogue=B.CG_EPI_RESIDUAL, n_run=max(1, shape.n - 1), name=shape.name, **rows)

@@ -263,10 +263,28 @@ TILES = [
     (S(527, 6, 4, 16, 100), True, {F: (1, 4, False)}),
     (S(49, 15, 6, 16, 344), True, {F: (1, 2, False)}),
     (S(1698, 1, 52, 8, 10, k=1, pad=0, stride=2, groups=2), True, {H: (1, 2, False)}),
+    (S(578, 2, 12, 96, 33, k=1, pad=0), False, {F: (2, 4, True)}),
+]
+
+# The same where every K step lies inside one tap, which are kernels of their own.  (All but fp32, 32 x 64, not split, which no layer was found to run in.)
+UNIFORM = [
+    (S(4, 33, 32, 128, 33, k=1, pad=0, stride=2, groups=2), False, {F: (1, 2, True), H: (1, 2, True), I: (1, 2, True)}),
+    (S(94, 7, 21, 128, 18, k=1, pad=0, stride=2, groups=2), False, {F: (2, 2, True), H: (2, 2, True), I: (2, 2, True)}),
+    (S(69, 21, 6, 128, 34, k=1, pad=0, stride=2, groups=2), False, {H: (1, 4, True), I: (1, 4, True)}),
+    (S(21, 11, 18, 128, 36, k=1, pad=0, groups=2), False, {H: (2, 4, True), I: (2, 4, True)}),
+    (S(204, 21, 11, 128, 17, k=1, pad=0, groups=2), False, {F: (1, 2, False), H: (1, 2, False), I: (1, 2, False)}),
+    (S(232, 23, 5, 128, 34, k=1, pad=0, groups=2), False, {F: (2, 2, False), H: (2, 4, False), I: (2, 4, False)}),
+    (S(27, 9, 12, 128, 299, k=1, pad=0, stride=2, groups=2), False, {F: (1, 4, True)}),
+    (S(43, 35, 35, 128, 20, k=1, pad=0, groups=2), False, {H: (2, 2, False), I: (2, 2, False)}),
+    (S(81, 32, 14, 128, 33, k=1, pad=0, groups=2), False, {H: (1, 4, False), I: (1, 4, False)}),
+    (S(29, 17, 11, 128, 358, k=1, pad=0), False, {F: (1, 4, False)}),
+    (S(8, 54, 35, 96, 33, k=1, pad=0, groups=2), False, {F: (2, 4, True)}),
+    (S(20, 13, 11, 128, 72, groups=2), False, {F: (1, 2, True), H: (2, 4, True), I: (2, 4, True)}),      # 3x3: K goes over taps and around the base group
+    (S(4, 14, 14, 512, 512), False, {I: (2, 4, True)}),
 ]
 
 
-@pytest.mark.parametrize("shape,grouped,forms", TILES, ids=[t[0].name + ("_grouped" if t[1] else "") for t in TILES])
+@pytest.mark.parametrize("shape,grouped,forms", TILES + UNIFORM, ids=[t[0].name + ("_grouped" if t[1] else "") for t in TILES + UNIFORM])
 def test_every_tile(shape, grouped, forms):
     inp = W.make_inputs(shape, 7500 + shape.c_out + shape.h, kind="iid", rho=0.3, round_bf16=True, grouped=grouped)
     gate = W.calibrate_gate(inp, 0.3, sample_images=None)

@@ -6,6 +6,7 @@ from paper_1805_12549_amd import binding as B
 from tests import kernels_of_calls as K
 from tests import test_gpu_nan_outputs as nan_outputs
 from tests import test_gpu_rows_edges as rows_edges
+from tests import test_gpu_rows_shapes as rows_shapes
 from tests import test_gpu_small_tiles as small_tiles
 
 
@@ -27,25 +28,28 @@ TYPE = {B.CG_F32: "F32Direct", B.CG_BF16: "Bf16Direct", B.CG_I8: "I8Direct"}
 
 def test_small_tile_forms(exe):
     seen = set()
-    for shape, grouped, forms in small_tiles.TILES:
+    for at, (shape, grouped, forms) in enumerate(small_tiles.TILES + small_tiles.UNIFORM):
         for dtype, (pf, nh, split) in forms.items():
-            kernel, args, _ = K.ask(exe, [_layer(dtype, shape, grouped)])[0]
+            kernel, args, _, types = K.ask(exe, [_layer(dtype, shape, grouped)])[0]
             assert (kernel, args) == ("gated_conv_direct_kernel", (TYPE[dtype], str(pf), str(nh), str(split).lower(), str(grouped).lower())), shape
-            seen.add(args)
+            assert at < len(small_tiles.TILES) or types == ("UniformArgs",), shape
+            seen.add(args + types)
     for shape in small_tiles.FORMS + small_tiles.SHAPES:
         for dtype, ch in ((B.CG_F32, 4), (B.CG_BF16, 8), (B.CG_I8, 16)):
             for grouped in (False, True):
                 if shape.c_in % ch == 0 and not (grouped and (shape.c_out % shape.groups or shape.k != 3)):
-                    seen.add(K.ask(exe, [_layer(dtype, shape, grouped)])[0][1])
+                    _, args, _, types = K.ask(exe, [_layer(dtype, shape, grouped)])[0]
+                    seen.add(args + types)
     tiles = [("1", "1", "true")] + [(pf, nh, split) for pf, nh in (("1", "2"), ("1", "4"), ("2", "2"), ("2", "4")) for split in ("true", "false")]
-    missing = [(TYPE[d],) + t + (mixed,) for d in TYPE for t in tiles for mixed in ("false", "true")
-               if (TYPE[d],) + t + (mixed,) not in seen and not (mixed == "true" and d == B.CG_I8)]
-    assert not missing
+    forms = [(TYPE[d],) + t + ("false", args) for d in TYPE for t in tiles for args in ("DirectArgs", "UniformArgs")]
+    forms += [(TYPE[d],) + t + ("true", "DirectArgs") for d in TYPE if d != B.CG_I8 for t in tiles]
+    missing = [f for f in forms if f not in seen]
+    assert missing == [("F32Direct", "2", "4", "false", "false", "UniformArgs")]
 
 
 def test_layers_with_a_base_group_that_ends_inside_a_chunk(exe):
     for dtype, (n, h, c, co, cb, groups), (pf, nh, split) in small_tiles.INSIDE:
-        kernel, args, _ = K.ask(exe, [K.layer(dtype, n, h, h, c, co, c_base=cb, groups=groups if groups > 1 else 0)])[0]
+        kernel, args, *_ = K.ask(exe, [K.layer(dtype, n, h, h, c, co, c_base=cb, groups=groups if groups > 1 else 0)])[0]
         assert (kernel, args) == ("gated_conv_direct_kernel", (TYPE[dtype], str(pf), str(nh), str(split).lower(), str(groups > 1).lower())), (dtype, n, h, c, co)
 
 
@@ -58,21 +62,35 @@ def test_layers_of_long_pixels(exe):
 def test_weights_of_a_tile_are_within_32_bits(exe, dtype, c):
     """K of 2^20 steps and more: 2 GiB of weights to 32 channels, so no tiles of 64."""
     for c_out in (512, 2048, 4096):
-        kernel, args, _ = K.ask(exe, [K.layer(dtype, 1, 100, 1, c, c_out)])[0]
+        kernel, args, *_ = K.ask(exe, [K.layer(dtype, 1, 100, 1, c, c_out)])[0]
         assert kernel == "gated_conv_direct_kernel" and args[2] in ("1", "2"), args
 
 
 def test_row_tiled_outputs_of_many_channels(exe):
     """The row-tiled kernel takes as many channels as before its outputs were at 32-bit offsets, beyond them in the form for any output."""
     for dtype, out, c_out, shuffle, form in rows_edges.MANY_CHANNELS:
-        kernel, args, _ = K.ask(exe, [K.layer(dtype, 1, 2, 2, 32, c_out, c_base=16, groups=2 if shuffle else 0, shuffle=shuffle, out_dtype=out, rq_shift=8,
+        kernel, args, *_ = K.ask(exe, [K.layer(dtype, 1, 2, 2, 32, c_out, c_base=16, groups=2 if shuffle else 0, shuffle=shuffle, out_dtype=out, rq_shift=8,
                                               variant=B.CG_VARIANT_MFMA_ROWS)])[0]
         assert (kernel, args[4]) == ("gated_conv_rows_kernel", form), (dtype, out, c_out)
 
 
+def test_row_tiled_forms_of_the_ends(exe):
+    """One and two wavefronts to a fragment, with and without a residual, stages of two chunks and of four, and 1x1: both types."""
+    seen = set()
+    for s in rows_shapes.ENDS:
+        for dtype in (B.CG_BF16, B.CG_I8):
+            for epilogue in (0, B.CG_EPI_RESIDUAL):
+                kernel, args, *_ = K.ask(exe, [K.layer(dtype, s.n, s.h, s.w, s.c_in, s.c_out, c_base=s.c_base, k=s.k, stride=s.stride, pad=s.pad, out_dtype=dtype,
+                                                       epilogue=epilogue, rq_shift=14, variant=B.CG_VARIANT_MFMA_ROWS if s.k == 3 else B.CG_VARIANT_AUTO)])[0]
+                assert kernel == "gated_conv_rows_kernel", s
+                seen.add(args)
+    for kind in ("Bf16Rows", "I8Rows"):
+        assert {(kind, cps, "1", "9", out) for cps in "24" for out in "0167"} <= seen and {(kind, "8", "1", "1", out) for out in "06"} <= seen
+
+
 def test_forms_of_the_sums(exe):
     for dtype, (n, h, w, c, co, k), (pf, nh, waves), _ in small_tiles.SUMS:
-        kernel, args, threads = K.ask(exe, [K.layer(dtype, n, h, w, c, co, k=k)])[0]
+        kernel, args, threads, _ = K.ask(exe, [K.layer(dtype, n, h, w, c, co, k=k)])[0]
         assert (kernel, args[:4]) == ("gated_conv_direct_kernel", (TYPE[dtype], str(pf), str(nh), str(waves > 1).lower())), (dtype, n, h, w, c, co, k)
         assert threads == (64 * waves if waves > 1 else 256), (dtype, n, h, w, c, co, k)
 
