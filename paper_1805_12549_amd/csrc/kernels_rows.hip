@@ -500,10 +500,6 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     issue();
     bare_barrier();                          // the counters are set up
     int free_to = 0;
-    // The loop starts behind a boundary of the instruction cache's lines, wherever the code before it ends: four wavefronts walk 5 KB with
-    // branches between any two loads, and where they enter a line decides what a fetch is worth.  Behind the boundary by the preheader's 16 bytes, or 48:
-    // 256 channels at 8x8, 128 images 14.1 us, 63x63 stride 2 73.0; 0 or 32 bytes: 14.4, 74.1.
-    asm volatile(".p2align 6");
     while (iv < V) {
       // the buffer of stage iv is free when every multiplying wavefront is done with stage iv - nb
       while (free_to < iv - a.nb + 1 && out < iv) {
