@@ -304,8 +304,10 @@ void pick_kernel(const cg_conv* h, CallPlan* c) {
     c->kernel = kDirect;
     return;
   }
-  // The estimated times of the two, in clocks.  Over 123 layers of 50 to 250000 output pixels (3x3 and 1x1, strides one and
-  // two) what is picked takes 0.2 % longer than the better of the two in the mean and 8 % at most.  Small-tile kernel / other, us:
+  // The estimated times of the two, in clocks, fitted to slower forms of both (its K loop and end, the row-tiled kernel's outputs).  Over 123 layers of 50 to
+  // 250000 output pixels (3x3 and 1x1, strides one and two) what was picked took 0.2 % longer there than the better of the two in the mean and 8 % at most; with the
+  // present kernels, over 109 layers of 64 to 16000 pixels and 64 to 1024 channels, 1.5 % in the mean, 6 % at the 95th percentile, and some few more (512
+  // to 192 channels at 6x6, 61 images 21.1, on the small-tile kernel 14.3).  Small-tile kernel / other in those forms, us:
   // 512 channels at 7x7, one image 8.9 / 18.9, eight 13.6 / 19.8; 64 at 56x56, one 5.7 / 8.5, four 9.8 / 9.0, eight 15.2 /
   // 10.0; int8 256 at 14x14, eight 8.3 / 10.9.  Strided 1x1 layers, where the other is the large-tile kernel: 256 to 448 at
   // 20x20, 193 images 34 / 188.  Fully connected, 448 to 3968, 49 images 5.4 / 17.8, 2816 to 3776, 378 images 40 / 30.

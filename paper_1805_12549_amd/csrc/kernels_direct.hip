@@ -14,7 +14,7 @@
 // instruction that waits for the one before.  Two forms:
 //
 //   whole   a wavefront owns a tile and walks all of K; the conditional path is walked only if one of
-//           the tile's gates fired.  No barrier, no LDS.
+//           the tile's gates fired.  No barrier; LDS for its own tables only.
 //   SPLIT   a workgroup of 2..8 wavefronts owns one tile and splits K: some wavefronts walk the base
 //           path, the others the conditional path, all at once; the partial sums meet in LDS.  No phase waits for the
 //           gate.  The weights are asked for first, then the pixels' addresses are formed; tables and residual are on their way
@@ -30,13 +30,13 @@
 //
 // (Those are with an end of branches on lanes' values and a K loop whose waits were for every load in flight.  Scalar offsets where a K step lies inside
 // one tap, waits for one batch at a time, sums that meet in straight code and an end shared by up to four wavefronts a unit take 60 layers of
-// 3.4 to 28 us to 0.81 of that time: int8 256 at 14x14 through the binding 5.3 -> 3.9, 96 to 80 at 45x33 7.9 -> 6.6.)
+// 3.4 to 28 us to 0.81 of that time: int8 256 at 14x14 through the binding 5.4 -> 4.1, 96 to 80 at 45x33 7.8 -> 6.6.)
 //
 // K is walked in steps of four units, unit u = tap * chunks + chunk, a unit being one 16-byte channel
 // chunk of one tap; lane group l/16 supplies unit 4k + l/16.  Padding (taps outside the image, units past
 // the last) is an out-of-range buffer load, which returns zeros.  In the chunk in which a base group ends the
-// packed weights are zero for the other path's channels; where a float sum is a NaN there, it is formed again from the path's own channels
-// (0 * inf would otherwise reach it).
+// packed weights are zero for the other path's channels; where a float sum is a NaN there, it is formed again from the path's own channels,
+// in the same order (0 * inf would otherwise reach it).
 #include <algorithm>
 #include <type_traits>
 
@@ -1087,9 +1087,10 @@ DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu) {
   const int ks = g.ksteps[0] + g.ksteps[1];
 
   // Tile and split with the least estimated time, in clocks, fitted to 4500 measured plans of 277 layers (bf16 and int8, fp32
-  // by itself; one to 31000 output pixels, 16 to 4000 channels).  What it picks takes 2.6 % longer than the best plan in
-  // the mean, 13 % at the 95th percentile.  (That is what plans are compared by.  `est`, by which the kernel is chosen, counts the output of many
-  // tiles more: over 123 layers it is 9 % off.)
+  // by itself; one to 31000 output pixels, 16 to 4000 channels), of a form of this kernel whose K loop and end were slower.  There what it picked took 2.6 %
+  // longer than the best plan in the mean, 13 % at the 95th percentile; with the present loop and end, the same constants and 60 layers of 32 to 32000
+  // pixels 4.0 and 22 %, 42 % at most (bf16 1x1, 80 to 224 channels at 19x19, 16 images 7.2 us, not split 5.1).  (That is what plans are compared by.
+  // `est`, by which the kernel is chosen, counts the output of many tiles more: over 123 layers it was 9 % off in that form.)
   //   A K step costs the vector-memory path 50 clocks for 16 pixels (64-byte pieces) and 12 (fp32: 32) for 16 channels of
   //   weights; the matrix cores take 16 (175) for a product, and a wavefront 450 (80) for the latency of a batch of
   //   steps.  Workgroups on a compute unit at the same time overlap in their latencies only.

@@ -22,7 +22,8 @@ def summarize(db_path: str, command: str = "") -> str:
     def shorten(name):
         name = name.replace("cg::(anonymous namespace)::", "").replace("void ", "")
         cut = name.find(">(")
-        name = name[:cut + 1] if cut > 0 else name
+        kept = "(UniformArgs)" if "UniformArgs" in name else ""      # (tells two kernels of the same template arguments apart)
+        name = name[:cut + 1] + kept if cut > 0 else name
         return name if len(name) < 110 else name[:107] + "..."
 
     for name, calls, tot, avg, mn, mx in rows[:12]:
