@@ -2,6 +2,7 @@
 // the input convolution on few channels (7x7 stride 2 on RGB), 3x3 stride-2 max pooling and global
 // average pooling followed by the fully connected layer.  None of them is gated.  bf16 activations
 // and weights, fp32 accumulation.  Also the 1x1 stride-2 shortcut convolutions (cg_pointwise_conv), which are dense too.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -531,7 +532,10 @@ struct PointArgs {
   char* y;
   int m_total, h, wd, c_in, c_out, stride, ho, wo, relu;
   cg::Div d_wo, d_ho;
+  int blocks, per_xcd, ncb;                        // pointwise_tile_kernel: its workgroups, those of an XCD, blocks of 128 channels
+  cg::Div d_ncb;
 };
+constexpr int kPointPx = 64;                       // pixels of its workgroup
 
 // byte offset of the input pixel of output pixel m
 __device__ __forceinline__ long long point_pixel(const PointArgs& a, unsigned m) {
@@ -542,7 +546,7 @@ __device__ __forceinline__ long long point_pixel(const PointArgs& a, unsigned m)
 
 // Few pixels: a workgroup of one wavefront owns 16 pixels x 32 channels and takes both operands straight from memory in 64-byte
 // pieces, all of up to eight K steps (256 channels) at once: what bounds it is one latency.  ResNet-18's three shortcuts of one
-// image 5.2, 6.4 and 9.0 us in the kernel below, whose blocks there are 14, 8 and 8; 3.6, 4.2 and 5.1 us here.
+// image 3.1, 3.5 and 4.0 us.
 __global__ __launch_bounds__(64) void pointwise_small_kernel(PointArgs a) {
   constexpr int U = 8;
   const int lane = threadIdx.x, lj = lane & 15, lg = lane >> 4;
@@ -592,75 +596,94 @@ __global__ __launch_bounds__(64) void pointwise_small_kernel(PointArgs a) {
   }
 }
 
-// Many pixels: a GEMM of the strided
-// pixels (column operand, 16 bytes per lane and K step straight from global memory: a pixel's
-// channels are contiguous) with the weights of a 64-channel block (row operand, laid out once
-// per block in LDS, rows permuted as in the kernel above).  Block = 128 output pixels x 64
-// channels, four wavefronts of 32 pixels each.
-__global__ __launch_bounds__(256) void pointwise_conv_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
-                                                             const float* __restrict__ scale,
-                                                             const float* __restrict__ shift, uint16_t* __restrict__ y,
-                                                             long long m_total, int h, int wd, int c_in, int c_out,
-                                                             int stride, int ho, int wo, int relu) {
-  extern __shared__ __align__(16) uint16_t wlp[];          // [c_in/8 chunks][64 rows][8]
-  const int tid = threadIdx.x;
-  const int cb = blockIdx.y;
-  const int nq = c_in >> 3;
-  for (int i = tid; i < nq * kCb; i += 256) {
-    const int col = i / nq, q = i - col * nq;            // consecutive threads read consecutive 16-byte pieces
-    const int ch = col & 31;
-    const int row = (col & 32) + 8 * ((ch & 15) >> 2) + 4 * (ch >> 4) + (ch & 3);
-    *(uint4*)(wlp + ((q * kCb + row) << 3)) = *(const uint4*)(w + ((long long)(cb * kCb + col) * c_in + q * 8));
-  }
-  __syncthreads();
-  const int lane = tid & 63, wave = tid >> 6;
-  const int lj = lane & 31, lh = lane >> 5;
-  const long long m = (long long)blockIdx.x * 128 + wave * 32 + lj;
-  const bool valid = m < m_total;
-  const long long mm = valid ? m : 0;
-  const int ox = (int)(mm % wo);
-  const long long t2 = mm / wo;
-  const int oy = (int)(t2 % ho);
-  const long long img = t2 / ho;
-  const uint16_t* src = x + ((img * h + (long long)oy * stride) * wd + (long long)ox * stride) * c_in + lh * 8;
-  stem_f32x16 acc[2];
-#pragma unroll
-  for (int fc = 0; fc < 2; ++fc)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[fc][i] = 0.0f;
-  const int steps = c_in >> 4;
-#pragma unroll 4
-  for (int st = 0; st < steps; ++st) {
-    stem_i32x4 b = {0, 0, 0, 0};
-    if (valid) b = *(const stem_i32x4*)(src + st * 16);
-    const int q = 2 * st + lh;
-#pragma unroll
-    for (int fc = 0; fc < 2; ++fc) {
-      const stem_i32x4 a = *(const stem_i32x4*)(wlp + ((q * kCb + 32 * fc + lj) << 3));
-      acc[fc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(stem_bf16x8, a), __builtin_bit_cast(stem_bf16x8, b),
-                                                        acc[fc], 0, 0, 0);
+// Many pixels: a workgroup of four wavefronts owns 64 pixels x 128 channels, a wavefront 32 of the channels.  The pixels go to LDS by
+// direct loads, [K step of 32][pixel][four 16-byte chunks], all K steps at once; a wavefront's weights come straight from memory into
+// registers, up to eight K steps at a time.  Several workgroups fit a compute unit, so one's loads run under another's products.
+// Chunk q of pixel p sits at position q ^ f(p / 4 % 4), f = 0, 2, 3, 1: each of the four groups of lanes that a 16-byte read is served in
+// ({0-3, 12-15, 20-27}, the rest of the first 32, the same 32 lanes on) then covers every bank once.  Bound by the vector-memory path (weights and
+// pixels in pieces of 64 bytes) and, with few channels, by memory.  ResNet-18's three shortcuts, 256 images 29.0, 20.8, 19.4 -> 22.6, 17.6, 15.1 us,
+// 64 images 10.7, 8.8, 8.6 -> 8.6, 6.7, 6.1; 512 to 512 channels at 28x28, 256 images 112 -> 71.  (Before: 128 pixels x 64 channels a workgroup, the
+// pixels in pieces of 32 bytes straight into registers, the weights in LDS, outputs in pieces of 32 bytes.)
+__global__ __launch_bounds__(256) void pointwise_tile_kernel(PointArgs a) {
+  constexpr int U = 8, PB = kPointPx / 16;
+  extern __shared__ __align__(16) char point_lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lj = lane & 15, lg = lane >> 4;
+  // block id mod 8 is the XCD: one takes a run of tiles with all their channel blocks, so that its L2 holds a tile's pixels once
+  const unsigned rank = (blockIdx.x & 7) * (unsigned)a.per_xcd + (blockIdx.x >> 3);
+  if (rank >= (unsigned)a.blocks) return;
+  const unsigned tile = cg::quot(rank, a.d_ncb);
+  const int c0 = (int)(rank - tile * (unsigned)a.ncb) * 128 + wave * 32;
+  const unsigned m0 = tile * kPointPx;
+  const int nq = a.c_in >> 3, steps = (nq + 3) >> 2;
+  auto swap_of = [](int t) { return (t >> 1) | (((t ^ (t >> 1)) & 1) << 1); };
+  {
+    const unsigned m = m0 + 16 * wave + (lane >> 2);
+    const char* const src = a.x + point_pixel(a, m < (unsigned)a.m_total ? m : m0);
+    const int chunk = (lane & 3) ^ swap_of(lane >> 4);
+    char* const dst = point_lds + wave * 1024;
+    for (int st = 0; st < steps; ++st) {
+      const int q = 4 * st + chunk < nq ? 4 * st + chunk : nq - 1;       // (chunks past the end: dropped where they are read)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) unsigned*)(src + q * 16),
+                                       (__attribute__((address_space(3))) unsigned*)(dst + st * (kPointPx * 64)), 16, 0, 0);
     }
   }
-  if (!valid) return;
+  const bool mine = c0 < a.c_out;                  // (c_out is a multiple of 64: the last block may have two idle wavefronts)
+  // row r of block i holds channel 8 * (r / 4) + 4 * i + r % 4: a lane ends up with eight consecutive ones
+  const char* const wr = a.w + (long long)((mine ? c0 : 0) + 8 * (lj >> 2) + (lj & 3)) * (a.c_in * 2) + lg * 16;
+  const int w4 = 4 * a.c_in * 2;
+  stem_i32x4 wv[U][2];
+  auto fetch = [&](int s0) __attribute__((always_inline)) {
 #pragma unroll
-  for (int fc = 0; fc < 2; ++fc) {
-    const int co0 = cb * kCb + 32 * fc + 16 * lh;
-    uint16_t out[16];
-#pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const float4 a4 = scale ? *(const float4*)(scale + co0 + 4 * q4) : float4{1.0f, 1.0f, 1.0f, 1.0f};
-      const float4 b4 = shift ? *(const float4*)(shift + co0 + 4 * q4) : float4{0.0f, 0.0f, 0.0f, 0.0f};
-      const float sc[4] = {a4.x, a4.y, a4.z, a4.w}, sh[4] = {b4.x, b4.y, b4.z, b4.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float v = acc[fc][4 * q4 + e] * sc[e] + sh[e];
-        if (relu) v = fmaxf(v, 0.0f);
-        out[4 * q4 + e] = float_to_bf16(v);
+    for (int u = 0; u < U; ++u) {
+      wv[u][0] = wv[u][1] = stem_i32x4{0, 0, 0, 0};
+      if (4 * (s0 + u) + lg < nq) {                // (a last step of two chunks)
+        wv[u][0] = *(const stem_i32x4*)(wr + (s0 + u) * 64);
+        wv[u][1] = *(const stem_i32x4*)(wr + w4 + (s0 + u) * 64);
       }
     }
-    uint4* dst = (uint4*)(y + m * c_out + co0);
-    dst[0] = *(const uint4*)(out);
-    dst[1] = *(const uint4*)(out + 8);
+  };
+  fetch(0);
+  cg::f32x4 acc[PB][2], sc[2], sh[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int at = (mine ? c0 : 0) + 8 * lg + 4 * i;
+    sc[i] = a.scale ? *(const cg::f32x4*)(a.scale + at) : cg::f32x4{1.0f, 1.0f, 1.0f, 1.0f};
+    sh[i] = a.shift ? *(const cg::f32x4*)(a.shift + at) : cg::f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int b = 0; b < PB; ++b) acc[b][i] = cg::f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  __syncthreads();
+  if (!mine) return;
+  const char* const at = point_lds + lj * 64 + (lg ^ swap_of(lj >> 2)) * 16;
+  for (int s0 = 0; s0 < steps; s0 += U) {
+    if (s0 > 0) fetch(s0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (s0 + u >= steps) break;
+      const bool on = 4 * (s0 + u) + lg < nq;
+#pragma unroll
+      for (int b = 0; b < PB; ++b) {
+        stem_i32x4 xv = *(const stem_i32x4*)(at + (s0 + u) * (kPointPx * 64) + b * 1024);
+        if (!on) xv = stem_i32x4{0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          acc[b][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(stem_bf16x8, wv[u][i]), __builtin_bit_cast(stem_bf16x8, xv),
+                                                              acc[b][i], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < PB; ++b) {
+    const unsigned m = m0 + 16 * b + lj;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      v[e] = acc[b][e >> 2][e & 3] * sc[e >> 2][e & 3] + sh[e >> 2][e & 3];
+      if (a.relu) v[e] = fmaxf(v[e], 0.0f);
+    }
+    if (m < (unsigned)a.m_total)
+      *(uint4*)(a.y + ((long long)m * a.c_out + c0 + 8 * lg) * 2) =
+          uint4{bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]), bf16_pair(v[4], v[5]), bf16_pair(v[6], v[7])};
   }
 }
 
@@ -923,19 +946,35 @@ int cg_pointwise_conv(const void* x, const void* w, const float* scale, const fl
   if (n == 0) return CG_OK;
   const int ho = (h - 1) / stride + 1, wo = (wd - 1) / stride + 1;
   const long long m_total = (long long)n * ho * wo;
-  const long long blocks = (m_total + 127) / 128;
-  if (blocks > 0x7fffffffll) return cg::set_error(CG_EUNSUPPORTED, "cg_pointwise_conv: too large");
-  // Small tiles below a quarter of a block per compute unit.  Small / large tiles, us: 64 to 128 channels, 784 pixels 3.6 / 5.2 and
-  // 12544 (196 blocks) 10.2 / 6.5; 128 to 256, 3136 pixels (100) 6.8 / 5.8; 256 to 512, 784 pixels (56) 5.5 / 9.0.
-  if (blocks * (c_out / kCb) * 4 < cg::cu_count()) {
-    const PointArgs a{(const char*)x, (const char*)w, scale, shift, (char*)y, (int)m_total, h, wd, c_in, c_out, stride, ho, wo, relu,
-                      cg::div_of(wo), cg::div_of(ho)};
+  PointArgs a{(const char*)x, (const char*)w, scale, shift, (char*)y, (int)m_total, h, wd, c_in, c_out, stride, ho, wo, relu,
+              cg::div_of(wo), cg::div_of(ho), 0, 0, (c_out + 127) / 128, cg::div_of((c_out + 127) / 128)};
+  // Small tiles below a quarter of 128 pixels x 64 channels per compute unit, where the large ones leave most of the chip idle.  Small / large, us: 64 to
+  // 128 channels, 3136 pixels (50 blocks of a line of 64) 3.5 and, just past the line, 6272 (98) 3.9; 256 to 512, 588 pixels (40) 5.2, 1176 (80) 5.7.
+  if ((m_total + 127) / 128 * (c_out / kCb) * 4 < cg::cu_count()) {
     hipLaunchKernelGGL(pointwise_small_kernel, dim3((unsigned)((m_total + 15) / 16), (unsigned)(c_out / 32)), dim3(64), 0,
                        (hipStream_t)hip_stream, a);
   } else {
-    hipLaunchKernelGGL(pointwise_conv_kernel, dim3((unsigned)blocks, (unsigned)(c_out / kCb)), dim3(256), (size_t)c_in * kCb * 2,
-                       (hipStream_t)hip_stream, (const uint16_t*)x, (const uint16_t*)w, scale, shift, (uint16_t*)y, m_total, h, wd,
-                       c_in, c_out, stride, ho, wo, relu);
+    // A launch holds less than 2^32 threads and 2^30 pixels; larger batches go in pieces of images, rows or columns.
+    long long cap = std::min(((1ll << 24) - 8) / a.ncb * kPointPx, 1ll << 30);
+    if (cap < kPointPx) return cg::set_error(CG_EUNSUPPORTED, "cg_pointwise_conv: too large");
+    const long long cols = std::min<long long>(wo, cap), rows = cols < wo ? 1 : std::min(cap / wo, (long long)ho);
+    const long long imgs = rows < ho ? 1 : std::min(cap / ((long long)ho * wo), (long long)n);
+    for (long long i = 0; i < n; i += imgs)
+      for (long long r = 0; r < ho; r += rows)
+        for (long long c = 0; c < wo; c += cols) {
+          PointArgs p = a;
+          p.x = a.x + ((i * h + r * stride) * wd + c * stride) * (c_in * 2ll);
+          p.y = a.y + ((i * ho + r) * wo + c) * (c_out * 2ll);
+          p.ho = (int)std::min<long long>(rows, ho - r);
+          p.wo = (int)std::min<long long>(cols, wo - c);
+          p.m_total = (int)(std::min(imgs, n - i) * p.ho * p.wo);
+          p.d_wo = cg::div_of(p.wo);
+          p.d_ho = cg::div_of(p.ho);
+          p.blocks = (p.m_total + kPointPx - 1) / kPointPx * a.ncb;
+          p.per_xcd = (p.blocks + 7) / 8;
+          hipLaunchKernelGGL(pointwise_tile_kernel, dim3((unsigned)p.per_xcd * 8u), dim3(256), (size_t)((c_in + 31) / 32) * (kPointPx * 64),
+                             (hipStream_t)hip_stream, p);
+        }
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return cg::set_error(CG_EHIP, "cg_pointwise_conv: %s", hipGetErrorString(e));
