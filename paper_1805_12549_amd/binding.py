@@ -135,6 +135,8 @@ _lib.cg_conv7x7s2_maxpool.argtypes = [C.c_void_p] * 5 + [C.c_int32] * 6 + [C.c_v
 _lib.cg_conv7x7s2_maxpool.restype = C.c_int
 _lib.cg_pointwise_conv.argtypes = [C.c_void_p] * 5 + [C.c_int32] * 7 + [C.c_void_p]
 _lib.cg_pointwise_conv.restype = C.c_int
+_lib.cg_conv_call_beside.argtypes = [C.c_void_p, C.c_int32] + [C.c_void_p] * 6 + [C.c_int32] * 2 + [C.c_void_p]
+_lib.cg_conv_call_beside.restype = C.c_int
 _lib.cg_maxpool3x3s2.argtypes = [C.c_void_p, C.c_void_p] + [C.c_int32] * 4 + [C.c_void_p]
 _lib.cg_maxpool3x3s2.restype = C.c_int
 _lib.cg_avgpool_fc.argtypes = [C.c_void_p] * 4 + [C.c_int32] * 4 + [C.c_void_p]
@@ -378,6 +380,15 @@ class GatedConv:
         if rc != CG_OK:
             raise CGError(rc, cg_last_error())
         return y, bitmap, counts
+
+    def forward_beside(self, x, w1, scale1, shift1, c_out1):
+        """forward(x) of a bf16 layer without bitmap and counts, and beside it the 1x1 convolution of x with the layer's stride (cg_pointwise_conv,
+        no ReLU): one launch where the layer has few pixels.  Returns (y, y1)."""
+        n = x.shape[0]
+        y, y1 = empty_beside(x, n, self.ho, self.wo, self.c_out), empty_beside(x, n, self.ho, self.wo, c_out1)
+        _check(_lib.cg_conv_call_beside(self.handle, n, x.data_ptr(), y.data_ptr(), w1.data_ptr(), 0 if scale1 is None else scale1.data_ptr(),
+                                        0 if shift1 is None else shift1.data_ptr(), y1.data_ptr(), c_out1, 0, self._stream_ptr()))
+        return y, y1
 
     def close(self):
         if self.handle:

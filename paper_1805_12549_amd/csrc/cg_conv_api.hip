@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "cg_internal.h"
+#include "point_piece.h"
 
 namespace {
 
@@ -694,7 +695,7 @@ namespace {
 // counts: [n][c_out] fired counts; total: their sum, cleared first if clear_total (both NULL or neither)
 int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap,
                  uint32_t* counts, uint32_t* total, bool clear_total, Scratch mode, void* workspace, size_t workspace_bytes,
-                 void* hip_stream);
+                 void* hip_stream, cg::Beside* beside = nullptr);
 
 }  // namespace
 
@@ -714,6 +715,25 @@ size_t cg_conv_call_scratch_bytes(const cg_conv* h, int32_t n, int has_bitmap, i
 int cg_conv_call(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap, uint32_t* counts, void* workspace,
                  size_t workspace_bytes, void* hip_stream) {
   return forward_impl(h, n, x, residual, y, bitmap, counts ? counts + 2 : nullptr, counts, true, kThisCall, workspace, workspace_bytes, hip_stream);
+}
+
+int cg_conv_call_beside(cg_conv* h, int32_t n, const void* x, void* y, const void* w1, const float* scale1, const float* shift1, void* y1, int32_t c_out1,
+                        int32_t relu1, void* hip_stream) {
+  if (!h) return fail(CG_EINVAL, "handle is NULL");
+  const cg_conv_desc& d = h->d;
+  if (d.in_dtype != CG_BF16 || d.x_pixel_stride != d.c_in) return fail(CG_EUNSUPPORTED, "cg_conv_call_beside: bf16 layers of whole pixels only");
+  if (d.epilogue & CG_EPI_RESIDUAL) return fail(CG_EUNSUPPORTED, "cg_conv_call_beside: layers without a residual only");
+  if (d.tau_c > 0.0f) return fail(CG_EUNSUPPORTED, "cg_conv_call_beside: no channel-wise gate");
+  if (h->ho != (d.h - 1) / d.stride + 1 || h->wo != (d.w - 1) / d.stride + 1)
+    return fail(CG_EUNSUPPORTED, "cg_conv_call_beside: layers whose output has the size of the 1x1's only");
+  const int rc = cg::point_check(x, w1, scale1, shift1, y1, n, d.h, d.w, d.c_in, c_out1, d.stride);
+  if (rc != CG_OK || n == 0) return rc;
+  // One launch where the layer runs on the small-tile kernel with its K split and the 1x1 would run in small pieces, else two.
+  cg::Beside both{cg::point_args(x, w1, scale1, shift1, y1, n, d.h, d.w, d.c_in, c_out1, d.stride, relu1), false};
+  const bool pieces = cg::point_in_pieces((long long)n * both.what.ho * both.what.wo, c_out1, cg::cu_count());
+  const int first = forward_impl(h, n, x, nullptr, y, nullptr, nullptr, nullptr, true, kThisCall, nullptr, 0, hip_stream, pieces ? &both : nullptr);
+  if (first != CG_OK || both.done) return first;
+  return cg_pointwise_conv(x, w1, scale1, shift1, y1, n, d.h, d.w, d.c_in, c_out1, d.stride, relu1, hip_stream);
 }
 
 int cg_conv_forward_noalloc(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap,
@@ -767,7 +787,7 @@ namespace {
 
 int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, void* y, uint32_t* bitmap,
                  uint32_t* counts, uint32_t* total, bool clear_total, Scratch mode, void* workspace, size_t workspace_bytes,
-                 void* hip_stream) {
+                 void* hip_stream, cg::Beside* beside) {
   if (!h) return fail(CG_EINVAL, "handle is NULL");
   if (n < 0 || n > h->d.n_max) return fail(CG_EINVAL, "n = %d is outside [0, n_max = %d]", n, h->d.n_max);
   if (n == 0) return CG_OK;
@@ -827,7 +847,10 @@ int forward_impl(cg_conv* h, int32_t n, const void* x, const void* residual, voi
           if (q.bitmap) r.bitmap = q.bitmap + i * px * q.words;
           if (q.chan_mask) r.chan_mask = q.chan_mask + (long long)i * q.words;
           r.clear_total = q.clear_total && i == 0;
-          err = cg::launch_direct(r.n == cp.piece ? cp.direct : cp.direct_rest, r, pk + l.wpd_base_off, pk + l.wpd_cond_off, s);
+          // (a batch in one piece, and the layer's only pass)
+          const bool both = beside && cp.piece >= n && d.tau_c <= 0.0f && cg::takes_beside(cp.direct, r);
+          err = cg::launch_direct(r.n == cp.piece ? cp.direct : cp.direct_rest, r, pk + l.wpd_base_off, pk + l.wpd_cond_off, s, both ? &beside->what : nullptr);
+          if (both) beside->done = true;
         }
         return err;
       }

@@ -136,7 +136,10 @@ struct DirectPlan {
 
 DirectPlan direct_plan(const cg_conv_desc& d, int n, int n_cu);
 hipError_t launch_direct_pack(const DirectPlan& plan, const Params& p, void* wpk_base, void* wpk_cond, hipStream_t s);
-hipError_t launch_direct(const DirectPlan& plan, const Params& p, const void* wpk_base, const void* wpk_cond, hipStream_t s);
+// beside: a 1x1 convolution that the launch does too (takes_beside), or NULL
+struct PointArgs;
+bool takes_beside(const DirectPlan& plan, const Params& p);
+hipError_t launch_direct(const DirectPlan& plan, const Params& p, const void* wpk_base, const void* wpk_cond, hipStream_t s, const PointArgs* beside = nullptr);
 
 // Geometry of the row-tiled matrix-core kernel (kernels_rows.hip): persistent workgroups of 64 output channels
 // that walk runs of output rows in tiles of at most 256 pixels; K in stages of `cps` 16-byte channel chunks

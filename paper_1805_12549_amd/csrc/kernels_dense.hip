@@ -8,6 +8,7 @@
 #include <cstdio>
 
 #include "cg_mfma_common.h"
+#include "point_piece.h"
 
 namespace cg {
 int set_error(int code, const char* fmt, ...);   // defined with the host API
@@ -523,78 +524,12 @@ int launch_conv7x7s2c3(bool pool, const char* who, const void* x, const void* w,
   return CG_OK;
 }
 
-// 1x1 convolution with stride (the ResNet shortcut) on the matrix cores.
-struct PointArgs {
-  const char* x;
-  const char* w;
-  const float* scale;
-  const float* shift;
-  char* y;
-  int m_total, h, wd, c_in, c_out, stride, ho, wo, relu;
-  cg::Div d_wo, d_ho;
-  int blocks, per_xcd, ncb;                        // pointwise_tile_kernel: its workgroups, those of an XCD, blocks of 128 channels
-  cg::Div d_ncb;
-};
-constexpr int kPointPx = 64;                       // pixels of its workgroup
+using cg::PointArgs;
+using cg::point_pixel;
+constexpr int kPointPx = 64;                       // pixels of a workgroup of pointwise_tile_kernel
 
-// byte offset of the input pixel of output pixel m
-__device__ __forceinline__ long long point_pixel(const PointArgs& a, unsigned m) {
-  const unsigned q = cg::quot(m, a.d_wo), img = cg::quot(q, a.d_ho);
-  const long long row = (long long)img * a.h + (q - img * (unsigned)a.ho) * (unsigned)a.stride;
-  return (row * a.wd + (m - q * (unsigned)a.wo) * (unsigned)a.stride) * (a.c_in * 2);
-}
-
-// Few pixels: a workgroup of one wavefront owns 16 pixels x 32 channels and takes both operands straight from memory in 64-byte
-// pieces, all of up to eight K steps (256 channels) at once: what bounds it is one latency.  ResNet-18's three shortcuts of one
-// image 3.1, 3.5 and 4.0 us.
-__global__ __launch_bounds__(64) void pointwise_small_kernel(PointArgs a) {
-  constexpr int U = 8;
-  const int lane = threadIdx.x, lj = lane & 15, lg = lane >> 4;
-  const int c0 = blockIdx.y * 32, nq = a.c_in >> 3, steps = (nq + 3) >> 2;
-  const unsigned m = blockIdx.x * 16 + lj;
-  const bool valid = m < (unsigned)a.m_total;
-  const char* const wr = a.w + (long long)(c0 + lj) * (a.c_in * 2) + lg * 16;
-  const int w16 = 16 * a.c_in * 2;
-  stem_i32x4 wv[U][2], xv[U];
-  cg::f32x4 acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}}, sc[2], sh[2];
-  const char* const xr = a.x + point_pixel(a, valid ? m : 0u) + lg * 16;
-  for (int s0 = 0; s0 < steps; s0 += U) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool on = 4 * (s0 + u) + lg < nq;        // (a last step of two chunks)
-      xv[u] = wv[u][0] = wv[u][1] = stem_i32x4{0, 0, 0, 0};
-      if (on) {
-        wv[u][0] = *(const stem_i32x4*)(wr + (s0 + u) * 64);
-        wv[u][1] = *(const stem_i32x4*)(wr + w16 + (s0 + u) * 64);
-        xv[u] = *(const stem_i32x4*)(xr + (s0 + u) * 64);
-      }
-    }
-    if (s0 == 0) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        sc[i] = a.scale ? *(const cg::f32x4*)(a.scale + c0 + 16 * i + 4 * lg) : cg::f32x4{1.0f, 1.0f, 1.0f, 1.0f};
-        sh[i] = a.shift ? *(const cg::f32x4*)(a.shift + c0 + 16 * i + 4 * lg) : cg::f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(stem_bf16x8, wv[u][i]), __builtin_bit_cast(stem_bf16x8, xv[u]),
-                                                         acc[i], 0, 0, 0);
-  }
-  if (!valid) return;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    float v[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      v[e] = acc[i][e] * sc[i][e] + sh[i][e];
-      if (a.relu) v[e] = fmaxf(v[e], 0.0f);
-    }
-    *(uint2*)(a.y + ((long long)m * a.c_out + c0 + 16 * i + 4 * lg) * 2) = uint2{bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3])};
-  }
-}
+// Few pixels: a workgroup of one wavefront does a piece (point_piece.h), all of up to eight K steps (256 channels) at once.
+__global__ __launch_bounds__(64) void pointwise_small_kernel(PointArgs a) { cg::point_piece<8>(a, blockIdx.x, (int)blockIdx.y); }
 
 // Many pixels: a workgroup of four wavefronts owns 64 pixels x 128 channels, a wavefront 32 of the channels.  The pixels go to LDS by
 // direct loads, [K step of 32][pixel][four 16-byte chunks], all K steps at once; a wavefront's weights come straight from memory into
@@ -889,6 +824,22 @@ __global__ __launch_bounds__(1024) void avgpool_fc_kernel(const uint16_t* __rest
 
 }  // namespace
 
+namespace cg {
+
+int point_check(const void* x, const void* w, const float* scale, const float* shift, const void* y, int n, int h, int wd, int c_in, int c_out, int stride) {
+  if (!x || !w || !y) return cg::set_error(CG_EINVAL, "cg_pointwise_conv: x, w and y must not be NULL");
+  if (n < 0 || h <= 0 || wd <= 0) return cg::set_error(CG_EINVAL, "cg_pointwise_conv: bad image size");
+  if (stride < 1) return cg::set_error(CG_EINVAL, "cg_pointwise_conv: stride must be >= 1");
+  if (c_in <= 0 || c_in % 16 || c_in > 512)
+    return cg::set_error(CG_EUNSUPPORTED, "cg_pointwise_conv: c_in must be a multiple of 16, at most 512");
+  if (c_out <= 0 || c_out % kCb) return cg::set_error(CG_EUNSUPPORTED, "cg_pointwise_conv: c_out must be a multiple of 64");
+  if ((((uintptr_t)x) | ((uintptr_t)w) | ((uintptr_t)y) | ((uintptr_t)scale) | ((uintptr_t)shift)) & 15)
+    return cg::set_error(CG_EINVAL, "cg_pointwise_conv: x, w, y, scale and shift must be 16-byte aligned");
+  return CG_OK;
+}
+
+}  // namespace cg
+
 extern "C" {
 
 int cg_small_cin_conv(const void* x, const void* w, const float* scale, const float* shift, void* y, int32_t n,
@@ -935,22 +886,15 @@ int cg_conv7x7s2_maxpool(const void* x, const void* w, const float* scale, const
 int cg_pointwise_conv(const void* x, const void* w, const float* scale, const float* shift, void* y, int32_t n,
                       int32_t h, int32_t wd, int32_t c_in, int32_t c_out, int32_t stride, int32_t relu,
                       void* hip_stream) {
-  if (!x || !w || !y) return cg::set_error(CG_EINVAL, "cg_pointwise_conv: x, w and y must not be NULL");
-  if (n < 0 || h <= 0 || wd <= 0) return cg::set_error(CG_EINVAL, "cg_pointwise_conv: bad image size");
-  if (stride < 1) return cg::set_error(CG_EINVAL, "cg_pointwise_conv: stride must be >= 1");
-  if (c_in <= 0 || c_in % 16 || c_in > 512)
-    return cg::set_error(CG_EUNSUPPORTED, "cg_pointwise_conv: c_in must be a multiple of 16, at most 512");
-  if (c_out <= 0 || c_out % kCb) return cg::set_error(CG_EUNSUPPORTED, "cg_pointwise_conv: c_out must be a multiple of 64");
-  if ((((uintptr_t)x) | ((uintptr_t)w) | ((uintptr_t)y) | ((uintptr_t)scale) | ((uintptr_t)shift)) & 15)
-    return cg::set_error(CG_EINVAL, "cg_pointwise_conv: x, w, y, scale and shift must be 16-byte aligned");
+  const int rc = cg::point_check(x, w, scale, shift, y, n, h, wd, c_in, c_out, stride);
+  if (rc != CG_OK) return rc;
   if (n == 0) return CG_OK;
-  const int ho = (h - 1) / stride + 1, wo = (wd - 1) / stride + 1;
+  const PointArgs a = cg::point_args(x, w, scale, shift, y, n, h, wd, c_in, c_out, stride, relu);
+  const int ho = a.ho, wo = a.wo;
   const long long m_total = (long long)n * ho * wo;
-  PointArgs a{(const char*)x, (const char*)w, scale, shift, (char*)y, (int)m_total, h, wd, c_in, c_out, stride, ho, wo, relu,
-              cg::div_of(wo), cg::div_of(ho), 0, 0, (c_out + 127) / 128, cg::div_of((c_out + 127) / 128)};
   // Small tiles below a quarter of 128 pixels x 64 channels per compute unit, where the large ones leave most of the chip idle.  Small / large, us: 64 to
   // 128 channels, 3136 pixels (50 blocks of a line of 64) 3.5 and, just past the line, 6272 (98) 3.9; 256 to 512, 588 pixels (40) 5.2, 1176 (80) 5.7.
-  if ((m_total + 127) / 128 * (c_out / kCb) * 4 < cg::cu_count()) {
+  if (cg::point_in_pieces(m_total, c_out, cg::cu_count())) {
     hipLaunchKernelGGL(pointwise_small_kernel, dim3((unsigned)((m_total + 15) / 16), (unsigned)(c_out / 32)), dim3(64), 0,
                        (hipStream_t)hip_stream, a);
   } else {

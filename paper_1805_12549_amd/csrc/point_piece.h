@@ -1,0 +1,103 @@
+// 1x1 convolution with stride (the ResNet shortcut) on the matrix cores, in pieces of one wavefront: a launch of its own (kernels_dense.hip)
+// or further workgroups of the block's first layer (kernels_direct.hip).
+#pragma once
+
+#include "cg_device.h"
+
+namespace cg {
+
+struct PointArgs {
+  const char* x;
+  const char* w;
+  const float* scale;
+  const float* shift;
+  char* y;
+  int m_total, h, wd, c_in, c_out, stride, ho, wo, relu;
+  Div d_wo, d_ho;
+  int blocks, per_xcd, ncb;                        // pointwise_tile_kernel: its workgroups, those of an XCD, blocks of 128 channels
+  Div d_ncb;
+};
+
+inline PointArgs point_args(const void* x, const void* w, const float* scale, const float* shift, void* y, int n, int h, int wd, int c_in, int c_out,
+                            int stride, int relu) {
+  const int ho = (h - 1) / stride + 1, wo = (wd - 1) / stride + 1, ncb = (c_out + 127) / 128;
+  return PointArgs{(const char*)x, (const char*)w, scale, shift, (char*)y, (int)((long long)n * ho * wo), h, wd, c_in, c_out, stride, ho, wo, relu,
+                   div_of(wo), div_of(ho), 0, 0, ncb, div_of(ncb)};
+}
+
+// A 1x1 convolution that a layer's launch may do too; done: it has.
+struct Beside {
+  PointArgs what;
+  bool done;
+};
+
+// Whether the small pieces are taken: below a quarter of 128 pixels x 64 channels per compute unit (see cg_pointwise_conv).
+inline bool point_in_pieces(long long m_total, int c_out, int n_cu) { return (m_total + 127) / 128 * (c_out / 64) * 4 < n_cu; }
+
+// What cg_pointwise_conv refuses (kernels_dense.hip).
+int point_check(const void* x, const void* w, const float* scale, const float* shift, const void* y, int n, int h, int wd, int c_in, int c_out, int stride);
+
+// byte offset of the input pixel of output pixel m
+__device__ __forceinline__ long long point_pixel(const PointArgs& a, unsigned m) {
+  const unsigned q = quot(m, a.d_wo), img = quot(q, a.d_ho);
+  const long long row = (long long)img * a.h + (q - img * (unsigned)a.ho) * (unsigned)a.stride;
+  return (row * a.wd + (m - q * (unsigned)a.wo) * (unsigned)a.stride) * (a.c_in * 2);
+}
+
+// Sixteen pixels (number `px` of them) x 32 channels by one wavefront, which takes both operands straight from memory in 64-byte pieces, U K steps
+// at once: what bounds it is one latency.  ResNet-18's three shortcuts of one image, each a launch of eight steps 3.1, 3.5 and 4.0 us.
+template <int U>
+__device__ __forceinline__ void point_piece(const PointArgs& a, unsigned px, int block) {
+  typedef __attribute__((ext_vector_type(4))) int chunk_t;
+  typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+  typedef __attribute__((ext_vector_type(4))) float sums_t;
+  const int lane = threadIdx.x & 63, lj = lane & 15, lg = lane >> 4;
+  const int c0 = block * 32, nq = a.c_in >> 3, steps = (nq + 3) >> 2;
+  const unsigned m = px * 16 + lj;
+  const bool valid = m < (unsigned)a.m_total;
+  const char* const wr = a.w + (long long)(c0 + lj) * (a.c_in * 2) + lg * 16;
+  const int w16 = 16 * a.c_in * 2;
+  chunk_t wv[U][2], xv[U];
+  sums_t acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}}, sc[2], sh[2];
+  const char* const xr = a.x + point_pixel(a, valid ? m : 0u) + lg * 16;
+  for (int s0 = 0; s0 < steps; s0 += U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool on = 4 * (s0 + u) + lg < nq;        // (a last step of two chunks)
+      xv[u] = wv[u][0] = wv[u][1] = chunk_t{0, 0, 0, 0};
+      if (on) {
+        wv[u][0] = *(const chunk_t*)(wr + (s0 + u) * 64);
+        wv[u][1] = *(const chunk_t*)(wr + w16 + (s0 + u) * 64);
+        xv[u] = *(const chunk_t*)(xr + (s0 + u) * 64);
+      }
+    }
+    if (s0 == 0) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        sc[i] = a.scale ? *(const sums_t*)(a.scale + c0 + 16 * i + 4 * lg) : sums_t{1.0f, 1.0f, 1.0f, 1.0f};
+        sh[i] = a.shift ? *(const sums_t*)(a.shift + c0 + 16 * i + 4 * lg) : sums_t{0.0f, 0.0f, 0.0f, 0.0f};
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wv[u][i]), __builtin_bit_cast(bf16x8_t, xv[u]), acc[i], 0, 0, 0);
+  }
+  if (!valid) return;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = acc[i][e] * sc[i][e] + sh[i][e];
+      if (a.relu) v[e] = fmaxf(v[e], 0.0f);
+    }
+    uint2 out;
+    out.x = (uint32_t)float_to_bf16(v[0]) | (uint32_t)float_to_bf16(v[1]) << 16;
+    out.y = (uint32_t)float_to_bf16(v[2]) | (uint32_t)float_to_bf16(v[3]) << 16;
+    *(uint2*)(a.y + ((long long)m * a.c_out + c0 + 16 * i + 4 * lg) * 2) = out;
+  }
+}
+
+}  // namespace cg

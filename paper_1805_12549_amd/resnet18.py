@@ -228,11 +228,18 @@ class GatedResNet18:
         if trace is not None:
             trace["input"] = dict(x=x, y=stem, pooled=cur)
         block_in = cur
-        fired = 0.0
+        shortcut = None
         for i, spec in enumerate(self.specs):
+            if i + 1 in self.shortcuts and trace is None and not want_counts:
+                # the first layer and the shortcut of the block, of the same input
+                sc = self.shortcuts[i + 1]
+                cur, shortcut = self.layers[i].forward_beside(cur, sc.w, sc.scale, sc.shift, sc.spec.c_out)
+                continue
             res = None
             if spec.residual:
-                if i in self.shortcuts:
+                if i in self.shortcuts and shortcut is not None:
+                    res, shortcut = shortcut, None
+                elif i in self.shortcuts:
                     res, _, _ = self.shortcuts[i].forward(block_in, bitmap=False, counts=False)
                     if trace is not None:
                         trace[self.specs[i - 1].name + ".sc"] = dict(x=block_in, y=res)

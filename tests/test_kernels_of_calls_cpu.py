@@ -4,6 +4,7 @@ import pytest
 
 from paper_1805_12549_amd import binding as B
 from tests import kernels_of_calls as K
+from tests import test_gpu_beside as beside
 from tests import test_gpu_nan_outputs as nan_outputs
 from tests import test_gpu_rows_edges as rows_edges
 from tests import test_gpu_rows_shapes as rows_shapes
@@ -106,3 +107,14 @@ def test_layers_of_the_nan_test(exe):
             assert got[1][2:] == args, (variant, n, hw, c, k)
         elif kernel == "gated_conv_direct_kernel":
             assert got[1][3] == args[0], (variant, n, hw, c, k)
+
+
+def test_layers_with_a_1x1_beside(exe):
+    """The tiles that the layers of test_gpu_beside.py name, and that the 1x1 of the last ones or their own kernel is not for one launch."""
+    for (n, h, w, c_in, c_out, c_base, k, stride, c1), tile in beside.FORMS:
+        kernel, args, _, types = K.ask(exe, [K.layer(B.CG_BF16, n, h, w, c_in, c_out, c_base=c_base, k=k, stride=stride, out_dtype=B.CG_BF16)])[0]
+        pieces = (n * -(-h // stride) * -(-w // stride) + 127) // 128 * (c1 // 64) * 4 < 256
+        one = kernel == "gated_conv_direct_kernel" and args[3] == "true" and pieces
+        assert one == (tile is not None), (n, h, w, c_in)
+        if one:
+            assert (int(args[1]), int(args[2]), types == ("UniformArgs",)) == tile, (n, h, w, c_in)
