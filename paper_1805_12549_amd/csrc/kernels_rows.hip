@@ -35,7 +35,7 @@
 // corrected where a gate fired.
 //
 // TAPS = 1 (1x1 layers of stride 1): a row is a pixel, a patch the tile's pixels (no halo), a stage up to eight chunks of one
-// tap.  1024 channels at 14x14, 64 images: bf16 50 us, int8 38; 99 and 105 on the large-tile kernel.
+// tap.  1024 channels at 14x14, 64 images: bf16 40 us, int8 26; 99 and 105 on the large-tile kernel.
 //
 // What bounds the kernel: at 64 and 128 channels the instructions of gate and output (a third of a wavefront's time each
 // side of the products), at 256 and 512 the LDS reads and, for few images, the start: the first stage of all workgroups
@@ -500,6 +500,73 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     issue();
     bare_barrier();                          // the counters are set up
     int free_to = 0;
+    if (TAPS == 1 && a.nb >= kLw && V >= (a.nb > kLw ? 3 : 12) * a.nb) {
+      // Once all have filled the buffers together a loading wavefront takes whole stages, nb + lw, nb + 4 + lw ...: its waits, for a buffer and for its
+      // loads, are under the others' loads.  With a quarter of every stage each, as below, all four issue at the same time, with the memory path full, and
+      // then wait, look and publish at the same time, with the path idle: of 1400 clocks of a stage of 33 KB 800, of one of 8 KB nearly all.  What is
+      // published is the first stage of a wavefront's own that has not landed, so the smallest of the four is again the number of stages that have.
+      //   bf16 320 to 640 channels at 14x14, 100 images 41.8 -> 27.0 us, int8 33.9 -> 24.6; 192 to 128, 200 images 15.2 -> 12.4; int8 768 to 384 at
+      // 20x20, 50 images 16.5 -> 15.2; bf16 1024 at 14x14, 64 images 42.0 -> 39.7.  Fewer stages than that behind the first ones do not make up for a stage
+      // that one wavefront brings more slowly than four: three rounds of the buffers where a stage is small (64 at 28x28, two rounds, 14.6 -> 15.1), twelve
+      // where four buffers are all that fit (stages of 30 KB and more; six rounds, bf16 768 to 384 at 20x20 20.4 -> 21.1; eight, 512 at 14x14 29.8 -> 30.0).
+      constexpr int kPx = 64 / CPS, kOwn = 4 * CPS;          // pixels of a load; loads of the largest patch
+      const int lane_at = lane / CPS * a.xps + ((lane % CPS) ^ slot_perm<CPS>(lane / CPS, a.bit)) * 16;
+      int own[kOwn], t = -1, landed_to = 0;
+      auto whole = [&]() __attribute__((always_inline)) {
+        const unsigned buf = lds0 + ib * a.pstr;
+        int c = is < a.s0 ? b0 + is * SB : (is - a.s0) * SB;
+        if (is >= a.s0 && c >= b0) c += a.gap_chn;
+        if (a.wres < 0 || iv < a.s) {
+          const unsigned wd = a.wres < 0 ? buf + a.psz : lds0 + a.wres + is * WB;
+          const i32x4 r = is < a.s0 ? wr0 : wr1;
+          const int so = (is < a.s0 ? is : is - a.s0) * WB;
+#pragma unroll
+          for (int k = 0; k < WB / 1024; ++k) dma(r, lane * 16, so + k * 1024, wd + k * 1024);
+        }
+        if (t != itile) {
+          t = itile;
+          tile_setup(t);
+#pragma unroll
+          for (int k = 0; k < kOwn; ++k) own[k] = lane / CPS + kPx * k < here ? (R0 + kPx * k) * a.xps + lane_at : kOut;
+        }
+#pragma unroll
+        for (int k = 0; k < kOwn; ++k) {
+          if (k >= a.n_pl) break;
+          dma(xr, own[k], c, buf + k * 1024);
+        }
+      };
+      auto go_on = [&](int by) __attribute__((always_inline)) {       // from the stage behind the last one issued
+        iv += by;
+        is += by;
+        ib += by;
+        while (is >= a.s) {
+          is -= a.s;
+          ++itile;
+        }
+        while (ib >= a.nb) ib -= a.nb;
+      };
+      const int fill = V < a.nb ? V : a.nb;
+      while (iv < fill) {
+        issue();
+        if (iv - out > 2) land();
+      }
+      while (out < fill - 1) land();
+      wait_vm<0, 2>(0);
+      go_on(lw);
+      publish(landed + 4 * lw, iv);                          // (its parts of those)
+      while (iv < V) {
+        // its buffer is free: every multiplying wavefront is done with the stage before in it, or has passed that by, and it has landed
+        wait_counters<kCw>(done, lane, iv - a.nb + 1, free_to);
+        wait_counters<kLw>(landed, lane, iv - a.nb + 1, landed_to);
+        whole();
+        wait_vm<0, 2>(0);
+        publish(landed + 4 * lw, iv + kLw);
+        go_on(kLw);
+      }
+      mark_if_gave_up(free_to);
+      mark_if_gave_up(landed_to);
+      return;
+    }
     while (iv < V) {
       // the buffer of stage iv is free when every multiplying wavefront is done with stage iv - nb
       while (free_to < iv - a.nb + 1 && out < iv) {

@@ -236,3 +236,25 @@ def test_int8_outputs_with_and_without_residual(shape):
         assert fits_32_bits(rq, hi // 2, True) == fits_32_bits(rq, 0, False) == fits
         P.run_int8(q, thr, out_i8=True, rq=rq, epilogue=B.CG_EPI_RELU, n_run=max(1, shape.n - 1), name=shape.name, **rows)
         P.run_int8(q, thr, out_i8=True, rq=rq, residual=r8, rq_res_mult=hi // 2, epilogue=B.CG_EPI_RESIDUAL, n_run=max(1, shape.n - 1), name=shape.name, **rows)
+
+
+# 1x1 layers of several tiles to a workgroup, whose stages the loading wavefronts take in turn: stages of eight chunks (four buffers) and of four,
+# weights that stay in LDS and stages of two (eight buffers), the last tile shorter than the others, gates that hardly ever fire (stages passed by before they land).
+IN_TURN = [
+    (S(33, 14, 14, 512, 1024, k=1, pad=0), 0.3, False), (S(33, 14, 14, 512, 1024, k=1, pad=0), 0.01, False), (S(33, 14, 14, 512, 1024, k=1, pad=0), 0.3, True),
+    (S(61, 25, 25, 192, 128, k=1, pad=0), 0.3, False), (S(117, 25, 25, 192, 128, k=1, pad=0), 0.01, False), (S(29, 13, 13, 384, 1024, k=1, pad=0), 0.3, False),
+    (S(19, 16, 16, 384, 1024, k=1, pad=0), 0.02, True)]
+
+
+@pytest.mark.parametrize("shape,rho,grouped", IN_TURN, ids=["%s_%g_%d" % (s.name, r, g) for s, r, g in IN_TURN])
+def test_point_wise_stages_in_turn(shape, rho, grouped):
+    inp = W.make_inputs(shape, 9600 + shape.c_in, kind="coherent", rho=rho, round_bf16=True, grouped=grouped)
+    gate = W.calibrate_gate(inp, rho, sample_images=2)
+    print("\n  " + str(P.run_float(inp, gate, name=shape.name, out_dtype=B.CG_BF16, epilogue=B.CG_EPI_RELU)), flush=True)
+
+
+def test_point_wise_stages_in_turn_int8():
+    shape = S(29, 13, 13, 768, 1024, k=1, pad=0)
+    q = W.quantize_int8(W.make_inputs(shape, 9650, kind="coherent", rho=0.3))
+    thr = W.calibrate_gate_int8(q, 0.3, sample_images=None)
+    print("\n  " + str(P.run_int8(q, thr, name=shape.name + " int8")), flush=True)
