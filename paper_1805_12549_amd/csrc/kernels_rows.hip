@@ -300,6 +300,7 @@ enum : unsigned {
   kOnePair = 256u,                           // the two scale/shift pairs are the same
   kFit32 = 512u,                             // int8: the requantisation fits 32 bits
   kPairs = 1024u,                            // two wavefronts to a fragment
+  kTurns = 4096u,                            // 1x1: loading wavefronts take whole stages in turn (kInTurn)
   kFourBytes = 2048u,                        // float (int8 layers: 32-bit) outputs in natural channel order, within 32-bit offsets
 };
 
@@ -316,10 +317,12 @@ enum RowsOut {
                                              // more channels than 32-bit offsets reach over (near_outputs)
   kWide,                                     // float and 32-bit outputs in natural order
   kAdded, kPairedAdded,                      // kNatural and kPaired of layers with a residual, which is read before a tile's stages
+  kInTurn = 8,                               // beside one of these, 1x1 layers: a loading wavefront takes whole stages
 };
 
-template <typename Tr, int CPS, int PF, int TAPS, int OUT>
+template <typename Tr, int CPS, int PF, int TAPS, int FORM>
 __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params) {
+  constexpr int OUT = FORM & ~kInTurn;
   using acc16 = typename Tr::acc16;
   using acc_t = typename Tr::acc_t;
   using Base = typename Tr::Base;
@@ -500,15 +503,13 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
     issue();
     bare_barrier();                          // the counters are set up
     int free_to = 0;
-    if (TAPS == 1 && a.nb >= kLw && V >= (a.nb > kLw ? 3 : 12) * a.nb) {
+    if constexpr ((FORM & kInTurn) != 0) {
       // Once all have filled the buffers together a loading wavefront takes whole stages, nb + lw, nb + 4 + lw ...: its waits, for a buffer and for its
       // loads, are under the others' loads.  With a quarter of every stage each, as below, all four issue at the same time, with the memory path full, and
       // then wait, look and publish at the same time, with the path idle: of 1400 clocks of a stage of 33 KB 800, of one of 8 KB nearly all.  What is
       // published is the first stage of a wavefront's own that has not landed, so the smallest of the four is again the number of stages that have.
       //   bf16 320 to 640 channels at 14x14, 100 images 41.8 -> 27.0 us, int8 33.9 -> 24.6; 192 to 128, 200 images 15.2 -> 12.4; int8 768 to 384 at
-      // 20x20, 50 images 16.5 -> 15.2; bf16 1024 at 14x14, 64 images 42.0 -> 39.7.  Fewer stages than that behind the first ones do not make up for a stage
-      // that one wavefront brings more slowly than four: three rounds of the buffers where a stage is small (64 at 28x28, two rounds, 14.6 -> 15.1), twelve
-      // where four buffers are all that fit (stages of 30 KB and more; six rounds, bf16 768 to 384 at 20x20 20.4 -> 21.1; eight, 512 at 14x14 29.8 -> 30.0).
+      // 20x20, 50 images 16.5 -> 15.2; bf16 1024 at 14x14, 64 images 42.0 -> 39.7.  (A kernel of its own: in one with the other loop that was 3 to 4 % slower.)
       constexpr int kPx = 64 / CPS, kOwn = 4 * CPS;          // pixels of a load; loads of the largest patch
       const int lane_at = lane / CPS * a.xps + ((lane % CPS) ^ slot_perm<CPS>(lane / CPS, a.bit)) * 16;
       int own[kOwn], t = -1, landed_to = 0;
@@ -1454,19 +1455,23 @@ __global__ void pack_rows_kernel(const char* __restrict__ w, char* __restrict__ 
 }
 
 
-template <typename Tr, int CPS, int PF, int TAPS, int OUT>
+template <typename Tr, int CPS, int PF, int TAPS, int FORM>
 hipError_t launch_rows_one(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
   const unsigned blocks = a.xcd_cb ? (unsigned)(g.n_slots * g.n_cb) : (unsigned)a.per_xcd * 8u;
   static std::atomic<uint64_t> asked{0};
-  const hipError_t attr = allow_lds((const void*)gated_conv_rows_kernel<Tr, CPS, PF, TAPS, OUT>, kLds, asked);
+  const hipError_t attr = allow_lds((const void*)gated_conv_rows_kernel<Tr, CPS, PF, TAPS, FORM>, kLds, asked);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((gated_conv_rows_kernel<Tr, CPS, PF, TAPS, OUT>), dim3(blocks), dim3(kNt), (size_t)g.lds_bytes, s, a, p);
+  hipLaunchKernelGGL((gated_conv_rows_kernel<Tr, CPS, PF, TAPS, FORM>), dim3(blocks), dim3(kNt), (size_t)g.lds_bytes, s, a, p);
   return hipGetLastError();
 }
 
 template <typename Tr, int OUT>
 hipError_t launch_rows_out(const RowsPlan& g, const Params& p, const RowsArgs& a, hipStream_t s) {
   if constexpr (OUT != kHalves && OUT != kPaired && OUT != kPairedAdded) if (g.taps == 1) {
+    if (a.flags & kTurns) {
+      if (g.cps == 8) return launch_rows_one<Tr, 8, 1, 1, OUT | kInTurn>(g, p, a, s);
+      return g.cps == 4 ? launch_rows_one<Tr, 4, 1, 1, OUT | kInTurn>(g, p, a, s) : launch_rows_one<Tr, 2, 1, 1, OUT | kInTurn>(g, p, a, s);
+    }
     if (g.cps == 8) return launch_rows_one<Tr, 8, 1, 1, OUT>(g, p, a, s);
     return g.cps == 4 ? launch_rows_one<Tr, 4, 1, 1, OUT>(g, p, a, s) : launch_rows_one<Tr, 2, 1, 1, OUT>(g, p, a, s);
   }
@@ -1829,6 +1834,14 @@ hipError_t launch_rows(const RowsPlan& g, const Params& p, const void* w0, const
             (near && !p.shuffle && (p.out_dtype == CG_F32 || p.out_dtype == CG_I32) ? kFourBytes : 0u);
   const bool pairs = (a.flags & kFast) && !p.shuffle && !a.spg && g.pf == 1 && g.taps == 9 && tile_fragments(g.tr, g.fwl, g.nfc, p.wo) <= kCw / 2;
   if (pairs) a.flags |= kPairs;
+  // Loading wavefronts of 1x1 layers take whole stages in turn where a workgroup has enough of them behind its first ones to make up for a stage that one
+  // wavefront brings more slowly than four: three rounds of the buffers where a stage is small (64 channels at 28x28, 256 images, two rounds, 14.6 -> 15.1
+  // us), twelve where four buffers are all that fit, stages of 30 KB and more (six rounds, bf16 768 to 384 at 20x20, 50 images 20.4 -> 21.1; eight, 512 at
+  // 14x14, 128 images 29.8 -> 30.0; sixteen, 1024 at 14x14, 64 images 42.0 -> 39.7).  Not with fewer buffers (4096 to 4096, 1024 pixels 48 -> 51).
+  // Nor where a tile has few stages, whose time is the outputs': two, 64 to 256 at 52x52, 193 images 98.6 -> 105.2; four, 64 to 64 at 28x28 the same; from
+  // twelve on the gains above.
+  const int stages = (a.full + (tail > 0 ? 1 : 0)) * a.s;
+  if (g.taps == 1 && a.nb >= kLw && a.s >= 8 && stages >= (a.nb > kLw ? 3 : 12) * a.nb) a.flags |= kTurns;
   // rows of the patch lie in the banks of others: runs of 32 pixels over several of them, fragments of up to 8 columns (counted for widths of 2
   // to 56: never more passes than with the fixed bit; from 32 columns on and at stride 2 there are)
   const bool narrow = p.stride == 1 && (g.fwl < 0 ? p.wo < 32 : g.fwl <= 3);

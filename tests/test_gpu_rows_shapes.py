@@ -241,7 +241,7 @@ def test_int8_outputs_with_and_without_residual(shape):
 # 1x1 layers of several tiles to a workgroup, whose stages the loading wavefronts take in turn: stages of eight chunks (four buffers) and of four,
 # weights that stay in LDS and stages of two (eight buffers), the last tile shorter than the others, gates that hardly ever fire (stages passed by before they land).
 IN_TURN = [
-    (S(33, 14, 14, 512, 1024, k=1, pad=0), 0.3, False), (S(33, 14, 14, 512, 1024, k=1, pad=0), 0.01, False), (S(33, 14, 14, 512, 1024, k=1, pad=0), 0.3, True),
+    (S(106, 14, 14, 512, 1024, k=1, pad=0), 0.3, False), (S(106, 14, 14, 512, 1024, k=1, pad=0), 0.01, False), (S(106, 14, 14, 512, 1024, k=1, pad=0), 0.3, True),
     (S(61, 25, 25, 192, 128, k=1, pad=0), 0.3, False), (S(117, 25, 25, 192, 128, k=1, pad=0), 0.01, False), (S(29, 13, 13, 384, 1024, k=1, pad=0), 0.3, False),
     (S(19, 16, 16, 384, 1024, k=1, pad=0), 0.02, True)]
 

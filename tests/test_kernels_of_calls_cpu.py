@@ -118,3 +118,14 @@ def test_layers_with_a_1x1_beside(exe):
         assert one == (tile is not None), (n, h, w, c_in)
         if one:
             assert (int(args[1]), int(args[2]), types == ("UniformArgs",)) == tile, (n, h, w, c_in)
+
+
+def test_layers_whose_stages_are_taken_in_turn(exe):
+    for s, _, grouped in rows_shapes.IN_TURN:
+        kernel, args, *_ = K.ask(exe, [K.layer(B.CG_BF16, s.n, s.h, s.w, s.c_in, s.c_out, c_base=s.c_base, k=1, pad=0, groups=s.groups if grouped else 0,
+                                              out_dtype=B.CG_BF16)])[0]
+        assert (kernel, args[4]) == ("gated_conv_rows_kernel", "8"), (s.name, args)
+    kernel, args, *_ = K.ask(exe, [K.layer(B.CG_I8, 29, 13, 13, 768, 1024, c_base=192, k=1, pad=0)])[0]
+    assert (kernel, args[4]) == ("gated_conv_rows_kernel", "13"), args
+    kernel, args, *_ = K.ask(exe, [K.layer(B.CG_BF16, 8, 28, 28, 512, 512, c_base=128, k=1, pad=0, out_dtype=B.CG_BF16)])[0]      # one tile to a workgroup
+    assert (kernel, args[4]) == ("gated_conv_rows_kernel", "0"), args
