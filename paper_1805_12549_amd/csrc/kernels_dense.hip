@@ -890,35 +890,22 @@ int cg_pointwise_conv(const void* x, const void* w, const float* scale, const fl
   if (rc != CG_OK) return rc;
   if (n == 0) return CG_OK;
   const PointArgs a = cg::point_args(x, w, scale, shift, y, n, h, wd, c_in, c_out, stride, relu);
-  const int ho = a.ho, wo = a.wo;
-  const long long m_total = (long long)n * ho * wo;
+  const long long m_total = (long long)n * a.ho * a.wo;
   // Small tiles below a quarter of 128 pixels x 64 channels per compute unit, where the large ones leave most of the chip idle.  Small / large, us: 64 to
   // 128 channels, 3136 pixels (50 blocks of a line of 64) 3.5 and, just past the line, 6272 (98) 3.9; 256 to 512, 588 pixels (40) 5.2, 1176 (80) 5.7.
   if (cg::point_in_pieces(m_total, c_out, cg::cu_count())) {
     hipLaunchKernelGGL(pointwise_small_kernel, dim3((unsigned)((m_total + 15) / 16), (unsigned)(c_out / 32)), dim3(64), 0,
                        (hipStream_t)hip_stream, a);
   } else {
-    // A launch holds less than 2^32 threads and 2^30 pixels; larger batches go in pieces of images, rows or columns.
-    long long cap = std::min(((1ll << 24) - 8) / a.ncb * kPointPx, 1ll << 30);
+    // A launch holds less than 2^32 threads and at most 2^30 pixels; larger batches go in pieces of images, rows or columns.
+    const long long cap = std::min(((1ll << 24) - 8) / a.ncb * kPointPx, 1ll << 30);
     if (cap < kPointPx) return cg::set_error(CG_EUNSUPPORTED, "cg_pointwise_conv: too large");
-    const long long cols = std::min<long long>(wo, cap), rows = cols < wo ? 1 : std::min(cap / wo, (long long)ho);
-    const long long imgs = rows < ho ? 1 : std::min(cap / ((long long)ho * wo), (long long)n);
-    for (long long i = 0; i < n; i += imgs)
-      for (long long r = 0; r < ho; r += rows)
-        for (long long c = 0; c < wo; c += cols) {
-          PointArgs p = a;
-          p.x = a.x + ((i * h + r * stride) * wd + c * stride) * (c_in * 2ll);
-          p.y = a.y + ((i * ho + r) * wo + c) * (c_out * 2ll);
-          p.ho = (int)std::min<long long>(rows, ho - r);
-          p.wo = (int)std::min<long long>(cols, wo - c);
-          p.m_total = (int)(std::min(imgs, n - i) * p.ho * p.wo);
-          p.d_wo = cg::div_of(p.wo);
-          p.d_ho = cg::div_of(p.ho);
-          p.blocks = (p.m_total + kPointPx - 1) / kPointPx * a.ncb;
-          p.per_xcd = (p.blocks + 7) / 8;
-          hipLaunchKernelGGL(pointwise_tile_kernel, dim3((unsigned)p.per_xcd * 8u), dim3(256), (size_t)((c_in + 31) / 32) * (kPointPx * 64),
-                             (hipStream_t)hip_stream, p);
-        }
+    cg::for_point_pieces(a, n, cap, [&](PointArgs& p) {
+      p.blocks = (p.m_total + kPointPx - 1) / kPointPx * a.ncb;
+      p.per_xcd = (p.blocks + 7) / 8;
+      hipLaunchKernelGGL(pointwise_tile_kernel, dim3((unsigned)p.per_xcd * 8u), dim3(256), (size_t)((c_in + 31) / 32) * (kPointPx * 64),
+                         (hipStream_t)hip_stream, p);
+    });
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return cg::set_error(CG_EHIP, "cg_pointwise_conv: %s", hipGetErrorString(e));

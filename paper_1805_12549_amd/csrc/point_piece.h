@@ -37,6 +37,27 @@ inline bool point_in_pieces(long long m_total, int c_out, int n_cu) { return (m_
 // What cg_pointwise_conv refuses (kernels_dense.hip).
 int point_check(const void* x, const void* w, const float* scale, const float* shift, const void* y, int n, int h, int wd, int c_in, int c_out, int stride);
 
+// The convolution `a` of n images in pieces of at most `cap` output pixels (cap >= 1): whole images, else whole rows of one image, else columns of one row.
+template <typename Launch>
+void for_point_pieces(const PointArgs& a, int n, long long cap, Launch&& launch) {
+  const long long cols = a.wo < cap ? a.wo : cap;
+  const long long rows = cols < a.wo ? 1 : cap / a.wo < a.ho ? cap / a.wo : a.ho;
+  const long long px = (long long)a.ho * a.wo, imgs = cols < a.wo || rows < a.ho ? 1 : cap / px < n ? cap / px : n;
+  for (long long i = 0; i < n; i += imgs)
+    for (long long r = 0; r < a.ho; r += rows)
+      for (long long c = 0; c < a.wo; c += cols) {
+        PointArgs p = a;
+        p.x = a.x + ((i * a.h + r * a.stride) * a.wd + c * a.stride) * (a.c_in * 2ll);
+        p.y = a.y + ((i * a.ho + r) * a.wo + c) * (a.c_out * 2ll);
+        p.ho = (int)(rows < a.ho - r ? rows : a.ho - r);
+        p.wo = (int)(cols < a.wo - c ? cols : a.wo - c);
+        p.m_total = (int)((imgs < n - i ? imgs : n - i) * p.ho * p.wo);
+        p.d_wo = div_of(p.wo);
+        p.d_ho = div_of(p.ho);
+        launch(p);
+      }
+}
+
 // byte offset of the input pixel of output pixel m
 __device__ __forceinline__ long long point_pixel(const PointArgs& a, unsigned m) {
   const unsigned q = quot(m, a.d_wo), img = quot(q, a.d_ho);

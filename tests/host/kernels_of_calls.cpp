@@ -2,6 +2,8 @@
 // loader finds before the runtime's own, keeps the kernels' names as they are registered and "launches" nothing.
 // One layer a line on standard input: in_dtype out_dtype n_max n h w c_in c_out c_base k stride pad groups shuffle epilogue
 // variant rq_shift; a line with the kernel's name and its threads to a workgroup for each.  Run by tests/test_kernels_of_calls_cpu.py.
+//   "pointwise": n h w c_in c_out stride a line, for cg_pointwise_conv; "cut": the same and the pixels to a piece, for the cutting alone.  A line with the pieces,
+// x (bytes) y (bytes) m_total ho wo each, or the kernel's name where it has no pieces.
 #include <cxxabi.h>
 #include <hip/hip_runtime.h>
 
@@ -14,12 +16,14 @@
 #include <vector>
 
 #include "cg_conv.h"
+#include "point_piece.h"
 
 static std::map<const void*, std::string>& names() {      // (the library registers its kernels before main)
   static std::map<const void*, std::string> m;
   return m;
 }
-struct Launch { const void* kernel; unsigned threads; };
+struct Launch { const void* kernel; unsigned threads; cg::PointArgs piece; };
+static const char *const kX = (const char*)0x200000000ull, *const kY = (const char*)0x1000000000000ull;
 static std::vector<Launch> launches;
 static dim3 config_block;
 
@@ -56,13 +60,41 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
   *s = nullptr;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t) {
-  launches.push_back({f, config_block.x});
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t) {
+  launches.push_back({f, config_block.x, {}});
+  if (names()[f].find("pointwise_tile_kernel") != std::string::npos) launches.back().piece = *(const cg::PointArgs*)args[0];
+  if (launches.size() > 10000) {
+    std::fprintf(stderr, "a call that does not stop launching\n");
+    std::exit(3);
+  }
   return hipSuccess;
 }
 }
 
-int main() {
+static void print_piece(const cg::PointArgs& p) { std::printf("%lld %lld %d %d %d ", (long long)(p.x - kX), (long long)(p.y - kY), p.m_total, p.ho, p.wo); }
+
+static int pointwise_calls(bool cut) {
+  int n, h, w, c_in, c_out, stride;
+  long long cap;
+  while (std::scanf("%d %d %d %d %d %d", &n, &h, &w, &c_in, &c_out, &stride) == 6) {
+    if (cut) {
+      if (std::scanf("%lld", &cap) != 1) return 2;
+      cg::for_point_pieces(cg::point_args(kX, kX, nullptr, nullptr, (void*)kY, n, h, w, c_in, c_out, stride, 0), n, cap, print_piece);
+    } else {
+      launches.clear();
+      if (cg_pointwise_conv(kX, kX, nullptr, nullptr, (void*)kY, n, h, w, c_in, c_out, stride, 0, nullptr) != CG_OK) std::printf("%s", cg_last_error());
+      for (const Launch& l : launches) {
+        if (l.piece.x) print_piece(l.piece);
+        else std::printf("%s ", names()[l.kernel].c_str());
+      }
+    }
+    std::printf("\n");
+  }
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  if (argc > 1) return pointwise_calls(!std::strcmp(argv[1], "cut"));
   int in_dtype, out_dtype, n_max, n, h, w, c_in, c_out, c_base, k, stride, pad, groups, shuffle, variant, rq_shift;
   unsigned epilogue;
   while (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %u %d %d", &in_dtype, &out_dtype, &n_max, &n, &h, &w, &c_in, &c_out, &c_base, &k,

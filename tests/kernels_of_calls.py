@@ -17,7 +17,7 @@ def build(folder):
         return None
     exe = Path(folder) / "kernels_of_calls"
     r = subprocess.run([hipcc, "--offload-arch=gfx950", "-O1", "-std=c++17", "-Wall", "-rdynamic", "-I", str(ROOT / "include"),
-                        str(ROOT / "tests" / "host" / "kernels_of_calls.cpp"), "-L", str(LIB.parent), "-lcg_conv", "-Wl,-rpath," + str(LIB.parent),
+                        "-I", str(LIB.parent / "csrc"), str(ROOT / "tests" / "host" / "kernels_of_calls.cpp"), "-L", str(LIB.parent), "-lcg_conv", "-Wl,-rpath," + str(LIB.parent),
                         "-o", str(exe)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr[-3000:]
     return exe
@@ -45,3 +45,12 @@ def ask(exe, layers):
         names = lambda text: tuple(a.strip().split("::")[-1] for a in text.split(","))
         out.append((m.group(1), names(m.group(2) or ""), int(m.group(4)), names(m.group(3))))
     return out
+
+
+def pieces(exe, mode, calls):
+    """The pieces (x offset, y offset, m_total, ho, wo) of 1x1 convolutions: "pointwise", of the library's calls, "cut", cut at a given number of pixels."""
+    text = "\n".join(" ".join(str(v) for v in call) for call in calls) + "\n"
+    r = subprocess.run([str(exe), mode], input=text, capture_output=True, text=True, timeout=120)
+    lines = r.stdout.splitlines()
+    assert r.returncode == 0 and len(lines) == len(calls), r.stderr[-2000:]
+    return [[tuple(map(int, line.split()[i:i + 5])) for i in range(0, len(line.split()), 5)] for line in lines]

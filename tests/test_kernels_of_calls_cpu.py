@@ -1,5 +1,7 @@
 """That the layers of the GPU tests run on the kernels, and in the forms, which those tests are there for: the choice of kernel and plan is the
 library's own, asked for through forward calls without a GPU."""
+import itertools
+
 import pytest
 
 from paper_1805_12549_amd import binding as B
@@ -129,3 +131,29 @@ def test_layers_whose_stages_are_taken_in_turn(exe):
     assert (kernel, args[4]) == ("gated_conv_rows_kernel", "13"), args
     kernel, args, *_ = K.ask(exe, [K.layer(B.CG_BF16, 8, 28, 28, 512, 512, c_base=128, k=1, pad=0, out_dtype=B.CG_BF16)])[0]      # one tile to a workgroup
     assert (kernel, args[4]) == ("gated_conv_rows_kernel", "0"), args
+
+
+def test_1x1_convolutions_of_many_pixels_end(exe):
+    """More output pixels than one launch holds: in one row, in rows of one image, in images; every one once."""
+    for n, h, w, c_out, stride in [(1, 1, 1 << 30, 64, 1), (1, 1, (1 << 30) + 64, 64, 1), (1, 1, 1 << 29, 192, 1), (2, 2, 1 << 30, 64, 2), (3, 40000, 40000, 64, 1),
+                                   (2000, 1000, 999, 128, 1)]:
+        got = K.pieces(exe, "pointwise", [(n, h, w, 16, c_out, stride)])[0]
+        at = 0
+        for x, y, m, ho, wo in got:
+            assert 0 < m <= 1 << 30 and m % (ho * wo) == 0 and y == at * c_out * 2
+            at += m
+        assert len(got) > 1 and at == n * -(-h // stride) * -(-w // stride), (n, h, w)
+
+
+def test_pieces_of_1x1_convolutions_cover_every_pixel_once(exe):
+    calls = [(n, h, w, 16, 64, s, cap) for n, h, w, s in itertools.product((1, 2, 5), (1, 2, 7), (1, 3, 9), (1, 2, 3)) for cap in (1, 2, 3, 4, 8, 20, 63, 1000)]
+    for (n, h, w, c_in, c_out, s, cap), pieces in zip(calls, K.pieces(exe, "cut", calls)):
+        ho, wo = -(-h // s), -(-w // s)
+        want = [((((i * h + r * s) * w) + c * s) * c_in * 2, ((i * ho + r) * wo + c) * c_out * 2) for i in range(n) for r in range(ho) for c in range(wo)]
+        got = []
+        for x, y, m_total, pho, pwo in pieces:
+            assert 0 < m_total <= cap
+            for m in range(m_total):                          # (the pixel of the kernel's point_pixel)
+                q, img = m // pwo, m // pwo // pho
+                got.append((x + ((img * h + (q - img * pho) * s) * w + (m - q * pwo) * s) * c_in * 2, y + m * c_out * 2))
+        assert sorted(got) == want, (n, h, w, s, cap)
