@@ -230,10 +230,10 @@ def cg_avgpool_fc(x: int, wfc: int, bias: int, logits: int, n: int, hw: int, c: 
                               hip_stream))
 
 
-def empty_beside(x, *sizes):
-    """A contiguous bf16 tensor of that shape on x's device."""
-    t = _calls.empty_bf16(x, *sizes) if _calls is not None else None
-    return t if t is not None else torch.empty(sizes, dtype=torch.bfloat16, device=x.device)
+def empty_beside(x, *sizes, dtype=torch.bfloat16):
+    """A contiguous tensor of that shape and type on x's device."""
+    t = _calls.empty_bf16(x, *sizes) if _calls is not None and dtype == torch.bfloat16 else None
+    return t if t is not None else torch.empty(sizes, dtype=dtype, device=x.device)
 
 
 def cg_conv_info(handle: int):
@@ -385,7 +385,8 @@ class GatedConv:
         """forward(x) of a bf16 layer without bitmap and counts, and beside it the 1x1 convolution of x with the layer's stride (cg_pointwise_conv,
         no ReLU): one launch where the layer has few pixels.  Returns (y, y1)."""
         n = x.shape[0]
-        y, y1 = empty_beside(x, n, self.ho, self.wo, self.c_out), empty_beside(x, n, self.ho, self.wo, c_out1)
+        y = empty_beside(x, n, self.ho, self.wo, self.c_out, dtype=self._y_dtype)
+        y1 = empty_beside(x, n, self.ho, self.wo, c_out1)
         _check(_lib.cg_conv_call_beside(self.handle, n, x.data_ptr(), y.data_ptr(), w1.data_ptr(), 0 if scale1 is None else scale1.data_ptr(),
                                         0 if shift1 is None else shift1.data_ptr(), y1.data_ptr(), c_out1, 0, self._stream_ptr()))
         return y, y1

@@ -50,6 +50,27 @@ def test_beside_is_the_two_calls(form, scaled):
     layer.close()
 
 
+@pytest.mark.parametrize("form", [(2, 28, 28, 128, 256, 32, 3, 2, 256), (3, 56, 56, 64, 128, 64, 3, 2, 128), (40, 28, 28, 128, 128, 32, 3, 1, 128)],
+                         ids=lambda f: "x".join(map(str, f)))
+def test_beside_of_layers_with_float_outputs(form):
+    """One launch, of a gated and a dense layer, and two."""
+    n, h, w, c_in, c_out, c_base, k, stride, c1 = form
+    gen = torch.Generator(device="cuda").manual_seed(h * c_in + n)
+    rand = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    x = torch.relu(rand(n, h, w, c_in)).to(torch.bfloat16)
+    wt, w1 = rand(c_out, k, k, c_in).to(torch.bfloat16), rand(c1, c_in).to(torch.bfloat16)
+    gate = dict(gate_mean=np.zeros(c_out), gate_var=np.ones(c_out), delta=np.full(c_out, 0.3)) if c_base < c_in else {}
+    layer = B.GatedConv(n_max=n, h=h, w=w, c_in=c_in, c_out=c_out, c_base=c_base, w_base=wt[..., :c_base].contiguous(),
+                        w_cond=wt[..., c_base:].contiguous() if c_base < c_in else None, in_dtype=B.CG_BF16, out_dtype=B.CG_F32, kh=k, kw=k, stride=stride,
+                        pad=k // 2, **gate)
+    want, _, _ = layer.forward(x, bitmap=False, counts=False)
+    want1 = torch.empty((n, layer.ho, layer.wo, c1), dtype=torch.bfloat16, device="cuda")
+    B.cg_pointwise_conv(x.data_ptr(), w1.data_ptr(), 0, 0, want1.data_ptr(), n, h, w, c_in, c1, stride, False, B.current_stream_ptr())
+    y, y1 = layer.forward_beside(x, w1, None, None, c1)
+    assert y.dtype == torch.float32 and torch.equal(y, want) and torch.equal(y1, want1)
+    layer.close()
+
+
 def test_beside_refuses_what_it_does_not_cover():
     x = torch.zeros((1, 8, 8, 64), dtype=torch.bfloat16, device="cuda")
     wt, w1, one = torch.zeros((64, 3, 3, 64), dtype=torch.bfloat16, device="cuda"), torch.zeros((64, 64), dtype=torch.bfloat16, device="cuda"), torch.ones(64, device="cuda")
