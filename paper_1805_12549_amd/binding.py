@@ -383,8 +383,10 @@ class GatedConv:
 
     def forward_beside(self, x, w1, scale1, shift1, c_out1):
         """forward(x) of a bf16 layer without bitmap and counts, and beside it the 1x1 convolution of x with the layer's stride (cg_pointwise_conv,
-        no ReLU): one launch where the layer has few pixels.  Returns (y, y1)."""
+        no ReLU): one launch where the layer has few pixels.  w1: c_out1 x C_in, scale1 and shift1: c_out1 each or None.  Returns (y, y1)."""
         n = x.shape[0]
+        if w1.numel() != c_out1 * self.desc.c_in or any(t is not None and t.numel() != c_out1 for t in (scale1, shift1)):
+            raise CGError(CG_EINVAL, "forward_beside: w1, scale1 and shift1 are not of %d channels" % c_out1)
         y = empty_beside(x, n, self.ho, self.wo, self.c_out, dtype=self._y_dtype)
         y1 = empty_beside(x, n, self.ho, self.wo, c_out1)
         _check(_lib.cg_conv_call_beside(self.handle, n, x.data_ptr(), y.data_ptr(), w1.data_ptr(), 0 if scale1 is None else scale1.data_ptr(),
