@@ -4,6 +4,8 @@
 // variant rq_shift; a line with the kernel's name and its threads to a workgroup for each.  Run by tests/test_kernels_of_calls_cpu.py.
 //   "pointwise": n h w c_in c_out stride a line, for cg_pointwise_conv; "cut": the same and the pixels to a piece, for the cutting alone.  A line with the pieces,
 // x (bytes) y (bytes) m_total ho wo each, or the kernel's name where it has no pieces.
+//   "beside": n h w c_in c_out c_base k stride c_out1 groups a line, for cg_conv_call_beside on a bf16 layer.  A line with all launches: name, threads to a
+// workgroup and workgroups each, with a semicolon behind.
 #include <cxxabi.h>
 #include <hip/hip_runtime.h>
 
@@ -15,6 +17,7 @@
 #include <string>
 #include <vector>
 
+#include "cg_calls.h"
 #include "cg_conv.h"
 #include "point_piece.h"
 
@@ -22,10 +25,10 @@ static std::map<const void*, std::string>& names() {      // (the library regist
   static std::map<const void*, std::string> m;
   return m;
 }
-struct Launch { const void* kernel; unsigned threads; cg::PointArgs piece; };
+struct Launch { const void* kernel; unsigned threads, blocks; cg::PointArgs piece; };
 static const char *const kX = (const char*)0x200000000ull, *const kY = (const char*)0x1000000000000ull;
 static std::vector<Launch> launches;
-static dim3 config_block;
+static dim3 config_grid, config_block;
 
 extern "C" {
 void** __hipRegisterFatBinary(const void*) {
@@ -50,7 +53,8 @@ hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t
 hipError_t hipGetSymbolAddress(void** p, const void*) { *p = (void*)0x700000000000ull; return hipSuccess; }
 hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) { *p = std::calloc(1, bytes); return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
-hipError_t __hipPushCallConfiguration(dim3, dim3 block, size_t, hipStream_t) {
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t) {
+  config_grid = grid;
   config_block = block;
   return hipSuccess;
 }
@@ -61,7 +65,7 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
   return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t) {
-  launches.push_back({f, config_block.x, {}});
+  launches.push_back({f, config_block.x, config_grid.x * config_grid.y * config_grid.z, {}});
   if (names()[f].find("pointwise_tile_kernel") != std::string::npos) launches.back().piece = *(const cg::PointArgs*)args[0];
   if (launches.size() > 10000) {
     std::fprintf(stderr, "a call that does not stop launching\n");
@@ -93,7 +97,37 @@ static int pointwise_calls(bool cut) {
   return 0;
 }
 
+static int beside_calls() {
+  int n, h, w, c_in, c_out, c_base, k, stride, c_out1, groups;
+  while (std::scanf("%d %d %d %d %d %d %d %d %d %d", &n, &h, &w, &c_in, &c_out, &c_base, &k, &stride, &c_out1, &groups) == 10) {
+    const std::vector<float> zero(c_out, 0.0f), one(c_out, 1.0f);
+    cg_conv_desc d;
+    std::memset(&d, 0, sizeof d);
+    d.struct_size = sizeof d;
+    d.n_max = n; d.h = h; d.w = w; d.c_in = c_in; d.c_out = c_out; d.c_base = c_base; d.kh = d.kw = k; d.stride = stride; d.pad = k / 2;
+    d.in_dtype = d.out_dtype = CG_BF16; d.groups = groups;
+    d.gate_mean = d.delta = zero.data();
+    d.gate_var = one.data();
+    d.w_base = (const void*)0x1000;
+    d.w_cond = c_base < c_in ? (const void*)0x2000 : nullptr;
+    d.packed = (void*)0x100000;
+    d.packed_bytes = cg_conv_packed_bytes(&d);
+    cg_conv* layer = nullptr;
+    if (cg_conv_create(&layer, &d, nullptr) != CG_OK) {
+      std::printf("%s\n", cg_last_error());
+      continue;
+    }
+    launches.clear();
+    if (cg_conv_call_beside(layer, n, kX, (void*)0x300000000ull, kX, nullptr, nullptr, (void*)kY, c_out1, 0, nullptr) != CG_OK) std::printf("%s", cg_last_error());
+    for (const Launch& l : launches) std::printf("%s %u %u;", names()[l.kernel].c_str(), l.threads, l.blocks);
+    std::printf("\n");
+    cg_conv_destroy(layer);
+  }
+  return 0;
+}
+
 int main(int argc, char** argv) {
+  if (argc > 1 && !std::strcmp(argv[1], "beside")) return beside_calls();
   if (argc > 1) return pointwise_calls(!std::strcmp(argv[1], "cut"));
   int in_dtype, out_dtype, n_max, n, h, w, c_in, c_out, c_base, k, stride, pad, groups, shuffle, variant, rq_shift;
   unsigned epilogue;

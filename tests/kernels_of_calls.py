@@ -38,12 +38,27 @@ def ask(exe, layers):
     r = subprocess.run([str(exe)], input=text, capture_output=True, text=True, timeout=120)
     lines = r.stdout.splitlines()
     assert r.returncode == 0 and len(lines) == len(layers), r.stderr[-2000:]
+    return [_launch(line) for line in lines]
+
+
+def _launch(line):
+    m = re.search(r"(\w+)(?:<([^()]*)>)?\(([^()]*)\) (\d+)$", line.replace("(anonymous namespace)", "anonymous"))
+    assert m, line
+    names = lambda text: tuple(a.strip().split("::")[-1] for a in text.split(","))
+    return m.group(1), names(m.group(2) or ""), int(m.group(4)), names(m.group(3))
+
+
+def beside(exe, calls):
+    """The launches of cg_conv_call_beside for layers (n, h, w, c_in, c_out, c_base, kernel, stride, channels of the 1x1, groups): each as `ask` gives it, and its
+    workgroups."""
+    text = "\n".join(" ".join(str(v) for v in call) for call in calls) + "\n"
+    r = subprocess.run([str(exe), "beside"], input=text, capture_output=True, text=True, timeout=120)
+    lines = r.stdout.splitlines()
+    assert r.returncode == 0 and len(lines) == len(calls), r.stderr[-2000:]
     out = []
     for line in lines:
-        m = re.search(r"(\w+)(?:<([^()]*)>)?\(([^()]*)\) (\d+)$", line.replace("(anonymous namespace)", "anonymous"))
-        assert m, line
-        names = lambda text: tuple(a.strip().split("::")[-1] for a in text.split(","))
-        out.append((m.group(1), names(m.group(2) or ""), int(m.group(4)), names(m.group(3))))
+        assert line.endswith(";"), line
+        out.append([_launch(text.rsplit(" ", 1)[0]) + (int(text.rsplit(" ", 1)[1]),) for text in line[:-1].split(";")])
     return out
 
 

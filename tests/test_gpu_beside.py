@@ -25,11 +25,14 @@ FORMS = [
     ((2, 30, 30, 64, 64, 16, 3, 1, 512), None),
 ]
 
+# the same of layers with channel groups, the last number: blocks of 64 channels inside a group (one launch), over several (two)
+GROUPED = [(2, 14, 14, 128, 256, 32, 3, 2, 256, 4), (2, 14, 14, 128, 96, 32, 3, 2, 128, 4)]
 
-@pytest.mark.parametrize("form", [f for f, _ in FORMS], ids=lambda f: "x".join(map(str, f)))
+
+@pytest.mark.parametrize("form", [f for f, _ in FORMS] + GROUPED, ids=lambda f: "x".join(map(str, f)))
 @pytest.mark.parametrize("scaled", [True, False])
 def test_beside_is_the_two_calls(form, scaled):
-    n, h, w, c_in, c_out, c_base, k, stride, c1 = form
+    n, h, w, c_in, c_out, c_base, k, stride, c1, *groups = form
     gen = torch.Generator(device="cuda").manual_seed(h * c_in + n)
     rand = lambda *s: torch.randn(s, generator=gen, device="cuda")
     x = torch.relu(rand(n, h, w, c_in)).to(torch.bfloat16)
@@ -39,7 +42,7 @@ def test_beside_is_the_two_calls(form, scaled):
     gate = dict(gate_mean=np.zeros(c_out), gate_var=np.ones(c_out), delta=np.full(c_out, 0.3)) if c_base < c_in else {}
     layer = B.GatedConv(n_max=n, h=h, w=w, c_in=c_in, c_out=c_out, c_base=c_base, w_base=wt[..., :c_base].contiguous(),
                         w_cond=wt[..., c_base:].contiguous() if c_base < c_in else None, in_dtype=B.CG_BF16, out_dtype=B.CG_BF16, kh=k, kw=k, stride=stride,
-                        pad=k // 2, **gate)
+                        pad=k // 2, groups=groups[0] if groups else 0, **gate)
     want, _, _ = layer.forward(x, bitmap=False, counts=False)
     want1 = torch.empty((n, layer.ho, layer.wo, c1), dtype=torch.bfloat16, device="cuda")
     B.cg_pointwise_conv(x.data_ptr(), w1.data_ptr(), sc.data_ptr() if scaled else 0, sh.data_ptr() if scaled else 0, want1.data_ptr(), n, h, w, c_in, c1,

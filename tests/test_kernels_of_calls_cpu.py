@@ -122,6 +122,21 @@ def test_layers_with_a_1x1_beside(exe):
             assert (int(args[1]), int(args[2]), types == ("UniformArgs",)) == tile, (n, h, w, c_in)
 
 
+def test_launches_of_layers_with_a_1x1_beside(exe):
+    """One launch, of the kernel and tile that test_gpu_beside.py names, or two."""
+    got = K.beside(exe, [form + (0,) for form, _ in beside.FORMS])
+    for (form, tile), launches in zip(beside.FORMS, got):
+        if tile is None:
+            assert [l[0] for l in launches][1:] in (["pointwise_small_kernel"], ["pointwise_tile_kernel"]) and launches[0][0] != "gated_conv_beside_kernel", form
+        else:
+            assert [l[0] for l in launches] == ["gated_conv_beside_kernel"], form
+            args = launches[0][1]
+            assert (args[0], int(args[1]), int(args[2]), args[3] == "UniformArgs") == ("Bf16Direct",) + tile, form
+    # grouped layers: 64-channel blocks inside one group are a kernel's that may have a 1x1 beside it, blocks over several not
+    for form, names in ((beside.GROUPED[0], ["gated_conv_beside_kernel"]), (beside.GROUPED[1], ["gated_conv_direct_kernel", "pointwise_small_kernel"])):
+        assert [l[0] for l in K.beside(exe, [form])[0]] == names, form
+
+
 def test_layers_whose_stages_are_taken_in_turn(exe):
     for s, _, grouped in rows_shapes.IN_TURN:
         kernel, args, *_ = K.ask(exe, [K.layer(B.CG_BF16, s.n, s.h, s.w, s.c_in, s.c_out, c_base=s.c_base, k=1, pad=0, groups=s.groups if grouped else 0,
