@@ -972,13 +972,15 @@ __global__ __launch_bounds__(SPLIT ? 64 * kMaxSplit : 256, SPLIT ? 4 : 2) void g
 
 // A layer and, in further workgroups of its launch, a 1x1 convolution of the same input beside it (a ResNet block's shortcut): the two need nothing of each
 // other, a layer of few pixels leaves room beside it, and a launch of few workgroups is 1.5 us between two kernels and its own chain of latencies.
-// K steps four at a time here: the layer's wavefronts have 128 registers.
-// ResNet-18, one image of 224x224 (three such layers) 111 -> 103 us.
+// K steps in batches of four here: the layer's wavefronts have 128 registers.  A few wavefronts of a further workgroup do a piece each (pieces_to_workgroup).
+// ResNet-18, one image of 224x224 (three such layers) 113 -> 102 us, four 145 -> 136, eight 181 -> 174, twelve 224 -> 218.
 template <typename Tr, int PF, int NH, typename Args>
 __global__ __launch_bounds__(64 * kMaxSplit, 4) void gated_conv_beside_kernel(Args p, PointArgs q) {
   const unsigned layer = (unsigned)p.per_xcd * 8u;
   if (blockIdx.x >= layer) {
-    const unsigned piece = (blockIdx.x - layer) * (unsigned)p.waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave >= (unsigned)q.waves) return;
+    const unsigned piece = (blockIdx.x - layer) * (unsigned)q.waves + wave;
     const unsigned blocks = (unsigned)q.c_out >> 5, px = piece / blocks;
     if (px * 16u < (unsigned)q.m_total) point_piece<4>(q, px, (int)(piece - px * blocks));
     return;
@@ -1039,9 +1041,10 @@ hipError_t launch_direct_form(const DirectPlan& g, const Args& a, hipStream_t s)
 }
 
 template <typename Tr, int PF, int NH, typename Args>
-hipError_t launch_beside(const DirectPlan& g, const Args& a, const PointArgs& q, hipStream_t s) {
+hipError_t launch_beside(const DirectPlan& g, const Args& a, PointArgs q, hipStream_t s) {
   const long long pieces = ((long long)q.m_total + 15) / 16 * (q.c_out / 32);
-  const unsigned more = (unsigned)((pieces + a.waves - 1) / a.waves);
+  q.waves = pieces_to_workgroup((long long)a.per_xcd * 8, pieces, q.c_in, a.waves, g.est, cu_count());
+  const unsigned more = (unsigned)((pieces + q.waves - 1) / q.waves);
   const auto k = gated_conv_beside_kernel<Tr, PF, NH, Args>;
   hipLaunchKernelGGL(k, dim3((unsigned)a.per_xcd * 8u + more), dim3(64 * g.split), 0, s, a, q);
   return hipGetLastError();

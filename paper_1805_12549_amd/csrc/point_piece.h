@@ -16,13 +16,14 @@ struct PointArgs {
   Div d_wo, d_ho;
   int blocks, per_xcd, ncb;                        // pointwise_tile_kernel: its workgroups, those of an XCD, blocks of 128 channels
   Div d_ncb;
+  int waves;                                       // gated_conv_beside_kernel: wavefronts of a workgroup that do a piece
 };
 
 inline PointArgs point_args(const void* x, const void* w, const float* scale, const float* shift, void* y, int n, int h, int wd, int c_in, int c_out,
                             int stride, int relu) {
   const int ho = (h - 1) / stride + 1, wo = (wd - 1) / stride + 1, ncb = (c_out + 127) / 128;
   return PointArgs{(const char*)x, (const char*)w, scale, shift, (char*)y, (int)((long long)n * ho * wo), h, wd, c_in, c_out, stride, ho, wo, relu,
-                   div_of(wo), div_of(ho), 0, 0, ncb, div_of(ncb)};
+                   div_of(wo), div_of(ho), 0, 0, ncb, div_of(ncb), 0};
 }
 
 // A 1x1 convolution that a layer's launch may do too; done: it has.
@@ -33,6 +34,24 @@ struct Beside {
 
 // Whether the small pieces are taken: below a quarter of 128 pixels x 64 channels per compute unit (see cg_pointwise_conv).
 inline bool point_in_pieces(long long m_total, int c_out, int n_cu) { return (m_total + 127) / 128 * (c_out / 64) * 4 < n_cu; }
+
+// Pieces to a workgroup of `most` wavefronts in the launch of a layer of `layer` workgroups that takes some `est` clocks (as a call).  A piece of 256 channels is
+// 24 KB through its compute unit's memory path: a workgroup of k pieces takes 2.7 us and 5.1 more for k * channels = 2048.  As few as let layer and pieces have
+// a compute unit to a workgroup, if they are done with the layer then; else as few as come to two and a half workgroups to a compute unit, from 256
+// channels to a workgroup on (fewer gain nothing there).
+//   Eight everywhere, before, and now: 256 to 512 channels, one image of 14x14 7.8 -> 5.2 us (two launches 7.4), five 10.8 -> 6.3 (8.0), ten 11.8 -> 8.1 (10.0);
+// 512 to 512 at 7x7 13.0 -> 7.2 (10.3); 128 to 256, five images of 28x28 7.5 -> 5.6 (7.4); 64 to 128, five of 56x56 6.0 -> 5.7 (7.4).  Where eight are still
+// taken 4.9 (64 to 128, three of 56x56) and 9.0 (256 to 512, twelve of 14x14); four there 5.4 and 11.0.
+inline int pieces_to_workgroup(long long layer, long long pieces, int c_in, int most, double est, int n_cu) {
+  auto workgroups = [&](int k) { return layer + (pieces + k - 1) / k; };
+  int k = 1;
+  while (k < most && workgroups(k) > n_cu) k *= 2;
+  if (workgroups(k) > n_cu || 6100.0 + 5.6 * k * c_in > est - 3400.0) {
+    k = c_in < 256 ? 256 / c_in : 1;
+    while (k < most && 2 * workgroups(k) > 5ll * n_cu) k *= 2;
+  }
+  return k < most ? k : most;
+}
 
 // What cg_pointwise_conv refuses (kernels_dense.hip).
 int point_check(const void* x, const void* w, const float* scale, const float* shift, const void* y, int n, int h, int wd, int c_in, int c_out, int stride);
@@ -65,8 +84,11 @@ __device__ __forceinline__ long long point_pixel(const PointArgs& a, unsigned m)
   return (row * a.wd + (m - q * (unsigned)a.wo) * (unsigned)a.stride) * (a.c_in * 2);
 }
 
-// Sixteen pixels (number `px` of them) x 32 channels by one wavefront, which takes both operands straight from memory in 64-byte pieces, U K steps
-// at once: what bounds it is one latency.  ResNet-18's three shortcuts of one image, each a launch of eight steps 3.1, 3.5 and 4.0 us.
+// Sixteen pixels (number `px` of them) x 32 channels by one wavefront, which takes both operands straight from memory in 64-byte pieces.  With U = 8 and 128
+// registers free (a launch of its own) all loads of eight K steps are in flight at once: what bounds it is one latency.  ResNet-18's three shortcuts of
+// one image 3.1, 3.5 and 4.0 us.  With U = 4, beside a layer, the compiler waits after each step's loads (they are under a lane's condition): four short latencies a
+// batch.  Without that condition all are in flight there too, which gained nothing: layer and 1x1 in one launch, eight pieces to a workgroup, 4.1, 5.4
+// and 7.8 -> 3.9, 5.2 and 7.9, and in two 5.6, 6.0 and 7.4 -> 5.5, 6.1 and 7.7.
 template <int U>
 __device__ __forceinline__ void point_piece(const PointArgs& a, unsigned px, int block) {
   typedef __attribute__((ext_vector_type(4))) int chunk_t;

@@ -28,8 +28,12 @@ FORMS = [
 # the same of layers with channel groups, the last number: blocks of 64 channels inside a group (one launch), over several (two)
 GROUPED = [(2, 14, 14, 128, 256, 32, 3, 2, 256, 4), (2, 14, 14, 128, 96, 32, 3, 2, 128, 4)]
 
+# the layer's workgroups and the 1x1's pieces to one of the further ones
+SHARES = [((1, 14, 14, 256, 512, 64, 3, 2, 512), 128, 1), ((5, 14, 14, 256, 512, 64, 3, 2, 512), 256, 1), ((10, 14, 14, 256, 512, 64, 3, 2, 512), 248, 2),
+          ((1, 28, 28, 128, 256, 32, 3, 2, 256), 208, 4), ((12, 14, 14, 256, 512, 64, 3, 2, 512), 152, 8), ((3, 27, 29, 48, 96, 16, 3, 2, 64), 240, 5)]
 
-@pytest.mark.parametrize("form", [f for f, _ in FORMS] + GROUPED, ids=lambda f: "x".join(map(str, f)))
+
+@pytest.mark.parametrize("form", [f for f, _ in FORMS] + [f for f, _, _ in SHARES] + GROUPED, ids=lambda f: "x".join(map(str, f)))
 @pytest.mark.parametrize("scaled", [True, False])
 def test_beside_is_the_two_calls(form, scaled):
     n, h, w, c_in, c_out, c_base, k, stride, c1, *groups = form

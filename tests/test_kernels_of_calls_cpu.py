@@ -137,6 +137,14 @@ def test_launches_of_layers_with_a_1x1_beside(exe):
         assert [l[0] for l in K.beside(exe, [form])[0]] == names, form
 
 
+def test_pieces_of_a_1x1_beside_are_spread_over_compute_units(exe):
+    """(eight of 24 KB to a workgroup took longer than the layer and a launch of their own)"""
+    for (form, layer, share), launches in zip(beside.SHARES, K.beside(exe, [form + (0,) for form, _, _ in beside.SHARES])):
+        n, h, w, *_, stride, c1 = form
+        pieces = -(-n * -(-h // stride) * -(-w // stride) // 16) * (c1 // 32)
+        assert [l[0] for l in launches] == ["gated_conv_beside_kernel"] and launches[0][4] == layer + -(-pieces // share), (form, launches)
+
+
 def test_layers_whose_stages_are_taken_in_turn(exe):
     for s, _, grouped in rows_shapes.IN_TURN:
         kernel, args, *_ = K.ask(exe, [K.layer(B.CG_BF16, s.n, s.h, s.w, s.c_in, s.c_out, c_base=s.c_base, k=1, pad=0, groups=s.groups if grouped else 0,
