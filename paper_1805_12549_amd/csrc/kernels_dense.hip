@@ -533,7 +533,8 @@ __global__ __launch_bounds__(64) void pointwise_small_kernel(PointArgs a) { cg::
 
 // Many pixels: a workgroup of four wavefronts owns 64 pixels x 128 channels, a wavefront 32 of the channels.  The pixels go to LDS by
 // direct loads, [K step of 32][pixel][four 16-byte chunks], all K steps at once; a wavefront's weights come straight from memory into
-// registers, up to eight K steps at a time.  Several workgroups fit a compute unit, so one's loads run under another's products.
+// registers, in batches of eight K steps (the compiler waits for all loads so far, the pixels' too, behind the second of a batch's; with all eight in flight
+// the kernel takes 176 registers instead of 124).  Several workgroups fit a compute unit, so one's loads run under another's products.
 // Chunk q of pixel p sits at position q ^ f(p / 4 % 4), f = 0, 2, 3, 1: each of the four groups of lanes that a 16-byte read is served in
 // ({0-3, 12-15, 20-27}, the rest of the first 32, the same 32 lanes on) then covers every bank once.  Bound by the vector-memory path (weights and
 // pixels in pieces of 64 bytes) and, with few channels, by memory.  ResNet-18's three shortcuts, 256 images 29.0, 20.8, 19.4 -> 22.6, 17.6, 15.1 us,
@@ -619,6 +620,76 @@ __global__ __launch_bounds__(256) void pointwise_tile_kernel(PointArgs a) {
     if (m < (unsigned)a.m_total)
       *(uint4*)(a.y + ((long long)m * a.c_out + c0 + 8 * lg) * 2) =
           uint4{bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]), bf16_pair(v[4], v[5]), bf16_pair(v[6], v[7])};
+  }
+}
+
+// As many pixels where the kernel above would leave half of a last block's wavefronts idle (64 channels beyond a multiple of 128): a workgroup owns
+// 128 pixels x 64 channels, a wavefront 32 of the pixels, which it takes straight from memory (16 bytes per lane and K step); the weights are in LDS,
+// rows permuted so that a lane ends up with sixteen consecutive channels.
+__global__ __launch_bounds__(256) void pointwise_conv_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
+                                                             const float* __restrict__ scale,
+                                                             const float* __restrict__ shift, uint16_t* __restrict__ y,
+                                                             long long m_total, int h, int wd, int c_in, int c_out,
+                                                             int stride, int ho, int wo, int relu) {
+  extern __shared__ __align__(16) uint16_t wlp[];          // [c_in/8 chunks][64 rows][8]
+  const int tid = threadIdx.x;
+  const int cb = blockIdx.y;
+  const int nq = c_in >> 3;
+  for (int i = tid; i < nq * kCb; i += 256) {
+    const int col = i / nq, q = i - col * nq;            // consecutive threads read consecutive 16-byte pieces
+    const int ch = col & 31;
+    const int row = (col & 32) + 8 * ((ch & 15) >> 2) + 4 * (ch >> 4) + (ch & 3);
+    *(uint4*)(wlp + ((q * kCb + row) << 3)) = *(const uint4*)(w + ((long long)(cb * kCb + col) * c_in + q * 8));
+  }
+  __syncthreads();
+  const int lane = tid & 63, wave = tid >> 6;
+  const int lj = lane & 31, lh = lane >> 5;
+  const long long m = (long long)blockIdx.x * 128 + wave * 32 + lj;
+  const bool valid = m < m_total;
+  const long long mm = valid ? m : 0;
+  const int ox = (int)(mm % wo);
+  const long long t2 = mm / wo;
+  const int oy = (int)(t2 % ho);
+  const long long img = t2 / ho;
+  const uint16_t* src = x + ((img * h + (long long)oy * stride) * wd + (long long)ox * stride) * c_in + lh * 8;
+  stem_f32x16 acc[2];
+#pragma unroll
+  for (int fc = 0; fc < 2; ++fc)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[fc][i] = 0.0f;
+  const int steps = c_in >> 4;
+#pragma unroll 4
+  for (int st = 0; st < steps; ++st) {
+    stem_i32x4 b = {0, 0, 0, 0};
+    if (valid) b = *(const stem_i32x4*)(src + st * 16);
+    const int q = 2 * st + lh;
+#pragma unroll
+    for (int fc = 0; fc < 2; ++fc) {
+      const stem_i32x4 a = *(const stem_i32x4*)(wlp + ((q * kCb + 32 * fc + lj) << 3));
+      acc[fc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(stem_bf16x8, a), __builtin_bit_cast(stem_bf16x8, b),
+                                                        acc[fc], 0, 0, 0);
+    }
+  }
+  if (!valid) return;
+#pragma unroll
+  for (int fc = 0; fc < 2; ++fc) {
+    const int co0 = cb * kCb + 32 * fc + 16 * lh;
+    uint16_t out[16];
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const float4 a4 = scale ? *(const float4*)(scale + co0 + 4 * q4) : float4{1.0f, 1.0f, 1.0f, 1.0f};
+      const float4 b4 = shift ? *(const float4*)(shift + co0 + 4 * q4) : float4{0.0f, 0.0f, 0.0f, 0.0f};
+      const float sc[4] = {a4.x, a4.y, a4.z, a4.w}, sh[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float v = acc[fc][4 * q4 + e] * sc[e] + sh[e];
+        if (relu) v = fmaxf(v, 0.0f);
+        out[4 * q4 + e] = float_to_bf16(v);
+      }
+    }
+    uint4* dst = (uint4*)(y + m * c_out + co0);
+    dst[0] = *(const uint4*)(out);
+    dst[1] = *(const uint4*)(out + 8);
   }
 }
 
@@ -896,6 +967,10 @@ int cg_pointwise_conv(const void* x, const void* w, const float* scale, const fl
   if (cg::point_in_pieces(m_total, c_out, cg::cu_count())) {
     hipLaunchKernelGGL(pointwise_small_kernel, dim3((unsigned)((m_total + 15) / 16), (unsigned)(c_out / 32)), dim3(64), 0,
                        (hipStream_t)hip_stream, a);
+  } else if (cg::point_in_wide_blocks(m_total, c_in, c_out, cg::cu_count())) {
+    hipLaunchKernelGGL(pointwise_conv_kernel, dim3((unsigned)((m_total + 127) / 128), (unsigned)(c_out / kCb)), dim3(256), (size_t)c_in * kCb * 2,
+                       (hipStream_t)hip_stream, (const uint16_t*)x, (const uint16_t*)w, scale, shift, (uint16_t*)y, m_total, h, wd,
+                       c_in, c_out, stride, a.ho, a.wo, relu);
   } else {
     // A launch holds less than 2^32 threads and at most 2^30 pixels; larger batches go in pieces of images, rows or columns.
     const long long cap = std::min(((1ll << 24) - 8) / a.ncb * kPointPx, 1ll << 30);

@@ -53,6 +53,18 @@ inline int pieces_to_workgroup(long long layer, long long pieces, int c_in, int 
   return k < most ? k : most;
 }
 
+// Whether 128 pixels x 64 channels a workgroup are taken instead of 64 x 128 (cg_pointwise_conv): where the last block of 128 channels is half empty and the
+// other form comes to at least 5/3 as many workgroups to a compute unit, if these are all on the chip at once (the weights of 64 channels in LDS; beyond
+// 384 channels two, as one alone has too few loads in flight) and the channels are whole rounds of that kernel's loop of four steps of 16.
+//   64 x 128 and 128 x 64, us: 256 to 64 channels, 20000 pixels 8.2 and 7.4, 65536 14.7 and 12.6; 512 to 64, 55000 23.5 and 20.7; 256 to 320, 5441 8.2 and 7.5;
+// 128 to 64, 120000 15.2 and 14.2.  Outside: 256 to 64, 33000 pixels (516 workgroups and 258) 10.4 and 11.0; 512 to 64, 20000 10.7 and 13.9; 208 to 64,
+// 55000 9.7 and 11.2.
+inline bool point_in_wide_blocks(long long m_total, int c_in, int c_out, int n_cu) {
+  const long long tiles = (m_total + 63) / 64 * ((c_out + 127) / 128), wide = (m_total + 127) / 128 * (c_out / 64);
+  const long long rounds = (tiles + n_cu - 1) / n_cu, each = (wide + n_cu - 1) / n_cu;
+  return c_out % 128 != 0 && c_in % 64 == 0 && 3 * rounds >= 5 * each && each <= 4 && each * c_in <= 1152 && (each > 1 || c_in <= 384);
+}
+
 // What cg_pointwise_conv refuses (kernels_dense.hip).
 int point_check(const void* x, const void* w, const float* scale, const float* shift, const void* y, int n, int h, int wd, int c_in, int c_out, int stride);
 

@@ -48,15 +48,20 @@ def _launch(line):
     return m.group(1), names(m.group(2) or ""), int(m.group(4)), names(m.group(3))
 
 
+def lines(exe, mode, calls):
+    """The default line for each call, in one of its modes."""
+    text = "\n".join(" ".join(str(v) for v in call) for call in calls) + "\n"
+    r = subprocess.run([str(exe), mode], input=text, capture_output=True, text=True, timeout=120)
+    said = r.stdout.splitlines()
+    assert r.returncode == 0 and len(said) == len(calls), r.stderr[-2000:]
+    return said
+
+
 def beside(exe, calls):
     """The launches of cg_conv_call_beside for layers (n, h, w, c_in, c_out, c_base, kernel, stride, channels of the 1x1, groups): each as `ask` gives it, and its
     workgroups."""
-    text = "\n".join(" ".join(str(v) for v in call) for call in calls) + "\n"
-    r = subprocess.run([str(exe), "beside"], input=text, capture_output=True, text=True, timeout=120)
-    lines = r.stdout.splitlines()
-    assert r.returncode == 0 and len(lines) == len(calls), r.stderr[-2000:]
     out = []
-    for line in lines:
+    for line in lines(exe, "beside", calls):
         assert line.endswith(";"), line
         out.append([_launch(text.rsplit(" ", 1)[0]) + (int(text.rsplit(" ", 1)[1]),) for text in line[:-1].split(";")])
     return out
@@ -64,8 +69,4 @@ def beside(exe, calls):
 
 def pieces(exe, mode, calls):
     """The pieces (x offset, y offset, m_total, ho, wo) of 1x1 convolutions: "pointwise", of the library's calls, "cut", cut at a given number of pixels."""
-    text = "\n".join(" ".join(str(v) for v in call) for call in calls) + "\n"
-    r = subprocess.run([str(exe), mode], input=text, capture_output=True, text=True, timeout=120)
-    lines = r.stdout.splitlines()
-    assert r.returncode == 0 and len(lines) == len(calls), r.stderr[-2000:]
-    return [[tuple(map(int, line.split()[i:i + 5])) for i in range(0, len(line.split()), 5)] for line in lines]
+    return [[tuple(map(int, line.split()[i:i + 5])) for i in range(0, len(line.split()), 5)] for line in lines(exe, mode, calls)]

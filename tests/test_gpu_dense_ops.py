@@ -272,7 +272,7 @@ def test_dense_ops_on_random_shapes(seed):
 
 @pytest.mark.parametrize("n,h,w,c_in,c_out,stride", [
     (1, 4, 4, 16, 64, 1), (1, 1, 17, 48, 64, 1), (3, 9, 7, 272, 128, 2), (1, 31, 33, 512, 192, 2),      # few pixels: 16 x 32 tiles
-    (70, 56, 57, 64, 128, 2), (19, 43, 41, 16, 64, 1), (64, 28, 28, 512, 64, 1), (130, 30, 29, 208, 256, 2)])    # many: runs of 128
+    (70, 56, 57, 64, 128, 2), (19, 43, 41, 16, 64, 1), (64, 28, 28, 512, 64, 1), (130, 30, 29, 208, 256, 2)])    # many: 64 x 128 or 128 x 64
 def test_pointwise_conv_forms(n, h, w, c_in, c_out, stride):
     gen = torch.Generator(device="cuda").manual_seed(c_in + h)
     x = torch.randn((n, h, w, c_in), generator=gen, device="cuda").to(torch.bfloat16)
@@ -283,6 +283,31 @@ def test_pointwise_conv_forms(n, h, w, c_in, c_out, stride):
     xs = x[:, ::stride, ::stride].reshape(-1, c_in).double().cpu()
     ref = torch.relu(xs @ wt.double().cpu().t() * sc.double().cpu() + sh.double().cpu()).reshape(y.shape)
     _check(y.double().cpu().numpy(), ref.numpy())
+
+
+# workgroups of 64 pixels x 128 channels, the last block of channels half empty, and of 128 x 64 (test_kernels_of_calls_cpu.py holds which)
+HALF_EMPTY = [((1, 1, 9600, 192, 64, 1), True), ((3, 57, 61, 208, 192, 1), True), ((2, 73, 61, 48, 320, 1), True), ((9, 60, 61, 512, 64, 1), True), ((1, 150, 61, 112, 192, 1), True),
+              ((5, 64, 61, 320, 64, 1), False), ((13, 71, 77, 128, 64, 1), False), ((11, 139, 131, 512, 64, 2), False), ((3, 61, 57, 64, 192, 1), False),
+              ((5, 66, 70, 384, 320, 2), False)]
+
+
+@pytest.mark.parametrize("scaled,relu", [(True, True), (False, False)])
+@pytest.mark.parametrize("shape", [s for s, _ in HALF_EMPTY], ids=lambda s: "x".join(map(str, s)))
+def test_pointwise_conv_half_empty_blocks(shape, scaled, relu):
+    n, h, w, c_in, c_out, stride = shape
+    gen = torch.Generator(device="cuda").manual_seed(c_in + h)
+    x = torch.randn((n, h, w, c_in), generator=gen, device="cuda").to(torch.bfloat16)
+    wt = (torch.randn((c_out, c_in), generator=gen, device="cuda") * (2.0 / c_in) ** 0.5).to(torch.bfloat16)
+    sc, sh = torch.rand(c_out, generator=gen, device="cuda") + 0.5, torch.randn(c_out, generator=gen, device="cuda") * 0.1
+    ho, wo = (h - 1) // stride + 1, (w - 1) // stride + 1
+    y = torch.full((n * ho * wo + 1, c_out), 7.0, dtype=torch.bfloat16, device="cuda")          # (a pixel more, that stays as it is)
+    B.cg_pointwise_conv(x.data_ptr(), wt.data_ptr(), sc.data_ptr() if scaled else 0, sh.data_ptr() if scaled else 0, y.data_ptr(), n, h, w, c_in, c_out, stride, relu,
+                        _stream())
+    ref = x[:, ::stride, ::stride].reshape(-1, c_in).double().cpu() @ wt.double().cpu().t()
+    if scaled:
+        ref = ref * sc.double().cpu() + sh.double().cpu()
+    _check(y[:-1].double().cpu().numpy(), (torch.relu(ref) if relu else ref).numpy())
+    assert torch.equal(y[-1], torch.full_like(y[-1], 7.0))
 
 
 @pytest.mark.parametrize("n,hw,c,classes", [(1, 49, 512, 1000), (1, 3, 32, 33), (5, 49, 2048, 40), (17, 16, 96, 1000), (70, 9, 352, 257),

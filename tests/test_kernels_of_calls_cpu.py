@@ -7,6 +7,7 @@ import pytest
 from paper_1805_12549_amd import binding as B
 from tests import kernels_of_calls as K
 from tests import test_gpu_beside as beside
+from tests import test_gpu_dense_ops as dense_ops
 from tests import test_gpu_nan_outputs as nan_outputs
 from tests import test_gpu_rows_edges as rows_edges
 from tests import test_gpu_rows_shapes as rows_shapes
@@ -180,3 +181,10 @@ def test_pieces_of_1x1_convolutions_cover_every_pixel_once(exe):
                 q, img = m // pwo, m // pwo // pho
                 got.append((x + ((img * h + (q - img * pho) * s) * w + (m - q * pwo) * s) * c_in * 2, y + m * c_out * 2))
         assert sorted(got) == want, (n, h, w, s, cap)
+
+
+def test_1x1_convolutions_whose_last_block_is_half_empty(exe):
+    """(64 x 128 everywhere was up to 17 % slower than 128 x 64, where that comes to fewer workgroups to a compute unit)"""
+    for (shape, tiles), line in zip(dense_ops.HALF_EMPTY, K.lines(exe, "pointwise", [s for s, _ in dense_ops.HALF_EMPTY])):
+        (n, h, w, _, _, stride), wide = shape, "pointwise_conv_kernel" in line
+        assert wide == (not tiles) and (wide or int(line.split()[2]) == n * -(-h // stride) * -(-w // stride)), (shape, line)
