@@ -258,3 +258,42 @@ def test_point_wise_stages_in_turn_int8():
     q = W.quantize_int8(W.make_inputs(shape, 9650, kind="coherent", rho=0.3))
     thr = W.calibrate_gate_int8(q, 0.3, sample_images=None)
     print("\n  " + str(P.run_int8(q, thr, name=shape.name + " int8")), flush=True)
+
+
+# The same with other outputs, whose kernels are others: two-byte outputs beside a residual (stages of two, four and eight chunks), in shuffled order, of four
+# bytes, int8 ones of a shift below two; (shape, what is asked for, the form in test_kernels_of_calls_cpu.py).
+IN_TURN_OUTPUTS = [
+    (S(61, 25, 25, 192, 128, k=1, pad=0), "residual", 2, 14), (S(29, 13, 13, 384, 1024, k=1, pad=0), "residual", 4, 14), (S(64, 14, 14, 768, 1024, k=1, pad=0), "residual", 8, 14),
+    (S(83, 25, 25, 192, 128, k=1, pad=0), "shuffled", 4, 11), (S(61, 25, 25, 192, 128, k=1, pad=0), "float", 2, 13), (S(61, 25, 25, 192, 128, k=1, pad=0), "tau", 2, 8),
+    (S(106, 14, 14, 512, 1024, k=1, pad=0), "residual", 8, 6)]        # (eight stages, four buffers and a residual: not in turn)
+IN_TURN_INT8 = [("bytes", 8), ("residual", 14), ("shift of one", 12), ("32 bits, residual", 13)]
+
+
+@pytest.mark.parametrize("shape,what", [(s, w) for s, w, _, _ in IN_TURN_OUTPUTS], ids=["%s_%s" % (s.name, w) for s, w, _, _ in IN_TURN_OUTPUTS])
+def test_point_wise_stages_in_turn_outputs(shape, what):
+    c, rng = shape.c_out, np.random.default_rng(shape.n)
+    inp = W.make_inputs(shape, 9660 + shape.c_in, kind="coherent", rho=0.3, round_bf16=True, grouped=what == "shuffled")
+    gate = W.calibrate_gate(inp, 0.3, sample_images=2)
+    aff = dict(scale0=rng.uniform(0.5, 1.5, c), shift0=rng.normal(0, 0.1, c), scale1=rng.uniform(0.5, 1.5, c), shift1=rng.normal(0, 0.1, c))
+    more = dict(out_dtype=B.CG_F32 if what == "float" else B.CG_BF16, epilogue=B.CG_EPI_RELU | B.CG_EPI_AFFINE, affine=aff, shuffle=what == "shuffled")
+    if what == "residual":
+        more.update(epilogue=more["epilogue"] | B.CG_EPI_RESIDUAL, residual=rng.standard_normal((shape.n, shape.ho, shape.wo, c)).astype(np.float32))
+    if what == "tau":
+        more.update(tau_c=0.3)
+    print("\n  " + str(P.run_float(inp, gate, name=shape.name, **more)), flush=True)
+
+
+@pytest.mark.parametrize("what", [w for w, _ in IN_TURN_INT8])
+def test_point_wise_stages_in_turn_int8_outputs(what):
+    shape = S(29, 13, 13, 768, 1024, k=1, pad=0)
+    c, rng = shape.c_out, np.random.default_rng(77)
+    q = W.quantize_int8(W.make_inputs(shape, 9651, kind="coherent", rho=0.3))
+    thr = W.calibrate_gate_int8(q, 0.3, sample_images=None)
+    r8 = rng.integers(-128, 128, (shape.n, shape.ho, shape.wo, c)).astype(np.int8)
+    shift = 1 if what == "shift of one" else 14
+    rq = dict(rq_mult0=rng.integers(20, 200, c).astype(np.int32), rq_mult1=rng.integers(20, 200, c).astype(np.int32), rq_bias=rng.integers(-200, 200, c).astype(np.int32),
+              rq_shift=shift)
+    more = dict(out_i8=True, rq=rq) if what != "32 bits, residual" else {}
+    if "residual" in what:
+        more.update(residual=r8, rq_res_mult=100, epilogue=B.CG_EPI_RESIDUAL)
+    print("\n  " + str(P.run_int8(q, thr, name=shape.name + " int8", **more)), flush=True)

@@ -147,10 +147,20 @@ def test_pieces_of_a_1x1_beside_are_spread_over_compute_units(exe):
 
 
 def test_layers_whose_stages_are_taken_in_turn(exe):
-    for s, _, grouped in rows_shapes.IN_TURN:
+    for (s, _, grouped), cps in zip(rows_shapes.IN_TURN, "8882244"):
         kernel, args, *_ = K.ask(exe, [K.layer(B.CG_BF16, s.n, s.h, s.w, s.c_in, s.c_out, c_base=s.c_base, k=1, pad=0, groups=s.groups if grouped else 0,
                                               out_dtype=B.CG_BF16)])[0]
-        assert (kernel, args[4]) == ("gated_conv_rows_kernel", "8"), (s.name, args)
+        assert (kernel, args[1], args[4]) == ("gated_conv_rows_kernel", cps, "8"), (s.name, args)
+    for s, what, cps, form in rows_shapes.IN_TURN_OUTPUTS:
+        grouped = what == "shuffled"
+        kernel, args, *_ = K.ask(exe, [K.layer(B.CG_BF16, s.n, s.h, s.w, s.c_in, s.c_out, c_base=s.c_base, k=1, pad=0, groups=s.groups if grouped else 0, shuffle=grouped,
+                                              out_dtype=B.CG_F32 if what == "float" else B.CG_BF16, epilogue=B.CG_EPI_RESIDUAL if what == "residual" else 0)])[0]
+        assert (kernel, args[1], args[4]) == ("gated_conv_rows_kernel", str(cps), str(form)), (s.name, what, args)
+    for what, form in rows_shapes.IN_TURN_INT8:
+        wide, residual = what.startswith("32"), "residual" in what
+        kernel, args, *_ = K.ask(exe, [K.layer(B.CG_I8, 29, 13, 13, 768, 1024, c_base=192, k=1, pad=0, out_dtype=B.CG_I32 if wide else B.CG_I8,
+                                              rq_shift=1 if what == "shift of one" else 14, epilogue=B.CG_EPI_RESIDUAL if residual else 0)])[0]
+        assert (kernel, args[1], args[4]) == ("gated_conv_rows_kernel", "4", str(form)), (what, args)
     kernel, args, *_ = K.ask(exe, [K.layer(B.CG_I8, 29, 13, 13, 768, 1024, c_base=192, k=1, pad=0)])[0]
     assert (kernel, args[4]) == ("gated_conv_rows_kernel", "13"), args
     kernel, args, *_ = K.ask(exe, [K.layer(B.CG_BF16, 8, 28, 28, 512, 512, c_base=128, k=1, pad=0, out_dtype=B.CG_BF16)])[0]      # one tile to a workgroup
