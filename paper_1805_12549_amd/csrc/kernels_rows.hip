@@ -1839,14 +1839,15 @@ hipError_t launch_rows(const RowsPlan& g, const Params& p, const void* w0, const
   //   More than four buffers, from eight stages to a tile and three rounds of the buffers on: nine stages (int8 192 to 512 channels at 14x14, 128 images)
   // 22.8 and 20.6; twelve, bf16 192 to 1024 at 7x7, 128 images (three rounds) 16.8 and 13.6; 28, 448 to 256 at 28x28, 64 images 57.4 and 35.0; but four, 256 to
   // 512 at 28x28, 64 images 31.3 and 32.1, 64 to 256 at 52x52, 193 images 98.6 and 105.2.
-  //   Four buffers, all that fit of stages of 30 KB and more, from twelve rounds on: sixteen stages, 1024 to 1024 at 14x14, 64 images 46.1 and 43.1; twelve, 768
-  // to 512 at 28x28, 32 images 37.7 and 36.4 (nine rounds, 768 to 768 at 14x14, 80 images 32.4 and 32.6); eight, int8 1024 at 14x14, 128 images 48.7 and 47.7,
-  // bf16 512 to 1024, 106 images 44.8 and 44.8.  There bf16 layers of eight stages lose with a residual, which is read at a tile's start as its first stages
-  // are: 45.3 and 47.8.  (Sixteen stages and more gain with fewer rounds too: 1024 to 256 at 28x28, 32 images, four rounds 26.0 and 24.8.)
+  //   Four buffers, all that fit of stages of 30 KB and more, from twelve rounds on, x and y in the Infinity Cache / beyond it: bf16 from sixteen stages on, 1024 to
+  // 1024 at 14x14, 64 images 46.1 and 43.1 / 49.0 and 48.8; int8 from eight on, 1024 to 1024, 128 images 48.7 and 47.7 / 48.1 and 47.9.  bf16 of fewer lose where x
+  // and y come from beyond it, and, with a residual, which is read at a tile's start as its first stages are, everywhere: twelve stages, 768 to 512 at 28x28,
+  // 32 images 37.7 and 36.4 / 40.4 and 42.0; eight, 512 to 1024 at 14x14, 106 images 44.8 and 44.8 / 44.5 and 45.8, with a residual 45.3 and 47.8 / 50.7 and
+  // 52.8.  (Sixteen stages and more gain with fewer rounds too: 1024 to 256 at 28x28, 32 images, four rounds 26.0 and 24.8.)
   //   Not with fewer buffers (4096 to 4096, 1024 pixels 48 and 51).
   const int stages = (a.full + (tail > 0 ? 1 : 0)) * a.s;
-  const bool bare = a.nb > kLw || a.s >= 12 || p.in_dtype == CG_I8 || !(p.epilogue & CG_EPI_RESIDUAL);
-  if (g.taps == 1 && a.nb >= kLw && a.s >= 8 && bare && stages >= (a.nb > kLw ? 3 : 12) * a.nb) a.flags |= kTurns;
+  const int least = a.nb > kLw || p.in_dtype == CG_I8 ? 8 : 16;
+  if (g.taps == 1 && a.nb >= kLw && a.s >= least && stages >= (a.nb > kLw ? 3 : 12) * a.nb) a.flags |= kTurns;
   // rows of the patch lie in the banks of others: runs of 32 pixels over several of them, fragments of up to 8 columns (counted for widths of 2
   // to 56: never more passes than with the fixed bit; from 32 columns on and at stride 2 there are)
   const bool narrow = p.stride == 1 && (g.fwl < 0 ? p.wo < 32 : g.fwl <= 3);

@@ -241,7 +241,7 @@ def test_int8_outputs_with_and_without_residual(shape):
 # 1x1 layers of several tiles to a workgroup, whose stages the loading wavefronts take in turn: stages of eight chunks (four buffers) and of four,
 # weights that stay in LDS and stages of two (eight buffers), the last tile shorter than the others, gates that hardly ever fire (stages passed by before they land).
 IN_TURN = [
-    (S(106, 14, 14, 512, 1024, k=1, pad=0), 0.3, False), (S(106, 14, 14, 512, 1024, k=1, pad=0), 0.01, False), (S(106, 14, 14, 512, 1024, k=1, pad=0), 0.3, True),
+    (S(43, 14, 14, 1024, 1024, k=1, pad=0), 0.3, False), (S(43, 14, 14, 1024, 1024, k=1, pad=0), 0.01, False), (S(43, 14, 14, 1024, 1024, k=1, pad=0), 0.3, True),
     (S(61, 25, 25, 192, 128, k=1, pad=0), 0.3, False), (S(117, 25, 25, 192, 128, k=1, pad=0), 0.01, False), (S(29, 13, 13, 384, 1024, k=1, pad=0), 0.3, False),
     (S(19, 16, 16, 384, 1024, k=1, pad=0), 0.02, True)]
 
@@ -263,9 +263,9 @@ def test_point_wise_stages_in_turn_int8():
 # The same with other outputs, whose kernels are others: two-byte outputs beside a residual (stages of two, four and eight chunks), in shuffled order, of four
 # bytes, int8 ones of a shift below two; (shape, what is asked for, the form in test_kernels_of_calls_cpu.py).
 IN_TURN_OUTPUTS = [
-    (S(61, 25, 25, 192, 128, k=1, pad=0), "residual", 2, 14), (S(29, 13, 13, 384, 1024, k=1, pad=0), "residual", 4, 14), (S(64, 14, 14, 768, 1024, k=1, pad=0), "residual", 8, 14),
+    (S(61, 25, 25, 192, 128, k=1, pad=0), "residual", 2, 14), (S(29, 13, 13, 384, 1024, k=1, pad=0), "residual", 4, 14), (S(43, 14, 14, 1024, 1024, k=1, pad=0), "residual", 8, 14),
     (S(83, 25, 25, 192, 128, k=1, pad=0), "shuffled", 4, 11), (S(61, 25, 25, 192, 128, k=1, pad=0), "float", 2, 13), (S(61, 25, 25, 192, 128, k=1, pad=0), "tau", 2, 8),
-    (S(106, 14, 14, 512, 1024, k=1, pad=0), "residual", 8, 6)]        # (eight stages, four buffers and a residual: not in turn)
+    (S(106, 14, 14, 512, 1024, k=1, pad=0), "residual", 8, 6), (S(106, 14, 14, 512, 1024, k=1, pad=0), "natural", 8, 0)]     # (eight stages, four buffers: not in turn)
 IN_TURN_INT8 = [("bytes", 8), ("residual", 14), ("shift of one", 12), ("32 bits, residual", 13)]
 
 
