@@ -252,7 +252,7 @@ int resolve_variant(const cg_conv_desc& d, Plans* pl) {
   if (v == CG_VARIANT_AUTO) v = pl->v3.ok ? CG_VARIANT_MFMA_ROWS : pl->v4.ok ? CG_VARIANT_TILE : CG_VARIANT_NAIVE;
   pl->variant = v;
   // 1x1 layers of stride 1 whose channel walk is whole stages run on the row-tiled kernel (unless a family was asked for by
-  // name): 1024 channels at 14x14 x64, bf16 50 us against 99 on the large-tile kernel, int8 38 against 105
+  // name): 1024 channels at 14x14 x64, bf16 40 us against 99 on the large-tile kernel, int8 28 against 105
   pl->point_ok = false;
   if (d.variant == CG_VARIANT_AUTO && v != CG_VARIANT_MFMA_ROWS) {
     const cg::RowsPlan q = cg::point_plan(d, cg::cu_count());

@@ -35,7 +35,7 @@
 // corrected where a gate fired.
 //
 // TAPS = 1 (1x1 layers of stride 1): a row is a pixel, a patch the tile's pixels (no halo), a stage up to eight chunks of one
-// tap.  1024 channels at 14x14, 64 images: bf16 40 us, int8 26; 99 and 105 on the large-tile kernel.
+// tap.  1024 channels at 14x14, 64 images: bf16 40 us, int8 28; 99 and 105 on the large-tile kernel.
 //
 // What bounds the kernel: at 64 and 128 channels the instructions of gate and output (a third of a wavefront's time each
 // side of the products), at 256 and 512 the LDS reads and, for few images, the start: the first stage of all workgroups
@@ -508,8 +508,8 @@ __global__ __launch_bounds__(kNt) void gated_conv_rows_kernel(RowsArgs a, Params
       // loads, are under the others' loads.  With a quarter of every stage each, as below, all four issue at the same time, with the memory path full, and
       // then wait, look and publish at the same time, with the path idle: of 1400 clocks of a stage of 33 KB 800, of one of 8 KB nearly all.  What is
       // published is the first stage of a wavefront's own that has not landed, so the smallest of the four is again the number of stages that have.
-      //   bf16 320 to 640 channels at 14x14, 100 images 41.8 -> 27.0 us, int8 33.9 -> 24.6; 192 to 128, 200 images 15.2 -> 12.4; int8 768 to 384 at
-      // 20x20, 50 images 16.5 -> 15.2; bf16 1024 at 14x14, 64 images 42.0 -> 39.7.  (A kernel of its own: in one with the other loop that was 3 to 4 % slower.)
+      //   bf16 320 to 640 channels at 14x14, 100 images 43.7 -> 30.2 us, int8 35.8 -> 26.9; 192 to 128, 200 images 16.3 -> 13.1; int8 768 to 384 at
+      // 20x20, 50 images 19.7 -> 18.1; bf16 1024 at 14x14, 64 images 46.1 -> 43.1.  (A kernel of its own: in one with the other loop that was 3 to 4 % slower.)
       constexpr int kPx = 64 / CPS, kOwn = 4 * CPS;          // pixels of a load; loads of the largest patch
       const int lane_at = lane / CPS * a.xps + ((lane % CPS) ^ slot_perm<CPS>(lane / CPS, a.bit)) * 16;
       int own[kOwn], t = -1, landed_to = 0;
@@ -1737,7 +1737,8 @@ RowsPlan point_plan(const cg_conv_desc& d, int n_cu) {
   g.wpk_base_bytes = (size_t)g.n_cb * g.stages[0] * wb;
   g.wpk_cond_bytes = (size_t)g.n_cb * g.stages[1] * wb;
   // The estimated time, with the call's host part, in clocks of 2.25 GHz, fitted to 40 layers of 100 to 100000 pixels (4 % off, 10 % at most): a stage
-  // takes its products, its lines of memory or, where it is short, 980 clocks of latency; a conditional one half of that.
+  // takes its products, its lines of memory or, where it is short, 980 clocks of latency; a conditional one half of that.  (Fitted before layers of many stages
+  // had them loaded in turn, whose time is up to 40 % shorter than this.)
   g.cost = 8450.0 + (g.resident ? S * wb / 60.0 : 0.0);
   for (long long left = each; left > 0; left -= g.tr) {
     const long long here = left < g.tr ? left : g.tr, frags = (here + 31) / 32;

@@ -1,6 +1,6 @@
 // The calls a program makes per forward pass, as a Python extension: what binding.py does with ctypes, without the interpreter's part of it.
 //
-// One image through ResNet-18 is 22 launches of 3 to 9 us each; with tensors, workspace and arguments handled in Python a call took 5.0 us of host time
+// One image through ResNet-18 was 22 launches of 3 to 9 us each (19 now); with tensors, workspace and arguments handled in Python a call took 5.0 us of host time
 // (7.8 where it allocates its output, 11.6 with bitmap and counts too) beside the 2.7 us of a launch, and the GPU waited for the host.
 //
 // Only what a plain call needs is here.  A call with anything else - a tensor subclass, an active __torch_function__ mode, symbolic sizes, an argument

@@ -1,5 +1,5 @@
 """Times gated 1x1 convolutions and gated fully connected layers (h = w = k = 1) beside the dense
-layer of the same shape, through the C ABI (large-tile matrix-core kernel), and prints one JSON line.
+layer of the same shape, through the C ABI (whichever kernel the library takes), and prints one JSON line.
 
     python -m paper_1805_12549_amd.pointwise_probe [--rho 0.3] [--kind coherent]
 
